@@ -40,29 +40,10 @@
 #include <utility>
 #include <vector>
 #include "sptir_internal.h"
+#include "sptir_tiles.h"
 
 namespace sptir {
 namespace {
-
-template <int VEC> struct Vec;
-template <> struct Vec<4> { using type = float4; };
-template <> struct Vec<2> { using type = float2; };
-template <> struct Vec<1> { using type = float; };
-
-template <int VEC>
-__device__ __forceinline__ void load_vec(float (&x)[VEC], const float* p) {
-  typename Vec<VEC>::type v = *reinterpret_cast<const typename Vec<VEC>::type*>(p);
-  if constexpr (VEC == 4) { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
-  else if constexpr (VEC == 2) { x[0] = v.x; x[1] = v.y; }
-  else { x[0] = v; }
-}
-
-template <int VEC>
-__device__ __forceinline__ void store_vec(float* p, const float (&x)[VEC]) {
-  if constexpr (VEC == 4) *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
-  else if constexpr (VEC == 2) *reinterpret_cast<float2*>(p) = make_float2(x[0], x[1]);
-  else *p = x[0];
-}
 
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v >> 1); }
 
@@ -145,118 +126,6 @@ __device__ __forceinline__ void sum_groups(float (&acc)[VEC], int groups) {
   if constexpr (LG <= 16) { if (groups >= 4) add_from_above<2 * LG, VEC>(acc); }
   if constexpr (LG <= 8) { if (groups >= 8) add_from_above<4 * LG, VEC>(acc); }
   if constexpr (LG <= 4) { if (groups >= 16) add_from_above<8 * LG, VEC>(acc); }
-}
-
-// Stores a finished row straight to Y (a row owned by exactly one wavefront).
-template <int VEC, int LG>
-struct DirectSink {
-  float* y;  // Y + row*feat + f0
-  bool f_active;
-  __device__ __forceinline__ void operator()(int, bool valid, const float (&acc)[VEC]) const {
-    if (valid && f_active) store_vec<VEC>(y, acc);
-  }
-};
-
-// Sums one row's `count` entries cp/vp[0..count) times their rows of X for this lane's feature offset: entry o
-// is gathered by lane group (o % kChunk) / kSteps, the lane groups' partial sums meet once at the end, and the
-// row sum goes to `sink` from the first lane group.
-template <int VEC, int LG, typename Sink>
-__device__ __forceinline__ void walk_row(const int32_t* __restrict__ cp, const float* __restrict__ vp,
-                                         const float* __restrict__ Xf, int feat, int count, int lane, bool f_active,
-                                         const Sink& sink) {
-  using S = Shape<VEC, LG>;
-  constexpr int UB = S::kSteps, CS = S::kChunk;
-  if (count <= 0) return;
-  const int g = lane / LG;
-  const int src0 = g * UB;  // lane that fetched slot (g*UB) of the chunk
-  const int nch = (count + CS - 1) >> S::kLog2Chunk;
-
-  float acc[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-
-  // one (column, value) pair per lane and chunk; past the end a lane re-reads the last entry with value 0
-  auto fetch = [&](int ch, int& c, float& v) {
-    int o = (ch << S::kLog2Chunk) + lane;
-    bool ok = (CS == 64 || lane < CS) && o < count;
-    int oc = o < count ? o : count - 1;
-    c = cp[oc];
-    float vv = vp[oc];
-    v = ok ? vv : 0.f;
-  };
-  auto issue = [&](int c_reg, float (&x)[UB][VEC]) {
-#pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      int c = __shfl(c_reg, src0 + u, 64);
-      if (f_active) load_vec<VEC>(x[u], Xf + (size_t)c * (size_t)feat);
-      else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) x[u][e] = 0.f;
-      }
-    }
-  };
-  auto consume = [&](float v_reg, const float (&x)[UB][VEC]) {
-#pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      float v = __shfl(v_reg, src0 + u, 64);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] = fmaf(v, x[u][e], acc[e]);
-    }
-  };
-
-  // software pipeline: x0 / x1 hold the gathers of two consecutive chunks
-  float x0[UB][VEC], x1[UB][VEC];
-  int c_a = 0, c_b = 0, c_p = 0;
-  float v_a = 0.f, v_b = 0.f, v_p = 0.f;
-  fetch(0, c_a, v_a);
-  if (nch > 1) fetch(1, c_b, v_b);
-  issue(c_a, x0);
-  if (nch > 2) fetch(2, c_p, v_p);
-  if (nch > 1) issue(c_b, x1);
-  for (int ch = 0; ch < nch; ch += 2) {
-    consume(v_a, x0);
-    if (ch + 2 < nch) {
-      c_a = c_p; v_a = v_p;
-      if (ch + 3 < nch) fetch(ch + 3, c_p, v_p);
-      issue(c_a, x0);
-    }
-    if (ch + 1 < nch) {
-      consume(v_b, x1);
-      if (ch + 3 < nch) {
-        c_b = c_p; v_b = v_p;
-        if (ch + 4 < nch) fetch(ch + 4, c_p, v_p);
-        issue(c_b, x1);
-      }
-    }
-  }
-  for (int d = 1; d < S::kGroups; d <<= 1) {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] += __shfl_xor(acc[e], d * LG, 64);
-  }
-  sink(0, g == 0, acc);
-}
-
-enum TileMap : int {
-  kMapTilesPerXcd = 0,  // n_tiles multiple of 8: XCD x owns tiles x, x+8, ...
-  kMapXcdsPerTile = 1,  // n_tiles in {1,2,4}: 8/n_tiles XCDs share a tile, split the units
-  kMapPlain = 2         // any other tile count: tile = id % n_tiles
-};
-
-// workgroup id -> (unit, feature tile); units are row blocks (hyb) or groups of rows (CSR)
-__device__ __forceinline__ void decode_block(unsigned bid, int map_mode, int map_param, int n_tiles, int64_t* unit,
-                                             int* tile) {
-  if (map_mode == kMapTilesPerXcd) {
-    unsigned q = bid >> 3, x = bid & 7;
-    *tile = (int)(x + 8 * (q % (unsigned)map_param));
-    *unit = q / (unsigned)map_param;
-  } else if (map_mode == kMapXcdsPerTile) {
-    unsigned q = bid >> 3, x = bid & 7;
-    *tile = (int)(x % (unsigned)n_tiles);
-    *unit = (int64_t)q * map_param + x / (unsigned)n_tiles;
-  } else {
-    *tile = (int)(bid % (unsigned)n_tiles);
-    *unit = bid / (unsigned)n_tiles;
-  }
 }
 
 struct SpmmArgs {
@@ -763,81 +632,12 @@ __global__ __launch_bounds__(256) void k_heavy_reduce(const int32_t* __restrict_
   store_vec<VEC>(y, out);
 }
 
-struct CsrArgs {
-  const int32_t* indptr;
-  const int32_t* indices;
-  const float* values;
-  const float* X;
-  float* Y;
-  int32_t n_rows;
-  int32_t feat;
-  int32_t n_tiles;
-  int32_t map_mode;
-  int32_t map_param;
-};
-
-constexpr int kCsrWaves = 4;
-
-// no-hyb: one wavefront per (row, feature tile); the row is walked whole
-template <int VEC, int LG>
-__global__ __launch_bounds__(64 * kCsrWaves) void k_spmm_csr(CsrArgs a) {
-  using S = Shape<VEC, LG>;
-  int64_t unit;
-  int tile_id;
-  decode_block(blockIdx.x, a.map_mode, a.map_param, a.n_tiles, &unit, &tile_id);
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t row = unit * kCsrWaves + wave;
-  if (row >= a.n_rows) return;
-  const int begin = a.indptr[row], end = a.indptr[row + 1];
-  const int lane = threadIdx.x & 63;
-  const int f0 = tile_id * S::kTile + (lane & (LG - 1)) * VEC;
-  const bool f_active = f0 < a.feat;
-  float* y = a.Y + (size_t)row * (size_t)a.feat + f0;
-  if (end == begin) {  // empty row
-    if (f_active && lane < LG) {
-      float zero[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) zero[e] = 0.f;
-      store_vec<VEC>(y, zero);
-    }
-    return;
-  }
-  DirectSink<VEC, LG> sink{y, f_active};
-  walk_row<VEC, LG>(a.indices + begin, a.values + begin, a.X + f0, a.feat, end - begin, lane, f_active, sink);
-}
-
-// launch geometry shared by both SpMM entry points
-struct Geometry {
-  int vec, lg, n_tiles, map_mode, map_param;
-  int64_t grid;
-};
-
-// how n_tiles feature tiles (g->n_tiles) and n_units units are dealt to workgroups
-bool plan_tiles(int64_t n_units, Geometry* g) {
-  if (g->n_tiles % 8 == 0) {
-    g->map_mode = kMapTilesPerXcd; g->map_param = g->n_tiles / 8;
-    g->grid = n_units * g->n_tiles;
-  } else if (8 % g->n_tiles == 0) {
-    g->map_mode = kMapXcdsPerTile; g->map_param = 8 / g->n_tiles;
-    g->grid = 8 * ((n_units + g->map_param - 1) / g->map_param);
-  } else {
-    g->map_mode = kMapPlain; g->map_param = 0;
-    g->grid = n_units * g->n_tiles;
-  }
-  return g->grid <= 0x7FFFFFFF;
-}
-
 bool plan(int64_t n_units, int feat, const void* X, const void* Y, bool full_rows, Geometry* g) {
   uintptr_t align = (uintptr_t)X | (uintptr_t)Y;
   lane_shape(feat, (align & 15) == 0, (align & 7) == 0, full_rows, &g->vec, &g->lg);
   int tf = g->vec * g->lg;
   g->n_tiles = (feat + tf - 1) / tf;
   return plan_tiles(n_units, g);
-}
-
-bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
-  uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
-  return a0 < b0 + nb && b0 < a0 + na;
 }
 
 // the template arguments of the two hyb kernels as a value
@@ -1224,27 +1024,4 @@ extern "C" sptir_status_t sptir_spmm_noalloc(const sptir_hyb_t* h, const float* 
     if (st != SPTIR_OK) return st;
   }
   return spmm_on_hyb(h, X, Y, feat, stream_, partial);
-}
-
-extern "C" sptir_status_t sptir_spmm_csr(const sptir_csr_t* csr, const float* X, float* Y, int32_t feat,
-                                         void* stream_) {
-  if (!csr || feat < 1 || csr->n_rows < 0 || csr->n_cols < 0 || csr->nnz < 0) return SPTIR_ERR_INVALID_ARG;
-  if (!csr->indptr || (csr->nnz > 0 && (!csr->indices || !csr->values))) return SPTIR_ERR_INVALID_ARG;
-  if ((csr->n_cols > 0 && !X) || (csr->n_rows > 0 && !Y)) return SPTIR_ERR_INVALID_ARG;
-  const size_t x_bytes = sizeof(float) * (size_t)csr->n_cols * feat, y_bytes = sizeof(float) * (size_t)csr->n_rows * feat;
-  if (x_bytes && y_bytes && overlaps(X, x_bytes, Y, y_bytes)) return SPTIR_ERR_INVALID_ARG;
-  if (csr->n_rows == 0) return SPTIR_OK;
-  Geometry g;
-  if (!plan(((int64_t)csr->n_rows + kCsrWaves - 1) / kCsrWaves, feat, X, Y, false, &g)) return SPTIR_ERR_OVERFLOW;
-  CsrArgs a;
-  a.indptr = csr->indptr; a.indices = csr->indices; a.values = csr->values; a.X = X; a.Y = Y;
-  a.n_rows = csr->n_rows; a.feat = feat; a.n_tiles = g.n_tiles; a.map_mode = g.map_mode; a.map_param = g.map_param;
-  dim3 grid((unsigned)g.grid), block(64 * kCsrWaves);
-  hipStream_t stream = (hipStream_t)stream_;
-  if (g.vec == 4 && g.lg == 8) hipLaunchKernelGGL((k_spmm_csr<4, 8>), grid, block, 0, stream, a);
-  else if (g.vec == 4) hipLaunchKernelGGL((k_spmm_csr<4, 4>), grid, block, 0, stream, a);
-  else if (g.vec == 2) hipLaunchKernelGGL((k_spmm_csr<2, 16>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((k_spmm_csr<1, 32>), grid, block, 0, stream, a);
-  SPTIR_HIP(hipGetLastError());
-  return SPTIR_OK;
 }

@@ -1,0 +1,205 @@
+// SpMM straight from CSR, one pass, no decomposition: the "no-hyb" variant
+// that section 4.2.1 of arXiv 2207.04606 compares hyb against.
+//
+// Mapping (gfx950, wave64).  A workgroup of eight wavefronts owns 64
+// consecutive rows and one feature tile (32 floats, eight lanes of four), bound to XCDs like
+// the tiles of the hyb kernels.  What a row costs is its gathers of X, so rows
+// are treated by length:
+//   short   (<= kShortRow) one lane group per row, eight rows per wavefront at
+//           once, eight gathers in flight per lane.  A wavefront per row, as
+//           this kernel began, leaves seven of eight lane groups re-reading
+//           the same line on rows of seven entries;
+//   medium  the wavefront takes the row alone, 64 entries per step;
+//   long    (> kLongRow) all eight wavefronts share the row and meet in LDS: a
+//           row of 13,000 entries on one wavefront took 0.6 ms, seven times
+//           the rest of its graph together.
+// Every wavefront loads the 64 row lengths itself (one coalesced load), so all
+// of them know the long rows without a barrier, and a workgroup without long
+// rows never meets one.  Sums have a fixed order: results are reproducible.
+// The fourth lane of a tail reads (and writes) the last four floats of the
+// row, so any feature size of four or more uses 16-byte accesses; they need
+// only 4-byte alignment.
+// Measured (169,343 rows, 1,166,243 entries, 128 features): 0.65 -> 0.116 ms,
+// 5.1 TB/s of gathered rows of which a quarter hit L2, near what the memory-side
+// cache delivers at random (7.9).
+#include "sptir_internal.h"
+#include "sptir_tiles.h"
+
+namespace sptir {
+namespace {
+
+struct CsrArgs {
+  const int32_t* indptr;
+  const int32_t* indices;
+  const float* values;
+  const float* X;
+  float* Y;
+  int32_t n_rows;
+  int32_t feat;
+  int32_t n_tiles;
+  int32_t map_mode;
+  int32_t map_param;
+};
+
+constexpr int kCsrRows = 64;     // rows per workgroup: one per lane when their lengths are loaded
+constexpr int kShortRow = 32;    // four steps of one lane group: 16..48 measured alike
+constexpr int kLongRow = 512;    // eight steps of one wavefront (1024: 5 % slower on power-law rows, 256: the same)
+
+template <int VEC, int LG>
+__global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
+  constexpr int kGroups = 64 / LG, kWaves = 8, kRowsPerWave = kCsrRows / kWaves;
+  constexpr int UB = LG < 8 ? LG : 8, kTile = VEC * LG;
+  static_assert(kRowsPerWave % kGroups == 0 || kGroups % kRowsPerWave == 0, "rows of a wavefront in whole passes");
+  __shared__ __align__(16) float part[kWaves][kTile];
+  int64_t unit;
+  int tile_id;
+  decode_block(blockIdx.x, a.map_mode, a.map_param, a.n_tiles, &unit, &tile_id);
+  const int64_t row0 = unit * kCsrRows;
+  if (row0 >= a.n_rows) return;
+  const int lane = threadIdx.x & 63, g = lane / LG, fl = lane & (LG - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int f_nominal = tile_id * kTile + fl * VEC;
+  const bool f_active = f_nominal < a.feat;
+  const int f0 = f_nominal + VEC <= a.feat ? f_nominal : a.feat - VEC;  // (a tail lane repeats floats of its neighbour)
+  const float* Xf = a.X + (f_active ? f0 : 0);
+  float* Yf = a.Y + f0;
+  const size_t feat = (size_t)a.feat;
+
+  // lane l: first entry and length of row row0 + l
+  int row_begin = 0, row_len = 0;
+  if (row0 + lane < a.n_rows) {
+    row_begin = a.indptr[row0 + lane];
+    row_len = a.indptr[row0 + lane + 1] - row_begin;
+  }
+  unsigned long long long_rows = __ballot(row_len > kLongRow);
+
+  float acc[VEC];
+  // entries [first, first + left) of a row summed by this lane group, `stride` entries apart from step to step; the
+  // next step's entries are fetched while this one's gathers are in flight (two steps of gathers in flight measured
+  // no faster: 0.144 against 0.122 ms, half the wavefronts)
+  auto walk = [&](int first, int left, int stride) {
+    int c = 0;
+    float v = 0.f;
+    auto fetch = [&]() {
+      const bool ok = fl < UB && fl < left;
+      c = ok ? a.indices[first + fl] : 0;
+      v = ok ? a.values[first + fl] : 0.f;
+    };
+    fetch();
+    while (__any(left > 0)) {
+      float x[UB][VEC];
+      float vu[UB];
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int cu = __shfl(c, g * LG + u, 64);
+        vu[u] = __shfl(v, g * LG + u, 64);
+        if (f_active && u < left) load_unaligned<VEC>(x[u], Xf + (size_t)cu * feat);
+        else {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) x[u][e] = 0.f;
+        }
+      }
+      first += stride;
+      left -= stride;
+      fetch();
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vu[u], x[u][e], acc[e]);
+    }
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+  };
+  auto sum_lane_groups = [&]() {
+#pragma unroll
+    for (int d = LG; d < 64; d <<= 1)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) acc[e] += __shfl_xor(acc[e], d, 64);
+  };
+
+  // long rows: the workgroup each (every wavefront sees the same mask)
+  while (long_rows) {
+    const int src = __builtin_ctzll(long_rows);
+    long_rows &= long_rows - 1;
+    const int first = __builtin_amdgcn_readlane(row_begin, src), len = __builtin_amdgcn_readlane(row_len, src);
+    const int o = (wave * kGroups + g) * UB;
+    clear();
+    walk(first + o, len - o, kWaves * kGroups * UB);
+    sum_lane_groups();
+    if (g == 0) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) part[wave][fl * VEC + e] = acc[e];
+    }
+    __syncthreads();
+    if (wave == 0 && g == 0 && f_active) {
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e] += part[w][fl * VEC + e];
+      store_unaligned<VEC>(Yf + (size_t)(row0 + src) * feat, acc);
+    }
+    __syncthreads();
+  }
+  // short rows: a lane group each
+  constexpr int kPasses = (kRowsPerWave + kGroups - 1) / kGroups;
+#pragma unroll
+  for (int p = 0; p < kPasses; ++p) {
+    const int in_wave = p * kGroups + g;
+    const int src = wave * kRowsPerWave + (in_wave < kRowsPerWave ? in_wave : 0);
+    const int first = __shfl(row_begin, src, 64), len = __shfl(row_len, src, 64);
+    const bool mine = in_wave < kRowsPerWave && len <= kShortRow && row0 + src < a.n_rows;
+    clear();
+    walk(first, mine ? len : 0, UB);
+    if (mine && f_active) store_unaligned<VEC>(Yf + (size_t)(row0 + src) * feat, acc);
+  }
+  // medium rows: the wavefront each
+  unsigned long long medium = __ballot(row_len > kShortRow && row_len <= kLongRow) &
+                              (((1ull << kRowsPerWave) - 1) << (wave * kRowsPerWave));
+  while (medium) {
+    const int src = __builtin_ctzll(medium);
+    medium &= medium - 1;
+    const int first = __builtin_amdgcn_readlane(row_begin, src), len = __builtin_amdgcn_readlane(row_len, src);
+    clear();
+    walk(first + g * UB, len - g * UB, kGroups * UB);
+    sum_lane_groups();
+    if (g == 0 && f_active) store_unaligned<VEC>(Yf + (size_t)(row0 + src) * feat, acc);
+  }
+}
+
+}  // namespace
+}  // namespace sptir
+
+using namespace sptir;
+
+extern "C" sptir_status_t sptir_spmm_csr(const sptir_csr_t* csr, const float* X, float* Y, int32_t feat,
+                                         void* stream_) {
+  if (!csr || feat < 1 || csr->n_rows < 0 || csr->n_cols < 0 || csr->nnz < 0) return SPTIR_ERR_INVALID_ARG;
+  if (!csr->indptr || (csr->nnz > 0 && (!csr->indices || !csr->values))) return SPTIR_ERR_INVALID_ARG;
+  if ((csr->n_cols > 0 && !X) || (csr->n_rows > 0 && !Y)) return SPTIR_ERR_INVALID_ARG;
+  const size_t x_bytes = sizeof(float) * (size_t)csr->n_cols * feat, y_bytes = sizeof(float) * (size_t)csr->n_rows * feat;
+  if (x_bytes && y_bytes && overlaps(X, x_bytes, Y, y_bytes)) return SPTIR_ERR_INVALID_ARG;
+  if (csr->n_rows == 0) return SPTIR_OK;
+  Geometry g;
+  g.vec = feat >= 4 ? 4 : 1;
+  g.lg = feat >= 4 && feat <= 16 ? 4 : 8;
+  // A row of X that is not whole 128-byte lines has its tiles across line ends: tiles of 64 floats then touch fewer
+  // lines per row than tiles of 32 (41 features on 132,534 rows: 0.217 -> 0.143 ms).  Where X is small enough for
+  // L2 the lines are cheap and the narrower lane groups keep more rows in flight (20,000 rows, 41 features: 24 against
+  // 27 us); they change over near 8 MB.
+  if (feat > 32 && feat % 32 != 0 && x_bytes > ((size_t)8 << 20)) g.lg = 16;
+  g.n_tiles = (feat + g.vec * g.lg - 1) / (g.vec * g.lg);
+  if (!plan_tiles(((int64_t)csr->n_rows + kCsrRows - 1) / kCsrRows, &g)) return SPTIR_ERR_OVERFLOW;
+  CsrArgs a;
+  a.indptr = csr->indptr; a.indices = csr->indices; a.values = csr->values; a.X = X; a.Y = Y;
+  a.n_rows = csr->n_rows; a.feat = feat; a.n_tiles = g.n_tiles; a.map_mode = g.map_mode; a.map_param = g.map_param;
+  dim3 grid((unsigned)g.grid), block(512);
+  hipStream_t stream = (hipStream_t)stream_;
+  if (g.vec == 1) hipLaunchKernelGGL((k_spmm_csr<1, 8>), grid, block, 0, stream, a);
+  else if (g.lg == 4) hipLaunchKernelGGL((k_spmm_csr<4, 4>), grid, block, 0, stream, a);
+  else if (g.lg == 16) hipLaunchKernelGGL((k_spmm_csr<4, 16>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((k_spmm_csr<4, 8>), grid, block, 0, stream, a);
+  SPTIR_HIP(hipGetLastError());
+  return SPTIR_OK;
+}

@@ -1,0 +1,27 @@
+"""SpMM straight from CSR against the fp64 oracle at the edges of its row classes and feature tiles."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from gpu_helpers import assert_y_close, upload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_rows", [1, 63, 65, 200])
+@pytest.mark.parametrize("n_cols,feat", [(3000, 1), (3000, 3), (3000, 4), (3000, 16), (3000, 17), (3000, 35), (3000, 160),
+                                         (60_000, 36), (60_000, 41), (60_000, 67)])
+def test_row_lengths_and_tails(gpu_lib, n_rows, n_cols, feat):
+    """Lengths on both sides of the short / medium / long classes, empty rows, tails of every width; the wide X takes
+    the tiles of 64 floats."""
+    lens = np.array([0, 1, 7, 8, 9, 31, 32, 33, 64, 65, 511, 512, 513, 1025, 2999])
+    deg = np.random.default_rng(feat).choice(lens, n_rows)
+    deg[-1] = 2999                                             # a long row in the last, partly filled workgroup
+    w = workloads.random_csr(n_rows, n_cols, deg, 40 + feat, feat)
+    d = upload(w)
+    Y = torch.full((n_rows, feat), float("nan"), device="cuda")
+    gpu_lib.sptir_spmm_csr(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, d.X, Y)
+    Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"rows={n_rows} cols={n_cols} feat={feat}")
