@@ -423,12 +423,10 @@ sptir_status_t sptir_sddmm_plan_destroy(sptir_sddmm_plan_t* plan); /* NULL is ac
  *             int32 indices strictly ascending inside a stacked row, float32
  *             values; validated like sptir_hyb_build's input)
  *   max_bucket_log2   0..5, or negative for the paper's 5
- *   workspace_d_out   0, or a multiple of 32: the handle then also owns a scatter workspace of one row of
- *             workspace_d_out floats per (relation, row) pair, and sptir_rgms calls with d_out <= workspace_d_out
- *             (and a 16-byte aligned Y) store the product rows there and sum them per row of Y in a second pass,
- *             in a fixed order: results are then reproducible bit for bit, for about 20 % more time than the
- *             float atomics used otherwise.  This is not the n_relations x n_rows x d_out intermediate the
- *             paper avoids: it has one row per non-empty pair.
+ *   workspace_d_out   0, or a multiple of 32: sptir_rgms calls with d_out <= workspace_d_out then add their products
+ *             in a fixed order, and results are reproducible bit for bit, for 5 to 30 % more time.  The handle also owns the
+ *             memory in which the sums of divided row blocks meet (see sptir_rgms_info_t.n_tiles); it is far
+ *             smaller than the n_relations x n_rows x d_out intermediate the paper avoids.
  * sptir_rgms_build owns device memory through the allocator hook and
  * synchronises `stream`.  Errors: those of sptir_hyb_build; INVALID_ARG if
  * stacked->n_rows is not a multiple of n_relations.
@@ -439,9 +437,9 @@ typedef struct {
   int32_t n_relations, n_rows, n_cols, max_bucket_log2;
   int64_t nnz;
   int64_t n_stacked_rows_stored;  /* (relation, row) pairs with at least one entry, remainder pieces included */
-  int64_t n_pad_slots;
-  int64_t n_tiles;                /* 32-row tiles, one wavefront each */
-  int32_t workspace_d_out;        /* widest d_out the scatter workspace serves (0: none) */
+  int64_t n_pad_slots;            /* of the hyb(1, k) decomposition */
+  int64_t n_tiles;                /* matrix-core products: up to 16 (relation, row) pairs of one relation and row block */
+  int32_t workspace_d_out;        /* widest d_out that is summed in a fixed order (0: none) */
   int32_t reserved;
   int64_t device_bytes;
 } sptir_rgms_info_t;
@@ -454,9 +452,9 @@ sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n_relations,
  *   Y  device, [n_rows, d_out] row-major float32, overwritten (rows without entries become 0)
  *   d_in in {32, 64, 128}, d_out a multiple of 32 (UNSUPPORTED otherwise; the paper runs 32 x 32)
  * Only enqueues work on `stream`; no allocation.  Products and sums are float32 (float32 matrix-core
- * instructions).  Without the workspace the contributions of different relations and buckets meet in Y through
- * float atomic adds in no fixed order, so results agree between runs to rounding, not bit for bit; with it only
- * pairs of more than 2^k entries still do.  Calls that share a handle's workspace must not overlap in time.
+ * instructions; the sums over relations are float64 on chip).  Without the workspace the contributions of different
+ * relations meet in no fixed order, so results agree between runs to rounding, not bit for bit.  Calls that share a
+ * handle's workspace must not overlap in time.
  * X must be finite (pad slots).
  */
 sptir_status_t sptir_rgms(const sptir_rgms_t* rgms, const float* X, const float* W, float* Y, int32_t d_in,

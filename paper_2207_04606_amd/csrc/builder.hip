@@ -90,6 +90,7 @@ __device__ __forceinline__ int bin_of_length(int l, int k) {
 // The counters exist kFlagSlots times, 64 bytes apart, and a wavefront adds to the copy its workgroup id picks:
 // tens of thousands of atomic adds to one address would take longer than reading the matrix.  The host adds up.
 constexpr int kFlagSlots = 64, kFlagStride = 8;
+static_assert(kFlagSlots * kFlagStride == kValidationWords, "the words a caller provides");
 __device__ __forceinline__ unsigned long long* flag_slot(unsigned long long* flags) {
   return flags + (blockIdx.x & (kFlagSlots - 1)) * kFlagStride;
 }
@@ -817,7 +818,7 @@ __global__ void k_heavy_counts(int64_t n_pieces, const int32_t* __restrict__ row
   if ((threadIdx.x & 63) == 0 && mine) atomicAdd(flag_slot(heavy_nnz), mine);  // (kFlagSlots counters, see there)
 }
 
-constexpr int kScanSeq = 4096;  // elements per sequence of the device-wide scan
+
 
 // What the host needs to know before it can size the stream, in one array: report[0] = chunks of all lists,
 // [1] = entries of heavy pieces (the sum of the counters k_heavy_counts added to; the longest list is the maximum
@@ -1047,7 +1048,7 @@ __global__ void k_heavy_row_fill(int32_t n_rows, const int32_t* __restrict__ row
 // of the process (pinning memory costs more than a small build) and lent to one build at a time.
 class PinnedPool {
  public:
-  struct Buf { char* p = nullptr; size_t size = 0; };
+  using Buf = PinnedBuf;
   Buf acquire(size_t bytes) {
     {
       std::lock_guard<std::mutex> g(m_);
@@ -1095,6 +1096,7 @@ struct Blob {  // bump allocator over one device allocation
 
 // Exclusive scan of data[0 .. n) in place on `stream`; data must have room for n rounded up to whole sequences
 // (the tail is zeroed here), seq_base for one int per sequence plus one.
+}  // namespace
 sptir_status_t device_exclusive_scan(int32_t* data, int64_t n, int32_t* seq_base, hipStream_t stream) {
   if (n <= 0) return SPTIR_OK;
   const int64_t n_seq = (n + kScanSeq - 1) / kScanSeq;
@@ -1109,6 +1111,33 @@ sptir_status_t device_exclusive_scan(int32_t* data, int64_t n, int32_t* seq_base
   return SPTIR_OK;
 }
 size_t scan_room(int64_t n) { return (size_t)((n + kScanSeq - 1) / kScanSeq) * kScanSeq; }
+
+PinnedBuf pinned_acquire(size_t bytes) { return pinned_pool().acquire(bytes); }
+void pinned_release(PinnedBuf b) { pinned_pool().release(b); }
+
+void launch_validation(const sptir_csr_t* csr, bool with_values, unsigned long long* flags, hipStream_t stream) {
+  const int32_t* value_bits = with_values ? (const int32_t*)csr->values : nullptr;
+  if (csr->n_rows > 0)
+    hipLaunchKernelGGL(k_validate_rows, dim3((unsigned)std::min<int64_t>(((int64_t)csr->n_rows + 255) / 256, 4096)),
+                       dim3(256), 0, stream, csr->n_rows, csr->nnz, csr->indptr, csr->indices, value_bits, flags);
+  if (csr->nnz > 0)
+    hipLaunchKernelGGL(k_validate_elems, dim3((unsigned)std::min<int64_t>((csr->nnz + 2047) / 2048, 8192)), dim3(256), 0,
+                       stream, csr->nnz, csr->n_cols,
+                       (int)((((uintptr_t)csr->indices | (uintptr_t)csr->values) & 15) == 0), csr->indices, value_bits,
+                       flags);
+}
+
+sptir_status_t validation_verdict(const unsigned long long* flag_slots, bool* one_value_per_row) {
+  unsigned long long flags[6] = {0, 0, 0, 0, 0, 0};
+  for (int slot = 0; slot < kFlagSlots; ++slot)
+    for (int i = 0; i < 6; ++i) flags[i] += flag_slots[slot * kFlagStride + i];
+  if (flags[0]) return SPTIR_ERR_INVALID_ARG;
+  if (flags[1] || flags[2] != flags[3]) return SPTIR_ERR_UNSORTED;
+  if (one_value_per_row) *one_value_per_row = flags[4] == flags[5];
+  return SPTIR_OK;
+}
+
+namespace {
 
 int log2_row_block_setting(int32_t n_rows, bool rounds, bool full_rows, const sptir_build_options_t& opt) {
   long v = opt.row_block;
@@ -1259,7 +1288,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
   Blob tmp;
   // (flags, tot_rnnz and tot_bins lie next to each other: one copy brings them to the host)
   const size_t o_flags = tmp.size;
-  tmp.size += kFlagSlots * kFlagStride * sizeof(unsigned long long);
+  tmp.size += kValidationWords * sizeof(unsigned long long);
   const size_t o_tot_rnnz = tmp.size;
   tmp.size += sizeof(int64_t) * (size_t)s.c;
   const size_t o_tot_bins = tmp.size;
@@ -1326,21 +1355,13 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     // ---- validation of the CSR input, and with it (their results are only used if the input is valid, and they
     // read nothing at a position the input names without clamping it) the piece boundaries, histogram and scans
     const unsigned long long* flag_slots = (const unsigned long long*)(host.base + h_report1);
-    unsigned long long flags[6] = {0, 0, 0, 0, 0, 0};
+    bool one_value = false;
     const int64_t* tot_rnnz = (const int64_t*)(host.base + h_report1 + (o_tot_rnnz - o_flags));
     const int32_t* tot_bins = (const int32_t*)(host.base + h_report1 + (o_tot_bins - o_flags));
     // (values are only looked at when a value-less stream is an option)
     const int32_t* value_bits = (with_spmm_plan && !opt.keep_values) ? (const int32_t*)csr->values : nullptr;
     BUILD_HIP(hipMemsetAsync(d_flags, 0, report1_bytes, stream));
-    if (s.n_rows > 0)
-      hipLaunchKernelGGL(k_validate_rows, dim3((unsigned)std::min<int64_t>(((int64_t)s.n_rows + 255) / 256, 4096)),
-                         dim3(256), 0, stream, s.n_rows, csr->nnz,
-                         csr->indptr, csr->indices, value_bits, d_flags);
-    if (csr->nnz > 0)
-      hipLaunchKernelGGL(k_validate_elems, dim3((unsigned)std::min<int64_t>((csr->nnz + 2047) / 2048, 8192)),
-                         dim3(256), 0, stream, csr->nnz, s.n_cols,
-                         (int)((((uintptr_t)csr->indices | (uintptr_t)csr->values) & 15) == 0), csr->indices,
-                         value_bits, d_flags);
+    launch_validation(csr, value_bits != nullptr, d_flags, stream);
     if (s.NB > 0) {
       if (n_bound_blocks > 0)
         hipLaunchKernelGGL(k_piece_bounds, dim3((unsigned)n_bound_blocks), dim3(256), 0, stream, s, (int32_t)csr->nnz,
@@ -1355,17 +1376,14 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     BUILD_HIP(hipGetLastError());
     BUILD_HIP(hipMemcpyAsync(host.base + h_report1, d_flags, report1_bytes, hipMemcpyDeviceToHost, stream));
     BUILD_HIP(hipStreamSynchronize(stream));
-    for (int slot = 0; slot < kFlagSlots; ++slot)
-      for (int i = 0; i < 6; ++i) flags[i] += flag_slots[slot * kFlagStride + i];
-    bool bad_indptr = flags[0] != 0;
     if (s.n_rows == 0) {
       int32_t* first = (int32_t*)(host.base + h_misc);
       BUILD_HIP(hipMemcpyAsync(first, csr->indptr, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
       BUILD_HIP(hipStreamSynchronize(stream));
-      if (*first != 0 || csr->nnz != 0) bad_indptr = true;
+      if (*first != 0 || csr->nnz != 0) { st = SPTIR_ERR_INVALID_ARG; goto fail; }
     }
-    if (bad_indptr) { st = SPTIR_ERR_INVALID_ARG; goto fail; }
-    if (flags[1] || flags[2] != flags[3]) { st = SPTIR_ERR_UNSORTED; goto fail; }
+    st = validation_verdict(flag_slots, &one_value);
+    if (st != SPTIR_OK) goto fail;
 
     // ---- sizes and the small prefix arrays (host)
     int64_t* row_ptr = (int64_t*)(host.base + h_row_ptr);
@@ -1413,7 +1431,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     h->full_rows = ls.full_rows;
     // Every row has one value for all its entries (a row-normalised adjacency matrix, say): the stream
     // carries no values, the kernels sum rows of X and scale each row of Y once.
-    const bool one_value_per_row = value_bits && csr->nnz > 0 && flags[4] == flags[5];
+    const bool one_value_per_row = value_bits && csr->nnz > 0 && one_value;
     h->sweep_kb = opt.sweep_kb;  // (0: the defaults of the two sweep rules)
     cs.n_rb = (int32_t)(((int64_t)s.n_rows + (1 << cs.log2_rb) - 1) >> cs.log2_rb);
     cs.long_len = heavy_len_setting(csr->nnz, (int64_t)cs.n_phases * cs.n_rb, ls.rounds != 0, opt);

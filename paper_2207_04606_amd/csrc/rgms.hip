@@ -1,291 +1,478 @@
 // Relational gather-matmul-scatter (RGMS, section 4.4 of arXiv 2207.04606):
 //     Y[i,l] = sum_r sum_j sum_k A[r,i,j] * X[j,k] * W[r,k,l].
-// The paper decomposes every relation's matrix into hyb(1, 5) (a "3-D hyb"),
-// pins W[r] on chip for each ELL sub-matrix of relation r, gathers the rows
-// of X it needs, multiplies on the matrix cores and scatters into Y, all in
+// The paper decomposes every relation's matrix into hyb(1, 5), gathers the
+// rows of X, multiplies by W[r] on the matrix cores and scatters into Y, all in
 // one kernel, so that T[r] = X W[r] never exists in memory.
 //
-// Here A arrives as one CSR over stacked rows r*n + i, and its 3-D hyb is the
-// ordinary hyb(1, k) of that stacked matrix: bucket i holds the stacked rows
-// with 2^(i-1) < l <= 2^i entries, ascending, hence relation after relation.
-// The buckets are cut into tiles of 32 stacked rows of one relation (pieces
-// longer than 2^k go to the remainder and are cut into 32-entry segments).
-// One wavefront takes a tile:
-//   gather     eight 8-lane groups sum a[i,j] * X[j,:] for four rows each
-//              (aggregating before the product is the same sum and leaves one
-//              matrix row per stacked row instead of one per non-zero);
-//              the 32 x d_in block Z goes to LDS;
-//   matmul     Z (32 x d_in) times W[r] (d_in x d_out) with
-//              v_mfma_f32_32x32x2_f32, float32 throughout, W[r] read from L2;
-//   scatter    float atomic adds of the 32 x 32 results into the rows of Y
-//              (a row of Y collects from every relation and bucket, in no
-//              fixed order: results agree to rounding, not bit for bit).
-//              The operator moves 128-byte rows at random addresses (rows of
-//              X in, rows of Y out): about 3 TB/s on this chip, whatever the
-//              order of the tiles and however many loads are in flight
-//              (measured).  The optional workspace path stores the product
-//              rows and sums them per row of Y in a fixed order: reproducible
-//              bits for about 20 % more time (one more pass over the rows).
-// Y is zero-filled first by a kernel of its own (the operator overwrites Y).
+// Here the kernel is stationary in Y instead of in r.  A arrives as one CSR
+// over stacked rows r*n + i.  Rows of Y are cut into blocks of 2^s; a
+// workgroup owns a block, keeps its rows of Y in LDS, walks the block's pairs
+// (r, i) relation after relation and writes Y once.  The scatter of the
+// relation-stationary order (a float atomic per element of every pair's product
+// row, at L2) was what bound it.  32 x 32 features: 94 K rows, 51 relations, 4.76 M entries 0.257 -> 0.171 ms; 1.38 M rows, 25
+// relations, 5.6 M entries 0.472 -> 0.310; 1.9 M rows, 96 relations, 5.7 M entries 0.560 -> 0.519, where a
+// (relation, block) has few entries and what bounds the kernel is the trips to L2 for W[r].
+//
+// The entries of (relation, block) are consecutive in the stacked CSR, so the handle needs little more than a copy of the
+// entries in their order.  A piece is the entries of one pair (longer pairs are several pieces of 8), a tile up to
+// 16 consecutive pieces of one relation in one block.  A wavefront takes a tile:
+//   gather    Z^T = X^T S on the matrix cores, four entries a step: S holds the value of an entry in the column of its
+//             piece.  Lane (m, q) brings the features of entry q that are its row of X^T, so every load is whole rows of X
+//             and nothing but rows that are needed: L1 returns 64 bytes a cycle, and loads laid out by piece, a
+//             row per four lanes and most of them masked off, were what bound an earlier form (84 % of its
+//             time).  Z comes out as the A operand of the next product;
+//   multiply  Z W[r], v_mfma_f32_16x16x4_f32, float32 throughout, W[r] from L1 / L2, where the tiles of one relation
+//             that a workgroup's wavefronts take together meet;
+//   add       the 16 x 32 results to the block's rows in LDS, as float64 atomics: ds_add_f64 takes 21 cycles a
+//             wavefront, ds_add_f32 193 (measured), and the sums lose nothing.
+// Blocks are as large as gives (relation, block) a tile's worth of pieces, and small enough that there are workgroups
+// for all CUs; a block with far more tiles than the others is several work items, whose sums meet in Y by global atomics.
+//
+// The order of the adds is not fixed (the last float32 bit may differ from call to call) unless the handle was built
+// with a workspace: then every tile waits for its predecessor before it adds, item sums meet in the workspace,
+// and results are reproducible bit for bit.
 #include <string.h>
 
 #include <algorithm>
 #include <new>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "sptir_internal.h"
 #include "sptir_scan.h"
+#include "sptir_tiles.h"
 
 namespace sptir {
 namespace {
 
+constexpr int kTileRows = 16;      // pieces per tile: the rows of one matrix-core product
+constexpr int kPieceEntries = 8;   // most entries per piece: at most two batches of 64 per tile
+constexpr int kNoRow = 0xFFFF;
+constexpr int kMinLog2Block = 5, kMaxLog2Block = 8;
+constexpr int kYTileBytes = 64 * 1024;  // LDS for the rows of Y: two workgroups per CU
+
+struct RgmsItem {
+  int32_t block;    // rows block << log2_block .. of Y
+  int32_t tile0;
+  int32_t n_tiles;
+  int32_t part;     // -1: the whole block; otherwise number of this item among the items of divided blocks
+};
+
 struct RgmsTile {
-  int64_t slot0;      // first slot of the tile's first row in the fused (cols, vals) arrays
-  int32_t row0;       // index of the tile's first row in row_ids
-  int32_t n_rows;     // 1..32 rows (ELL) or 32-entry segments (remainder)
-  int32_t log2w;      // ELL: log2 of the bucket width; -1: segments of one remainder piece
+  int32_t first, end;  // its entries
   int32_t rel;
-  int32_t last_len;   // remainder: entries in the tile's last segment (1..32)
   int32_t pad_;
 };
-static_assert(sizeof(RgmsTile) == 32, "RgmsTile must stay 32 bytes");
-
-constexpr int kRgmsWaves = 4;
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 struct RgmsArgs {
+  const RgmsItem* items;
   const RgmsTile* tiles;
-  const int32_t* row_ids;
-  const int32_t* cols;
-  const float* vals;
+  const ushort4* tile_rows;  // [n_tiles][4]: the row in the block of each of the tile's 16 pieces, kNoRow: none
+  const int2* entries;       // column, value bits
+  const uint8_t* entry_piece;  // which of its tile's pieces an entry belongs to
   const float* X;
   const float* W;
   float* Y;
-  int64_t n_tiles;
-  int32_t n_rows;  // rows of Y = rows per relation
-  int32_t d_in, d_out;
-  // scatter through the workspace: row pos_of_row[q] of `partial` receives the product row of stacked row q
-  const int32_t* pos_of_row;
-  float* partial;
+  float* partial;           // ORDERED: sums of the items of divided blocks
+  int32_t n_rows;
+  int32_t log2_block;
+  int32_t d_out;
+  int32_t width;            // columns of Y per workgroup, a multiple of 32
+  int32_t n_waves;          // per workgroup
+  int32_t sharers;          // workgroups per item
+  uint32_t x_bytes;
 };
 
-__global__ void k_fill_zero(float* p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = 0.f;
-}
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// bounds[(i * (n_rel + 1)) + r] = first position in [lo_i, hi_i) of row_ids whose stacked row is >= r * n_rows,
-// for every list i (the k+1 ELL buckets, then the remainder)
-__global__ void k_relation_bounds(int32_t n_lists, int32_t n_rel, int32_t n_rows, const int64_t* __restrict__ list_lo,
-                                  const int64_t* __restrict__ list_hi, const int32_t* __restrict__ row_ids,
-                                  int64_t* bounds) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_lists * (n_rel + 1)) return;
-  int i = t / (n_rel + 1), r = t % (n_rel + 1);
-  int64_t lo = list_lo[i], hi = list_hi[i];
-  const int64_t bound = (int64_t)r * n_rows;
-  while (lo < hi) {
-    int64_t mid = lo + ((hi - lo) >> 1);
-    if ((int64_t)row_ids[mid] < bound) lo = mid + 1; else hi = mid;
+// Place in the LDS tile: an instruction adds to 16 columns of any four rows; every other row has its halves of 32 columns
+// swapped, so that the four are spread over all banks.
+__device__ __forceinline__ int y_index(int row, int col, int width) { return row * width + (col ^ ((row & 1) << 4)); }
+
+// f(0), f(1), .. f(N - 1) with the number as a type
+template <int N, typename F, int I = 0>
+__device__ __forceinline__ void for_steps(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    for_steps<N, F, I + 1>(std::forward<F>(f));
   }
-  bounds[t] = lo;
 }
 
-// The gather step of one tile, for rows of 2^LOG2W slots (a remainder tile takes LOG2W = 5 and masks the tail of
-// its last segment).  Lane group g owns rows g, g + 8, g + 16, g + 24.  All column / value loads of the tile are
-// issued before the first gather and every gather is independent of the others, so that the two memory
-// round trips of a tile overlap inside the wavefront instead of repeating once per row.
-template <int TIN, int LOG2W>
-__device__ __forceinline__ void gather_tile(const RgmsArgs& a, const RgmsTile& tile, bool ell, int lane, float* z,
-                                            int z_stride) {
-  constexpr int kW = 1 << LOG2W;
-  constexpr int kOct = kW >= 8 ? kW / 8 : 1;       // octets per row
-  constexpr int kPer = kW >= 8 ? 8 : kW;           // slots per octet
-  const int g = lane >> 3, fl = lane & 7;
-  int col[4][kOct];
-  float val[4][kOct];
+// An entry of a tile as lane (m, q) holds it: number 4 m + q of a batch of 64.
+struct Entry {
+  int col;
+  float val;
+  int piece;  // (past the end of the tile: a piece that is none of the 16)
+};
+
+// lane S of every 16
+template <int S>
+__device__ __forceinline__ int bcast16(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x150 + S, 0xF, 0xF, true);  // row_newbcast:S
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
+constexpr int kPass = 32;       // columns of Y per pass: two products side by side
+
+// TIN: d_in / 32.  Lane (m, q) = 16 q + m of a 16x16x4 product holds row m of A and column m of B at k = q, and rows
+// 4 q .. + 3 of column m of the result.  The features are dealt to the rows of X^T so that a lane's are consecutive:
+// row m of product (g, l) is feature 16 VW g + VW m + l.  Column m of product j of a pass over Y stands for the pass's
+// column 4 (m & 7) + 2 (m >> 3) + j: that is what the lanes hold after a load of 16 consecutive bytes each (see
+// load_w).  In the LDS tile the columns lie in the order of the products.
+// WIDE_X: X has 4 GB or more.
+template <int TIN, bool ORDERED, bool WIDE_X>
+__global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
+  constexpr int VW = TIN == 1 ? 2 : 4;              // floats per lane and load of a row of X
+  constexpr int kLoads = 2 * TIN / VW;              // loads per row
+  constexpr int kZ = 2 * TIN;                       // 16-feature products per step
+  constexpr int kAhead = TIN <= 2 ? 8 : 4;                        // steps of four entries whose rows are in flight together
+  constexpr int kDin = 32 * TIN, kRowBytes = 4 * kDin;
+  extern __shared__ __align__(16) double y_tile[];  // [rows][width], then ORDERED: turn[width / kPass]
+  RgmsItem item = a.items[blockIdx.x / (unsigned)a.sharers];
+  if (a.sharers > 1) {
+    const int part = (int)(blockIdx.x % (unsigned)a.sharers), n = item.n_tiles;
+    const int lo = (int)((int64_t)n * part / a.sharers);
+    item.n_tiles = (int)((int64_t)n * (part + 1) / a.sharers) - lo;
+    item.tile0 += lo;
+    item.part = 0;  // (its sums are added to Y)
+  }
+  const int rows = 1 << a.log2_block, width = a.width;
+  const int n0 = blockIdx.y * width;
+  const int cols = min(width, a.d_out - n0);
+  int* turn = reinterpret_cast<int*>(y_tile + rows * width);
+  for (int i = threadIdx.x * 2; i < rows * width; i += blockDim.x * 2)
+    *reinterpret_cast<double2*>(y_tile + i) = make_double2(0., 0.);
+  if (ORDERED && threadIdx.x < (unsigned)(width / kPass)) turn[threadIdx.x] = 0;
+  __syncthreads();
+
+  const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), n_waves = a.n_waves;
+
+  // A tile's loads depend on each other (the tile, its entries, the rows those name), each a trip past L2, so they run
+  // ahead by three tiles, two and one: what is issued while tile t is multiplied has arrived when t + 1 begins.
+  auto tile_number = [&](int t) { return item.tile0 + (t < item.n_tiles ? t : 0); };
+  auto load_tile = [&](int t) -> RgmsTile { return a.tiles[tile_number(t)]; };
+  auto load_rows = [&](int t) -> ushort4 { return a.tile_rows[(size_t)tile_number(t) * 4 + q]; };
+  auto load_entry = [&](const RgmsTile& t, int batch) -> Entry {
+    const int i = t.first + 64 * batch + 4 * m + q, at = min(i, t.end - 1);
+    const int2 e = a.entries[at];
+    const int p = a.entry_piece[at];
+    return Entry{e.x, __int_as_float(e.y), i < t.end ? p : kNoRow};
+  };
+  const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.X, a.x_bytes);
+  auto load_x = [&](int col, float (&x)[kLoads][VW]) {
+    typedef float vec __attribute__((ext_vector_type(VW)));
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int row = m * 8 + g;
-    const bool row_in = row < tile.n_rows;
-    const int len = !row_in ? 0 : (ell || row < tile.n_rows - 1) ? kW : tile.last_len;
-    const int64_t base = tile.slot0 + (int64_t)(row_in ? row : 0) * kW;
+    for (int g = 0; g < kLoads; ++g) {
+      vec v;
+      if constexpr (WIDE_X) v = *reinterpret_cast<const vec*>(a.X + (size_t)col * kDin + VW * m + 16 * VW * g);
+      else if constexpr (VW == 2)
+        v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(x_buf, (int)((unsigned)col * kRowBytes + 8u * m), 128 * g, 0));
+      else
+        v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(x_buf, (int)((unsigned)col * kRowBytes + 16u * m), 256 * g, 0));
 #pragma unroll
-    for (int o = 0; o < kOct; ++o) {
-      const int j = o * 8 + fl;
-      const bool in = j < len;
-      col[m][o] = a.cols[base + (in ? j : 0)];
-      val[m][o] = in ? a.vals[base + j] : 0.f;
+      for (int l = 0; l < VW; ++l) x[g][l] = v[l];
     }
-  }
+  };
+  // the rows of X of steps S0 .. S0 + kAhead - 1 of a batch with n entries left (steps past them: nothing)
+  float x[kAhead][kLoads][VW];
+  auto load_steps = [&](auto s0, const Entry& e, int n) {
+    for_steps<kAhead>([&](auto i) {
+      constexpr int S = decltype(s0)::value + decltype(i)::value;
+      if (4 * S < n) load_x(bcast16<S>(e.col), x[decltype(i)::value]);
+    });
+  };
+  floatx4 z[kLoads][VW];
+  auto sum_steps = [&](auto s0, const Entry& e, int n) {
+    for_steps<kAhead>([&](auto i) {
+      constexpr int S = decltype(s0)::value + decltype(i)::value;
+      if (4 * S < n) {
+        const float v = __int_as_float(bcast16<S>(__float_as_int(e.val)));
+        const float b = bcast16<S>(e.piece) == m ? v : 0.f;
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    float4 acc[TIN];
+        for (int g = 0; g < kLoads; ++g)
 #pragma unroll
-    for (int q = 0; q < TIN; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+          for (int l = 0; l < VW; ++l)
+            z[g][l] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[decltype(i)::value][g][l], b, z[g][l], 0, 0, 0);
+      }
+    });
+  };
+  auto sum_rest = [&](const Entry& e, int n) {  // the steps of a batch that were not loaded ahead
+    for_steps<16 / kAhead - 1>([&](auto c) {
+      constexpr int S0 = (decltype(c)::value + 1) * kAhead;
+      if (4 * S0 < n) {
+        load_steps(std::integral_constant<int, S0>{}, e, n);
+        sum_steps(std::integral_constant<int, S0>{}, e, n);
+      }
+    });
+  };
+  // W[r], part (g, l): the rows k = 16 VW g + VW (4 q + i) + l, i = 0 .. 3, that meet z[g][l][i].  Parts l and l + 1
+  // are loaded together, a pair of rows (k, k + 1) at a time: lanes m < 8 take row k, the others k + 1, eight lanes to 128
+  // consecutive bytes; take_w then trades halves between lanes m and m ^ 8, so that every lane holds two columns
+  // of both rows.  (A lane loading its own two columns of one row costs L1 twice the cycles.)
+  const bool upper = (m & 8) != 0;
+  const int w_lane = 4 * ((4 * VW * q + (m >> 3)) * a.d_out + 4 * (m & 7));
+  auto load_w = [&](int rel, int c0, int part, float4 (&wb)[4]) {  // part: number of a pair of parts
+    const int g = part / (VW / 2), l = part % (VW / 2) * 2;
+    const __amdgpu_buffer_rsrc_t w_buf = buffer_of(a.W + (size_t)rel * kDin * (size_t)a.d_out, (uint32_t)(kRowBytes * a.d_out));
 #pragma unroll
-    for (int o = 0; o < kOct; ++o) {
+    for (int i = 0; i < 4; ++i)
+      wb[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(
+                                             w_buf, w_lane, 4 * ((16 * VW * g + VW * i + l) * a.d_out + n0 + c0), 0));
+  };
+  auto take_w = [&](const float4 w, float2& even, float2& odd) {
+    auto pick = [&](float when_upper, float otherwise) { return upper ? when_upper : otherwise; };
+    auto other_half = [&](float v) {  // lane m ^ 8's: row_ror:8
+      return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, true));
+    };
+    const float here_x = other_half(pick(w.x, w.z)), here_y = other_half(pick(w.y, w.w));
+    even = make_float2(pick(here_x, w.x), pick(here_y, w.y));
+    odd = make_float2(pick(w.z, here_x), pick(w.w, here_y));
+  };
+  constexpr int kParts = kZ / 2, kHeld = kParts < 2 ? kParts : 2;  // pairs of parts of W, and how many are held at a time
+
+  using std::integral_constant;
+  if (wave < item.n_tiles) {
+    RgmsTile tile = load_tile(wave), tile_1 = load_tile(wave + n_waves), tile_2 = load_tile(wave + 2 * n_waves);
+    Entry e = load_entry(tile, 0), e_1 = load_entry(tile_1, 0);
+    ushort4 rows_now = load_rows(wave), rows_next;
+    float4 w[kHeld][4];  // a part is loaded anew as soon as it is used
+    load_steps(integral_constant<int, 0>{}, e, tile.end - tile.first);
 #pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const int c = __shfl(col[m][o], g * 8 + u, 64);
-        const float v = __shfl(val[m][o], g * 8 + u, 64);
-        const float* xr = a.X + (size_t)c * (32 * TIN) + 4 * fl;
+    for (int p = 0; p < kHeld; ++p) load_w(tile.rel, 0, p, w[p]);
+    for (int t = wave; t < item.n_tiles; t += n_waves) {
+      // ---- gather
 #pragma unroll
-        for (int q = 0; q < TIN; ++q) {
-          const float4 x = *reinterpret_cast<const float4*>(xr + 32 * q);
-          acc[q].x = fmaf(v, x.x, acc[q].x); acc[q].y = fmaf(v, x.y, acc[q].y);
-          acc[q].z = fmaf(v, x.z, acc[q].z); acc[q].w = fmaf(v, x.w, acc[q].w);
+      for (int g = 0; g < kLoads; ++g)
+#pragma unroll
+        for (int l = 0; l < VW; ++l) z[g][l] = floatx4{0.f, 0.f, 0.f, 0.f};
+      const int n = tile.end - tile.first;
+      sum_steps(integral_constant<int, 0>{}, e, n);
+      sum_rest(e, n);
+#pragma unroll 1
+      for (int batch = 1; 64 * batch < n; ++batch) {
+        const Entry more = load_entry(tile, batch);
+        load_steps(integral_constant<int, 0>{}, more, n - 64 * batch);
+        sum_steps(integral_constant<int, 0>{}, more, n - 64 * batch);
+        sum_rest(more, n - 64 * batch);
+      }
+      // ---- what the next tiles need
+      load_steps(integral_constant<int, 0>{}, e_1, tile_1.end - tile_1.first);
+      e = e_1;
+      e_1 = load_entry(tile_2, 0);
+      rows_next = load_rows(t + n_waves);
+      const int rel = tile.rel, rel_next = tile_1.rel;
+      tile = tile_1; tile_1 = tile_2;
+      tile_2 = load_tile(t + 3 * n_waves);
+      const int y_row[4] = {rows_now.x, rows_now.y, rows_now.z, rows_now.w};
+      // ---- multiply, a pass at a time
+#pragma unroll 1
+      for (int c0 = 0; c0 < cols; c0 += kPass) {
+        const bool last = c0 + kPass >= cols;
+        const int rel_then = last ? rel_next : rel, c_then = last ? 0 : c0 + kPass;
+        floatx4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) {
+          constexpr int kPairs = VW / 2;
+          const int g = p / kPairs, l = p % kPairs * 2;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float2 even, odd;
+            take_w(w[p % kHeld][i], even, odd);
+            d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l][i], even.x, d0, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l][i], even.y, d1, 0, 0, 0);
+            d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l + 1][i], odd.x, d0, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l + 1][i], odd.y, d1, 0, 0, 0);
+          }
+          if (p + kHeld < kParts) load_w(rel, c0, p + kHeld, w[p % kHeld]);
+          else load_w(rel_then, c_then, p + kHeld - kParts, w[p % kHeld]);
+        }
+        // ---- add: d[v] belongs to piece 4q + v
+        if constexpr (ORDERED) {
+          // tile t adds after tile t - 1, which an earlier turn of this loop or another wavefront of this workgroup
+          // is on its way to: the wait ends
+          while (__hip_atomic_load(turn + c0 / kPass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != t)
+            __builtin_amdgcn_s_sleep(1);
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (y_row[v] != kNoRow) {
+            double* y = y_tile + y_row[v] * width + c0 + m;
+            const int half = (y_row[v] & 1) << 4;
+            atomicAdd(y + half, (double)d0[v]);
+            atomicAdd(y + (half ^ 16), (double)d1[v]);
+          }
+        if constexpr (ORDERED) {
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  // (LDS only: the prefetches stay in flight)
+          if (lane == 0)
+            __hip_atomic_store(turn + c0 / kPass, t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
       }
-    }
-    const int row = m * 8 + g;
-#pragma unroll
-    for (int q = 0; q < TIN; ++q) {
-      float* zr = z + row * z_stride + 32 * q + 4 * fl;
-      zr[0] = acc[q].x; zr[1] = acc[q].y; zr[2] = acc[q].z; zr[3] = acc[q].w;
+      rows_now = rows_next;
     }
   }
-}
+  __syncthreads();
 
-// TIN float4 per lane cover d_in = 32 * TIN floats of a row of X.  TO_WORKSPACE: the product rows are stored to
-// `partial` (plain stores; k_rgms_reduce sums them per row of Y) instead of added to Y with atomics.
-// The matrix product and the scatter of one tile whose 32 x d_in block sits in z.
-template <int TIN, bool TO_WORKSPACE>
-__device__ __forceinline__ void multiply_and_scatter(const RgmsArgs& a, const RgmsTile& tile, int lane, const float* z,
-                                                     int z_stride) {
-  constexpr int kDin = 32 * TIN;
-  const bool ell = tile.log2w >= 0;
-  // the stacked row of every tile row -> its row of Y, or of the workspace (lanes 0..31 hold rows 0..31)
-  int y_row_reg = 0;
-  if (lane < tile.n_rows) {
-    if constexpr (TO_WORKSPACE) {
-      y_row_reg = a.pos_of_row[tile.row0 + lane];  // (only ELL tiles take this path)
+  // ---- the block's rows
+  const int row0 = item.block << a.log2_block;
+  const int rows_here = min(rows, a.n_rows - row0);
+  const int quads = cols / 4;
+  for (int i = threadIdx.x; i < rows_here * quads; i += blockDim.x) {
+    const int row = i / quads, c = (i - row * quads) * 4;
+    float y[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int p = (c + k) % kPass;
+      y[k] = (float)y_tile[y_index(row, c + k - p + 16 * (p & 1) + 8 * ((p >> 1) & 1) + (p >> 2), width)];
+    }
+    if (item.part < 0) {
+      store_unaligned<4>(a.Y + (size_t)(row0 + row) * a.d_out + n0 + c, y);
+    } else if constexpr (ORDERED) {
+      store_vec<4>(a.partial + ((size_t)item.part * rows + row) * a.d_out + n0 + c, y);
     } else {
-      const int stacked = a.row_ids[tile.row0 + (ell ? lane : 0)];
-      y_row_reg = stacked - tile.rel * a.n_rows;
-    }
-  }
-  const float* w_rel = a.W + (size_t)tile.rel * kDin * (size_t)a.d_out;
-  const int mi = lane & 31, kh = lane >> 5;  // this lane's row of A / column of B, and which of the two k it holds
-  for (int n0 = 0; n0 < a.d_out; n0 += 32) {  // 32 columns of Y at a time
-    floatx16 d;
+      float* p = a.Y + (size_t)(row0 + row) * a.d_out + n0 + c;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) d[v] = 0.f;
-#pragma unroll 4
-    for (int kk = 0; kk < kDin / 2; ++kk) {
-      const float av = z[mi * z_stride + 2 * kk + kh];                      // A[mi][2kk + kh]
-      const float bv = w_rel[(size_t)(2 * kk + kh) * a.d_out + n0 + mi];    // B[2kk + kh][mi]
-      d = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, d, 0, 0, 0);
-    }
-    // d[v] = D[8*(v/4) + 4*kh + v%4][mi]
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = 8 * (v >> 2) + 4 * kh + (v & 3);
-      const int y_row = __shfl(y_row_reg, row, 64);
-      if (row < tile.n_rows) {
-        if constexpr (TO_WORKSPACE) a.partial[(size_t)y_row * a.d_out + n0 + mi] = d[v];
-        else atomicAdd(a.Y + (size_t)y_row * a.d_out + n0 + mi, d[v]);
-      }
+      for (int k = 0; k < 4; ++k)
+        if (y[k] != 0.f) atomicAdd(p + k, y[k]);
     }
   }
 }
 
-// One tile per wavefront.  TIN float4 per lane cover d_in = 32 * TIN floats of a row of X.  TO_WORKSPACE: the
-// product rows are stored to `partial` (k_rgms_reduce sums them per row of Y) instead of added to Y with atomics.
-template <int TIN, bool TO_WORKSPACE>
-__global__ __launch_bounds__(64 * kRgmsWaves) void k_rgms(RgmsArgs a) {
-  constexpr int kZStride = 32 * TIN + 1;  // odd stride: the column reads of the matrix product hit 32 different banks
-  __shared__ float z_all[kRgmsWaves][32 * kZStride];
+__global__ __launch_bounds__(256) void k_fill_zero(float* p, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0.f;
+}
+
+// The rows of a divided block: cleared before its items add to them, or, with a workspace, the sum of its items' parts
+// in their order.  divided[b] = {block, first part, parts}.
+__global__ __launch_bounds__(256) void k_rgms_divided(const int4* __restrict__ divided, int32_t n_rows,
+                                                      int32_t log2_block, int32_t d_out,
+                                                      const float* __restrict__ partial, float* Y) {
+  const int4 d = divided[blockIdx.x];
+  const int row0 = d.x << log2_block, rows = min(1 << log2_block, n_rows - row0);
+  for (int i = threadIdx.x; i < rows * d_out; i += blockDim.x) {
+    float sum = 0.f;
+    if (partial)
+      for (int p = 0; p < d.z; ++p) sum += partial[(((size_t)(d.y + p)) << log2_block) * d_out + i];
+    Y[(size_t)row0 * d_out + i] = sum;
+  }
+}
+
+// ------------------------------------------------------------------- build
+// cells are (block, relation), block-major; one wavefront each
+struct CellArgs {
+  const int32_t* indptr;
+  int64_t n_cells;
+  int32_t n_rel, n_rows, log2_block, k;
+};
+constexpr int kCountSlots = 64, kCountStride = 8;
+
+// tiles of every cell, entries of every block (zeroed before); counts[slot][0] += pairs with entries, [1] += slots of padding that hyb(1, k) has for them
+__global__ __launch_bounds__(256) void k_cell_tiles(CellArgs a, int32_t* cell_tiles, int32_t* block_entries,
+                                                    unsigned long long* counts) {
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int64_t t = (int64_t)blockIdx.x * kRgmsWaves + wave;
-  if (t >= a.n_tiles) return;  // (no barriers below: the wavefronts of a workgroup are independent)
-  const RgmsTile tile = a.tiles[t];
-  float* z = z_all[wave];
-  const bool ell = tile.log2w >= 0;
-  switch (tile.log2w) {  // (the bucket width is the same for the whole wavefront)
-    case 0: gather_tile<TIN, 0>(a, tile, ell, lane, z, kZStride); break;
-    case 1: gather_tile<TIN, 1>(a, tile, ell, lane, z, kZStride); break;
-    case 2: gather_tile<TIN, 2>(a, tile, ell, lane, z, kZStride); break;
-    case 3: gather_tile<TIN, 3>(a, tile, ell, lane, z, kZStride); break;
-    case 4: gather_tile<TIN, 4>(a, tile, ell, lane, z, kZStride); break;
-    default: gather_tile<TIN, 5>(a, tile, ell, lane, z, kZStride); break;
-  }
-  multiply_and_scatter<TIN, TO_WORKSPACE>(a, tile, lane, z, kZStride);
-}
-
-// Row i of Y = sum of the rows node_ptr[i] .. node_ptr[i+1] of `partial`, in that order (the (relation, row)
-// pairs of row i, relations ascending).  Eight lanes per four consecutive rows of Y (their partial rows are
-// neighbours in memory, and four independent sums keep four loads in flight), 32 columns at a time.
-constexpr int kReduceRows = 4;
-__global__ __launch_bounds__(256) void k_rgms_reduce(int32_t n_rows, int32_t d_out, const int32_t* __restrict__ node_ptr,
-                                                     const float* __restrict__ partial, float* Y) {
-  const int64_t row0 = ((int64_t)blockIdx.x * 32 + (threadIdx.x >> 3)) * kReduceRows;
-  if (row0 >= n_rows) return;
-  const int fl = threadIdx.x & 7;
-  int lo[kReduceRows], cnt[kReduceRows], longest = 0;
-#pragma unroll
-  for (int k = 0; k < kReduceRows; ++k) {
-    const int64_t r = row0 + k < n_rows ? row0 + k : n_rows - 1;
-    lo[k] = node_ptr[r];
-    cnt[k] = row0 + k < n_rows ? node_ptr[r + 1] - lo[k] : 0;
-    longest = max(longest, cnt[k]);
-  }
-  for (int c0 = 0; c0 < d_out; c0 += 32) {
-    float4 acc[kReduceRows];
-#pragma unroll
-    for (int k = 0; k < kReduceRows; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int t = 0; t < longest; ++t) {
-#pragma unroll
-      for (int k = 0; k < kReduceRows; ++k) {
-        if (t < cnt[k]) {
-          const float4 v = *reinterpret_cast<const float4*>(partial + (size_t)(lo[k] + t) * d_out + c0 + 4 * fl);
-          acc[k].x += v.x; acc[k].y += v.y; acc[k].z += v.z; acc[k].w += v.w;
-        }
-      }
+  const int64_t cell = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (cell >= a.n_cells) return;
+  const int64_t block = cell / a.n_rel, rel = cell - block * a.n_rel;
+  const int64_t row0 = block << a.log2_block;
+  const int rows = (int)min((int64_t)1 << a.log2_block, (int64_t)a.n_rows - row0);
+  const int32_t* ptr = a.indptr + rel * a.n_rows + row0;
+  int pieces = 0, pairs = 0, pads = 0;
+  for (int i = lane; i < rows; i += 64) {
+    const int len = ptr[i + 1] - ptr[i];
+    pieces += (len + kPieceEntries - 1) / kPieceEntries;
+    pairs += len > 0;
+    if (len > 1) {
+      const int log2w = 32 - __clz(len - 1);
+      if (log2w <= a.k) pads += (1 << log2w) - len;
     }
-#pragma unroll
-    for (int k = 0; k < kReduceRows; ++k)
-      if (row0 + k < n_rows) *reinterpret_cast<float4*>(Y + (size_t)(row0 + k) * d_out + c0 + 4 * fl) = acc[k];
+  }
+  for (int d = 32; d > 0; d >>= 1) {
+    pieces += __shfl_down(pieces, d, 64);
+    pairs += __shfl_down(pairs, d, 64);
+    pads += __shfl_down(pads, d, 64);
+  }
+  if (lane == 0) {
+    cell_tiles[cell] = (pieces + kTileRows - 1) / kTileRows;
+    const int entries = ptr[rows] - ptr[0];
+    if (entries > 0) atomicAdd(&block_entries[block], entries);
+    unsigned long long* c = counts + (blockIdx.x & (kCountSlots - 1)) * kCountStride;
+    if (pairs) atomicAdd(&c[0], (unsigned long long)pairs);
+    if (pads) atomicAdd(&c[1], (unsigned long long)pads);
   }
 }
 
-// mask[i * words + r / 64] bit r % 64: the pair (relation r, row i) has 1 .. max_len entries (it is an ELL row of
-// the 3-D hyb); count[i] = number of such relations
-__global__ void k_node_masks(int32_t n_rows, int32_t n_rel, int32_t words, int32_t max_len,
-                             const int32_t* __restrict__ indptr, unsigned long long* mask, int32_t* count) {
+// block_tile[b] = first tile of block b (b = n_blocks: their number)
+__global__ void k_block_tiles(int32_t n_blocks, int32_t n_rel, const int32_t* __restrict__ cell_tile0,
+                              const int32_t* __restrict__ total, int32_t* block_tile) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b <= n_blocks) block_tile[b] = b < n_blocks ? cell_tile0[(int64_t)b * n_rel] : *total;
+}
+
+// the tiles of every cell: pieces in row order
+__global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* __restrict__ cell_tile0,
+                                                    const int32_t* __restrict__ total, RgmsTile* tiles,
+                                                    uint16_t* tile_rows, uint8_t* entry_piece) {
+  const int lane = threadIdx.x & 63;
+  const int64_t cell = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (cell >= a.n_cells) return;
+  const int64_t block = cell / a.n_rel, rel = cell - block * a.n_rel;
+  const int tile0 = cell_tile0[cell], tile_end = cell + 1 < a.n_cells ? cell_tile0[cell + 1] : *total;
+  if (tile0 == tile_end) return;
+  const int64_t row0 = block << a.log2_block;
+  const int rows = (int)min((int64_t)1 << a.log2_block, (int64_t)a.n_rows - row0);
+  const int32_t* ptr = a.indptr + rel * a.n_rows + row0;
+  const int cell_end = ptr[rows];
+  uint16_t* out = tile_rows + (size_t)tile0 * kTileRows;
+  for (int t = tile0 + lane; t < tile_end; t += 64) tiles[t].rel = (int)rel;
+  int done = 0;
+  for (int i0 = 0; i0 < rows; i0 += 64) {
+    const int i = i0 + lane;
+    int first = 0, len = 0;
+    if (i < rows) { first = ptr[i]; len = ptr[i + 1] - first; }
+    const int n = (len + kPieceEntries - 1) / kPieceEntries;
+    const int incl = wave_inclusive_scan(n, lane);
+    const int slot0 = done + incl - n;
+    for (int p = 0; p < n; ++p) {
+      const int slot = slot0 + p, at = first + p * kPieceEntries, end = min(at + kPieceEntries, first + len);
+      out[slot] = (uint16_t)i;
+      RgmsTile* t = tiles + tile0 + slot / kTileRows;
+      if (slot % kTileRows == 0) t->first = at;
+      if (slot % kTileRows == kTileRows - 1 || end == cell_end) t->end = end;
+    }
+    // an entry's piece, 64 entries of a row at a time (short rows: a lane each)
+    if (len <= 8)
+      for (int k = 0; k < len; ++k) entry_piece[first + k] = (uint8_t)(slot0 % kTileRows);
+    unsigned long long longer = __ballot(len > 8);
+    while (longer) {
+      const int src = __builtin_ctzll(longer);
+      longer &= longer - 1;
+      const int f = __shfl(first, src, 64), l = __shfl(len, src, 64), s0 = __shfl(slot0, src, 64);
+      for (int k = lane; k < l; k += 64) entry_piece[f + k] = (uint8_t)((s0 + k / kPieceEntries) % kTileRows);
+    }
+    done += __shfl(incl, 63, 64);
+  }
+  for (int i = done + lane; i < (tile_end - tile0) * kTileRows; i += 64) out[i] = kNoRow;
+}
+
+__global__ __launch_bounds__(256) void k_pair_entries(int64_t nnz, const int32_t* __restrict__ cols,
+                                                      const float* __restrict__ vals, int2* entries) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_rows) return;
-  int total = 0;
-  for (int w = 0; w < words; ++w) {
-    unsigned long long m = 0;
-    for (int b = 0; b < 64 && w * 64 + b < n_rel; ++b) {
-      const int64_t row = (int64_t)(w * 64 + b) * n_rows + i;
-      const int len = indptr[row + 1] - indptr[row];
-      if (len >= 1 && len <= max_len) m |= 1ull << b;
-    }
-    mask[i * words + w] = m;
-    total += __popcll(m);
-  }
-  count[i] = total;
+  if (i < nnz) entries[i] = make_int2(cols[i], __float_as_int(vals[i]));
 }
 
-// pos_of_row[q] for every ELL row q: first partial row of its row of Y + the number of that row's relations below its own
-__global__ void k_pair_positions(int64_t n_ell_rows, int32_t n_rows, int32_t words, const int32_t* __restrict__ row_ids,
-                                 const unsigned long long* __restrict__ mask, const int32_t* __restrict__ node_ptr,
-                                 int32_t* pos_of_row) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n_ell_rows) return;
-  const int stacked = row_ids[q];
-  const int r = stacked / n_rows, i = stacked - r * n_rows;
-  int rank = 0;
-  for (int w = 0; w * 64 < r; ++w) {
-    unsigned long long m = mask[(int64_t)i * words + w];
-    if ((w + 1) * 64 > r) m &= (1ull << (r - w * 64)) - 1ull;
-    rank += __popcll(m);
-  }
-  pos_of_row[q] = node_ptr[i] + rank;
+// Rows per block: 32 entries for every (relation, block), so that tiles fill (16: 4 to 14 % slower, 64: the same), as long
+// as that leaves 160 blocks, about what keeps the matrix cores of 256 CUs busy with 16 wavefronts each.  Fewer,
+// larger blocks divided into items were tried and lose more in global atomics than fuller tiles gain (27,163 rows,
+// 64 x 64: 0.042 -> 0.093 ms).
+int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz) {
+  int s = kMinLog2Block;
+  while (s < kMaxLog2Block && ((int64_t)1 << s) * nnz < 32 * n_rows * n_rel && (n_rows >> (s + 1)) >= 160) ++s;
+  return s;
 }
 
 }  // namespace
@@ -294,15 +481,20 @@ __global__ void k_pair_positions(int64_t n_ell_rows, int32_t n_rows, int32_t wor
 // The handle behind sptir_rgms_t.
 struct sptir_rgms_handle {
   int32_t n_rel, n_rows, n_cols, k;
-  int64_t nnz;
-  sptir_hyb_t* hyb;  // hyb(1, k) of the stacked matrix (canonical arrays only)
-  sptir::RgmsTile* tiles;  // the ELL tiles, then the remainder tiles
-  int64_t n_tiles, n_ell_tiles;
-  // scatter workspace (optional): one row of workspace_d_out floats per ELL row
+  int64_t nnz, n_pairs, n_pads;
+  int32_t log2_block;
+  int64_t n_tiles;
+  sptir::RgmsTile* tiles;
+  uint16_t* tile_rows;    // [n_tiles][16]
+  int2* entries;          // [nnz]
+  uint8_t* entry_piece;   // [nnz]
+  sptir::RgmsItem* items;
+  int32_t n_items;
+  int4* divided;          // divided blocks: block, first part, parts
+  int32_t n_divided, n_parts;
   int32_t workspace_d_out;
-  float* partial;
-  int32_t* pos_of_row;   // [R]
-  int32_t* node_ptr;     // [n_rows + 1]
+  float* partial;         // workspace: [n_parts][rows of a block][d_out]
+  void* blob;             // one allocation holds all of them
   size_t device_bytes;
   sptir_alloc_fn alloc;
   sptir_free_fn free_;
@@ -313,24 +505,18 @@ using namespace sptir;
 
 extern "C" sptir_status_t sptir_rgms_destroy(sptir_rgms_t* p) {
   if (!p) return SPTIR_OK;
-  void* ptrs[] = {p->tiles, p->partial, p->pos_of_row, p->node_ptr};
-  for (void* q : ptrs)
-    if (q) p->free_(q, p->alloc_ctx);
-  sptir_hyb_destroy(p->hyb);
+  if (p->blob) p->free_(p->blob, p->alloc_ctx);
   delete p;
   return SPTIR_OK;
 }
 
 extern "C" sptir_status_t sptir_rgms_info(const sptir_rgms_t* p, sptir_rgms_info_t* out) {
   if (!p || !out) return SPTIR_ERR_INVALID_ARG;
-  sptir_hyb_info_t hi;
-  sptir_status_t st = sptir_hyb_info(p->hyb, &hi);
-  if (st != SPTIR_OK) return st;
   sptir_rgms_info_t o;
   o.n_relations = p->n_rel; o.n_rows = p->n_rows; o.n_cols = p->n_cols; o.max_bucket_log2 = p->k;
-  o.nnz = p->nnz; o.n_stacked_rows_stored = hi.n_ell_rows + hi.n_rem_pieces; o.n_pad_slots = hi.n_pad_slots;
+  o.nnz = p->nnz; o.n_stacked_rows_stored = p->n_pairs; o.n_pad_slots = p->n_pads;
   o.n_tiles = p->n_tiles; o.workspace_d_out = p->workspace_d_out; o.reserved = 0;
-  o.device_bytes = (int64_t)p->device_bytes + hi.device_bytes;
+  o.device_bytes = (int64_t)p->device_bytes;
   *out = o;
   return SPTIR_OK;
 }
@@ -341,130 +527,151 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
   if (workspace_d_out < 0 || workspace_d_out % 32 != 0) return SPTIR_ERR_INVALID_ARG;
   if (stacked->n_rows < 0 || stacked->n_rows % n_relations != 0) return SPTIR_ERR_INVALID_ARG;
   const int32_t k = max_bucket_log2 < 0 ? 5 : max_bucket_log2;  // the paper decomposes every relation as hyb(1, 5)
-  if (k > 5) return SPTIR_ERR_INVALID_ARG;  // a tile row holds at most 32 entries
+  if (k > 5) return SPTIR_ERR_INVALID_ARG;
+  const int64_t nnz = stacked->nnz;
+  if (stacked->n_cols < 0 || nnz < 0) return SPTIR_ERR_INVALID_ARG;
+  if (nnz >= ((int64_t)1 << 31)) return SPTIR_ERR_OVERFLOW;
+  if (!stacked->indptr || (nnz > 0 && (!stacked->indices || !stacked->values))) return SPTIR_ERR_INVALID_ARG;
+  if (nnz > 0 && (stacked->n_rows == 0 || stacked->n_cols == 0)) return SPTIR_ERR_INVALID_ARG;
   hipStream_t stream = (hipStream_t)stream_;
+
   sptir_rgms_handle* p = new (std::nothrow) sptir_rgms_handle();
   if (!p) return SPTIR_ERR_ALLOC;
   memset(p, 0, sizeof(*p));
   current_allocator(&p->alloc, &p->free_, &p->alloc_ctx);
   p->n_rel = n_relations; p->n_rows = stacked->n_rows / n_relations; p->n_cols = stacked->n_cols; p->k = k;
-  p->nnz = stacked->nnz;
-  sptir_build_options_t opt = complete_options(nullptr);
-  opt.no_spmm_plan = 1;
-  sptir_status_t st = hyb_build_impl(stacked, 1, k, opt, stream_, &p->hyb);
-  if (st != SPTIR_OK) { delete p; return st; }
+  p->nnz = nnz; p->workspace_d_out = workspace_d_out;
+  p->log2_block = log2_block_rows(p->n_rows, n_relations, nnz);
+  const int32_t n_blocks = (int32_t)(((int64_t)p->n_rows + (1 << p->log2_block) - 1) >> p->log2_block);
+  CellArgs ca;
+  ca.indptr = stacked->indptr; ca.n_cells = (int64_t)n_blocks * n_relations; ca.n_rel = n_relations;
+  ca.n_rows = p->n_rows; ca.log2_block = p->log2_block; ca.k = k;
+  const int64_t cell_wgs = (ca.n_cells + 3) / 4;
+  const int64_t n_seq = (int64_t)(scan_room(std::max<int64_t>(ca.n_cells, 1)) / kScanSeq);
 
-  const sptir_hyb* h = p->hyb;
-  const int n_lists = k + 2;  // the ELL buckets and the remainder
-  std::vector<int64_t> bucket_row_ptr((size_t)k + 2), bucket_slot_ptr((size_t)k + 2), rem_ptr((size_t)h->M + 1);
-  std::vector<int64_t> list_lo((size_t)n_lists), list_hi((size_t)n_lists), bounds((size_t)n_lists * (n_relations + 1));
-  std::vector<RgmsTile> tiles;
-  int64_t* d_lists = nullptr;
-  int64_t* d_bounds = nullptr;
-  unsigned long long* d_mask = nullptr;
+  // temporaries: validation flags and counts (one copy brings both to the host), cells, block starts
+  constexpr size_t kReport = (kValidationWords + kCountSlots * kCountStride) * sizeof(unsigned long long);
+  const size_t cleared = kReport + sizeof(int32_t) * (size_t)n_blocks;
+  size_t tmp_bytes = cleared;
+  auto reserve = [](size_t* size, size_t bytes) { const size_t at = *size; *size = (at + bytes + 255) & ~(size_t)255; return at; };
+  const size_t o_block_tile = reserve(&tmp_bytes, sizeof(int32_t) * ((size_t)n_blocks + 1));
+  const size_t report_bytes = o_block_tile + sizeof(int32_t) * ((size_t)n_blocks + 1);
+  const size_t o_cells = reserve(&tmp_bytes, sizeof(int32_t) * (size_t)n_seq * kScanSeq);
+  const size_t o_seq = reserve(&tmp_bytes, sizeof(int32_t) * ((size_t)n_seq + 1));
+  char* tmp = (char*)scratch_alloc(tmp_bytes, p->alloc, p->alloc_ctx, stream);
+  PinnedBuf host = pinned_acquire(std::max(report_bytes, (size_t)16));
+  std::vector<RgmsItem> items;
+  std::vector<int4> divided;
+  sptir_status_t st = SPTIR_OK;
 #define RGMS_HIP(call)                                                 \
   do {                                                                 \
     hipError_t e_ = (call);                                            \
     if (e_ != hipSuccess) { st = note_hip_error(e_, #call); goto fail; } \
   } while (0)
-  RGMS_HIP(hipMemcpyAsync(bucket_row_ptr.data(), h->bucket_row_ptr, sizeof(int64_t) * (k + 2), hipMemcpyDeviceToHost,
-                          stream));
-  RGMS_HIP(hipMemcpyAsync(bucket_slot_ptr.data(), h->bucket_slot_ptr, sizeof(int64_t) * (k + 2), hipMemcpyDeviceToHost,
-                          stream));
-  RGMS_HIP(hipMemcpyAsync(rem_ptr.data(), h->rem_ptr, sizeof(int64_t) * (h->M + 1), hipMemcpyDeviceToHost, stream));
-  RGMS_HIP(hipStreamSynchronize(stream));
-  for (int i = 0; i <= k; ++i) { list_lo[i] = bucket_row_ptr[i]; list_hi[i] = bucket_row_ptr[i + 1]; }
-  list_lo[k + 1] = h->R; list_hi[k + 1] = h->R + h->M;
-  d_lists = (int64_t*)p->alloc(sizeof(int64_t) * 2 * n_lists, p->alloc_ctx, stream);
-  d_bounds = (int64_t*)p->alloc(sizeof(int64_t) * bounds.size(), p->alloc_ctx, stream);
-  if (!d_lists || !d_bounds) { st = SPTIR_ERR_ALLOC; goto fail; }
-  RGMS_HIP(hipMemcpyAsync(d_lists, list_lo.data(), sizeof(int64_t) * n_lists, hipMemcpyHostToDevice, stream));
-  RGMS_HIP(hipMemcpyAsync(d_lists + n_lists, list_hi.data(), sizeof(int64_t) * n_lists, hipMemcpyHostToDevice, stream));
+  if (!tmp || !host.p) { st = SPTIR_ERR_ALLOC; goto fail; }
   {
-    const int n_searches = n_lists * (n_relations + 1);
-    hipLaunchKernelGGL(k_relation_bounds, dim3((n_searches + 255) / 256), dim3(256), 0, stream, n_lists, n_relations,
-                       p->n_rows, d_lists, d_lists + n_lists, h->row_ids, d_bounds);
-  }
-  RGMS_HIP(hipGetLastError());
-  RGMS_HIP(hipMemcpyAsync(bounds.data(), d_bounds, sizeof(int64_t) * bounds.size(), hipMemcpyDeviceToHost, stream));
-  RGMS_HIP(hipStreamSynchronize(stream));
-
-  // ---- tiles: ELL buckets relation by relation, widest first (the longest-running tiles start first), then
-  //      the remainder pieces
-  for (int i = k; i >= 0; --i) {
-    for (int32_t r = 0; r < n_relations; ++r) {
-      const int64_t qa = bounds[(size_t)i * (n_relations + 1) + r], qb = bounds[(size_t)i * (n_relations + 1) + r + 1];
-      for (int64_t q = qa; q < qb; q += 32) {
-        RgmsTile tl;
-        tl.slot0 = bucket_slot_ptr[i] + ((q - bucket_row_ptr[i]) << i);
-        tl.row0 = (int32_t)q; tl.n_rows = (int32_t)std::min<int64_t>(32, qb - q); tl.log2w = i; tl.rel = r;
-        tl.last_len = 0; tl.pad_ = 0;
-        tiles.push_back(tl);
-      }
+    unsigned long long* d_flags = (unsigned long long*)tmp;
+    unsigned long long* d_counts = d_flags + kValidationWords;
+    int32_t* d_block_tile = (int32_t*)(tmp + o_block_tile);
+    int32_t* d_cells = (int32_t*)(tmp + o_cells);
+    int32_t* d_seq = (int32_t*)(tmp + o_seq);
+    if (cell_wgs > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
+    RGMS_HIP(hipMemsetAsync(tmp, 0, cleared, stream));
+    launch_validation(stacked, false, d_flags, stream);
+    if (ca.n_cells > 0) {
+      // (the numbers below mean something only if the verdict is good, and index nothing before it is known)
+      hipLaunchKernelGGL(k_cell_tiles, dim3((unsigned)cell_wgs), dim3(256), 0, stream, ca, d_cells,
+                         (int32_t*)(tmp + kReport), d_counts);
+      RGMS_HIP(hipGetLastError());
+      st = device_exclusive_scan(d_cells, ca.n_cells, d_seq, stream);
+      if (st != SPTIR_OK) goto fail;
+      hipLaunchKernelGGL(k_block_tiles, dim3((unsigned)(n_blocks / 256 + 1)), dim3(256), 0, stream, n_blocks,
+                         n_relations, d_cells, d_seq + n_seq, d_block_tile);
+      RGMS_HIP(hipGetLastError());
     }
-  }
-  p->n_ell_tiles = (int64_t)tiles.size();
-  for (int32_t r = 0; r < n_relations; ++r) {
-    const size_t o = (size_t)(k + 1) * (n_relations + 1);
-    for (int64_t q = bounds[o + r]; q < bounds[o + r + 1]; ++q) {
-      const int64_t m = q - h->R;
-      const int64_t begin = rem_ptr[m], len = rem_ptr[m + 1] - begin;
-      const int64_t n_seg = (len + 31) / 32;
-      for (int64_t s0 = 0; s0 < n_seg; s0 += 32) {
-        RgmsTile tl;
-        tl.slot0 = h->S + begin + s0 * 32;
-        tl.row0 = (int32_t)q; tl.n_rows = (int32_t)std::min<int64_t>(32, n_seg - s0); tl.log2w = -1; tl.rel = r;
-        const int64_t covered = (s0 + tl.n_rows) * 32;
-        tl.last_len = (int32_t)(covered <= len ? 32 : len - (covered - 32));
-        tl.pad_ = 0;
-        tiles.push_back(tl);
-      }
-    }
-  }
-  p->n_tiles = (int64_t)tiles.size();
-  p->tiles = (RgmsTile*)p->alloc(sizeof(RgmsTile) * std::max<size_t>(tiles.size(), 1), p->alloc_ctx, stream);
-  if (!p->tiles) { st = SPTIR_ERR_ALLOC; goto fail; }
-  p->device_bytes += sizeof(RgmsTile) * std::max<size_t>(tiles.size(), 1);
-  if (!tiles.empty())
-    RGMS_HIP(hipMemcpyAsync(p->tiles, tiles.data(), sizeof(RgmsTile) * tiles.size(), hipMemcpyHostToDevice, stream));
-  if (workspace_d_out > 0 && h->R > 0) {
-    // ---- where every ELL row's product row goes: the pairs of a row of Y side by side, relations ascending
-    const int32_t words = (n_relations + 63) / 64;
-    std::vector<int32_t> node_ptr((size_t)p->n_rows + 1, 0);
-    d_mask = (unsigned long long*)p->alloc(sizeof(unsigned long long) * (size_t)p->n_rows * words, p->alloc_ctx, stream);
-    p->node_ptr = (int32_t*)p->alloc(sizeof(int32_t) * ((size_t)p->n_rows + 1), p->alloc_ctx, stream);
-    p->pos_of_row = (int32_t*)p->alloc(sizeof(int32_t) * (size_t)h->R, p->alloc_ctx, stream);
-    p->partial = (float*)p->alloc(sizeof(float) * (size_t)h->R * workspace_d_out, p->alloc_ctx, stream);
-    if (!d_mask || !p->node_ptr || !p->pos_of_row || !p->partial) { st = SPTIR_ERR_ALLOC; goto fail; }
-    p->device_bytes += sizeof(int32_t) * ((size_t)p->n_rows + 1 + (size_t)h->R) +
-                       sizeof(float) * (size_t)h->R * workspace_d_out;
-    hipLaunchKernelGGL(k_node_masks, dim3((unsigned)((p->n_rows + 255) / 256)), dim3(256), 0, stream, p->n_rows,
-                       n_relations, words, 1 << k, stacked->indptr, d_mask, p->node_ptr + 1);
-    RGMS_HIP(hipGetLastError());
-    RGMS_HIP(hipMemcpyAsync(node_ptr.data() + 1, p->node_ptr + 1, sizeof(int32_t) * (size_t)p->n_rows,
-                            hipMemcpyDeviceToHost, stream));
+    RGMS_HIP(hipMemcpyAsync(host.p, tmp, report_bytes, hipMemcpyDeviceToHost, stream));
+    int32_t first = 0;
+    if (stacked->n_rows == 0)
+      RGMS_HIP(hipMemcpyAsync(&first, stacked->indptr, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
     RGMS_HIP(hipStreamSynchronize(stream));
-    for (int32_t i = 0; i < p->n_rows; ++i) node_ptr[(size_t)i + 1] += node_ptr[i];  // (ends at R < 2^31)
-    RGMS_HIP(hipMemcpyAsync(p->node_ptr, node_ptr.data(), sizeof(int32_t) * node_ptr.size(), hipMemcpyHostToDevice,
-                            stream));
-    hipLaunchKernelGGL(k_pair_positions, dim3((unsigned)((h->R + 255) / 256)), dim3(256), 0, stream, (int64_t)h->R,
-                       p->n_rows, words, h->row_ids, d_mask, p->node_ptr, p->pos_of_row);
+    if (stacked->n_rows == 0 && first != 0) { st = SPTIR_ERR_INVALID_ARG; goto fail; }
+    st = validation_verdict((const unsigned long long*)host.p, nullptr);
+    if (st != SPTIR_OK) goto fail;
+    const unsigned long long* counts = (const unsigned long long*)host.p + kValidationWords;
+    for (int s = 0; s < kCountSlots; ++s) {
+      p->n_pairs += (int64_t)counts[s * kCountStride];
+      p->n_pads += (int64_t)counts[s * kCountStride + 1];
+    }
+    const int32_t* block_tile = (const int32_t*)(host.p + o_block_tile);
+    p->n_tiles = n_blocks > 0 ? block_tile[n_blocks] : 0;
+
+    // ---- work items: a block each.  A block of more than twice the mean work is divided; where there are few blocks,
+    //      all are, into about 512 items.
+    const int32_t* block_entries = (const int32_t*)(host.p + kReport);
+    auto tiles_of = [&](int32_t b) { return block_tile[b + 1] - block_tile[b]; };
+    auto cost_of = [&](int32_t b) { return (int64_t)tiles_of(b) + block_entries[b] / 32; };  // (measured: 32 entries cost about what a tile does)
+    const int64_t cost = p->n_tiles + nnz / 32, mean = n_blocks > 0 ? cost / n_blocks : 0;
+    const int64_t most = n_blocks >= 160 ? std::max<int64_t>(64, 2 * mean) : std::max<int64_t>(8, cost / 512);
+    items.reserve((size_t)n_blocks + 16);
+    for (int32_t b = 0; b < n_blocks; ++b) {  // divided blocks first: theirs are the longest items
+      const int64_t c = cost_of(b);
+      if (c <= most) continue;
+      const int32_t t0 = block_tile[b], n = tiles_of(b);
+      const int32_t parts = (int32_t)std::min<int64_t>(n, (c + most - 1) / most);
+      divided.push_back(make_int4(b, p->n_parts, parts, 0));
+      for (int32_t i = 0; i < parts; ++i) {
+        const int32_t lo = (int32_t)((int64_t)n * i / parts), hi = (int32_t)((int64_t)n * (i + 1) / parts);
+        items.push_back({b, t0 + lo, hi - lo, p->n_parts++});
+      }
+    }
+    for (int32_t b = 0; b < n_blocks; ++b)
+      if (cost_of(b) <= most) items.push_back({b, block_tile[b], tiles_of(b), -1});
+    p->n_items = (int32_t)items.size();
+    p->n_divided = (int32_t)divided.size();
+
+    // ---- the handle's arrays
+    size_t bytes = 0;
+    const size_t o_tiles = reserve(&bytes, sizeof(RgmsTile) * (size_t)p->n_tiles);
+    const size_t o_rows = reserve(&bytes, sizeof(uint16_t) * (size_t)p->n_tiles * kTileRows);
+    const size_t o_entries = reserve(&bytes, sizeof(int2) * (size_t)nnz);
+    const size_t o_piece = reserve(&bytes, (size_t)nnz);
+    const size_t o_items = reserve(&bytes, sizeof(RgmsItem) * items.size());
+    const size_t o_divided = reserve(&bytes, sizeof(int4) * divided.size());
+    const size_t o_partial = reserve(&bytes, sizeof(float) * (((size_t)p->n_parts * workspace_d_out) << p->log2_block));
+    bytes = std::max<size_t>(bytes, 256);
+    p->blob = p->alloc(bytes, p->alloc_ctx, stream);
+    if (!p->blob) { st = SPTIR_ERR_ALLOC; goto fail; }
+    p->device_bytes = bytes;
+    char* base = (char*)p->blob;
+    p->tiles = (RgmsTile*)(base + o_tiles);
+    p->tile_rows = (uint16_t*)(base + o_rows);
+    p->entries = (int2*)(base + o_entries);
+    p->entry_piece = (uint8_t*)(base + o_piece);
+    p->items = (RgmsItem*)(base + o_items);
+    p->divided = (int4*)(base + o_divided);
+    p->partial = (float*)(base + o_partial);
+    if (p->n_tiles > 0)
+      hipLaunchKernelGGL(k_fill_tiles, dim3((unsigned)cell_wgs), dim3(256), 0, stream, ca, d_cells, d_seq + n_seq,
+                         p->tiles, p->tile_rows, p->entry_piece);
+    if (nnz > 0)
+      hipLaunchKernelGGL(k_pair_entries, dim3((unsigned)((nnz + 255) / 256)), dim3(256), 0, stream, nnz,
+                         stacked->indices, stacked->values, p->entries);
     RGMS_HIP(hipGetLastError());
-    RGMS_HIP(hipStreamSynchronize(stream));  // node_ptr (host) goes out of scope
-    p->workspace_d_out = workspace_d_out;
+    if (!items.empty())
+      RGMS_HIP(hipMemcpyAsync(p->items, items.data(), sizeof(RgmsItem) * items.size(), hipMemcpyHostToDevice, stream));
+    if (!divided.empty())
+      RGMS_HIP(hipMemcpyAsync(p->divided, divided.data(), sizeof(int4) * divided.size(), hipMemcpyHostToDevice, stream));
+    RGMS_HIP(hipStreamSynchronize(stream));  // (also: the host vectors go out of scope)
   }
-  RGMS_HIP(hipStreamSynchronize(stream));
-  p->free_(d_lists, p->alloc_ctx);
-  p->free_(d_bounds, p->alloc_ctx);
-  if (d_mask) p->free_(d_mask, p->alloc_ctx);
+  scratch_free(tmp, p->free_, p->alloc_ctx);
+  pinned_release(host);
   *out = p;
   return SPTIR_OK;
 
 fail:
   (void)hipStreamSynchronize(stream);
-  if (d_lists) p->free_(d_lists, p->alloc_ctx);
-  if (d_bounds) p->free_(d_bounds, p->alloc_ctx);
-  if (d_mask) p->free_(d_mask, p->alloc_ctx);
+  scratch_free(tmp, p->free_, p->alloc_ctx);
+  pinned_release(host);
   sptir_rgms_destroy(p);
   return st;
 #undef RGMS_HIP
@@ -478,39 +685,52 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   if ((d_in != 32 && d_in != 64 && d_in != 128) || d_out % 32 != 0 || (((uintptr_t)X) & 15) != 0)
     return SPTIR_ERR_UNSUPPORTED;
   hipStream_t stream = (hipStream_t)stream_;
-  const int64_t y_elems = (int64_t)p->n_rows * d_out;
   RgmsArgs a;
-  a.tiles = p->tiles; a.row_ids = p->hyb->row_ids; a.cols = p->hyb->cols; a.vals = p->hyb->vals;
-  a.X = X; a.W = W; a.Y = Y; a.n_tiles = p->n_tiles; a.n_rows = p->n_rows; a.d_in = d_in; a.d_out = d_out;
-  a.pos_of_row = p->pos_of_row; a.partial = p->partial;
-  const dim3 block(64 * kRgmsWaves);
-  auto launch = [&](bool to_workspace, int64_t first, int64_t n) {
-    if (n <= 0) return;
-    RgmsArgs b = a;
-    b.tiles = p->tiles + first; b.n_tiles = n;
-    const dim3 grid((unsigned)((n + kRgmsWaves - 1) / kRgmsWaves));
-    if (to_workspace) {
-      if (d_in == 32) hipLaunchKernelGGL((k_rgms<1, true>), grid, block, 0, stream, b);
-      else if (d_in == 64) hipLaunchKernelGGL((k_rgms<2, true>), grid, block, 0, stream, b);
-      else hipLaunchKernelGGL((k_rgms<4, true>), grid, block, 0, stream, b);
-    } else {
-      if (d_in == 32) hipLaunchKernelGGL((k_rgms<1, false>), grid, block, 0, stream, b);
-      else if (d_in == 64) hipLaunchKernelGGL((k_rgms<2, false>), grid, block, 0, stream, b);
-      else hipLaunchKernelGGL((k_rgms<4, false>), grid, block, 0, stream, b);
-    }
+  a.items = p->items; a.tiles = p->tiles; a.tile_rows = (const ushort4*)p->tile_rows;
+  a.entries = p->entries; a.entry_piece = p->entry_piece;
+  a.X = X; a.W = W; a.Y = Y; a.partial = p->partial;
+  a.n_rows = p->n_rows; a.log2_block = p->log2_block; a.d_out = d_out;
+  a.width = std::min<int32_t>(d_out, (kYTileBytes / 8 >> p->log2_block) / 32 * 32);
+  const int64_t chunks = (d_out + a.width - 1) / a.width;
+  if (chunks > 65535) return SPTIR_ERR_OVERFLOW;
+  const bool ordered = d_out <= p->workspace_d_out;
+  // Where the matrices W[r] are large (32 KB and up, more than L1 holds) the tiles are long, and a few hundred workgroups
+  // leave the CUs unevenly filled: every item is then shared by as many workgroups as make 512, eight wavefronts each,
+  // whose sums meet in Y by atomics (8,370 rows, 128 x 128, 262 items: 0.215 -> 0.168 ms; 1024 or 256 workgroups, 4 or
+  // 16 wavefronts each were slower).
+  const int64_t whole = (int64_t)p->n_items * chunks;
+  const bool large_w = d_in * d_out >= 64 * 128;
+  a.sharers = !ordered && large_w && whole < 512 ? (int32_t)std::min<int64_t>(8, (512 + whole - 1) / whole) : 1;
+  // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do
+  const int64_t tiles_each = p->n_tiles / std::max<int64_t>((int64_t)p->n_items * a.sharers, 1);
+  a.n_waves = large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;
+  const size_t lds = sizeof(double) * ((size_t)a.width << p->log2_block) + (ordered ? sizeof(int) * (a.width / 16) : 0);
+  const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);
+  auto divided = [&](const float* partial) {
+    if (p->n_divided > 0)
+      hipLaunchKernelGGL(k_rgms_divided, dim3((unsigned)p->n_divided), dim3(256), 0, stream, p->divided, p->n_rows,
+                         p->log2_block, d_out, partial, Y);
   };
-  if (p->partial && d_out <= p->workspace_d_out && (((uintptr_t)Y) & 15) == 0) {
-    // product rows to the workspace, one pass that sums them into Y (every row of Y is written: no zero fill),
-    // then the few remainder tiles on top with atomics
-    launch(true, 0, p->n_ell_tiles);
-    hipLaunchKernelGGL(k_rgms_reduce, dim3((unsigned)((p->n_rows + 32 * kReduceRows - 1) / (32 * kReduceRows))), dim3(256),
-                       0, stream, p->n_rows, d_out, p->node_ptr, p->partial, Y);
-    launch(false, p->n_ell_tiles, p->n_tiles - p->n_ell_tiles);
-  } else {
-    hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)std::min<int64_t>((y_elems + 255) / 256, 8192)), dim3(256), 0,
-                       stream, Y, y_elems);
-    launch(false, 0, p->n_tiles);
+  if (a.sharers > 1) {
+    const int64_t n = (int64_t)p->n_rows * d_out;
+    hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 8192)), dim3(256), 0, stream, Y, n);
+  } else if (!ordered) {
+    divided(nullptr);
   }
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, stream, a); };
+  auto launch_for = [&](auto ord, auto wide) {
+    constexpr bool kOrdered = decltype(ord)::value, kWide = decltype(wide)::value;
+    if (d_in == 32) launch(k_rgms<1, kOrdered, kWide>);
+    else if (d_in == 64) launch(k_rgms<2, kOrdered, kWide>);
+    else launch(k_rgms<4, kOrdered, kWide>);
+  };
+  // (a buffer has a 32-bit size)
+  const uint64_t x_bytes = (uint64_t)p->n_cols * d_in * sizeof(float);
+  const bool wide_x = x_bytes > 0xFFFFFFFFull;
+  a.x_bytes = wide_x ? 0 : (uint32_t)x_bytes;
+  if (ordered) wide_x ? launch_for(std::true_type{}, std::true_type{}) : launch_for(std::true_type{}, std::false_type{});
+  else wide_x ? launch_for(std::false_type{}, std::true_type{}) : launch_for(std::false_type{}, std::false_type{});
+  if (ordered) divided(p->partial);
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;
 }

@@ -121,6 +121,23 @@ sptir_status_t hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts, int32
 // the options a NULL pointer stands for / a caller's struct with unknown tail fields zeroed
 sptir_build_options_t complete_options(const sptir_build_options_t* given);
 
+// Validation of a CSR input on the GPU (builder.hip): `flags` is device memory, kValidationWords zeroed 64-bit words;
+// the verdict is read from a host copy of them.  *one_value_per_row is only meaningful if the values were looked at.
+constexpr int kValidationWords = 64 * 8;
+void launch_validation(const sptir_csr_t* csr, bool with_values, unsigned long long* flags, hipStream_t stream);
+sptir_status_t validation_verdict(const unsigned long long* flags, bool* one_value_per_row);
+
+// Exclusive scan of data[0 .. n) in place; data has room for scan_room(n) elements, seq_base for one int per
+// kScanSeq of them plus one, which receives the total (at element n_seq = scan_room(n) / kScanSeq).
+constexpr int kScanSeq = 4096;
+sptir_status_t device_exclusive_scan(int32_t* data, int64_t n, int32_t* seq_base, hipStream_t stream);
+size_t scan_room(int64_t n);
+
+// pinned host memory, kept between calls
+struct PinnedBuf { char* p = nullptr; size_t size = 0; };
+PinnedBuf pinned_acquire(size_t bytes);
+void pinned_release(PinnedBuf b);
+
 // What the builder decides about the SpMM launches from the sizes alone (builder.hip; host code, no device access).
 struct LaunchShape {
   int32_t log2_row_block;   // rows of Y per wavefront

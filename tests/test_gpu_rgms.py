@@ -156,3 +156,46 @@ def test_rgms_named_configs(gpu_lib, name, workspace):
     Yr, Sr = oracle.rgms(w.n_rel, w.n, w.indptr, w.indices, w.values, w.X, w.W)
     worst = assert_y_close(Y, Yr, Sr, name)
     say(f"[rgms config] {name}: max_err={worst:.2e}")
+
+
+@pytest.mark.parametrize("workspace", [0, 160])
+@pytest.mark.parametrize("n,n_rel,d_in,d_out", [(1, 3, 32, 32), (31, 2, 32, 96), (257, 1, 64, 32), (700, 3, 32, 160),
+                                                (4000, 2, 128, 64), (60_000, 4, 32, 32), (9000, 1, 128, 128)])
+def test_rgms_tile_edges(gpu_lib, n, n_rel, d_in, d_out, workspace):
+    """Pairs of 1, 4 +- 1, 8 +- 1, 64 +- 1 and 1500 entries (steps, pieces and batches of a tile), cells of 15 to 17 pairs,
+    row blocks of every size, undivided, divided and shared between workgroups, one and several passes over Y."""
+    rng = np.random.default_rng(n + d_out)
+    counts = np.zeros(n_rel * n, dtype=np.int64)
+    lens = np.minimum([1, 1, 2, 3, 4, 5, 7, 8, 9, 63, 64, 65], n)
+    some = rng.choice(n_rel * n, min(n_rel * n, 3000), replace=False)
+    counts[some] = rng.choice(lens, some.size)
+    counts[: min(17, n_rel * n)] = 1
+    counts[int(rng.integers(n_rel * n))] = min(1500, n)
+    w0 = workloads.random_csr(n_rel * n, n, counts, 3, 1, "uniform")
+    w = workloads.HeteroWorkload("edges", n, n_rel, w0.indptr, w0.indices, w0.values,
+                                 rng.standard_normal((n, d_in)).astype(np.float32),
+                                 rng.standard_normal((n_rel, d_in, d_out)).astype(np.float32))
+    (Y, Y2), info = run_rgms(gpu_lib, w, workspace_d_out=workspace, repeat=2)
+    assert info["n_stacked_rows_stored"] == int((counts > 0).sum()) and info["nnz"] == w.nnz
+    Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, w.X, w.W)
+    assert_y_close(Y, Yr, Sr, f"n={n} d_in={d_in} d_out={d_out}")
+    assert np.array_equal(Y, Y2) if workspace >= d_out else np.allclose(Y, Y2, rtol=1e-4, atol=1e-4)
+
+
+def test_rgms_features_beyond_4_gb(gpu_lib):
+    """Offsets into an X of more than 4 GB."""
+    n_cols, d = (1 << 23) + 100, 128
+    cols = [3, 1 << 22, (1 << 23) - 1, 1 << 23, n_cols - 1]
+    ip = torch.tensor([0, 2, 5], dtype=torch.int32, device="cuda")
+    ix = torch.tensor([cols[0], cols[3], cols[1], cols[2], cols[4]], dtype=torch.int32, device="cuda")
+    va = torch.tensor([1.0, 2.0, -1.0, 0.5, 3.0], device="cuda")
+    X = torch.zeros(n_cols, d, device="cuda")
+    X[cols] = torch.randn(len(cols), d, device="cuda")
+    W = torch.randn(1, d, 32, device="cuda")
+    h = gpu_lib.sptir_rgms_build(1, 2, n_cols, ip, ix, va)
+    Y = torch.full((2, 32), float("nan"), device="cuda")
+    gpu_lib.sptir_rgms(h, X, W, Y)
+    rows = X[ix.long()].cpu().double() * va.cpu().double()[:, None]
+    want = torch.stack([rows[:2].sum(0), rows[2:].sum(0)]) @ W[0].cpu().double()
+    assert torch.allclose(Y.cpu().double(), want, rtol=1e-4, atol=1e-3)
+    h.destroy()
