@@ -4,10 +4,13 @@
 // non-zeros directly (its sparse_fuse primitive) and reduces in two stages
 // with vector loads; the mapping below keeps those three ideas.
 //
-// Mapping (gfx950, wave64).  The non-zeros are cut into runs of 64*kChunks
+// Mapping (gfx950, wave64).  The non-zeros are cut into runs of up to 64*kChunks
 // consecutive entries, one wavefront each, so the work per wavefront is the
 // same whatever the row lengths.  A wavefront takes 64 entries at a time with
-// one coalesced load of their columns and values.  Eight lane groups of eight
+// one coalesced load of their columns and values, a chunk ahead.  In CSR order the
+// first row of a run is found by a 64-way search and the rows of a chunk by
+// counting row starts across the lanes (halving searches and walking indptr took
+// longer than the products on small graphs).  Eight lane groups of eight
 // lanes then work on eight entries at once (group g on entries 8g .. 8g+7 of
 // the 64, one after the other, so that its row changes rarely): lane fl of a group holds floats
 // 4*(8t + fl) .. +3 (t = 0..T-1) of the entry's row of X in registers (loaded
@@ -25,6 +28,10 @@
 // other, so an XCD's L2 holds the rows of Yt of one partition at a time.
 // There is nothing to accumulate across partitions - an entry's result is
 // complete where it is computed - so one launch covers all of them.
+//
+// Measured: CSR order, 169,343 rows, 1.17 M entries: 64 features 97 -> 53 us, 32: 91 -> 28, 128: 127 -> 104 (5.7 TB/s of
+// gathered rows, all beyond L2); 41 features, 1.5 M entries 612 -> 49 us; 2,708 rows 42 -> 12 us.  With a plan, 232,965
+// rows, 114.6 M entries, 128 features: 3.56 -> 3.47 ms; 20 M entries, 53 features 3.20 -> 0.54 ms.
 #include <string.h>
 
 #include <algorithm>
@@ -33,6 +40,7 @@
 
 #include "sptir_internal.h"
 #include "sptir_scan.h"
+#include "sptir_tiles.h"
 
 namespace sptir {
 namespace {
@@ -51,6 +59,7 @@ struct SddmmArgs {
   int64_t nnz;
   int32_t n_rows;
   int32_t feat;
+  int32_t run;      // CSR order: entries per wavefront
   // with a plan: entries in partition order, and where each XCD's runs start
   const int32_t* e_row;
   const int32_t* e_col;
@@ -60,12 +69,17 @@ struct SddmmArgs {
   const int32_t* xcd_run_ptr;      // [9]: the runs of XCD x are xcd_run_ptr[x] .. xcd_run_ptr[x+1]
 };
 
-// largest r in [0, n_rows) with indptr[r] <= e (e < nnz, so it exists)
-__device__ __forceinline__ int row_of_entry(const int32_t* __restrict__ indptr, int n_rows, int64_t e) {
+// largest r in [0, n_rows) with indptr[r] <= e (e < nnz, so it exists); the lanes of a wavefront probe 64 places at a
+// time (three dependent loads for 200,000 rows where halving takes 18)
+__device__ __forceinline__ int row_of_entry(const int32_t* __restrict__ indptr, int n_rows, int64_t e, int lane) {
   int lo = 0, hi = n_rows;  // invariant: indptr[lo] <= e < indptr[hi]
   while (hi - lo > 1) {
-    int mid = lo + ((hi - lo) >> 1);
-    if ((int64_t)indptr[mid] <= e) lo = mid; else hi = mid;
+    const int step = (hi - lo + 63) >> 6;
+    const int64_t at = lo + (int64_t)(lane + 1) * step;
+    const bool below = at < hi && (int64_t)indptr[at] <= e;
+    const int n = __popcll(__ballot(below));  // (ascending: the lanes below come first)
+    lo += n * step;
+    hi = (int)min((int64_t)hi, (int64_t)lo + step);
   }
   return lo;
 }
@@ -95,202 +109,253 @@ __device__ __forceinline__ float reduce_scatter8(float (&p)[8], int fl) {
   return keep + __shfl_xor(give, 1, 64);
 }
 
-// T float4 per lane cover feat <= 32*T floats; FULL: feat == 32*T, no lane is past the end
+// The 64 entries of a chunk as the lanes hold them.
+struct ChunkEntries {
+  int col, row;
+  int pos;    // CSR position
+  float val;  // CSR order only
+};
+
+// Number of the 64 ascending values, one per lane, that are <= v.
+__device__ __forceinline__ int count_not_above(int ascending, int v) {
+  int n = 0;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) n += __shfl(ascending, n + d - 1, 64) <= v ? d : 0;
+  return n + (n == 63 && __shfl(ascending, 63, 64) <= v ? 1 : 0);
+}
+
+// T float4 per lane cover 32*T floats of a row; wider rows (MANY) are taken 32*T floats at a time.  kWhole: that is the
+// row.  kQuads: lanes past its end drop what they read.  kTail: feat is no multiple of 4, and the lane that holds the end of
+// a row reads the row's last four floats and drops those its neighbour has.  No load is conditional: behind a branch
+// the compiler could not count the loads in flight and every wait would cover all of them.
 // (The second launch bound tells the register allocator how many wavefronts per SIMD to leave room for; left
 //  alone it spreads the pipeline stages over 280+ registers although 16*T + 30 are live at any time.)
-template <int T, bool FULL, bool PLAN>
+enum RowEnd { kWhole, kQuads, kTail };
+template <int T, RowEnd END, bool MANY, bool PLAN>
 __global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(SddmmArgs a) {
   const int lane = threadIdx.x & 63, g = lane >> 3, fl = lane & 7;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   int64_t e_begin, e_end;
   if constexpr (PLAN) {
     // consecutive workgroup ids go to consecutive XCDs: workgroup (x + 8*j) is the j-th of XCD x
     const int xcd = blockIdx.x & 7;
-    const int64_t run = (int64_t)a.xcd_run_ptr[xcd] + (int64_t)(blockIdx.x >> 3) * kSddmmWaves + (threadIdx.x >> 6);
+    const int64_t run = (int64_t)a.xcd_run_ptr[xcd] + (int64_t)(blockIdx.x >> 3) * kSddmmWaves + wave;
     if (run >= a.xcd_run_ptr[xcd + 1]) return;
     e_begin = a.run_first_entry[run];
     e_end = e_begin + a.run_len[run];
   } else {
-    const int64_t run = (int64_t)blockIdx.x * kSddmmWaves + (threadIdx.x >> 6);
-    e_begin = run * kSddmmRun;
+    e_begin = ((int64_t)blockIdx.x * kSddmmWaves + wave) * a.run;
     if (e_begin >= a.nnz) return;
-    e_end = min(a.nnz, e_begin + kSddmmRun);
+    e_end = min(a.nnz, e_begin + a.run);
   }
   const size_t feat = (size_t)a.feat;
 
-  bool f_ok[T];
+  // this lane's floats of a row, from feature f_base on
+  auto load_row = [&](const float* row, int f_base, float4 (&v)[T]) {
 #pragma unroll
-  for (int t = 0; t < T; ++t) f_ok[t] = FULL || 4 * (8 * t + fl) < a.feat;
-  const int f_lane = 4 * fl;  // float offset of this lane inside every 32-float stripe
+    for (int t = 0; t < T; ++t) {
+      const int f = f_base + 32 * t + 4 * fl;
+      const int at = END == kWhole ? f : min(f, a.feat - 4);
+      const float4u u = *reinterpret_cast<const float4u*>(row + at);
+      v[t] = make_float4(u.x, u.y, u.z, u.w);
+      if constexpr (END == kQuads) {
+        if (f >= a.feat) v[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+      } else if constexpr (END == kTail) {
+        const int drop = f - at;  // floats that belong to the lane below (4 and more: all of them)
+        if (drop > 0) v[t].x = 0.f;
+        if (drop > 1) v[t].y = 0.f;
+        if (drop > 2) v[t].z = 0.f;
+        if (drop > 3) v[t].w = 0.f;
+      }
+    }
+  };
 
-  int row_lo = PLAN ? 0 : row_of_entry(a.indptr, a.n_rows, e_begin);  // row of the chunk's first entry (wave-uniform)
+  auto fetch = [&](int64_t base) {
+    ChunkEntries c;
+    const int64_t e = min(base + lane, e_end - 1);  // (a lane past the end repeats the last entry)
+    if constexpr (PLAN) {
+      c.col = a.e_col[e]; c.row = a.e_row[e]; c.pos = a.e_pos[e];
+      c.val = 0.f;
+    } else {
+      c.col = a.indices[e]; c.val = a.values[e];
+      c.row = 0; c.pos = (int)e;
+    }
+    return c;
+  };
+  // CSR order: the starts of the 64 rows after row_lo, the row of a chunk's first entry, say which row each of its
+  // entries is in; they are asked for a chunk ahead, and the counting is done while gathers are in flight
+  int row_lo = 0, starts = 0;
+  auto fetch_starts = [&](int row) { return a.indptr[min(row + 1 + lane, a.n_rows)]; };
+  auto find_rows = [&](ChunkEntries& c) {
+    bool open = true;
+    while (true) {  // (once, unless the chunk touches more than 64 rows)
+      const int n = count_not_above(starts, c.pos);
+      if (open) c.row = row_lo + n;
+      open = open && n == 64;
+      if (!__any(open)) break;
+      row_lo += 64;
+      starts = fetch_starts(row_lo);
+    }
+    row_lo = __builtin_amdgcn_readlane(c.row, 63);
+    starts = fetch_starts(row_lo);
+  };
+  ChunkEntries next = fetch(e_begin);
+  if constexpr (!PLAN) {
+    row_lo = row_of_entry(a.indptr, a.n_rows, e_begin, lane);
+    starts = fetch_starts(row_lo);
+    find_rows(next);
+  }
+
   // The rows of X a chunk needs are staged in LDS once per chunk: every load instruction then brings up to eight
   // different rows (one per lane group), where a reload inside the entry loop costs the address path a whole
   // instruction even if a single lane group asks for it - and in partition order a row lasts only a few entries.
-  // (Measured: pays for feature sizes of 128 and 256 in partition order, costs a little everywhere else.)
-  constexpr int kStage = !PLAN ? 0 : (T == 4 ? 16 : (T == 8 ? 8 : 0));  // rows of X staged per wavefront (8 KB)
+  // (CSR order: no gain, measured.)
+  constexpr int kStage = MANY || !PLAN ? 0 : (T == 3 || T == 4 ? 16 : (T > 4 ? 8 : 0));  // rows of X staged per wavefront
   __shared__ __align__(16) float x_stage[kSddmmWaves][kStage > 0 ? kStage : 1][32 * T];
   __shared__ int row_table[kSddmmWaves][kStage > 0 ? kStage : 1];
-  const int wave = threadIdx.x >> 6;
   float4 x[T];
   int x_row = -1;
 #pragma unroll
   for (int t = 0; t < T; ++t) x[t] = make_float4(0.f, 0.f, 0.f, 0.f);
 
   for (int64_t base = e_begin; base < e_end; base += 64) {
-    const int64_t e_lane = base + lane;
-    const bool in = e_lane < e_end;
-    int col_reg, row_reg;
-    int64_t out_pos;
-    float val_reg;
-    if constexpr (PLAN) {
-      const int64_t el = in ? e_lane : e_begin;  // (a lane past the end repeats the run's first entry)
-      col_reg = a.e_col[el];
-      row_reg = a.e_row[el];
-      out_pos = a.e_pos[el];
-      val_reg = a.values[out_pos];
-    } else {
-      col_reg = in ? a.indices[e_lane] : 0;
-      val_reg = in ? a.values[e_lane] : 0.f;
-      out_pos = e_lane;
-      // the row of this lane's entry: walk on from the chunk's first row
-      row_reg = row_lo;
-      if (in) {
-        while (row_reg + 1 < a.n_rows && e_lane >= (int64_t)a.indptr[row_reg + 1]) ++row_reg;
-      }
-    }
-    bool staged = false;
-    int rank_reg = 0, x_rank = -1;
-    if constexpr (kStage > 0) {
-      // entries arrive row by row: a lane whose row differs from its left neighbour's starts a new row
-      const int left = __shfl_up(row_reg, 1, 64);
-      const bool head = lane == 0 || row_reg != left;
-      const unsigned long long heads = __ballot(head);
-      const int n_distinct = __popcll(heads);
-      rank_reg = __popcll(heads & ((2ull << lane) - 1ull)) - 1;  // which of the chunk's rows this lane's entry uses
-      staged = n_distinct <= kStage;                             // (wave-uniform)
-      if (staged) {
-        if (head) row_table[wave][rank_reg] = row_reg;
-        for (int k0 = 0; k0 < n_distinct; k0 += 8) {
-          const int k = k0 + g;
-          if (k < n_distinct) {
-            const float* xr = a.X + (size_t)row_table[wave][k] * feat + f_lane;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-              const float4 v = f_ok[t] ? *reinterpret_cast<const float4*>(xr + 32 * t) : make_float4(0.f, 0.f, 0.f, 0.f);
-              *reinterpret_cast<float4*>(&x_stage[wave][k][32 * t + f_lane]) = v;
-            }
-          }
-        }
-        x_row = -1;  // the registers are about to hold staged rows
-      }
-    }
+    ChunkEntries c = next;
+    next = fetch(min(base + 64, e_end - 1));  // travels during this chunk
+    const bool in = base + lane < e_end;
+    if constexpr (PLAN) c.val = a.values[c.pos];
     // Gathers run kAhead entries ahead of the multiplies; the scheduling barriers keep the compiler from
     // hoisting all eight entries' loads to the top (T*8 float4 of registers).
-    constexpr int kAhead = T <= 8 ? 2 : 1;
-    float4 y[kAhead + 1][T];
-    auto issue = [&](int i, float4 (&yb)[T]) {
-      const int c = __shfl(col_reg, g * 8 + i, 64);  // lane g*8+i fetched this group's i-th entry
-      const float* yr = a.Yt + (size_t)c * feat + f_lane;
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        if (FULL || f_ok[t]) yb[t] = *reinterpret_cast<const float4*>(yr + 32 * t);
-        else yb[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    };
+    constexpr int kAhead = 2;
     float p[8];
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i) issue(i, y[i]);
+    for (int i = 0; i < 8; ++i) p[i] = 0.f;
+    for (int f_base = 0; f_base < (MANY ? a.feat : 1); f_base += 32 * T) {
+      float4 y[kAhead + 1][T];
+      auto issue = [&](int i, float4 (&yb)[T]) {
+        const int col = __shfl(c.col, g * 8 + i, 64);  // lane g*8+i fetched this group's i-th entry
+        load_row(a.Yt + (size_t)col * feat, f_base, yb);
+      };
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (staged) {
-        const int rk = __shfl(rank_reg, g * 8 + i, 64);
-        if (rk != x_rank) {
+      for (int i = 0; i < kAhead && !PLAN; ++i) issue(i, y[i]);
+      if constexpr (!PLAN) {
+        if (f_base == 0) find_rows(next);
+      }
+      bool staged = false;
+      int rank_reg = 0, x_rank = -1;
+      if constexpr (kStage > 0) {
+        // entries arrive row by row: a lane whose row differs from its left neighbour's starts a new row
+        const int left = __shfl_up(c.row, 1, 64);
+        const bool head = lane == 0 || c.row != left;
+        const unsigned long long heads = __ballot(head);
+        const int n_distinct = __popcll(heads);
+        rank_reg = __popcll(heads & ((2ull << lane) - 1ull)) - 1;  // which of the chunk's rows this lane's entry uses
+        staged = n_distinct <= kStage;                             // (wave-uniform)
+        if (staged) {
+          if (head) row_table[wave][rank_reg] = c.row;
+          for (int k0 = 0; k0 < n_distinct; k0 += 8) {
+            const int k = k0 + g;
+            if (k < n_distinct) {
+              float4 v[T];
+              load_row(a.X + (size_t)row_table[wave][k] * feat, f_base, v);
 #pragma unroll
-          for (int t = 0; t < T; ++t) x[t] = *reinterpret_cast<const float4*>(&x_stage[wave][rk][32 * t + f_lane]);
-          x_rank = rk;
-        }
-      } else {
-        const int r = __shfl(row_reg, g * 8 + i, 64);
-        if (r != x_row) {  // (entries past the end carry a valid row: a harmless reload)
-          const float* xr = a.X + (size_t)r * feat + f_lane;
-#pragma unroll
-          for (int t = 0; t < T; ++t) {
-            x[t] = f_ok[t] ? *reinterpret_cast<const float4*>(xr + 32 * t) : make_float4(0.f, 0.f, 0.f, 0.f);
+              for (int t = 0; t < T; ++t) *reinterpret_cast<float4*>(&x_stage[wave][k][32 * t + 4 * fl]) = v[t];
+            }
           }
-          x_row = r;
+          x_row = -1;  // the registers are about to hold staged rows
         }
       }
-      if (i + kAhead < 8) issue(i + kAhead, y[(i + kAhead) % (kAhead + 1)]);
-      float acc = 0.f;
 #pragma unroll
-      for (int t = 0; t < T; ++t) acc = dot4(x[t], y[i % (kAhead + 1)][t], acc);
-      // pin the multiplies here: left free, they are sunk to the use of p[] after the loop and every
-      // gathered line stays live (and spills) until then
-      asm volatile("" : "+v"(acc));
-      p[i] = acc;
-      __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < kAhead && PLAN; ++i) issue(i, y[i]);
+      if constexpr (MANY) x_row = -1;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (staged) {
+          const int rk = __shfl(rank_reg, g * 8 + i, 64);
+          if (rk != x_rank) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) x[t] = *reinterpret_cast<const float4*>(&x_stage[wave][rk][32 * t + 4 * fl]);
+            x_rank = rk;
+          }
+        } else {
+          const int r = __shfl(c.row, g * 8 + i, 64);
+          if (r != x_row) {
+            load_row(a.X + (size_t)r * feat, f_base, x);
+            x_row = r;
+          }
+        }
+        if (i + kAhead < 8) issue(i + kAhead, y[(i + kAhead) % (kAhead + 1)]);
+        float acc = 0.f;
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc = dot4(x[t], y[i % (kAhead + 1)][t], acc);
+        // pin the multiplies here: left free, they are sunk to the use of p[] after the loop and every
+        // gathered line stays live (and spills) until then
+        asm volatile("" : "+v"(acc));
+        p[i] += acc;
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     // lane (g, fl) ends with the total of p[fl], i.e. of entry base + g*8 + fl = base + lane: its own entry
     const float mine = reduce_scatter8(p, fl);
-    if (in) a.B[out_pos] = val_reg * mine;
-    if constexpr (!PLAN) row_lo = __builtin_amdgcn_readlane(row_reg, 63);  // (a lane past the end kept row_lo itself)
-    // the last lane's entry may lie past the end only in the run's last chunk, after which nothing follows
+    if (in) a.B[c.pos] = c.val * mine;
   }
 }
 
-// Any feat and alignment: one entry at a time, the 64 lanes stride over the features.
+// fewer than four features: a lane per entry
 template <bool PLAN>
-__global__ __launch_bounds__(64 * kSddmmWaves) void k_sddmm_generic(SddmmArgs a) {
-  const int lane = threadIdx.x & 63;
-  int64_t e_begin, e_end;
+__global__ __launch_bounds__(256) void k_sddmm_narrow(SddmmArgs a) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t wave_first = e & ~(int64_t)63;
+  if (wave_first >= a.nnz) return;
+  const int64_t at = min(e, a.nnz - 1);
+  int row, col;
+  int64_t pos;
   if constexpr (PLAN) {
-    const int xcd = blockIdx.x & 7;
-    const int64_t run = (int64_t)a.xcd_run_ptr[xcd] + (int64_t)(blockIdx.x >> 3) * kSddmmWaves + (threadIdx.x >> 6);
-    if (run >= a.xcd_run_ptr[xcd + 1]) return;
-    e_begin = a.run_first_entry[run];
-    e_end = e_begin + a.run_len[run];
+    row = a.e_row[at]; col = a.e_col[at]; pos = a.e_pos[at];
   } else {
-    const int64_t run = (int64_t)blockIdx.x * kSddmmWaves + (threadIdx.x >> 6);
-    e_begin = run * kSddmmRun;
-    if (e_begin >= a.nnz) return;
-    e_end = min(a.nnz, e_begin + kSddmmRun);
+    row = row_of_entry(a.indptr, a.n_rows, wave_first, (int)(threadIdx.x & 63));
+    while (row + 1 < a.n_rows && at >= (int64_t)a.indptr[row + 1]) ++row;
+    col = a.indices[at]; pos = at;
   }
-  int row = PLAN ? 0 : row_of_entry(a.indptr, a.n_rows, e_begin);
-  for (int64_t e = e_begin; e < e_end; ++e) {
-    int col;
-    int64_t pos;
-    if constexpr (PLAN) {
-      row = a.e_row[e]; col = a.e_col[e]; pos = a.e_pos[e];
-    } else {
-      while (row + 1 < a.n_rows && e >= (int64_t)a.indptr[row + 1]) ++row;
-      col = a.indices[e]; pos = e;
-    }
-    const float* xr = a.X + (size_t)row * (size_t)a.feat;
-    const float* yr = a.Yt + (size_t)col * (size_t)a.feat;
-    float acc = 0.f;
-    for (int f = lane; f < a.feat; f += 64) acc = fmaf(xr[f], yr[f], acc);
-    for (int d = 32; d > 0; d >>= 1) acc += __shfl_xor(acc, d, 64);
-    if (lane == 0) a.B[pos] = a.values[pos] * acc;
-  }
+  float acc = 0.f;
+  for (int f = 0; f < a.feat; ++f) acc = fmaf(a.X[(size_t)row * a.feat + f], a.Yt[(size_t)col * a.feat + f], acc);
+  if (e < a.nnz) a.B[pos] = a.values[pos] * acc;
 }
 
-template <int T, bool PLAN>
-void launch_sddmm(const SddmmArgs& a, dim3 grid, hipStream_t stream) {
-  if (a.feat == 32 * T) hipLaunchKernelGGL((k_sddmm<T, true, PLAN>), grid, dim3(64 * kSddmmWaves), 0, stream, a);
-  else hipLaunchKernelGGL((k_sddmm<T, false, PLAN>), grid, dim3(64 * kSddmmWaves), 0, stream, a);
+template <bool PLAN, int T>
+void launch_stripes(const SddmmArgs& a, dim3 grid, hipStream_t stream) {
+  const dim3 block(64 * kSddmmWaves);
+  if (a.feat == 32 * T) hipLaunchKernelGGL((k_sddmm<T, kWhole, false, PLAN>), grid, block, 0, stream, a);
+  else if (a.feat % 4 == 0) hipLaunchKernelGGL((k_sddmm<T, kQuads, false, PLAN>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((k_sddmm<T, kTail, false, PLAN>), grid, block, 0, stream, a);
 }
 
+// grid: the workgroups of k_sddmm
 template <bool PLAN>
-void launch_sddmm_for_feat(const SddmmArgs& a, dim3 grid, hipStream_t stream) {
-  if (a.feat <= 32) launch_sddmm<1, PLAN>(a, grid, stream);
-  else if (a.feat <= 64) launch_sddmm<2, PLAN>(a, grid, stream);
-  else if (a.feat <= 128) launch_sddmm<4, PLAN>(a, grid, stream);
-  else if (a.feat <= 256) launch_sddmm<8, PLAN>(a, grid, stream);
-  else launch_sddmm<16, PLAN>(a, grid, stream);
+void launch_sddmm(const SddmmArgs& a, dim3 grid, hipStream_t stream) {
+  const dim3 block(64 * kSddmmWaves);
+  if (a.feat < 4) {
+    hipLaunchKernelGGL(k_sddmm_narrow<PLAN>, dim3((unsigned)((a.nnz + 255) / 256)), dim3(256), 0, stream, a);
+    return;
+  }
+  switch ((a.feat + 31) / 32) {
+    case 1: return launch_stripes<PLAN, 1>(a, grid, stream);
+    case 2: return launch_stripes<PLAN, 2>(a, grid, stream);
+    case 3: return launch_stripes<PLAN, 3>(a, grid, stream);
+    case 4: return launch_stripes<PLAN, 4>(a, grid, stream);
+    case 5: return launch_stripes<PLAN, 5>(a, grid, stream);
+    case 6: return launch_stripes<PLAN, 6>(a, grid, stream);
+    case 7: return launch_stripes<PLAN, 7>(a, grid, stream);
+    case 8: return launch_stripes<PLAN, 8>(a, grid, stream);
+    default:
+      if (a.feat % 4) hipLaunchKernelGGL((k_sddmm<8, kTail, true, PLAN>), grid, block, 0, stream, a);
+      else hipLaunchKernelGGL((k_sddmm<8, kQuads, true, PLAN>), grid, block, 0, stream, a);
+  }
 }
 
-bool vector_path_ok(const float* X, const float* Yt, int32_t feat) {
-  return feat % 4 == 0 && feat <= 512 && ((((uintptr_t)X) | ((uintptr_t)Yt)) & 15) == 0;
+// entries per wavefront in CSR order: short runs while there are few entries, so that every CU has 16 wavefronts
+int32_t csr_run(int64_t nnz) {
+  const int64_t chunks = nnz / (64 * 4096);
+  return 64 * (int32_t)std::min<int64_t>(kSddmmChunks, std::max<int64_t>(1, chunks));
 }
 
 // ------------------------------------------------------------------- plan
@@ -539,16 +604,12 @@ extern "C" sptir_status_t sptir_sddmm(const sptir_sddmm_plan_t* p, const float* 
   a.X = X; a.Yt = Yt; a.B = B_values; a.nnz = p->nnz; a.n_rows = p->n_rows; a.feat = feat;
   a.e_row = p->e_row; a.e_col = p->e_col; a.e_pos = p->e_pos;
   a.run_first_entry = p->run_first_entry; a.run_len = p->run_len; a.xcd_run_ptr = p->xcd_run_ptr;
-  const bool vec = vector_path_ok(X, Yt, feat);
+  a.run = csr_run(p->nnz);
   if (p->c == 1) {
-    const int64_t runs = (p->nnz + kSddmmRun - 1) / kSddmmRun;
-    dim3 grid((unsigned)((runs + kSddmmWaves - 1) / kSddmmWaves));
-    if (!vec) hipLaunchKernelGGL(k_sddmm_generic<false>, grid, dim3(64 * kSddmmWaves), 0, stream, a);
-    else launch_sddmm_for_feat<false>(a, grid, stream);
+    const int64_t runs = (p->nnz + a.run - 1) / a.run;
+    launch_sddmm<false>(a, dim3((unsigned)((runs + kSddmmWaves - 1) / kSddmmWaves)), stream);
   } else {
-    dim3 grid((unsigned)(8 * ((p->max_runs_per_xcd + kSddmmWaves - 1) / kSddmmWaves)));
-    if (!vec) hipLaunchKernelGGL(k_sddmm_generic<true>, grid, dim3(64 * kSddmmWaves), 0, stream, a);
-    else launch_sddmm_for_feat<true>(a, grid, stream);
+    launch_sddmm<true>(a, dim3((unsigned)(8 * ((p->max_runs_per_xcd + kSddmmWaves - 1) / kSddmmWaves))), stream);
   }
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;
@@ -570,13 +631,12 @@ extern "C" sptir_status_t sptir_sddmm_csr(const sptir_csr_t* csr, const float* X
   SddmmArgs a;
   a.indptr = csr->indptr; a.indices = csr->indices; a.values = csr->values;
   a.X = X; a.Yt = Yt; a.B = B_values; a.nnz = csr->nnz; a.n_rows = csr->n_rows; a.feat = feat;
-  const int64_t runs = (csr->nnz + kSddmmRun - 1) / kSddmmRun;
+  a.run = csr_run(csr->nnz);
+  const int64_t runs = (csr->nnz + a.run - 1) / a.run;
   dim3 grid((unsigned)((runs + kSddmmWaves - 1) / kSddmmWaves));
   hipStream_t stream = (hipStream_t)stream_;
   a.e_row = a.e_col = a.e_pos = nullptr; a.run_first_entry = nullptr; a.run_len = nullptr; a.xcd_run_ptr = nullptr;
-  if (!vector_path_ok(X, Yt, feat))
-    hipLaunchKernelGGL(k_sddmm_generic<false>, grid, dim3(64 * kSddmmWaves), 0, stream, a);
-  else launch_sddmm_for_feat<false>(a, grid, stream);
+  launch_sddmm<false>(a, grid, stream);
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;
 }

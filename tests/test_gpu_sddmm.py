@@ -180,3 +180,17 @@ def test_sddmm_plan_named_configs(gpu_lib, name):
     say(f"[sddmm plan config] {name}: c={info['n_col_parts']} runs={info['n_runs']} bytes={info['device_bytes']}")
     Br, Mr = oracle.sddmm_csr(w.n_rows, w.indptr, w.indices, w.values, Xr, w.X)
     assert_b_close(B, Br, Mr, name)
+
+
+@pytest.mark.parametrize("feat", [2, 5, 33, 63, 96, 160, 224, 257, 300])
+@pytest.mark.parametrize("gap", [0, 1, 90, 700])
+def test_sddmm_rows_of_a_chunk_and_row_ends(gpu_lib, gap, feat):
+    """Chunks of 64 entries inside one row, over rows of one entry, and over more than 64 rows at a time (`gap` empty rows
+    after each), with rows of X and Yt that end anywhere in a lane's four floats; in CSR order and with a plan."""
+    say(f"[sddmm rows] gap={gap} feat={feat}")
+    deg = np.concatenate([[200], np.tile(np.r_[[1], np.zeros(gap, dtype=int)], 150), [0, 63, 64, 65, 1, 1]])
+    w = workloads.random_csr(deg.size, 900, deg, feat + gap, feat)
+    Xr = left_operand(w, feat, 5)
+    Br, Mr = oracle.sddmm_csr(w.n_rows, w.indptr, w.indices, w.values, Xr, w.X)
+    assert_b_close(run_sddmm(gpu_lib, w, Xr, w.X), Br, Mr, f"gap={gap} feat={feat}")
+    assert_b_close(run_sddmm_plan(gpu_lib, w, Xr, w.X, 8)[0], Br, Mr, f"plan gap={gap} feat={feat}")
