@@ -125,9 +125,9 @@ __device__ __forceinline__ int count_not_above(int ascending, int v) {
 }
 
 // T float4 per lane cover 32*T floats of a row; wider rows (MANY) are taken 32*T floats at a time.  kWhole: that is the
-// row.  kQuads: lanes past its end drop what they read.  kTail: feat is no multiple of 4, and the lane that holds the end of
-// a row reads the row's last four floats and drops those its neighbour has.  No load is conditional: behind a branch
-// the compiler could not count the loads in flight and every wait would cover all of them.
+// row.  kQuads: lanes past its end read nothing.  kTail: feat is no multiple of 4, and the lane that holds the end of
+// a row reads the row's last four floats and drops those its neighbour has.  No other load is conditional: behind a branch
+// the compiler cannot count the loads in flight, and a wait covers all of them.
 // (The second launch bound tells the register allocator how many wavefronts per SIMD to leave room for; left
 //  alone it spreads the pipeline stages over 280+ registers although 16*T + 30 are live at any time.)
 enum RowEnd { kWhole, kQuads, kTail };
@@ -156,11 +156,13 @@ __global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(Sddm
     for (int t = 0; t < T; ++t) {
       const int f = f_base + 32 * t + 4 * fl;
       const int at = END == kWhole ? f : min(f, a.feat - 4);
+      if (END == kQuads && (MANY || t == T - 1) && f >= a.feat) {  // (few lanes left: their loads would cost L1 as much)
+        v[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+        continue;
+      }
       const float4u u = *reinterpret_cast<const float4u*>(row + at);
       v[t] = make_float4(u.x, u.y, u.z, u.w);
-      if constexpr (END == kQuads) {
-        if (f >= a.feat) v[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-      } else if constexpr (END == kTail) {
+      if constexpr (END == kTail) {
         const int drop = f - at;  // floats that belong to the lane below (4 and more: all of them)
         if (drop > 0) v[t].x = 0.f;
         if (drop > 1) v[t].y = 0.f;
@@ -187,6 +189,10 @@ __global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(Sddm
   int row_lo = 0, starts = 0;
   auto fetch_starts = [&](int row) { return a.indptr[min(row + 1 + lane, a.n_rows)]; };
   auto find_rows = [&](ChunkEntries& c) {
+    if (__builtin_amdgcn_readlane(starts, 0) > __builtin_amdgcn_readlane(c.pos, 63)) {  // still the same row
+      c.row = row_lo;
+      return;
+    }
     bool open = true;
     while (true) {  // (once, unless the chunk touches more than 64 rows)
       const int n = count_not_above(starts, c.pos);
