@@ -255,7 +255,8 @@ typedef struct sptir_launch_plan {
   int32_t parts_per_launch;  /* column partitions one chunk list sweeps */
   int32_t n_launches;        /* chunk-list launches per sweep when rounds == 0 */
   int32_t compact_stream;    /* 1: 8-byte records, 0: 12-byte records */
-  int32_t n_feature_tiles;   /* tiles of 32 (16 for feat <= 16) floats that Y is cut into */
+  int32_t n_feature_tiles;   /* tiles of 32 floats (16 for feat <= 16; 64 for some feat that are no multiple of 32; 128
+                              * with full_rows) that Y is cut into */
   int32_t tiles_per_sweep;   /* feature tiles one sweep over the launches covers */
   int32_t n_sweeps;
   int32_t rounds;            /* 1: the chunk lists run in rounds and Y is written once */

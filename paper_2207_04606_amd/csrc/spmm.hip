@@ -199,6 +199,9 @@ struct HybWalker {
   Sink sink;
   float acc[VEC];
   float next_acc[VEC];   // heavy lists: what a chunk holds of the piece after the one that ends in it
+  // queue chunks: a lane group of 16 or 32 lanes walks the queues of SUB steps in turn, each with a sum of its own
+  static constexpr bool kQueueAlone = UB == 8;
+  float queue_acc[kQueueAlone ? SUB : 1][VEC];
 
   __device__ __forceinline__ void fetch(int q, Fetched& f) const {
     q = q < n_quads ? q : n_quads - 1;
@@ -263,9 +266,9 @@ struct HybWalker {
       if constexpr (IDX32) {
         // column ids are below 2^24 here, so the 24-bit multiply-add is exact
         unsigned off = __umul24(col, row_bytes) + lane_bytes;
-        load_vec<VEC>(x[j], reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + off));
+        load_unaligned<VEC>(x[j], reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + off));
       } else {
-        load_vec<VEC>(x[j], reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) +
+        load_unaligned<VEC>(x[j], reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) +
                                                             (size_t)col * row_bytes + lane_bytes));
       }
     }
@@ -292,26 +295,27 @@ struct HybWalker {
       } else {
         read_ints(rows + first_slot(s), r);
       }
+      float (&sum)[VEC] = queue_acc[kQueueAlone ? sub : 0];
 #pragma unroll
       for (int j = 0; j < UB; ++j) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[e] = fmaf(v[j], x[j][e], acc[e]);
+        for (int e = 0; e < VEC; ++e) sum[e] = fmaf(v[j], x[j][e], sum[e]);
         if (slot_hands_over(r[j])) {  // (only entries carry the flag: the slots past the end of a queue do not)
-          sink(local_row(r[j]), true, acc);
+          sink(local_row(r[j]), true, sum);
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+          for (int e = 0; e < VEC; ++e) sum[e] = 0.f;
         }
       }
-      if constexpr (SUB == 1 && UB == 8) return;  // this lane group walks the queue alone: the sum stays in registers
-      // Any other shape meets the queue again in another lane group or step, so what has been summed of an
+      if constexpr (kQueueAlone) return;  // a lane group walks its queues alone: the sums stay in registers
+      // A lane group of four lanes meets the queue again in another lane group, so what has been summed of an
       // unfinished row is handed over now.  Lane groups that share the eight slots of a queue may hold
       // parts of the same row: they take turns.
       constexpr int kTurns = UB < 8 ? 8 / UB : 1;
 #pragma unroll
       for (int turn = 0; turn < kTurns; ++turn)
-        sink(local_row(r[UB - 1]), row_valid(r[UB - 1]) && (g & (kTurns - 1)) == turn, acc);
+        sink(local_row(r[UB - 1]), row_valid(r[UB - 1]) && (g & (kTurns - 1)) == turn, sum);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+      for (int e = 0; e < VEC; ++e) sum[e] = 0.f;
       return;
     }
     if constexpr (!Sink::kQueues) {
@@ -360,7 +364,11 @@ struct HybWalker {
 
   __device__ __forceinline__ void run() {
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) { acc[e] = 0.f; next_acc[e] = 0.f; }
+    for (int e = 0; e < VEC; ++e) {
+      acc[e] = 0.f; next_acc[e] = 0.f;
+#pragma unroll
+      for (int i = 0; i < (kQueueAlone ? SUB : 1); ++i) queue_acc[i][e] = 0.f;
+    }
     if (n_quads <= 0) return;
     // Quads 0 and 1 are requested at once and quad 0 is parked.  From then on, at the start of quad Q, quad Q+1
     // (requested a whole quad earlier, so long arrived: a load that is waited for too early stalls every load
@@ -449,8 +457,11 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
   const int rb_first = (int)(rb << a.log2_row_block);
   const int rows_here = min(row_block, a.n_rows - rb_first);
   const int g = lane / LG, fl = lane & (LG - 1);
-  const int f0 = (a.tile0 + tile_id) * S::kTile + fl * VEC;
-  const bool f_active = f0 < a.feat;
+  const int f_nominal = (a.tile0 + tile_id) * S::kTile + fl * VEC;
+  const bool f_active = f_nominal < a.feat;
+  // (where feat is no multiple of VEC, the last lane of a row takes the row's last VEC floats, of which the first `again`
+  //  are its neighbour's: it sums them too, but writes only its own)
+  const int f0 = min(f_nominal, a.feat - VEC), again = f_nominal - f0;
   const int wave_floats = row_block * S::kTile + W::kRingInts;
   float* tile = smem + wave * wave_floats;
   int* ring = reinterpret_cast<int*>(tile + row_block * S::kTile);
@@ -462,7 +473,7 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
     float init[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) init[e] = 0.f;
-    if (!UNIT && a.accumulate && f_active && r < rows_here) load_vec<VEC>(init, y0 + (size_t)r * (size_t)a.feat);
+    if (!UNIT && a.accumulate && f_active && r < rows_here) load_unaligned<VEC>(init, y0 + (size_t)r * (size_t)a.feat);
     store_vec<VEC>(tile + tile_index<VEC, LG>(r, fl), init);
   }
 
@@ -470,7 +481,7 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
   const int n_list = (int)(a.rb_chunk_ptr[rb + 1] - c0);  // a multiple of kChunksPerQuad
   const int f_read = f_active ? f0 : 0;  // lanes past the last feature read a valid address, never store
   W wk{a.X, a.stream + (size_t)c0 * (W::kArrays * kChunkSlots), n_list / kChunksPerQuad, lane, g, ring,
-       (unsigned)a.feat * 4u, (unsigned)f_read * 4u, TileSink<VEC, LG>{tile, fl}, {}, {}};
+       (unsigned)a.feat * 4u, (unsigned)f_read * 4u, TileSink<VEC, LG>{tile, fl}, {}, {}, {}};
   wk.run();
 
   // write the tile: a lane group per row, one 128-byte line per group
@@ -483,11 +494,17 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
         float before[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) before[e] = 0.f;
-        if (a.accumulate) load_vec<VEC>(before, y0 + (size_t)r * (size_t)a.feat);
+        if (a.accumulate) load_unaligned<VEC>(before, y0 + (size_t)r * (size_t)a.feat);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) out[e] = fmaf(v, out[e], before[e]);
       }
-      store_vec<VEC>(y0 + (size_t)r * (size_t)a.feat, out);
+      float* y = y0 + (size_t)r * (size_t)a.feat;
+      if (again == 0) store_unaligned<VEC>(y, out);
+      else {
+#pragma unroll
+        for (int e = 1; e < VEC; ++e)
+          if (e >= again) y[e] = out[e];
+      }
     }
   }
 }
@@ -534,8 +551,8 @@ __device__ __forceinline__ void heavy_workgroup(const HeavyArgs& a, unsigned bid
   const int64_t list = a.list0 + unit * kHybWaves + wave;
   const int g = lane / LG, fl = lane & (LG - 1);
   const int f_in_sweep = tile_id * S::kTile + fl * VEC;
-  const int f0 = a.feat0 + f_in_sweep;
-  const bool f_active = f0 < a.feat;
+  const bool f_active = a.feat0 + f_in_sweep < a.feat;
+  const int f0 = min(a.feat0 + f_in_sweep, a.feat - VEC);
   int* ring = reinterpret_cast<int*>(smem) + wave * W::kRingInts;
   const int64_t c0 = list * a.list_chunks;
   const int64_t left = a.n_chunks - c0;
@@ -543,7 +560,7 @@ __device__ __forceinline__ void heavy_workgroup(const HeavyArgs& a, unsigned bid
   const int f_read = f_active ? f0 : 0;  // lanes past the last feature read a valid address, never store
   W wk{a.X, a.stream + (size_t)(a.chunk0 + c0) * (W::kArrays * kChunkSlots), n_list / kChunksPerQuad, lane, g, ring,
        (unsigned)a.feat * 4u, (unsigned)f_read * 4u,
-       PartialSink<VEC, LG>{a.partial + f_in_sweep, __builtin_amdgcn_readfirstlane(a.first_slot[list]), f_active}, {}, {}};
+       PartialSink<VEC, LG>{a.partial + f_in_sweep, __builtin_amdgcn_readfirstlane(a.first_slot[list]), f_active}, {}, {}, {}};
   wk.run();
   sum_groups<VEC, LG>(wk.acc, S::kGroups);
   wk.sink(0, g == 0, wk.acc);
@@ -579,7 +596,7 @@ __global__ __launch_bounds__(256) void k_heavy_reduce(const int32_t* __restrict_
                                                       const float* __restrict__ row_val, float* Y, int32_t n_rows,
                                                       int32_t feat, int32_t feat0, int32_t width) {
   __shared__ float part_sum[SPLIT > 1 ? 256 * VEC : 1];
-  const int per_row = width / VEC;
+  const int per_row = (width + VEC - 1) / VEC;
   const int group = per_row * SPLIT;    // threads per row (at most 256: per_row <= 32 when SPLIT > 1)
   const int rows_per_wg = 256 / group;
   const int local = threadIdx.x;
@@ -624,17 +641,25 @@ __global__ __launch_bounds__(256) void k_heavy_reduce(const int32_t* __restrict_
   }
   if (!active || part != 0) return;
   const float scale = row_val ? row_val[r] : 1.f;  // (the heavy lists of a value-less stream sum rows of X only)
-  float* y = Y + (size_t)r * (size_t)feat + feat0 + f;
+  // (the partial sums of a row's last VEC floats, where feat is no multiple of VEC: the first `again` are its neighbour's)
+  const int f_here = min(feat0 + f, feat - VEC), again = feat0 + f - f_here;
+  float* y = Y + (size_t)r * (size_t)feat + f_here;
   float out[VEC];
-  load_vec<VEC>(out, y);
+  if (again == 0) {
+    load_unaligned<VEC>(out, y);
 #pragma unroll
-  for (int i = 0; i < VEC; ++i) out[i] = fmaf(scale, sum[i], out[i]);
-  store_vec<VEC>(y, out);
+    for (int i = 0; i < VEC; ++i) out[i] = fmaf(scale, sum[i], out[i]);
+    store_unaligned<VEC>(y, out);
+  } else {
+#pragma unroll
+    for (int i = 1; i < VEC; ++i)
+      if (i >= again) y[i] = fmaf(scale, sum[i], y[i]);
+  }
 }
 
-bool plan(int64_t n_units, int feat, const void* X, const void* Y, bool full_rows, Geometry* g) {
+bool plan(int64_t n_units, int feat, const void* X, const void* Y, const ListShape& lists, Geometry* g) {
   uintptr_t align = (uintptr_t)X | (uintptr_t)Y;
-  lane_shape(feat, (align & 15) == 0, (align & 7) == 0, full_rows, &g->vec, &g->lg);
+  lane_shape(feat, (align & 15) == 0, lists, &g->vec, &g->lg);
   int tf = g->vec * g->lg;
   g->n_tiles = (feat + tf - 1) / tf;
   return plan_tiles(n_units, g);
@@ -659,10 +684,10 @@ void with_flags(bool idx32, bool wide, F&& f) {
 template <bool UNIT, typename F>
 void with_shape(int vec, int lg, bool idx32, bool wide, F&& f) {
   if (vec == 4 && lg == 32) with_flags<4, 32, UNIT>(idx32, wide, f);
+  else if (vec == 4 && lg == 16) with_flags<4, 16, UNIT>(idx32, wide, f);
   else if (vec == 4 && lg == 8) with_flags<4, 8, UNIT>(idx32, wide, f);
   else if (vec == 4) with_flags<4, 4, UNIT>(idx32, wide, f);
-  else if (vec == 2) with_flags<2, 16, UNIT>(idx32, wide, f);
-  else with_flags<1, 32, UNIT>(idx32, wide, f);
+  else with_flags<1, 4, UNIT>(idx32, wide, f);
 }
 
 // calls f with the Variant that matches the lane geometry and the stream's record form
@@ -722,12 +747,29 @@ void launch_heavy(V, const Geometry& g, hipStream_t stream, const HeavyArgs& a) 
 
 }  // namespace
 
-// 8 lanes x 16 bytes (one 128-byte line of X per lane group) where size and alignment allow
-void lane_shape(int32_t feat, bool aligned16, bool aligned8, bool full_rows, int* vec, int* lg) {
-  if (full_rows && feat % 128 == 0 && aligned16) { *vec = 4; *lg = 32; }  // 32 lanes x 16 bytes: 512 bytes of a row
-  else if (feat % 4 == 0 && aligned16) { *vec = 4; *lg = feat <= 16 ? 4 : 8; }
-  else if (feat % 2 == 0 && aligned8) { *vec = 2; *lg = 16; }
-  else { *vec = 1; *lg = 32; }
+// 8 lanes x 16 bytes, one 128-byte piece of a row of X per lane group (16-byte accesses need 4-byte alignment only: on
+// 61,403 rows of 5 floats a dword a lane took 2.4 times as long); fewer than four features: a lane each.
+//
+// Rows that are no whole number of 128-byte lines: a piece of 128 bytes lies across two of them, so 8 lanes fetch nearly
+// every line twice, 16 lanes three lines for two (50,021 rows, 41 floats, 1.5 M non-zeros: 93 -> 53 us; 132,534 rows, 50
+// floats, 39.6 M: 1.12 -> 0.87 ms).  But 16 lanes make half as many wavefronts, each with twice as far to go: they are
+// taken where that does not leave the GPU waiting for the longest list -- in rounds, whose lists are about equally long;
+// with at least 5000 wavefronts (30,000 rows, 200 floats, 1.8 M: 301 -> 185 us; with 3750, 60,000 rows of 100 floats
+// lost 12 %); or with an X so far beyond an XCD's L2 (26 MB) that the lines fetched twice decide (169,343 rows, 41 floats, 2646
+// wavefronts: 115 -> 87 us).
+void lane_shape(int32_t feat, bool aligned16, const ListShape& lists, int* vec, int* lg) {
+  *vec = 4;
+  if (lists.full_rows && full_rows_fit(lists.log2_row_block) && feat % 128 == 0 && aligned16) {
+    *lg = 32;  // 32 lanes x 16 bytes: 512 bytes of a row
+  } else if (feat > 32 && feat % 32 != 0 && half_rows_fit(lists.log2_row_block) &&
+             (lists.rounds || lists.n_row_blocks * ((feat + 63) / 64) >= 5000 ||
+              lists.n_cols * feat >= 6500000)) {
+    *lg = 16;
+  } else if (feat >= 4) {
+    *lg = feat <= 16 ? 4 : 8;
+  } else {
+    *vec = 1; *lg = 4;
+  }
 }
 
 // Feature tiles per sweep over the launches of a call when every launch but the first reads back what the one
@@ -744,16 +786,17 @@ int tiles_per_sweep(int n_tiles, int tile_floats, int64_t n_rows, int n_launches
 }
 
 // Feature tiles per sweep of a call that runs in rounds: all of them while the part of X they cover stays within
-// half of the 256 MB memory-side cache (or sweep_kb kilobytes, if given), else groups of whole kPartialFeat (8 or 4 tiles of 32 floats), so that the
+// half of the 256 MB memory-side cache (or sweep_kb kilobytes, if given), else groups of one or two kPartialFeat, so that the
 // heavy pieces' partial sums follow the same sweeps.  (The largest graph at 256 features, X of 238 MB: one sweep
 // 5.54 ms, two sweeps of 128 features measured faster.)
 int round_tiles_per_sweep(int n_tiles, int tile_floats, int64_t n_cols, int sweep_kb) {
-  if (tile_floats * 4 != kPartialFeat || n_tiles <= 4) return n_tiles;
+  const int per_partial = kPartialFeat / tile_floats;
+  if (per_partial < 2 || n_tiles <= per_partial) return n_tiles;
   const double limit_mb = (double)(sweep_kb > 0 ? sweep_kb : 128 * 1024) / 1024.0;
   const double tile_mb = (double)n_cols * tile_floats * sizeof(float) / (1024.0 * 1024.0);
   if (tile_mb * n_tiles <= limit_mb) return n_tiles;
-  if (tile_mb * 8 <= limit_mb) return 8;
-  return 4;
+  if (tile_mb * 2 * per_partial <= limit_mb) return 2 * per_partial;
+  return per_partial;
 }
 
 // May the gather offsets of a launch be formed with the 24-bit multiply (column x bytes per row of X)?
@@ -800,9 +843,10 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   Geometry g;
   const int64_t n_units = ((int64_t)h->n_row_blocks + kHybWaves - 1) / kHybWaves;
   // (512-byte tiles only where a workgroup's Y tiles fit the CU's LDS: a caller who fixes large row blocks and
-  //  asks for full rows gets the 128-byte tiles)
-  static_assert(kHybWaves == 4, "full_rows_fit() counts four wavefronts per workgroup");
-  if (!plan(n_units, feat, X, Y, h->full_rows != 0 && full_rows_fit(h->log2_row_block), &g)) return SPTIR_ERR_OVERFLOW;
+  //  asks for full rows gets narrower tiles)
+  static_assert(kHybWaves == 4, "full_rows_fit() and half_rows_fit() count four wavefronts per workgroup");
+  const ListShape lists{h->rounds != 0, h->full_rows != 0, h->log2_row_block, h->n_row_blocks, h->n_cols};
+  if (!plan(n_units, feat, X, Y, lists, &g)) return SPTIR_ERR_OVERFLOW;
   SpmmArgs a;
   a.stream = h->stream;
   a.X = X; a.Y = Y; a.n_rows = h->n_rows; a.n_row_blocks = h->n_row_blocks; a.log2_row_block = h->log2_row_block;
@@ -840,7 +884,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   // lists went with the chunk lists' launch, only the sums remain to be added.
   auto heavy_sweeps = [&](int feat_begin, int feat_end, bool already_launched = false) -> sptir_status_t {
     if (h->n_heavy <= 0) return SPTIR_OK;
-    const bool y_vec4 = feat % 4 == 0 && ((uintptr_t)Y & 15) == 0;
+    const bool y_vec4 = feat >= 4;
     for (int feat0 = feat_begin; feat0 < feat_end; feat0 += kPartialFeat) {
       const int width = feat_end - feat0 < kPartialFeat ? feat_end - feat0 : kPartialFeat;
       HeavyArgs ha;
@@ -854,7 +898,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         with_variant(g.vec, g.lg, idx32_all, wide, unit, [&](auto v) { launch_heavy(v, gh, stream, ha); });
         if (timers) timers->mark(stream, LaunchTimers::kHeavy, 1);
       }
-      const int per_row = width / (y_vec4 ? 4 : 1);
+      const int per_row = y_vec4 ? (width + 3) / 4 : width;
       // few rows with heavy pieces: eight groups of threads share a row's partial sums
       const int split = (y_vec4 && (int64_t)h->n_heavy_rows * per_row < 32768) ? 8 : 1;
       const int rows_per_wg = 256 / (per_row * split);

@@ -9,21 +9,18 @@ namespace {
 
 template <int VEC> struct Vec;
 template <> struct Vec<4> { using type = float4; };
-template <> struct Vec<2> { using type = float2; };
 template <> struct Vec<1> { using type = float; };
 
 template <int VEC>
 __device__ __forceinline__ void load_vec(float (&x)[VEC], const float* p) {
   typename Vec<VEC>::type v = *reinterpret_cast<const typename Vec<VEC>::type*>(p);
   if constexpr (VEC == 4) { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
-  else if constexpr (VEC == 2) { x[0] = v.x; x[1] = v.y; }
   else { x[0] = v; }
 }
 
 template <int VEC>
 __device__ __forceinline__ void store_vec(float* p, const float (&x)[VEC]) {
   if constexpr (VEC == 4) *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
-  else if constexpr (VEC == 2) *reinterpret_cast<float2*>(p) = make_float2(x[0], x[1]);
   else *p = x[0];
 }
 

@@ -574,3 +574,28 @@ def test_spmm_and_sddmm_replay_in_a_hip_graph(gpu_lib):
         gpu_lib.sptir_sddmm(plan, d.values, Xl, X, B_eager)
         torch.cuda.synchronize()
         assert torch.equal(Y, Y_eager) and torch.equal(B, B_eager), f"replay {rep}"
+
+
+@pytest.mark.parametrize("n_rows,knobs", [
+    (1500, {"rounds": 1, "heavy_len": 40}), (1500, {"rounds": 1, "wide_stream": 1}), (1500, {"rounds": 1, "row_block": 256}),
+    (1500, {"rounds": 2, "heavy_len": 33}), (42000, {"rounds": 2, "row_block": 8, "parts_per_launch": 1})])
+@pytest.mark.parametrize("feat", [5, 17, 33, 63, 65, 129, 319])
+def test_rows_that_are_no_whole_number_of_lines(gpu_lib, n_rows, knobs, feat):
+    """Feature sizes whose last lanes move back over their neighbours' features, in tiles of 16, 32 and 64 floats (lists
+    in rounds or at least 5000 of them take the widest), from chunk lists, heavy lists and sums over several launches."""
+    sptir = gpu_lib
+    rng = np.random.default_rng(feat)
+    n_cols = 777
+    deg = rng.integers(0, 6, n_rows)
+    deg[[0, n_rows // 2, n_rows - 1]] = [n_cols, 300, 65]
+    w = workloads.random_csr(n_rows, n_cols, deg, feat, feat)
+    d = upload(w)
+    hyb = sptir.sptir_hyb_build_ex(n_rows, n_cols, d.indptr, d.indices, d.values, 3, 4, dict(knobs, feat_hint=feat))
+    Y = torch.full((n_rows * feat + 1,), float("nan"), device="cuda")[1:].view(n_rows, feat)   # 4-byte aligned only
+    Y2 = torch.full((n_rows, feat), float("nan"), device="cuda")
+    sptir.sptir_spmm(hyb, d.X, Y)
+    sptir.sptir_spmm(hyb, d.X, Y2)
+    Yr, Sr = oracle.spmm_csr(n_rows, w.indptr, w.indices, w.values, w.X)
+    assert_y_close(Y.cpu().numpy(), Yr, Sr, what="4-byte aligned Y")
+    assert_y_close(Y2.cpu().numpy(), Yr, Sr, what="aligned Y")
+    hyb.destroy()
