@@ -221,54 +221,31 @@ __global__ __launch_bounds__(kBuildBlock) void k_count(BuildShape s, const int32
   if (tid == 0) rem_nnz[(int64_t)p * s.NB + rb] = (int64_t)sum_nnz;
 }
 
-// ------------------------------------------------------------------- scatter
-struct ScatterArgs {
+// --------------------------------------------------------------------- place
+struct PlaceArgs {
   const int32_t* indptr;
-  const int32_t* indices;
-  const float* values;
   const int32_t* bound;        // piece boundaries (k_piece_bounds)
   const int32_t* counts;       // scanned: rank of the block's first piece of each bin
   const int64_t* rem_nnz;      // scanned
   const int64_t* bucket_row_ptr;
-  const int64_t* bucket_slot_ptr;
   const int32_t* rem_part_ptr;
   const int64_t* rem_nnz_base;   // [c] first remainder nnz of each partition
   int32_t* row_ids;
-  int32_t* cols;
-  float* vals;
   int64_t* rem_ptr;
   int32_t* row_len;  // [R+M] real (unpadded) length of every ELL row and remainder piece
   int32_t* piece_of; // [c][n_rows] position in row_ids of the piece of (row, partition), -1 where the piece is empty
-  int64_t R, S, M, T;
+  int64_t R, M, T;
 };
 
-__global__ __launch_bounds__(kBuildBlock) void k_scatter(BuildShape s, ScatterArgs a) {
+// Every piece finds its position in row_ids; the entries follow in k_copy, once the lists of the SpMM are known.
+__global__ __launch_bounds__(kBuildBlock) void k_place(BuildShape s, PlaceArgs a) {
   __shared__ int wave_cnt[kWaves][kMaxBins];
   __shared__ long long wave_sums[kWaves];
-  // the pieces of a wavefront, for the copy: slots before each piece, where it lies in the input, its real
-  // length, where it goes
-  __shared__ long long pre[kWaves][65];
-  __shared__ unsigned pre32[kWaves][65];
-  __shared__ long long piece_dst[kWaves][64];
-  __shared__ int piece_lo[kWaves][64], piece_len[kWaves][64];
   int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // The c workgroups that copy the pieces of one block of rows read the same cache lines of the input (a piece
-  // ends in the middle of a line, the next partition's starts there), so they are made neighbours in time and
-  // share an XCD: workgroup ids go round the 8 XCDs, hence ids b, b + 8, b + 16, .. take consecutive work numbers.
-  const long long n_work = (long long)gridDim.x, per_xcd = (n_work + 7) / 8;
-  long long work = (long long)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  // (when the grid is not a multiple of 8 the last XCDs have one workgroup less: the numbers past the end wrap
-  //  into the gaps those leave)
-  const int full = (int)(n_work & 7);  // XCDs that have per_xcd workgroups (0: all of them)
-  if (full != 0 && (int)(blockIdx.x & 7) >= full) work -= (int)(blockIdx.x & 7) - full;
-  int rb = (int)(work / s.c), p = (int)(work % s.c);
+  const int p = blockIdx.x / s.NB, rb = blockIdx.x % s.NB;
   if (tid < kWaves * kMaxBins) (&wave_cnt[0][0])[tid] = 0;
   if (blockIdx.x == 0 && tid == 0) a.rem_ptr[a.M] = a.T;
-  if (blockIdx.x == 0 && tid < kChunkSlots) {  // the spare entries past the end of the arrays
-    a.row_ids[a.R + a.M + tid] = 0;
-    a.cols[a.S + a.T + tid] = 0;
-    a.vals[a.S + a.T + tid] = 0.f;
-  }
+  if (blockIdx.x == 0 && tid < kChunkSlots) a.row_ids[a.R + a.M + tid] = 0;  // the spare entries past the end
   __syncthreads();
 
   int r = rb * kBuildBlock + tid;
@@ -295,92 +272,23 @@ __global__ __launch_bounds__(kBuildBlock) void k_scatter(BuildShape s, ScatterAr
   long long tot;
   long long nnz_before = block_exclusive_scan<long long>(my_nnz, wave_sums, &tot);
   // (block_exclusive_scan synchronises the workgroup, so wave_cnt is complete here)
-  // Lanes without a piece stay alive with width 0: the wide copies below need all 64 lanes.
-  int width = 0;
-  int64_t dst = 0;
+  if (r >= s.n_rows) return;
   int32_t where = -1;  // position of this piece in row_ids
   if (bin >= 0) {
     int before = 0;
     for (int wv = 0; wv < wave; ++wv) before += wave_cnt[wv][bin];
     int64_t q = (int64_t)a.counts[((int64_t)p * s.nb + bin) * s.NB + rb] + before + rank_in_wave;
     if (!is_rem) {
-      int64_t b = (int64_t)p * (s.k + 1) + bin;
-      width = 1 << bin;
-      where = (int32_t)(a.bucket_row_ptr[b] + q);
-      a.row_ids[where] = r;
-      a.row_len[where] = l;
-      dst = a.bucket_slot_ptr[b] + q * width;
+      where = (int32_t)(a.bucket_row_ptr[(int64_t)p * (s.k + 1) + bin] + q);
     } else {
       int64_t m = (int64_t)a.rem_part_ptr[p] + q;
-      int64_t t0 = a.rem_nnz_base[p] + a.rem_nnz[(int64_t)p * s.NB + rb] + nnz_before;
       where = (int32_t)(a.R + m);
-      a.row_ids[where] = r;
-      a.row_len[where] = l;
-      a.rem_ptr[m] = t0;
-      width = l;
-      dst = a.S + t0;
+      a.rem_ptr[m] = a.rem_nnz_base[p] + a.rem_nnz[(int64_t)p * s.NB + rb] + nnz_before;
     }
+    a.row_ids[where] = r;
+    a.row_len[where] = l;
   }
-  if (a.piece_of && r < s.n_rows) a.piece_of[(int64_t)p * s.n_rows + r] = where;
-  // ---- the copy.  The pieces of a wavefront, `width` slots each (real entries, then pads: a pad repeats the last
-  // real column and holds +0.0f), form one sequence; every step the 64 lanes take 64 consecutive slots of it, so
-  // that lanes are busy whatever the lengths of the pieces and neighbouring lanes touch neighbouring addresses.
-  long long inc = width;
-  for (int d = 1; d < 64; d <<= 1) {
-    const long long t = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += t;
-  }
-  if (lane == 0) { pre[wave][0] = 0; pre32[wave][0] = 0; }
-  pre[wave][lane + 1] = inc;
-  pre32[wave][lane + 1] = (unsigned)inc;
-  piece_lo[wave][lane] = lo; piece_len[wave][lane] = l; piece_dst[wave][lane] = dst;
-  __syncthreads();
-  const long long total = pre[wave][64];
-  const int32_t* __restrict__ indices = a.indices;
-  const float* __restrict__ values = a.values;
-  int32_t* __restrict__ cols = a.cols;
-  float* __restrict__ vals = a.vals;
-  if (total >= 0x7FFFFFFFll) {
-    // (a wavefront with 2^31 slots or more: piece after piece, the 32-bit positions below do not reach)
-    for (int i = 0; i < 64; ++i) {
-      const long long width_i = pre[wave][i + 1] - pre[wave][i];
-      const int len_i = piece_len[wave][i];
-      for (long long j = lane; j < width_i; j += 64) {
-        const long long src = piece_lo[wave][i] + (j < len_i ? j : (long long)len_i - 1);
-        cols[piece_dst[wave][i] + j] = indices[src];
-        vals[piece_dst[wave][i] + j] = j < len_i ? values[src] : 0.0f;
-      }
-    }
-    return;
-  }
-  constexpr int kUnroll = 4;
-  const unsigned total32 = (unsigned)total;
-  for (unsigned f0 = 0; f0 < total32; f0 += 64 * kUnroll) {
-    int32_t col[kUnroll];
-    float val[kUnroll];
-    long long at[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const unsigned f = f0 + u * 64 + lane;
-      at[u] = -1; col[u] = 0; val[u] = 0.f;
-      if (f < total32) {
-        int i = 0;  // the piece with pre[i] <= f < pre[i + 1]
-#pragma unroll
-        for (int step = 32; step > 0; step >>= 1)
-          if (pre32[wave][i + step] <= f) i += step;
-        const int j = (int)(f - pre32[wave][i]);
-        const int len_i = piece_len[wave][i];
-        const bool real = j < len_i;
-        const long long src = (long long)piece_lo[wave][i] + (real ? j : len_i - 1);
-        col[u] = indices[src];
-        val[u] = real ? values[src] : 0.0f;
-        at[u] = piece_dst[wave][i] + j;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      if (at[u] >= 0) { cols[at[u]] = col[u]; vals[at[u]] = val[u]; }
-  }
+  a.piece_of[(int64_t)p * s.n_rows + r] = where;
 }
 
 // ------------------------------------------------------- SpMM work-item list
@@ -445,92 +353,126 @@ __global__ void k_cell_bounds(CellShape cs, const int64_t* __restrict__ bucket_r
 __device__ __forceinline__ int cells_per_part(const CellShape& cs) { return cs.nb + 1; }
 __device__ __forceinline__ int cells_per_group(const CellShape& cs) { return cs.ppg * (cs.nb + 1) + 1; }
 
-struct PiecePlace {     // where the entries of a queued row piece go (len 0: the piece is not queued)
-  uint32_t slot0;       // its first slot in the fused (cols, vals) arrays (fewer than 2^32: at most 2 * nnz)
-  int32_t first_chunk;  // first chunk of the queue cell
-  int32_t where;        // position of its first entry in the queue | queue << 28
-  int32_t len;          // real entries
-};
-static_assert(sizeof(PiecePlace) == 16, "PiecePlace must stay 16 bytes");
-constexpr uint32_t kChunkIsQueue = 1u << 14;
-
 __device__ __forceinline__ int chunks_of_length(int len) { return (len + kChunkSlots - 1) / kChunkSlots; }
 inline int64_t chunks_of_slots(int64_t slots) { return (slots + kChunkSlots - 1) / kChunkSlots; }
 
-// Walks the row pieces of partition p in row block rb and tells the visitor what becomes of each:
-//   (pieces of more than cs.long_len entries are not part of the lists: the heavy-piece launch sums them)
-//   v.on_wide(bin, q, len)                 cut into 64-entry chunks
-//   v.on_queued(bin, q, len, g, start)     entries start .. start + len - 1 of queue g
-//   v.on_dealt(load, chunks)               at the end: entries per queue, chunks of the queue cell
-// and returns the chunks of the queue cell.
-template <typename Visitor>
-__device__ __forceinline__ int deal_partition(const CellShape& cs, const int32_t* __restrict__ bin_rb_ptr,
-                                              const int32_t* __restrict__ row_len, int p, int rb, Visitor& v) {
-  const int64_t per_bin = (int64_t)cs.n_rb + 1;
-  long long to_deal = 0;  // entries not dealt yet
-  for (int bin = 0; bin < cs.nb; ++bin) {
-    const int32_t* ptr = bin_rb_ptr + ((int64_t)p * cs.nb + bin) * per_bin + rb;
-    for (int32_t q = ptr[0]; q < ptr[1]; ++q) {
-      const int len = row_len[q];
-      if (len <= cs.long_len) to_deal += len;
-    }
-  }
-  int load[8];
-#pragma unroll
-  for (int g = 0; g < 8; ++g) load[g] = 0;
-  for (int bin = cs.nb - 1; bin >= 0; --bin) {
-    const int32_t* ptr = bin_rb_ptr + ((int64_t)p * cs.nb + bin) * per_bin + rb;
-    for (int32_t q = ptr[0]; q < ptr[1]; ++q) {
-      const int len = row_len[q];
-      if (len > cs.long_len) continue;
-      const long long share = (to_deal + 7) >> 3;
-      to_deal -= len;
-      if (len > kChunkSlots && len > share) { v.on_wide(bin, q, len); continue; }
-      int best = 0, best_load = load[0];
-#pragma unroll
-      for (int g = 1; g < 8; ++g)
-        if (load[g] < best_load) { best_load = load[g]; best = g; }
-      v.on_queued(bin, q, len, best, best_load);
-#pragma unroll
-      for (int g = 0; g < 8; ++g) load[g] += (g == best) ? len : 0;
-    }
-  }
-  int longest = 0;
-#pragma unroll
-  for (int g = 0; g < 8; ++g) longest = max(longest, load[g]);
-  const int chunks = (longest + 7) >> 3;
-  v.on_dealt(load, chunks);
-  return chunks;
+// What becomes of a piece of at most long_len entries, one word per piece (in the order of row_ids):
+//   queued    its first entry's position in the queue (bits 0..27) and the queue (28..30)
+//   cut wide  bit 31 and the chunks of the pieces before it in its bin's cell
+constexpr uint32_t kWidePiece = 0x80000000u;
+
+__device__ __forceinline__ unsigned min_of_8(unsigned v) {  // over the eight lanes of a lane group
+  v = min(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));   // quad_perm 1 0 3 2
+  v = min(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));   // quad_perm 2 3 0 1
+  return min(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));  // row_half_mirror
 }
 
-// One thread per (group, partition of its phase): chunk counts of that partition's cells.
-struct CountVisitor {
-  long long* cell;  // the partition's nb + 1 counts
-  __device__ void on_wide(int bin, int32_t, int len) { cell[bin] += chunks_of_length(len); }
-  __device__ void on_queued(int, int32_t, int, int, int) {}
-  __device__ void on_dealt(const int (&)[8], int) {}
-};
-
-__global__ void k_part_chunk_counts(CellShape cs, int64_t n_parts, const int32_t* __restrict__ bin_rb_ptr,
-                                    const int32_t* __restrict__ row_len, long long* cell_chunks) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_parts) return;
+// Eight lanes per (group, partition of its phase), one per queue.  The lengths are fetched side by side into LDS first;
+// what remains serial, a piece after the other to the shortest queue, runs on registers.  (A thread per partition that
+// read a length at a time, once to count and once more to fill, took 35 + 93 us on 169,343 rows; this takes 9.)
+// Writes the chunk counts of the partition's cells, a word per piece (see above) and the entries of every queue.
+constexpr int kDealParts = 32;  // partitions per workgroup
+__global__ __launch_bounds__(256) void k_deal(CellShape cs, int64_t n_parts, const int32_t* __restrict__ bin_rb_ptr,
+                                              const int32_t* __restrict__ row_len, long long* __restrict__ cell_chunks,
+                                              uint32_t* __restrict__ dealt, int32_t* __restrict__ queue_len) {
+  extern __shared__ int piece_len[];                 // [kDealParts][rows of a row block]
+  __shared__ int before[kDealParts][kMaxBins + 1];   // pieces before a bin, widest bin first
+  __shared__ int first[kDealParts][kMaxBins];        // first piece of a bin
+  __shared__ int wide[kDealParts][kMaxBins];         // chunks cut wide so far
+  const int l = threadIdx.x & 7, part = threadIdx.x >> 3;
+  const int64_t t = (int64_t)blockIdx.x * kDealParts + part;
   const int64_t grp = t / cs.ppg;
   const int p_local = (int)(t % cs.ppg);
   const int rb = (int)(grp % cs.n_rb), phase = (int)(grp / cs.n_rb);
   const int p = phase * cs.ppg + p_local;
-  long long* cell = cell_chunks + grp * cells_per_group(cs) + (int64_t)p_local * cells_per_part(cs);
-  for (int i = 0; i <= cs.nb; ++i) cell[i] = 0;
-  if (p >= cs.c) return;  // a partition past the last one
-  CountVisitor v{cell};
-  cell[cs.nb] = deal_partition(cs, bin_rb_ptr, row_len, p, rb, v);
+  const bool real = t < n_parts && p < cs.c;  // (the last phase may have fewer partitions)
+  int* len_of = piece_len + (part << cs.log2_rb);
+
+  int count[kMaxBins / 8], mine = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxBins / 8; ++i) {
+    const int at = l * (kMaxBins / 8) + i, bin = cs.nb - 1 - at;
+    count[i] = 0;
+    if (real && bin >= 0) {
+      const int32_t* ptr = bin_rb_ptr + ((int64_t)p * cs.nb + bin) * ((int64_t)cs.n_rb + 1) + rb;
+      first[part][at] = ptr[0];
+      count[i] = ptr[1] - ptr[0];
+    }
+    mine += count[i];
+    wide[part][at] = 0;
+  }
+  int sum = mine;
+#pragma unroll
+  for (int d = 1; d < 8; d <<= 1) {
+    const int o = __shfl_up(sum, d, 8);
+    if (l >= d) sum += o;
+  }
+  int at0 = sum - mine;
+#pragma unroll
+  for (int i = 0; i < kMaxBins / 8; ++i) {
+    before[part][l * (kMaxBins / 8) + i] = at0;
+    at0 += count[i];
+  }
+  if (l == 7) before[part][kMaxBins] = at0;
+  __syncthreads();
+  const int n = before[part][kMaxBins];
+  auto piece = [&](int i) {  // position in row_ids of the i-th piece to deal
+    int b = 0;  // the last bin that starts at or before i
+#pragma unroll
+    for (int step = kMaxBins / 2; step > 0; step >>= 1)
+      if (before[part][b + step] <= i) b += step;
+    return first[part][b] + (i - before[part][b]);
+  };
+  long long to_deal = 0;  // entries not dealt yet
+  for (int i = l; i < n; i += 8) {
+    const int len = row_len[piece(i)];
+    len_of[i] = len;
+    if (len <= cs.long_len) to_deal += len;
+  }
+#pragma unroll
+  for (int d = 1; d < 8; d <<= 1) to_deal += __shfl_xor(to_deal, d, 8);
+  __syncthreads();
+
+  unsigned load = 0;  // entries of queue l
+  int len = n > 0 ? len_of[0] : 0;
+  for (int i = 0; i < n; ++i) {
+    const int next = len_of[i + 1 < n ? i + 1 : i];
+    if (len <= cs.long_len) {
+      const long long share = (to_deal + 7) >> 3;
+      to_deal -= len;
+      uint32_t word;
+      if (len > kChunkSlots && len > share) {
+        const int at = cs.nb - 1 - bin_of_length(len, cs.k);
+        const int w = wide[part][at];
+        if (l == 0) wide[part][at] = w + chunks_of_length(len);
+        word = kWidePiece | (uint32_t)w;
+      } else {
+        const unsigned best = min_of_8(load * 8 + l);  // of equally short queues the first
+        word = (best >> 3) | ((best & 7u) << 28);
+        if ((best & 7u) == (unsigned)l) load += (unsigned)len;
+      }
+      if (l == 0) len_of[i] = (int)word;
+    }
+    len = next;
+  }
+  unsigned longest = load;
+#pragma unroll
+  for (int d = 1; d < 8; d <<= 1) longest = max(longest, (unsigned)__shfl_xor((int)longest, d, 8));
+  __syncthreads();
+  for (int i = l; i < n; i += 8) dealt[piece(i)] = (uint32_t)len_of[i];  // (a heavy piece's word is not looked at)
+  if (t < n_parts) {
+    long long* cell = cell_chunks + grp * cells_per_group(cs) + (int64_t)p_local * cells_per_part(cs);
+    for (int bin = l; bin < cs.nb; bin += 8) cell[bin] = wide[part][cs.nb - 1 - bin];
+    if (l == 0) cell[cs.nb] = (longest + 7) >> 3;
+    queue_len[t * 8 + l] = (int32_t)load;
+  }
 }
 
-// One thread per (phase, row block) group: the pad cell gets what is missing to a multiple of kChunksPerQuad,
-// the group's counts become their exclusive prefix inside the group, group_total[grp] their sum.
+// One wavefront per (phase, row block) group: its cells' counts become their exclusive prefix inside the group (the pad
+// cell's is then the number of chunks before the padding), group_total[grp] the group's chunks, a multiple of
+// kChunksPerQuad.
 __global__ __launch_bounds__(256) void k_group_scan(CellShape cs, int64_t n_groups, long long* cell_chunks,
-                                                    long long* group_total, unsigned long long* longest) {
-  // one wavefront per group: an exclusive scan over the group's cells, 64 at a time
+                                                    long long* group_total) {
   const int64_t grp = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (grp >= n_groups) return;
   const int lane = threadIdx.x & 63;
@@ -546,15 +488,9 @@ __global__ __launch_bounds__(256) void k_group_scan(CellShape cs, int64_t n_grou
   }
   if (lane == 0) {
     c[cpg - 1] = carry;
-    const long long padded = carry + (kChunksPerQuad - carry % kChunksPerQuad) % kChunksPerQuad;
-    group_total[grp] = padded;
-    // the longest list (the sort of the launch order needs to know how many digits can differ)
-    // (one of kFlagSlots counters, for the reason given there; the report takes their maximum)
-    if (padded > 0) atomicMax(longest + (grp & (kFlagSlots - 1)) * kFlagStride, (unsigned long long)padded);
+    group_total[grp] = (carry + kChunksPerQuad - 1) / kChunksPerQuad * kChunksPerQuad;
   }
 }
-
-constexpr int kGroupSeq = 1024;  // groups per sequence of the two-level scan over group totals
 
 // ------------------------------------------------------------ chunk stream
 // What the SpMM kernel actually reads: the chunks as fixed records, in list
@@ -592,202 +528,38 @@ __device__ __forceinline__ void put_slot(const StreamShape& ss, int64_t chunk, i
   if (!ss.compact) quad[(n_arrays - 1) * kQuadSlots + at] = row_word;
 }
 
-// entry e of a queued piece
-__device__ __forceinline__ void put_queue_entry(const StreamShape& ss, int64_t first_chunk, int where, int e,
-                                                int32_t col, float val, int32_t row, bool last) {
-  const int pos = (where & 0x0FFFFFFF) + e, g = (where >> 28) & 7;
-  const int local_row = row & ((1 << ss.log2_rb) - 1);
-  int32_t col_word, row_word = 0;
-  if (ss.compact) {
-    const uint32_t col_rel = (uint32_t)(col - (col / ss.phase_width) * ss.phase_width);
-    col_word = (int32_t)(col_rel | ((uint32_t)local_row << kCompactColBits) | (1u << 27) | (3u << 28) |
-                         ((uint32_t)last << 31));
-  } else {
-    col_word = col;
-    row_word = local_row | (3 << 16) | ((int)last << 22);
-  }
-  put_slot(ss, first_chunk + (pos >> 3), g * 8 + (pos & 7), col_word, __float_as_int(val), row_word);
-}
-
-// One thread per (group, partition): writes the chunk descriptors the counts above announced, the place of
-// every queued piece, and the slots past the end of each queue.
-struct FillVisitor {
-  const CellShape& cs;
-  const StreamShape& ss;
-  int p;
-  int64_t first_chunk;          // of the partition's first cell
-  const long long* cell;        // scanned counts: chunks of this group before each of the partition's cells ...
-  long long cell0;              // ... minus those before its first cell
-  const int32_t* row_ids;
-  const int64_t* bucket_row_ptr;
-  const int64_t* bucket_slot_ptr;
-  const int64_t* rem_ptr;
-  int64_t S;
-  Chunk* chunks;
-  PiecePlace* place;
-  int wide_bin;                 // bin whose wide rows are being written, and the next free chunk of its cell
-  int64_t wide_it;
-
-  __device__ int64_t cell_first(int i) const { return first_chunk + (cell[i] - cell0); }
-  __device__ int64_t slot_of(int bin, int32_t q) const {
-    if (bin <= cs.k) {
-      const int64_t b = (int64_t)p * (cs.k + 1) + bin;
-      return bucket_slot_ptr[b] + (((int64_t)q - bucket_row_ptr[b]) << bin);
-    }
-    return S + rem_ptr[q - cs.R];
-  }
-  __device__ void on_wide(int bin, int32_t q, int len) {
-    if (bin != wide_bin) { wide_bin = bin; wide_it = cell_first(bin); }
-    const int64_t slot0 = slot_of(bin, q);
-    for (int off = 0; off < len; off += kChunkSlots) {
-      Chunk ck;
-      ck.slot0 = slot0 + off; ck.row0 = q;
-      const int count = len - off < kChunkSlots ? len - off : kChunkSlots;
-      ck.meta = (uint32_t)kRowLog2W | ((uint32_t)count << 6) | (off + kChunkSlots >= len ? (1u << 13) : 0u);
-      chunks[wide_it++] = ck;
-    }
-  }
-  __device__ void on_queued(int bin, int32_t q, int len, int g, int start) {
-    PiecePlace pl;
-    pl.slot0 = (uint32_t)slot_of(bin, q); pl.first_chunk = (int32_t)cell_first(cs.nb);
-    pl.where = start | (g << 28); pl.len = len;
-    place[q] = pl;
-  }
-  __device__ void on_dealt(const int (&load)[8], int n_chunks) {
-    const int64_t first = cell_first(cs.nb);
-    for (int i = 0; i < n_chunks; ++i) {  // the slots of a queue chunk are written piece by piece, not from here
-      Chunk ck;
-      ck.slot0 = 0; ck.row0 = 0;
-      ck.meta = 3u | ((uint32_t)kChunkSlots << 6) | kChunkIsQueue;
-      chunks[first + i] = ck;
-    }
-#pragma unroll
-    for (int g = 0; g < 8; ++g)  // past the end of a queue: zeros that belong to no row
-      for (int pos = load[g]; pos < 8 * n_chunks; ++pos)
-        put_slot(ss, first + (pos >> 3), g * 8 + (pos & 7), ss.compact ? (int32_t)(3u << 28) : 0, 0,
-                 (3 << 16) | (1 << 23));
-  }
-};
-
-__global__ void k_part_fill_chunks(CellShape cs, StreamShape ss, int64_t n_parts,
-                                   const int32_t* __restrict__ bin_rb_ptr,
-                                   const long long* __restrict__ cell_first_chunk,
-                                   const long long* __restrict__ group_first_chunk,
-                                   const long long* __restrict__ seq_first_chunk,
-                                   const int32_t* __restrict__ row_len, const int32_t* __restrict__ row_ids,
-                                   const int64_t* __restrict__ bucket_row_ptr,
-                                   const int64_t* __restrict__ bucket_slot_ptr, const int64_t* __restrict__ rem_ptr,
-                                   int64_t S, Chunk* chunks, PiecePlace* place, int64_t* rb_chunk_ptr,
-                                   int64_t n_chunks_total) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Eight lanes per (group, partition): the slots past the end of each queue; the first partition of a group also writes
+// the chunks that round the group up to whole quads, and rb_chunk_ptr.
+__global__ __launch_bounds__(256) void k_list_ends(CellShape cs, StreamShape ss, int64_t n_parts,
+                                                   const long long* __restrict__ cell_first_chunk,
+                                                   const long long* __restrict__ group_first_chunk,
+                                                   const int32_t* __restrict__ queue_len, int64_t* rb_chunk_ptr,
+                                                   int64_t n_chunks_total) {
+  const int l = threadIdx.x & 7;
+  const int64_t t = (int64_t)blockIdx.x * (blockDim.x >> 3) + (threadIdx.x >> 3);
   if (t >= n_parts) return;
   const int64_t grp = t / cs.ppg;
   const int p_local = (int)(t % cs.ppg);
-  const int rb = (int)(grp % cs.n_rb), phase = (int)(grp / cs.n_rb);
-  const int p = phase * cs.ppg + p_local;
-  const long long* cell = cell_first_chunk + grp * cells_per_group(cs) + (int64_t)p_local * cells_per_part(cs);
-  const int64_t group_first = group_first_chunk[grp] + seq_first_chunk[grp / kGroupSeq];
-  if (p_local == 0) rb_chunk_ptr[(int64_t)phase * cs.n_rb + rb] = group_first;
-  if (grp == 0 && p_local == 0) rb_chunk_ptr[(int64_t)cs.n_phases * cs.n_rb] = n_chunks_total;
-  if (p >= cs.c) return;
-  FillVisitor v{cs, ss, p, group_first + cell[0], cell, cell[0], row_ids, bucket_row_ptr, bucket_slot_ptr, rem_ptr, S,
-                chunks, place, -1, 0};
-  deal_partition(cs, bin_rb_ptr, row_len, p, rb, v);
-}
-
-// One lane per row piece, 64 pieces per wavefront: the entries of the wavefront's queued pieces form one
-// sequence of which every step the lanes take 64 consecutive ones (as in k_scatter), each going to its place in
-// its queue.
-__global__ __launch_bounds__(256) void k_pack_pieces(int64_t n_pieces, StreamShape ss,
-                                                     const PiecePlace* __restrict__ place,
-                                                     const int32_t* __restrict__ row_ids,
-                                                     const int32_t* __restrict__ cols,
-                                                     const float* __restrict__ vals) {
-  __shared__ int pre[4][65];
-  __shared__ PiecePlace pl_of[4][64];
-  __shared__ int32_t row_of[4][64];
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  PiecePlace pl;
-  pl.slot0 = 0; pl.first_chunk = 0; pl.where = 0; pl.len = 0;
-  int32_t row = 0;
-  if (q < n_pieces) { pl = place[q]; row = row_ids[q]; }
-  int inc = pl.len;
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += t;
-  }
-  if (lane == 0) pre[wave][0] = 0;
-  pre[wave][lane + 1] = inc;
-  pl_of[wave][lane] = pl;
-  row_of[wave][lane] = row;
-  __syncthreads();
-  const int total = pre[wave][64];
-  constexpr int kUnroll = 4;
-  for (int f0 = 0; f0 < total; f0 += 64 * kUnroll) {
-    int32_t col[kUnroll];
-    float val[kUnroll];
-    int piece[kUnroll], e[kUnroll];
+  const long long* cells = cell_first_chunk + grp * cells_per_group(cs);
+  const int64_t group_first = group_first_chunk[grp];
+  const long long* queue_cell = cells + (int64_t)p_local * cells_per_part(cs) + cs.nb;
+  const int load = queue_len[t * 8 + l];
+  const int64_t chunk0 = group_first + queue_cell[0];
+  const int n_chunks = (int)(queue_cell[1] - queue_cell[0]);
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int f = f0 + u * 64 + lane;
-      piece[u] = -1; e[u] = 0; col[u] = 0; val[u] = 0.f;
-      if (f < total) {
-        int i = 0;  // the piece with pre[i] <= f < pre[i + 1]
-#pragma unroll
-        for (int step = 32; step > 0; step >>= 1)
-          if (pre[wave][i + step] <= f) i += step;
-        piece[u] = i;
-        e[u] = f - pre[wave][i];
-        const int64_t src = (int64_t)pl_of[wave][i].slot0 + e[u];
-        col[u] = cols[src];
-        val[u] = ss.unit ? 0.f : vals[src];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      if (piece[u] >= 0) {
-        const PiecePlace& w = pl_of[wave][piece[u]];
-        put_queue_entry(ss, w.first_chunk, w.where, e[u], col[u], val[u], row_of[wave][piece[u]], e[u] == w.len - 1);
-      }
+  for (int g = 0; g < 8; ++g) {
+    const int from = __shfl(load, g, 8);
+    for (int ck = from >> 3; ck < n_chunks; ++ck)  // zeros that belong to no row
+      if (ck * 8 + l >= from)
+        put_slot(ss, chunk0 + ck, g * 8 + l, ss.compact ? (int32_t)(3u << 28) : 0, 0, (3 << 16) | (1 << 23));
   }
-}
-
-// One wavefront per chunk of a wide row (and per padding chunk of a group); reads the canonical arrays
-// through the descriptor.  Queue chunks are written by k_pack_pieces and k_part_fill_chunks.
-__global__ __launch_bounds__(256) void k_pack_stream(int64_t n_chunks, StreamShape ss,
-                                                     const Chunk* __restrict__ chunks,
-                                                     const int32_t* __restrict__ row_ids,
-                                                     const int32_t* __restrict__ cols,
-                                                     const float* __restrict__ vals) {
-  int64_t q = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (q >= n_chunks) return;
-  int lane = threadIdx.x & 63;
-  const Chunk ck = chunks[q];
-  if (ck.meta & kChunkIsQueue) return;
-  const int lw = (int)(ck.meta & 63u), count = (int)((ck.meta >> 6) & 127u);
-  if (count == 0) {  // padding of a group: contributes nothing, hands nothing over
-    put_slot(ss, q, lane, ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
-    return;
-  }
-  const int hand_over = (int)((ck.meta >> 13) & 1u);
-  const int o = lane < count ? lane : count - 1;
-  const int64_t src = ck.slot0 + o;
-  const int32_t rid = row_ids[ck.row0 + (o >> lw)];
-  const bool real = lane < count;
-  const int32_t col = cols[src];
-  const float val = vals[src];
-  const int local_row = rid & ((1 << ss.log2_rb) - 1);
-  if (ss.compact) {
-    const uint32_t col_rel = (uint32_t)(col - (col / ss.phase_width) * ss.phase_width);
-    put_slot(ss, q, lane,
-             (int32_t)(col_rel | ((uint32_t)local_row << kCompactColBits) | ((uint32_t)real << 27) |
-                       ((uint32_t)(lw > 6 ? 7 : lw) << 28) | ((uint32_t)hand_over << 31)),
-             real ? __float_as_int(val) : 0, 0);
-  } else {
-    put_slot(ss, q, lane, col, real ? __float_as_int(val) : 0,
-             real ? (local_row | (lw << 16) | (hand_over << 22)) : -1);
-  }
+  if (p_local != 0) return;
+  const int64_t used = cells[cells_per_group(cs) - 1];
+  for (int64_t ck = used; ck % kChunksPerQuad != 0; ++ck)  // contribute nothing, hand nothing over
+    for (int i = l; i < kChunkSlots; i += 8)
+      put_slot(ss, group_first + ck, i, ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
+  if (l == 0) rb_chunk_ptr[grp] = group_first;
+  if (l == 0 && grp == 0) rb_chunk_ptr[n_parts / cs.ppg] = n_chunks_total;
 }
 
 // ------------------------------------------------------------ heavy pieces
@@ -795,57 +567,82 @@ __global__ __launch_bounds__(256) void k_pack_stream(int64_t n_chunks, StreamSha
 // the order of row_ids (buckets in bucket order, then the remainder: partition-major), which is cut into 64-slot
 // chunks.  When heavy_len >= kChunkSlots the pieces follow each other without a gap (a chunk then holds the end
 // of at most one piece, which is what the kernel can hand over per chunk); shorter heavy pieces each start a
-// chunk of their own.  Exclusive prefixes over the pieces:
-//   unit_before[q]  heavy pieces before piece q
-//   hent_before[q]  slots of the heavy sequence before piece q
-// Both arrays have one element more than there are pieces, so that after the scan the last one is the total.
-// *heavy_nnz receives the real entries of all heavy pieces.
+// chunk of their own.
 __device__ __forceinline__ int heavy_footprint(int len, int heavy_len) {
   return heavy_len >= kChunkSlots ? len : chunks_of_length(len) * kChunkSlots;
 }
 
-__global__ void k_heavy_counts(int64_t n_pieces, const int32_t* __restrict__ row_len, int32_t heavy_len,
-                               int32_t* unit_before, int32_t* hent_before, unsigned long long* heavy_nnz) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int len = q < n_pieces ? row_len[q] : 0;
-  const bool heavy = len > heavy_len;
-  if (q <= n_pieces) {
-    unit_before[q] = heavy ? 1 : 0;
-    hent_before[q] = heavy ? heavy_footprint(len, heavy_len) : 0;
+// Heavy pieces are numbered, and given their slots, by an exclusive scan over all pieces: sums over kHeavySpan pieces,
+// their scan (k_totals), then the numbers of the heavy pieces themselves (k_heavy_units).
+constexpr int kHeavyPerThread = 16, kHeavySpan = kBuildBlock * kHeavyPerThread;
+struct HeavySums {  // one of each per kHeavySpan pieces
+  long long *units, *slots, *entries;
+};
+
+__global__ __launch_bounds__(kBuildBlock) void k_heavy_sums(int64_t n_pieces, const int32_t* __restrict__ row_len,
+                                                            int32_t heavy_len, HeavySums sums) {
+  __shared__ long long wave_sums[kWaves];
+  long long units = 0, slots = 0, entries = 0;
+#pragma unroll
+  for (int i = 0; i < kHeavyPerThread; ++i) {
+    const int64_t q = (int64_t)blockIdx.x * kHeavySpan + i * kBuildBlock + threadIdx.x;
+    const int len = q < n_pieces ? row_len[q] : 0;
+    if (len > heavy_len) { ++units; slots += heavy_footprint(len, heavy_len); entries += len; }
   }
-  unsigned long long mine = heavy ? (unsigned long long)len : 0ull;
-  for (int d = 32; d > 0; d >>= 1) mine += __shfl_down(mine, d, 64);
-  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(flag_slot(heavy_nnz), mine);  // (kFlagSlots counters, see there)
+  long long tot[3];
+  block_exclusive_scan(units, wave_sums, &tot[0]);
+  block_exclusive_scan(slots, wave_sums, &tot[1]);
+  block_exclusive_scan(entries, wave_sums, &tot[2]);
+  if (threadIdx.x == 0) {
+    sums.units[blockIdx.x] = tot[0]; sums.slots[blockIdx.x] = tot[1]; sums.entries[blockIdx.x] = tot[2];
+  }
 }
 
+// Exclusive scan of data[0 .. n) in place by one workgroup of kOneBlock threads (a run of elements each); *total and
+// *most receive the sum and the largest element.
+constexpr int kOneBlock = 1024;
+__device__ __forceinline__ void scan_by_one_block(long long* data, int64_t n, long long* total, long long* most) {
+  __shared__ long long wave_sum[kOneBlock / 64], wave_most[kOneBlock / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t per = (n + kOneBlock - 1) / kOneBlock;
+  const int64_t i0 = threadIdx.x * per, i1 = i0 + per < n ? i0 + per : n;
+  long long mine = 0, largest = 0;
+  for (int64_t i = i0; i < i1; ++i) { mine += data[i]; largest = max(largest, data[i]); }
+  const long long incl = wave_inclusive_scan(mine, lane);
+  for (int d = 32; d > 0; d >>= 1) largest = max(largest, __shfl_xor(largest, d, 64));
+  __syncthreads();  // (the arrays may still be read from a previous call)
+  if (lane == 63) wave_sum[wave] = incl;
+  if (lane == 0) wave_most[wave] = largest;
+  __syncthreads();
+  long long before = incl - mine, all = 0;
+  largest = 0;
+  for (int w = 0; w < kOneBlock / 64; ++w) {
+    if (w < wave) before += wave_sum[w];
+    all += wave_sum[w];
+    largest = max(largest, wave_most[w]);
+  }
+  for (int64_t i = i0; i < i1; ++i) {
+    const long long v = data[i];
+    data[i] = before;
+    before += v;
+  }
+  *total = all;
+  *most = largest;
+}
 
-
-// What the host needs to know before it can size the stream, in one array: report[0] = chunks of all lists,
-// [1] = entries of heavy pieces (the sum of the counters k_heavy_counts added to; the longest list is the maximum
-// of the counters next to them), [2] = heavy pieces, [3] = slots of the heavy sequence, [4] = chunks of the longest
-// list.
+// The last step of the scans over groups and over heavy pieces, and what the host needs to know before it can size the
+// stream, written to its memory: report[0] = chunks of all lists, [1] = entries of heavy pieces, [2] = heavy pieces,
+// [3] = slots of the heavy sequence, [4] = chunks of the longest list.
 constexpr int kReport2 = 5;
-__global__ void k_report(const long long* totals, const long long* heavy_nnz_slots, const int32_t* unit_before,
-                         const int32_t* hent_before, int64_t n_pieces, long long* report) {
-  const int i = threadIdx.x;
-  if (i >= kReport2) return;
-  long long v;
-  if (i == 0) v = totals[0];
-  else if (i == 1) { v = 0; for (int slot = 0; slot < kFlagSlots; ++slot) v += heavy_nnz_slots[slot * kFlagStride]; }
-  else if (i == 2) v = unit_before ? unit_before[n_pieces] : 0;
-  else if (i == 3) v = hent_before ? hent_before[n_pieces] : 0;
-  else {
-    v = 0;
-    for (int slot = 0; slot < kFlagSlots; ++slot) {
-      const long long o = heavy_nnz_slots[slot * kFlagStride + 1];
-      v = o > v ? o : v;
-    }
-  }
-  report[i] = v;
-}
-
-__global__ void k_pick2(const int32_t* a, const int32_t* b, int32_t* dst) {
-  if (threadIdx.x == 0) { dst[0] = *a; dst[1] = *b; }
+__global__ __launch_bounds__(kOneBlock) void k_totals(int64_t n_groups, long long* group_chunks, int64_t n_spans,
+                                                      HeavySums sums, long long* report) {
+  long long chunks, longest, units, slots, entries, unused;
+  scan_by_one_block(group_chunks, n_groups, &chunks, &longest);
+  scan_by_one_block(sums.units, n_spans, &units, &unused);
+  scan_by_one_block(sums.slots, n_spans, &slots, &unused);
+  scan_by_one_block(sums.entries, n_spans, &entries, &unused);
+  if (threadIdx.x != 0) return;
+  report[0] = chunks; report[1] = entries; report[2] = units; report[3] = slots; report[4] = longest;
 }
 
 // data[i] += seq_base[i / kScanSeq]: the last step of the device-wide exclusive scan
@@ -854,134 +651,37 @@ __global__ void k_add_seq_base(int64_t n, int32_t* data, const int32_t* __restri
   if (i < n) data[i] += seq_base[i / kScanSeq];
 }
 
-// first slot of piece q in the fused (cols, vals) arrays
-__device__ __forceinline__ int64_t piece_slot0(int64_t q, int64_t B, int32_t k, int64_t R, int64_t S,
-                                               const int64_t* __restrict__ bucket_row_ptr,
-                                               const int64_t* __restrict__ bucket_slot_ptr,
-                                               const int64_t* __restrict__ rem_ptr) {
-  if (q >= R) return S + rem_ptr[q - R];
-  int64_t lo = 0, hi = B;  // last bucket b with bucket_row_ptr[b] <= q
-  while (hi - lo > 1) {
-    const int64_t mid = lo + ((hi - lo) >> 1);
-    if (bucket_row_ptr[mid] <= q) lo = mid; else hi = mid;
-  }
-  const int bin = (int)(lo % (k + 1));
-  return bucket_slot_ptr[lo] + ((q - bucket_row_ptr[lo]) << bin);
-}
-
-// One thread per piece: heavy piece number u notes where its slots start in the heavy sequence, where its real
-// entries end there, and where its entries lie in the fused (cols, vals) arrays (unit_start, unit_end, unit_slot0;
-// unit_start has one more element, the total).
-__global__ void k_heavy_units(int64_t n_pieces, const int32_t* __restrict__ row_len,
-                              const int32_t* __restrict__ unit_before, const int32_t* __restrict__ hent_before,
-                              int64_t B, int32_t k, int64_t R, int64_t S,
-                              const int64_t* __restrict__ bucket_row_ptr,
-                              const int64_t* __restrict__ bucket_slot_ptr, const int64_t* __restrict__ rem_ptr,
-                              int32_t heavy_len, int32_t* __restrict__ unit_start,
-                              int32_t* __restrict__ unit_end, int64_t* __restrict__ unit_slot0,
-                              int32_t* __restrict__ quad_unit) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q > n_pieces) return;
-  if (q == n_pieces) { unit_start[unit_before[q]] = hent_before[q]; return; }
-  if (unit_before[q + 1] == unit_before[q]) return;
-  const int u = unit_before[q];
-  const int64_t start = hent_before[q], len = row_len[q];
-  unit_start[u] = (int32_t)start;
-  unit_end[u] = (int32_t)(start + len);
-  unit_slot0[u] = piece_slot0(q, B, k, R, S, bucket_row_ptr, bucket_slot_ptr, rem_ptr);
-  // every quad of the heavy sequence whose first slot lies in this piece learns so (the pieces follow each other
-  // without a gap, so every quad that starts before the end of the sequence hears from exactly one piece)
-  constexpr int kQuadSlots = kChunkSlots * kChunksPerQuad;
-  const int64_t end = start + heavy_footprint((int)len, heavy_len);
-  for (int64_t quad = (start + kQuadSlots - 1) / kQuadSlots; quad * kQuadSlots < end; ++quad) quad_unit[quad] = u;
-}
-
-// One wavefront per kPackRun consecutive chunks of the heavy sequence (a whole quad), a lane per slot: writes the
-// chunks' stream records.  The slot words of a chunk all name the slot at which a piece ends in it (in the place of
-// the local row of the list records), with the hand-over flag set if one does.  Which pieces a chunk covers is the
-// same for all lanes: quad_unit names the piece the quad starts in, the walk over unit_start from there runs on
-// wave-uniform values.
-constexpr int kPackRun = kChunksPerQuad;
-
-__global__ __launch_bounds__(256) void k_pack_heavy(int64_t n_heavy_chunks, int64_t first_chunk, StreamShape ss,
-                                                    int32_t n_units, const int32_t* __restrict__ unit_start,
-                                                    const int32_t* __restrict__ unit_end,
-                                                    const int64_t* __restrict__ unit_slot0,
-                                                    const int32_t* __restrict__ quad_unit,
-                                                    const int32_t* __restrict__ cols, const float* __restrict__ vals) {
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t ck0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + wave) * kPackRun;
-  if (ck0 >= n_heavy_chunks) return;  // (n_heavy_chunks is a whole number of quads)
-  const int lane = threadIdx.x & 63;
-  const int64_t total = n_units > 0 ? (int64_t)unit_start[n_units] : 0;
-  // the last unit that starts at or before the first slot of the run
-  int lo = ck0 * kChunkSlots < total ? quad_unit[ck0 / kPackRun] : 0;
-  int64_t src[kPackRun];
-  int32_t word[kPackRun];  // everything of the record but the column
-  bool pad[kPackRun];
-#pragma unroll
-  for (int i = 0; i < kPackRun; ++i) {
-    const int64_t e0 = (ck0 + i) * kChunkSlots;
-    pad[i] = e0 >= total;  // past the last piece: padding up to a whole quad
-    src[i] = 0; word[i] = 0;
-    if (pad[i]) continue;
-    while (lo + 1 < n_units && (int64_t)unit_start[lo + 1] <= e0) ++lo;
-    const int64_t start_lo = unit_start[lo], end_lo = unit_end[lo], slot0_lo = unit_slot0[lo];
-    const bool has_next = lo + 1 < n_units;
-    const int64_t start_hi = unit_start[lo + 1];  // (the total when lo is the last unit)
-    const int64_t end_hi = has_next ? unit_end[lo + 1] : 0, slot0_hi = has_next ? unit_slot0[lo + 1] : 0;
-    const int64_t e = e0 + lane;
-    const bool second = has_next && e >= start_hi;
-    const int64_t start = second ? start_hi : start_lo, len = (second ? end_hi : end_lo) - start;
-    const int64_t j = e - start;
-    const bool real = j < len;
-    src[i] = (second ? slot0_hi : slot0_lo) + (real ? j : len - 1);
-    // the piece that ends inside this chunk, if any, is the one the chunk starts in (a later one would have to
-    // start and end here: heavy pieces are longer than that, or start a chunk of their own)
-    const int64_t last = end_lo - 1 - e0;
-    const int hand_over = last >= 0 && last < kChunkSlots;
-    const int end_slot = hand_over ? (int)last : 0;
-    if (ss.compact)
-      word[i] = (int32_t)(((uint32_t)end_slot << kCompactColBits) | ((uint32_t)real << 27) | (7u << 28) |
-                          ((uint32_t)hand_over << 31));
-    else
-      word[i] = real ? (end_slot | (kRowLog2W << 16) | (hand_over << 22)) : -1;
-  }
-  int32_t col[kPackRun];
-  float val[kPackRun];
-#pragma unroll
-  for (int i = 0; i < kPackRun; ++i) {
-    col[i] = cols[src[i]];
-    val[i] = ss.unit ? 0.f : vals[src[i]];
-  }
-#pragma unroll
-  for (int i = 0; i < kPackRun; ++i) {
-    if (pad[i]) {
-      put_slot(ss, first_chunk + ck0 + i, lane, ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
-    } else if (ss.compact) {
-      const bool real = (word[i] >> 27) & 1;
-      put_slot(ss, first_chunk + ck0 + i, lane, (int32_t)((uint32_t)col[i] | (uint32_t)word[i]),
-               real ? __float_as_int(val[i]) : 0, 0);
-    } else {
-      put_slot(ss, first_chunk + ck0 + i, lane, col[i], word[i] >= 0 ? __float_as_int(val[i]) : 0, word[i]);
-    }
-  }
-}
-
 // Heavy list w covers the chunks [w*L, (w+1)*L) of the heavy sequence.  A wavefront writes a partial-sum row at
 // every piece end and one more where its list ends, so its first write goes to row (pieces that end before
 // chunk w*L) + w.
-__global__ void k_heavy_list_slots(int32_t n_lists, int32_t list_chunks, int32_t n_units,
-                                   const int32_t* __restrict__ unit_end, int32_t* hlist_first_slot) {
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= n_lists) return;
-  const int64_t x = (int64_t)w * list_chunks * kChunkSlots;
-  int lo = 0, hi = n_units;  // first unit whose real entries end beyond slot x
-  while (lo < hi) {
-    const int mid = lo + ((hi - lo) >> 1);
-    if ((int64_t)unit_end[mid] <= x) lo = mid + 1; else hi = mid;
+// A heavy piece q learns its number and its first slot (unit[q] = number << 32 | slot; the words of other pieces are not
+// written), and the lists that start in it (in it: their first slot is one of its own) where their first write goes.
+__global__ __launch_bounds__(kBuildBlock) void k_heavy_units(int64_t n_pieces, const int32_t* __restrict__ row_len,
+                                                             int32_t heavy_len, HeavySums sums, int32_t list_chunks,
+                                                             unsigned long long* __restrict__ unit,
+                                                             int32_t* __restrict__ hlist_first_slot) {
+  __shared__ unsigned long long wave_sums[kWaves];
+  const int64_t q0 = (int64_t)blockIdx.x * kHeavySpan + threadIdx.x * kHeavyPerThread;
+  int len[kHeavyPerThread];
+  unsigned long long mine = 0;
+#pragma unroll
+  for (int i = 0; i < kHeavyPerThread; ++i) {
+    len[i] = q0 + i < n_pieces ? row_len[q0 + i] : 0;
+    if (len[i] > heavy_len) mine += (1ull << 32) + (unsigned)heavy_footprint(len[i], heavy_len);
   }
-  hlist_first_slot[w] = lo + w;
+  unsigned long long tot;
+  unsigned long long at = block_exclusive_scan(mine, wave_sums, &tot) + ((unsigned long long)sums.units[blockIdx.x] << 32) +
+                          (unsigned long long)sums.slots[blockIdx.x];
+  const int per_list = list_chunks * kChunkSlots;
+#pragma unroll
+  for (int i = 0; i < kHeavyPerThread; ++i) {
+    if (len[i] <= heavy_len) continue;
+    unit[q0 + i] = at;
+    const unsigned start = (unsigned)at, u = (unsigned)(at >> 32), end = start + (unsigned)len[i];
+    for (unsigned w = (start + per_list - 1) / per_list; (unsigned long long)w * per_list < end; ++w)
+      hlist_first_slot[w] = (int32_t)(u + w);
+    at += (1ull << 32) + (unsigned)heavy_footprint(len[i], heavy_len);
+  }
 }
 
 // The partial-sum rows of heavy piece number u whose real entries are the slots [e0, e1) of the heavy sequence:
@@ -993,54 +693,242 @@ __device__ __forceinline__ void piece_slots(int list_chunks, int u, int e0, int 
   *count = w1 - w0 + 1;
 }
 
-// One thread per row: how many partial-sum rows the heavy pieces of the row have (row_slot_ptr before its scan)
-__global__ void k_row_slot_counts(int32_t n_rows, int32_t c, int32_t list_chunks,
-                                  const int32_t* __restrict__ piece_of,
-                                  const int32_t* __restrict__ row_len, const int32_t* __restrict__ unit_before,
-                                  const int32_t* __restrict__ hent_before, int32_t* row_slot_ptr) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r > n_rows) return;
-  int n = 0;
-  if (r < n_rows) {
-    for (int p = 0; p < c; ++p) {
-      const int32_t q = piece_of[(int64_t)p * n_rows + r];
-      if (q < 0 || unit_before[q + 1] == unit_before[q]) continue;
-      int first, count;
-      piece_slots(list_chunks, unit_before[q], hent_before[q], hent_before[q] + row_len[q], &first, &count);
-      n += count;
+// The partial-sum rows of every row, partition by partition, and the rows that have any: counts per kBuildBlock rows
+// (slots << 32 | rows), their scan, then the lists.
+struct RowSlotArgs {
+  int32_t n_rows, c, list_chunks, heavy_len;
+  const int32_t *indptr, *piece_of, *row_len;
+  const unsigned long long* unit;
+  unsigned long long* sums;  // one per kBuildBlock rows
+  int32_t *row_slot_ptr, *row_slots, *heavy_rows;
+};
+
+template <typename F>
+__device__ __forceinline__ void for_row_slots(const RowSlotArgs& a, int r, F&& f) {
+  if (r >= a.n_rows || a.indptr[r + 1] - a.indptr[r] <= a.heavy_len) return;
+  for (int p = 0; p < a.c; ++p) {
+    const int32_t q = a.piece_of[(int64_t)p * a.n_rows + r];
+    if (q < 0) continue;
+    const int len = a.row_len[q];
+    if (len <= a.heavy_len) continue;
+    const unsigned long long unit = a.unit[q];
+    int first, count;
+    piece_slots(a.list_chunks, (int)(unit >> 32), (int)(unsigned)unit, (int)(unsigned)unit + len, &first, &count);
+    f(first, count);
+  }
+}
+
+__global__ __launch_bounds__(kBuildBlock) void k_row_slot_sums(RowSlotArgs a) {
+  __shared__ unsigned long long wave_sums[kWaves];
+  unsigned long long n = 0, tot;
+  for_row_slots(a, blockIdx.x * kBuildBlock + threadIdx.x, [&](int, int count) { n += count; });
+  block_exclusive_scan((n << 32) + (n > 0), wave_sums, &tot);
+  if (threadIdx.x == 0) a.sums[blockIdx.x] = tot;
+}
+
+__global__ __launch_bounds__(kOneBlock) void k_row_slot_scan(unsigned long long* sums, int64_t n, int32_t* report) {
+  long long total, unused;
+  scan_by_one_block((long long*)sums, n, &total, &unused);
+  if (threadIdx.x == 0) { report[0] = (int32_t)(total >> 32); report[1] = (int32_t)(uint32_t)total; }
+}
+
+__global__ __launch_bounds__(kBuildBlock) void k_row_slot_fill(RowSlotArgs a) {
+  __shared__ unsigned long long wave_sums[kWaves];
+  const int r = blockIdx.x * kBuildBlock + threadIdx.x;
+  unsigned long long n = 0, tot;
+  for_row_slots(a, r, [&](int, int count) { n += count; });
+  const unsigned long long at = a.sums[blockIdx.x] + block_exclusive_scan((n << 32) + (n > 0), wave_sums, &tot);
+  if (r >= a.n_rows) return;
+  a.row_slot_ptr[r] = (int32_t)(at >> 32);
+  if (r == a.n_rows - 1) a.row_slot_ptr[a.n_rows] = (int32_t)((at >> 32) + n);
+  if (n == 0) return;
+  a.heavy_rows[(uint32_t)at] = r;
+  int32_t* out = a.row_slots + (at >> 32);
+  for_row_slots(a, r, [&](int first, int count) {
+    for (int i = 0; i < count; ++i) *out++ = first + i;
+  });
+}
+
+// ---------------------------------------------------------------------- copy
+// Every entry of A goes to its slot of the canonical arrays and of the stream in one pass over the CSR input.  A
+// workgroup takes 2^log2_rows consecutive rows, whose entries are consecutive too: what is the same for all entries of a
+// piece (where it goes) is put into LDS first, then a lane per entry finds its row by a search over the rows' starts and
+// its partition from its column.  The cost of a long row is spread over the workgroup that way, and the input is read
+// once: 169,343 rows, 1.17 M entries, four partitions 22 us (three kernels, each with a wavefront per 64 pieces: 78 us,
+// most of it a few wavefronts with long pieces).
+struct CopyArgs {
+  const int32_t *indptr, *indices;
+  const float* values;
+  const int32_t *bound, *piece_of;
+  const int64_t *bucket_row_ptr, *bucket_slot_ptr, *rem_ptr;
+  int32_t* cols;
+  float* vals;
+  int64_t R, S, T;
+  double inv_w;
+  int32_t log2_rows;
+  // the stream (stream.stream NULL: canonical arrays only)
+  const uint32_t* dealt;
+  const unsigned long long* unit;
+  const long long *cell_first_chunk, *group_first_chunk;
+  int64_t heavy_chunk0, heavy_slots, n_heavy_chunks;
+};
+constexpr int kCopyPieces = 1024;  // most pieces a workgroup holds at a time
+constexpr int kCopyWords = 6;      // LDS words per piece
+
+__global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, StreamShape ss, CopyArgs a, int pieces_at_a_time) {
+  extern __shared__ int lds[];
+  __shared__ int row_lo[65];
+  const int log2_rows = a.log2_rows, n_rows_here = 1 << log2_rows;
+  int* piece_lo = lds;                                                 // first entry in the input
+  int* piece_len = piece_lo + pieces_at_a_time;
+  uint32_t* piece_dst = (uint32_t*)(piece_len + pieces_at_a_time);     // first slot in the canonical arrays
+  uint32_t* piece_word = piece_dst + pieces_at_a_time;                 // see k_deal
+  int* piece_chunk = (int*)(piece_word + pieces_at_a_time);            // first chunk of its cell; heavy: its first slot
+  int* piece_last = piece_chunk + pieces_at_a_time;                    // last column
+  const int tid = threadIdx.x;
+  const int r0 = blockIdx.x << log2_rows;
+  const bool with_stream = ss.stream != nullptr, gapless = cs.long_len >= kChunkSlots;
+  if (blockIdx.x == 0 && tid < kChunkSlots) {  // the spare entries past the end of the arrays
+    a.cols[a.S + a.T + tid] = 0;
+    a.vals[a.S + a.T + tid] = 0.f;
+  }
+  if (tid <= n_rows_here) row_lo[tid] = a.indptr[r0 + tid < s.n_rows ? r0 + tid : s.n_rows];
+  const int parts_at_a_time = pieces_at_a_time >> log2_rows;
+  const int row_mask = (1 << cs.log2_rb) - 1;
+
+  // one slot of the stream: entry (or pad, real == false) number j of piece i
+  auto put = [&](int i, int p, int rl, int j, int32_t col, float val, bool real) {
+    const int len = piece_len[i], chunk_or_slot = piece_chunk[i];
+    int64_t chunk;
+    int slot, field, flag, code = 7;
+    uint32_t col_field = (uint32_t)col;
+    if (len > cs.long_len) {
+      // all slots of a chunk name the slot at which a piece ends in it: this one, or (nothing lies between two pieces
+      // unless each starts a chunk) the one before it
+      const int64_t x = (int64_t)chunk_or_slot + j, e0 = x / kChunkSlots * kChunkSlots;
+      const int64_t last = (int64_t)chunk_or_slot + len - 1 - e0;
+      const bool ends = last >= 0 && last < kChunkSlots, before = !ends && gapless && chunk_or_slot > e0;
+      chunk = a.heavy_chunk0 + x / kChunkSlots;
+      slot = (int)(x - e0);
+      flag = ends || before;
+      field = ends ? (int)last : before ? (int)(chunk_or_slot - 1 - e0) : 0;
+    } else {
+      const uint32_t word = piece_word[i];
+      field = (r0 + rl) & row_mask;
+      col_field -= cs.n_phases == 1 ? 0u : (uint32_t)((int64_t)(p / cs.ppg) * ss.phase_width);
+      if (word & kWidePiece) {
+        chunk = (int64_t)chunk_or_slot + (word & ~kWidePiece) + j / kChunkSlots;
+        slot = j % kChunkSlots;
+        flag = j / kChunkSlots == (len - 1) / kChunkSlots;
+      } else {
+        const int pos = (int)(word & 0x0FFFFFFFu) + j;
+        chunk = (int64_t)chunk_or_slot + (pos >> 3);
+        slot = (int)(word >> 28) * 8 + (pos & 7);
+        flag = j == len - 1;
+        code = 3;
+      }
+    }
+    if (ss.compact)
+      put_slot(ss, chunk, slot,
+               (int32_t)(col_field | ((uint32_t)field << kCompactColBits) | ((uint32_t)real << 27) | ((uint32_t)code << 28) |
+                         ((uint32_t)flag << 31)),
+               real ? __float_as_int(val) : 0, 0);
+    else
+      put_slot(ss, chunk, slot, col, real ? __float_as_int(val) : 0,
+               real ? (field | ((code == 3 ? 3 : kRowLog2W) << 16) | (flag << 22)) : -1);
+  };
+
+  for (int p0 = 0; p0 < s.c; p0 += parts_at_a_time) {
+    const int np = s.c - p0 < parts_at_a_time ? s.c - p0 : parts_at_a_time;
+    __syncthreads();  // (row_lo is complete, the pieces of the last turn are no longer read)
+    for (int i = tid; i < np << log2_rows; i += 256) {
+      const int p = p0 + (i >> log2_rows), r = r0 + (i & (n_rows_here - 1));
+      int lo = 0, len = 0;
+      if (r < s.n_rows) row_piece(s, a.indptr, a.bound, r, p, &lo, &len);
+      piece_lo[i] = lo;
+      piece_len[i] = len;
+      if (len <= 0) continue;
+      const int64_t q = a.piece_of[(int64_t)p * s.n_rows + r];
+      const int bin = bin_of_length(len, s.k);
+      const int64_t b = (int64_t)p * (s.k + 1) + bin;
+      piece_dst[i] = bin <= s.k ? (uint32_t)(a.bucket_slot_ptr[b] + ((q - a.bucket_row_ptr[b]) << bin))
+                                : (uint32_t)(a.S + a.rem_ptr[q - a.R]);
+      if (!with_stream) continue;
+      if (len > cs.long_len) {
+        piece_word[i] = 0;
+        piece_chunk[i] = (int)(uint32_t)a.unit[q];
+      } else {
+        const uint32_t word = a.dealt[q];
+        const int64_t grp = (int64_t)(p / cs.ppg) * cs.n_rb + (r >> cs.log2_rb);
+        const long long* cell = a.cell_first_chunk + grp * cells_per_group(cs) + (int64_t)(p % cs.ppg) * cells_per_part(cs);
+        piece_word[i] = word;
+        piece_chunk[i] = (int)(a.group_first_chunk[grp] + cell[(word & kWidePiece) ? bin : cs.nb]);
+      }
+    }
+    __syncthreads();
+    const unsigned e_end = (unsigned)row_lo[n_rows_here];
+    constexpr int kUnroll = 4;
+    for (unsigned e0 = (unsigned)row_lo[0]; e0 < e_end; e0 += 256 * kUnroll) {
+      int32_t col[kUnroll];
+      float val[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const unsigned e = e0 + u * 256 + tid;
+        col[u] = 0; val[u] = 0.f;
+        if (e < e_end) { col[u] = a.indices[e]; val[u] = a.values[e]; }
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const unsigned e = e0 + u * 256 + tid;
+        if (e >= e_end) continue;
+        int rl = 0;  // the last row that starts at or before e
+        for (int step = n_rows_here >> 1; step > 0; step >>= 1)
+          if ((unsigned)row_lo[rl + step] <= e) rl += step;
+        int p = (int)((double)col[u] * a.inv_w);  // off by one at most
+        const int over = (int)((unsigned)col[u] - (unsigned)p * (unsigned)s.w);
+        p += over >= s.w ? 1 : over < 0 ? -1 : 0;
+        if (p < p0 || p >= p0 + np) continue;
+        const int i = ((p - p0) << log2_rows) + rl;
+        const int j = (int)(e - (unsigned)piece_lo[i]);
+        const uint32_t dst = piece_dst[i] + (uint32_t)j;
+        a.cols[dst] = col[u];
+        a.vals[dst] = val[u];
+        if (j == piece_len[i] - 1) piece_last[i] = col[u];
+        if (with_stream) put(i, p, rl, j, col[u], val[u], true);
+      }
+    }
+    __syncthreads();
+    // Pads, eight lanes per piece: of a bucket row they repeat the last column and hold +0.0f; of the last chunk of a
+    // piece cut wide and of a heavy piece that no other follows in its chunk they repeat it too, but are marked.
+    const int l = tid & 7;
+    for (int i = tid >> 3; i < np << log2_rows; i += 256 / 8) {
+      const int len = piece_len[i];
+      if (len <= 0) continue;
+      const int bin = bin_of_length(len, s.k);
+      const int32_t col = piece_last[i];
+      if (bin <= s.k)
+        for (int j = len + l; j < (1 << bin); j += 8) {
+          a.cols[piece_dst[i] + (uint32_t)j] = col;
+          a.vals[piece_dst[i] + (uint32_t)j] = 0.f;
+        }
+      if (!with_stream) continue;
+      const int p = p0 + (i >> log2_rows), rl = i & (n_rows_here - 1);
+      if (len > cs.long_len) {
+        const int64_t end = (int64_t)piece_chunk[i] + len;
+        const bool last_piece = end + (gapless ? 0 : (kChunkSlots - len % kChunkSlots) % kChunkSlots) == a.heavy_slots;
+        if (gapless && !last_piece) continue;
+        const int pads = (int)((kChunkSlots - end % kChunkSlots) % kChunkSlots);
+        for (int j = l; j < pads; j += 8) put(i, p, rl, len + j, col, 0.f, false);
+        if (last_piece)  // chunks up to a whole quad
+          for (int64_t x = (end + pads) / kChunkSlots * kChunkSlots + l; x < a.n_heavy_chunks * kChunkSlots; x += 8)
+            put_slot(ss, a.heavy_chunk0 + x / kChunkSlots, (int)(x % kChunkSlots),
+                     ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
+      } else if (piece_word[i] & kWidePiece) {
+        for (int j = len + l; j < (len + kChunkSlots - 1) / kChunkSlots * kChunkSlots; j += 8)
+          put(i, p, rl, j, col, 0.f, false);
+      }
     }
   }
-  row_slot_ptr[r] = n;
-}
-
-__global__ void k_row_slot_fill(int32_t n_rows, int32_t c, int32_t list_chunks,
-                                const int32_t* __restrict__ piece_of,
-                                const int32_t* __restrict__ row_len, const int32_t* __restrict__ unit_before,
-                                const int32_t* __restrict__ hent_before, const int32_t* __restrict__ row_slot_ptr,
-                                int32_t* row_slots) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n_rows) return;
-  int32_t* out = row_slots + row_slot_ptr[r];
-  for (int p = 0; p < c; ++p) {
-    const int32_t q = piece_of[(int64_t)p * n_rows + r];
-    if (q < 0 || unit_before[q + 1] == unit_before[q]) continue;
-    int first, count;
-    piece_slots(list_chunks, unit_before[q], hent_before[q], hent_before[q] + row_len[q], &first, &count);
-    for (int i = 0; i < count; ++i) *out++ = first + i;
-  }
-}
-
-// heavy_rows (compacted): flags, then after their scan the rows themselves
-__global__ void k_heavy_row_flags(int32_t n_rows, const int32_t* __restrict__ row_slot_ptr, int32_t* flag) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r > n_rows) return;
-  flag[r] = (r < n_rows && row_slot_ptr[r + 1] > row_slot_ptr[r]) ? 1 : 0;
-}
-__global__ void k_heavy_row_fill(int32_t n_rows, const int32_t* __restrict__ row_slot_ptr,
-                                 const int32_t* __restrict__ before, int32_t* heavy_rows) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n_rows) return;
-  if (row_slot_ptr[r + 1] > row_slot_ptr[r]) heavy_rows[before[r]] = r;
 }
 
 // --------------------------------------------------------------- host helpers
@@ -1295,24 +1183,22 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
   const size_t report1_bytes = tmp.reserve(sizeof(int32_t) * (size_t)s.c * s.nb) + sizeof(int32_t) * (size_t)s.c * s.nb;
   const size_t o_counts = tmp.reserve(sizeof(int32_t) * (size_t)s.c * s.nb * nbk);
   const size_t o_rnnz = tmp.reserve(sizeof(int64_t) * (size_t)s.c * nbk);
-  const size_t o_rnnz_base = tmp.reserve(sizeof(int64_t) * (size_t)s.c);
   const size_t o_bound = tmp.reserve(sizeof(int32_t) * (size_t)(s.c - 1) * (size_t)(s.n_rows ? s.n_rows : 1) + 16);
-  const size_t o_totals = tmp.reserve(sizeof(long long) * 4);  // chunks of all lists; -; longest list
-  const size_t o_nnz_slots = tmp.reserve(sizeof(long long) * kFlagSlots * kFlagStride);  // entries of heavy pieces
-  const size_t report2_count = kReport2;
-  const size_t o_report2 = tmp.reserve(sizeof(long long) * report2_count);
-  const size_t o_report3 = tmp.reserve(sizeof(int32_t) * 2);
   const int64_t n_bound_blocks =
       (((int64_t)s.n_rows + kBoundRows - 1) / kBoundRows) * (((int64_t)s.c - 1 + kBoundParts - 1) / kBoundParts);
   if (n_bound_blocks > 0x7FFFFFFF) return SPTIR_ERR_OVERFLOW;
   Blob host;
   const size_t h_report1 = host.reserve(report1_bytes);
-  const size_t h_row_ptr = host.reserve(sizeof(int64_t) * (size_t)(B + 1));
-  const size_t h_slot_ptr = host.reserve(sizeof(int64_t) * (size_t)(B + 1));
-  const size_t h_rem_part_ptr = host.reserve(sizeof(int32_t) * (size_t)(s.c + 1));
-  const size_t h_rnnz_base = host.reserve(sizeof(int64_t) * (size_t)s.c);
-  const size_t h_report2 = host.reserve(sizeof(long long) * report2_count);
-  const size_t h_report3 = host.reserve(sizeof(int32_t) * 4);
+  // (these four reach the device in one copy, into the start of the handle's first allocation)
+  Blob ba;
+  const size_t a_row_ptr = ba.reserve(sizeof(int64_t) * (size_t)(B + 1));
+  const size_t a_slot_ptr = ba.reserve(sizeof(int64_t) * (size_t)(B + 1));
+  const size_t a_rem_part = ba.reserve(sizeof(int32_t) * (size_t)(s.c + 1));
+  const size_t a_rnnz_base = ba.reserve(sizeof(int64_t) * (size_t)s.c);
+  const size_t small_bytes = ba.size;
+  const size_t h_small = host.reserve(small_bytes);
+  const size_t h_report2 = host.reserve(sizeof(long long) * kReport2);
+  const size_t h_report3 = host.reserve(sizeof(int32_t) * 2);
   const size_t h_misc = host.reserve(64);
   PinnedPool::Buf pinned = pinned_pool().acquire(host.size);
   if (!pinned.p) return SPTIR_ERR_ALLOC;
@@ -1320,8 +1206,6 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
   tmp.base = (char*)scratch_alloc(tmp.size, alloc, actx, stream);
   if (!tmp.base) { pinned_pool().release(pinned); return SPTIR_ERR_ALLOC; }
   Blob tmp2;
-  void* tmp_chunks = nullptr;
-  void* tmp_place = nullptr;
   void* tmp_order = nullptr;
 
   sptir_hyb* h = new (std::nothrow) sptir_hyb();
@@ -1345,12 +1229,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     int64_t* d_rnnz = (int64_t*)(tmp.base + o_rnnz);
     int32_t* d_tot_bins = (int32_t*)(tmp.base + o_tot_bins);
     int64_t* d_tot_rnnz = (int64_t*)(tmp.base + o_tot_rnnz);
-    int64_t* d_rnnz_base = (int64_t*)(tmp.base + o_rnnz_base);
     int32_t* d_bound = (int32_t*)(tmp.base + o_bound);
-    long long* d_totals = (long long*)(tmp.base + o_totals);
-    long long* d_nnz_slots = (long long*)(tmp.base + o_nnz_slots);
-    long long* d_report2 = (long long*)(tmp.base + o_report2);
-    int32_t* d_report3 = (int32_t*)(tmp.base + o_report3);
 
     // ---- validation of the CSR input, and with it (their results are only used if the input is valid, and they
     // read nothing at a position the input names without clamping it) the piece boundaries, histogram and scans
@@ -1386,10 +1265,10 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     if (st != SPTIR_OK) goto fail;
 
     // ---- sizes and the small prefix arrays (host)
-    int64_t* row_ptr = (int64_t*)(host.base + h_row_ptr);
-    int64_t* slot_ptr = (int64_t*)(host.base + h_slot_ptr);
-    int32_t* rem_part_ptr = (int32_t*)(host.base + h_rem_part_ptr);
-    int64_t* rnnz_base = (int64_t*)(host.base + h_rnnz_base);
+    int64_t* row_ptr = (int64_t*)(host.base + h_small + a_row_ptr);
+    int64_t* slot_ptr = (int64_t*)(host.base + h_small + a_slot_ptr);
+    int32_t* rem_part_ptr = (int32_t*)(host.base + h_small + a_rem_part);
+    int64_t* rnnz_base = (int64_t*)(host.base + h_small + a_rnnz_base);
     int64_t M = 0, T = 0;
     row_ptr[0] = 0; slot_ptr[0] = 0; rem_part_ptr[0] = 0;
     for (int32_t p = 0; p < s.c; ++p) {
@@ -1448,43 +1327,39 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     if (n_cells > 0x7FFFFFFF || n_bounds > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
     const size_t o_bounds = tmp2.reserve(sizeof(int32_t) * (size_t)(n_bounds ? n_bounds : 1));
     const size_t o_cell_chunks = tmp2.reserve(sizeof(long long) * (size_t)(n_cells ? n_cells : 1));
-    const int64_t n_seq = (n_groups + kGroupSeq - 1) / kGroupSeq;
-    const size_t o_group_tot = tmp2.reserve(sizeof(long long) * (size_t)(n_seq ? n_seq * kGroupSeq : 1));
-    const size_t o_seq_tot = tmp2.reserve(sizeof(long long) * (size_t)(n_seq ? n_seq : 1));
-    // heavy pieces: the two prefix arrays over the pieces, the (row, partition) -> piece map, scan scratch
+    const size_t o_group_tot = tmp2.reserve(sizeof(long long) * (size_t)(n_groups ? n_groups : 1));
+    const size_t o_queue_len = tmp2.reserve(sizeof(int32_t) * 8 * (size_t)(n_parts ? n_parts : 1));
+    const size_t o_piece_of = tmp2.reserve(sizeof(int32_t) * (size_t)s.c * (size_t)(s.n_rows ? s.n_rows : 1));
+    // per piece: what the lists do with it, or its number among the heavy pieces; the sums of the scans
     const bool want_heavy = with_spmm_plan && n_pieces > 0;
-    const size_t o_unit = tmp2.reserve(sizeof(int32_t) * (want_heavy ? scan_room(n_pieces + 1) : 1));
-    const size_t o_hent = tmp2.reserve(sizeof(int32_t) * (want_heavy ? scan_room(n_pieces + 1) : 1));
-    const size_t o_piece_of = tmp2.reserve(sizeof(int32_t) * (want_heavy ? (size_t)s.c * (size_t)s.n_rows : 1));
-    const size_t o_seq_base = tmp2.reserve(sizeof(int32_t) * 2 * (scan_room(std::max<int64_t>(n_pieces + 1, s.n_rows + 1)) / kScanSeq + 2));
-    const size_t o_row_flags = tmp2.reserve(sizeof(int32_t) * (want_heavy ? scan_room((int64_t)s.n_rows + 1) : 1));
+    const int64_t n_spans = want_heavy ? (n_pieces + kHeavySpan - 1) / kHeavySpan : 0;
+    const size_t o_dealt = tmp2.reserve(sizeof(uint32_t) * (size_t)(want_heavy ? n_pieces : 1));
+    const size_t o_unit = tmp2.reserve(sizeof(long long) * (size_t)(want_heavy ? n_pieces : 1));
+    const size_t o_spans = tmp2.reserve(sizeof(long long) * 3 * (size_t)(n_spans ? n_spans : 1));
+    const size_t o_row_sums = tmp2.reserve(sizeof(long long) * nbk);
     tmp2.base = (char*)scratch_alloc(tmp2.size, alloc, actx, stream);
     if (!tmp2.base) { st = SPTIR_ERR_ALLOC; goto fail; }
     int32_t* d_bounds = (int32_t*)(tmp2.base + o_bounds);
     long long* d_cell_chunks = (long long*)(tmp2.base + o_cell_chunks);
     long long* d_group_tot = (long long*)(tmp2.base + o_group_tot);
-    long long* d_seq_tot = (long long*)(tmp2.base + o_seq_tot);
-    int32_t* d_unit = (int32_t*)(tmp2.base + o_unit);
-    int32_t* d_hent = (int32_t*)(tmp2.base + o_hent);
-    int32_t* d_piece_of = want_heavy ? (int32_t*)(tmp2.base + o_piece_of) : nullptr;
-    int32_t* d_seq_base = (int32_t*)(tmp2.base + o_seq_base);
-    int32_t* d_row_flags = (int32_t*)(tmp2.base + o_row_flags);
+    int32_t* d_queue_len = (int32_t*)(tmp2.base + o_queue_len);
+    int32_t* d_piece_of = (int32_t*)(tmp2.base + o_piece_of);
+    uint32_t* d_dealt = (uint32_t*)(tmp2.base + o_dealt);
+    unsigned long long* d_unit = (unsigned long long*)(tmp2.base + o_unit);
+    HeavySums sums;
+    sums.units = (long long*)(tmp2.base + o_spans); sums.slots = sums.units + n_spans; sums.entries = sums.slots + n_spans;
 
     // ---- the handle's device arrays whose sizes are known now: two allocations (cols and vals can be released
     // on their own); the arrays of the SpMM plan follow further down
     {
-      Blob ba, bb;
-      const size_t a_row_ptr = ba.reserve(sizeof(int64_t) * (size_t)(B + 1));
-      const size_t a_slot_ptr = ba.reserve(sizeof(int64_t) * (size_t)(B + 1));
-      const size_t a_rem_part = ba.reserve(sizeof(int32_t) * (size_t)(s.c + 1));
+      Blob bb;
       const size_t a_rem_ptr = ba.reserve(sizeof(int64_t) * (size_t)(M + 1));
-      // (row_ids, cols and vals end in kChunkSlots spare zero entries: whole 64-slot chunks are read from them
-      //  when the stream is packed, the last one of an array may be shorter)
+      // (row_ids, cols and vals end in kChunkSlots spare zero entries)
       const size_t a_row_ids = ba.reserve(sizeof(int32_t) * (size_t)(h->R + M + kChunkSlots));
       const size_t a_row_len = ba.reserve(sizeof(int32_t) * (size_t)(h->R + M + 1));
       const size_t a_rb_chunk = ba.reserve(sizeof(int64_t) * ((size_t)cs.n_phases * cs.n_rb + 1));
       const size_t a_row_val = ba.reserve(one_value_per_row ? sizeof(float) * (size_t)s.n_rows : 0);
-      const size_t a_row_slot = ba.reserve(want_heavy ? sizeof(int32_t) * scan_room((int64_t)s.n_rows + 1) : 0);
+      const size_t a_row_slot = ba.reserve(want_heavy ? sizeof(int32_t) * ((size_t)s.n_rows + 1) : 0);
       const size_t b_cols = bb.reserve(sizeof(int32_t) * (size_t)(h->S + T + kChunkSlots));
       const size_t b_vals = bb.reserve(sizeof(float) * (size_t)(h->S + T + kChunkSlots));
       h->blobs[0] = alloc(ba.size, actx, stream);
@@ -1507,22 +1382,17 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
                          csr->indptr, csr->values, h->row_val);
       BUILD_HIP(hipGetLastError());
     }
-    BUILD_HIP(hipMemcpyAsync(h->bucket_row_ptr, row_ptr, sizeof(int64_t) * (B + 1), hipMemcpyHostToDevice, stream));
-    BUILD_HIP(hipMemcpyAsync(h->bucket_slot_ptr, slot_ptr, sizeof(int64_t) * (B + 1), hipMemcpyHostToDevice, stream));
-    BUILD_HIP(hipMemcpyAsync(h->rem_part_ptr, rem_part_ptr, sizeof(int32_t) * (s.c + 1), hipMemcpyHostToDevice, stream));
-    BUILD_HIP(hipMemcpyAsync(d_rnnz_base, rnnz_base, sizeof(int64_t) * s.c, hipMemcpyHostToDevice, stream));
+    BUILD_HIP(hipMemcpyAsync(h->blobs[0], host.base + h_small, small_bytes, hipMemcpyHostToDevice, stream));
 
-    // ---- stable scatter
+    // ---- stable placement
     if (s.NB > 0) {
-      ScatterArgs a;
-      a.indptr = csr->indptr; a.indices = csr->indices; a.values = csr->values;
-      a.bound = d_bound; a.counts = d_counts; a.rem_nnz = d_rnnz;
-      a.bucket_row_ptr = h->bucket_row_ptr; a.bucket_slot_ptr = h->bucket_slot_ptr;
-      a.rem_part_ptr = h->rem_part_ptr; a.rem_nnz_base = d_rnnz_base;
-      a.row_ids = h->row_ids; a.cols = h->cols; a.vals = h->vals; a.rem_ptr = h->rem_ptr; a.row_len = h->row_len;
-      a.piece_of = d_piece_of;
-      a.R = h->R; a.S = h->S; a.M = M; a.T = T;
-      hipLaunchKernelGGL(k_scatter, dim3((unsigned)n_pair_blocks), dim3(kBuildBlock), 0, stream, s, a);
+      PlaceArgs a;
+      a.indptr = csr->indptr; a.bound = d_bound; a.counts = d_counts; a.rem_nnz = d_rnnz;
+      a.bucket_row_ptr = h->bucket_row_ptr; a.rem_part_ptr = h->rem_part_ptr;
+      a.rem_nnz_base = (const int64_t*)((char*)h->blobs[0] + a_rnnz_base);
+      a.row_ids = h->row_ids; a.rem_ptr = h->rem_ptr; a.row_len = h->row_len; a.piece_of = d_piece_of;
+      a.R = h->R; a.M = M; a.T = T;
+      hipLaunchKernelGGL(k_place, dim3((unsigned)n_pair_blocks), dim3(kBuildBlock), 0, stream, s, a);
     } else {
       int64_t* zero = (int64_t*)(host.base + h_misc + 8);
       *zero = 0;
@@ -1532,50 +1402,23 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       BUILD_HIP(hipMemsetAsync(h->vals + h->S + T, 0, sizeof(float) * kChunkSlots, stream));
     }
     BUILD_HIP(hipGetLastError());
+    if (n_spans > 0)
+      hipLaunchKernelGGL(k_heavy_sums, dim3((unsigned)n_spans), dim3(kBuildBlock), 0, stream, n_pieces, h->row_len,
+                         cs.long_len, sums);
 
-    // ---- heavy pieces: how many, and how many chunks (prefixes over the pieces in row_ids order)
-    BUILD_HIP(hipMemsetAsync(d_totals, 0, o_nnz_slots - o_totals + sizeof(long long) * kFlagSlots * kFlagStride, stream));
-    if (want_heavy) {
-      hipLaunchKernelGGL(k_heavy_counts, dim3((unsigned)((n_pieces + 256) / 256)), dim3(256), 0, stream, n_pieces,
-                         h->row_len, cs.long_len, d_unit, d_hent, (unsigned long long*)d_nnz_slots);
-      BUILD_HIP(hipGetLastError());
-      st = device_exclusive_scan(d_unit, n_pieces + 1, d_seq_base, stream);
-      if (st != SPTIR_OK) goto fail;
-      st = device_exclusive_scan(d_hent, n_pieces + 1, d_seq_base, stream);
-      if (st != SPTIR_OK) goto fail;
-    }
-
-    // ---- chunk descriptors of the lists, grouped by (phase, row block)
+    // ---- the pieces of every (launch, row block, partition) dealt to its queues; chunks of the lists
     if (n_cells > 0) {
-      BUILD_HIP(hipMemsetAsync(d_group_tot, 0, sizeof(long long) * (size_t)n_seq * kGroupSeq, stream));
       hipLaunchKernelGGL(k_cell_bounds, dim3((unsigned)((n_bounds + 255) / 256)), dim3(256), 0, stream, cs,
                          h->bucket_row_ptr, h->rem_part_ptr, h->row_ids, d_bounds);
-      hipLaunchKernelGGL(k_part_chunk_counts, dim3((unsigned)((n_parts + 255) / 256)), dim3(256), 0, stream, cs,
-                         n_parts, d_bounds, h->row_len, d_cell_chunks);
+      hipLaunchKernelGGL(k_deal, dim3((unsigned)((n_parts + kDealParts - 1) / kDealParts)), dim3(256),
+                         (sizeof(int) * kDealParts) << cs.log2_rb, stream, cs, n_parts, d_bounds, h->row_len, d_cell_chunks,
+                         d_dealt, d_queue_len);
       hipLaunchKernelGGL(k_group_scan, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, stream, cs, n_groups,
-                         d_cell_chunks, d_group_tot, (unsigned long long*)(d_nnz_slots + 1));
-      // chunks before a cell = its prefix inside the group + the group's inside its sequence + the sequence's
-      hipLaunchKernelGGL(k_scan_sequences<long long>, dim3((unsigned)n_seq), dim3(kBuildBlock), 0, stream,
-                         d_group_tot, (int32_t)kGroupSeq, d_seq_tot);
-      hipLaunchKernelGGL(k_scan_sequences<long long>, dim3(1), dim3(kBuildBlock), 0, stream, d_seq_tot,
-                         (int32_t)n_seq, d_totals);
-      BUILD_HIP(hipGetLastError());
+                         d_cell_chunks, d_group_tot);
     }
-    // one report for the host: the totals
-    {
-      hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, stream, d_totals, d_nnz_slots,
-                         want_heavy ? d_unit : nullptr, want_heavy ? d_hent : nullptr, n_pieces, d_report2);
-      BUILD_HIP(hipGetLastError());
-      BUILD_HIP(hipMemcpyAsync(host.base + h_report2, d_report2, sizeof(long long) * report2_count,
-                               hipMemcpyDeviceToHost, stream));
-    }
-    // (the GPU is busy: the allocations whose sizes are known come now)
-    if (with_spmm_plan) {
-      const size_t bytes = sizeof(PiecePlace) * (size_t)(n_pieces ? n_pieces : 1);
-      tmp_place = scratch_alloc(bytes, alloc, actx, stream);
-      if (!tmp_place) { st = SPTIR_ERR_ALLOC; goto fail; }
-      BUILD_HIP(hipMemsetAsync(tmp_place, 0, bytes, stream));  // len 0: not queued
-    }
+    hipLaunchKernelGGL(k_totals, dim3(1), dim3(kOneBlock), 0, stream, n_cells > 0 ? n_groups : 0, d_group_tot, n_spans,
+                       sums, (long long*)(host.base + h_report2));
+    BUILD_HIP(hipGetLastError());
     BUILD_HIP(hipStreamSynchronize(stream));
     const long long* report2 = (const long long*)(host.base + h_report2);
     const long long n_chunks = report2[0];
@@ -1597,15 +1440,12 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     h->n_partial_rows = h->n_heavy + h->n_heavy_lists;
     if (h->n_heavy == 0) h->row_slot_ptr = nullptr;  // (its room in the first allocation stays unused)
     const int64_t all_chunks = n_chunks + n_heavy_chunks;
-    if (h->n_partial_rows > 0x7FFFFFFF || all_chunks > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
-    const int32_t n_units = (int32_t)h->n_heavy;
-    int64_t* unit_slot0 = nullptr;
-    int32_t *unit_start = nullptr, *unit_end = nullptr, *quad_unit = nullptr;
-    // ---- the arrays of the SpMM plan, one allocation; the temporaries of this stage, another.  A row of Y takes
+    if (h->n_partial_rows > 0x7FFFFFFF || all_chunks > 0x7FFFFFFF || report2[3] > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
+    // ---- the arrays of the SpMM plan, one allocation.  A row of Y takes
     // one partial-sum row per heavy piece it has plus one per list boundary such a piece crosses, so there are at
     // most n_partial_rows of them; the rows with heavy pieces are at most as many as there are such pieces.
     {
-      Blob bc, bt;
+      Blob bc;
       const bool heavy = h->n_heavy > 0;
       const size_t c_first_slot = bc.reserve(heavy ? sizeof(int32_t) * (size_t)h->n_heavy_lists : 0);
       const size_t c_row_slots = bc.reserve(heavy ? sizeof(int32_t) * (size_t)h->n_partial_rows : 0);
@@ -1614,77 +1454,56 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       const size_t c_stream = bc.reserve(sizeof(int32_t) * ((h->compact_stream ? 2 : 3) - (one_value_per_row ? 1 : 0)) *
                                          kChunkSlots * (size_t)(all_chunks ? all_chunks : 1));
       const size_t c_partial = bc.reserve(heavy ? sizeof(float) * kPartialFeat * (size_t)h->n_partial_rows : 0);
-      const size_t t_chunks = bt.reserve(sizeof(Chunk) * (size_t)(n_chunks ? n_chunks : 1));
-      const size_t t_slot0 = bt.reserve(heavy ? sizeof(int64_t) * (size_t)n_units : 0);
-      const size_t t_start = bt.reserve(heavy ? sizeof(int32_t) * ((size_t)n_units + 1) : 0);
-      const size_t t_end = bt.reserve(heavy ? sizeof(int32_t) * (size_t)n_units : 0);
-      const size_t t_quad = bt.reserve(heavy ? sizeof(int32_t) * (size_t)(n_heavy_chunks / kChunksPerQuad + 1) : 0);
       h->blobs[2] = alloc(bc.size, actx, stream);
-      tmp_chunks = scratch_alloc(bt.size, alloc, actx, stream);
-      if (!h->blobs[2] || !tmp_chunks) { st = SPTIR_ERR_ALLOC; goto fail; }
+      if (!h->blobs[2]) { st = SPTIR_ERR_ALLOC; goto fail; }
       h->device_bytes += bc.size;
       char* c0 = (char*)h->blobs[2];
-      char* t0 = (char*)tmp_chunks;
       if (heavy) {
         h->hlist_first_slot = (int32_t*)(c0 + c_first_slot); h->row_slots = (int32_t*)(c0 + c_row_slots);
         h->heavy_rows = (int32_t*)(c0 + c_heavy_rows); h->partial = (float*)(c0 + c_partial);
-        unit_slot0 = (int64_t*)(t0 + t_slot0); unit_start = (int32_t*)(t0 + t_start);
-        unit_end = (int32_t*)(t0 + t_end); quad_unit = (int32_t*)(t0 + t_quad);
       }
       if (n_groups > 0) h->rb_order = (int32_t*)(c0 + c_rb_order);
       h->stream = (int32_t*)(c0 + c_stream);
-      (void)t_chunks;  // (offset 0)
-      BUILD_HIP(hipMemsetAsync(tmp_chunks, 0, sizeof(Chunk) * (size_t)(n_chunks ? n_chunks : 1), stream));  // count 0 marks the padding chunks
     }
     if (h->n_heavy > 0) {
-      // ---- heavy pieces: where every piece lies, the first partial-sum row of every heavy list, which
-      // partial-sum rows each row of Y takes
-      hipLaunchKernelGGL(k_heavy_units, dim3((unsigned)((n_pieces + 256) / 256)), dim3(256), 0, stream, n_pieces,
-                         h->row_len, d_unit, d_hent, B, s.k, h->R, h->S, h->bucket_row_ptr, h->bucket_slot_ptr,
-                         h->rem_ptr, cs.long_len, unit_start, unit_end, unit_slot0, quad_unit);
-      hipLaunchKernelGGL(k_heavy_list_slots, dim3((unsigned)((h->n_heavy_lists + 255) / 256)), dim3(256), 0, stream,
-                         h->n_heavy_lists, list_chunks, n_units, unit_end, h->hlist_first_slot);
-      hipLaunchKernelGGL(k_row_slot_counts, dim3((unsigned)((s.n_rows + 256) / 256)), dim3(256), 0, stream, s.n_rows,
-                         s.c, list_chunks, d_piece_of, h->row_len, d_unit, d_hent, h->row_slot_ptr);
-      BUILD_HIP(hipGetLastError());
-      st = device_exclusive_scan(h->row_slot_ptr, (int64_t)s.n_rows + 1, d_seq_base, stream);
-      if (st != SPTIR_OK) goto fail;
-      // the rows that have heavy pieces, compacted: the launch that adds their partial sums to Y visits only them
-      hipLaunchKernelGGL(k_heavy_row_flags, dim3((unsigned)((s.n_rows + 256) / 256)), dim3(256), 0, stream, s.n_rows,
-                         h->row_slot_ptr, d_row_flags);
-      BUILD_HIP(hipGetLastError());
-      st = device_exclusive_scan(d_row_flags, (int64_t)s.n_rows + 1, d_seq_base, stream);
-      if (st != SPTIR_OK) goto fail;
-      hipLaunchKernelGGL(k_row_slot_fill, dim3((unsigned)((s.n_rows + 255) / 256)), dim3(256), 0, stream, s.n_rows,
-                         s.c, list_chunks, d_piece_of, h->row_len, d_unit, d_hent, h->row_slot_ptr, h->row_slots);
-      hipLaunchKernelGGL(k_heavy_row_fill, dim3((unsigned)((s.n_rows + 255) / 256)), dim3(256), 0, stream, s.n_rows,
-                         h->row_slot_ptr, d_row_flags, h->heavy_rows);
-      hipLaunchKernelGGL(k_pick2, dim3(1), dim3(64), 0, stream, h->row_slot_ptr + s.n_rows,
-                         d_row_flags + s.n_rows, d_report3);
-      BUILD_HIP(hipGetLastError());
-      BUILD_HIP(hipMemcpyAsync(host.base + h_report3, d_report3, sizeof(int32_t) * 2, hipMemcpyDeviceToHost, stream));
+      // ---- heavy pieces: their numbers and slots, the first partial-sum row of every heavy list, which
+      // partial-sum rows each row of Y takes, the rows that have any (the launch that adds them visits only those)
+      hipLaunchKernelGGL(k_heavy_units, dim3((unsigned)n_spans), dim3(kBuildBlock), 0, stream, n_pieces, h->row_len,
+                         cs.long_len, sums, list_chunks, d_unit, h->hlist_first_slot);
+      RowSlotArgs a;
+      a.n_rows = s.n_rows; a.c = s.c; a.list_chunks = list_chunks; a.heavy_len = cs.long_len;
+      a.indptr = csr->indptr; a.piece_of = d_piece_of; a.row_len = h->row_len; a.unit = d_unit;
+      a.sums = (unsigned long long*)(tmp2.base + o_row_sums);
+      a.row_slot_ptr = h->row_slot_ptr; a.row_slots = h->row_slots; a.heavy_rows = h->heavy_rows;
+      hipLaunchKernelGGL(k_row_slot_sums, dim3((unsigned)s.NB), dim3(kBuildBlock), 0, stream, a);
+      hipLaunchKernelGGL(k_row_slot_scan, dim3(1), dim3(kOneBlock), 0, stream, a.sums, (int64_t)s.NB,
+                         (int32_t*)(host.base + h_report3));
+      hipLaunchKernelGGL(k_row_slot_fill, dim3((unsigned)s.NB), dim3(kBuildBlock), 0, stream, a);
     }
     StreamShape ss;
     ss.stream = h->stream; ss.compact = h->compact_stream; ss.log2_rb = cs.log2_rb; ss.unit = h->row_val ? 1 : 0;
     ss.phase_width = (int32_t)((int64_t)cs.ppg * s.w > 0x7FFFFFFF ? 0x7FFFFFFF : (int64_t)cs.ppg * s.w);
-    if (n_parts > 0)
-      hipLaunchKernelGGL(k_part_fill_chunks, dim3((unsigned)((n_parts + 255) / 256)), dim3(256), 0, stream, cs, ss,
-                         n_parts, d_bounds, d_cell_chunks, d_group_tot, d_seq_tot, h->row_len, h->row_ids,
-                         h->bucket_row_ptr, h->bucket_slot_ptr, h->rem_ptr, h->S, (Chunk*)tmp_chunks,
-                         (PiecePlace*)tmp_place, h->rb_chunk_ptr, (int64_t)n_chunks);
-    if (h->n_heavy > 0)
-      hipLaunchKernelGGL(k_pack_heavy, dim3((unsigned)((n_heavy_chunks / kPackRun + 3) / 4)), dim3(256), 0, stream,
-                         n_heavy_chunks, (int64_t)n_chunks, ss, n_units, unit_start, unit_end, unit_slot0, quad_unit,
-                         h->cols, h->vals);
-    if (n_chunks > 0) {
-      int64_t blocks = (n_chunks + 3) / 4;
-      if (blocks > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
-      hipLaunchKernelGGL(k_pack_stream, dim3((unsigned)blocks), dim3(256), 0, stream, (int64_t)n_chunks, ss,
-                         (const Chunk*)tmp_chunks, h->row_ids, h->cols, h->vals);
-      if (n_pieces > 0)
-        hipLaunchKernelGGL(k_pack_pieces, dim3((unsigned)((n_pieces + 255) / 256)), dim3(256), 0, stream, n_pieces, ss,
-                           (const PiecePlace*)tmp_place, h->row_ids, h->cols, h->vals);
+    if (!with_spmm_plan) ss.stream = nullptr;
+    if (s.NB > 0) {
+      CopyArgs a;
+      a.indptr = csr->indptr; a.indices = csr->indices; a.values = csr->values; a.bound = d_bound; a.piece_of = d_piece_of;
+      a.bucket_row_ptr = h->bucket_row_ptr; a.bucket_slot_ptr = h->bucket_slot_ptr; a.rem_ptr = h->rem_ptr;
+      a.cols = h->cols; a.vals = h->vals; a.R = h->R; a.S = h->S; a.T = T;
+      a.inv_w = 1.0 / (double)(s.w > 0 ? s.w : 1);
+      a.dealt = d_dealt; a.unit = d_unit; a.cell_first_chunk = d_cell_chunks; a.group_first_chunk = d_group_tot;
+      a.heavy_chunk0 = n_chunks; a.heavy_slots = report2[3]; a.n_heavy_chunks = n_heavy_chunks;
+      // rows per workgroup: at most 64 (so that a long row is a small part of the grid), fewer where the grid would have
+      // less than four workgroups per CU, or where the pieces of that many rows would not fit the LDS arrays
+      a.log2_rows = 6;
+      while (a.log2_rows > 2 && (s.n_rows >> a.log2_rows) < 1024) --a.log2_rows;
+      while (a.log2_rows > 0 && ((int64_t)s.c << a.log2_rows) > kCopyPieces) --a.log2_rows;
+      const int pieces = (int)std::min<int64_t>((int64_t)s.c << a.log2_rows, kCopyPieces);
+      hipLaunchKernelGGL(k_copy, dim3((unsigned)(((int64_t)s.n_rows + (1 << a.log2_rows) - 1) >> a.log2_rows)), dim3(256),
+                         sizeof(int) * kCopyWords * (size_t)pieces, stream, s, cs, ss, a, pieces);
     }
+    if (n_parts > 0)
+      hipLaunchKernelGGL(k_list_ends, dim3((unsigned)((n_parts + 31) / 32)), dim3(256), 0, stream, cs, ss, n_parts,
+                         d_cell_chunks, d_group_tot, d_queue_len, h->rb_chunk_ptr, (int64_t)n_chunks);
     BUILD_HIP(hipGetLastError());
     if (n_parts == 0) {  // no lists: the one element of rb_chunk_ptr
       int64_t* zero = (int64_t*)(host.base + h_misc + 16);
@@ -1714,8 +1533,6 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
   }
   scratch_free(tmp.base, free_, actx);
   scratch_free(tmp2.base, free_, actx);
-  scratch_free(tmp_chunks, free_, actx);
-  scratch_free(tmp_place, free_, actx);
   scratch_free(tmp_order, free_, actx);
   pinned_pool().release(pinned);
   *out = h;
@@ -1725,8 +1542,6 @@ fail:
   (void)hipStreamSynchronize(stream);
   scratch_free(tmp.base, free_, actx);
   scratch_free(tmp2.base, free_, actx);
-  scratch_free(tmp_chunks, free_, actx);
-  scratch_free(tmp_place, free_, actx);
   scratch_free(tmp_order, free_, actx);
   pinned_pool().release(pinned);
   sptir_hyb_destroy(h);
