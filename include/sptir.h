@@ -151,10 +151,11 @@ typedef void (*sptir_free_fn)(void* ptr, void* ctx);
 sptir_status_t sptir_set_allocator(sptir_alloc_fn alloc, sptir_free_fn free_, void* ctx);
 
 /*
- * Under the default allocator sptir_hyb_build keeps the temporary device blocks of a call (at most 8 blocks and
- * 512 MB in all, none larger than 256 MB) for the next call instead of giving them back with hipFree, which costs more
- * than a whole small build.  This call frees what is being kept.  Handles are not affected.  With an allocator of
- * the caller's nothing is ever kept.
+ * Under the default allocator the device blocks of destroyed hyb handles and the temporary blocks of sptir_hyb_build are
+ * kept (at most 16 blocks and 2 GB in all, none larger than 1 GB, the oldest go first) for the next build instead of
+ * giving them back with hipFree, which costs as much as a small build.  This call frees what is being kept; an allocation
+ * that fails does so before it is tried again.  Live handles are not affected.  With an allocator of the caller's nothing
+ * is ever kept.
  */
 sptir_status_t sptir_release_scratch(void);
 

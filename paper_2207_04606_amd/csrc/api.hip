@@ -38,18 +38,64 @@ void current_allocator(sptir_alloc_fn* a, sptir_free_fn* f, void** ctx) {
   }
 }
 
-// ---- temporaries under the default allocator
-// A hipFree costs 0.17 - 0.23 ms on this system (it waits for the device and unmaps the block), and a build has five
-// temporaries: a quarter of its time.  Blocks that hipMalloc gave out for temporaries are therefore kept when they are
-// released (a few, bounded in size) and handed to the next call that asks for about as much on the same device.
-// With a caller's allocator temporaries go straight to it: it has its own policy.
+// ---- kept blocks of the default allocator
+// hipMalloc and hipFree map and unmap memory: 0.05 - 0.3 ms for each of the eight blocks of a build and its handle, a
+// third of the time of a small build and its release.  Blocks that hipMalloc gave out for temporaries and for hyb handles
+// are therefore kept when they are released (a few, bounded in size, the oldest go first) and handed to the next call
+// that asks for about as much on the same device.  With a caller's allocator everything goes straight to it: it has its
+// own policy.
 namespace {
 struct ScratchBlock { void* p; size_t size; int dev; };
 std::mutex g_scratch_mu;
 std::vector<ScratchBlock> g_scratch_free, g_scratch_live;
 size_t g_scratch_free_bytes = 0;
-constexpr size_t kScratchKeepBytes = (size_t)512 << 20, kScratchKeepBlock = (size_t)256 << 20;
-constexpr size_t kScratchKeepCount = 8;
+constexpr size_t kScratchKeepBytes = (size_t)2048 << 20, kScratchKeepBlock = (size_t)1024 << 20;
+constexpr size_t kScratchKeepCount = 16;
+
+void free_blocks(const std::vector<ScratchBlock>& blocks) {
+  if (blocks.empty()) return;
+  int before = 0;
+  const bool have_dev = hipGetDevice(&before) == hipSuccess;
+  for (const auto& b : blocks) {
+    if (have_dev && hipSetDevice(b.dev) != hipSuccess) { (void)hipGetLastError(); continue; }
+    (void)hipFree(b.p);
+  }
+  if (have_dev) (void)hipSetDevice(before);
+}
+
+void take_kept_blocks(std::vector<ScratchBlock>* blocks) {
+  std::lock_guard<std::mutex> lock(g_scratch_mu);
+  blocks->swap(g_scratch_free);
+  g_scratch_free_bytes = 0;
+}
+
+bool take_live_block(void* p, ScratchBlock* b) {
+  std::lock_guard<std::mutex> lock(g_scratch_mu);
+  for (size_t i = 0; i < g_scratch_live.size(); ++i)
+    if (g_scratch_live[i].p == p) {
+      *b = g_scratch_live[i];
+      g_scratch_live.erase(g_scratch_live.begin() + (long)i);
+      return true;
+    }
+  return false;
+}
+
+void keep_or_free(const ScratchBlock& b) {  // no work on the device uses the block any more
+  std::vector<ScratchBlock> out;
+  if (b.size > kScratchKeepBlock) {
+    out.push_back(b);
+  } else {
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    g_scratch_free.push_back(b);
+    g_scratch_free_bytes += b.size;
+    while (g_scratch_free.size() > kScratchKeepCount || g_scratch_free_bytes > kScratchKeepBytes) {
+      out.push_back(g_scratch_free.front());
+      g_scratch_free_bytes -= g_scratch_free.front().size;
+      g_scratch_free.erase(g_scratch_free.begin());
+    }
+  }
+  free_blocks(out);
+}
 }  // namespace
 
 void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream) {
@@ -74,6 +120,12 @@ void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream
     }
   }
   void* p = default_alloc(bytes, nullptr, stream);
+  if (!p) {
+    std::vector<ScratchBlock> kept;
+    take_kept_blocks(&kept);
+    free_blocks(kept);
+    p = default_alloc(bytes, nullptr, stream);
+  }
   if (p) {
     std::lock_guard<std::mutex> lock(g_scratch_mu);
     g_scratch_live.push_back({p, bytes, dev});
@@ -84,23 +136,28 @@ void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream
 void scratch_free(void* p, sptir_free_fn free_, void* actx) {
   if (!p) return;
   ScratchBlock b{nullptr, 0, 0};
-  {
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    for (size_t i = 0; i < g_scratch_live.size(); ++i)
-      if (g_scratch_live[i].p == p) {
-        b = g_scratch_live[i];
-        g_scratch_live.erase(g_scratch_live.begin() + (long)i);
-        break;
-      }
-    if (b.p && b.size <= kScratchKeepBlock && g_scratch_free.size() < kScratchKeepCount &&
-        g_scratch_free_bytes + b.size <= kScratchKeepBytes) {
-      g_scratch_free.push_back(b);
-      g_scratch_free_bytes += b.size;
-      return;
+  if (take_live_block(p, &b)) keep_or_free(b);
+  else free_(p, actx);  // came from the caller's allocator
+}
+
+void handle_free(void* const* blobs, int n, sptir_free_fn free_, void* actx) {
+  int synced = -1;
+  for (int i = 0; i < n; ++i) {
+    if (!blobs[i]) continue;
+    ScratchBlock b{nullptr, 0, 0};
+    if (!take_live_block(blobs[i], &b)) { free_(blobs[i], actx); continue; }
+    // Launches that read the handle may still be running on any stream: as hipFree would, wait for the device.
+    if (b.dev != synced) {
+      int before = 0;
+      const bool other = hipGetDevice(&before) == hipSuccess && before != b.dev;
+      if (other) (void)hipSetDevice(b.dev);
+      const bool ok = hipDeviceSynchronize() == hipSuccess;
+      if (other) (void)hipSetDevice(before);
+      if (!ok) { (void)hipGetLastError(); free_blocks({b}); continue; }
+      synced = b.dev;
     }
+    keep_or_free(b);
   }
-  if (b.p) default_free(p, nullptr);  // ours, but not kept
-  else free_(p, actx);                // came from the caller's allocator
 }
 
 sptir_status_t note_hip_error(hipError_t e, const char* what) {
@@ -117,18 +174,8 @@ extern "C" {
 
 sptir_status_t sptir_release_scratch(void) {
   std::vector<sptir::ScratchBlock> blocks;
-  {
-    std::lock_guard<std::mutex> lock(sptir::g_scratch_mu);
-    blocks.swap(sptir::g_scratch_free);
-    sptir::g_scratch_free_bytes = 0;
-  }
-  int before = 0;
-  const bool have_dev = hipGetDevice(&before) == hipSuccess;
-  for (const auto& b : blocks) {
-    if (have_dev && hipSetDevice(b.dev) != hipSuccess) { (void)hipGetLastError(); continue; }
-    (void)hipFree(b.p);
-  }
-  if (have_dev) (void)hipSetDevice(before);
+  sptir::take_kept_blocks(&blocks);
+  sptir::free_blocks(blocks);
   return SPTIR_OK;
 }
 
@@ -143,8 +190,7 @@ sptir_status_t sptir_set_allocator(sptir_alloc_fn alloc, sptir_free_fn free_, vo
 
 sptir_status_t sptir_hyb_destroy(sptir_hyb_t* h) {
   if (!h) return SPTIR_OK;
-  for (void* p : h->blobs)
-    if (p) h->free_(p, h->alloc_ctx);
+  sptir::handle_free(h->blobs, 3, h->free_, h->alloc_ctx);
   delete h;
   return SPTIR_OK;
 }

@@ -371,8 +371,8 @@ __device__ __forceinline__ unsigned min_of_8(unsigned v) {  // over the eight la
 // what remains serial, a piece after the other to the shortest queue, runs on registers.  (A thread per partition that
 // read a length at a time, once to count and once more to fill, took 35 + 93 us on 169,343 rows; this takes 9.)
 // Writes the chunk counts of the partition's cells, a word per piece (see above) and the entries of every queue.
-constexpr int kDealParts = 32;  // partitions per workgroup
-__global__ __launch_bounds__(256) void k_deal(CellShape cs, int64_t n_parts, const int32_t* __restrict__ bin_rb_ptr,
+constexpr int kDealParts = 8;  // partitions per workgroup, a wavefront
+__global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n_parts, const int32_t* __restrict__ bin_rb_ptr,
                                               const int32_t* __restrict__ row_len, long long* __restrict__ cell_chunks,
                                               uint32_t* __restrict__ dealt, int32_t* __restrict__ queue_len) {
   extern __shared__ int piece_len[];                 // [kDealParts][rows of a row block]
@@ -530,7 +530,7 @@ __device__ __forceinline__ void put_slot(const StreamShape& ss, int64_t chunk, i
 
 // Eight lanes per (group, partition): the slots past the end of each queue; the first partition of a group also writes
 // the chunks that round the group up to whole quads, and rb_chunk_ptr.
-__global__ __launch_bounds__(256) void k_list_ends(CellShape cs, StreamShape ss, int64_t n_parts,
+__global__ __launch_bounds__(64) void k_list_ends(CellShape cs, StreamShape ss, int64_t n_parts,
                                                    const long long* __restrict__ cell_first_chunk,
                                                    const long long* __restrict__ group_first_chunk,
                                                    const int32_t* __restrict__ queue_len, int64_t* rb_chunk_ptr,
@@ -574,7 +574,7 @@ __device__ __forceinline__ int heavy_footprint(int len, int heavy_len) {
 
 // Heavy pieces are numbered, and given their slots, by an exclusive scan over all pieces: sums over kHeavySpan pieces,
 // their scan (k_totals), then the numbers of the heavy pieces themselves (k_heavy_units).
-constexpr int kHeavyPerThread = 16, kHeavySpan = kBuildBlock * kHeavyPerThread;
+constexpr int kHeavyPerThread = 4, kHeavySpan = kBuildBlock * kHeavyPerThread;
 struct HeavySums {  // one of each per kHeavySpan pieces
   long long *units, *slots, *entries;
 };
@@ -630,25 +630,18 @@ __device__ __forceinline__ void scan_by_one_block(long long* data, int64_t n, lo
   *most = largest;
 }
 
-// The last step of the scans over groups and over heavy pieces, and what the host needs to know before it can size the
-// stream, written to its memory: report[0] = chunks of all lists, [1] = entries of heavy pieces, [2] = heavy pieces,
-// [3] = slots of the heavy sequence, [4] = chunks of the longest list.
+// The last step of the scans over groups and over heavy pieces (a workgroup per array), and what the host needs to know
+// before it can size the stream, written to its memory: report[0] = chunks of all lists, [1] = chunks of the longest
+// list, [2] = heavy pieces, [3] = slots of the heavy sequence, [4] = entries of heavy pieces.
 constexpr int kReport2 = 5;
 __global__ __launch_bounds__(kOneBlock) void k_totals(int64_t n_groups, long long* group_chunks, int64_t n_spans,
                                                       HeavySums sums, long long* report) {
-  long long chunks, longest, units, slots, entries, unused;
-  scan_by_one_block(group_chunks, n_groups, &chunks, &longest);
-  scan_by_one_block(sums.units, n_spans, &units, &unused);
-  scan_by_one_block(sums.slots, n_spans, &slots, &unused);
-  scan_by_one_block(sums.entries, n_spans, &entries, &unused);
+  const int which = blockIdx.x;
+  long long* data = which == 0 ? group_chunks : which == 1 ? sums.units : which == 2 ? sums.slots : sums.entries;
+  long long total, most;
+  scan_by_one_block(data, which == 0 ? n_groups : n_spans, &total, &most);
   if (threadIdx.x != 0) return;
-  report[0] = chunks; report[1] = entries; report[2] = units; report[3] = slots; report[4] = longest;
-}
-
-// data[i] += seq_base[i / kScanSeq]: the last step of the device-wide exclusive scan
-__global__ void k_add_seq_base(int64_t n, int32_t* data, const int32_t* __restrict__ seq_base) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) data[i] += seq_base[i / kScanSeq];
+  if (which == 0) { report[0] = total; report[1] = most; } else report[which + 1] = total;
 }
 
 // Heavy list w covers the chunks [w*L, (w+1)*L) of the heavy sequence.  A wavefront writes a partial-sum row at
@@ -751,11 +744,10 @@ __global__ __launch_bounds__(kBuildBlock) void k_row_slot_fill(RowSlotArgs a) {
 
 // ---------------------------------------------------------------------- copy
 // Every entry of A goes to its slot of the canonical arrays and of the stream in one pass over the CSR input.  A
-// workgroup takes 2^log2_rows consecutive rows, whose entries are consecutive too: what is the same for all entries of a
-// piece (where it goes) is put into LDS first, then a lane per entry finds its row by a search over the rows' starts and
-// its partition from its column.  The cost of a long row is spread over the workgroup that way, and the input is read
-// once: 169,343 rows, 1.17 M entries, four partitions 22 us (three kernels, each with a wavefront per 64 pieces: 78 us,
-// most of it a few wavefronts with long pieces).
+// workgroup takes `per_wg` consecutive entries, whatever rows they belong to, so that the longest row costs no more than
+// its share; it walks them by blocks of 2^log2_rows rows.  What is the same for all entries of a piece (where it goes) is
+// put into LDS first, then a lane per entry finds its row by a search over the rows' starts and its partition from its
+// column.
 struct CopyArgs {
   const int32_t *indptr, *indices;
   const float* values;
@@ -764,8 +756,9 @@ struct CopyArgs {
   int32_t* cols;
   float* vals;
   int64_t R, S, T;
+  int64_t nnz;
   double inv_w;
-  int32_t log2_rows;
+  int32_t log2_rows, per_wg;
   // the stream (stream.stream NULL: canonical arrays only)
   const uint32_t* dealt;
   const unsigned long long* unit;
@@ -786,16 +779,15 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
   int* piece_chunk = (int*)(piece_word + pieces_at_a_time);            // first chunk of its cell; heavy: its first slot
   int* piece_last = piece_chunk + pieces_at_a_time;                    // last column
   const int tid = threadIdx.x;
-  const int r0 = blockIdx.x << log2_rows;
   const bool with_stream = ss.stream != nullptr, gapless = cs.long_len >= kChunkSlots;
   if (blockIdx.x == 0 && tid < kChunkSlots) {  // the spare entries past the end of the arrays
     a.cols[a.S + a.T + tid] = 0;
     a.vals[a.S + a.T + tid] = 0.f;
   }
-  if (tid <= n_rows_here) row_lo[tid] = a.indptr[r0 + tid < s.n_rows ? r0 + tid : s.n_rows];
   const int parts_at_a_time = pieces_at_a_time >> log2_rows;
   const int row_mask = (1 << cs.log2_rb) - 1;
 
+  int r0 = 0;
   // one slot of the stream: entry (or pad, real == false) number j of piece i
   auto put = [&](int i, int p, int rl, int j, int32_t col, float val, bool real) {
     const int len = piece_len[i], chunk_or_slot = piece_chunk[i];
@@ -838,94 +830,113 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
                real ? (field | ((code == 3 ? 3 : kRowLog2W) << 16) | (flag << 22)) : -1);
   };
 
-  for (int p0 = 0; p0 < s.c; p0 += parts_at_a_time) {
-    const int np = s.c - p0 < parts_at_a_time ? s.c - p0 : parts_at_a_time;
-    __syncthreads();  // (row_lo is complete, the pieces of the last turn are no longer read)
-    for (int i = tid; i < np << log2_rows; i += 256) {
-      const int p = p0 + (i >> log2_rows), r = r0 + (i & (n_rows_here - 1));
-      int lo = 0, len = 0;
-      if (r < s.n_rows) row_piece(s, a.indptr, a.bound, r, p, &lo, &len);
-      piece_lo[i] = lo;
-      piece_len[i] = len;
-      if (len <= 0) continue;
-      const int64_t q = a.piece_of[(int64_t)p * s.n_rows + r];
-      const int bin = bin_of_length(len, s.k);
-      const int64_t b = (int64_t)p * (s.k + 1) + bin;
-      piece_dst[i] = bin <= s.k ? (uint32_t)(a.bucket_slot_ptr[b] + ((q - a.bucket_row_ptr[b]) << bin))
-                                : (uint32_t)(a.S + a.rem_ptr[q - a.R]);
-      if (!with_stream) continue;
-      if (len > cs.long_len) {
-        piece_word[i] = 0;
-        piece_chunk[i] = (int)(uint32_t)a.unit[q];
-      } else {
-        const uint32_t word = a.dealt[q];
-        const int64_t grp = (int64_t)(p / cs.ppg) * cs.n_rb + (r >> cs.log2_rb);
-        const long long* cell = a.cell_first_chunk + grp * cells_per_group(cs) + (int64_t)(p % cs.ppg) * cells_per_part(cs);
-        piece_word[i] = word;
-        piece_chunk[i] = (int)(a.group_first_chunk[grp] + cell[(word & kWidePiece) ? bin : cs.nb]);
-      }
-    }
+  // Workgroup ids go round the 8 XCDs: ids b, b + 8, b + 16, .. take consecutive ranges, so that the lines two ranges
+  // write parts of (pieces of neighbouring rows lie next to each other) meet in one L2.
+  const int64_t per_xcd = ((int64_t)gridDim.x + 7) / 8;
+  int64_t work = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  // (a grid that is no multiple of 8 leaves the last XCDs one workgroup short: numbers past the end wrap into the gaps)
+  const int full = (int)(gridDim.x & 7);
+  if (full != 0 && (int)(blockIdx.x & 7) >= full) work -= (int)(blockIdx.x & 7) - full;
+  const int64_t first = work * a.per_wg;
+  const int64_t last = first + a.per_wg < a.nnz ? first + a.per_wg : a.nnz;
+  for (int64_t at = first; at < last;) {
+    r0 = row_of_entry(a.indptr, s.n_rows, at, tid & 63);
+    __syncthreads();  // (the last block's rows are no longer read)
+    if (tid <= n_rows_here) row_lo[tid] = a.indptr[tid < s.n_rows - r0 ? r0 + tid : s.n_rows];
     __syncthreads();
-    const unsigned e_end = (unsigned)row_lo[n_rows_here];
-    constexpr int kUnroll = 4;
-    for (unsigned e0 = (unsigned)row_lo[0]; e0 < e_end; e0 += 256 * kUnroll) {
-      int32_t col[kUnroll];
-      float val[kUnroll];
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const unsigned e = e0 + u * 256 + tid;
-        col[u] = 0; val[u] = 0.f;
-        if (e < e_end) { col[u] = a.indices[e]; val[u] = a.values[e]; }
-      }
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const unsigned e = e0 + u * 256 + tid;
-        if (e >= e_end) continue;
-        int rl = 0;  // the last row that starts at or before e
-        for (int step = n_rows_here >> 1; step > 0; step >>= 1)
-          if ((unsigned)row_lo[rl + step] <= e) rl += step;
-        int p = (int)((double)col[u] * a.inv_w);  // off by one at most
-        const int over = (int)((unsigned)col[u] - (unsigned)p * (unsigned)s.w);
-        p += over >= s.w ? 1 : over < 0 ? -1 : 0;
-        if (p < p0 || p >= p0 + np) continue;
-        const int i = ((p - p0) << log2_rows) + rl;
-        const int j = (int)(e - (unsigned)piece_lo[i]);
-        const uint32_t dst = piece_dst[i] + (uint32_t)j;
-        a.cols[dst] = col[u];
-        a.vals[dst] = val[u];
-        if (j == piece_len[i] - 1) piece_last[i] = col[u];
-        if (with_stream) put(i, p, rl, j, col[u], val[u], true);
-      }
-    }
-    __syncthreads();
-    // Pads, eight lanes per piece: of a bucket row they repeat the last column and hold +0.0f; of the last chunk of a
-    // piece cut wide and of a heavy piece that no other follows in its chunk they repeat it too, but are marked.
-    const int l = tid & 7;
-    for (int i = tid >> 3; i < np << log2_rows; i += 256 / 8) {
-      const int len = piece_len[i];
-      if (len <= 0) continue;
-      const int bin = bin_of_length(len, s.k);
-      const int32_t col = piece_last[i];
-      if (bin <= s.k)
-        for (int j = len + l; j < (1 << bin); j += 8) {
-          a.cols[piece_dst[i] + (uint32_t)j] = col;
-          a.vals[piece_dst[i] + (uint32_t)j] = 0.f;
+    const unsigned e_begin = (unsigned)at;
+    const unsigned e_end = row_lo[n_rows_here] < last ? (unsigned)row_lo[n_rows_here] : (unsigned)last;
+    at = e_end;
+    for (int p0 = 0; p0 < s.c; p0 += parts_at_a_time) {
+      const int np = s.c - p0 < parts_at_a_time ? s.c - p0 : parts_at_a_time;
+      if (p0 > 0) __syncthreads();  // (the pieces of the last turn are no longer read)
+      for (int i = tid; i < np << log2_rows; i += 256) {
+        const int p = p0 + (i >> log2_rows), rl = i & (n_rows_here - 1), r = r0 + rl;
+        int lo = 0, len = 0;
+        if (rl < s.n_rows - r0) row_piece(s, a.indptr, a.bound, r, p, &lo, &len);
+        piece_lo[i] = lo;
+        piece_len[i] = len;
+        if (len <= 0) continue;
+        const int64_t q = a.piece_of[(int64_t)p * s.n_rows + r];
+        const int bin = bin_of_length(len, s.k);
+        const int64_t b = (int64_t)p * (s.k + 1) + bin;
+        piece_dst[i] = bin <= s.k ? (uint32_t)(a.bucket_slot_ptr[b] + ((q - a.bucket_row_ptr[b]) << bin))
+                                  : (uint32_t)(a.S + a.rem_ptr[q - a.R]);
+        if (!with_stream) continue;
+        if (len > cs.long_len) {
+          piece_word[i] = 0;
+          piece_chunk[i] = (int)(uint32_t)a.unit[q];
+        } else {
+          const uint32_t word = a.dealt[q];
+          const int64_t grp = (int64_t)(p / cs.ppg) * cs.n_rb + (r >> cs.log2_rb);
+          const long long* cell = a.cell_first_chunk + grp * cells_per_group(cs) + (int64_t)(p % cs.ppg) * cells_per_part(cs);
+          piece_word[i] = word;
+          piece_chunk[i] = (int)(a.group_first_chunk[grp] + cell[(word & kWidePiece) ? bin : cs.nb]);
         }
-      if (!with_stream) continue;
-      const int p = p0 + (i >> log2_rows), rl = i & (n_rows_here - 1);
-      if (len > cs.long_len) {
-        const int64_t end = (int64_t)piece_chunk[i] + len;
-        const bool last_piece = end + (gapless ? 0 : (kChunkSlots - len % kChunkSlots) % kChunkSlots) == a.heavy_slots;
-        if (gapless && !last_piece) continue;
-        const int pads = (int)((kChunkSlots - end % kChunkSlots) % kChunkSlots);
-        for (int j = l; j < pads; j += 8) put(i, p, rl, len + j, col, 0.f, false);
-        if (last_piece)  // chunks up to a whole quad
-          for (int64_t x = (end + pads) / kChunkSlots * kChunkSlots + l; x < a.n_heavy_chunks * kChunkSlots; x += 8)
-            put_slot(ss, a.heavy_chunk0 + x / kChunkSlots, (int)(x % kChunkSlots),
-                     ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
-      } else if (piece_word[i] & kWidePiece) {
-        for (int j = len + l; j < (len + kChunkSlots - 1) / kChunkSlots * kChunkSlots; j += 8)
-          put(i, p, rl, j, col, 0.f, false);
+      }
+      __syncthreads();
+      constexpr int kUnroll = 4;
+      for (unsigned e0 = e_begin; e0 < e_end; e0 += 256 * kUnroll) {
+        int32_t col[kUnroll];
+        float val[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const unsigned e = e0 + u * 256 + tid;
+          col[u] = 0; val[u] = 0.f;
+          if (e < e_end) { col[u] = a.indices[e]; val[u] = a.values[e]; }
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const unsigned e = e0 + u * 256 + tid;
+          if (e >= e_end) continue;
+          int rl = 0;  // the last row that starts at or before e
+          for (int step = n_rows_here >> 1; step > 0; step >>= 1)
+            if ((unsigned)row_lo[rl + step] <= e) rl += step;
+          int p = (int)((double)col[u] * a.inv_w);  // off by one at most
+          const int over = (int)((unsigned)col[u] - (unsigned)p * (unsigned)s.w);
+          p += over >= s.w ? 1 : over < 0 ? -1 : 0;
+          if (p < p0 || p >= p0 + np) continue;
+          const int i = ((p - p0) << log2_rows) + rl;
+          const int j = (int)(e - (unsigned)piece_lo[i]);
+          const uint32_t dst = piece_dst[i] + (uint32_t)j;
+          a.cols[dst] = col[u];
+          a.vals[dst] = val[u];
+          if (j == piece_len[i] - 1) piece_last[i] = col[u];
+          if (with_stream) put(i, p, rl, j, col[u], val[u], true);
+        }
+      }
+      __syncthreads();
+      // Pads, eight lanes per piece that ends here: of a bucket row they repeat the last column and hold +0.0f; of the
+      // last chunk of a piece cut wide and of a heavy piece that no other follows in its chunk they repeat it too, but
+      // are marked.
+      const int l = tid & 7;
+      for (int i = tid >> 3; i < np << log2_rows; i += 256 / 8) {
+        const int len = piece_len[i];
+        const unsigned end_at = (unsigned)piece_lo[i] + (unsigned)len;
+        if (len <= 0 || end_at <= e_begin || end_at > e_end) continue;
+        const int bin = bin_of_length(len, s.k);
+        const int32_t col = piece_last[i];
+        if (bin <= s.k)
+          for (int j = len + l; j < (1 << bin); j += 8) {
+            a.cols[piece_dst[i] + (uint32_t)j] = col;
+            a.vals[piece_dst[i] + (uint32_t)j] = 0.f;
+          }
+        if (!with_stream) continue;
+        const int p = p0 + (i >> log2_rows), rl = i & (n_rows_here - 1);
+        if (len > cs.long_len) {
+          const int64_t end = (int64_t)piece_chunk[i] + len;
+          const bool last_piece = end + (gapless ? 0 : (kChunkSlots - len % kChunkSlots) % kChunkSlots) == a.heavy_slots;
+          if (gapless && !last_piece) continue;
+          const int pads = (int)((kChunkSlots - end % kChunkSlots) % kChunkSlots);
+          for (int j = l; j < pads; j += 8) put(i, p, rl, len + j, col, 0.f, false);
+          if (last_piece)  // chunks up to a whole quad
+            for (int64_t x = (end + pads) / kChunkSlots * kChunkSlots + l; x < a.n_heavy_chunks * kChunkSlots; x += 8)
+              put_slot(ss, a.heavy_chunk0 + x / kChunkSlots, (int)(x % kChunkSlots),
+                       ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
+        } else if (piece_word[i] & kWidePiece) {
+          for (int j = len + l; j < (len + kChunkSlots - 1) / kChunkSlots * kChunkSlots; j += 8)
+            put(i, p, rl, j, col, 0.f, false);
+        }
       }
     }
   }
@@ -981,6 +992,12 @@ struct Blob {  // bump allocator over one device allocation
     return off;
   }
 };
+
+// data[i] += seq_base[i / kScanSeq]: the last step of the device-wide exclusive scan
+__global__ void k_add_seq_base(int64_t n, int32_t* data, const int32_t* __restrict__ seq_base) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) data[i] += seq_base[i / kScanSeq];
+}
 
 // Exclusive scan of data[0 .. n) in place on `stream`; data must have room for n rounded up to whole sequences
 // (the tail is zeroed here), seq_base for one int per sequence plus one.
@@ -1362,8 +1379,8 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       const size_t a_row_slot = ba.reserve(want_heavy ? sizeof(int32_t) * ((size_t)s.n_rows + 1) : 0);
       const size_t b_cols = bb.reserve(sizeof(int32_t) * (size_t)(h->S + T + kChunkSlots));
       const size_t b_vals = bb.reserve(sizeof(float) * (size_t)(h->S + T + kChunkSlots));
-      h->blobs[0] = alloc(ba.size, actx, stream);
-      h->blobs[1] = alloc(bb.size, actx, stream);
+      h->blobs[0] = scratch_alloc(ba.size, alloc, actx, stream);
+      h->blobs[1] = scratch_alloc(bb.size, alloc, actx, stream);
       if (!h->blobs[0] || !h->blobs[1]) { st = SPTIR_ERR_ALLOC; goto fail; }
       h->device_bytes += ba.size + bb.size;
       char* a0 = (char*)h->blobs[0];
@@ -1410,20 +1427,20 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     if (n_cells > 0) {
       hipLaunchKernelGGL(k_cell_bounds, dim3((unsigned)((n_bounds + 255) / 256)), dim3(256), 0, stream, cs,
                          h->bucket_row_ptr, h->rem_part_ptr, h->row_ids, d_bounds);
-      hipLaunchKernelGGL(k_deal, dim3((unsigned)((n_parts + kDealParts - 1) / kDealParts)), dim3(256),
+      hipLaunchKernelGGL(k_deal, dim3((unsigned)((n_parts + kDealParts - 1) / kDealParts)), dim3(8 * kDealParts),
                          (sizeof(int) * kDealParts) << cs.log2_rb, stream, cs, n_parts, d_bounds, h->row_len, d_cell_chunks,
                          d_dealt, d_queue_len);
       hipLaunchKernelGGL(k_group_scan, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, stream, cs, n_groups,
                          d_cell_chunks, d_group_tot);
     }
-    hipLaunchKernelGGL(k_totals, dim3(1), dim3(kOneBlock), 0, stream, n_cells > 0 ? n_groups : 0, d_group_tot, n_spans,
+    hipLaunchKernelGGL(k_totals, dim3(4), dim3(kOneBlock), 0, stream, n_cells > 0 ? n_groups : 0, d_group_tot, n_spans,
                        sums, (long long*)(host.base + h_report2));
     BUILD_HIP(hipGetLastError());
     BUILD_HIP(hipStreamSynchronize(stream));
     const long long* report2 = (const long long*)(host.base + h_report2);
     const long long n_chunks = report2[0];
-    h->n_heavy_nnz = report2[1];
-    const int64_t max_list_len = report2[4];
+    h->n_heavy_nnz = report2[4];
+    const int64_t max_list_len = report2[1];
     // the lists' chunks come first in the stream (each list a whole number of quads), then the heavy chunks
     // (report2[3]: slots of the heavy sequence)
     const int64_t n_heavy_chunks = (chunks_of_slots(report2[3]) + kChunksPerQuad - 1) / kChunksPerQuad * kChunksPerQuad;
@@ -1454,7 +1471,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       const size_t c_stream = bc.reserve(sizeof(int32_t) * ((h->compact_stream ? 2 : 3) - (one_value_per_row ? 1 : 0)) *
                                          kChunkSlots * (size_t)(all_chunks ? all_chunks : 1));
       const size_t c_partial = bc.reserve(heavy ? sizeof(float) * kPartialFeat * (size_t)h->n_partial_rows : 0);
-      h->blobs[2] = alloc(bc.size, actx, stream);
+      h->blobs[2] = scratch_alloc(bc.size, alloc, actx, stream);
       if (!h->blobs[2]) { st = SPTIR_ERR_ALLOC; goto fail; }
       h->device_bytes += bc.size;
       char* c0 = (char*)h->blobs[2];
@@ -1492,17 +1509,20 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       a.inv_w = 1.0 / (double)(s.w > 0 ? s.w : 1);
       a.dealt = d_dealt; a.unit = d_unit; a.cell_first_chunk = d_cell_chunks; a.group_first_chunk = d_group_tot;
       a.heavy_chunk0 = n_chunks; a.heavy_slots = report2[3]; a.n_heavy_chunks = n_heavy_chunks;
-      // rows per workgroup: at most 64 (so that a long row is a small part of the grid), fewer where the grid would have
-      // less than four workgroups per CU, or where the pieces of that many rows would not fit the LDS arrays
-      a.log2_rows = 6;
-      while (a.log2_rows > 2 && (s.n_rows >> a.log2_rows) < 1024) --a.log2_rows;
+      // Entries per workgroup: 512 give a medium graph's grid eight workgroups per CU; large inputs take up to 4096, which
+      // share the search and the pieces' data among more entries.  Rows per block: about what those entries belong to.
+      a.nnz = csr->nnz;
+      a.per_wg = (int32_t)std::min<int64_t>(4096, std::max<int64_t>(512, csr->nnz / 8192 / 512 * 512));
+      a.log2_rows = 0;
+      while (a.log2_rows < 6 && ((int64_t)csr->nnz << a.log2_rows) < (int64_t)a.per_wg * s.n_rows) ++a.log2_rows;
       while (a.log2_rows > 0 && ((int64_t)s.c << a.log2_rows) > kCopyPieces) --a.log2_rows;
       const int pieces = (int)std::min<int64_t>((int64_t)s.c << a.log2_rows, kCopyPieces);
-      hipLaunchKernelGGL(k_copy, dim3((unsigned)(((int64_t)s.n_rows + (1 << a.log2_rows) - 1) >> a.log2_rows)), dim3(256),
-                         sizeof(int) * kCopyWords * (size_t)pieces, stream, s, cs, ss, a, pieces);
+      const int64_t n_wg = std::max<int64_t>(1, (csr->nnz + a.per_wg - 1) / a.per_wg);
+      hipLaunchKernelGGL(k_copy, dim3((unsigned)n_wg), dim3(256), sizeof(int) * kCopyWords * (size_t)pieces, stream, s, cs,
+                         ss, a, pieces);
     }
     if (n_parts > 0)
-      hipLaunchKernelGGL(k_list_ends, dim3((unsigned)((n_parts + 31) / 32)), dim3(256), 0, stream, cs, ss, n_parts,
+      hipLaunchKernelGGL(k_list_ends, dim3((unsigned)((n_parts + 7) / 8)), dim3(64), 0, stream, cs, ss, n_parts,
                          d_cell_chunks, d_group_tot, d_queue_len, h->rb_chunk_ptr, (int64_t)n_chunks);
     BUILD_HIP(hipGetLastError());
     if (n_parts == 0) {  // no lists: the one element of rb_chunk_ptr
@@ -1524,7 +1544,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     }
     if (opt.release_canonical && with_spmm_plan) {
       // sptir_spmm reads the stream only
-      free_(h->blobs[1], actx);
+      scratch_free(h->blobs[1], free_, actx);
       h->blobs[1] = nullptr;
       h->cols = nullptr; h->vals = nullptr;
       h->device_bytes -= h->canonical_bytes;

@@ -69,21 +69,6 @@ struct SddmmArgs {
   const int32_t* xcd_run_ptr;      // [9]: the runs of XCD x are xcd_run_ptr[x] .. xcd_run_ptr[x+1]
 };
 
-// largest r in [0, n_rows) with indptr[r] <= e (e < nnz, so it exists); the lanes of a wavefront probe 64 places at a
-// time (three dependent loads for 200,000 rows where halving takes 18)
-__device__ __forceinline__ int row_of_entry(const int32_t* __restrict__ indptr, int n_rows, int64_t e, int lane) {
-  int lo = 0, hi = n_rows;  // invariant: indptr[lo] <= e < indptr[hi]
-  while (hi - lo > 1) {
-    const int step = (hi - lo + 63) >> 6;
-    const int64_t at = lo + (int64_t)(lane + 1) * step;
-    const bool below = at < hi && (int64_t)indptr[at] <= e;
-    const int n = __popcll(__ballot(below));  // (ascending: the lanes below come first)
-    lo += n * step;
-    hi = (int)min((int64_t)hi, (int64_t)lo + step);
-  }
-  return lo;
-}
-
 __device__ __forceinline__ float dot4(const float4& a, const float4& b, float acc) {
   acc = fmaf(a.x, b.x, acc);
   acc = fmaf(a.y, b.y, acc);

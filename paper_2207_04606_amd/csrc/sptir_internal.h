@@ -113,6 +113,8 @@ void* default_alloc(size_t bytes, void* ctx, void* stream);
 // earlier calls have released (api.hip).  scratch_free takes back what scratch_alloc gave.
 void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream);
 void scratch_free(void* p, sptir_free_fn free_, void* actx);
+// the same for the blocks of a handle that launches on any stream may still be reading
+void handle_free(void* const* blobs, int n, sptir_free_fn free_, void* actx);
 void default_free(void* p, void* ctx);
 
 // sptir_hyb_build_ex; `opt` is complete (defaults filled in by the caller)

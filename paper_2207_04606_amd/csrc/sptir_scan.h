@@ -19,6 +19,21 @@ __device__ __forceinline__ int lower_bound_col(const int32_t* __restrict__ indic
   return lo;
 }
 
+// largest r in [0, n_rows) with indptr[r] <= e (e < nnz, so it exists); the lanes of a wavefront probe 64 places at a
+// time (three dependent loads for 200,000 rows where halving takes 18)
+__device__ __forceinline__ int row_of_entry(const int32_t* __restrict__ indptr, int n_rows, int64_t e, int lane) {
+  int lo = 0, hi = n_rows;  // invariant: indptr[lo] <= e < indptr[hi]
+  while (hi - lo > 1) {
+    const int step = (hi - lo + 63) >> 6;
+    const int64_t at = lo + (int64_t)(lane + 1) * step;
+    const bool below = at < hi && (int64_t)indptr[at] <= e;
+    const int n = __popcll(__ballot(below));  // (ascending: the lanes below come first)
+    lo += n * step;
+    hi = (int)min((int64_t)hi, (int64_t)lo + step);
+  }
+  return lo;
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T v, int lane) {
 #pragma unroll
