@@ -94,13 +94,14 @@ static_assert(kFlagSlots * kFlagStride == kValidationWords, "the words a caller 
 __device__ __forceinline__ unsigned long long* flag_slot(unsigned long long* flags) {
   return flags + (blockIdx.x & (kFlagSlots - 1)) * kFlagStride;
 }
-__global__ void k_validate_rows(int32_t n_rows, int64_t nnz, const int32_t* __restrict__ indptr,
-                                const int32_t* __restrict__ indices, const int32_t* __restrict__ values,
-                                unsigned long long* flags) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+__device__ __forceinline__ void validate_rows(int n_wg, int wg, int32_t n_rows, int64_t nnz,
+                                              const int32_t* __restrict__ indptr,
+                                              const int32_t* __restrict__ indices,
+                                              const int32_t* __restrict__ values, unsigned long long* flags) {
+  const int64_t stride = (int64_t)n_wg * blockDim.x;
   unsigned int legal_descents = 0, legal_changes = 0;
   bool bad = false;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n_rows; r += stride) {
+  for (int64_t r = (int64_t)wg * blockDim.x + threadIdx.x; r < n_rows; r += stride) {
     int64_t a = indptr[r], b = indptr[r + 1];
     const bool bad_here = (a < 0) || (b > nnz) || (a > b) || (r == 0 && a != 0) || (r == n_rows - 1 && b != nnz);
     bad |= bad_here;
@@ -137,17 +138,16 @@ __device__ __forceinline__ int changes_of(int prev, const int4& a, const int4& b
          (b.z != b.y) + (b.w != b.z);
 }
 
-__global__ __launch_bounds__(256) void k_validate_elems(int64_t nnz, int32_t n_cols, int vec,
-                                                        const int32_t* __restrict__ indices,
-                                                        const int32_t* __restrict__ values,
-                                                        unsigned long long* flags) {
+__device__ __forceinline__ void validate_elems(int n_wg, int wg, int64_t nnz, int32_t n_cols, int vec,
+                                               const int32_t* __restrict__ indices,
+                                               const int32_t* __restrict__ values, unsigned long long* flags) {
   constexpr int kPer = 8;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x * kPer;
+  const int64_t stride = (int64_t)n_wg * blockDim.x * kPer;
   const int lane = threadIdx.x & 63;
   const bool with_values = values != nullptr;
   unsigned int descents = 0, changes = 0;
   bool range = false;
-  int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * kPer;
+  int64_t q = ((int64_t)wg * blockDim.x + threadIdx.x) * kPer;
   for (; q + kPer <= nnz; q += stride) {  // whole groups
     const int64_t q_prev = q > 0 ? q - 1 : 0;
     const int4 c0 = load4(indices + q, vec), c1 = load4(indices + q + 4, vec);
@@ -186,6 +186,16 @@ __global__ __launch_bounds__(256) void k_validate_elems(int64_t nnz, int32_t n_c
   }
 }
 
+// Both checks in one launch: the first row_wgs workgroups take the rows, the others the entries.
+__global__ __launch_bounds__(256) void k_validate(int row_wgs, int32_t n_rows, int64_t nnz, int32_t n_cols, int vec,
+                                                  const int32_t* __restrict__ indptr,
+                                                  const int32_t* __restrict__ indices,
+                                                  const int32_t* __restrict__ values, unsigned long long* flags) {
+  const int wg = (int)blockIdx.x;
+  if (wg < row_wgs) validate_rows(row_wgs, wg, n_rows, nnz, indptr, indices, values, flags);
+  else validate_elems((int)gridDim.x - row_wgs, wg - row_wgs, nnz, n_cols, vec, indices, values, flags);
+}
+
 // row_val[r] = the value of row r's first entry (0 for an empty row)
 __global__ void k_row_values(int32_t n_rows, const int32_t* __restrict__ indptr, const float* __restrict__ values,
                              float* row_val) {
@@ -219,6 +229,30 @@ __global__ __launch_bounds__(kBuildBlock) void k_count(BuildShape s, const int32
   __syncthreads();
   if (tid < s.nb) counts[((int64_t)p * s.nb + tid) * s.NB + rb] = hist[tid];
   if (tid == 0) rem_nnz[(int64_t)p * s.NB + rb] = (int64_t)sum_nnz;
+}
+
+// The counts become positions, a workgroup per sequence; their totals and (the last workgroup) the verdict's words go to
+// the host's memory, where it reads them once the stream has drained.
+struct FirstReport {
+  unsigned long long* flags;  // [kValidationWords]
+  int64_t* rem_nnz;           // [c]
+  int32_t* bins;              // [c][nb]
+};
+__global__ __launch_bounds__(kBuildBlock) void k_first_totals(BuildShape s, int32_t* counts, int64_t* rem_nnz,
+                                                              const unsigned long long* __restrict__ flags,
+                                                              FirstReport report) {
+  __shared__ int bin_sums[kWaves];
+  __shared__ long long nnz_sums[kWaves];
+  const int n_bins = s.c * s.nb, seq = (int)blockIdx.x;
+  if (seq < n_bins) {
+    const int total = scan_sequence(counts + (int64_t)seq * s.NB, s.NB, bin_sums);
+    if (threadIdx.x == 0) report.bins[seq] = total;
+  } else if (seq < n_bins + s.c) {
+    const long long total = scan_sequence((long long*)rem_nnz + (int64_t)(seq - n_bins) * s.NB, s.NB, nnz_sums);
+    if (threadIdx.x == 0) report.rem_nnz[seq - n_bins] = total;
+  } else {
+    for (int i = threadIdx.x; i < kValidationWords; i += kBuildBlock) report.flags[i] = flags[i];
+  }
 }
 
 // --------------------------------------------------------------------- place
@@ -369,13 +403,13 @@ __device__ __forceinline__ unsigned min_of_8(unsigned v) {  // over the eight la
 
 // Eight lanes per (group, partition of its phase), one per queue.  The lengths are fetched side by side into LDS first;
 // what remains serial, a piece after the other to the shortest queue, runs on registers.  (A thread per partition that
-// read a length at a time, once to count and once more to fill, took 35 + 93 us on 169,343 rows; this takes 9.)
+// read a length at a time, once to count and once more to fill, took 35 + 93 us on 169,343 rows; this takes 15.)
 // Writes the chunk counts of the partition's cells, a word per piece (see above) and the entries of every queue.
 constexpr int kDealParts = 8;  // partitions per workgroup, a wavefront
 __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n_parts, const int32_t* __restrict__ bin_rb_ptr,
                                               const int32_t* __restrict__ row_len, long long* __restrict__ cell_chunks,
                                               uint32_t* __restrict__ dealt, int32_t* __restrict__ queue_len) {
-  extern __shared__ int piece_len[];                 // [kDealParts][rows of a row block]
+  extern __shared__ int piece_len[];                 // [kDealParts][rows of a row block]: lengths, then positions
   __shared__ int before[kDealParts][kMaxBins + 1];   // pieces before a bin, widest bin first
   __shared__ int first[kDealParts][kMaxBins];        // first piece of a bin
   __shared__ int wide[kDealParts][kMaxBins];         // chunks cut wide so far
@@ -387,6 +421,7 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
   const int p = phase * cs.ppg + p_local;
   const bool real = t < n_parts && p < cs.c;  // (the last phase may have fewer partitions)
   int* len_of = piece_len + (part << cs.log2_rb);
+  int* piece_at = len_of + (kDealParts << cs.log2_rb);
 
   int count[kMaxBins / 8], mine = 0;
 #pragma unroll
@@ -423,14 +458,15 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
       if (before[part][b + step] <= i) b += step;
     return first[part][b] + (i - before[part][b]);
   };
-  long long to_deal = 0;  // entries not dealt yet
+  unsigned to_deal = 0;  // entries not dealt yet (fewer than 2^31)
   for (int i = l; i < n; i += 8) {
-    const int len = row_len[piece(i)];
+    const int q = piece(i), len = row_len[q];
     len_of[i] = len;
-    if (len <= cs.long_len) to_deal += len;
+    piece_at[i] = q;
+    if (len <= cs.long_len) to_deal += (unsigned)len;
   }
 #pragma unroll
-  for (int d = 1; d < 8; d <<= 1) to_deal += __shfl_xor(to_deal, d, 8);
+  for (int d = 1; d < 8; d <<= 1) to_deal += (unsigned)__shfl_xor((int)to_deal, d, 8);
   __syncthreads();
 
   unsigned load = 0;  // entries of queue l
@@ -438,10 +474,10 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
   for (int i = 0; i < n; ++i) {
     const int next = len_of[i + 1 < n ? i + 1 : i];
     if (len <= cs.long_len) {
-      const long long share = (to_deal + 7) >> 3;
-      to_deal -= len;
+      const unsigned share = (to_deal + 7) >> 3;
+      to_deal -= (unsigned)len;
       uint32_t word;
-      if (len > kChunkSlots && len > share) {
+      if (len > kChunkSlots && (unsigned)len > share) {
         const int at = cs.nb - 1 - bin_of_length(len, cs.k);
         const int w = wide[part][at];
         if (l == 0) wide[part][at] = w + chunks_of_length(len);
@@ -459,7 +495,7 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
 #pragma unroll
   for (int d = 1; d < 8; d <<= 1) longest = max(longest, (unsigned)__shfl_xor((int)longest, d, 8));
   __syncthreads();
-  for (int i = l; i < n; i += 8) dealt[piece(i)] = (uint32_t)len_of[i];  // (a heavy piece's word is not looked at)
+  for (int i = l; i < n; i += 8) dealt[piece_at[i]] = (uint32_t)len_of[i];  // (a heavy piece's word is not looked at)
   if (t < n_parts) {
     long long* cell = cell_chunks + grp * cells_per_group(cs) + (int64_t)p_local * cells_per_part(cs);
     for (int bin = l; bin < cs.nb; bin += 8) cell[bin] = wide[part][cs.nb - 1 - bin];
@@ -528,38 +564,35 @@ __device__ __forceinline__ void put_slot(const StreamShape& ss, int64_t chunk, i
   if (!ss.compact) quad[(n_arrays - 1) * kQuadSlots + at] = row_word;
 }
 
-// Eight lanes per (group, partition): the slots past the end of each queue; the first partition of a group also writes
-// the chunks that round the group up to whole quads, and rb_chunk_ptr.
-__global__ __launch_bounds__(64) void k_list_ends(CellShape cs, StreamShape ss, int64_t n_parts,
+// One wavefront per (group, partition), a lane per slot of a chunk: the slots past the end of each queue; the first
+// partition of a group also writes the chunks that round the group up to whole quads, and rb_chunk_ptr.
+__global__ __launch_bounds__(256) void k_list_ends(CellShape cs, StreamShape ss, int64_t n_parts,
                                                    const long long* __restrict__ cell_first_chunk,
                                                    const long long* __restrict__ group_first_chunk,
                                                    const int32_t* __restrict__ queue_len, int64_t* rb_chunk_ptr,
                                                    int64_t n_chunks_total) {
-  const int l = threadIdx.x & 7;
-  const int64_t t = (int64_t)blockIdx.x * (blockDim.x >> 3) + (threadIdx.x >> 3);
+  const int lane = threadIdx.x & 63;
+  const int64_t t = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (t >= n_parts) return;
   const int64_t grp = t / cs.ppg;
   const int p_local = (int)(t % cs.ppg);
   const long long* cells = cell_first_chunk + grp * cells_per_group(cs);
   const int64_t group_first = group_first_chunk[grp];
   const long long* queue_cell = cells + (int64_t)p_local * cells_per_part(cs) + cs.nb;
-  const int load = queue_len[t * 8 + l];
+  const int from = queue_len[t * 8 + (lane >> 3)];
   const int64_t chunk0 = group_first + queue_cell[0];
   const int n_chunks = (int)(queue_cell[1] - queue_cell[0]);
+  int shortest = from;
 #pragma unroll
-  for (int g = 0; g < 8; ++g) {
-    const int from = __shfl(load, g, 8);
-    for (int ck = from >> 3; ck < n_chunks; ++ck)  // zeros that belong to no row
-      if (ck * 8 + l >= from)
-        put_slot(ss, chunk0 + ck, g * 8 + l, ss.compact ? (int32_t)(3u << 28) : 0, 0, (3 << 16) | (1 << 23));
-  }
+  for (int d = 8; d < 64; d <<= 1) shortest = min(shortest, __shfl_xor(shortest, d, 64));
+  for (int ck = shortest >> 3; ck < n_chunks; ++ck)  // zeros that belong to no row
+    if (ck * 8 + (lane & 7) >= from)
+      put_slot(ss, chunk0 + ck, lane, ss.compact ? (int32_t)(3u << 28) : 0, 0, (3 << 16) | (1 << 23));
   if (p_local != 0) return;
-  const int64_t used = cells[cells_per_group(cs) - 1];
-  for (int64_t ck = used; ck % kChunksPerQuad != 0; ++ck)  // contribute nothing, hand nothing over
-    for (int i = l; i < kChunkSlots; i += 8)
-      put_slot(ss, group_first + ck, i, ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
-  if (l == 0) rb_chunk_ptr[grp] = group_first;
-  if (l == 0 && grp == 0) rb_chunk_ptr[n_parts / cs.ppg] = n_chunks_total;
+  for (int64_t ck = cells[cells_per_group(cs) - 1]; ck % kChunksPerQuad != 0; ++ck)  // contribute nothing
+    put_slot(ss, group_first + ck, lane, ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
+  if (lane == 0) rb_chunk_ptr[grp] = group_first;
+  if (lane == 0 && grp == 0) rb_chunk_ptr[n_parts / cs.ppg] = n_chunks_total;
 }
 
 // ------------------------------------------------------------ heavy pieces
@@ -747,7 +780,8 @@ __global__ __launch_bounds__(kBuildBlock) void k_row_slot_fill(RowSlotArgs a) {
 // workgroup takes `per_wg` consecutive entries, whatever rows they belong to, so that the longest row costs no more than
 // its share; it walks them by blocks of 2^log2_rows rows.  What is the same for all entries of a piece (where it goes) is
 // put into LDS first, then a lane per entry finds its row by a search over the rows' starts and its partition from its
-// column.
+// column.  169,343 rows, 1.17 M entries in four partitions: 27 us, of which 18 are the chain of loads up to the pieces
+// (three kernels with a wavefront per 64 pieces took 78 us, most of it in a few wavefronts with long pieces).
 struct CopyArgs {
   const int32_t *indptr, *indices;
   const float* values;
@@ -767,10 +801,11 @@ struct CopyArgs {
 };
 constexpr int kCopyPieces = 1024;  // most pieces a workgroup holds at a time
 constexpr int kCopyWords = 6;      // LDS words per piece
+constexpr int kCopyLog2Rows = 7;   // at most 128 rows a block
 
 __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, StreamShape ss, CopyArgs a, int pieces_at_a_time) {
   extern __shared__ int lds[];
-  __shared__ int row_lo[65];
+  __shared__ int row_lo[(1 << kCopyLog2Rows) + 1];
   const int log2_rows = a.log2_rows, n_rows_here = 1 << log2_rows;
   int* piece_lo = lds;                                                 // first entry in the input
   int* piece_len = piece_lo + pieces_at_a_time;
@@ -842,7 +877,7 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
   for (int64_t at = first; at < last;) {
     r0 = row_of_entry(a.indptr, s.n_rows, at, tid & 63);
     __syncthreads();  // (the last block's rows are no longer read)
-    if (tid <= n_rows_here) row_lo[tid] = a.indptr[tid < s.n_rows - r0 ? r0 + tid : s.n_rows];
+    for (int i = tid; i <= n_rows_here; i += 256) row_lo[i] = a.indptr[i < s.n_rows - r0 ? r0 + i : s.n_rows];
     __syncthreads();
     const unsigned e_begin = (unsigned)at;
     const unsigned e_end = row_lo[n_rows_here] < last ? (unsigned)row_lo[n_rows_here] : (unsigned)last;
@@ -851,15 +886,26 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
       const int np = s.c - p0 < parts_at_a_time ? s.c - p0 : parts_at_a_time;
       if (p0 > 0) __syncthreads();  // (the pieces of the last turn are no longer read)
       for (int i = tid; i < np << log2_rows; i += 256) {
-        const int p = p0 + (i >> log2_rows), rl = i & (n_rows_here - 1), r = r0 + rl;
-        int lo = 0, len = 0;
-        if (rl < s.n_rows - r0) row_piece(s, a.indptr, a.bound, r, p, &lo, &len);
+        const int p = p0 + (i >> log2_rows), rl = i & (n_rows_here - 1);
+        if (rl >= s.n_rows - r0) { piece_len[i] = 0; continue; }
+        const int r = r0 + rl;
+        // (everything that the row alone decides is on its way before the piece's position is needed)
+        const int32_t q = a.piece_of[(int64_t)p * s.n_rows + r];
+        int lo, len;
+        row_piece(s, a.indptr, a.bound, r, p, &lo, &len);
+        int64_t group_first = 0;
+        const long long* cell = nullptr;
+        if (with_stream) {
+          const int64_t grp = (int64_t)(p / cs.ppg) * cs.n_rb + (r >> cs.log2_rb);
+          cell = a.cell_first_chunk + grp * cells_per_group(cs) + (int64_t)(p % cs.ppg) * cells_per_part(cs);
+          group_first = a.group_first_chunk[grp];
+        }
         piece_lo[i] = lo;
         piece_len[i] = len;
         if (len <= 0) continue;
-        const int64_t q = a.piece_of[(int64_t)p * s.n_rows + r];
         const int bin = bin_of_length(len, s.k);
         const int64_t b = (int64_t)p * (s.k + 1) + bin;
+        piece_last[i] = a.indices[lo + len - 1];
         piece_dst[i] = bin <= s.k ? (uint32_t)(a.bucket_slot_ptr[b] + ((q - a.bucket_row_ptr[b]) << bin))
                                   : (uint32_t)(a.S + a.rem_ptr[q - a.R]);
         if (!with_stream) continue;
@@ -867,11 +913,10 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
           piece_word[i] = 0;
           piece_chunk[i] = (int)(uint32_t)a.unit[q];
         } else {
+          const int64_t queue = cell[cs.nb], wide = cell[bin];
           const uint32_t word = a.dealt[q];
-          const int64_t grp = (int64_t)(p / cs.ppg) * cs.n_rb + (r >> cs.log2_rb);
-          const long long* cell = a.cell_first_chunk + grp * cells_per_group(cs) + (int64_t)(p % cs.ppg) * cells_per_part(cs);
           piece_word[i] = word;
-          piece_chunk[i] = (int)(a.group_first_chunk[grp] + cell[(word & kWidePiece) ? bin : cs.nb]);
+          piece_chunk[i] = (int)(group_first + ((word & kWidePiece) ? wide : queue));
         }
       }
       __syncthreads();
@@ -898,44 +943,35 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
           if (p < p0 || p >= p0 + np) continue;
           const int i = ((p - p0) << log2_rows) + rl;
           const int j = (int)(e - (unsigned)piece_lo[i]);
+          const int len = piece_len[i];
           const uint32_t dst = piece_dst[i] + (uint32_t)j;
           a.cols[dst] = col[u];
           a.vals[dst] = val[u];
-          if (j == piece_len[i] - 1) piece_last[i] = col[u];
-          if (with_stream) put(i, p, rl, j, col[u], val[u], true);
-        }
-      }
-      __syncthreads();
-      // Pads, eight lanes per piece that ends here: of a bucket row they repeat the last column and hold +0.0f; of the
-      // last chunk of a piece cut wide and of a heavy piece that no other follows in its chunk they repeat it too, but
-      // are marked.
-      const int l = tid & 7;
-      for (int i = tid >> 3; i < np << log2_rows; i += 256 / 8) {
-        const int len = piece_len[i];
-        const unsigned end_at = (unsigned)piece_lo[i] + (unsigned)len;
-        if (len <= 0 || end_at <= e_begin || end_at > e_end) continue;
-        const int bin = bin_of_length(len, s.k);
-        const int32_t col = piece_last[i];
-        if (bin <= s.k)
-          for (int j = len + l; j < (1 << bin); j += 8) {
-            a.cols[piece_dst[i] + (uint32_t)j] = col;
-            a.vals[piece_dst[i] + (uint32_t)j] = 0.f;
+          // Pads: number j of a piece is written with its entry j (a bucket row is less than half pads).  Those of a bucket
+          // row repeat the last column and hold +0.0f.
+          const int bin = bin_of_length(len, s.k);
+          if (bin <= s.k && j < (1 << bin) - len) {
+            a.cols[dst + (uint32_t)len] = piece_last[i];
+            a.vals[dst + (uint32_t)len] = 0.f;
           }
-        if (!with_stream) continue;
-        const int p = p0 + (i >> log2_rows), rl = i & (n_rows_here - 1);
-        if (len > cs.long_len) {
-          const int64_t end = (int64_t)piece_chunk[i] + len;
-          const bool last_piece = end + (gapless ? 0 : (kChunkSlots - len % kChunkSlots) % kChunkSlots) == a.heavy_slots;
-          if (gapless && !last_piece) continue;
-          const int pads = (int)((kChunkSlots - end % kChunkSlots) % kChunkSlots);
-          for (int j = l; j < pads; j += 8) put(i, p, rl, len + j, col, 0.f, false);
-          if (last_piece)  // chunks up to a whole quad
-            for (int64_t x = (end + pads) / kChunkSlots * kChunkSlots + l; x < a.n_heavy_chunks * kChunkSlots; x += 8)
-              put_slot(ss, a.heavy_chunk0 + x / kChunkSlots, (int)(x % kChunkSlots),
-                       ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
-        } else if (piece_word[i] & kWidePiece) {
-          for (int j = len + l; j < (len + kChunkSlots - 1) / kChunkSlots * kChunkSlots; j += 8)
-            put(i, p, rl, j, col, 0.f, false);
+          if (!with_stream) continue;
+          put(i, p, rl, j, col[u], val[u], true);
+          // In the stream the last chunk of a piece cut wide, and of a heavy piece that no other follows in its chunk, is
+          // filled with marked slots that repeat the last column too; the last heavy piece also fills its quad.
+          int pads = 0;
+          if (len > cs.long_len) {
+            const int64_t end = (int64_t)piece_chunk[i] + len;
+            const int to_chunk = (int)((kChunkSlots - end % kChunkSlots) % kChunkSlots);
+            const bool last_piece = end + (gapless ? 0 : to_chunk) == a.heavy_slots;
+            if (!gapless || last_piece) pads = to_chunk;
+            if (last_piece)
+              for (int64_t x = end + to_chunk + j; x < a.n_heavy_chunks * kChunkSlots; x += len)
+                put_slot(ss, a.heavy_chunk0 + x / kChunkSlots, (int)(x % kChunkSlots),
+                         ss.compact ? (int32_t)0xF0000000u : 0, 0, -1);
+          } else if (piece_word[i] & kWidePiece) {
+            pads = (kChunkSlots - len % kChunkSlots) % kChunkSlots;
+          }
+          for (int k = j; k < pads; k += len) put(i, p, rl, len + k, piece_last[i], 0.f, false);
         }
       }
     }
@@ -1022,14 +1058,12 @@ void pinned_release(PinnedBuf b) { pinned_pool().release(b); }
 
 void launch_validation(const sptir_csr_t* csr, bool with_values, unsigned long long* flags, hipStream_t stream) {
   const int32_t* value_bits = with_values ? (const int32_t*)csr->values : nullptr;
-  if (csr->n_rows > 0)
-    hipLaunchKernelGGL(k_validate_rows, dim3((unsigned)std::min<int64_t>(((int64_t)csr->n_rows + 255) / 256, 4096)),
-                       dim3(256), 0, stream, csr->n_rows, csr->nnz, csr->indptr, csr->indices, value_bits, flags);
-  if (csr->nnz > 0)
-    hipLaunchKernelGGL(k_validate_elems, dim3((unsigned)std::min<int64_t>((csr->nnz + 2047) / 2048, 8192)), dim3(256), 0,
-                       stream, csr->nnz, csr->n_cols,
-                       (int)((((uintptr_t)csr->indices | (uintptr_t)csr->values) & 15) == 0), csr->indices, value_bits,
-                       flags);
+  const int row_wgs = (int)std::min<int64_t>(((int64_t)csr->n_rows + 255) / 256, 4096);
+  const int elem_wgs = (int)std::min<int64_t>((csr->nnz + 2047) / 2048, 8192);
+  if (row_wgs + elem_wgs > 0)
+    hipLaunchKernelGGL(k_validate, dim3((unsigned)(row_wgs + elem_wgs)), dim3(256), 0, stream, row_wgs, csr->n_rows,
+                       csr->nnz, csr->n_cols, (int)((((uintptr_t)csr->indices | (uintptr_t)csr->values) & 15) == 0),
+                       csr->indptr, csr->indices, value_bits, flags);
 }
 
 sptir_status_t validation_verdict(const unsigned long long* flag_slots, bool* one_value_per_row) {
@@ -1191,13 +1225,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
   // for everything that crosses to or from the host (pageable memory would make every small copy a blocking one)
   const size_t nbk = (size_t)(s.NB ? s.NB : 1);
   Blob tmp;
-  // (flags, tot_rnnz and tot_bins lie next to each other: one copy brings them to the host)
-  const size_t o_flags = tmp.size;
-  tmp.size += kValidationWords * sizeof(unsigned long long);
-  const size_t o_tot_rnnz = tmp.size;
-  tmp.size += sizeof(int64_t) * (size_t)s.c;
-  const size_t o_tot_bins = tmp.size;
-  const size_t report1_bytes = tmp.reserve(sizeof(int32_t) * (size_t)s.c * s.nb) + sizeof(int32_t) * (size_t)s.c * s.nb;
+  const size_t o_flags = tmp.reserve(kValidationWords * sizeof(unsigned long long));
   const size_t o_counts = tmp.reserve(sizeof(int32_t) * (size_t)s.c * s.nb * nbk);
   const size_t o_rnnz = tmp.reserve(sizeof(int64_t) * (size_t)s.c * nbk);
   const size_t o_bound = tmp.reserve(sizeof(int32_t) * (size_t)(s.c - 1) * (size_t)(s.n_rows ? s.n_rows : 1) + 16);
@@ -1205,7 +1233,9 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       (((int64_t)s.n_rows + kBoundRows - 1) / kBoundRows) * (((int64_t)s.c - 1 + kBoundParts - 1) / kBoundParts);
   if (n_bound_blocks > 0x7FFFFFFF) return SPTIR_ERR_OVERFLOW;
   Blob host;
-  const size_t h_report1 = host.reserve(report1_bytes);
+  const size_t h_flags = host.reserve(kValidationWords * sizeof(unsigned long long));
+  const size_t h_tot_rnnz = host.reserve(sizeof(int64_t) * (size_t)s.c);
+  const size_t h_tot_bins = host.reserve(sizeof(int32_t) * (size_t)s.c * s.nb);
   // (these four reach the device in one copy, into the start of the handle's first allocation)
   Blob ba;
   const size_t a_row_ptr = ba.reserve(sizeof(int64_t) * (size_t)(B + 1));
@@ -1244,19 +1274,18 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     unsigned long long* d_flags = (unsigned long long*)(tmp.base + o_flags);
     int32_t* d_counts = (int32_t*)(tmp.base + o_counts);
     int64_t* d_rnnz = (int64_t*)(tmp.base + o_rnnz);
-    int32_t* d_tot_bins = (int32_t*)(tmp.base + o_tot_bins);
-    int64_t* d_tot_rnnz = (int64_t*)(tmp.base + o_tot_rnnz);
     int32_t* d_bound = (int32_t*)(tmp.base + o_bound);
 
     // ---- validation of the CSR input, and with it (their results are only used if the input is valid, and they
     // read nothing at a position the input names without clamping it) the piece boundaries, histogram and scans
-    const unsigned long long* flag_slots = (const unsigned long long*)(host.base + h_report1);
+    const FirstReport report1{(unsigned long long*)(host.base + h_flags), (int64_t*)(host.base + h_tot_rnnz),
+                              (int32_t*)(host.base + h_tot_bins)};
     bool one_value = false;
-    const int64_t* tot_rnnz = (const int64_t*)(host.base + h_report1 + (o_tot_rnnz - o_flags));
-    const int32_t* tot_bins = (const int32_t*)(host.base + h_report1 + (o_tot_bins - o_flags));
+    const int64_t* tot_rnnz = report1.rem_nnz;
+    const int32_t* tot_bins = report1.bins;
     // (values are only looked at when a value-less stream is an option)
     const int32_t* value_bits = (with_spmm_plan && !opt.keep_values) ? (const int32_t*)csr->values : nullptr;
-    BUILD_HIP(hipMemsetAsync(d_flags, 0, report1_bytes, stream));
+    BUILD_HIP(hipMemsetAsync(d_flags, 0, kValidationWords * sizeof(unsigned long long), stream));
     launch_validation(csr, value_bits != nullptr, d_flags, stream);
     if (s.NB > 0) {
       if (n_bound_blocks > 0)
@@ -1264,13 +1293,10 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
                            csr->indptr, csr->indices, d_bound);
       hipLaunchKernelGGL(k_count, dim3((unsigned)n_pair_blocks), dim3(kBuildBlock), 0, stream, s, csr->indptr,
                          d_bound, d_counts, d_rnnz);
-      hipLaunchKernelGGL(k_scan_sequences<int32_t>, dim3((unsigned)(s.c * s.nb)), dim3(kBuildBlock), 0, stream,
-                         d_counts, s.NB, d_tot_bins);
-      hipLaunchKernelGGL(k_scan_sequences<long long>, dim3((unsigned)s.c), dim3(kBuildBlock), 0, stream,
-                         (long long*)d_rnnz, s.NB, (long long*)d_tot_rnnz);
     }
+    hipLaunchKernelGGL(k_first_totals, dim3((unsigned)(s.c * s.nb + s.c + 1)), dim3(kBuildBlock), 0, stream, s, d_counts,
+                       d_rnnz, d_flags, report1);
     BUILD_HIP(hipGetLastError());
-    BUILD_HIP(hipMemcpyAsync(host.base + h_report1, d_flags, report1_bytes, hipMemcpyDeviceToHost, stream));
     BUILD_HIP(hipStreamSynchronize(stream));
     if (s.n_rows == 0) {
       int32_t* first = (int32_t*)(host.base + h_misc);
@@ -1278,7 +1304,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       BUILD_HIP(hipStreamSynchronize(stream));
       if (*first != 0 || csr->nnz != 0) { st = SPTIR_ERR_INVALID_ARG; goto fail; }
     }
-    st = validation_verdict(flag_slots, &one_value);
+    st = validation_verdict(report1.flags, &one_value);
     if (st != SPTIR_OK) goto fail;
 
     // ---- sizes and the small prefix arrays (host)
@@ -1428,7 +1454,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       hipLaunchKernelGGL(k_cell_bounds, dim3((unsigned)((n_bounds + 255) / 256)), dim3(256), 0, stream, cs,
                          h->bucket_row_ptr, h->rem_part_ptr, h->row_ids, d_bounds);
       hipLaunchKernelGGL(k_deal, dim3((unsigned)((n_parts + kDealParts - 1) / kDealParts)), dim3(8 * kDealParts),
-                         (sizeof(int) * kDealParts) << cs.log2_rb, stream, cs, n_parts, d_bounds, h->row_len, d_cell_chunks,
+                         (sizeof(int) * 2 * kDealParts) << cs.log2_rb, stream, cs, n_parts, d_bounds, h->row_len, d_cell_chunks,
                          d_dealt, d_queue_len);
       hipLaunchKernelGGL(k_group_scan, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, stream, cs, n_groups,
                          d_cell_chunks, d_group_tot);
@@ -1514,7 +1540,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       a.nnz = csr->nnz;
       a.per_wg = (int32_t)std::min<int64_t>(4096, std::max<int64_t>(512, csr->nnz / 8192 / 512 * 512));
       a.log2_rows = 0;
-      while (a.log2_rows < 6 && ((int64_t)csr->nnz << a.log2_rows) < (int64_t)a.per_wg * s.n_rows) ++a.log2_rows;
+      while (a.log2_rows < kCopyLog2Rows && ((int64_t)csr->nnz << a.log2_rows) < (int64_t)a.per_wg * s.n_rows) ++a.log2_rows;
       while (a.log2_rows > 0 && ((int64_t)s.c << a.log2_rows) > kCopyPieces) --a.log2_rows;
       const int pieces = (int)std::min<int64_t>((int64_t)s.c << a.log2_rows, kCopyPieces);
       const int64_t n_wg = std::max<int64_t>(1, (csr->nnz + a.per_wg - 1) / a.per_wg);
@@ -1522,7 +1548,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
                          ss, a, pieces);
     }
     if (n_parts > 0)
-      hipLaunchKernelGGL(k_list_ends, dim3((unsigned)((n_parts + 7) / 8)), dim3(64), 0, stream, cs, ss, n_parts,
+      hipLaunchKernelGGL(k_list_ends, dim3((unsigned)((n_parts + 3) / 4)), dim3(256), 0, stream, cs, ss, n_parts,
                          d_cell_chunks, d_group_tot, d_queue_len, h->rb_chunk_ptr, (int64_t)n_chunks);
     BUILD_HIP(hipGetLastError());
     if (n_parts == 0) {  // no lists: the one element of rb_chunk_ptr

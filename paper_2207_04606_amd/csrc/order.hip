@@ -15,27 +15,32 @@ constexpr int kSortTile = 1024;            // elements per workgroup and pass
 constexpr int kSortRounds = kSortTile / 256;
 constexpr int kDigits = 256;
 
-__global__ void k_order_keys(int64_t n_groups, int32_t n_rb, const int64_t* __restrict__ rb_chunk_ptr,
-                             uint32_t* __restrict__ keys, int32_t* __restrict__ row_blocks) {
-  const int64_t grp = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (grp >= n_groups) return;
-  const int64_t len = rb_chunk_ptr[grp + 1] - rb_chunk_ptr[grp];
-  keys[grp] = 0xFFFFFFFFu - (len < 0xFFFFFFFFll ? (uint32_t)len : 0xFFFFFFFFu);
-  row_blocks[grp] = (int32_t)(grp % n_rb);
-}
+// What a pass sorts: the first one takes list lengths and row block numbers as they come, the later ones what the pass
+// before them wrote.
+struct SortInput {
+  const int64_t* list_ptr;  // first pass: first chunk of every list (NULL otherwise)
+  const uint32_t* keys;
+  const int32_t* vals;
+  __device__ uint32_t key(int64_t at) const {
+    if (!list_ptr) return keys[at];
+    const int64_t len = list_ptr[at + 1] - list_ptr[at];
+    return 0xFFFFFFFFu - (len < 0xFFFFFFFFll ? (uint32_t)len : 0xFFFFFFFFu);
+  }
+  __device__ int32_t val(int64_t at, int i) const { return list_ptr ? i : vals[at]; }
+};
 
 // hist[(launch * 256 + digit) * tiles + tile] = elements of the tile with that digit; workgroup = launch * tiles + tile
-__global__ __launch_bounds__(256) void k_sort_hist(const uint32_t* __restrict__ keys, int32_t n_rb, int tiles,
-                                                   int shift, int32_t* __restrict__ hist) {
+__global__ __launch_bounds__(256) void k_sort_hist(SortInput in, int32_t n_rb, int tiles, int shift,
+                                                   int32_t* __restrict__ hist) {
   __shared__ int count[kDigits];
   const int tile = blockIdx.x % tiles, launch = blockIdx.x / tiles;
   count[threadIdx.x] = 0;
   __syncthreads();
-  const uint32_t* seg = keys + (int64_t)launch * n_rb;
+  const int64_t seg0 = (int64_t)launch * n_rb;
 #pragma unroll
   for (int r = 0; r < kSortRounds; ++r) {
     const int i = tile * kSortTile + r * 256 + threadIdx.x;
-    if (i < n_rb) atomicAdd(&count[(seg[i] >> shift) & 255u], 1);
+    if (i < n_rb) atomicAdd(&count[(in.key(seg0 + i) >> shift) & 255u], 1);
   }
   __syncthreads();
   hist[((int64_t)launch * kDigits + threadIdx.x) * tiles + tile] = count[threadIdx.x];
@@ -44,10 +49,9 @@ __global__ __launch_bounds__(256) void k_sort_hist(const uint32_t* __restrict__ 
 // `hist` scanned per launch (exclusive, digit-major): the first output position of each (digit, tile).  Elements
 // keep their order inside a digit: the tile is walked 256 elements at a time, in order, and inside such a round a
 // lane's rank is the number of lower lanes, then of lower wavefronts, with the same digit.
-__global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t* __restrict__ keys_in,
-                                                      const int32_t* __restrict__ vals_in, int32_t n_rb, int tiles,
-                                                      int shift, const int32_t* __restrict__ hist,
-                                                      uint32_t* __restrict__ keys_out,
+__global__ __launch_bounds__(256) void k_sort_scatter(SortInput in, int32_t n_rb, int tiles, int shift,
+                                                      const int32_t* __restrict__ hist,
+                                                      uint32_t* __restrict__ keys_out /* NULL: the last pass */,
                                                       int32_t* __restrict__ vals_out) {
   __shared__ int base[kDigits];
   __shared__ int wave_cnt[4][kDigits];
@@ -61,8 +65,8 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t* __restrict
   for (int r = 0; r < kSortRounds; ++r) {
     const int i = tile * kSortTile + r * 256 + tid;
     const bool valid = i < n_rb;
-    const uint32_t key = valid ? keys_in[seg0 + i] : 0u;
-    const int32_t val = valid ? vals_in[seg0 + i] : 0;
+    const uint32_t key = valid ? in.key(seg0 + i) : 0u;
+    const int32_t val = valid ? in.val(seg0 + i, i) : 0;
     const int digit = (int)((key >> shift) & 255u);
     unsigned long long peers = __ballot(valid);
 #pragma unroll
@@ -78,7 +82,7 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t* __restrict
       int before = 0;
       for (int w = 0; w < wave; ++w) before += wave_cnt[w][digit];
       const int64_t at = seg0 + base[digit] + before + rank_in_wave;
-      keys_out[at] = key;
+      if (keys_out) keys_out[at] = key;
       vals_out[at] = val;
     }
     __syncthreads();
@@ -121,16 +125,15 @@ sptir_status_t order_row_blocks(const int64_t* rb_chunk_ptr, int32_t n_launches,
   int32_t* vals[2];
   vals[passes % 2] = rb_order;
   vals[1 - passes % 2] = other_vals;
-  hipLaunchKernelGGL(k_order_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, n, n_rb, rb_chunk_ptr,
-                     keys[0], vals[0]);
   for (int pass = 0; pass < passes; ++pass) {
-    const int in = pass % 2, out = 1 - in;
-    hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)(tiles * n_launches)), dim3(256), 0, stream, keys[in], n_rb,
+    const int from = pass % 2, to = 1 - from;
+    const SortInput in{pass == 0 ? rb_chunk_ptr : nullptr, keys[from], vals[from]};
+    hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)(tiles * n_launches)), dim3(256), 0, stream, in, n_rb,
                        (int)tiles, 8 * pass, hist);
     hipLaunchKernelGGL(k_scan_sequences<int32_t>, dim3((unsigned)n_launches), dim3(kBuildBlock), 0, stream, hist,
                        (int32_t)(kDigits * tiles), totals);
-    hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)(tiles * n_launches)), dim3(256), 0, stream, keys[in],
-                       vals[in], n_rb, (int)tiles, 8 * pass, hist, keys[out], vals[out]);
+    hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)(tiles * n_launches)), dim3(256), 0, stream, in, n_rb, (int)tiles,
+                       8 * pass, hist, pass + 1 < passes ? keys[to] : nullptr, vals[to]);
   }
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;

@@ -63,15 +63,12 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T* wave_sums /* [kWaves] 
   return base + incl - v;
 }
 
-// One workgroup per sequence: data[seq*len .. +len) becomes its exclusive
-// prefix, totals[seq] its sum.  A thread scans kScanPerThread consecutive
-// elements itself, so a long sequence costs few workgroup-wide steps.
+// seq[0 .. len) becomes its exclusive prefix; returns its sum.  By one workgroup of kBuildBlock threads; a thread scans
+// kScanPerThread consecutive elements itself, so a long sequence costs few workgroup-wide steps.
 constexpr int kScanPerThread = 8;
 
 template <typename T>
-__global__ __launch_bounds__(kBuildBlock) void k_scan_sequences(T* data, int32_t len, T* totals) {
-  __shared__ T wave_sums[kWaves];
-  T* seq = data + (int64_t)blockIdx.x * len;
+__device__ __forceinline__ T scan_sequence(T* seq, int32_t len, T* wave_sums /* [kWaves] shared */) {
   T carry = 0;
   for (int64_t base = 0; base < len; base += (int64_t)kBuildBlock * kScanPerThread) {
     const int64_t e0 = base + (int64_t)threadIdx.x * kScanPerThread;
@@ -91,7 +88,15 @@ __global__ __launch_bounds__(kBuildBlock) void k_scan_sequences(T* data, int32_t
     }
     carry += tot;
   }
-  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+  return carry;
+}
+
+// One workgroup per sequence: data[seq*len .. +len) becomes its exclusive prefix, totals[seq] its sum.
+template <typename T>
+__global__ __launch_bounds__(kBuildBlock) void k_scan_sequences(T* data, int32_t len, T* totals) {
+  __shared__ T wave_sums[kWaves];
+  const T total = scan_sequence(data + (int64_t)blockIdx.x * len, len, wave_sums);
+  if (threadIdx.x == 0) totals[blockIdx.x] = total;
 }
 
 }  // namespace

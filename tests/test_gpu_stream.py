@@ -7,8 +7,10 @@ The expected triplets come from the CSR input, not from the GPU."""
 import numpy as np
 import pytest
 
+import oracle
 import workloads
-from gpu_helpers import upload
+from gpu_helpers import fetch_hyb, upload
+from hyb_checks import assert_same_hyb
 
 pytestmark = pytest.mark.gpu
 
@@ -189,3 +191,26 @@ def test_stream_holds_every_non_zero_exactly_once(gpu_lib, options, one_value_pe
     if (options or {}).get("heavy_len"):
         lens = np.diff(w.indptr)
         assert info["n_heavy_pieces"] > 0 or lens.max() <= options["heavy_len"]
+
+
+@pytest.mark.parametrize("c,options", [(1, None), (3, {"heavy_len": 64}), (3, {"heavy_len": 9, "wide_stream": 1, "row_block": 256}),
+                                       (1100, {"heavy_len": 5}), (5, {"rounds": 2, "parts_per_launch": 2, "row_block": 8})])
+def test_long_rows_empty_runs_and_many_partitions(gpu_lib, c, options):
+    """Rows as long as one, two and nine workgroups of the copy (512 entries each), one entry more and less, runs of
+    empty rows longer than the blocks it walks, and more partitions than it holds pieces for."""
+    sptir = gpu_lib
+    n_rows, n_cols = 700, 4700
+    deg = np.zeros(n_rows, dtype=np.int64)
+    deg[[0, 1, 2, 3, 200, 201, 202, 330, 699]] = [511, 1, 513, 1024, 4608, 63, 65, 512, 4700]
+    deg[400:560] = np.random.default_rng(3).integers(1, 9, 160)
+    w = workloads.random_csr(n_rows, n_cols, deg, 5, 4)
+    d = upload(w)
+    hyb = sptir.sptir_hyb_build_ex(n_rows, n_cols, d.indptr, d.indices, d.values, c, 6, options)
+    got, info = fetch_hyb(sptir, hyb)
+    assert_same_hyb(got, oracle.hyb_build(n_rows, n_cols, w.indptr, w.indices, w.values, c, 6))
+    rows, cols, vals = decode(sptir, hyb, info, w)
+    want_key = np.repeat(np.arange(n_rows, dtype=np.int64), deg) * n_cols + w.indices
+    o = np.argsort(rows * n_cols + cols, kind="stable")
+    assert np.array_equal((rows * n_cols + cols)[o], want_key), "the stream's (row, column) pairs are not those of A"
+    assert np.array_equal(vals[o], w.values.view(np.int32).astype(np.int64)), "a value differs"
+    hyb.destroy()
