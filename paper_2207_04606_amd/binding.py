@@ -217,7 +217,8 @@ def _hip_runtime():
 
 def _stream_ptr(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # (torch.cuda.current_stream() makes a Stream object: 2.7 us of the 8 that a small call took)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
