@@ -333,10 +333,11 @@ sptir_status_t sptir_roof_fma(int32_t n_workgroups, int32_t iters, float* sink, 
  * sptir_spmm for callers that cannot allocate device memory or let a library do so: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical
  * Y.  The one buffer sptir_spmm needs beyond its inputs and outputs, the partial sums of heavy row pieces
- * (sptir_hyb_info_t.n_heavy_pieces > 0; 128 floats for every heavy piece and every heavy list), does not come
+ * (sptir_hyb_info_t.n_heavy_pieces > 0; 64 to 512 floats for every heavy piece and every heavy list), does not come
  * from the handle here but from a static device array of SPTIR_NOALLOC_SCRATCH_BYTES inside the library, which
  * every GPU the library runs on holds until the process ends.  The call allocates and frees nothing, on any path.
- * A matrix whose partial sums do not fit ((n_heavy_pieces + n_heavy_lists) * 512 bytes exceed the array) is
+ * A matrix whose partial sums do not fit ((n_heavy_pieces + n_heavy_lists) * 512 bytes exceed the array; * 256 bytes,
+ * taken in more sweeps, where the library chose a heavy_len below 2048 and rounds == 0) is
  * refused with SPTIR_ERR_UNSUPPORTED before anything is enqueued, and sptir_last_hip_error() then says by how
  * much.  Every call on one GPU shares that GPU's array: calls that overlap in time on one GPU race (also calls
  * on different handles and different streams); calls ordered by a stream or by the caller are fine.  Nothing in

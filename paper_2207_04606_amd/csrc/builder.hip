@@ -85,6 +85,7 @@ __device__ __forceinline__ int bin_of_length(int l, int k) {
 //           column stored just before it (descents that are legal)
 // Columns ascend strictly inside every row iff flags[2] == flags[3].
 // flags[4]: number of positions q >= 1 whose value differs (as a bit pattern) from the one stored before it
+// flags[6]: entries of the longest row
 // flags[5]: number of non-empty rows whose first value differs from the value stored just before it
 // Every row has one value for all of its entries iff flags[4] == flags[5] (only counted when `values` is given).
 // The counters exist kFlagSlots times, 64 bytes apart, and a wavefront adds to the copy its workgroup id picks:
@@ -99,12 +100,13 @@ __device__ __forceinline__ void validate_rows(int n_wg, int wg, int32_t n_rows, 
                                               const int32_t* __restrict__ indices,
                                               const int32_t* __restrict__ values, unsigned long long* flags) {
   const int64_t stride = (int64_t)n_wg * blockDim.x;
-  unsigned int legal_descents = 0, legal_changes = 0;
+  unsigned int legal_descents = 0, legal_changes = 0, longest = 0;
   bool bad = false;
   for (int64_t r = (int64_t)wg * blockDim.x + threadIdx.x; r < n_rows; r += stride) {
     int64_t a = indptr[r], b = indptr[r + 1];
     const bool bad_here = (a < 0) || (b > nnz) || (a > b) || (r == 0 && a != 0) || (r == n_rows - 1 && b != nnz);
     bad |= bad_here;
+    if (!bad_here) longest = max(longest, (unsigned int)(b - a));
     legal_descents += !bad_here && a < b && a > 0 && indices[a] <= indices[a - 1];
     if (values) legal_changes += !bad_here && a < b && a > 0 && values[a] != values[a - 1];
   }
@@ -112,6 +114,7 @@ __device__ __forceinline__ void validate_rows(int n_wg, int wg, int32_t n_rows, 
   for (int d = 32; d > 0; d >>= 1) {
     legal_descents += __shfl_down(legal_descents, d, 64);
     legal_changes += __shfl_down(legal_changes, d, 64);
+    longest = max(longest, (unsigned int)__shfl_down((int)longest, d, 64));
   }
   const unsigned long long any_bad = __ballot(bad);
   flags = flag_slot(flags);
@@ -119,6 +122,7 @@ __device__ __forceinline__ void validate_rows(int n_wg, int wg, int32_t n_rows, 
     if (legal_changes) atomicAdd(&flags[5], (unsigned long long)legal_changes);
     if (legal_descents) atomicAdd(&flags[3], (unsigned long long)legal_descents);
     if (any_bad) flags[0] = 1;
+    if (longest) atomicMax(&flags[6], (unsigned long long)longest);
   }
 }
 
@@ -1120,17 +1124,28 @@ bool partitions_matter(int32_t c, int32_t w, int32_t n_rows, int64_t slots, long
 }
 
 // A wavefront walks a chunk list alone, so the longest list bounds a launch from below, and the lists of a round
-// run only as fast as the longest of them.  A piece with more entries than two average lists (at least 256, at
-// most kHeavyLenMax) therefore leaves the lists (measured on the 169,343-row graph with rows of up to 13,000
-// entries: SpMM 0.134 -> 0.11 ms).  In rounds every piece longer than one chunk does: what stays in the lists is
-// then so even that the wavefronts of a round sweep the column partitions nearly in step.
-int32_t heavy_len_setting(int64_t nnz, int64_t n_lists, bool rounds, const sptir_build_options_t& opt) {
+// run only as fast as the longest of them.  In rounds every piece longer than one chunk therefore leaves the lists: what
+// stays is then so even that the wavefronts of a round sweep the column partitions nearly in step.  Otherwise long
+// pieces leave when the longest row shows that lists are uneven; the launches that sum them cost some 8 microseconds:
+//  * the longest row (its share of one launch, `longest`) is worth two average lists and 16 chunks or more (32 on
+//    a small graph: 123,202 rows, 455,732 entries, a row of 12,320: 188 -> 76 us; 11,985 rows, one of 1,549, would lose);
+//  * or the graph is large enough for 8 microseconds not to matter (25,683 rows, 11.6 M entries: 270 -> 221 us; 30,886
+//    rows, 7.5 M: 147 -> 83; 14,118 rows, 3.1 M, lost 15 %);
+//  * or it has so few lists that they leave most of the GPU idle (3,106 rows, 602,952 entries: 36 -> 25 us).
+// An even matrix (no row four times the mean) keeps all of its pieces in the lists.  Pieces leave from one chunk on, or
+// from four on where the whole takes tens of microseconds (11,151 rows, 773,309 entries: 20 us against 23).
+int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int32_t n_phases, int64_t longest_row,
+                          bool rounds, const sptir_build_options_t& opt) {
   if (opt.heavy_len >= 1) return opt.heavy_len;
   if (rounds) return kChunkSlots;
-  // (the heavy-piece launches cost some 8 microseconds of their own: not worth it on a graph that is done in 10)
-  if (nnz < (1 << 19)) return kHeavyLenMax;
-  const int64_t per_list = n_lists > 0 ? nnz / n_lists : 0;
-  return (int32_t)std::min<int64_t>(kHeavyLenMax, std::max<int64_t>(256, 2 * per_list));
+  const int64_t n_lists = n_row_blocks * n_phases, per_list = n_lists > 0 ? nnz / n_lists : 0;
+  const int64_t longest = longest_row / std::max(1, n_phases);
+  const bool small = nnz < (1 << 19);
+  const bool uneven = longest_row * n_rows >= 4 * nnz;
+  const bool worth = (longest >= (small ? 32 : 16) * kChunkSlots && longest >= 2 * per_list) || nnz >= (1 << 22) ||
+                     (!small && n_row_blocks < 1024 && longest >= 12 * kChunkSlots);
+  if (!uneven || !worth) return kHeavyLenMax;
+  return nnz >= (1 << 20) ? kChunkSlots : 4 * kChunkSlots;
 }
 
 }  // namespace
@@ -1356,7 +1371,24 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     const bool one_value_per_row = value_bits && csr->nnz > 0 && one_value;
     h->sweep_kb = opt.sweep_kb;  // (0: the defaults of the two sweep rules)
     cs.n_rb = (int32_t)(((int64_t)s.n_rows + (1 << cs.log2_rb) - 1) >> cs.log2_rb);
-    cs.long_len = heavy_len_setting(csr->nnz, (int64_t)cs.n_phases * cs.n_rb, ls.rounds != 0, opt);
+    int64_t longest_row = 0;
+    for (int slot = 0; slot < kFlagSlots; ++slot)
+      longest_row = std::max<int64_t>(longest_row, (int64_t)report1.flags[slot * kFlagStride + 6]);
+    cs.long_len = heavy_len_setting(csr->nnz, s.n_rows, cs.n_rb, cs.n_phases, longest_row, ls.rounds != 0, opt);
+    if (opt.heavy_len < 1 && !ls.rounds && cs.long_len < kHeavyLenMax) {
+      // sptir_spmm_noalloc has room for so many narrow partial-sum rows; bucket i > 6 holds the pieces of
+      // 2^(i-1)+1 .. 2^i entries, and a heavy list takes at least the entries of 16 chunks once there are thousands
+      const int64_t most = (int64_t)(SPTIR_NOALLOC_SCRATCH_BYTES / sizeof(float)) / (ls.full_rows ? kPartialFeat : kNarrowPartialFeat);
+      auto partial_rows = [&](int32_t len) {
+        int64_t n = std::max<int64_t>(csr->nnz / (kHeavyListChunks * kChunkSlots), 2 * 4096);
+        for (int32_t p = 0; p < s.c; ++p)
+          for (int32_t i = 0; i < s.nb; ++i)
+            if (i == s.k + 1 || ((int64_t)1 << i) > len) n += tot_bins[(size_t)p * s.nb + i];
+        return n;
+      };
+      while (cs.long_len < kHeavyLenMax && partial_rows(cs.long_len) > most) cs.long_len *= 2;
+      h->lowered_heavy_len = 1;
+    }
     h->heavy_len = cs.long_len;
     if (!with_spmm_plan) cs.n_rb = 0;  // no row blocks, no cells, no chunks: only the canonical arrays are built
     h->spmm_plan = with_spmm_plan ? 1 : 0;
@@ -1481,6 +1513,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     h->heavy_list_chunks = list_chunks;
     h->n_heavy_lists = (int32_t)((n_heavy_chunks + list_chunks - 1) / list_chunks);
     h->n_partial_rows = h->n_heavy + h->n_heavy_lists;
+    h->partial_feat = h->n_partial_rows <= kWidePartialRows ? kWidePartialFeat : kPartialFeat;
     if (h->n_heavy == 0) h->row_slot_ptr = nullptr;  // (its room in the first allocation stays unused)
     const int64_t all_chunks = n_chunks + n_heavy_chunks;
     if (h->n_partial_rows > 0x7FFFFFFF || all_chunks > 0x7FFFFFFF || report2[3] > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
@@ -1496,7 +1529,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       const size_t c_rb_order = bc.reserve(sizeof(int32_t) * (size_t)(n_groups ? n_groups : 1));
       const size_t c_stream = bc.reserve(sizeof(int32_t) * ((h->compact_stream ? 2 : 3) - (one_value_per_row ? 1 : 0)) *
                                          kChunkSlots * (size_t)(all_chunks ? all_chunks : 1));
-      const size_t c_partial = bc.reserve(heavy ? sizeof(float) * kPartialFeat * (size_t)h->n_partial_rows : 0);
+      const size_t c_partial = bc.reserve(heavy ? sizeof(float) * (size_t)h->partial_feat * (size_t)h->n_partial_rows : 0);
       h->blobs[2] = scratch_alloc(bc.size, alloc, actx, stream);
       if (!h->blobs[2]) { st = SPTIR_ERR_ALLOC; goto fail; }
       h->device_bytes += bc.size;

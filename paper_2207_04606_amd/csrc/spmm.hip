@@ -96,9 +96,10 @@ struct PartialSink {
   static constexpr bool kQueues = false;  // heavy lists hold chunks cut from one long piece only
   float* out;      // partial + this lane's feature offset inside a partial-sum row
   int slot;        // next row
+  int row_floats;  // floats per row
   bool f_active;
   __device__ __forceinline__ void operator()(int, bool valid, const float (&acc)[VEC]) {
-    if (valid && f_active) store_vec<VEC>(out + (size_t)slot * kPartialFeat, acc);
+    if (valid && f_active) store_vec<VEC>(out + (size_t)slot * row_floats, acc);
     ++slot;
   }
 };
@@ -200,8 +201,10 @@ struct HybWalker {
   float acc[VEC];
   float next_acc[VEC];   // heavy lists: what a chunk holds of the piece after the one that ends in it
   // queue chunks: a lane group of 16 or 32 lanes walks the queues of SUB steps in turn, each with a sum of its own
+  // (of one step a chunk, that is acc)
   static constexpr bool kQueueAlone = UB == 8;
-  float queue_acc[kQueueAlone ? SUB : 1][VEC];
+  static constexpr int kMoreSums = kQueueAlone && SUB > 1 ? SUB - 1 : 0;
+  float queue_acc[kMoreSums > 0 ? kMoreSums : 1][VEC];
 
   __device__ __forceinline__ void fetch(int q, Fetched& f) const {
     q = q < n_quads ? q : n_quads - 1;
@@ -295,7 +298,7 @@ struct HybWalker {
       } else {
         read_ints(rows + first_slot(s), r);
       }
-      float (&sum)[VEC] = queue_acc[kQueueAlone ? sub : 0];
+      float (&sum)[VEC] = kMoreSums > 0 && sub > 0 ? queue_acc[sub - 1] : acc;
 #pragma unroll
       for (int j = 0; j < UB; ++j) {
 #pragma unroll
@@ -367,7 +370,7 @@ struct HybWalker {
     for (int e = 0; e < VEC; ++e) {
       acc[e] = 0.f; next_acc[e] = 0.f;
 #pragma unroll
-      for (int i = 0; i < (kQueueAlone ? SUB : 1); ++i) queue_acc[i][e] = 0.f;
+      for (int i = 0; i < (kMoreSums > 0 ? kMoreSums : 1); ++i) queue_acc[i][e] = 0.f;
     }
     if (n_quads <= 0) return;
     // Quads 0 and 1 are requested at once and quad 0 is parked.  From then on, at the start of quad Q, quad Q+1
@@ -520,14 +523,15 @@ struct HeavyArgs {
   const int32_t* stream;       // the whole chunk stream
   const int32_t* first_slot;   // [n_lists] partial-sum row of each list's first write
   const float* X;
-  float* partial;              // [n_partial_rows][kPartialFeat]
+  float* partial;              // [n_partial_rows][partial_feat]
   int64_t chunk0;              // first heavy chunk in the stream
   int64_t n_chunks;            // heavy chunks (a multiple of kChunksPerQuad)
   int32_t list0;               // this launch sums lists list0 .. list0 + n_lists - 1
   int32_t n_lists;
   int32_t list_chunks;         // chunks per list
   int32_t feat;
-  int32_t feat0;               // first feature of this sweep (partial-sum rows hold kPartialFeat features)
+  int32_t feat0;               // first feature of this sweep
+  int32_t partial_feat;        // features a partial-sum row holds
   int32_t n_tiles;             // feature tiles of this sweep
   int32_t map_mode;
   int32_t map_param;
@@ -560,7 +564,7 @@ __device__ __forceinline__ void heavy_workgroup(const HeavyArgs& a, unsigned bid
   const int f_read = f_active ? f0 : 0;  // lanes past the last feature read a valid address, never store
   W wk{a.X, a.stream + (size_t)(a.chunk0 + c0) * (W::kArrays * kChunkSlots), n_list / kChunksPerQuad, lane, g, ring,
        (unsigned)a.feat * 4u, (unsigned)f_read * 4u,
-       PartialSink<VEC, LG>{a.partial + f_in_sweep, __builtin_amdgcn_readfirstlane(a.first_slot[list]), f_active}, {}, {}, {}};
+       PartialSink<VEC, LG>{a.partial + f_in_sweep, __builtin_amdgcn_readfirstlane(a.first_slot[list]), a.partial_feat, f_active}, {}, {}, {}};
   wk.run();
   sum_groups<VEC, LG>(wk.acc, S::kGroups);
   wk.sink(0, g == 0, wk.acc);
@@ -588,16 +592,21 @@ __global__ __launch_bounds__(kHybBlock) void k_spmm_hyb_heavy(SpmmArgs a, HeavyA
 // order of additions whatever the launch, so the result is reproducible.  SPLIT = 8 serves matrices with few, long
 // heavy rows (a row of 13,000 entries cut into lists of 4 chunks has 50 partial sums), SPLIT = 1 the others.
 // Runs after the chunk-list launches have written Y.
+constexpr int kReduceFeat = 128;
 template <int VEC, int SPLIT>
 __global__ __launch_bounds__(256) void k_heavy_reduce(const int32_t* __restrict__ heavy_rows,
                                                       const int32_t* __restrict__ row_slot_ptr,
                                                       const int32_t* __restrict__ row_slots,
                                                       const float* __restrict__ partial,
                                                       const float* __restrict__ row_val, float* Y, int32_t n_rows,
-                                                      int32_t feat, int32_t feat0, int32_t width) {
+                                                      int32_t feat, int32_t feat0, int32_t width, int32_t partial_feat) {
   __shared__ float part_sum[SPLIT > 1 ? 256 * VEC : 1];
+  // a grid row per kReduceFeat features of the sweep
+  const int block0 = blockIdx.y * kReduceFeat;
+  feat0 += block0;
+  width = min(width - block0, kReduceFeat);
   const int per_row = (width + VEC - 1) / VEC;
-  const int group = per_row * SPLIT;    // threads per row (at most 256: per_row <= 32 when SPLIT > 1)
+  const int group = per_row * SPLIT;    // threads per row (at most 256)
   const int rows_per_wg = 256 / group;
   const int local = threadIdx.x;
   const int row_in_wg = local / group, part = (local % group) / per_row, f = (local % per_row) * VEC;
@@ -621,7 +630,7 @@ __global__ __launch_bounds__(256) void k_heavy_reduce(const int32_t* __restrict_
         const int jj = j + u * SPLIT;
         if (jj < e) {
           float v[VEC];
-          load_vec<VEC>(v, partial + (size_t)row_slots[jj] * kPartialFeat + f);
+          load_vec<VEC>(v, partial + (size_t)row_slots[jj] * partial_feat + block0 + f);
 #pragma unroll
           for (int i = 0; i < VEC; ++i) acc[u][i] += v[i];
         }
@@ -753,7 +762,8 @@ void launch_heavy(V, const Geometry& g, hipStream_t stream, const HeavyArgs& a) 
 // Rows that are no whole number of 128-byte lines: a piece of 128 bytes lies across two of them, so 8 lanes fetch nearly
 // every line twice, 16 lanes three lines for two (50,021 rows, 41 floats, 1.5 M non-zeros: 93 -> 53 us; 132,534 rows, 50
 // floats, 39.6 M: 1.12 -> 0.87 ms).  But 16 lanes make half as many wavefronts, each with twice as far to go: they are
-// taken where that does not leave the GPU waiting for the longest list -- in rounds, whose lists are about equally long;
+// taken where that does not leave the GPU waiting for the longest list -- in rounds, whose lists are about equally long,
+// unless X lies in an XCD's L2 (21,403 rows, 36 floats: 68 us against 48);
 // with at least 5000 wavefronts (30,000 rows, 200 floats, 1.8 M: 301 -> 185 us; with 3750, 60,000 rows of 100 floats
 // lost 12 %); or with an X so far beyond an XCD's L2 (26 MB) that the lines fetched twice decide (169,343 rows, 41 floats, 2646
 // wavefronts: 115 -> 87 us).
@@ -762,7 +772,7 @@ void lane_shape(int32_t feat, bool aligned16, const ListShape& lists, int* vec, 
   if (lists.full_rows && full_rows_fit(lists.log2_row_block) && feat % 128 == 0 && aligned16) {
     *lg = 32;  // 32 lanes x 16 bytes: 512 bytes of a row
   } else if (feat > 32 && feat % 32 != 0 && half_rows_fit(lists.log2_row_block) &&
-             (lists.rounds || lists.n_row_blocks * ((feat + 63) / 64) >= 5000 ||
+             ((lists.rounds && lists.n_cols * feat >= 1000000) || lists.n_row_blocks * ((feat + 63) / 64) >= 5000 ||
               lists.n_cols * feat >= 6500000)) {
     *lg = 16;
   } else if (feat >= 4) {
@@ -828,10 +838,10 @@ struct LaunchTimers {
   }
 };
 
-// The work of sptir_spmm; `partial` is where the sums of heavy pieces meet ([n_partial_rows][kPartialFeat] floats;
+// The work of sptir_spmm; `partial` is where the sums of heavy pieces meet ([n_partial_rows][partial_feat] floats;
 // only touched when the matrix has heavy pieces).
 static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y, int32_t feat, void* stream_,
-                                  float* partial, LaunchTimers* timers = nullptr) {
+                                  float* partial, int partial_feat, LaunchTimers* timers = nullptr) {
   if (!h || feat < 1) return SPTIR_ERR_INVALID_ARG;
   if ((h->n_cols > 0 && !X) || (h->n_rows > 0 && !Y)) return SPTIR_ERR_INVALID_ARG;
   const size_t x_bytes = sizeof(float) * (size_t)h->n_cols * feat, y_bytes = sizeof(float) * (size_t)h->n_rows * feat;
@@ -861,11 +871,15 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   const int64_t span = (int64_t)h->parts_per_phase * (int64_t)h->w;
   const bool idx32 = offsets_fit_32(wide ? (int64_t)h->n_cols : (span < h->n_cols ? span : (int64_t)h->n_cols), feat);
   const int all_tiles = g.n_tiles;
+  // Wide partial-sum rows take the heavy lists through all features at once.  Feature tiles that do not map to whole XCDs
+  // then share the L2s, which an X beyond them pays for (62,000 rows of 160 floats, five tiles: 150 us against 127).
+  if (partial_feat > kPartialFeat && x_bytes > ((size_t)16 << 20) && (all_tiles > 8 || (all_tiles & (all_tiles - 1)) != 0))
+    partial_feat = kPartialFeat;
   int n_list_launches = 0;
   bool heavy_with_lists = false;
   if (timers) timers->mark(stream, LaunchTimers::kStart, 0);
   const bool idx32_all = offsets_fit_32(h->n_cols, feat);
-  // the launch over the heavy lists for the features feat0 .. feat0 + width - 1 (width <= kPartialFeat)
+  // the launch over the heavy lists for the features feat0 .. feat0 + width - 1 (width <= partial_feat)
   auto heavy_launch_shape = [&](int feat0, int width, HeavyArgs* ha, Geometry* gh) -> bool {
     ha->stream = h->stream; ha->first_slot = h->hlist_first_slot; ha->X = X; ha->partial = partial;
     ha->chunk0 = h->heavy_chunk0; ha->n_chunks = h->n_heavy_chunks; ha->feat = feat;
@@ -873,20 +887,20 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
     *gh = g;
     const int tile = g.vec * g.lg;
     gh->n_tiles = (width + tile - 1) / tile;
-    ha->feat0 = feat0; ha->n_tiles = gh->n_tiles;
+    ha->feat0 = feat0; ha->n_tiles = gh->n_tiles; ha->partial_feat = partial_feat;
     ha->list0 = 0; ha->n_lists = h->n_heavy_lists;
     if (!plan_tiles(((int64_t)ha->n_lists + kHybWaves - 1) / kHybWaves, gh)) return false;
     ha->map_mode = gh->map_mode; ha->map_param = gh->map_param;
     return true;
   };
-  // Heavy pieces: partial sums of kPartialFeat features at a time, added to the Y the lists have written, for
-  // the features feat_begin .. feat_end - 1 (feat_begin a multiple of kPartialFeat).  already_launched: the heavy
+  // Heavy pieces: partial sums of partial_feat features at a time, added to the Y the lists have written, for
+  // the features feat_begin .. feat_end - 1.  already_launched: the heavy
   // lists went with the chunk lists' launch, only the sums remain to be added.
   auto heavy_sweeps = [&](int feat_begin, int feat_end, bool already_launched = false) -> sptir_status_t {
     if (h->n_heavy <= 0) return SPTIR_OK;
     const bool y_vec4 = feat >= 4;
-    for (int feat0 = feat_begin; feat0 < feat_end; feat0 += kPartialFeat) {
-      const int width = feat_end - feat0 < kPartialFeat ? feat_end - feat0 : kPartialFeat;
+    for (int feat0 = feat_begin; feat0 < feat_end; feat0 += partial_feat) {
+      const int width = feat_end - feat0 < partial_feat ? feat_end - feat0 : partial_feat;
       HeavyArgs ha;
       Geometry gh;
       // The heavy chunks are in partition order and so are the lists: one launch walks them all.  Workgroups start
@@ -898,16 +912,19 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         with_variant(g.vec, g.lg, idx32_all, wide, unit, [&](auto v) { launch_heavy(v, gh, stream, ha); });
         if (timers) timers->mark(stream, LaunchTimers::kHeavy, 1);
       }
-      const int per_row = y_vec4 ? (width + 3) / 4 : width;
-      // few rows with heavy pieces: eight groups of threads share a row's partial sums
-      const int split = (y_vec4 && (int64_t)h->n_heavy_rows * per_row < 32768) ? 8 : 1;
+      const int block = width < kReduceFeat ? width : kReduceFeat;
+      const int per_row = y_vec4 ? (block + 3) / 4 : block;
+      // few rows with heavy pieces: eight groups of threads share a row's partial sums (a rule on feat, not on the width
+      // of a sweep: the order of additions is the same whatever a partial-sum row holds)
+      const int per_row_rule = ((feat < kReduceFeat ? feat : kReduceFeat) + 3) / 4;
+      const int split = (y_vec4 && (int64_t)h->n_heavy_rows * per_row_rule < 32768) ? 8 : 1;
       const int rows_per_wg = 256 / (per_row * split);
       const int64_t n_wg = ((int64_t)h->n_heavy_rows + rows_per_wg - 1) / rows_per_wg;
       if (n_wg > 0x7FFFFFFF) return SPTIR_ERR_OVERFLOW;
-      const dim3 grid((unsigned)n_wg), block(256);
+      const dim3 grid((unsigned)n_wg, (unsigned)((width + kReduceFeat - 1) / kReduceFeat));
       auto reduce = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, stream, h->heavy_rows, h->row_slot_ptr, h->row_slots, partial,
-                           h->row_val, Y, h->n_heavy_rows, feat, feat0, width);
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, h->heavy_rows, h->row_slot_ptr, h->row_slots, partial,
+                           h->row_val, Y, h->n_heavy_rows, feat, feat0, width, partial_feat);
       };
       if (!y_vec4) reduce(k_heavy_reduce<1, 1>);
       else if (split == 8) reduce(k_heavy_reduce<4, 8>);
@@ -966,7 +983,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         // waiting for them (19,717 rows, 88,651 non-zeros, two heavy rows: 0.026 -> 0.023 ms per call).
         HeavyArgs ha;
         Geometry gh;
-        if (h->n_heavy > 0 && h->n_phases == 1 && per_sweep == all_tiles && feat <= kPartialFeat &&
+        if (h->n_heavy > 0 && h->n_phases == 1 && per_sweep == all_tiles && feat <= partial_feat &&
             idx32 == idx32_all && heavy_launch_shape(0, feat, &ha, &gh) && gh.grid <= g.grid &&
             (gh.grid + 7) / 8 * 8 + g.grid <= 0x7FFFFFFF) {
           const int64_t heavy_wgs = (gh.grid + 7) / 8 * 8;
@@ -995,14 +1012,14 @@ extern "C" int32_t sptir_gather_offsets_fit_32(int64_t n_cols, int32_t feat) {
 }
 
 extern "C" sptir_status_t sptir_spmm(const sptir_hyb_t* h, const float* X, float* Y, int32_t feat, void* stream_) {
-  return spmm_on_hyb(h, X, Y, feat, stream_, h ? h->partial : nullptr);
+  return spmm_on_hyb(h, X, Y, feat, stream_, h ? h->partial : nullptr, h ? h->partial_feat : 0);
 }
 
 extern "C" sptir_status_t sptir_spmm_timed(const sptir_hyb_t* h, const float* X, float* Y, int32_t feat,
                                            void* stream_, sptir_spmm_times_t* out) {
   if (!out) return SPTIR_ERR_INVALID_ARG;
   LaunchTimers timers;
-  const sptir_status_t st = spmm_on_hyb(h, X, Y, feat, stream_, h ? h->partial : nullptr, &timers);
+  const sptir_status_t st = spmm_on_hyb(h, X, Y, feat, stream_, h ? h->partial : nullptr, h ? h->partial_feat : 0, &timers);
   if (st != SPTIR_OK) return st;
   SPTIR_HIP(hipStreamSynchronize((hipStream_t)stream_));
   if (timers.failed) return note_hip_error(hipGetLastError(), "recording events");
@@ -1053,9 +1070,15 @@ extern "C" sptir_status_t sptir_spmm_noalloc(const sptir_hyb_t* h, const float* 
                                              void* stream_) {
   if (!h || feat < 1) return SPTIR_ERR_INVALID_ARG;
   float* partial = nullptr;
+  int partial_feat = kPartialFeat;
   if (h->n_heavy > 0) {
+    // as many features at a time as fit: 512 (one sweep for most), 128, or 64 where the length from which pieces are
+    // heavy was lowered to even out the lists
     const size_t need = (size_t)h->n_partial_rows * kPartialFeat;
-    if (need > kStaticScratchFloats) {
+    if (need * (kWidePartialFeat / kPartialFeat) <= kStaticScratchFloats) partial_feat = kWidePartialFeat;
+    else if (need > kStaticScratchFloats && h->lowered_heavy_len && !h->full_rows &&
+             need / (kPartialFeat / kNarrowPartialFeat) <= kStaticScratchFloats) partial_feat = kNarrowPartialFeat;
+    else if (need > kStaticScratchFloats) {
       char msg[256];
       snprintf(msg, sizeof(msg),
                "sptir_spmm_noalloc: the partial sums of %lld heavy row pieces need %zu bytes, more than the "
@@ -1067,5 +1090,5 @@ extern "C" sptir_status_t sptir_spmm_noalloc(const sptir_hyb_t* h, const float* 
     const sptir_status_t st = scratch_of_current_device(&partial);
     if (st != SPTIR_OK) return st;
   }
-  return spmm_on_hyb(h, X, Y, feat, stream_, partial);
+  return spmm_on_hyb(h, X, Y, feat, stream_, partial, partial_feat);
 }

@@ -37,7 +37,11 @@ constexpr int kHeavyLenMax = 2048;      // largest threshold the size rules choo
 constexpr int kHeavyListChunks = 16;    // most chunks per heavy list (a multiple of kChunksPerQuad; on the largest graph 16
                                         // beat 32 by 2 % and 64 by 4 % of the heavy launch; graphs with few heavy
                                         // chunks get shorter lists)
-constexpr int kPartialFeat = 128;       // features per partial sum row: wider Y is produced in sweeps of this many
+// features per partial-sum row: a wider Y is produced in sweeps of this many.  Wide rows (one sweep for most Y) where there
+// are few of them; narrow ones only for sptir_spmm_noalloc.  (All of them hold whole feature tiles: lanes past the last
+// feature of a sweep store too.)
+constexpr int kPartialFeat = 128, kWidePartialFeat = 512, kNarrowPartialFeat = 64;
+constexpr int64_t kWidePartialRows = 8192;  // (16 MB)
 // Compact stream records spend 8 bytes per slot instead of 12: one word holds the column relative to the first
 // column of the launch (bits 0..19), the row relative to the row block (20..26), "slot is real" (27), the chunk's
 // log2w code (28..30; 3 = queue chunk, 7 = cut from one long row) and the hand-over flag (31; of the chunk, or in a
@@ -83,7 +87,9 @@ struct sptir_hyb {
   int32_t n_heavy_rows;       // rows with at least one heavy piece
   int32_t n_row_slots;        // elements of row_slots
   int32_t* heavy_rows;        // device [n_heavy_rows], ascending
-  float* partial;             // device [(n_heavy + n_heavy_lists)][kPartialFeat]
+  float* partial;             // device [(n_heavy + n_heavy_lists)][partial_feat]
+  int32_t partial_feat;
+  int32_t lowered_heavy_len;  // 1: heavy_len was chosen below kHeavyLenMax to even out the lists of a single sweep
   int64_t n_partial_rows;
   int32_t log2_row_block;    // rows of Y one wavefront accumulates in LDS (power of two)
   int32_t n_row_blocks;

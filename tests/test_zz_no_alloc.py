@@ -96,3 +96,42 @@ def test_noalloc_refuses_what_the_scratch_cannot_hold(gpu_lib):
     sptir.sptir_spmm(hyb2, d2.X, Yb)
     torch.cuda.synchronize()
     assert torch.equal(Ya, Yb)
+
+
+@pytest.mark.parametrize("feat", [32, 40, 200])
+def test_noalloc_takes_narrow_sweeps_where_the_lists_were_evened_out(gpu_lib, feat):
+    """18,001 heavy pieces, because one row of 8,000 entries made the library lower heavy_len: their partial sums fit the
+    static scratch 64 features at a time, and Y is the same bit for bit."""
+    sptir = gpu_lib
+    deg = np.full(20000, 3, dtype=np.int64)
+    deg[:18000] = 70
+    deg[19000] = 8000
+    w = workloads.random_csr(20000, 9000, deg, 9, feat)
+    d = upload(w)
+    hyb = sptir.sptir_hyb_build(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, 1, 7)
+    info = sptir.sptir_hyb_info(hyb)
+    assert info["rounds"] == 0 and info["n_heavy_pieces"] == 18001
+    assert (info["n_heavy_pieces"] + info["n_heavy_lists"]) * 128 * 4 > 8 * 1024 * 1024
+    Ya = torch.full((w.n_rows, feat), float("nan"), device="cuda"); Yb = torch.full_like(Ya, float("nan"))
+    sptir.sptir_spmm_noalloc(hyb, d.X, Ya)
+    sptir.sptir_spmm(hyb, d.X, Yb)
+    torch.cuda.synchronize()
+    assert torch.equal(Ya, Yb)
+    Yo, So = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    assert_y_close(Ya.cpu().numpy(), Yo, So, what="narrow sweeps")
+
+
+@pytest.mark.parametrize("hub,heavy", [(2047, 0), (2048, 1), (4000, 1)])
+def test_long_rows_of_a_small_matrix_leave_the_lists(gpu_lib, hub, heavy):
+    """From 32 chunks on a row of a small, otherwise even matrix is summed apart; 300 features take one wide sweep."""
+    sptir = gpu_lib
+    deg = np.full(3000, 2, dtype=np.int64)
+    deg[1500] = hub
+    w = workloads.random_csr(3000, 5000, deg, 4, 300)
+    d = upload(w)
+    hyb = sptir.sptir_hyb_build(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, 1, 4)
+    assert sptir.sptir_hyb_info(hyb)["n_heavy_pieces"] == heavy
+    Y = torch.full((w.n_rows, 300), float("nan"), device="cuda")
+    sptir.sptir_spmm(hyb, d.X, Y)
+    Yo, So = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    assert_y_close(Y.cpu().numpy(), Yo, So, what=f"hub of {hub}")
