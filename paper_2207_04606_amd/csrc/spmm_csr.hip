@@ -1,8 +1,8 @@
 // SpMM straight from CSR, one pass, no decomposition: the "no-hyb" variant
 // that section 4.2.1 of arXiv 2207.04606 compares hyb against.
 //
-// Mapping (gfx950, wave64).  A workgroup of eight wavefronts owns 64
-// consecutive rows and one feature tile (32 floats, eight lanes of four), bound to XCDs like
+// Mapping (gfx950, wave64).  A workgroup of eight wavefronts owns 64 (a small
+// dense matrix: 16 or 8) consecutive rows and one feature tile (32 floats, eight lanes of four), bound to XCDs like
 // the tiles of the hyb kernels.  What a row costs is its gathers of X, so rows
 // are treated by length:
 //   short   (<= kShortRow) one lane group per row, eight rows per wavefront at
@@ -22,6 +22,8 @@
 // Measured (169,343 rows, 1,166,243 entries, 128 features): 0.65 -> 0.116 ms,
 // 5.1 TB/s of gathered rows of which a quarter hit L2, near what the memory-side
 // cache delivers at random (7.9).
+#include <type_traits>
+
 #include "sptir_internal.h"
 #include "sptir_tiles.h"
 
@@ -41,20 +43,21 @@ struct CsrArgs {
   int32_t map_param;
 };
 
-constexpr int kCsrRows = 64;     // rows per workgroup: one per lane when their lengths are loaded
+constexpr int kCsrRows = 64;     // most rows per workgroup: one per lane when their lengths are loaded
 constexpr int kShortRow = 32;    // four steps of one lane group: 16..48 measured alike
-constexpr int kLongRow = 512;    // eight steps of one wavefront (1024: 5 % slower on power-law rows, 256: the same)
+constexpr int kLongRow = 512;    // eight steps of one wavefront (1024: 5 % slower on power-law rows, 256: the same); half
+                                 // of it where a workgroup has fewer than 64 rows
 
-template <int VEC, int LG>
+template <int VEC, int LG, int ROWS>
 __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
-  constexpr int kGroups = 64 / LG, kWaves = 8, kRowsPerWave = kCsrRows / kWaves;
+  constexpr int kGroups = 64 / LG, kWaves = 8, kRowsPerWave = ROWS / kWaves;
   constexpr int UB = LG < 8 ? LG : 8, kTile = VEC * LG;
   static_assert(kRowsPerWave % kGroups == 0 || kGroups % kRowsPerWave == 0, "rows of a wavefront in whole passes");
   __shared__ __align__(16) float part[kWaves][kTile];
   int64_t unit;
   int tile_id;
   decode_block(blockIdx.x, a.map_mode, a.map_param, a.n_tiles, &unit, &tile_id);
-  const int64_t row0 = unit * kCsrRows;
+  const int64_t row0 = unit * ROWS;
   if (row0 >= a.n_rows) return;
   const int lane = threadIdx.x & 63, g = lane / LG, fl = lane & (LG - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -67,17 +70,19 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
 
   // lane l: first entry and length of row row0 + l
   int row_begin = 0, row_len = 0;
-  if (row0 + lane < a.n_rows) {
+  if (lane < ROWS && row0 + lane < a.n_rows) {
     row_begin = a.indptr[row0 + lane];
     row_len = a.indptr[row0 + lane + 1] - row_begin;
   }
-  unsigned long long long_rows = __ballot(row_len > kLongRow);
 
+  constexpr int kLong = ROWS < kCsrRows ? kLongRow / 2 : kLongRow;
+  unsigned long long long_rows = __ballot(row_len > kLong);
   float acc[VEC];
   // entries [first, first + left) of a row summed by this lane group, `stride` entries apart from step to step; the
   // next step's entries are fetched while this one's gathers are in flight (two steps of gathers in flight measured
   // no faster: 0.144 against 0.122 ms, half the wavefronts)
   auto walk = [&](int first, int left, int stride) {
+    if (!__any(left > 0)) return;
     int c = 0;
     float v = 0.f;
     auto fetch = [&]() {
@@ -86,7 +91,7 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
       v = ok ? a.values[first + fl] : 0.f;
     };
     fetch();
-    while (__any(left > 0)) {
+    do {
       float x[UB][VEC];
       float vu[UB];
 #pragma unroll
@@ -106,7 +111,7 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
       for (int u = 0; u < UB; ++u)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vu[u], x[u][e], acc[e]);
-    }
+    } while (__any(left > 0));
   };
   auto clear = [&]() {
 #pragma unroll
@@ -155,7 +160,7 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
     if (mine && f_active) store_unaligned<VEC>(Yf + (size_t)(row0 + src) * feat, acc);
   }
   // medium rows: the wavefront each
-  unsigned long long medium = __ballot(row_len > kShortRow && row_len <= kLongRow) &
+  unsigned long long medium = __ballot(row_len > kShortRow && row_len <= kLong) &
                               (((1ull << kRowsPerWave) - 1) << (wave * kRowsPerWave));
   while (medium) {
     const int src = __builtin_ctzll(medium);
@@ -190,16 +195,30 @@ extern "C" sptir_status_t sptir_spmm_csr(const sptir_csr_t* csr, const float* X,
   // 27 us); they change over near 8 MB.
   if (feat > 32 && feat % 32 != 0 && x_bytes > ((size_t)8 << 20)) g.lg = 16;
   g.n_tiles = (feat + g.vec * g.lg - 1) / (g.vec * g.lg);
-  if (!plan_tiles(((int64_t)csr->n_rows + kCsrRows - 1) / kCsrRows, &g)) return SPTIR_ERR_OVERFLOW;
+  // Rows per workgroup: 64, or fewer where workgroups of 64 would leave CUs idle and rows are long enough for a wavefront
+  // each (a small dense graph: 4,168 rows, 603,937 entries, 32 features: 43 -> 17 us with 8 rows; 8,382 rows, 1.2 M, 64
+  // features: 44 -> 29 with 16).  Short rows want eight of them per wavefront however few there are (10,403 rows of 20
+  // entries: 9 us against 14).
+  const int64_t n_wg = ((int64_t)csr->n_rows + kCsrRows - 1) / kCsrRows * g.n_tiles;
+  const bool dense = csr->nnz >= 40 * (int64_t)csr->n_rows;
+  const int rows = !dense || n_wg >= 512 ? kCsrRows : n_wg >= 128 ? 16 : 8;
+  if (!plan_tiles(((int64_t)csr->n_rows + rows - 1) / rows, &g)) return SPTIR_ERR_OVERFLOW;
   CsrArgs a;
   a.indptr = csr->indptr; a.indices = csr->indices; a.values = csr->values; a.X = X; a.Y = Y;
   a.n_rows = csr->n_rows; a.feat = feat; a.n_tiles = g.n_tiles; a.map_mode = g.map_mode; a.map_param = g.map_param;
   dim3 grid((unsigned)g.grid), block(512);
   hipStream_t stream = (hipStream_t)stream_;
-  if (g.vec == 1) hipLaunchKernelGGL((k_spmm_csr<1, 8>), grid, block, 0, stream, a);
-  else if (g.lg == 4) hipLaunchKernelGGL((k_spmm_csr<4, 4>), grid, block, 0, stream, a);
-  else if (g.lg == 16) hipLaunchKernelGGL((k_spmm_csr<4, 16>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((k_spmm_csr<4, 8>), grid, block, 0, stream, a);
+  auto launch = [&](auto n) {
+    constexpr int kRows = decltype(n)::value;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, a); };
+    if (g.vec == 1) go(k_spmm_csr<1, 8, kRows>);
+    else if (g.lg == 4) go(k_spmm_csr<4, 4, kRows>);
+    else if (g.lg == 16) go(k_spmm_csr<4, 16, kRows>);
+    else go(k_spmm_csr<4, 8, kRows>);
+  };
+  if (rows == kCsrRows) launch(std::integral_constant<int, kCsrRows>{});
+  else if (rows == 16) launch(std::integral_constant<int, 16>{});
+  else launch(std::integral_constant<int, 8>{});
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;
 }

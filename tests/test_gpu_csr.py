@@ -25,3 +25,21 @@ def test_row_lengths_and_tails(gpu_lib, n_rows, n_cols, feat):
     gpu_lib.sptir_spmm_csr(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, d.X, Y)
     Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
     assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"rows={n_rows} cols={n_cols} feat={feat}")
+
+
+@pytest.mark.parametrize("n_rows,feat,mean", [(200, 3, 20), (200, 17, 20), (129, 36, 20), (1000, 130, 20),   # 64 rows a workgroup
+                                              (8200, 3, 45), (8193, 16, 45), (2049, 160, 60), (2050, 161, 60),   # 16
+                                              (90, 40, 60), (89, 5, 60)])                                        # 8
+def test_rows_per_workgroup(gpu_lib, n_rows, feat, mean):
+    """Row classes in workgroups of 64, 16 and 8 rows, the last one partly filled."""
+    rng = np.random.default_rng(feat)
+    deg = rng.integers(0, 2 * mean, n_rows)
+    some = rng.choice(n_rows, 8, replace=False)
+    deg[some] = [0, 32, 33, 256, 257, 512, 513, 300]
+    deg[:] = np.minimum(deg, 700)
+    w = workloads.random_csr(n_rows, 700, deg, feat, feat)
+    d = upload(w)
+    Y = torch.full((n_rows, feat), float("nan"), device="cuda")
+    gpu_lib.sptir_spmm_csr(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, d.X, Y)
+    Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"rows={n_rows} feat={feat} mean={mean}")
