@@ -223,6 +223,8 @@ def _stream_ptr(stream):
 
 
 def _dev(t: torch.Tensor, dtype, what: str) -> torch.Tensor:
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.is_contiguous():
+        return t
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{what} must be a CUDA/HIP tensor")
     if t.dtype != dtype:
@@ -230,6 +232,16 @@ def _dev(t: torch.Tensor, dtype, what: str) -> torch.Tensor:
     if not t.is_contiguous():
         raise ValueError(f"{what} must be contiguous")
     return t
+
+
+def _feat_2d(X, Y, x_rows, y_rows, names: str, rows_message: str) -> int:
+    """The feature size of two dense operands.  (A tensor's .shape is a new object at every access: 0.1 us.)"""
+    xs, ys = X.shape, Y.shape
+    if len(xs) != 2 or len(ys) != 2 or xs[1] != ys[1]:
+        raise ValueError(f"{names} must be 2-D with the same number of columns")
+    if xs[0] != x_rows or ys[0] != y_rows:
+        raise ValueError(rows_message)
+    return xs[1]
 
 
 def _csr_struct(n_rows, n_cols, indptr, indices, values):
@@ -374,12 +386,8 @@ def sptir_hyb_array(hyb: Hyb, name: str) -> np.ndarray:
 def sptir_spmm(hyb: Hyb, X, Y, stream=None) -> None:
     """Y[n_rows, feat] = A @ X[n_cols, feat]; Y is overwritten."""
     _dev(X, torch.float32, "X"); _dev(Y, torch.float32, "Y")
-    if X.dim() != 2 or Y.dim() != 2 or X.shape[1] != Y.shape[1]:
-        raise ValueError("X and Y must be 2-D with the same number of columns")
-    if X.shape[0] != hyb.n_cols or Y.shape[0] != hyb.n_rows:
-        raise ValueError("X / Y row counts do not match the matrix")
-    st = load_library().sptir_spmm(hyb.handle, X.data_ptr() or None, Y.data_ptr() or None, X.shape[1],
-                                   _stream_ptr(stream))
+    feat = _feat_2d(X, Y, hyb.n_cols, hyb.n_rows, "X and Y", "X / Y row counts do not match the matrix")
+    st = load_library().sptir_spmm(hyb.handle, X.data_ptr() or None, Y.data_ptr() or None, feat, _stream_ptr(stream))
     if st != SPTIR_OK:
         raise SptirError(st, "sptir_spmm")
 
@@ -436,12 +444,9 @@ def sptir_spmm_noalloc(hyb: Hyb, X, Y, stream=None) -> None:
 
 def sptir_spmm_csr(n_rows: int, n_cols: int, indptr, indices, values, X, Y, stream=None) -> None:
     _dev(X, torch.float32, "X"); _dev(Y, torch.float32, "Y")
-    if X.dim() != 2 or Y.dim() != 2 or X.shape[1] != Y.shape[1]:
-        raise ValueError("X and Y must be 2-D with the same number of columns")
-    if X.shape[0] != n_cols or Y.shape[0] != n_rows:
-        raise ValueError("X / Y row counts do not match the matrix")
+    feat = _feat_2d(X, Y, n_cols, n_rows, "X and Y", "X / Y row counts do not match the matrix")
     csr = _csr_struct(n_rows, n_cols, indptr, indices, values)
-    st = load_library().sptir_spmm_csr(ctypes.byref(csr), X.data_ptr() or None, Y.data_ptr() or None, X.shape[1],
+    st = load_library().sptir_spmm_csr(ctypes.byref(csr), X.data_ptr() or None, Y.data_ptr() or None, feat,
                                        _stream_ptr(stream))
     if st != SPTIR_OK:
         raise SptirError(st, "sptir_spmm_csr")
@@ -496,15 +501,12 @@ def sptir_set_allocator(use_torch: bool) -> None:
 def sptir_sddmm_csr(n_rows: int, n_cols: int, indptr, indices, values, X, Yt, B_values, stream=None) -> None:
     """B_values[q] = values[q] * <X[row(q)], Yt[indices[q]]> for every stored position q."""
     _dev(X, torch.float32, "X"); _dev(Yt, torch.float32, "Yt"); _dev(B_values, torch.float32, "B_values")
-    if X.dim() != 2 or Yt.dim() != 2 or X.shape[1] != Yt.shape[1]:
-        raise ValueError("X and Yt must be 2-D with the same number of columns")
-    if X.shape[0] != n_rows or Yt.shape[0] != n_cols:
-        raise ValueError("X / Yt row counts do not match the matrix")
+    feat = _feat_2d(X, Yt, n_rows, n_cols, "X and Yt", "X / Yt row counts do not match the matrix")
     if B_values.dim() != 1 or B_values.shape[0] != values.shape[0]:
         raise ValueError("B_values must have one entry per stored position")
     csr = _csr_struct(n_rows, n_cols, indptr, indices, values)
     st = load_library().sptir_sddmm_csr(ctypes.byref(csr), X.data_ptr() or None, Yt.data_ptr() or None,
-                                        B_values.data_ptr() or None, X.shape[1], _stream_ptr(stream))
+                                        B_values.data_ptr() or None, feat, _stream_ptr(stream))
     if st != SPTIR_OK:
         raise SptirError(st, "sptir_sddmm_csr")
 
@@ -548,15 +550,11 @@ def sptir_sddmm_plan_build(n_rows: int, n_cols: int, indptr, indices, n_col_part
 def sptir_sddmm(plan: SddmmPlan, values, X, Yt, B_values, stream=None) -> None:
     _dev(values, torch.float32, "values"); _dev(X, torch.float32, "X"); _dev(Yt, torch.float32, "Yt")
     _dev(B_values, torch.float32, "B_values")
-    if X.dim() != 2 or Yt.dim() != 2 or X.shape[1] != Yt.shape[1]:
-        raise ValueError("X and Yt must be 2-D with the same number of columns")
-    if X.shape[0] != plan.n_rows or Yt.shape[0] != plan.n_cols:
-        raise ValueError("X / Yt row counts do not match the plan")
+    feat = _feat_2d(X, Yt, plan.n_rows, plan.n_cols, "X and Yt", "X / Yt row counts do not match the plan")
     if values.dim() != 1 or values.shape[0] != plan.nnz or B_values.shape != values.shape:
         raise ValueError("values and B_values must have one entry per stored position")
     st = load_library().sptir_sddmm(plan.handle, values.data_ptr() or None, X.data_ptr() or None,
-                                    Yt.data_ptr() or None, B_values.data_ptr() or None, X.shape[1],
-                                    _stream_ptr(stream))
+                                    Yt.data_ptr() or None, B_values.data_ptr() or None, feat, _stream_ptr(stream))
     if st != SPTIR_OK:
         raise SptirError(st, "sptir_sddmm")
 
@@ -617,14 +615,15 @@ def sptir_rgms_build(n_relations: int, n_rows: int, n_cols: int, indptr, indices
 
 def sptir_rgms(rgms: Rgms, X, W, Y, stream=None) -> None:
     _dev(X, torch.float32, "X"); _dev(W, torch.float32, "W"); _dev(Y, torch.float32, "Y")
-    if X.dim() != 2 or W.dim() != 3 or Y.dim() != 2:
+    xs, ws, ys = X.shape, W.shape, Y.shape
+    if len(xs) != 2 or len(ws) != 3 or len(ys) != 2:
         raise ValueError("X and Y must be 2-D, W 3-D")
-    if X.shape[0] != rgms.n_cols or Y.shape[0] != rgms.n_rows or W.shape[0] != rgms.n_rel:
+    if xs[0] != rgms.n_cols or ys[0] != rgms.n_rows or ws[0] != rgms.n_rel:
         raise ValueError("operand sizes do not match the tensor")
-    if W.shape[1] != X.shape[1] or W.shape[2] != Y.shape[1]:
+    if ws[1] != xs[1] or ws[2] != ys[1]:
         raise ValueError("W must be [n_relations, d_in, d_out]")
     st = load_library().sptir_rgms(rgms.handle, X.data_ptr() or None, W.data_ptr() or None, Y.data_ptr() or None,
-                                   X.shape[1], Y.shape[1], _stream_ptr(stream))
+                                   xs[1], ys[1], _stream_ptr(stream))
     if st != SPTIR_OK:
         raise SptirError(st, "sptir_rgms")
 

@@ -46,7 +46,8 @@ struct CsrArgs {
 constexpr int kCsrRows = 64;     // most rows per workgroup: one per lane when their lengths are loaded
 constexpr int kShortRow = 32;    // four steps of one lane group: 16..48 measured alike
 constexpr int kLongRow = 512;    // eight steps of one wavefront (1024: 5 % slower on power-law rows, 256: the same); half
-                                 // of it where a workgroup has fewer than 64 rows
+                                 // of it with 16 rows per workgroup, twice of it where every wavefront has one row
+                                 // (3,576 rows, 514,589 entries: 14 us against 17)
 
 template <int VEC, int LG, int ROWS>
 __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
     row_len = a.indptr[row0 + lane + 1] - row_begin;
   }
 
-  constexpr int kLong = ROWS < kCsrRows ? kLongRow / 2 : kLongRow;
+  constexpr int kLong = ROWS == 8 ? 2 * kLongRow : ROWS == 16 ? kLongRow / 2 : kLongRow;
   unsigned long long long_rows = __ballot(row_len > kLong);
   float acc[VEC];
   // entries [first, first + left) of a row summed by this lane group, `stride` entries apart from step to step; the
