@@ -1133,7 +1133,7 @@ bool partitions_matter(int32_t c, int32_t w, int32_t n_rows, int64_t slots, long
 //    rows, 7.5 M: 147 -> 83; 14,118 rows, 3.1 M, lost 15 %);
 //  * or it has so few lists that they leave most of the GPU idle (3,106 rows, 602,952 entries: 36 -> 25 us).
 // An even matrix (no row four times the mean) keeps all of its pieces in the lists.  Pieces leave from one chunk on, or
-// from four on where the whole takes tens of microseconds (11,151 rows, 773,309 entries: 20 us against 23).
+// from two or four on where the whole takes tens of microseconds (11,151 rows, 773,309 entries: 20 us against 23).
 int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int32_t n_phases, int64_t longest_row,
                           bool rounds, const sptir_build_options_t& opt) {
   if (opt.heavy_len >= 1) return opt.heavy_len;
@@ -1145,7 +1145,7 @@ int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int
   const bool worth = (longest >= (small ? 32 : 16) * kChunkSlots && longest >= 2 * per_list) || nnz >= (1 << 22) ||
                      (!small && n_row_blocks < 1024 && longest >= 12 * kChunkSlots);
   if (!uneven || !worth) return kHeavyLenMax;
-  return nnz >= (1 << 20) ? kChunkSlots : 4 * kChunkSlots;
+  return nnz >= (1 << 21) ? kChunkSlots : nnz >= (1 << 20) ? 2 * kChunkSlots : 4 * kChunkSlots;
 }
 
 }  // namespace

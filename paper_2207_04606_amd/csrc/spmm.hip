@@ -875,6 +875,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   // then share the L2s, which an X beyond them pays for (62,000 rows of 160 floats, five tiles: 150 us against 127).
   if (partial_feat > kPartialFeat && x_bytes > ((size_t)16 << 20) && (all_tiles > 8 || (all_tiles & (all_tiles - 1)) != 0))
     partial_feat = kPartialFeat;
+  partial_feat = std::min(partial_feat, all_tiles * g.vec * g.lg);  // rows no wider than Y
   int n_list_launches = 0;
   bool heavy_with_lists = false;
   if (timers) timers->mark(stream, LaunchTimers::kStart, 0);
