@@ -344,6 +344,7 @@ struct CellShape {
   int32_t c, k, nb;
   int32_t log2_rb, n_rb, ppg, n_phases;
   int32_t long_len;  // pieces with more real entries are not in the lists (heavy pieces)
+  int32_t wide_margin;  // see below
   int64_t R;
 };
 
@@ -385,8 +386,12 @@ __global__ void k_cell_bounds(CellShape cs, const int64_t* __restrict__ bucket_r
 //    keeps the running sum in registers, hands it over at a flag and needs no cross-lane reduction; no pad of
 //    a bucket row is ever walked.  A piece goes to the queue that is shortest so far (buckets are visited
 //    widest first, so this is the longest-first rule up to a factor of two);
-//  * unless the piece is longer than a chunk and than an even share of what is still to be dealt: such a
-//    piece is cut "wide" instead, into chunks of 64 entries that all eight lane groups share, in its bin's cell.
+//  * unless that would leave the queues uneven: a piece that is longer than a chunk and than an even share of what is
+//    still to be dealt, or a shorter one that would reach wide_margin entries beyond the level at which all queues
+//    would end, is cut "wide" instead, into chunks of 64 entries that all eight lane groups share, in its bin's cell.
+//    (A piece of 60 entries among rows of four makes its queue, and with it the list, 60 entries long: 14,964 rows,
+//    156,998 entries in 16 partitions 59 -> 33 us.  Two chunks of margin, as the wide chunk costs one; in rounds, whose
+//    lists are long enough to be even, four.)
 // The rows of one partition are distinct, so two queues never hand over the same row of Y in one instruction.
 __device__ __forceinline__ int cells_per_part(const CellShape& cs) { return cs.nb + 1; }
 __device__ __forceinline__ int cells_per_group(const CellShape& cs) { return cs.ppg * (cs.nb + 1) + 1; }
@@ -474,22 +479,24 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
   __syncthreads();
 
   unsigned load = 0;  // entries of queue l
+  unsigned queued = 0;  // entries of all queues
   int len = n > 0 ? len_of[0] : 0;
   for (int i = 0; i < n; ++i) {
     const int next = len_of[i + 1 < n ? i + 1 : i];
     if (len <= cs.long_len) {
-      const unsigned share = (to_deal + 7) >> 3;
+      const unsigned share = (to_deal + 7) >> 3, level = (queued + to_deal) >> 3;
       to_deal -= (unsigned)len;
+      const unsigned best = min_of_8(load * 8 + l);  // of equally short queues the first
       uint32_t word;
-      if (len > kChunkSlots && (unsigned)len > share) {
+      if (len > kChunkSlots ? (unsigned)len > share : (best >> 3) + (unsigned)len > level + (unsigned)cs.wide_margin) {
         const int at = cs.nb - 1 - bin_of_length(len, cs.k);
         const int w = wide[part][at];
         if (l == 0) wide[part][at] = w + chunks_of_length(len);
         word = kWidePiece | (uint32_t)w;
       } else {
-        const unsigned best = min_of_8(load * 8 + l);  // of equally short queues the first
         word = (best >> 3) | ((best & 7u) << 28);
         if ((best & 7u) == (unsigned)l) load += (unsigned)len;
+        queued += (unsigned)len;
       }
       if (l == 0) len_of[i] = (int)word;
     }
@@ -1374,6 +1381,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     int64_t longest_row = 0;
     for (int slot = 0; slot < kFlagSlots; ++slot)
       longest_row = std::max<int64_t>(longest_row, (int64_t)report1.flags[slot * kFlagStride + 6]);
+    cs.wide_margin = ls.rounds ? 32 : 16;
     cs.long_len = heavy_len_setting(csr->nnz, s.n_rows, cs.n_rb, cs.n_phases, longest_row, ls.rounds != 0, opt);
     if (opt.heavy_len < 1 && !ls.rounds && cs.long_len < kHeavyLenMax) {
       // sptir_spmm_noalloc has room for so many narrow partial-sum rows; bucket i > 6 holds the pieces of

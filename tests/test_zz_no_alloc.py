@@ -104,7 +104,7 @@ def test_noalloc_takes_narrow_sweeps_where_the_lists_were_evened_out(gpu_lib, fe
     static scratch 64 features at a time, and Y is the same bit for bit."""
     sptir = gpu_lib
     deg = np.full(20000, 3, dtype=np.int64)
-    deg[:18000] = 70
+    deg[:18000] = 130
     deg[19000] = 8000
     w = workloads.random_csr(20000, 9000, deg, 9, feat)
     d = upload(w)
