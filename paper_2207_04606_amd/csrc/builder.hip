@@ -1089,7 +1089,8 @@ sptir_status_t validation_verdict(const unsigned long long* flag_slots, bool* on
 
 namespace {
 
-int log2_row_block_setting(int32_t n_rows, bool rounds, bool full_rows, const sptir_build_options_t& opt) {
+int log2_row_block_setting(int32_t n_rows, bool rounds, bool several_launches, bool full_rows,
+                           const sptir_build_options_t& opt) {
   long v = opt.row_block;
   if ((v < 8 || v > 256 || (v & (v - 1))) && full_rows) {
     // 16 rows x 512 bytes: the same 8 KB of LDS per wavefront as 64 rows of a 128-byte tile
@@ -1106,7 +1107,10 @@ int log2_row_block_setting(int32_t n_rows, bool rounds, bool full_rows, const sp
     // A launch has (row blocks x feature tiles) wavefronts.  With one or two tiles (feat <= 64) that is too few
     // to balance 3,000 wavefront slots, and smaller row blocks win (measured at feat = 32: 32 rows 21 % faster).
     const long tiles = opt.feat_hint > 0 ? (opt.feat_hint + 31) / 32 : 4;
-    while (v > 16 && (n_rows / v) * tiles < 6144) v >>= 1;
+    // A launch per group of partitions ends in a partly filled GPU that many times: three times the 3,300 wavefronts that
+    // are resident at 64 rows keep that small (132,534 rows, 39.6 M entries, 8 launches, 32 rows instead of 64: 1.07 ->
+    // 1.04 ms; 106,797 rows, 9.8 M, 33 features: 212 -> 188 us).
+    while (v > 16 && (n_rows / v) * tiles < (several_launches ? 10240 : 6144)) v >>= 1;
     // ... but keep at least ~1024 row blocks, or the 256 CUs do not fill
     while (v > 8 && n_rows / v < 1024) v >>= 1;
   }
@@ -1185,13 +1189,13 @@ LaunchShape decide_launch_shape(int32_t n_rows, int32_t n_cols, int32_t c, int32
   ls.rounds = opt.rounds == 1 ? 1 : opt.rounds == 2 ? 0 : (matter && !parts_given && short_pieces ? 1 : 0);
   // Whole 512-byte runs of X per entry: only when asked for.  Measured at feat = 128 against the 128-byte tiles
   // bound to XCDs: 7 entries per row 0.108 -> 0.151 ms, 4.5 per row 0.037 -> 0.090 ms, 300 per row
-  // 1.09 -> 1.66 ms.  Two lane groups instead of eight meet every queue four times per chunk, so partial sums go
-  // through LDS at every step, and every XCD's L2 then sees all of X instead of a quarter of it.
+  // 1.09 -> 1.66 ms: two lane groups instead of eight have a quarter of the rows in flight, and every XCD's L2 then sees
+  // all of X instead of a quarter of it.
   ls.full_rows = opt.full_rows == 1 ? 1 : 0;
-  ls.log2_row_block = log2_row_block_setting(n_rows, ls.rounds != 0, ls.full_rows != 0, opt);
   if (ls.rounds) ls.parts_per_phase = c;
   else if (parts_given) ls.parts_per_phase = opt.parts_per_launch;
   else ls.parts_per_phase = matter ? (int32_t)fit : c;
+  ls.log2_row_block = log2_row_block_setting(n_rows, ls.rounds != 0, ls.parts_per_phase < c, ls.full_rows != 0, opt);
   // a compact record holds a column in kCompactColBits bits and a row of the row block in 7
   const int64_t max_span = (int64_t)1 << kCompactColBits;
   ls.compact = (!opt.wide_stream && n_cols <= max_span && ls.log2_row_block <= kCompactMaxLog2RowBlock) ? 1 : 0;
