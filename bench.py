@@ -43,10 +43,10 @@ def bytes_hyb(info, n_rows, n_cols, feat):
 
 def bytes_build(info, nnz, n_rows):
     """Algorithmic bytes of sptir_hyb_build: the CSR read twice (validation reads column ids and values; the scatter
-    reads both again; the piece boundaries come from a few probes per row piece), the canonical slots written,
-    the real entries read again and written as the SpMM stream."""
+    reads both again; the piece boundaries come from a few probes per row piece), the canonical slots and the SpMM
+    stream written."""
     slots = info["n_ell_slots"] + info["n_rem_nnz"]
-    return 4.0 * nnz + 4.0 * nnz + 8.0 * nnz + 8.0 * slots + 8.0 * nnz + 8.0 * nnz + 8.0 * n_rows
+    return 4.0 * nnz + 4.0 * nnz + 8.0 * nnz + 8.0 * slots + 8.0 * nnz + 8.0 * n_rows
 
 
 def source_fingerprint():

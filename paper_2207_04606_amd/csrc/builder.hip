@@ -722,7 +722,7 @@ __global__ __launch_bounds__(kBuildBlock) void k_heavy_units(int64_t n_pieces, c
 }
 
 // The partial-sum rows of heavy piece number u whose real entries are the slots [e0, e1) of the heavy sequence:
-// rows u + w for every heavy list w that holds one of them (see k_heavy_list_slots).
+// rows u + w for every heavy list w that holds one of them (see k_heavy_units).
 __device__ __forceinline__ void piece_slots(int list_chunks, int u, int e0, int e1, int* first, int* count) {
   const int per_list = list_chunks * kChunkSlots;
   const int w0 = e0 / per_list, w1 = (e1 - 1) / per_list;

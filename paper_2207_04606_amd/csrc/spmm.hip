@@ -2,7 +2,8 @@
 // 2207.04606), and the single-pass CSR variant the paper calls "no-hyb".
 //
 // Mapping (gfx950, wave64).  The feature dimension is cut into tiles of
-// LG*VEC floats (32 floats = one 128-byte line of X by default).  A wavefront
+// LG*VEC floats (32 floats = one 128-byte line of X by default; 64 where rows
+// of X are no whole lines).  A wavefront
 // owns one (row block, feature tile): it keeps that tile of the row block's Y
 // rows (64 rows, 8 KB, unless the graph is small) in its own piece of LDS, walks
 // every chunk of the row block's list (all column partitions of the launch, the
@@ -31,8 +32,9 @@
 //
 // Row pieces too long for that (more than a chunk's worth of entries in
 // rounds) are summed by k_spmm_heavy: their chunks form one sequence in
-// partition order, cut into lists of 32 chunks, a wavefront each, which leave
+// partition order, cut into lists of 16 chunks, a wavefront each, which leave
 // partial sums in memory; k_heavy_reduce adds them to Y in a fixed order.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>

@@ -9,21 +9,7 @@
 
 namespace sptir {
 
-// The SpMM kernel walks the real entries of the stored rows in chunks of kChunkSlots slots.  A builder-side
-// descriptor stands for a chunk cut from one row (an ELL row of section 4.2.1 or a piece of the CSR remainder)
-// that is too long to be walked by one lane group: `count` consecutive slots of the fused (cols, vals) arrays
-// starting at `slot0`, all of row row_ids[row0]; it carries log2w = kRowLog2W.  Queue chunks, which hold eight
-// entries of each of eight lane-group queues, are written piece by piece and have a descriptor only to mark
-// their place; a descriptor with count 0 is the padding at the end of a (launch, row block) list.
-struct Chunk {
-  int64_t slot0;
-  int32_t row0;
-  // bits 0..5 log2w, bits 6..12 count (1..64), bit 13: hand the row's partial sum over after this chunk,
-  // bit 14: queue chunk
-  uint32_t meta;
-};
-static_assert(sizeof(Chunk) == 16, "Chunk must stay 16 bytes");
-
+// The SpMM kernel walks the real entries of the stored rows in chunks of kChunkSlots slots.
 constexpr int kChunkSlots = 64;
 constexpr int kRowLog2W = 31;
 constexpr int kChunksPerQuad = 4;  // chunks the SpMM kernel fetches with one load per lane and array
