@@ -490,19 +490,23 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
   wk.run();
 
   // write the tile: a lane group per row, one 128-byte line per group
-  if (f_active) {
+  if (!f_active) return;
+  auto row_of_tile = [&](int r, float (&out)[VEC]) {
+    load_vec<VEC>(out, tile + tile_index<VEC, LG>(r, fl));
+    if constexpr (UNIT) {
+      const float v = a.row_val[rb_first + r];
+      float before[VEC];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) before[e] = 0.f;
+      if (a.accumulate) load_unaligned<VEC>(before, y0 + (size_t)r * (size_t)a.feat);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) out[e] = fmaf(v, out[e], before[e]);
+    }
+  };
+  if (__any(again != 0)) {
     for (int r = g; r < rows_here; r += S::kGroups) {
       float out[VEC];
-      load_vec<VEC>(out, tile + tile_index<VEC, LG>(r, fl));
-      if constexpr (UNIT) {
-        const float v = a.row_val[rb_first + r];
-        float before[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) before[e] = 0.f;
-        if (a.accumulate) load_unaligned<VEC>(before, y0 + (size_t)r * (size_t)a.feat);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) out[e] = fmaf(v, out[e], before[e]);
-      }
+      row_of_tile(r, out);
       float* y = y0 + (size_t)r * (size_t)a.feat;
       if (again == 0) store_unaligned<VEC>(y, out);
       else {
@@ -510,6 +514,13 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
         for (int e = 1; e < VEC; ++e)
           if (e >= again) y[e] = out[e];
       }
+    }
+  } else {  // (on its own: with the branch above in it the loop waits for LDS row by row)
+#pragma unroll 4
+    for (int r = g; r < rows_here; r += S::kGroups) {
+      float out[VEC];
+      row_of_tile(r, out);
+      store_unaligned<VEC>(y0 + (size_t)r * (size_t)a.feat, out);
     }
   }
 }
