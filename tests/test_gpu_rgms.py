@@ -199,3 +199,37 @@ def test_rgms_features_beyond_4_gb(gpu_lib):
     want = torch.stack([rows[:2].sum(0), rows[2:].sum(0)]) @ W[0].cpu().double()
     assert torch.allclose(Y.cpu().double(), want, rtol=1e-4, atol=1e-3)
     h.destroy()
+
+
+@pytest.mark.parametrize("workspace", [0, 128])
+@pytest.mark.parametrize("n,n_rel,d_in,d_out", [(300, 5, 32, 32), (300, 5, 64, 64), (2000, 3, 128, 128), (9000, 2, 32, 64)])
+def test_rgms_non_finite_rows_stay_with_their_rows(gpu_lib, n, n_rel, d_in, d_out, workspace):
+    """A row of X with a NaN or an infinity reaches the rows of Y that have an entry naming it and no others, whatever
+    tile, step of four or repeated last entry it shares with theirs; an infinite value of A and an infinite W[r]
+    likewise.  (Which of infinity and NaN comes out depends on the order of the sums; that it is not finite does not.)"""
+    rng = np.random.default_rng(n + d_in)
+    counts = np.minimum(rng.integers(0, 4, n_rel * n), n)
+    counts[rng.choice(n_rel * n, 40, replace=False)] = rng.choice([5, 8, 9, 16, 64, 65, 130], 40)  # several pieces, batches
+    w = workloads.random_csr(n_rel * n, n, counts, 3, 1, "uniform")
+    X = rng.standard_normal((n, d_in)).astype(np.float32)
+    bad = rng.choice(n, 6, replace=False)
+    X[bad[0]] = np.nan
+    X[bad[1], 0] = np.inf
+    X[bad[2], d_in - 1] = -np.inf
+    X[bad[3], d_in // 2] = np.nan
+    X[n - 1, 3] = np.nan                             # the last column is the last entry of many a tile
+    values = w.values.copy()
+    values[rng.choice(values.size, 3, replace=False)] = [np.inf, -np.inf, np.nan]
+    W = rng.standard_normal((n_rel, d_in, d_out)).astype(np.float32)
+    for W_bad in (False, True):
+        if W_bad:
+            W[n_rel - 1, d_in // 3, 5] = np.inf
+        hw = workloads.HeteroWorkload("non-finite", n, n_rel, w.indptr, w.indices, values, X, W)
+        Y, _ = run_rgms(gpu_lib, hw, workspace_d_out=workspace)
+        with np.errstate(invalid="ignore", over="ignore"):
+            Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, values, X, W)
+        finite = np.isfinite(Yr)
+        assert finite.any() and not finite.all()
+        wrong = np.isfinite(Y) != finite
+        assert not wrong.any(), f"{int(wrong.sum())} of {int(finite.sum())} elements"
+        assert_y_close(np.where(finite, Y, 0), np.where(finite, Yr, 0), np.where(finite, Sr, 0), "finite rows")
