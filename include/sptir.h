@@ -466,7 +466,8 @@ sptir_status_t sptir_rgms(const sptir_rgms_t* rgms, const float* X, const float*
 sptir_status_t sptir_rgms_info(const sptir_rgms_t* rgms, sptir_rgms_info_t* out);
 sptir_status_t sptir_rgms_destroy(sptir_rgms_t* rgms); /* NULL is accepted */
 
-/* Releases the handle and its device arrays.  NULL is accepted. */
+/* Releases the handle and its device arrays.  NULL is accepted.  Under the default allocator it waits for the device, as
+ * hipFree does, and like hipFree it may be called while a stream is captured in relaxed mode only. */
 sptir_status_t sptir_hyb_destroy(sptir_hyb_t* hyb);
 
 /* Fills *out with sizes and parameters of the decomposition. */

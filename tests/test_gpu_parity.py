@@ -576,6 +576,32 @@ def test_spmm_and_sddmm_replay_in_a_hip_graph(gpu_lib):
         assert torch.equal(Y, Y_eager) and torch.equal(B, B_eager), f"replay {rep}"
 
 
+def test_destroy_while_a_stream_is_captured(gpu_lib):
+    """A handle may be released (by a finaliser, say) while another stream is captured in relaxed mode, as hipFree may be
+    called then: the capture goes on, and every replay gives what an eager call gives."""
+    w = workloads.make_config("tiny")
+    d = upload(w)
+    A, B = (gpu_lib.sptir_hyb_build(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, 1, 5) for _ in range(2))
+    Y = torch.empty(w.n_rows, w.feat, device="cuda")
+    gpu_lib.sptir_spmm(A, d.X, Y)
+    gpu_lib.sptir_spmm(B, d.X, Y)
+    want = Y.clone()
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+        gpu_lib.sptir_spmm(A, d.X, Y, stream=side)
+        B.destroy()
+    C = gpu_lib.sptir_hyb_build(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, 1, 5)   # takes B's blocks
+    for rep in range(3):
+        Y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, want), f"replay {rep}"
+        gpu_lib.sptir_spmm(C, d.X, Y)
+        assert torch.equal(Y, want), f"eager {rep}"
+
+
 @pytest.mark.parametrize("n_rows,knobs", [
     (1500, {"rounds": 1, "heavy_len": 40}), (1500, {"rounds": 1, "wide_stream": 1}), (1500, {"rounds": 1, "row_block": 256}),
     (1500, {"rounds": 2, "heavy_len": 33}), (42000, {"rounds": 2, "row_block": 8, "parts_per_launch": 1})])
