@@ -152,10 +152,12 @@ sptir_status_t sptir_set_allocator(sptir_alloc_fn alloc, sptir_free_fn free_, vo
 
 /*
  * Under the default allocator the device blocks of destroyed hyb handles and the temporary blocks of sptir_hyb_build are
- * kept (at most 16 blocks and 2 GB in all, none larger than 1 GB, the oldest go first) for the next build instead of
- * giving them back with hipFree, which costs as much as a small build.  This call frees what is being kept; an allocation
- * that fails does so before it is tried again.  Live handles are not affected.  With an allocator of the caller's nothing
- * is ever kept.
+ * kept for the next build instead of giving them back with hipFree, which costs as much as a small build: at most 16
+ * blocks, none larger than 1 GB, and 256 MB in all, or a 16th of what the device has free up to 2 GB if that is more; the
+ * oldest go first.  A build takes a kept block that is at most a quarter and 1 MB larger than it needs, and
+ * sptir_hyb_info_t.device_bytes counts it whole.  This call frees what is being kept (for other allocators of the process,
+ * which cannot); an allocation of the library's that fails does so before it is tried again.  Live handles are not
+ * affected.  With an allocator of the caller's nothing is ever kept.
  */
 sptir_status_t sptir_release_scratch(void);
 

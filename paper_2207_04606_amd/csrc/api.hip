@@ -3,6 +3,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -39,11 +40,10 @@ void current_allocator(sptir_alloc_fn* a, sptir_free_fn* f, void** ctx) {
 }
 
 // ---- kept blocks of the default allocator
-// hipMalloc and hipFree map and unmap memory: 0.05 - 0.3 ms for each of the eight blocks of a build and its handle, a
-// third of the time of a small build and its release.  Blocks that hipMalloc gave out for temporaries and for hyb handles
-// are therefore kept when they are released (a few, bounded in size, the oldest go first) and handed to the next call
-// that asks for about as much on the same device.  With a caller's allocator everything goes straight to it: it has its
-// own policy.
+// Blocks that hipMalloc gave out for temporaries and for hyb handles are kept when they are released (a few, bounded in
+// size, the oldest go first) and handed to the next call that asks for about as much on the same device: hipMalloc and
+// hipFree take 10 us each for a block of 4 to 64 MB and 30 + 235 us for one of 256 MB and more, and a build and its release
+// ask for eight.  With a caller's allocator everything goes straight to it: it has its own policy.
 namespace {
 struct ScratchBlock { void* p; size_t size; int dev; };
 std::mutex g_scratch_mu;
@@ -51,6 +51,23 @@ std::vector<ScratchBlock> g_scratch_free, g_scratch_live;
 size_t g_scratch_free_bytes = 0;
 constexpr size_t kScratchKeepBytes = (size_t)2048 << 20, kScratchKeepBlock = (size_t)1024 << 20;
 constexpr size_t kScratchKeepCount = 16;
+// What is kept is out of reach of other allocators in the process, so beyond kScratchKeepFreely it is at most a 16th of
+// what the device has free: close to its end the memory goes back.
+constexpr size_t kScratchKeepFreely = (size_t)256 << 20;
+
+// bytes that may be kept where `total` would be, `last` of them in a block of device `dev` that is just released (a small one
+// does not ask: the question takes 5 us)
+size_t may_keep(size_t total, size_t last, int dev) {
+  if (total <= kScratchKeepFreely || (last < total / 32 && total <= kScratchKeepBytes)) return total;
+  size_t free_bytes = 0, all = 0;
+  int before = 0;
+  const bool other = hipGetDevice(&before) == hipSuccess && before != dev;
+  if (other) (void)hipSetDevice(dev);
+  const bool known = hipMemGetInfo(&free_bytes, &all) == hipSuccess;
+  if (other) (void)hipSetDevice(before);
+  if (!known) { (void)hipGetLastError(); return kScratchKeepFreely; }
+  return std::min(kScratchKeepBytes, std::max(kScratchKeepFreely, free_bytes / 16));
+}
 
 // Waits until nothing that any stream of the current device has been given is still running, as hipFree does
 // (hipDeviceSynchronize would break a capture that runs in relaxed mode on another stream; this does not): 1.5 us idle.
@@ -97,7 +114,8 @@ void keep_or_free(const ScratchBlock& b) {  // no work on the device uses the bl
     std::lock_guard<std::mutex> lock(g_scratch_mu);
     g_scratch_free.push_back(b);
     g_scratch_free_bytes += b.size;
-    while (g_scratch_free.size() > kScratchKeepCount || g_scratch_free_bytes > kScratchKeepBytes) {
+    const size_t most = may_keep(g_scratch_free_bytes, b.size, b.dev);
+    while (g_scratch_free.size() > kScratchKeepCount || g_scratch_free_bytes > most) {
       out.push_back(g_scratch_free.front());
       g_scratch_free_bytes -= g_scratch_free.front().size;
       g_scratch_free.erase(g_scratch_free.begin());
@@ -107,7 +125,8 @@ void keep_or_free(const ScratchBlock& b) {  // no work on the device uses the bl
 }
 }  // namespace
 
-void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream) {
+void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream, size_t* got) {
+  if (got) *got = bytes;
   if (alloc != default_alloc) return alloc(bytes, actx, stream);
   if (bytes == 0) bytes = 1;
   int dev = 0;
@@ -117,7 +136,7 @@ void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream
     int best = -1;
     for (size_t i = 0; i < g_scratch_free.size(); ++i) {
       const ScratchBlock& b = g_scratch_free[i];
-      if (b.dev != dev || b.size < bytes || b.size > 2 * bytes + ((size_t)1 << 20)) continue;
+      if (b.dev != dev || b.size < bytes || b.size > bytes + bytes / 4 + ((size_t)1 << 20)) continue;
       if (best < 0 || b.size < g_scratch_free[(size_t)best].size) best = (int)i;
     }
     if (best >= 0) {
@@ -125,6 +144,7 @@ void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream
       g_scratch_free.erase(g_scratch_free.begin() + best);
       g_scratch_free_bytes -= b.size;
       g_scratch_live.push_back(b);
+      if (got) *got = b.size;
       return b.p;
     }
   }

@@ -1449,10 +1449,11 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       const size_t a_row_slot = ba.reserve(want_heavy ? sizeof(int32_t) * ((size_t)s.n_rows + 1) : 0);
       const size_t b_cols = bb.reserve(sizeof(int32_t) * (size_t)(h->S + T + kChunkSlots));
       const size_t b_vals = bb.reserve(sizeof(float) * (size_t)(h->S + T + kChunkSlots));
-      h->blobs[0] = scratch_alloc(ba.size, alloc, actx, stream);
-      h->blobs[1] = scratch_alloc(bb.size, alloc, actx, stream);
+      size_t index_bytes = 0;
+      h->blobs[0] = scratch_alloc(ba.size, alloc, actx, stream, &index_bytes);
+      h->blobs[1] = scratch_alloc(bb.size, alloc, actx, stream, &h->canonical_bytes);
       if (!h->blobs[0] || !h->blobs[1]) { st = SPTIR_ERR_ALLOC; goto fail; }
-      h->device_bytes += ba.size + bb.size;
+      h->device_bytes += index_bytes + h->canonical_bytes;
       char* a0 = (char*)h->blobs[0];
       char* b0 = (char*)h->blobs[1];
       h->bucket_row_ptr = (int64_t*)(a0 + a_row_ptr); h->bucket_slot_ptr = (int64_t*)(a0 + a_slot_ptr);
@@ -1462,7 +1463,6 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       if (one_value_per_row) h->row_val = (float*)(a0 + a_row_val);
       if (want_heavy) h->row_slot_ptr = (int32_t*)(a0 + a_row_slot);
       h->cols = (int32_t*)(b0 + b_cols); h->vals = (float*)(b0 + b_vals);
-      h->canonical_bytes = bb.size;
     }
     if (one_value_per_row) {
       hipLaunchKernelGGL(k_row_values, dim3((unsigned)((s.n_rows + 255) / 256)), dim3(256), 0, stream, s.n_rows,
@@ -1542,9 +1542,10 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       const size_t c_stream = bc.reserve(sizeof(int32_t) * ((h->compact_stream ? 2 : 3) - (one_value_per_row ? 1 : 0)) *
                                          kChunkSlots * (size_t)(all_chunks ? all_chunks : 1));
       const size_t c_partial = bc.reserve(heavy ? sizeof(float) * (size_t)h->partial_feat * (size_t)h->n_partial_rows : 0);
-      h->blobs[2] = scratch_alloc(bc.size, alloc, actx, stream);
+      size_t plan_bytes = 0;
+      h->blobs[2] = scratch_alloc(bc.size, alloc, actx, stream, &plan_bytes);
       if (!h->blobs[2]) { st = SPTIR_ERR_ALLOC; goto fail; }
-      h->device_bytes += bc.size;
+      h->device_bytes += plan_bytes;
       char* c0 = (char*)h->blobs[2];
       if (heavy) {
         h->hlist_first_slot = (int32_t*)(c0 + c_first_slot); h->row_slots = (int32_t*)(c0 + c_row_slots);

@@ -102,8 +102,9 @@ namespace sptir {
 void current_allocator(sptir_alloc_fn* a, sptir_free_fn* f, void** ctx);
 void* default_alloc(size_t bytes, void* ctx, void* stream);
 // Temporaries of a call: from `alloc`, or, when that is the default allocator, from a small cache of blocks that
-// earlier calls have released (api.hip).  scratch_free takes back what scratch_alloc gave.
-void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream);
+// earlier calls have released (api.hip).  scratch_free takes back what scratch_alloc gave.  *got: the size of the block,
+// which may be up to a quarter and 1 MB more than was asked for.
+void* scratch_alloc(size_t bytes, sptir_alloc_fn alloc, void* actx, void* stream, size_t* got = nullptr);
 void scratch_free(void* p, sptir_free_fn free_, void* actx);
 // the same for the blocks of a handle that launches on any stream may still be reading
 void handle_free(void* const* blobs, int n, sptir_free_fn free_, void* actx);

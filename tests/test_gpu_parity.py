@@ -576,6 +576,33 @@ def test_spmm_and_sddmm_replay_in_a_hip_graph(gpu_lib):
         assert torch.equal(Y, Y_eager) and torch.equal(B, B_eager), f"replay {rep}"
 
 
+def test_kept_blocks_are_counted_and_bounded(gpu_lib):
+    """device_bytes is what a handle holds, also where its blocks are larger than it needs because an earlier handle of
+    about its size left them; and what released handles leave is no more than the header says."""
+    def build(n_rows, deg=48):
+        cols = (torch.arange(deg, device="cuda") * 1000)[None, :] + torch.arange(n_rows, device="cuda")[:, None] % 1000
+        indptr = torch.arange(n_rows + 1, device="cuda") * deg
+        return gpu_lib.sptir_hyb_build(n_rows, 50_000, indptr.int(), cols.flatten().int(),
+                                       torch.ones(n_rows * deg, device="cuda") / 3, 1, 6)
+
+    def free_bytes():
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        return torch.cuda.mem_get_info()[0]
+
+    build(100).destroy()                                # one-time set-up
+    gpu_lib.sptir_release_scratch()
+    free0 = free_bytes()
+    for n_rows in (200_000, 170_000, 110_000, 60_000, 61_000):
+        build(n_rows).destroy()
+        assert free0 - free_bytes() <= max(256 << 20, free0 // 16) + (32 << 20), n_rows
+        h = build(n_rows - n_rows // 12)
+        gpu_lib.sptir_release_scratch()
+        held, said = free0 - free_bytes(), gpu_lib.sptir_hyb_info(h)["device_bytes"]
+        assert abs(held - said) <= 8 << 20, f"{n_rows} rows: holds {held}, says {said}"   # (three blocks in whole 2 MB pages)
+        h.destroy()
+
+
 def test_destroy_while_a_stream_is_captured(gpu_lib):
     """A handle may be released (by a finaliser, say) while another stream is captured in relaxed mode, as hipFree may be
     called then: the capture goes on, and every replay gives what an eager call gives."""
