@@ -124,9 +124,8 @@ constexpr int kPass = 32;       // columns of Y per pass: two products side by s
 // column 4 (m & 7) + 2 (m >> 3) + j: that is what the lanes hold after a load of 16 consecutive bytes each (see
 // load_w).  In the LDS tile the columns lie in the order of the products.
 // WIDE_X: X has 4 GB or more.
-// (The second launch bound: six wavefronts per SIMD where 80 registers do; two more, and the dense graph takes 176 us, not 158.)
 template <int TIN, bool ORDERED, bool WIDE_X>
-__global__ __launch_bounds__(1024, TIN == 1 && !ORDERED && !WIDE_X ? 6 : 4) void k_rgms(RgmsArgs a) {
+__global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
   constexpr int VW = TIN == 1 ? 2 : 4;              // floats per lane and load of a row of X
   constexpr int kLoads = 2 * TIN / VW;              // loads per row
   constexpr int kZ = 2 * TIN;                       // 16-feature products per step
@@ -145,12 +144,9 @@ __global__ __launch_bounds__(1024, TIN == 1 && !ORDERED && !WIDE_X ? 6 : 4) void
   const int n0 = blockIdx.y * width;
   const int cols = min(width, a.d_out - n0);
   int* turn = reinterpret_cast<int*>(y_tile + rows * width);
-  auto clear_rows = [&]() {
-    for (int i = threadIdx.x * 2; i < rows * width; i += blockDim.x * 2)
-      *reinterpret_cast<double2*>(y_tile + i) = make_double2(0., 0.);
-    if (ORDERED && threadIdx.x < (unsigned)(width / kPass)) turn[threadIdx.x] = 0;
-  };
-  clear_rows();
+  for (int i = threadIdx.x * 2; i < rows * width; i += blockDim.x * 2)
+    *reinterpret_cast<double2*>(y_tile + i) = make_double2(0., 0.);
+  if (ORDERED && threadIdx.x < (unsigned)(width / kPass)) turn[threadIdx.x] = 0;
   __syncthreads();
 
   const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
@@ -237,29 +233,6 @@ __global__ __launch_bounds__(1024, TIN == 1 && !ORDERED && !WIDE_X ? 6 : 4) void
     even = make_float2(pick(here_x, w.x), pick(here_y, w.y));
     odd = make_float2(pick(w.z, here_x), pick(w.w, here_y));
   };
-  // adds 32 columns of tile t's results to the block's rows: d[v] belongs to piece 4q + v
-  auto add = [&](int t, int c0, const int (&y_row)[4], const floatx4& d0, const floatx4& d1) {
-    if constexpr (ORDERED) {
-      // tile t adds after tile t - 1, which an earlier turn of the caller's loop or another wavefront of this workgroup
-      // is on its way to: the wait ends
-      while (__hip_atomic_load(turn + c0 / kPass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != t)
-        __builtin_amdgcn_s_sleep(1);
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (y_row[v] != kNoRow) {
-        double* y = y_tile + y_row[v] * width + c0 + m;
-        const int half = (y_row[v] & 1) << 4;
-        atomicAdd(y + half, (double)d0[v]);
-        atomicAdd(y + (half ^ 16), (double)d1[v]);
-      }
-    if constexpr (ORDERED) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  // (LDS only: the prefetches stay in flight)
-      if (lane == 0)
-        __hip_atomic_store(turn + c0 / kPass, t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-  };
   constexpr int kParts = kZ / 2, kHeld = kParts < 2 ? kParts : 2;  // pairs of parts of W, and how many are held at a time
 
   using std::integral_constant;
@@ -318,29 +291,118 @@ __global__ __launch_bounds__(1024, TIN == 1 && !ORDERED && !WIDE_X ? 6 : 4) void
           if (p + kHeld < kParts) load_w(rel, c0, p + kHeld, w[p % kHeld]);
           else load_w(rel_then, c_then, p + kHeld - kParts, w[p % kHeld]);
         }
-        add(t, c0, y_row, d0, d1);
+        // ---- add: d[v] belongs to piece 4q + v
+        if constexpr (ORDERED) {
+          // tile t adds after tile t - 1, which an earlier turn of this loop or another wavefront of this workgroup
+          // is on its way to: the wait ends
+          while (__hip_atomic_load(turn + c0 / kPass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != t)
+            __builtin_amdgcn_s_sleep(1);
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (y_row[v] != kNoRow) {
+            double* y = y_tile + y_row[v] * width + c0 + m;
+            const int half = (y_row[v] & 1) << 4;
+            atomicAdd(y + half, (double)d0[v]);
+            atomicAdd(y + (half ^ 16), (double)d1[v]);
+          }
+        if constexpr (ORDERED) {
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  // (LDS only: the prefetches stay in flight)
+          if (lane == 0)
+            __hip_atomic_store(turn + c0 / kPass, t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
       }
       rows_now = rows_next;
     }
   }
   __syncthreads();
-  // ---- the block's rows.  write_rows returns 0, or a NaN if an element of this thread's is not finite.
-  const int row0 = item.block << a.log2_block;
-  const int rows_here = min(rows, a.n_rows - row0);
-  const int quads = cols / 4;
-  const bool adds_to_y = !ORDERED && item.part >= 0;
-  auto write_rows = [&](bool only_look) {
-    float zero = 0.f;
-    for (int i = threadIdx.x; i < rows_here * quads; i += blockDim.x) {
+
+  // ---- what is left (in a scope of its own: anything kept since the loop above costs registers in it)
+  {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    // The gather multiplies an entry's row of X with the value 0 for the pieces it does not belong to, and a lane past the end
+    // of a tile does so with the tile's last row: a NaN or an infinity in a row of X has reached every pair of the tile.  Sums
+    // that are not finite are therefore formed again before they are written, from their own row's entries only; the
+    // wavefront takes a row of the block at a time.  y[0 .. 3] of a lane: columns n0 + c .. + 3 of row `row`.  (Testing every
+    // tile's sums in front of its product instead: 0.505 -> 0.542 ms on 1.9 M rows; here the test does not show.)
+    auto sum_again = [&](int row, int c, bool not_finite, float (&y)[4]) {
+      unsigned long long todo = __ballot(not_finite);
+      while (todo) {
+        const int r = __builtin_amdgcn_readlane(row, __builtin_ctzll(todo));
+        const bool here = not_finite && row == r;
+        todo &= ~__ballot(here);
+        double sum[4] = {0., 0., 0., 0.};
+        for (int t0 = 0; t0 < item.n_tiles; t0 += 64) {
+          bool has = false;  // a piece of row r in tile t0 + lane
+          if (t0 + lane < item.n_tiles)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const ushort4 of = a.tile_rows[(size_t)(item.tile0 + t0 + lane) * 4 + i];
+              has |= of.x == r || of.y == r || of.z == r || of.w == r;
+            }
+          for (unsigned long long tiles = __ballot(has); tiles; tiles &= tiles - 1) {
+            const int t = item.tile0 + t0 + __builtin_ctzll(tiles);
+            const RgmsTile tile = a.tiles[t];
+            const int of_slot = reinterpret_cast<const uint16_t*>(a.tile_rows + (size_t)t * 4)[lane & 15];
+            const unsigned slots = (unsigned)__ballot(of_slot == r) & 0xFFFFu;
+            constexpr int kPerLane = (kDin + 63) / 64;
+            float sums[kPerLane];  // features lane, lane + 64
+#pragma unroll
+            for (int i = 0; i < kPerLane; ++i) sums[i] = 0.f;
+            for (int first = tile.first; first < tile.end; first += 64) {
+              const int at = min(first + lane, tile.end - 1);
+              const int2 e = a.entries[at];
+              const bool take = first + lane < tile.end && (slots >> a.entry_piece[at] & 1u) != 0;
+              for (unsigned long long left = __ballot(take); left; left &= left - 1) {
+                const int from = __builtin_ctzll(left);
+                const float* x_row = a.X + (size_t)__builtin_amdgcn_readlane(e.x, from) * kDin;
+                const float v = __int_as_float(__builtin_amdgcn_readlane(e.y, from));
+#pragma unroll
+                for (int i = 0; i < kPerLane; ++i) sums[i] = fmaf(v, x_row[(64 * i + lane) % kDin], sums[i]);
+              }
+            }
+            const float* w = a.W + (size_t)tile.rel * kDin * (size_t)a.d_out + n0 + c;
+            float d[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < kPerLane; ++i)
+#pragma unroll 4
+              for (int k = 0; k < (kDin < 64 ? kDin : 64); ++k) {
+                const float s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sums[i]), k));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) d[j] = fmaf(s, w[(size_t)(64 * i + k) * a.d_out + j], d[j]);
+              }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sum[j] += d[j];
+          }
+        }
+        if (here) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y[j] = (float)sum[j];
+        }
+      }
+    };
+
+    // ---- the block's rows
+    const int row0 = item.block << a.log2_block;
+    const int rows_here = min(rows, a.n_rows - row0);
+    const int quads = cols / 4;
+    const int n_quads = rows_here * quads;
+    // (whole wavefronts: sum_again needs all lanes)
+    for (int i0 = __builtin_amdgcn_readfirstlane(tid); i0 < n_quads; i0 += (int)blockDim.x) {
+      const int i = min(i0 + lane, n_quads - 1);
       const int row = i / quads, c = (i - row * quads) * 4;
       float y[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int p = (c + k) % kPass;
         y[k] = (float)y_tile[y_index(row, c + k - p + 16 * (p & 1) + 8 * ((p >> 1) & 1) + (p >> 2), width)];
-        zero = fmaf(y[k], 0.f, zero);
       }
-      if (only_look) continue;
+      const bool not_finite = fmaf(y[0], 0.f, fmaf(y[1], 0.f, fmaf(y[2], 0.f, y[3] * 0.f))) != 0.f;
+      if (__any(not_finite)) sum_again(row, c, not_finite, y);
+      if (i0 + lane >= n_quads) continue;
       if (item.part < 0) {
         store_unaligned<4>(a.Y + (size_t)(row0 + row) * a.d_out + n0 + c, y);
       } else if constexpr (ORDERED) {
@@ -352,69 +414,7 @@ __global__ __launch_bounds__(1024, TIN == 1 && !ORDERED && !WIDE_X ? 6 : 4) void
           if (y[k] != 0.f) atomicAdd(p + k, y[k]);
       }
     }
-    return zero;
-  };
-  const float zero = write_rows(adds_to_y);
-  if (__any(zero != 0.f) && lane == 0) atomicAdd(y_tile, (double)NAN);
-  __syncthreads();
-  // The gather multiplies an entry's row of X with the value 0 for the pieces it does not belong to, and a lane past the end
-  // of a tile does so with the tile's last row: a NaN or an infinity in a row of X has reached every pair of the tile.  An item
-  // with a sum that is not finite (its first is then made a NaN, which every thread sees) is therefore done again with
-  // each row in its own piece only, and what was written is written over.  Looking at the sums as they are written out costs
-  // 0.6 % (1.9 M rows: 504 -> 507 us); at the gathered sums of every tile, in front of its product, it was 7 %.
-  const bool again = !isfinite(y_tile[0]);
-  if (again) {
-    __syncthreads();
-    clear_rows();
-    __syncthreads();
-    for (int t = wave; t < item.n_tiles; t += n_waves) {
-      const RgmsTile tile = load_tile(t);
-      const ushort4 tile_rows = load_rows(t);
-      const int y_row[4] = {tile_rows.x, tile_rows.y, tile_rows.z, tile_rows.w};
-#pragma unroll
-      for (int g = 0; g < kLoads; ++g)
-#pragma unroll
-        for (int l = 0; l < VW; ++l) z[g][l] = floatx4{0.f, 0.f, 0.f, 0.f};
-      for (int first = tile.first; first < tile.end; first += 64) {
-        const int n = min(64, tile.end - first), at = first + min(lane, n - 1);
-        const int2 e = a.entries[at];
-        const int p = a.entry_piece[at];
-#pragma unroll 2
-        for (int i = 0; i < n; ++i) {
-          const float* row = a.X + (size_t)__builtin_amdgcn_readlane(e.x, i) * kDin + 4 * VW * q;
-          const float v = __int_as_float(__builtin_amdgcn_readlane(e.y, i));
-          const bool mine = __builtin_amdgcn_readlane(p, i) == m;
-#pragma unroll
-          for (int g = 0; g < kLoads; ++g)
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-              for (int l = 0; l < VW; ++l) {
-                const float sum = fmaf(v, row[16 * VW * g + VW * k + l], z[g][l][k]);
-                z[g][l][k] = mine ? sum : z[g][l][k];
-              }
-        }
-      }
-      for (int c0 = 0; c0 < cols; c0 += kPass) {
-        const float* w = a.W + (size_t)tile.rel * kDin * (size_t)a.d_out + (size_t)(4 * VW * q) * a.d_out + n0 + c0 +
-                         4 * (m & 7) + 2 * (m >> 3);
-        floatx4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int g = 0; g < kLoads; ++g)
-#pragma unroll
-          for (int l = 0; l < VW; ++l)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float* w_row = w + (size_t)(16 * VW * g + VW * i + l) * a.d_out;
-              d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l][i], w_row[0], d0, 0, 0, 0);
-              d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l][i], w_row[1], d1, 0, 0, 0);
-            }
-        add(t, c0, y_row, d0, d1);
-      }
-    }
-    __syncthreads();
   }
-  if (again || adds_to_y) write_rows(false);
 }
 
 __global__ __launch_bounds__(256) void k_fill_zero(float* p, int64_t n) {
@@ -778,7 +778,7 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do
   const int64_t tiles_each = p->n_tiles / std::max<int64_t>((int64_t)p->n_items * a.sharers, 1);
   a.n_waves = large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;
-  const size_t lds = sizeof(double) * ((size_t)a.width << p->log2_block) + (ordered ? sizeof(int) * (a.width / kPass) : 0);
+  const size_t lds = sizeof(double) * ((size_t)a.width << p->log2_block) + (ordered ? sizeof(int) * (a.width / 16) : 0);
   const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);
   auto divided = [&](const float* partial) {
     if (p->n_divided > 0)
