@@ -1138,13 +1138,17 @@ bool partitions_matter(int32_t c, int32_t w, int32_t n_rows, int64_t slots, long
 // run only as fast as the longest of them.  In rounds every piece longer than one chunk therefore leaves the lists: what
 // stays is then so even that the wavefronts of a round sweep the column partitions nearly in step.  Otherwise long
 // pieces leave when the longest row shows that lists are uneven; the launches that sum them cost some 8 microseconds:
-//  * the longest row (its share of one launch, `longest`) is worth two average lists and 16 chunks or more (32 on
-//    a small graph: 123,202 rows, 455,732 entries, a row of 12,320: 188 -> 76 us; 11,985 rows, one of 1,549, would lose);
-//  * or the graph is large enough for 8 microseconds not to matter (25,683 rows, 11.6 M entries: 270 -> 221 us; 30,886
-//    rows, 7.5 M: 147 -> 83; 14,118 rows, 3.1 M, lost 15 %);
-//  * or it has so few lists that they leave most of the GPU idle (3,106 rows, 602,952 entries: 36 -> 25 us).
-// An even matrix (no row four times the mean) keeps all of its pieces in the lists.  Pieces leave from one chunk on, or
-// from two or four on where the whole takes tens of microseconds (11,151 rows, 773,309 entries: 20 us against 23).
+//  * the longest row (its share of one launch, `longest`) is worth two average lists and 16 chunks or more (32 where there
+//    are fewer than 2^19 entries and the whole takes about as long as those launches);
+//  * or the graph is large enough for 8 microseconds not to matter;
+//  * or it has so few lists that they leave most of the GPU idle.
+// An even matrix (no row four times the mean) keeps all of its pieces in the lists.  Pieces leave from one chunk on.
+// Measured on 260 graphs with power-law degrees, 2,500 to 170,000 rows, 0.5 to 8 M entries, 32 to 128 features.  Where the
+// rule takes pieces out, against taking out only those of more than two average lists (256 to 2048 entries): 1.34 times as
+// fast below 2^20 entries (0.85 to 2.8), 1.45 between 2^20 and 2^21 (0.84 to 2.9), 1.60 up to 2^22 (1.1 to 3.6), 1.42 beyond
+// (0.96 to 2.9); the third case alone 1.45 (0.84 to 3.6).  Where it leaves all in the lists, taking them out would be
+// 1.13 times as fast in the mean, but 0.78 to 2.0.  From two chunks on instead of one: 8 % slower between 2^20 and 2^21; from four
+// on: 12 % slower between 2^19 and 2^20, 9 % below (60 graphs).
 int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int32_t n_phases, int64_t longest_row,
                           bool rounds, const sptir_build_options_t& opt) {
   if (opt.heavy_len >= 1) return opt.heavy_len;
@@ -1156,7 +1160,7 @@ int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int
   const bool worth = (longest >= (small ? 32 : 16) * kChunkSlots && longest >= 2 * per_list) || nnz >= (1 << 22) ||
                      (!small && n_row_blocks < 1024 && longest >= 12 * kChunkSlots);
   if (!uneven || !worth) return kHeavyLenMax;
-  return nnz >= (1 << 21) ? kChunkSlots : nnz >= (1 << 20) ? 2 * kChunkSlots : 4 * kChunkSlots;
+  return kChunkSlots;
 }
 
 }  // namespace
