@@ -1143,12 +1143,13 @@ bool partitions_matter(int32_t c, int32_t w, int32_t n_rows, int64_t slots, long
 //  * or the graph is large enough for 8 microseconds not to matter;
 //  * or it has so few lists that they leave most of the GPU idle.
 // An even matrix (no row four times the mean) keeps all of its pieces in the lists.  Pieces leave from one chunk on.
-// Measured on 260 graphs with power-law degrees, 2,500 to 170,000 rows, 0.5 to 8 M entries, 32 to 128 features.  Where the
-// rule takes pieces out, against taking out only those of more than two average lists (256 to 2048 entries): 1.34 times as
-// fast below 2^20 entries (0.85 to 2.8), 1.45 between 2^20 and 2^21 (0.84 to 2.9), 1.60 up to 2^22 (1.1 to 3.6), 1.42 beyond
-// (0.96 to 2.9); the third case alone 1.45 (0.84 to 3.6).  Where it leaves all in the lists, taking them out would be
+// Measured on 320 graphs with power-law degrees, 2,500 to 235,000 rows, 60,000 to 8 M entries, 32 to 128 features.  Where the
+// rule takes pieces out, against the rule before it (nothing out below 2^19 entries, beyond that pieces of more than two
+// average lists, 256 to 2048 entries): 1.78 times as fast below 2^19 entries, 1.35 up to 2^20, 1.46 up to 2^21, 1.60 up to
+// 2^22, 1.42 beyond (single graphs 0.84 to 3.6); the third case alone 1.45.  160 to 256 features (200 graphs): 1.15, 1.10, 1.07,
+// 1.20, 1.15 (0.70 to 2.6: the partial sums of wide rows cost more).  Where it leaves all in the lists, taking them out would be
 // 1.13 times as fast in the mean, but 0.78 to 2.0.  From two chunks on instead of one: 8 % slower between 2^20 and 2^21; from four
-// on: 12 % slower between 2^19 and 2^20, 9 % below (60 graphs).
+// on: 12 % slower between 2^19 and 2^20, 9 % below.
 int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int32_t n_phases, int64_t longest_row,
                           bool rounds, const sptir_build_options_t& opt) {
   if (opt.heavy_len >= 1) return opt.heavy_len;

@@ -769,14 +769,20 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   if (chunks > 65535) return SPTIR_ERR_OVERFLOW;
   const bool ordered = d_out <= p->workspace_d_out;
   // Where the matrices W[r] are large (32 KB and up, more than L1 holds) the tiles are long, and a few hundred workgroups
-  // leave the CUs unevenly filled: every item is then shared by as many workgroups as make 512, eight wavefronts each,
-  // whose sums meet in Y by atomics (8,370 rows, 128 x 128, 262 items: 0.215 -> 0.168 ms; 1024 or 256 workgroups, 4 or
-  // 16 wavefronts each were slower).
+  // leave the CUs unevenly filled: items are then shared by several, eight wavefronts each, whose sums meet in Y by
+  // atomics, until there are 512 (8,370 rows, 128 x 128, 262 items: 0.215 -> 0.168 ms).  Clearing Y and the atomics have to be
+  // worth it, so an item needs 200,000 elements of W to read for two sharers and 250,000 more for each further one (27,608
+  // rows, 64 x 128, 188,000: 35 us alone, 80 shared by two; 6,903 rows, 128 x 128, 328,000: 75 alone, 62 by two, 72 by three;
+  // 6,110 rows, 983,000: 144 alone, 120 by two, 117 by three).  Where there are fewer than 160 row blocks all are
+  // divided into items already (26 graphs, shared until there were 512 workgroups: 12 % slower in the mean, up to 1.7 times).
   const int64_t whole = (int64_t)p->n_items * chunks;
   const bool large_w = d_in * d_out >= 64 * 128;
-  a.sharers = !ordered && large_w && whole < 512 ? (int32_t)std::min<int64_t>(8, (512 + whole - 1) / whole) : 1;
+  const int64_t tiles_each = p->n_tiles / std::max<int64_t>(p->n_items, 1), w_each = tiles_each * d_in * d_out;
+  const bool undivided = ((int64_t)p->n_rows - 1) >> p->log2_block >= 159;
+  a.sharers = 1;
+  if (!ordered && large_w && undivided && whole < 512 && w_each >= 200000)
+    a.sharers = (int32_t)std::min<int64_t>(std::max<int64_t>(2, w_each / 250000), std::min<int64_t>(8, (512 + whole - 1) / whole));
   // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do
-  const int64_t tiles_each = p->n_tiles / std::max<int64_t>((int64_t)p->n_items * a.sharers, 1);
   a.n_waves = large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;
   const size_t lds = sizeof(double) * ((size_t)a.width << p->log2_block) + (ordered ? sizeof(int) * (a.width / 16) : 0);
   const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);
