@@ -115,6 +115,7 @@ def test_scratch_blocks_are_kept_and_released(gpu_lib):
     """Under the default allocator the temporaries of a build are kept for the next one: repeated builds (the same
     sizes, then larger and smaller ones) stay bit-exact, and sptir_release_scratch gives the blocks back (free device
     memory does not shrink over the sequence)."""
+    build_both(gpu_lib, ragged_workload(1, 100, 100, 8, max_deg=40), 2, 3)[1].destroy()   # one-time set-up of the device
     gpu_lib.sptir_release_scratch()
     free0, _ = torch.cuda.mem_get_info()
     for n_rows, c, k in ((3000, 4, 5), (3000, 4, 5), (9000, 7, 3), (500, 2, 8), (3000, 4, 5)):
@@ -574,6 +575,27 @@ def test_spmm_and_sddmm_replay_in_a_hip_graph(gpu_lib):
         gpu_lib.sptir_sddmm(plan, d.values, Xl, X, B_eager)
         torch.cuda.synchronize()
         assert torch.equal(Y, Y_eager) and torch.equal(B, B_eager), f"replay {rep}"
+
+
+@pytest.mark.parametrize("release", [0, 1])
+@pytest.mark.parametrize("n_rows,n_cols,c,k", [(1, 1, 1, 0), (255, 300, 1, 5), (257, 90, 3, 2), (3000, 3100, 16, 5),
+                                               (3000, 500, 70, 0), (9000, 9000, 4, 10)])
+def test_canonical_arrays_without_a_spmm_plan(gpu_lib, n_rows, n_cols, c, k, release):
+    """no_spmm_plan: the canonical arrays as ever (they stay, whatever release_canonical says), no lists, no stream, and
+    sptir_spmm refuses the handle."""
+    w = ragged_workload(n_rows + c, n_rows, n_cols, 8, max_deg=min(n_cols, 400), long_rows=min(3, n_rows))
+    d, hyb, got, want, info = build_both(gpu_lib, w, c, k, {"no_spmm_plan": 1, "release_canonical": release})
+    assert_same_hyb(got, want)
+    assert info["nnz"] == w.nnz and info["n_work_items"] == 0 and info["n_heavy_items"] == 0 and info["n_row_blocks"] == 0
+    for name in ("plan_rb_chunk_ptr", "plan_rb_order", "plan_row_slots", "plan_heavy_rows", "plan_stream"):
+        assert gpu_lib.sptir_hyb_array(hyb, name).size == 0, name
+    Y = torch.full((n_rows, 8), 7.0, device="cuda")
+    for call in (gpu_lib.sptir_spmm, gpu_lib.sptir_spmm_noalloc):
+        with pytest.raises(gpu_lib.SptirError) as e:
+            call(hyb, d.X, Y)
+        assert e.value.status == 6
+    assert (Y == 7.0).all()
+    hyb.destroy()
 
 
 def test_kept_blocks_are_counted_and_bounded(gpu_lib):
