@@ -420,14 +420,18 @@ sptir_status_t sptir_sddmm_plan_destroy(sptir_sddmm_plan_t* plan); /* NULL is ac
  * Relational gather-matmul-scatter (RGMS equation of Section 4.4):
  *     Y[i,l] = sum_r sum_j sum_k A[r,i,j] * X[j,k] * W[r,k,l]
  * with A a 3-D sparse tensor of n_relations slices, each n_rows x n_cols.  As
- * in the paper, every slice is decomposed into hyb(1, k) buckets (k = 5 unless
- * given) and one fused kernel gathers rows of X, multiplies by W[r] on the
- * matrix cores and scatters into Y; X W[r] is never materialised.
+ * in the paper, one fused kernel gathers rows of X, multiplies by W[r] on the
+ * matrix cores and scatters into Y; X W[r] is never materialised.  Where the
+ * paper decomposes every slice into hyb(1, 5) buckets and goes relation by
+ * relation, the handle here holds the entries in their order, cut into tiles of
+ * up to 16 (relation, row) pairs by blocks of rows of Y, and a workgroup keeps
+ * the sums of its block on chip: no bucket is built and nothing is padded.
  *   stacked   A as one CSR matrix of n_relations * n_rows rows and n_cols
  *             columns: stacked row r * n_rows + i holds A[r,i,:] (device arrays,
  *             int32 indices strictly ascending inside a stacked row, float32
  *             values; validated like sptir_hyb_build's input)
- *   max_bucket_log2   0..5, or negative for the paper's 5
+ *   max_bucket_log2   0..5, or negative for the paper's 5: the k of the hyb(1, k) whose padding
+ *             sptir_rgms_info_t.n_pad_slots counts; the handle and sptir_rgms do not depend on it
  *   workspace_d_out   0, or a multiple of 32: sptir_rgms calls with d_out <= workspace_d_out then add their products
  *             in a fixed order, and results are reproducible bit for bit, for 5 to 30 % more time.  The handle also owns the
  *             memory in which the sums of divided row blocks meet (see sptir_rgms_info_t.n_tiles); it is far
@@ -441,9 +445,9 @@ typedef struct sptir_rgms_handle sptir_rgms_t;
 typedef struct {
   int32_t n_relations, n_rows, n_cols, max_bucket_log2;
   int64_t nnz;
-  int64_t n_stacked_rows_stored;  /* (relation, row) pairs with at least one entry, remainder pieces included */
-  int64_t n_pad_slots;            /* of the hyb(1, k) decomposition */
-  int64_t n_tiles;                /* matrix-core products: up to 16 (relation, row) pairs of one relation and row block */
+  int64_t n_stacked_rows_stored;  /* (relation, row) pairs with at least one entry */
+  int64_t n_pad_slots;            /* what a hyb(1, max_bucket_log2) decomposition of the slices would pad */
+  int64_t n_tiles;                /* matrix-core products: up to 16 pieces of at most 8 entries, of one relation and row block */
   int32_t workspace_d_out;        /* widest d_out that is summed in a fixed order (0: none) */
   int32_t reserved;
   int64_t device_bytes;

@@ -1,7 +1,6 @@
 """GPU parity tests of the relational gather-matmul-scatter operator: through the C ABI, against the fp64 oracle.
-Criterion: |Y_gpu - Y_oracle| <= 1e-5 * sum |a x w| per element of Y (float32 products and sums, the
-contributions meeting in float atomic adds in any order), and exactly 0 where that sum is 0.  The 3-D hyb arrays
-(the hyb(1, k) of the stacked matrix) are covered bit for bit by the builder tests; here the operator is checked."""
+Criterion: |Y_gpu - Y_oracle| <= 1e-5 * sum |a x w| per element of Y (float32 products, float32 sums inside a (relation,
+row) pair, float64 sums over pairs in any order), and exactly 0 where that sum is 0."""
 import numpy as np
 import pytest
 import torch
@@ -128,8 +127,7 @@ def capped_hetero(seed, n, n_rel, cap, d=32):
 
 
 def test_rgms_workspace_path_is_reproducible(gpu_lib):
-    """With the workspace, and no (relation, row) pair longer than the widest bucket (so nothing goes to the
-    remainder, whose pieces meet in atomic adds), every sum has a fixed order: calls agree bit for bit."""
+    """With the workspace every sum has a fixed order: calls agree bit for bit."""
     wl = capped_hetero(9, 700, 5, 32)
     assert np.diff(wl.indptr).max() == 32
     (Y1, Y2, Y3), info = run_rgms(gpu_lib, wl, workspace_d_out=32, repeat=3)
@@ -137,7 +135,7 @@ def test_rgms_workspace_path_is_reproducible(gpu_lib):
     assert np.array_equal(Y1, Y2) and np.array_equal(Y1, Y3)
     Yr, Sr = oracle.rgms(wl.n_rel, wl.n, wl.indptr, wl.indices, wl.values, wl.X, wl.W)
     assert_y_close(Y1, Yr, Sr, "capped workspace")
-    # and on a graph with remainder pieces the two paths agree with the oracle to rounding
+    # and on a graph with longer pairs the two paths agree with the oracle to rounding
     w = workloads.make_hetero("hetero_a")
     assert np.diff(w.indptr).max() > 32
     Ya, _ = run_rgms(gpu_lib, w, workspace_d_out=0)
