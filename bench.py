@@ -291,8 +291,8 @@ def main():
         build_times.append((time.perf_counter() - t0) * 1e3)
         hyb2.destroy()
     build_ms = sorted(build_times)[1]
-    # the same with the library's device memory coming from torch's caching allocator (sptir_set_allocator): the
-    # difference is what hipMalloc of the handle's arrays costs (temporaries are kept between builds either way)
+    # the same with the library's device memory coming from torch's caching allocator (sptir_set_allocator); the default
+    # allocator keeps the blocks of released handles and temporaries itself, none larger than 1 GB
     sptir.sptir_set_allocator(True)
     try:
         cached_times = []
@@ -516,15 +516,14 @@ def main():
             hY = torch.empty(hw.n, 32, device=dev)
             rg_ms = timed(lambda: sptir.sptir_rgms(rg, hX, hW, hY), reps=20)
             pairs = rinfo["n_stacked_rows_stored"]
-            # algorithmic bytes: a 128-byte row of X in per non-zero, a 128-byte row of Y out per (relation, row)
-            # pair, 8 bytes per stored slot, W once
-            slots = hw.nnz + rinfo["n_pad_slots"]
-            rg_bytes = 128.0 * hw.nnz + 128.0 * pairs + 8.0 * slots + 4.0 * hw.W.size
+            # algorithmic bytes: a 128-byte row of X in and 8 bytes of column and value per non-zero, Y and W once
+            rg_bytes = 136.0 * hw.nnz + 128.0 * hw.n + 4.0 * hw.W.size
             out["rgms_feat32"].append({
                 "workload": "%s: %d nodes, %d relations, %d non-zeros, d_in = d_out = 32" % (hname, hw.n, hw.n_rel, hw.nnz),
                 "ms_per_step": round(rg_ms, 4), "build_ms": round(rg_build_ms, 3),
                 "gflops": round((2.0 * hw.nnz * 32 + 2.0 * pairs * 32 * 32) / rg_ms / 1e6, 1),
-                "scatter_gbs": round(pairs * 128.0 / rg_ms / 1e6, 1), "tiles": rinfo["n_tiles"],
+                "gather_gbs": round(hw.nnz * 128.0 / rg_ms / 1e6, 1), "tiles": rinfo["n_tiles"],
+                "entries_per_tile": round(hw.nnz / max(rinfo["n_tiles"], 1), 2),
                 "roofline": {"bound": "hbm", "achieved": round(rg_bytes / rg_ms / 1e6, 1), "peak": HBM_PEAK_GBS,
                              "unit": "GB/s", "frac": round(rg_bytes / rg_ms / 1e6 / HBM_PEAK_GBS, 4),
                              "algorithmic_bytes": rg_bytes}})
