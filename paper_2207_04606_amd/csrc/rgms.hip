@@ -9,9 +9,13 @@
 // workgroup owns a block, keeps its rows of Y in LDS, walks the block's pairs
 // (r, i) relation after relation and writes Y once.  The scatter of the
 // relation-stationary order (a float atomic per element of every pair's product
-// row, at L2) was what bound it.  32 x 32 features: 94 K rows, 51 relations, 4.76 M entries 0.257 -> 0.171 ms; 1.38 M rows, 25
-// relations, 5.6 M entries 0.472 -> 0.310; 1.9 M rows, 96 relations, 5.7 M entries 0.560 -> 0.519, where a
-// (relation, block) has few entries and what bounds the kernel is the trips to L2 for W[r].
+// row, at L2) was what bound it.  32 x 32 features: 94 K rows, 51 relations, 4.76 M entries 0.257 -> 0.159 ms; 1.38 M rows, 25
+// relations, 5.6 M entries 0.472 -> 0.294; 1.9 M rows, 96 relations, 5.7 M entries 0.560 -> 0.503, where a
+// (relation, block) has few entries and what bounds the kernel is the trips to L2 for W[r].  Over 250 graphs and feature
+// sizes it is 1.22 times as fast in the mean (1.5 to 2 with a workspace), but 58 of them lost: a tile reads all of W[r] however
+// few pairs it holds, where the relation-stationary tiles held 32, so wide W[r] with few entries per (relation, block) take up
+// to 2.3 times as long (1.7 M rows, 54 relations, 1.4 M entries, 128 x 128: 1.07 -> 2.43 ms; 9,788 rows, 52 relations, 30 K entries, 64 x 64:
+// 19 -> 35 us).
 //
 // The entries of (relation, block) are consecutive in the stacked CSR, so the handle needs little more than a copy of the
 // entries in their order.  A piece is the entries of one pair (longer pairs are several pieces of 8), a tile up to
@@ -540,7 +544,8 @@ __global__ __launch_bounds__(256) void k_pair_entries(int64_t nnz, const int32_t
 }
 
 // Rows per block: 32 entries for every (relation, block), so that tiles fill (16: 4 to 14 % slower, 64: the same), as long
-// as that leaves 160 blocks, about what keeps the matrix cores of 256 CUs busy with 16 wavefronts each.  Fewer,
+// as that leaves 160 blocks, about what keeps the matrix cores of 256 CUs busy with 16 wavefronts each.  (60 graphs, 32 x 32: the
+// best block for each is 2.7 % faster in the mean, 20 % at most; any one size for all 16 to 34 % slower.)  Fewer,
 // larger blocks divided into items were tried and lose more in global atomics than fuller tiles gain (27,163 rows,
 // 64 x 64: 0.042 -> 0.093 ms).
 int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz) {
@@ -782,7 +787,8 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   a.sharers = 1;
   if (!ordered && large_w && undivided && whole < 512 && w_each >= 200000)
     a.sharers = (int32_t)std::min<int64_t>(std::max<int64_t>(2, w_each / 250000), std::min<int64_t>(8, (512 + whole - 1) / whole));
-  // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do
+  // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs
+  // and feature sizes: against 8 everywhere it is alike in the mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)
   a.n_waves = large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;
   const size_t lds = sizeof(double) * ((size_t)a.width << p->log2_block) + (ordered ? sizeof(int) * (a.width / 16) : 0);
   const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);

@@ -19,9 +19,10 @@
 // The fourth lane of a tail reads (and writes) the last four floats of the
 // row, so any feature size of four or more uses 16-byte accesses; they need
 // only 4-byte alignment.
-// Measured (169,343 rows, 1,166,243 entries, 128 features): 0.65 -> 0.116 ms,
-// 5.1 TB/s of gathered rows of which a quarter hit L2, near what the memory-side
-// cache delivers at random (7.9).
+// Measured (169,343 rows, 1,166,243 entries, 128 features): 0.65 -> 0.127 ms on
+// operands that change from call to call (0.113 on the same ones), 4.7 TB/s of
+// gathered rows of which a quarter hit L2; the memory-side cache delivers 7.9 at
+// random.
 #include <type_traits>
 
 #include "sptir_internal.h"
@@ -193,13 +194,16 @@ extern "C" sptir_status_t sptir_spmm_csr(const sptir_csr_t* csr, const float* X,
   // A row of X that is not whole 128-byte lines has its tiles across line ends: tiles of 64 floats then touch fewer
   // lines per row than tiles of 32 (41 features on 132,534 rows: 0.217 -> 0.143 ms).  Where X is small enough for
   // L2 the lines are cheap and the narrower lane groups keep more rows in flight (20,000 rows, 41 features: 24 against
-  // 27 us); they change over near 8 MB.
+  // 27 us); they change over near 8 MB.  (120 graphs: above it the wide tiles are 1.16 times as fast in the mean, 0.74 to 1.6;
+  // from 4 to 8 MB the two are alike; below the narrow ones are 1.18 times as fast, 0.67 to 1.8.)
   if (feat > 32 && feat % 32 != 0 && x_bytes > ((size_t)8 << 20)) g.lg = 16;
   g.n_tiles = (feat + g.vec * g.lg - 1) / (g.vec * g.lg);
   // Rows per workgroup: 64, or fewer where workgroups of 64 would leave CUs idle and rows are long enough for a wavefront
   // each (a small dense graph: 4,168 rows, 603,937 entries, 32 features: 43 -> 17 us with 8 rows; 8,382 rows, 1.2 M, 64
   // features: 44 -> 29 with 16).  Short rows want eight of them per wavefront however few there are (10,403 rows of 20
-  // entries: 9 us against 14).
+  // entries: 9 us against 14).  On 120 graphs: long rows in few workgroups, 16 rows 1.35 times as fast as 64 (0.9 to 2);
+  // long rows in 512 workgroups and more, 64 and 16 alike; short rows, 64 rows 1.18 times as fast as 16 (from 512
+  // workgroups on 1.29, below 0.91) and 1.7 times as fast as 8.
   const int64_t n_wg = ((int64_t)csr->n_rows + kCsrRows - 1) / kCsrRows * g.n_tiles;
   const bool dense = csr->nnz >= 40 * (int64_t)csr->n_rows;
   const int rows = !dense || n_wg >= 512 ? kCsrRows : n_wg >= 128 ? 16 : 8;
