@@ -1109,7 +1109,7 @@ int log2_row_block_setting(int32_t n_rows, bool rounds, bool several_launches, b
     const long tiles = opt.feat_hint > 0 ? (opt.feat_hint + 31) / 32 : 4;
     // A launch per group of partitions ends in a partly filled GPU that many times: three times the 3,300 wavefronts that
     // are resident at 64 rows keep that small (132,534 rows, 39.6 M entries, 8 launches, 32 rows instead of 64: 1.07 ->
-    // 1.04 ms; 106,797 rows, 9.8 M, 33 features: 212 -> 188 us).  On 80 graphs in several launches the rule is 7 % faster than
+    // 1.04 ms).  On 80 graphs in several launches the rule is 7 % faster than
     // 64 rows for all and level with 32 or 16 for all; the best size for each graph would be 5 % faster, 29 % at most.
     while (v > 16 && (n_rows / v) * tiles < (several_launches ? 10240 : 6144)) v >>= 1;
     // ... but keep at least ~1024 row blocks, or the 256 CUs do not fill

@@ -29,9 +29,10 @@
 // There is nothing to accumulate across partitions - an entry's result is
 // complete where it is computed - so one launch covers all of them.
 //
-// Measured: CSR order, 169,343 rows, 1.17 M entries: 64 features 97 -> 53 us, 32: 91 -> 28, 128: 127 -> 104 (5.7 TB/s of
-// gathered rows, all beyond L2); 41 features, 1.5 M entries 612 -> 49 us; 2,708 rows 42 -> 12 us.  With a plan, 232,965
-// rows, 114.6 M entries, 128 features: 3.56 -> 3.47 ms; 20 M entries, 53 features 3.20 -> 0.54 ms.
+// Measured: CSR order, 169,343 rows, 1.17 M entries: 64 features 97 -> 53 us (50 on the same operands again), 32: 91 -> 27, 128:
+// 127 -> 102 (5.8 TB/s of gathered rows, all beyond L2); 41 features, 1.5 M entries 612 -> 47 us; 2,708 rows 42 -> 7 us, most of
+// which is the call.  With a plan, 232,965 rows, 114.6 M entries, 128 features: 3.56 -> 3.46 ms; 20 M entries, 53 features
+// 3.20 -> 0.55 ms.
 #include <string.h>
 
 #include <algorithm>

@@ -773,15 +773,14 @@ void launch_heavy(V, const Geometry& g, hipStream_t stream, const HeavyArgs& a) 
 // 61,403 rows of 5 floats a dword a lane took 2.4 times as long); fewer than four features: a lane each.
 //
 // Rows that are no whole number of 128-byte lines: a piece of 128 bytes lies across two of them, so 8 lanes fetch nearly
-// every line twice, 16 lanes three lines for two (50,021 rows, 41 floats, 1.5 M non-zeros: 93 -> 53 us; 132,534 rows, 50
-// floats, 39.6 M: 1.12 -> 0.87 ms).  But 16 lanes make half as many wavefronts, each with twice as far to go: they are
+// every line twice, 16 lanes three lines for two (50,021 rows, 41 floats, 1.5 M non-zeros: 74 us against 52; 132,534 rows, 50
+// floats, 39.6 M: 1.03 ms against 0.71).  But 16 lanes make half as many wavefronts, each with twice as far to go: they are
 // taken where that does not leave the GPU waiting for the longest list -- in rounds, whose lists are about equally long,
-// unless X lies in an XCD's L2 (21,403 rows, 36 floats: 68 us against 48);
-// with at least 5000 wavefronts (30,000 rows, 200 floats, 1.8 M: 301 -> 185 us; with 3750, 60,000 rows of 100 floats
-// lost 12 %); or with an X so far beyond an XCD's L2 (26 MB) that the lines fetched twice decide (169,343 rows, 41 floats, 2646
-// wavefronts: 115 -> 87 us).  On 300 graphs 16 lanes are 1.21 times as fast where the first rule takes them (1.02 to 1.44), 1.20
-// where the second does (0.65 to 2.4; what loses is power-law graphs whose longest list is six times the mean) and 1.39 where
-// the third does (1.03 to 2.2); where none does, 8 lanes are 1.06 times as fast (0.49 to 1.6).
+// unless X lies in an XCD's L2; with at least 5000 wavefronts; or with an X so far beyond an XCD's L2 (26 MB) that the lines
+// fetched twice decide (169,343 rows, 41 floats, 2646 wavefronts: 96 us against 61).  On 300 graphs 16 lanes are 1.21 times as
+// fast where the first rule takes them (1.02 to 1.44), 1.20 where the second does (0.65 to 2.4; what loses is power-law graphs
+// whose longest list is six times the mean) and 1.39 where the third does (1.03 to 2.2); where none does, 8 lanes are 1.06
+// times as fast (0.49 to 1.6).
 void lane_shape(int32_t feat, bool aligned16, const ListShape& lists, int* vec, int* lg) {
   *vec = 4;
   if (lists.full_rows && full_rows_fit(lists.log2_row_block) && feat % 128 == 0 && aligned16) {
