@@ -476,7 +476,8 @@ def _torch_free(ptr, ctx):
 
 
 def sptir_release_scratch() -> None:
-    """Frees the temporary device blocks the library keeps between builds under the default allocator."""
+    """Frees the device blocks the library keeps under the default allocator: temporaries of builds and the blocks of
+    destroyed hyb handles."""
     lib = load_library()
     lib.sptir_release_scratch.restype = ctypes.c_int
     st = lib.sptir_release_scratch()
