@@ -377,7 +377,9 @@ sptir_status_t sptir_sddmm_csr(const sptir_csr_t* csr, const float* X, const flo
  * The same SDDMM with its entries visited in column-partition order, the way
  * Section 4.2.1 partitions columns for cache locality: a plan lists the entries
  * of every partition, each of the 8 XCDs sweeps its own partitions one after
- * the other, and the rows of Yt of one partition stay in that XCD's L2.  The
+ * the other, and the rows of Yt of one partition stay in that XCD's L2.  Where
+ * rows are so long that each has entries in every slice of columns whose rows of
+ * Yt (at feat_hint) fit a workgroup's LDS, they are listed by slices instead.  The
  * plan depends on the sparse structure only and is reused for any values, X,
  * Yt and feat.
  *   n_col_parts  number of column partitions; 0 chooses it from feat_hint (the
@@ -386,17 +388,17 @@ sptir_status_t sptir_sddmm_csr(const sptir_csr_t* csr, const float* X, const flo
  *   csr->values  is not read (may be NULL); indptr / indices are device arrays,
  *                columns strictly ascending inside a row (UNSORTED if the pieces
  *                do not tile the rows)
- * The plan owns device memory of about 12 bytes per non-zero, obtained through
+ * The plan owns device memory of about 12 bytes per non-zero (of long rows 3 to 8), obtained through
  * the allocator hook; sptir_sddmm_plan_build synchronises `stream`.
  */
 typedef struct sptir_sddmm_plan sptir_sddmm_plan_t;
 
 typedef struct {
   int32_t n_rows, n_cols;
-  int32_t n_col_parts;  /* partitions in use (1: entries stay in CSR order) */
+  int32_t n_col_parts;  /* partitions in use (1: entries that are not in column slices stay in CSR order) */
   int32_t part_width;
   int64_t nnz;
-  int64_t n_runs;       /* runs of at most 512 entries, one wavefront each (0 when n_col_parts == 1) */
+  int64_t n_runs;       /* runs of at most 512 entries, one wavefront each, of the rows that are not long (below) */
   int64_t device_bytes;
 } sptir_sddmm_plan_info_t;
 

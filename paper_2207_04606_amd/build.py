@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsptir.so")
-SOURCES = ["api.hip", "builder.hip", "order.hip", "spmm.hip", "spmm_csr.hip", "sddmm.hip", "search.hip", "rgms.hip", "roof.hip"]
+SOURCES = ["api.hip", "builder.hip", "order.hip", "spmm.hip", "spmm_csr.hip", "sddmm.hip", "sddmm_slices.hip", "search.hip", "rgms.hip", "roof.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -30,7 +30,7 @@ def is_stale() -> bool:
         return True
     t = os.path.getmtime(LIB)
     deps = sources() + [os.path.join(CSRC, "sptir_internal.h"), os.path.join(CSRC, "sptir_scan.h"),
-                        os.path.join(CSRC, "sptir_tiles.h"),
+                        os.path.join(CSRC, "sptir_tiles.h"), os.path.join(CSRC, "sddmm_lanes.h"),
                         os.path.join(ROOT, "include", "sptir.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 

@@ -28,6 +28,7 @@
 // other, so an XCD's L2 holds the rows of Yt of one partition at a time.
 // There is nothing to accumulate across partitions - an entry's result is
 // complete where it is computed - so one launch covers all of them.
+// Rows with entries in every slice of columns that fits LDS leave the lists (sddmm_slices.hip).
 //
 // Measured: CSR order, 169,343 rows, 1.17 M entries: 64 features 97 -> 53 us (50 on the same operands again), 32: 91 -> 27, 128:
 // 127 -> 102 (5.8 TB/s of gathered rows, all beyond L2); 41 features, 1.5 M entries 612 -> 47 us; 2,708 rows 42 -> 7 us, most of
@@ -39,6 +40,7 @@
 #include <new>
 #include <vector>
 
+#include "sddmm_lanes.h"
 #include "sptir_internal.h"
 #include "sptir_scan.h"
 #include "sptir_tiles.h"
@@ -69,31 +71,6 @@ struct SddmmArgs {
   const int32_t* run_len;          //           partition, run_len of them), runs grouped by XCD
   const int32_t* xcd_run_ptr;      // [9]: the runs of XCD x are xcd_run_ptr[x] .. xcd_run_ptr[x+1]
 };
-
-__device__ __forceinline__ float dot4(const float4& a, const float4& b, float acc) {
-  acc = fmaf(a.x, b.x, acc);
-  acc = fmaf(a.y, b.y, acc);
-  acc = fmaf(a.z, b.z, acc);
-  return fmaf(a.w, b.w, acc);
-}
-
-// Eight partial sums per lane -> lane fl of every 8-lane group ends with the group's total of p[fl].
-__device__ __forceinline__ float reduce_scatter8(float (&p)[8], int fl) {
-  float q[4], r[2];
-  const bool hi4 = (fl & 4) != 0, hi2 = (fl & 2) != 0, hi1 = (fl & 1) != 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {  // partner fl^4 keeps the other half
-    float keep = hi4 ? p[i + 4] : p[i], give = hi4 ? p[i] : p[i + 4];
-    q[i] = keep + __shfl_xor(give, 4, 64);
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    float keep = hi2 ? q[i + 2] : q[i], give = hi2 ? q[i] : q[i + 2];
-    r[i] = keep + __shfl_xor(give, 2, 64);
-  }
-  float keep = hi1 ? r[1] : r[0], give = hi1 ? r[0] : r[1];
-  return keep + __shfl_xor(give, 1, 64);
-}
 
 // The 64 entries of a chunk as the lanes hold them.
 struct ChunkEntries {
@@ -351,12 +328,16 @@ int32_t csr_run(int64_t nnz) {
 }
 
 // ------------------------------------------------------------------- plan
-// lens[p * n_rows + r] = entries of row r in column partition p
+// lens[p * n_rows + r] = entries of row r in column partition p; none where the slices have the row (rank, may be NULL, goes up)
 __global__ void k_piece_lengths(int32_t n_rows, int32_t c, int32_t w, const int32_t* __restrict__ indptr,
-                                const int32_t* __restrict__ indices, int32_t* lens) {
+                                const int32_t* __restrict__ indices, const int32_t* __restrict__ rank, int32_t* lens) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)n_rows * c) return;
   int r = (int)(t % n_rows), p = (int)(t / n_rows);
+  if (rank && rank[r + 1] > rank[r]) {
+    lens[t] = 0;
+    return;
+  }
   int a = indptr[r], b = indptr[r + 1];
   int first = (p == 0) ? a : lower_bound_col(indices, a, b, (int64_t)p * w);
   int last = (p == c - 1) ? b : lower_bound_col(indices, first, b, (int64_t)(p + 1) * w);
@@ -366,12 +347,13 @@ __global__ void k_piece_lengths(int32_t n_rows, int32_t c, int32_t w, const int3
 // Copies every (row, partition) piece to its place in the partition-ordered entry list:
 // offs[p * n_rows + r] is the piece's offset inside partition p, part_first[p] the partition's first entry.
 __global__ void k_scatter_entries(int32_t n_rows, int32_t c, int32_t w, const int32_t* __restrict__ indptr,
-                                  const int32_t* __restrict__ indices, const int32_t* __restrict__ offs,
-                                  const int64_t* __restrict__ part_first, int32_t* e_row, int32_t* e_col,
-                                  int32_t* e_pos) {
+                                  const int32_t* __restrict__ indices, const int32_t* __restrict__ rank,
+                                  const int32_t* __restrict__ offs, const int64_t* __restrict__ part_first, int32_t* e_row,
+                                  int32_t* e_col, int32_t* e_pos) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)n_rows * c) return;
   int r = (int)(t % n_rows), p = (int)(t / n_rows);
+  if (rank && rank[r + 1] > rank[r]) return;
   int a = indptr[r], b = indptr[r + 1];
   int first = (p == 0) ? a : lower_bound_col(indices, a, b, (int64_t)p * w);
   int last = (p == c - 1) ? b : lower_bound_col(indices, first, b, (int64_t)(p + 1) * w);
@@ -395,14 +377,15 @@ bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
 struct sptir_sddmm_plan {
   int32_t n_rows, n_cols, c, w;
   int64_t nnz;
-  // c >= 2: the entries in partition order and the runs of every XCD
+  // otherwise: the long rows in column slices, the entries of the others in partition order and the runs of every XCD
+  sptir::SddmmSlices slices;
   int32_t *e_row, *e_col, *e_pos;
   int64_t* run_first_entry;
   int32_t* run_len;
   int32_t* xcd_run_ptr;
   int64_t n_runs;
   int64_t max_runs_per_xcd;
-  // c == 1: entries stay in CSR order; the plan keeps its own copy of the structure
+  // c == 1 and no long rows: entries stay in CSR order; the plan keeps its own copy of the structure
   int32_t *indptr, *indices;
   size_t device_bytes;
   sptir_alloc_fn alloc;
@@ -417,6 +400,7 @@ extern "C" sptir_status_t sptir_sddmm_plan_destroy(sptir_sddmm_plan_t* p) {
   void* ptrs[] = {p->e_row, p->e_col, p->e_pos, p->run_first_entry, p->run_len, p->xcd_run_ptr, p->indptr, p->indices};
   for (void* q : ptrs)
     if (q) p->free_(q, p->alloc_ctx);
+  sddmm_slices_free(&p->slices, p->free_, p->alloc_ctx);
   delete p;
   return SPTIR_OK;
 }
@@ -462,11 +446,11 @@ extern "C" sptir_status_t sptir_sddmm_plan_build(const sptir_csr_t* csr, int32_t
 
   sptir_sddmm_plan* p = new (std::nothrow) sptir_sddmm_plan();
   if (!p) return SPTIR_ERR_ALLOC;
-  memset(p, 0, sizeof(*p));
   current_allocator(&p->alloc, &p->free_, &p->alloc_ctx);
   p->n_rows = n_rows; p->n_cols = n_cols; p->c = c; p->nnz = nnz;
   p->w = (int32_t)(((int64_t)n_cols + c - 1) / c);
   sptir_alloc_fn alloc = p->alloc; sptir_free_fn free_ = p->free_; void* actx = p->alloc_ctx;
+  int32_t* rank = nullptr;
   int32_t* lens = nullptr;
   int32_t* d_totals = nullptr;
   int64_t* d_part_first = nullptr;
@@ -482,7 +466,10 @@ extern "C" sptir_status_t sptir_sddmm_plan_build(const sptir_csr_t* csr, int32_t
     if (e_ != hipSuccess) { st = note_hip_error(e_, #call); goto fail; } \
   } while (0)
 
-  if (c == 1 || nnz == 0) {
+  st = sddmm_slices_build(csr, feat_hint, alloc, free_, actx, stream, &p->slices, &rank);
+  if (st != SPTIR_OK) goto fail;
+  p->device_bytes += p->slices.device_bytes;
+  if (nnz == 0 || (c == 1 && p->slices.n_units == 0)) {
     p->c = 1; p->w = n_cols;
     if (!take((void**)&p->indptr, sizeof(int32_t) * ((size_t)n_rows + 1)) ||
         !take((void**)&p->indices, sizeof(int32_t) * (size_t)nnz)) { st = SPTIR_ERR_ALLOC; goto fail; }
@@ -496,14 +483,14 @@ extern "C" sptir_status_t sptir_sddmm_plan_build(const sptir_csr_t* csr, int32_t
     return SPTIR_OK;
   }
   {
-    const int64_t n_pairs = (int64_t)n_rows * c;
+    const int64_t n_pairs = (int64_t)n_rows * c, n_listed = nnz - p->slices.nnz;
     lens = (int32_t*)alloc(sizeof(int32_t) * (size_t)n_pairs, actx, stream);
     d_totals = (int32_t*)alloc(sizeof(int32_t) * (size_t)c, actx, stream);
     d_part_first = (int64_t*)alloc(sizeof(int64_t) * (size_t)c, actx, stream);
     if (!lens || !d_totals || !d_part_first) { st = SPTIR_ERR_ALLOC; goto fail; }
     const unsigned pair_blocks = (unsigned)((n_pairs + 255) / 256);
     hipLaunchKernelGGL(k_piece_lengths, dim3(pair_blocks), dim3(256), 0, stream, n_rows, c, p->w, csr->indptr,
-                       csr->indices, lens);
+                       csr->indices, rank, lens);
     hipLaunchKernelGGL(k_scan_sequences<int32_t>, dim3((unsigned)c), dim3(kBuildBlock), 0, stream, lens, n_rows,
                        d_totals);
     PLAN_HIP(hipGetLastError());
@@ -516,13 +503,14 @@ extern "C" sptir_status_t sptir_sddmm_plan_build(const sptir_csr_t* csr, int32_t
       part_first[q + 1] = part_first[q] + totals[q];
     }
     // the pieces tile every row exactly when its columns ascend; anything else would not fit the arrays below
-    if (part_first[c] != nnz) { st = SPTIR_ERR_UNSORTED; goto fail; }
-    if (!take((void**)&p->e_row, sizeof(int32_t) * (size_t)nnz) || !take((void**)&p->e_col, sizeof(int32_t) * (size_t)nnz) ||
-        !take((void**)&p->e_pos, sizeof(int32_t) * (size_t)nnz)) { st = SPTIR_ERR_ALLOC; goto fail; }
+    if (part_first[c] != n_listed) { st = SPTIR_ERR_UNSORTED; goto fail; }
+    if (!take((void**)&p->e_row, sizeof(int32_t) * (size_t)n_listed) ||
+        !take((void**)&p->e_col, sizeof(int32_t) * (size_t)n_listed) ||
+        !take((void**)&p->e_pos, sizeof(int32_t) * (size_t)n_listed)) { st = SPTIR_ERR_ALLOC; goto fail; }
     PLAN_HIP(hipMemcpyAsync(d_part_first, part_first.data(), sizeof(int64_t) * (size_t)c, hipMemcpyHostToDevice,
                             stream));
     hipLaunchKernelGGL(k_scatter_entries, dim3(pair_blocks), dim3(256), 0, stream, n_rows, c, p->w, csr->indptr,
-                       csr->indices, lens, d_part_first, p->e_row, p->e_col, p->e_pos);
+                       csr->indices, rank, lens, d_part_first, p->e_row, p->e_col, p->e_pos);
     PLAN_HIP(hipGetLastError());
 
     // ---- partitions to XCDs (largest first onto the least loaded), runs of every XCD in partition order
@@ -544,12 +532,17 @@ extern "C" sptir_status_t sptir_sddmm_plan_build(const sptir_csr_t* csr, int32_t
     int64_t max_runs = 0;
     for (int x = 0; x < 8; ++x) {
       xcd_run_ptr[x] = (int32_t)run_first.size();
-      std::sort(of_xcd[x].begin(), of_xcd[x].end());
-      for (int32_t q : of_xcd[x]) {
-        for (int64_t off = 0; off < totals[q]; off += kSddmmRun) {
-          run_first.push_back(part_first[q] + off);
-          run_len.push_back((int32_t)std::min<int64_t>(kSddmmRun, totals[q] - off));
+      auto runs_of = [&](int64_t begin, int64_t end) {
+        for (int64_t at = begin; at < end; at += kSddmmRun) {
+          run_first.push_back(at);
+          run_len.push_back((int32_t)std::min<int64_t>(kSddmmRun, end - at));
         }
+      };
+      if (c == 1) {  // one partition: an eighth of its entries each
+        runs_of(n_listed * x / 8, n_listed * (x + 1) / 8);
+      } else {
+        std::sort(of_xcd[x].begin(), of_xcd[x].end());
+        for (int32_t q : of_xcd[x]) runs_of(part_first[q], part_first[q + 1]);
       }
       max_runs = std::max<int64_t>(max_runs, (int64_t)run_first.size() - xcd_run_ptr[x]);
     }
@@ -567,11 +560,13 @@ extern "C" sptir_status_t sptir_sddmm_plan_build(const sptir_csr_t* csr, int32_t
     PLAN_HIP(hipStreamSynchronize(stream));  // the host vectors go out of scope
   }
   free_(lens, actx); free_(d_totals, actx); free_(d_part_first, actx);
+  if (rank) free_(rank, actx);
   *out = p;
   return SPTIR_OK;
 
 fail:
   (void)hipStreamSynchronize(stream);
+  if (rank) free_(rank, actx);
   if (lens) free_(lens, actx);
   if (d_totals) free_(d_totals, actx);
   if (d_part_first) free_(d_part_first, actx);
@@ -597,10 +592,16 @@ extern "C" sptir_status_t sptir_sddmm(const sptir_sddmm_plan_t* p, const float* 
   a.e_row = p->e_row; a.e_col = p->e_col; a.e_pos = p->e_pos;
   a.run_first_entry = p->run_first_entry; a.run_len = p->run_len; a.xcd_run_ptr = p->xcd_run_ptr;
   a.run = csr_run(p->nnz);
-  if (p->c == 1) {
+  if (p->indptr) {
     const int64_t runs = (p->nnz + a.run - 1) / a.run;
     launch_sddmm<false>(a, dim3((unsigned)((runs + kSddmmWaves - 1) / kSddmmWaves)), stream);
   } else {
+    if (p->slices.n_units > 0) {
+      const sptir_status_t st = sddmm_slices_run(p->slices, p->n_cols, values, X, Yt, B_values, feat, stream);
+      if (st != SPTIR_OK) return st;
+    }
+    a.nnz = p->nnz - p->slices.nnz;
+    if (a.nnz == 0) return SPTIR_OK;
     launch_sddmm<true>(a, dim3((unsigned)(8 * ((p->max_runs_per_xcd + kSddmmWaves - 1) / kSddmmWaves))), stream);
   }
   SPTIR_HIP(hipGetLastError());

@@ -171,6 +171,23 @@ sptir_status_t order_row_blocks(const int64_t* rb_chunk_ptr, int32_t n_launches,
                                 int32_t* rb_order, sptir_alloc_fn alloc, sptir_free_fn free_, void* actx,
                                 hipStream_t stream, void** scratch_out);
 
+// The long rows of an SDDMM plan (sddmm_slices.hip): their entries by slices of `width` columns, in segments of up to eight entries of
+// one row.  n_units 0: none.
+struct SddmmSlices {
+  int32_t width = 0;
+  int64_t nnz = 0, n_segs = 0, n_units = 0;
+  int2* seg_at = nullptr;      // device
+  uint4* seg_cols = nullptr;
+  int4* units = nullptr;
+  size_t device_bytes = 0;
+};
+// *rank: device memory the caller frees, NULL if no row is taken; rank[r + 1] > rank[r] where row r is
+sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, sptir_alloc_fn alloc, sptir_free_fn free_, void* actx,
+                                  hipStream_t stream, SddmmSlices* out, int32_t** rank);
+void sddmm_slices_free(SddmmSlices* s, sptir_free_fn free_, void* actx);
+sptir_status_t sddmm_slices_run(const SddmmSlices& s, int32_t n_cols, const float* values, const float* X, const float* Yt, float* B,
+                                int32_t feat, hipStream_t stream);
+
 // records a failed HIP call for sptir_last_hip_error(); returns SPTIR_ERR_HIP
 sptir_status_t note_hip_error(hipError_t e, const char* what);
 

@@ -194,3 +194,51 @@ def test_sddmm_rows_of_a_chunk_and_row_ends(gpu_lib, gap, feat):
     Br, Mr = oracle.sddmm_csr(w.n_rows, w.indptr, w.indices, w.values, Xr, w.X)
     assert_b_close(run_sddmm(gpu_lib, w, Xr, w.X), Br, Mr, f"gap={gap} feat={feat}")
     assert_b_close(run_sddmm_plan(gpu_lib, w, Xr, w.X, 8)[0], Br, Mr, f"plan gap={gap} feat={feat}")
+
+
+def matrix_with_long_rows(n_rows, n_long, n_cols, seed, feat):
+    rng = np.random.default_rng(seed)
+    deg = rng.integers(0, 12, n_rows)
+    at = rng.choice(n_rows, n_long, replace=False)
+    deg[at] = rng.integers(n_cols // 2, n_cols, n_long)
+    deg[at[:3]] = n_cols - 1, n_cols, n_cols // 8
+    return workloads.random_csr(n_rows, n_cols, deg, seed, feat)
+
+
+@pytest.mark.parametrize("hint,feat", [(36, 36), (41, 41), (64, 64), (96, 96), (97, 97), (128, 128), (131, 131), (160, 160), (192, 192),
+                                       (224, 224), (250, 250), (255, 255), (256, 256),
+                                       (128, 3), (128, 20), (128, 64), (128, 132), (128, 300)])
+def test_sddmm_plan_takes_long_rows_in_column_slices(gpu_lib, hint, feat):
+    """Rows with entries in every slice of columns, next to short and empty ones; pieces of full segments, of every
+    remainder, and none; the last slice narrower; also calls with fewer and more features than the slices were made for."""
+    say(f"[sddmm slices] hint={hint} feat={feat}")
+    want_nnz = (1 << 29 if hint <= 64 or hint % 4 else 1 << 27) // hint     # (as many entries as the rule asks for)
+    n_cols = 12001 if want_nnz > 2_000_000 else 3001
+    n_long = want_nnz * 4 // (3 * n_cols) * 11 // 10 + 20
+    w = matrix_with_long_rows(n_long + 300, n_long, n_cols, hint, feat)
+    Xr = left_operand(w, feat, feat)
+    want = run_sddmm(gpu_lib, w, Xr, w.X)
+    got, info = run_sddmm_plan(gpu_lib, w, Xr, w.X, 8, feat_hint=hint)
+    assert info["n_runs"] < 64, "the long rows are in the runs"
+    assert np.array_equal(got, want)
+    Br, Mr = oracle.sddmm_csr(w.n_rows, w.indptr, w.indices, w.values, Xr, w.X)
+    assert_b_close(got, Br, Mr, f"hint={hint} feat={feat}")
+    one_part, _ = run_sddmm_plan(gpu_lib, w, Xr, w.X, 1, feat_hint=hint, in_place=True)
+    assert np.array_equal(one_part, want)
+
+
+def test_sddmm_plan_slices_keep_non_finite_rows_apart(gpu_lib):
+    """A row of X or Yt that is not finite reaches its own entries and no others, also past the end of a row that
+    fills its lanes only in part."""
+    n_long = 1100
+    deg = np.random.default_rng(3).integers(11000, 13000, n_long)
+    w = workloads.random_csr(n_long, 13500, deg, 3, 41)
+    Xr = left_operand(w, 41, 1)
+    Yt = w.X.copy()
+    Xr[17, 40] = np.inf; Xr[18, 3] = np.nan; Yt[1999, 40] = np.nan; Yt[13499, 0] = -np.inf
+    got, info = run_sddmm_plan(gpu_lib, w, Xr, Yt, 8, feat_hint=41)
+    assert info["n_runs"] == 0
+    rows = np.repeat(np.arange(n_long), deg)
+    with np.errstate(invalid="ignore"):
+        want = w.values * np.einsum("ij,ij->i", Xr[rows], Yt[w.indices])
+    assert np.array_equal(np.isfinite(got), np.isfinite(want))
