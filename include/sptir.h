@@ -104,7 +104,9 @@ typedef enum {
   SPTIR_PLAN_ROW_SLOT_PTR = 104,      /* int32 [n_rows + 1] */
   SPTIR_PLAN_ROW_SLOTS = 105,         /* int32: the partial-sum rows that are added to row r of Y */
   SPTIR_PLAN_HEAVY_ROWS = 106,        /* int32: the rows with heavy pieces, ascending */
-  SPTIR_PLAN_ROW_VAL = 107            /* float [n_rows], only with values_per_row */
+  SPTIR_PLAN_ROW_VAL = 107,           /* float [n_rows], only with values_per_row */
+  SPTIR_PLAN_LONG_ROWS = 108          /* int32: the rows in column slices, longest first: none of their entries is in
+                                       * the stream */
 } sptir_hyb_array_id;
 
 typedef struct {
@@ -126,9 +128,10 @@ typedef struct {
   int32_t rounds;           /* 1: every chunk list sweeps all column partitions and the lists run in rounds of as many
                                row blocks as the GPU holds at once (Y is written once); 0: one launch per group of
                                partitions, each adding to the Y of the one before */
-  int64_t n_heavy_pieces;   /* row pieces with more than heavy_len real entries: summed by a launch of their own */
-  int64_t n_heavy_items;    /* their 64-slot chunks */
-  int64_t n_heavy_nnz;      /* their real entries */
+  int64_t n_heavy_pieces;   /* row pieces with more than heavy_len real entries, summed by a launch of their own, and
+                               whole rows summed from column slices (SPTIR_PLAN_LONG_ROWS) */
+  int64_t n_heavy_items;    /* 64-slot chunks of those pieces */
+  int64_t n_heavy_nnz;      /* real entries of those pieces and rows */
   int32_t heavy_len;
   int32_t n_heavy_lists;    /* wavefronts of that launch per feature tile */
   int32_t values_per_row;   /* 1: every row of A has one value for all its entries and the SpMM stream holds none */
@@ -208,6 +211,8 @@ typedef struct {
                                  are 16-byte aligned and the row block has at most 64 rows, instead of one 128-byte line per entry and feature tile with
                                  the tiles bound to XCDs; 2: never.  Never chosen: it measured slower on every
                                  workload tried (the option stays so that the comparison can be repeated) */
+  int32_t column_slices;      /* rows with entries in every slice of columns whose rows of X (a tile of 16 features) fit a
+                                 workgroup's LDS, summed from there: 0: chosen; 1: all that are long enough; 2: none */
 } sptir_build_options_t;
 
 sptir_status_t sptir_hyb_build_ex(const sptir_csr_t* csr, int32_t n_col_parts, int32_t max_bucket_log2,

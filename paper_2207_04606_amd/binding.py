@@ -20,13 +20,14 @@ SPTIR_OK = 0
 ARRAY_IDS = {"bucket_row_ptr": 0, "bucket_slot_ptr": 1, "ell_row": 2, "ell_col": 3, "ell_val": 4,
              "rem_part_ptr": 5, "rem_row": 6, "rem_ptr": 7, "rem_col": 8, "rem_val": 9,
              "plan_stream": 100, "plan_rb_chunk_ptr": 101, "plan_rb_order": 102, "plan_hlist_first_slot": 103,
-             "plan_row_slot_ptr": 104, "plan_row_slots": 105, "plan_heavy_rows": 106, "plan_row_val": 107}
+             "plan_row_slot_ptr": 104, "plan_row_slots": 105, "plan_heavy_rows": 106, "plan_row_val": 107,
+             "plan_long_rows": 108}
 ARRAY_DTYPES = {"bucket_row_ptr": np.int64, "bucket_slot_ptr": np.int64, "ell_row": np.int32,
                 "ell_col": np.int32, "ell_val": np.float32, "rem_part_ptr": np.int32,
                 "rem_row": np.int32, "rem_ptr": np.int64, "rem_col": np.int32, "rem_val": np.float32,
                 "plan_stream": np.int32, "plan_rb_chunk_ptr": np.int64, "plan_rb_order": np.int32,
                 "plan_hlist_first_slot": np.int32, "plan_row_slot_ptr": np.int32, "plan_row_slots": np.int32,
-                "plan_heavy_rows": np.int32, "plan_row_val": np.float32}
+                "plan_heavy_rows": np.int32, "plan_row_val": np.float32, "plan_long_rows": np.int32}
 
 
 class SptirError(RuntimeError):
@@ -63,7 +64,7 @@ class _BuildOptions(ctypes.Structure):
                 ("parts_per_launch", ctypes.c_int32), ("rounds", ctypes.c_int32), ("wide_stream", ctypes.c_int32),
                 ("heavy_len", ctypes.c_int32), ("sweep_kb", ctypes.c_int32), ("release_canonical", ctypes.c_int32),
                 ("no_spmm_plan", ctypes.c_int32), ("keep_values", ctypes.c_int32), ("light_piece_len", ctypes.c_int32),
-                ("full_rows", ctypes.c_int32)]
+                ("full_rows", ctypes.c_int32), ("column_slices", ctypes.c_int32)]
 
 
 def _options(options):

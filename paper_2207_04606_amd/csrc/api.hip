@@ -219,7 +219,7 @@ sptir_status_t sptir_set_allocator(sptir_alloc_fn alloc, sptir_free_fn free_, vo
 
 sptir_status_t sptir_hyb_destroy(sptir_hyb_t* h) {
   if (!h) return SPTIR_OK;
-  sptir::handle_free(h->blobs, 3, h->free_, h->alloc_ctx);
+  sptir::handle_free(h->blobs, 4, h->free_, h->alloc_ctx);
   delete h;
   return SPTIR_OK;
 }
@@ -238,7 +238,8 @@ sptir_status_t sptir_hyb_info(const sptir_hyb_t* h, sptir_hyb_info_t* out) {
   o.n_work_items = h->n_chunks; o.item_slots = sptir::kChunkSlots; o.row_block = 1 << h->log2_row_block;
   o.n_phases = h->n_phases;
   o.rounds = h->rounds;
-  o.n_heavy_pieces = h->n_heavy; o.n_heavy_items = h->n_heavy_chunks; o.n_heavy_nnz = h->n_heavy_nnz;
+  o.n_heavy_pieces = h->n_heavy + h->slices.n_long; o.n_heavy_items = h->n_heavy_chunks;
+  o.n_heavy_nnz = h->n_heavy_nnz + h->slices.nnz;
   o.heavy_len = h->heavy_len; o.n_heavy_lists = h->n_heavy_lists;
   o.values_per_row = h->row_val ? 1 : 0;
   o.compact_stream = h->compact_stream; o.n_row_blocks = h->n_row_blocks; o.parts_per_launch = h->parts_per_phase;
@@ -274,6 +275,7 @@ sptir_status_t sptir_hyb_array(const sptir_hyb_t* h, int32_t which, const void**
     case SPTIR_PLAN_ROW_SLOT_PTR: p = h->row_slot_ptr; n = h->n_heavy > 0 ? (int64_t)h->n_rows + 1 : 0; break;
     case SPTIR_PLAN_ROW_SLOTS: p = h->row_slots; n = h->n_heavy > 0 ? h->n_row_slots : 0; break;
     case SPTIR_PLAN_HEAVY_ROWS: p = h->heavy_rows; n = h->n_heavy > 0 ? h->n_heavy_rows : 0; break;
+    case SPTIR_PLAN_LONG_ROWS: p = h->slices.rows; n = h->slices.n_long; break;
     case SPTIR_PLAN_ROW_VAL: p = h->row_val; n = h->row_val ? h->n_rows : 0; break;
     default: return SPTIR_ERR_INVALID_ARG;
   }

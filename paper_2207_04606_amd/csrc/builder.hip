@@ -86,6 +86,7 @@ __device__ __forceinline__ int bin_of_length(int l, int k) {
 // Columns ascend strictly inside every row iff flags[2] == flags[3].
 // flags[4]: number of positions q >= 1 whose value differs (as a bit pattern) from the one stored before it
 // flags[6]: entries of the longest row
+// flags[7]: rows of min_deg entries and more (bits 32 ..), and their entries
 // flags[5]: number of non-empty rows whose first value differs from the value stored just before it
 // Every row has one value for all of its entries iff flags[4] == flags[5] (only counted when `values` is given).
 // The counters exist kFlagSlots times, 64 bytes apart, and a wavefront adds to the copy its workgroup id picks:
@@ -98,8 +99,9 @@ __device__ __forceinline__ unsigned long long* flag_slot(unsigned long long* fla
 __device__ __forceinline__ void validate_rows(int n_wg, int wg, int32_t n_rows, int64_t nnz,
                                               const int32_t* __restrict__ indptr,
                                               const int32_t* __restrict__ indices,
-                                              const int32_t* __restrict__ values, unsigned long long* flags) {
+                                              const int32_t* __restrict__ values, int32_t min_deg, unsigned long long* flags) {
   const int64_t stride = (int64_t)n_wg * blockDim.x;
+  unsigned long long of_long = 0;
   unsigned int legal_descents = 0, legal_changes = 0, longest = 0;
   bool bad = false;
   for (int64_t r = (int64_t)wg * blockDim.x + threadIdx.x; r < n_rows; r += stride) {
@@ -107,6 +109,7 @@ __device__ __forceinline__ void validate_rows(int n_wg, int wg, int32_t n_rows, 
     const bool bad_here = (a < 0) || (b > nnz) || (a > b) || (r == 0 && a != 0) || (r == n_rows - 1 && b != nnz);
     bad |= bad_here;
     if (!bad_here) longest = max(longest, (unsigned int)(b - a));
+    if (!bad_here && b - a >= min_deg) of_long += (1ull << 32) + (unsigned long long)(b - a);
     legal_descents += !bad_here && a < b && a > 0 && indices[a] <= indices[a - 1];
     if (values) legal_changes += !bad_here && a < b && a > 0 && values[a] != values[a - 1];
   }
@@ -115,6 +118,7 @@ __device__ __forceinline__ void validate_rows(int n_wg, int wg, int32_t n_rows, 
     legal_descents += __shfl_down(legal_descents, d, 64);
     legal_changes += __shfl_down(legal_changes, d, 64);
     longest = max(longest, (unsigned int)__shfl_down((int)longest, d, 64));
+    of_long += __shfl_down(of_long, d, 64);
   }
   const unsigned long long any_bad = __ballot(bad);
   flags = flag_slot(flags);
@@ -123,6 +127,7 @@ __device__ __forceinline__ void validate_rows(int n_wg, int wg, int32_t n_rows, 
     if (legal_descents) atomicAdd(&flags[3], (unsigned long long)legal_descents);
     if (any_bad) flags[0] = 1;
     if (longest) atomicMax(&flags[6], (unsigned long long)longest);
+    if (of_long) atomicAdd(&flags[7], of_long);
   }
 }
 
@@ -194,9 +199,10 @@ __device__ __forceinline__ void validate_elems(int n_wg, int wg, int64_t nnz, in
 __global__ __launch_bounds__(256) void k_validate(int row_wgs, int32_t n_rows, int64_t nnz, int32_t n_cols, int vec,
                                                   const int32_t* __restrict__ indptr,
                                                   const int32_t* __restrict__ indices,
-                                                  const int32_t* __restrict__ values, unsigned long long* flags) {
+                                                  const int32_t* __restrict__ values, int32_t min_deg,
+                                                  unsigned long long* flags) {
   const int wg = (int)blockIdx.x;
-  if (wg < row_wgs) validate_rows(row_wgs, wg, n_rows, nnz, indptr, indices, values, flags);
+  if (wg < row_wgs) validate_rows(row_wgs, wg, n_rows, nnz, indptr, indices, values, min_deg, flags);
   else validate_elems((int)gridDim.x - row_wgs, wg - row_wgs, nnz, n_cols, vec, indices, values, flags);
 }
 
@@ -273,6 +279,7 @@ struct PlaceArgs {
   int32_t* row_len;  // [R+M] real (unpadded) length of every ELL row and remainder piece
   int32_t* piece_of; // [c][n_rows] position in row_ids of the piece of (row, partition), -1 where the piece is empty
   int64_t R, M, T;
+  int32_t min_deg;   // rows of so many entries are long: their pieces are in no list (negative row_len)
 };
 
 // Every piece finds its position in row_ids; the entries follow in k_copy, once the lists of the SpMM are known.
@@ -324,7 +331,7 @@ __global__ __launch_bounds__(kBuildBlock) void k_place(BuildShape s, PlaceArgs a
       a.rem_ptr[m] = a.rem_nnz_base[p] + a.rem_nnz[(int64_t)p * s.NB + rb] + nnz_before;
     }
     a.row_ids[where] = r;
-    a.row_len[where] = l;
+    a.row_len[where] = a.indptr[r + 1] - a.indptr[r] >= a.min_deg ? -l : l;
   }
   a.piece_of[(int64_t)p * s.n_rows + r] = where;
 }
@@ -469,7 +476,7 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
   };
   unsigned to_deal = 0;  // entries not dealt yet (fewer than 2^31)
   for (int i = l; i < n; i += 8) {
-    const int q = piece(i), len = row_len[q];
+    const int q = piece(i), len = max(row_len[q], 0);  // (of a long row: nothing to deal)
     len_of[i] = len;
     piece_at[i] = q;
     if (len <= cs.long_len) to_deal += (unsigned)len;
@@ -621,19 +628,33 @@ __device__ __forceinline__ int heavy_footprint(int len, int heavy_len) {
 constexpr int kHeavyPerThread = 4, kHeavySpan = kBuildBlock * kHeavyPerThread;
 struct HeavySums {  // one of each per kHeavySpan pieces
   long long *units, *slots, *entries;
+  unsigned long long* not_taken;  // [2], or NULL: pieces and slots that would be heavy if their rows were not long
 };
 
 __global__ __launch_bounds__(kBuildBlock) void k_heavy_sums(int64_t n_pieces, const int32_t* __restrict__ row_len,
                                                             int32_t heavy_len, HeavySums sums) {
   __shared__ long long wave_sums[kWaves];
-  long long units = 0, slots = 0, entries = 0;
+  long long units = 0, slots = 0, entries = 0, long_units = 0, long_slots = 0;
 #pragma unroll
   for (int i = 0; i < kHeavyPerThread; ++i) {
     const int64_t q = (int64_t)blockIdx.x * kHeavySpan + i * kBuildBlock + threadIdx.x;
     const int len = q < n_pieces ? row_len[q] : 0;
     if (len > heavy_len) { ++units; slots += heavy_footprint(len, heavy_len); entries += len; }
+    if (-len > heavy_len) { ++long_units; long_slots += heavy_footprint(-len, heavy_len); }
   }
   long long tot[3];
+  if (sums.not_taken) {
+    long long t;
+    block_exclusive_scan(long_units, wave_sums, &t);
+    if (t > 0) {  // (the same in all threads)
+      long long t_slots;
+      block_exclusive_scan(long_slots, wave_sums, &t_slots);
+      if (threadIdx.x == 0) {
+        atomicAdd(&sums.not_taken[0], (unsigned long long)t);
+        atomicAdd(&sums.not_taken[1], (unsigned long long)t_slots);
+      }
+    }
+  }
   block_exclusive_scan(units, wave_sums, &tot[0]);
   block_exclusive_scan(slots, wave_sums, &tot[1]);
   block_exclusive_scan(entries, wave_sums, &tot[2]);
@@ -676,8 +697,8 @@ __device__ __forceinline__ void scan_by_one_block(long long* data, int64_t n, lo
 
 // The last step of the scans over groups and over heavy pieces (a workgroup per array), and what the host needs to know
 // before it can size the stream, written to its memory: report[0] = chunks of all lists, [1] = chunks of the longest
-// list, [2] = heavy pieces, [3] = slots of the heavy sequence, [4] = entries of heavy pieces.
-constexpr int kReport2 = 5;
+// list, [2] = heavy pieces, [3] = slots of the heavy sequence, [4] = entries of heavy pieces, [5] and [6] = what not_taken holds.
+constexpr int kReport2 = 7;
 __global__ __launch_bounds__(kOneBlock) void k_totals(int64_t n_groups, long long* group_chunks, int64_t n_spans,
                                                       HeavySums sums, long long* report) {
   const int which = blockIdx.x;
@@ -685,7 +706,13 @@ __global__ __launch_bounds__(kOneBlock) void k_totals(int64_t n_groups, long lon
   long long total, most;
   scan_by_one_block(data, which == 0 ? n_groups : n_spans, &total, &most);
   if (threadIdx.x != 0) return;
-  if (which == 0) { report[0] = total; report[1] = most; } else report[which + 1] = total;
+  if (which == 0) {
+    report[0] = total; report[1] = most;
+    report[5] = sums.not_taken ? (long long)sums.not_taken[0] : 0;
+    report[6] = sums.not_taken ? (long long)sums.not_taken[1] : 0;
+  } else {
+    report[which + 1] = total;
+  }
 }
 
 // Heavy list w covers the chunks [w*L, (w+1)*L) of the heavy sequence.  A wavefront writes a partial-sum row at
@@ -809,6 +836,7 @@ struct CopyArgs {
   const unsigned long long* unit;
   const long long *cell_first_chunk, *group_first_chunk;
   int64_t heavy_chunk0, heavy_slots, n_heavy_chunks;
+  int32_t min_deg;  // rows of so many entries are not in the stream
 };
 constexpr int kCopyPieces = 1024;  // most pieces a workgroup holds at a time
 constexpr int kCopyWords = 6;      // LDS words per piece
@@ -920,7 +948,9 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
         piece_dst[i] = bin <= s.k ? (uint32_t)(a.bucket_slot_ptr[b] + ((q - a.bucket_row_ptr[b]) << bin))
                                   : (uint32_t)(a.S + a.rem_ptr[q - a.R]);
         if (!with_stream) continue;
-        if (len > cs.long_len) {
+        if (row_lo[rl + 1] - row_lo[rl] >= a.min_deg) {
+          piece_chunk[i] = -1;
+        } else if (len > cs.long_len) {
           piece_word[i] = 0;
           piece_chunk[i] = (int)(uint32_t)a.unit[q];
         } else {
@@ -965,7 +995,7 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
             a.cols[dst + (uint32_t)len] = piece_last[i];
             a.vals[dst + (uint32_t)len] = 0.f;
           }
-          if (!with_stream) continue;
+          if (!with_stream || piece_chunk[i] < 0) continue;
           put(i, p, rl, j, col[u], val[u], true);
           // In the stream the last chunk of a piece cut wide, and of a heavy piece that no other follows in its chunk, is
           // filled with marked slots that repeat the last column too; the last heavy piece also fills its quad.
@@ -1067,14 +1097,15 @@ size_t scan_room(int64_t n) { return (size_t)((n + kScanSeq - 1) / kScanSeq) * k
 PinnedBuf pinned_acquire(size_t bytes) { return pinned_pool().acquire(bytes); }
 void pinned_release(PinnedBuf b) { pinned_pool().release(b); }
 
-void launch_validation(const sptir_csr_t* csr, bool with_values, unsigned long long* flags, hipStream_t stream) {
+void launch_validation(const sptir_csr_t* csr, bool with_values, unsigned long long* flags, hipStream_t stream,
+                       int32_t min_deg) {
   const int32_t* value_bits = with_values ? (const int32_t*)csr->values : nullptr;
   const int row_wgs = (int)std::min<int64_t>(((int64_t)csr->n_rows + 255) / 256, 4096);
   const int elem_wgs = (int)std::min<int64_t>((csr->nnz + 2047) / 2048, 8192);
   if (row_wgs + elem_wgs > 0)
     hipLaunchKernelGGL(k_validate, dim3((unsigned)(row_wgs + elem_wgs)), dim3(256), 0, stream, row_wgs, csr->n_rows,
                        csr->nnz, csr->n_cols, (int)((((uintptr_t)csr->indices | (uintptr_t)csr->values) & 15) == 0),
-                       csr->indptr, csr->indices, value_bits, flags);
+                       csr->indptr, csr->indices, value_bits, min_deg, flags);
 }
 
 sptir_status_t validation_verdict(const unsigned long long* flag_slots, bool* one_value_per_row) {
@@ -1165,6 +1196,17 @@ int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int
   return kChunkSlots;
 }
 
+// Do the long rows leave lists and heavy pieces for column slices (spmm_slices.hip)?  Only where pieces leave the lists at all
+// and the longest row has one that does, so that no handle without heavy pieces comes to own partial sums; and from so many
+// entries on that a product wins what the build loses (some ten launches, 60 us; below 4 M entries products were 0.6 to 1.2 times as
+// fast, above 0.94 to 1.8 with 1.25 in the mean, a build and one product together 0.81 to 1.18).
+constexpr int64_t kMinSliceNnz = (int64_t)1 << 22;
+bool use_slices(const sptir_build_options_t& opt, int32_t heavy_len, int32_t c, int64_t longest_row, int64_t long_nnz) {
+  if (opt.no_spmm_plan || opt.column_slices == 2 || opt.full_rows == 1 || long_nnz == 0) return false;
+  if (opt.column_slices == 1) return true;
+  return opt.heavy_len < 1 && heavy_len < kHeavyLenMax && longest_row > (int64_t)heavy_len * c && long_nnz >= kMinSliceNnz;
+}
+
 }  // namespace
 
 sptir_build_options_t complete_options(const sptir_build_options_t* given) {
@@ -1224,7 +1266,7 @@ extern "C" sptir_status_t sptir_hyb_build_ex(const sptir_csr_t* csr, int32_t n_c
   if (opt.row_block != 0 && (opt.row_block < 8 || opt.row_block > 256 || (opt.row_block & (opt.row_block - 1))))
     return SPTIR_ERR_INVALID_ARG;
   if (opt.parts_per_launch < 0 || opt.rounds < 0 || opt.rounds > 2 || opt.heavy_len < 0 || opt.sweep_kb < 0 ||
-      opt.feat_hint < 0 || opt.full_rows < 0 || opt.full_rows > 2)
+      opt.feat_hint < 0 || opt.full_rows < 0 || opt.full_rows > 2 || opt.column_slices < 0 || opt.column_slices > 2)
     return SPTIR_ERR_INVALID_ARG;
   return sptir::hyb_build_impl(csr, n_col_parts, max_bucket_log2, opt, stream_, out);
 }
@@ -1257,7 +1299,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
   // for everything that crosses to or from the host (pageable memory would make every small copy a blocking one)
   const size_t nbk = (size_t)(s.NB ? s.NB : 1);
   Blob tmp;
-  const size_t o_flags = tmp.reserve(kValidationWords * sizeof(unsigned long long));
+  const size_t o_flags = tmp.reserve((kValidationWords + 2) * sizeof(unsigned long long));  // (the last two: HeavySums::not_taken)
   const size_t o_counts = tmp.reserve(sizeof(int32_t) * (size_t)s.c * s.nb * nbk);
   const size_t o_rnnz = tmp.reserve(sizeof(int64_t) * (size_t)s.c * nbk);
   const size_t o_bound = tmp.reserve(sizeof(int32_t) * (size_t)(s.c - 1) * (size_t)(s.n_rows ? s.n_rows : 1) + 16);
@@ -1286,10 +1328,11 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
   if (!tmp.base) { pinned_pool().release(pinned); return SPTIR_ERR_ALLOC; }
   Blob tmp2;
   void* tmp_order = nullptr;
+  SpmmSliceBuild slice_build;
+  int32_t min_deg = INT32_MAX;
 
   sptir_hyb* h = new (std::nothrow) sptir_hyb();
   if (!h) { scratch_free(tmp.base, free_, actx); pinned_pool().release(pinned); return SPTIR_ERR_ALLOC; }
-  memset(h, 0, sizeof(*h));
   h->alloc = alloc; h->free_ = free_; h->alloc_ctx = actx;
   h->n_rows = s.n_rows; h->n_cols = s.n_cols; h->c = s.c; h->k = s.k; h->w = s.w;
   h->nnz = csr->nnz; h->B = B;
@@ -1317,8 +1360,10 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     const int32_t* tot_bins = report1.bins;
     // (values are only looked at when a value-less stream is an option)
     const int32_t* value_bits = (with_spmm_plan && !opt.keep_values) ? (const int32_t*)csr->values : nullptr;
-    BUILD_HIP(hipMemsetAsync(d_flags, 0, kValidationWords * sizeof(unsigned long long), stream));
-    launch_validation(csr, value_bits != nullptr, d_flags, stream);
+    BUILD_HIP(hipMemsetAsync(d_flags, 0, (kValidationWords + 2) * sizeof(unsigned long long), stream));
+    const bool want_slices = with_spmm_plan && opt.column_slices != 2 && opt.full_rows != 1;
+    if (want_slices) min_deg = (int32_t)std::min<int64_t>(INT32_MAX, slice_min_degree(s.n_cols));
+    launch_validation(csr, value_bits != nullptr, d_flags, stream, min_deg);
     if (s.NB > 0) {
       if (n_bound_blocks > 0)
         hipLaunchKernelGGL(k_piece_bounds, dim3((unsigned)n_bound_blocks), dim3(256), 0, stream, s, (int32_t)csr->nnz,
@@ -1408,6 +1453,12 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       h->lowered_heavy_len = 1;
     }
     h->heavy_len = cs.long_len;
+    int64_t n_long = 0, long_nnz = 0;
+    for (int slot = 0; slot < kFlagSlots; ++slot) {
+      n_long += (int64_t)(report1.flags[slot * kFlagStride + 7] >> 32);
+      long_nnz += (int64_t)(uint32_t)report1.flags[slot * kFlagStride + 7];
+    }
+    if (!use_slices(opt, cs.long_len, s.c, longest_row, long_nnz)) { min_deg = INT32_MAX; n_long = 0; }
     if (!with_spmm_plan) cs.n_rb = 0;  // no row blocks, no cells, no chunks: only the canonical arrays are built
     h->spmm_plan = with_spmm_plan ? 1 : 0;
     h->log2_row_block = cs.log2_rb; h->n_row_blocks = cs.n_rb;
@@ -1440,6 +1491,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     uint32_t* d_dealt = (uint32_t*)(tmp2.base + o_dealt);
     unsigned long long* d_unit = (unsigned long long*)(tmp2.base + o_unit);
     HeavySums sums;
+    sums.not_taken = n_long > 0 ? d_flags + kValidationWords : nullptr;
     sums.units = (long long*)(tmp2.base + o_spans); sums.slots = sums.units + n_spans; sums.entries = sums.slots + n_spans;
 
     // ---- the handle's device arrays whose sizes are known now: two allocations (cols and vals can be released
@@ -1484,7 +1536,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       a.bucket_row_ptr = h->bucket_row_ptr; a.rem_part_ptr = h->rem_part_ptr;
       a.rem_nnz_base = (const int64_t*)((char*)h->blobs[0] + a_rnnz_base);
       a.row_ids = h->row_ids; a.rem_ptr = h->rem_ptr; a.row_len = h->row_len; a.piece_of = d_piece_of;
-      a.R = h->R; a.M = M; a.T = T;
+      a.R = h->R; a.M = M; a.T = T; a.min_deg = min_deg;
       hipLaunchKernelGGL(k_place, dim3((unsigned)n_pair_blocks), dim3(kBuildBlock), 0, stream, s, a);
     } else {
       int64_t* zero = (int64_t*)(host.base + h_misc + 8);
@@ -1509,6 +1561,10 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       hipLaunchKernelGGL(k_group_scan, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, stream, cs, n_groups,
                          d_cell_chunks, d_group_tot);
     }
+    if (n_long > 0) {
+      st = spmm_slices_count(&slice_build, csr, min_deg, (int32_t)n_long, longest_row, alloc, actx, stream);
+      if (st != SPTIR_OK) goto fail;
+    }
     hipLaunchKernelGGL(k_totals, dim3(4), dim3(kOneBlock), 0, stream, n_cells > 0 ? n_groups : 0, d_group_tot, n_spans,
                        sums, (long long*)(host.base + h_report2));
     BUILD_HIP(hipGetLastError());
@@ -1531,6 +1587,19 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     h->heavy_list_chunks = list_chunks;
     h->n_heavy_lists = (int32_t)((n_heavy_chunks + list_chunks - 1) / list_chunks);
     h->n_partial_rows = h->n_heavy + h->n_heavy_lists;
+    {
+      const int64_t chunks = (chunks_of_slots(report2[3] + report2[6]) + kChunksPerQuad - 1) / kChunksPerQuad * kChunksPerQuad;
+      int32_t per_list = kHeavyListChunks;
+      while (per_list > kChunksPerQuad && chunks / per_list < 4096) per_list /= 2;
+      h->whole_partial_rows = h->n_heavy + report2[5] + (chunks + per_list - 1) / per_list;
+    }
+    if (n_long > 0) {
+      st = spmm_slices_fill(&slice_build, csr, opt.feat_hint, !one_value_per_row, &h->slices, alloc, actx, stream);
+      h->blobs[3] = h->slices.blob;
+      h->device_bytes += h->slices.device_bytes;
+      h->slices.nnz = long_nnz;
+      if (st != SPTIR_OK) goto fail;
+    }
     h->partial_feat = h->n_partial_rows <= kWidePartialRows ? kWidePartialFeat : kPartialFeat;
     if (h->n_heavy == 0) h->row_slot_ptr = nullptr;  // (its room in the first allocation stays unused)
     const int64_t all_chunks = n_chunks + n_heavy_chunks;
@@ -1586,6 +1655,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       a.cols = h->cols; a.vals = h->vals; a.R = h->R; a.S = h->S; a.T = T;
       a.inv_w = 1.0 / (double)(s.w > 0 ? s.w : 1);
       a.dealt = d_dealt; a.unit = d_unit; a.cell_first_chunk = d_cell_chunks; a.group_first_chunk = d_group_tot;
+      a.min_deg = min_deg;
       a.heavy_chunk0 = n_chunks; a.heavy_slots = report2[3]; a.n_heavy_chunks = n_heavy_chunks;
       // Entries per workgroup: 512 give a medium graph's grid eight workgroups per CU; large inputs take up to 4096, which
       // share the search and the pieces' data among more entries.  Rows per block: about what those entries belong to.
@@ -1632,6 +1702,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
   scratch_free(tmp.base, free_, actx);
   scratch_free(tmp2.base, free_, actx);
   scratch_free(tmp_order, free_, actx);
+  spmm_slices_done(&slice_build, free_, actx);
   pinned_pool().release(pinned);
   *out = h;
   return SPTIR_OK;
@@ -1641,6 +1712,7 @@ fail:
   scratch_free(tmp.base, free_, actx);
   scratch_free(tmp2.base, free_, actx);
   scratch_free(tmp_order, free_, actx);
+  spmm_slices_done(&slice_build, free_, actx);
   pinned_pool().release(pinned);
   sptir_hyb_destroy(h);
   return st;

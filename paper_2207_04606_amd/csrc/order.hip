@@ -3,6 +3,9 @@
 // are sorted independently of each other by a stable least-significant-digit radix sort, 8 bits a pass:
 // key = 2^32 - 1 - list length, value = row block, so equal lengths stay in ascending row block order.  Only the
 // digits that can differ are sorted: the caller says how long a list can be at most.
+#include <math.h>
+
+#include <algorithm>
 #include <cstring>
 
 #include "sptir_internal.h"
@@ -19,14 +22,22 @@ constexpr int kDigits = 256;
 // before them wrote.
 struct SortInput {
   const int64_t* list_ptr;  // first pass: first chunk of every list (NULL otherwise)
+  const int32_t* row_ptr;   // or first entry of every row: those of min_len to max_len entries by class of length, the others last
+  int32_t min_len;
+  float log2_max, per_log2;
   const uint32_t* keys;
   const int32_t* vals;
   __device__ uint32_t key(int64_t at) const {
+    if (row_ptr) {
+      const int32_t len = row_ptr[at + 1] - row_ptr[at];
+      if (len < min_len) return kDigits - 1;
+      return (uint32_t)min(max((int)((log2_max - log2f((float)len)) * per_log2), 0), kDigits - 2);
+    }
     if (!list_ptr) return keys[at];
     const int64_t len = list_ptr[at + 1] - list_ptr[at];
     return 0xFFFFFFFFu - (len < 0xFFFFFFFFll ? (uint32_t)len : 0xFFFFFFFFu);
   }
-  __device__ int32_t val(int64_t at, int i) const { return list_ptr ? i : vals[at]; }
+  __device__ int32_t val(int64_t at, int i) const { return list_ptr || row_ptr ? i : vals[at]; }
 };
 
 // hist[(launch * 256 + digit) * tiles + tile] = elements of the tile with that digit; workgroup = launch * tiles + tile
@@ -127,7 +138,7 @@ sptir_status_t order_row_blocks(const int64_t* rb_chunk_ptr, int32_t n_launches,
   vals[1 - passes % 2] = other_vals;
   for (int pass = 0; pass < passes; ++pass) {
     const int from = pass % 2, to = 1 - from;
-    const SortInput in{pass == 0 ? rb_chunk_ptr : nullptr, keys[from], vals[from]};
+    const SortInput in{pass == 0 ? rb_chunk_ptr : nullptr, nullptr, 0, 0.f, 0.f, keys[from], vals[from]};
     hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)(tiles * n_launches)), dim3(256), 0, stream, in, n_rb,
                        (int)tiles, 8 * pass, hist);
     hipLaunchKernelGGL(k_scan_sequences<int32_t>, dim3((unsigned)n_launches), dim3(kBuildBlock), 0, stream, hist,
@@ -135,6 +146,31 @@ sptir_status_t order_row_blocks(const int64_t* rb_chunk_ptr, int32_t n_launches,
     hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)(tiles * n_launches)), dim3(256), 0, stream, in, n_rb, (int)tiles,
                        8 * pass, hist, pass + 1 < passes ? keys[to] : nullptr, vals[to]);
   }
+  SPTIR_HIP(hipGetLastError());
+  return SPTIR_OK;
+}
+
+size_t order_rows_scratch(int32_t n_rows) {
+  const int64_t n_hist = (int64_t)kDigits * (((int64_t)n_rows + kSortTile - 1) / kSortTile);
+  return sizeof(int32_t) * (scan_room(n_hist) + scan_room(n_hist) / kScanSeq + 1);
+}
+
+sptir_status_t order_rows_by_class(const int32_t* row_ptr, int32_t n_rows, int32_t min_len, int64_t max_len, int32_t* order,
+                                   void* scratch, hipStream_t stream) {
+  const int64_t tiles = ((int64_t)n_rows + kSortTile - 1) / kSortTile, n_hist = kDigits * tiles;
+  if (n_hist > 0x7FFFFFFF) return SPTIR_ERR_OVERFLOW;
+  int32_t *hist = (int32_t*)scratch, *seq_base = hist + scan_room(n_hist);
+  const float top = log2f((float)max_len), span = top - log2f((float)min_len);
+  const SortInput in{nullptr, row_ptr, min_len, top, (kDigits - 1) / std::max(span, 0.01f), nullptr, nullptr};
+  hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)tiles), dim3(256), 0, stream, in, n_rows, (int)tiles, 0, hist);
+  if (n_hist <= kScanOneMost) {  // (one launch instead of four)
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanThreads), 0, stream, hist, (int32_t)n_hist);
+  } else {
+    const sptir_status_t st = device_exclusive_scan(hist, n_hist, seq_base, stream);
+    if (st != SPTIR_OK) return st;
+  }
+  hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)tiles), dim3(256), 0, stream, in, n_rows, (int)tiles, 0, hist,
+                     (uint32_t*)nullptr, order);
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;
 }

@@ -1018,6 +1018,17 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
     const sptir_status_t st = heavy_sweeps(0, feat, heavy_with_lists);
     if (st != SPTIR_OK) return st;
   }
+  if (h->slices.n_long > 0) {  // (their rows of Y, which the lists have written zeros to, are overwritten)
+    for (int feat0 = 0; feat0 < feat; feat0 += kPartialFeat) {
+      const int width = feat - feat0 < kPartialFeat ? feat - feat0 : kPartialFeat;
+      sptir_status_t st = spmm_slices_gather(h->slices, h->n_cols, X, feat, feat0, width, stream);
+      if (st != SPTIR_OK) return st;
+      if (timers) timers->mark(stream, LaunchTimers::kHeavy, 1);
+      st = spmm_slices_add(h->slices, h->row_val, Y, feat, feat0, width, stream);
+      if (st != SPTIR_OK) return st;
+      if (timers) timers->mark(stream, LaunchTimers::kReduce, 1);
+    }
+  }
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;
 }
@@ -1086,10 +1097,11 @@ extern "C" sptir_status_t sptir_spmm_noalloc(const sptir_hyb_t* h, const float* 
   if (!h || feat < 1) return SPTIR_ERR_INVALID_ARG;
   float* partial = nullptr;
   int partial_feat = kPartialFeat;
-  if (h->n_heavy > 0) {
+  if (h->n_heavy + h->slices.n_long > 0) {
     // as many features at a time as fit: 512 (one sweep for most), 128, or 64 where the length from which pieces are
     // heavy was lowered to even out the lists
-    const size_t need = (size_t)h->n_partial_rows * kPartialFeat;
+    // (What does not fit is told from the whole matrix, long rows and all, whose sums have memory of the handle's.)
+    const size_t need = (size_t)h->whole_partial_rows * kPartialFeat;
     if (need * (kWidePartialFeat / kPartialFeat) <= kStaticScratchFloats) partial_feat = kWidePartialFeat;
     else if (need > kStaticScratchFloats && h->lowered_heavy_len && !h->full_rows &&
              need / (kPartialFeat / kNarrowPartialFeat) <= kStaticScratchFloats) partial_feat = kNarrowPartialFeat;
@@ -1098,7 +1110,7 @@ extern "C" sptir_status_t sptir_spmm_noalloc(const sptir_hyb_t* h, const float* 
       snprintf(msg, sizeof(msg),
                "sptir_spmm_noalloc: the partial sums of %lld heavy row pieces need %zu bytes, more than the "
                "static scratch of %zu bytes; use sptir_spmm",
-               (long long)h->n_heavy, need * sizeof(float), (size_t)SPTIR_NOALLOC_SCRATCH_BYTES);
+               (long long)(h->n_heavy + h->slices.n_long), need * sizeof(float), (size_t)SPTIR_NOALLOC_SCRATCH_BYTES);
       note_error_text(msg);
       return SPTIR_ERR_UNSUPPORTED;
     }

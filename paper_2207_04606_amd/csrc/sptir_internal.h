@@ -35,6 +35,22 @@ constexpr int64_t kWidePartialRows = 8192;  // (16 MB)
 constexpr int kCompactColBits = 20;
 constexpr int kCompactMaxLog2RowBlock = 7;
 
+// The long rows of a hyb handle (spmm_slices.hip): their entries by slices of kSliceCols columns.  n_long 0: none.
+constexpr int kSliceCols = 2496;      // of X in LDS: 64 bytes of each, next to a row of zeros
+// A row is long from so many entries per slice on.  70 power-law graphs of 1.5 M entries and more, against no slices: 6 1.066 times
+// as fast, 8 1.065, 12 1.049, 16 1.027, 24 1.007; 232,965 rows, 114.6 M entries: 6 1.82 ms, 8 1.80, 12 1.84, 16 1.88.
+constexpr int kMinSlicePiece = 8;
+struct SpmmSlices {
+  int32_t n_long = 0, n_units = 0, n_slices = 0;
+  int64_t nnz = 0;
+  void* blob = nullptr;               // one allocation that holds all of it
+  size_t device_bytes = 0;
+  const void *units = nullptr, *panels = nullptr;
+  const int32_t *panel_of = nullptr, *rows = nullptr, *step_of = nullptr;
+  const uint4* cols = nullptr;
+  const float4* vals = nullptr;
+  float* partial = nullptr;           // partial sums of kPartialFeat features
+};
 }  // namespace sptir
 
 // The handle behind sptir_hyb_t.  ELL and remainder share three device
@@ -51,7 +67,7 @@ struct sptir_hyb {
   int32_t* row_ids;          // device [R+M]
   int32_t* cols;             // device [S+T]
   float* vals;               // device [S+T]
-  int32_t* row_len;          // device [R+M], real length of every ELL row / remainder piece
+  int32_t* row_len;          // device [R+M], real length of every ELL row / remainder piece; negative: of a long row
   float* row_val;            // device [n_rows] or NULL: set when every row of A has one value for all its entries;
                              // the stream then holds no values and Y is scaled row by row at the end
   int32_t* stream;           // device [n_chunks * 128 or 192]: the chunks as fixed records, grouped by (phase, row block)
@@ -85,11 +101,13 @@ struct sptir_hyb {
   int32_t sweep_kb;          // kilobytes of Y (no rounds) or X (rounds) one sweep may touch; 0: the rules' defaults
   int32_t canonical_released;
   size_t device_bytes;
-  // The device arrays above are parts of at most kHybBlobs allocations: [0] the index arrays whose sizes the
-  // bucket totals fix, [1] cols and vals (can be released on their own), [2] the SpMM plan.
+  // The device arrays above are parts of these allocations: [0] the index arrays whose sizes the
+  // bucket totals fix, [1] cols and vals (can be released on their own), [2] the SpMM plan, [3] the long rows.
   int32_t heavy_list_chunks;  // chunks per heavy list of this handle: 4, 8, 16 or 32
   int32_t full_rows;        // sptir_spmm may use the 128-float tile (the row blocks are sized for it)
-  void* blobs[3];
+  sptir::SpmmSlices slices;   // the long rows: in no list and no heavy piece (their words in row_len are negative)
+  int64_t whole_partial_rows; // partial-sum rows the heavy pieces would need with them
+  void* blobs[4];
   size_t canonical_bytes;  // size of blobs[1]
   sptir_alloc_fn alloc;
   sptir_free_fn free_;
@@ -119,7 +137,9 @@ sptir_build_options_t complete_options(const sptir_build_options_t* given);
 // Validation of a CSR input on the GPU (builder.hip): `flags` is device memory, kValidationWords zeroed 64-bit words;
 // the verdict is read from a host copy of them.  *one_value_per_row is only meaningful if the values were looked at.
 constexpr int kValidationWords = 64 * 8;
-void launch_validation(const sptir_csr_t* csr, bool with_values, unsigned long long* flags, hipStream_t stream);
+// min_deg: rows of so many entries are counted as long
+void launch_validation(const sptir_csr_t* csr, bool with_values, unsigned long long* flags, hipStream_t stream,
+                       int32_t min_deg = INT32_MAX);
 sptir_status_t validation_verdict(const unsigned long long* flags, bool* one_value_per_row);
 
 // Exclusive scan of data[0 .. n) in place; data has room for scan_room(n) elements, seq_base for one int per
@@ -187,6 +207,28 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
 void sddmm_slices_free(SddmmSlices* s, sptir_free_fn free_, void* actx);
 sptir_status_t sddmm_slices_run(const SddmmSlices& s, int32_t n_cols, const float* values, const float* X, const float* Yt, float* B,
                                 int32_t feat, hipStream_t stream);
+
+struct SpmmSliceBuild {               // between the two halves of the build
+  int32_t n_long = 0, n_blocks = 0, n_slices = 0;
+  void* temporary = nullptr;
+  int32_t *bound = nullptr, *count = nullptr, *order = nullptr;
+  PinnedBuf host, tables;
+};
+int64_t slice_min_degree(int32_t n_cols);
+sptir_status_t spmm_slices_count(SpmmSliceBuild* b, const sptir_csr_t* csr, int32_t min_deg, int32_t n_long, int64_t longest,
+                                 sptir_alloc_fn alloc, void* actx, hipStream_t stream);
+sptir_status_t spmm_slices_fill(SpmmSliceBuild* b, const sptir_csr_t* csr, int32_t feat_hint, bool with_values, SpmmSlices* out,
+                                sptir_alloc_fn alloc, void* actx, hipStream_t stream);
+void spmm_slices_done(SpmmSliceBuild* b, sptir_free_fn free_, void* actx);
+sptir_status_t spmm_slices_gather(const SpmmSlices& s, int32_t n_cols, const float* X, int32_t feat, int32_t feat0, int32_t width,
+                                  hipStream_t stream);
+sptir_status_t spmm_slices_add(const SpmmSlices& s, const float* row_val, float* Y, int32_t feat, int32_t feat0, int32_t width,
+                               hipStream_t stream);
+// order[0 .. n_rows): the rows of at least min_len entries, longest first up to a class of length (a 255th of the logarithms
+// from min_len to max_len, the longest row) and ascending inside one, then the others (order.hip).  Only enqueues work.
+size_t order_rows_scratch(int32_t n_rows);
+sptir_status_t order_rows_by_class(const int32_t* row_ptr, int32_t n_rows, int32_t min_len, int64_t max_len, int32_t* order,
+                                   void* scratch, hipStream_t stream);
 
 // records a failed HIP call for sptir_last_hip_error(); returns SPTIR_ERR_HIP
 sptir_status_t note_hip_error(hipError_t e, const char* what);

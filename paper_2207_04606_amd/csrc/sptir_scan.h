@@ -91,6 +91,38 @@ __device__ __forceinline__ T scan_sequence(T* seq, int32_t len, T* wave_sums /* 
   return carry;
 }
 
+// data[0 .. n), n at most kScanOneMost, becomes its exclusive prefix, by one workgroup with a run of elements per thread
+constexpr int kScanThreads = 1024, kScanRun = 16, kScanOneMost = kScanThreads * kScanRun;
+__global__ __launch_bounds__(kScanThreads) void k_scan_one(int32_t* data, int32_t n) {
+  __shared__ int32_t wave_sum[kScanThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i0 = (int)threadIdx.x * kScanRun;
+  int32_t v[kScanRun], mine = 0;
+#pragma unroll
+  for (int k = 0; k < kScanRun; k += 4) {
+    int4 q = make_int4(0, 0, 0, 0);
+    if (i0 + k + 4 <= n) {
+      q = *reinterpret_cast<const int4*>(data + i0 + k);  // (allocations are aligned to 256 bytes)
+    } else {
+      if (i0 + k < n) q.x = data[i0 + k];
+      if (i0 + k + 1 < n) q.y = data[i0 + k + 1];
+      if (i0 + k + 2 < n) q.z = data[i0 + k + 2];
+    }
+    v[k] = q.x; v[k + 1] = q.y; v[k + 2] = q.z; v[k + 3] = q.w;
+  }
+#pragma unroll
+  for (int k = 0; k < kScanRun; ++k) mine += v[k];
+  const int32_t incl = wave_inclusive_scan(mine, lane);
+  if (lane == 63) wave_sum[wave] = incl;
+  __syncthreads();
+  int32_t before = incl - mine;
+  for (int w = 0; w < wave; ++w) before += wave_sum[w];
+#pragma unroll
+  for (int k = 0; k < kScanRun; ++k) {
+    if (i0 + k < n) data[i0 + k] = before;
+    before += v[k];
+  }
+}
+
 // One workgroup per sequence: data[seq*len .. +len) becomes its exclusive prefix, totals[seq] its sum.
 template <typename T>
 __global__ __launch_bounds__(kBuildBlock) void k_scan_sequences(T* data, int32_t len, T* totals) {

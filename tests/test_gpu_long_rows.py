@@ -1,0 +1,93 @@
+"""Rows of a hyb handle that are summed from column slices in LDS: which rows those are, that none of their entries is left in the
+stream, and Y against the fp64 oracle (|Y - Y_oracle| <= 1e-5 * sum_j |a_ij x_jk|, exactly 0 where that is 0)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from gpu_helpers import fetch_hyb, upload
+from hyb_checks import assert_same_hyb
+from test_gpu_parity import assert_y_close, say
+from test_gpu_stream import decode
+
+pytestmark = pytest.mark.gpu
+SLICE, PIECE, LEAST = 2496, 8, 64     # columns of a slice, entries per slice and entries from which on a row is long
+
+
+def matrix(n_rows, n_cols, n_long, feat, seed, one_value):
+    """n_long rows from the shortest long one to a full one, the others just too short, empty, or of a few entries."""
+    rng = np.random.default_rng(seed)
+    least = max(LEAST, PIECE * n_cols // SLICE)
+    deg = rng.integers(0, 9, n_rows)
+    at = rng.permutation(n_rows)
+    deg[at[:n_long]] = np.minimum(n_cols, (least * rng.uniform(1.0, 6.0, n_long)).astype(np.int64))
+    deg[at[0]], deg[at[n_long - 1]] = n_cols, min(n_cols, least)
+    deg[at[n_long:n_long + 3]] = min(n_cols, least - 1)
+    w = workloads.random_csr(n_rows, n_cols, deg, seed, feat)
+    if one_value:
+        w.values[:] = np.repeat(rng.standard_normal(n_rows).astype(np.float32), np.diff(w.indptr))
+    return w, np.flatnonzero(deg >= least)
+
+
+@pytest.mark.parametrize("n_rows,n_cols,n_long", [(40, 100, 1), (70, 2495, 16), (300, 2496, 17), (300, 2497, 33),
+                                                  (2700, 5200, 2300), (700, 30001, 260)])
+@pytest.mark.parametrize("feat", [1, 3, 4, 7, 16, 17, 41, 64, 128, 131])
+@pytest.mark.parametrize("one_value", [False, True])
+def test_long_rows(gpu_lib, n_rows, n_cols, n_long, feat, one_value):
+    sptir = gpu_lib
+    say(f"[long rows] {n_rows}x{n_cols} long={n_long} feat={feat} one_value={one_value}")
+    w, long_rows = matrix(n_rows, n_cols, n_long, feat, n_cols + feat, one_value)
+    d = upload(w)
+    Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    for c, options in ((3, {"column_slices": 1, "rounds": 1}), (2, {"column_slices": 1, "rounds": 2, "parts_per_launch": 1}),
+                       (1, {"column_slices": 1, "keep_values": 1, "feat_hint": 32})):
+        hyb = sptir.sptir_hyb_build_ex(n_rows, n_cols, d.indptr, d.indices, d.values, c, 5, options)
+        rows = sptir.sptir_hyb_array(hyb, "plan_long_rows")
+        lens = np.diff(w.indptr)[rows]
+        assert np.array_equal(np.sort(rows), long_rows)
+        assert (lens <= 1.03 * np.minimum.accumulate(lens)).all(), "longest first, up to a class of length"
+        Y = torch.full((n_rows, feat), float("nan"), device="cuda")
+        sptir.sptir_spmm(hyb, d.X, Y)
+        assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"{options}")
+        again = torch.full_like(Y, float("nan"))
+        sptir.sptir_spmm_noalloc(hyb, d.X, again)
+        assert torch.equal(Y, again)
+        hyb.destroy()
+
+
+@pytest.mark.parametrize("options", [{"rounds": 1}, {"rounds": 2, "wide_stream": 1, "heavy_len": 20}])
+def test_long_rows_leave_the_stream_and_nothing_else(gpu_lib, options):
+    sptir = gpu_lib
+    w, long_rows = matrix(400, 3000, 40, 4, 9, False)
+    d = upload(w)
+    hyb = sptir.sptir_hyb_build_ex(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, 3, 4, {**options, "column_slices": 1})
+    got, info = fetch_hyb(sptir, hyb)
+    assert_same_hyb(got, oracle.hyb_build(w.n_rows, w.n_cols, w.indptr, w.indices, w.values, 3, 4))
+    assert info["n_heavy_pieces"] >= long_rows.size
+    in_long = int(np.diff(w.indptr)[long_rows].sum())
+    assert info["n_heavy_nnz"] >= in_long
+    sequence = dict(info, n_heavy_pieces=info["n_heavy_pieces"] - long_rows.size)
+    rows, cols, vals = decode(sptir, hyb, sequence, w)
+    want_rows = np.repeat(np.arange(w.n_rows, dtype=np.int64), np.diff(w.indptr))
+    keep = ~np.isin(want_rows, long_rows)
+    o = np.argsort(rows * w.n_cols + cols, kind="stable")
+    assert np.array_equal((rows * w.n_cols + cols)[o], (want_rows * w.n_cols + w.indices)[keep])
+    assert np.array_equal(vals[o], w.values.view(np.int32).astype(np.int64)[keep])
+
+
+@pytest.mark.parametrize("one_value", [False, True])
+def test_rows_of_x_that_are_not_finite_stay_with_their_rows(gpu_lib, one_value):
+    sptir = gpu_lib
+    w, long_rows = matrix(200, 4000, 150, 20, 3, one_value)
+    w.X[17, 3] = np.inf; w.X[2495, 0] = np.nan; w.X[3999, 19] = -np.inf
+    d = upload(w)
+    hyb = sptir.sptir_hyb_build_ex(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, 1, 5, {"column_slices": 1, "rounds": 2})
+    Y = torch.empty(w.n_rows, 20, device="cuda")
+    sptir.sptir_spmm(hyb, d.X, Y)
+    got = np.isfinite(Y.cpu().numpy())
+    rows = np.repeat(np.arange(w.n_rows), np.diff(w.indptr))
+    want = np.ones((w.n_rows, 20), bool)
+    for col, f in ((17, 3), (2495, 0), (3999, 19)):
+        want[rows[w.indices == col], f] = False
+    assert np.array_equal(got[long_rows], want[long_rows])
