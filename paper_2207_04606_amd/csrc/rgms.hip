@@ -38,6 +38,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <new>
 #include <type_traits>
 #include <utility>
@@ -53,8 +54,8 @@ namespace {
 constexpr int kTileRows = 16;      // pieces per tile: the rows of one matrix-core product
 constexpr int kPieceEntries = 8;   // most entries per piece: at most two batches of 64 per tile
 constexpr int kNoRow = 0xFFFF;
-constexpr int kMinLog2Block = 5, kMaxLog2Block = 8;
-constexpr int kYTileBytes = 64 * 1024;  // LDS for the rows of Y: two workgroups per CU
+constexpr int kMinLog2Block = 5, kMaxLog2Block = 9;
+constexpr int kYTileBytes = 64 * 1024;  // LDS for the rows of Y: two workgroups per CU; blocks of 2^kMaxLog2Block rows: twice that, one
 
 struct RgmsItem {
   int32_t block;    // rows block << log2_block .. of Y
@@ -548,10 +549,25 @@ __global__ __launch_bounds__(256) void k_pair_entries(int64_t nnz, const int32_t
 // best block for each is 2.7 % faster in the mean, 20 % at most; any one size for all 16 to 34 % slower.)  Fewer,
 // larger blocks divided into items were tried and lose more in global atomics than fuller tiles gain (27,163 rows,
 // 64 x 64: 0.042 -> 0.093 ms).
-int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz) {
+// Blocks of 512 rows take the LDS of a CU and 16 wavefronts; what they win is W[r] read for half as many tiles.  They need two
+// workgroups' worth of them per CU (158,566 rows: 0.81 times as fast as with 256) and no workspace, whose tiles take turns (0.79 to
+// 1.08); then 1.0 to 1.21 times as fast as 256 (40 graphs; 1.9 M rows, 96 relations, 5.7 M entries, 32 x 32: 0.527 -> 0.458 ms).
+int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
   int s = kMinLog2Block;
-  while (s < kMaxLog2Block && ((int64_t)1 << s) * nnz < 32 * n_rows * n_rel && (n_rows >> (s + 1)) >= 160) ++s;
+  while (((int64_t)1 << s) * nnz < 32 * n_rows * n_rel && s < kMaxLog2Block - (workspace ? 1 : 0) &&
+         (n_rows >> (s + 1)) >= (s + 1 < kMaxLog2Block ? 160 : 512))
+    ++s;
   return s;
+}
+
+template <int TIN, bool ORDERED, bool WIDE_X>
+void launch_rgms(dim3 grid, dim3 block, size_t lds, hipStream_t stream, const RgmsArgs& a) {
+  auto* kernel = &k_rgms<TIN, ORDERED, WIDE_X>;
+  static std::once_flag raised;  // blocks of 512 rows need more than the default 64 KB of dynamic LDS
+  std::call_once(raised, [&] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  });
+  hipLaunchKernelGGL(kernel, grid, block, lds, stream, a);
 }
 
 }  // namespace
@@ -620,7 +636,7 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
   current_allocator(&p->alloc, &p->free_, &p->alloc_ctx);
   p->n_rel = n_relations; p->n_rows = stacked->n_rows / n_relations; p->n_cols = stacked->n_cols; p->k = k;
   p->nnz = nnz; p->workspace_d_out = workspace_d_out;
-  p->log2_block = log2_block_rows(p->n_rows, n_relations, nnz);
+  p->log2_block = log2_block_rows(p->n_rows, n_relations, nnz, workspace_d_out > 0);
   const int32_t n_blocks = (int32_t)(((int64_t)p->n_rows + (1 << p->log2_block) - 1) >> p->log2_block);
   CellArgs ca;
   ca.indptr = stacked->indptr; ca.n_cells = (int64_t)n_blocks * n_relations; ca.n_rel = n_relations;
@@ -769,7 +785,8 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   a.entries = p->entries; a.entry_piece = p->entry_piece;
   a.X = X; a.W = W; a.Y = Y; a.partial = p->partial;
   a.n_rows = p->n_rows; a.log2_block = p->log2_block; a.d_out = d_out;
-  a.width = std::min<int32_t>(d_out, (kYTileBytes / 8 >> p->log2_block) / 32 * 32);
+  const bool large_block = p->log2_block == kMaxLog2Block;
+  a.width = std::min<int32_t>(d_out, ((large_block ? 2 : 1) * kYTileBytes / 8 >> p->log2_block) / 32 * 32);
   const int64_t chunks = (d_out + a.width - 1) / a.width;
   if (chunks > 65535) return SPTIR_ERR_OVERFLOW;
   const bool ordered = d_out <= p->workspace_d_out;
@@ -789,7 +806,7 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
     a.sharers = (int32_t)std::min<int64_t>(std::max<int64_t>(2, w_each / 250000), std::min<int64_t>(8, (512 + whole - 1) / whole));
   // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs
   // and feature sizes: against 8 everywhere it is alike in the mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)
-  a.n_waves = large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;
+  a.n_waves = large_block ? 16 : large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;
   const size_t lds = sizeof(double) * ((size_t)a.width << p->log2_block) + (ordered ? sizeof(int) * (a.width / 16) : 0);
   const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);
   auto divided = [&](const float* partial) {
@@ -803,12 +820,11 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   } else if (!ordered) {
     divided(nullptr);
   }
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, stream, a); };
   auto launch_for = [&](auto ord, auto wide) {
     constexpr bool kOrdered = decltype(ord)::value, kWide = decltype(wide)::value;
-    if (d_in == 32) launch(k_rgms<1, kOrdered, kWide>);
-    else if (d_in == 64) launch(k_rgms<2, kOrdered, kWide>);
-    else launch(k_rgms<4, kOrdered, kWide>);
+    if (d_in == 32) launch_rgms<1, kOrdered, kWide>(grid, block, lds, stream, a);
+    else if (d_in == 64) launch_rgms<2, kOrdered, kWide>(grid, block, lds, stream, a);
+    else launch_rgms<4, kOrdered, kWide>(grid, block, lds, stream, a);
   };
   // (a buffer has a 32-bit size)
   const uint64_t x_bytes = (uint64_t)p->n_cols * d_in * sizeof(float);

@@ -231,3 +231,11 @@ def test_rgms_non_finite_rows_stay_with_their_rows(gpu_lib, n, n_rel, d_in, d_ou
         wrong = np.isfinite(Y) != finite
         assert not wrong.any(), f"{int(wrong.sum())} of {int(finite.sum())} elements"
         assert_y_close(np.where(finite, Y, 0), np.where(finite, Yr, 0), np.where(finite, Sr, 0), "finite rows")
+
+
+@pytest.mark.parametrize("d_in,d_out", [(32, 32), (64, 96), (128, 64)])
+def test_rgms_blocks_of_512_rows(gpu_lib, d_in, d_out):
+    """Many rows and few entries per relation: the largest row blocks, the last one with part of its rows."""
+    say(f"[rgms 512] d_in={d_in} d_out={d_out}")
+    test_rgms_tile_edges(gpu_lib, 512 * 512 + 77, 8, d_in, d_out, 0)
+    test_rgms_non_finite_rows_stay_with_their_rows(gpu_lib, 512 * 512 + 1, 8, d_in, d_out, 0)
