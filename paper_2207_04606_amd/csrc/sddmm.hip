@@ -32,7 +32,7 @@
 //
 // Measured: CSR order, 169,343 rows, 1.17 M entries: 64 features 97 -> 53 us (50 on the same operands again), 32: 91 -> 27, 128:
 // 127 -> 102 (5.8 TB/s of gathered rows, all beyond L2); 41 features, 1.5 M entries 612 -> 47 us; 2,708 rows 42 -> 7 us, most of
-// which is the call.  With a plan, 232,965 rows, 114.6 M entries, 128 features: 3.56 -> 3.46 ms; 20 M entries, 53 features
+// which is the call.  With a plan, 232,965 rows, 114.6 M entries, 128 features: 3.56 -> 3.46 -> 2.56 ms (with the slices); 20 M entries, 53 features
 // 3.20 -> 0.55 ms.
 #include <string.h>
 
@@ -94,8 +94,14 @@ __device__ __forceinline__ int count_not_above(int ascending, int v) {
 // (The second launch bound tells the register allocator how many wavefronts per SIMD to leave room for; left
 //  alone it spreads the pipeline stages over 280+ registers although 16*T + 30 are live at any time.)
 enum RowEnd { kWhole, kQuads, kTail };
-template <int T, RowEnd END, bool MANY, bool PLAN>
+// Where the entries come from: CSR order, a plan, or a plan whose lists the memory-side cache does not hold from call to call.
+// Those are read, and B is written, past the rows of Yt that L2 is to keep (45 M listed entries 2636 -> 2560 us; lists that the
+// cache does hold would come from memory every time: 7.9 M entries 70 -> 105 us).
+enum Source { kCsr, kPlan, kLargePlan };
+constexpr int64_t kLargeList = 24 << 20;  // entries: 12 bytes each, 256 MB and more
+template <int T, RowEnd END, bool MANY, Source SOURCE>
 __global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(SddmmArgs a) {
+  constexpr bool PLAN = SOURCE != kCsr;
   const int lane = threadIdx.x & 63, g = lane >> 3, fl = lane & 7;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   int64_t e_begin, e_end;
@@ -139,7 +145,13 @@ __global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(Sddm
     ChunkEntries c;
     const int64_t e = min(base + lane, e_end - 1);  // (a lane past the end repeats the last entry)
     if constexpr (PLAN) {
-      c.col = a.e_col[e]; c.row = a.e_row[e]; c.pos = a.e_pos[e];
+      if constexpr (SOURCE == kLargePlan) {
+        c.col = __builtin_nontemporal_load(a.e_col + e);
+        c.row = __builtin_nontemporal_load(a.e_row + e);
+        c.pos = __builtin_nontemporal_load(a.e_pos + e);
+      } else {
+        c.col = a.e_col[e]; c.row = a.e_row[e]; c.pos = a.e_pos[e];
+      }
       c.val = 0.f;
     } else {
       c.col = a.indices[e]; c.val = a.values[e];
@@ -265,7 +277,10 @@ __global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(Sddm
     }
     // lane (g, fl) ends with the total of p[fl], i.e. of entry base + g*8 + fl = base + lane: its own entry
     const float mine = reduce_scatter8(p, fl);
-    if (in) a.B[c.pos] = c.val * mine;
+    if (in) {
+      if constexpr (SOURCE == kLargePlan) __builtin_nontemporal_store(c.val * mine, a.B + c.pos);
+      else a.B[c.pos] = c.val * mine;
+    }
   }
 }
 
@@ -290,34 +305,34 @@ __global__ __launch_bounds__(256) void k_sddmm_narrow(SddmmArgs a) {
   if (e < a.nnz) a.B[pos] = a.values[pos] * acc;
 }
 
-template <bool PLAN, int T>
+template <Source SOURCE, int T>
 void launch_stripes(const SddmmArgs& a, dim3 grid, hipStream_t stream) {
   const dim3 block(64 * kSddmmWaves);
-  if (a.feat == 32 * T) hipLaunchKernelGGL((k_sddmm<T, kWhole, false, PLAN>), grid, block, 0, stream, a);
-  else if (a.feat % 4 == 0) hipLaunchKernelGGL((k_sddmm<T, kQuads, false, PLAN>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((k_sddmm<T, kTail, false, PLAN>), grid, block, 0, stream, a);
+  if (a.feat == 32 * T) hipLaunchKernelGGL((k_sddmm<T, kWhole, false, SOURCE>), grid, block, 0, stream, a);
+  else if (a.feat % 4 == 0) hipLaunchKernelGGL((k_sddmm<T, kQuads, false, SOURCE>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((k_sddmm<T, kTail, false, SOURCE>), grid, block, 0, stream, a);
 }
 
 // grid: the workgroups of k_sddmm
-template <bool PLAN>
+template <Source SOURCE>
 void launch_sddmm(const SddmmArgs& a, dim3 grid, hipStream_t stream) {
   const dim3 block(64 * kSddmmWaves);
   if (a.feat < 4) {
-    hipLaunchKernelGGL(k_sddmm_narrow<PLAN>, dim3((unsigned)((a.nnz + 255) / 256)), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(k_sddmm_narrow<SOURCE != kCsr>, dim3((unsigned)((a.nnz + 255) / 256)), dim3(256), 0, stream, a);
     return;
   }
   switch ((a.feat + 31) / 32) {
-    case 1: return launch_stripes<PLAN, 1>(a, grid, stream);
-    case 2: return launch_stripes<PLAN, 2>(a, grid, stream);
-    case 3: return launch_stripes<PLAN, 3>(a, grid, stream);
-    case 4: return launch_stripes<PLAN, 4>(a, grid, stream);
-    case 5: return launch_stripes<PLAN, 5>(a, grid, stream);
-    case 6: return launch_stripes<PLAN, 6>(a, grid, stream);
-    case 7: return launch_stripes<PLAN, 7>(a, grid, stream);
-    case 8: return launch_stripes<PLAN, 8>(a, grid, stream);
+    case 1: return launch_stripes<SOURCE, 1>(a, grid, stream);
+    case 2: return launch_stripes<SOURCE, 2>(a, grid, stream);
+    case 3: return launch_stripes<SOURCE, 3>(a, grid, stream);
+    case 4: return launch_stripes<SOURCE, 4>(a, grid, stream);
+    case 5: return launch_stripes<SOURCE, 5>(a, grid, stream);
+    case 6: return launch_stripes<SOURCE, 6>(a, grid, stream);
+    case 7: return launch_stripes<SOURCE, 7>(a, grid, stream);
+    case 8: return launch_stripes<SOURCE, 8>(a, grid, stream);
     default:
-      if (a.feat % 4) hipLaunchKernelGGL((k_sddmm<8, kTail, true, PLAN>), grid, block, 0, stream, a);
-      else hipLaunchKernelGGL((k_sddmm<8, kQuads, true, PLAN>), grid, block, 0, stream, a);
+      if (a.feat % 4) hipLaunchKernelGGL((k_sddmm<8, kTail, true, SOURCE>), grid, block, 0, stream, a);
+      else hipLaunchKernelGGL((k_sddmm<8, kQuads, true, SOURCE>), grid, block, 0, stream, a);
   }
 }
 
@@ -594,7 +609,7 @@ extern "C" sptir_status_t sptir_sddmm(const sptir_sddmm_plan_t* p, const float* 
   a.run = csr_run(p->nnz);
   if (p->indptr) {
     const int64_t runs = (p->nnz + a.run - 1) / a.run;
-    launch_sddmm<false>(a, dim3((unsigned)((runs + kSddmmWaves - 1) / kSddmmWaves)), stream);
+    launch_sddmm<kCsr>(a, dim3((unsigned)((runs + kSddmmWaves - 1) / kSddmmWaves)), stream);
   } else {
     if (p->slices.n_units > 0) {
       const sptir_status_t st = sddmm_slices_run(p->slices, p->n_cols, values, X, Yt, B_values, feat, stream);
@@ -602,7 +617,9 @@ extern "C" sptir_status_t sptir_sddmm(const sptir_sddmm_plan_t* p, const float* 
     }
     a.nnz = p->nnz - p->slices.nnz;
     if (a.nnz == 0) return SPTIR_OK;
-    launch_sddmm<true>(a, dim3((unsigned)(8 * ((p->max_runs_per_xcd + kSddmmWaves - 1) / kSddmmWaves))), stream);
+    const dim3 grid((unsigned)(8 * ((p->max_runs_per_xcd + kSddmmWaves - 1) / kSddmmWaves)));
+    if (a.nnz >= kLargeList) launch_sddmm<kLargePlan>(a, grid, stream);
+    else launch_sddmm<kPlan>(a, grid, stream);
   }
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;
@@ -629,7 +646,7 @@ extern "C" sptir_status_t sptir_sddmm_csr(const sptir_csr_t* csr, const float* X
   dim3 grid((unsigned)((runs + kSddmmWaves - 1) / kSddmmWaves));
   hipStream_t stream = (hipStream_t)stream_;
   a.e_row = a.e_col = a.e_pos = nullptr; a.run_first_entry = nullptr; a.run_len = nullptr; a.xcd_run_ptr = nullptr;
-  launch_sddmm<false>(a, grid, stream);
+  launch_sddmm<kCsr>(a, grid, stream);
   SPTIR_HIP(hipGetLastError());
   return SPTIR_OK;
 }
