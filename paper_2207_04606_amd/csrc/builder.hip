@@ -19,6 +19,7 @@
 
 #include "sptir_internal.h"
 #include "sptir_scan.h"
+#include "sptir_sort.h"
 
 namespace sptir {
 namespace {
@@ -37,13 +38,13 @@ struct BuildShape {
 // probes), and writes its results through an LDS tile, so that consecutive lanes write consecutive rows.
 constexpr int kBoundRows = 64, kBoundParts = 64;
 
-__global__ __launch_bounds__(256) void k_piece_bounds(BuildShape s, int32_t nnz,
-                                                      const int32_t* __restrict__ indptr,
-                                                      const int32_t* __restrict__ indices,
-                                                      int32_t* __restrict__ bound) {
+__device__ __forceinline__ void piece_bounds_workgroup(const BuildShape& s, int32_t nnz, unsigned wg,
+                                                       const int32_t* __restrict__ indptr,
+                                                       const int32_t* __restrict__ indices,
+                                                       int32_t* __restrict__ bound) {
   __shared__ int32_t tile[kBoundParts][kBoundRows + 1];
   const int n_pc = (s.c - 1 + kBoundParts - 1) / kBoundParts;
-  const int rb = blockIdx.x / n_pc, pc = blockIdx.x % n_pc;
+  const int rb = (int)wg / n_pc, pc = (int)wg % n_pc;
   const int r0 = rb * kBoundRows, p0 = 1 + pc * kBoundParts;
   const int np = s.c - p0 < kBoundParts ? s.c - p0 : kBoundParts;
   const int nr = s.n_rows - r0 < kBoundRows ? s.n_rows - r0 : kBoundRows;
@@ -206,6 +207,20 @@ __global__ __launch_bounds__(256) void k_validate(int row_wgs, int32_t n_rows, i
   else validate_elems((int)gridDim.x - row_wgs, wg - row_wgs, nnz, n_cols, vec, indices, values, flags);
 }
 
+// Both, and next to them the piece boundaries, which wait for nothing either: the first n_bound workgroups
+__global__ __launch_bounds__(256) void k_first_pass(unsigned n_bound, int row_wgs, BuildShape s, int64_t nnz, int vec,
+                                                    const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
+                                                    const int32_t* __restrict__ values, int32_t min_deg,
+                                                    unsigned long long* flags, int32_t* __restrict__ bound) {
+  if (blockIdx.x < n_bound) {
+    piece_bounds_workgroup(s, (int32_t)nnz, blockIdx.x, indptr, indices, bound);
+    return;
+  }
+  const int wg = (int)(blockIdx.x - n_bound);
+  if (wg < row_wgs) validate_rows(row_wgs, wg, s.n_rows, nnz, indptr, indices, values, min_deg, flags);
+  else validate_elems((int)(gridDim.x - n_bound) - row_wgs, wg - row_wgs, nnz, s.n_cols, vec, indices, values, flags);
+}
+
 // row_val[r] = the value of row r's first entry (0 for an empty row)
 __global__ void k_row_values(int32_t n_rows, const int32_t* __restrict__ indptr, const float* __restrict__ values,
                              float* row_val) {
@@ -357,10 +372,10 @@ struct CellShape {
 
 // bin_rb_ptr[(p*nb + bin)*(n_rb+1) + j] = first position in row_ids of bin
 // (p, bin) whose row id is >= j * row_block (absolute index into row_ids)
-__global__ void k_cell_bounds(CellShape cs, const int64_t* __restrict__ bucket_row_ptr,
-                              const int32_t* __restrict__ rem_part_ptr, const int32_t* __restrict__ row_ids,
-                              int32_t* bin_rb_ptr) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void cell_bounds_workgroup(const CellShape& cs, unsigned wg, const int64_t* __restrict__ bucket_row_ptr,
+                                                      const int32_t* __restrict__ rem_part_ptr,
+                                                      const int32_t* __restrict__ row_ids, int32_t* bin_rb_ptr) {
+  int64_t t = (int64_t)wg * blockDim.x + threadIdx.x;
   int64_t per_bin = (int64_t)cs.n_rb + 1;
   if (t >= (int64_t)cs.c * cs.nb * per_bin) return;
   int j = (int)(t % per_bin);
@@ -584,13 +599,13 @@ __device__ __forceinline__ void put_slot(const StreamShape& ss, int64_t chunk, i
 
 // One wavefront per (group, partition), a lane per slot of a chunk: the slots past the end of each queue; the first
 // partition of a group also writes the chunks that round the group up to whole quads, and rb_chunk_ptr.
-__global__ __launch_bounds__(256) void k_list_ends(CellShape cs, StreamShape ss, int64_t n_parts,
-                                                   const long long* __restrict__ cell_first_chunk,
-                                                   const long long* __restrict__ group_first_chunk,
-                                                   const int32_t* __restrict__ queue_len, int64_t* rb_chunk_ptr,
-                                                   int64_t n_chunks_total) {
+__device__ __forceinline__ void list_ends_workgroup(const CellShape& cs, const StreamShape& ss, int64_t n_parts, unsigned wg,
+                                                    const long long* __restrict__ cell_first_chunk,
+                                                    const long long* __restrict__ group_first_chunk,
+                                                    const int32_t* __restrict__ queue_len, int64_t* rb_chunk_ptr,
+                                                    int64_t n_chunks_total) {
   const int lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t t = (int64_t)wg * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (t >= n_parts) return;
   const int64_t grp = t / cs.ppg;
   const int p_local = (int)(t % cs.ppg);
@@ -631,13 +646,13 @@ struct HeavySums {  // one of each per kHeavySpan pieces
   unsigned long long* not_taken;  // [2], or NULL: pieces and slots that would be heavy if their rows were not long
 };
 
-__global__ __launch_bounds__(kBuildBlock) void k_heavy_sums(int64_t n_pieces, const int32_t* __restrict__ row_len,
-                                                            int32_t heavy_len, HeavySums sums) {
+__device__ __forceinline__ void heavy_sums_workgroup(int64_t n_pieces, unsigned wg, const int32_t* __restrict__ row_len,
+                                                     int32_t heavy_len, const HeavySums& sums) {
   __shared__ long long wave_sums[kWaves];
   long long units = 0, slots = 0, entries = 0, long_units = 0, long_slots = 0;
 #pragma unroll
   for (int i = 0; i < kHeavyPerThread; ++i) {
-    const int64_t q = (int64_t)blockIdx.x * kHeavySpan + i * kBuildBlock + threadIdx.x;
+    const int64_t q = (int64_t)wg * kHeavySpan + i * kBuildBlock + threadIdx.x;
     const int len = q < n_pieces ? row_len[q] : 0;
     if (len > heavy_len) { ++units; slots += heavy_footprint(len, heavy_len); entries += len; }
     if (-len > heavy_len) { ++long_units; long_slots += heavy_footprint(-len, heavy_len); }
@@ -659,8 +674,19 @@ __global__ __launch_bounds__(kBuildBlock) void k_heavy_sums(int64_t n_pieces, co
   block_exclusive_scan(slots, wave_sums, &tot[1]);
   block_exclusive_scan(entries, wave_sums, &tot[2]);
   if (threadIdx.x == 0) {
-    sums.units[blockIdx.x] = tot[0]; sums.slots[blockIdx.x] = tot[1]; sums.entries[blockIdx.x] = tot[2];
+    sums.units[wg] = tot[0]; sums.slots[wg] = tot[1]; sums.entries[wg] = tot[2];
   }
+}
+
+// The sums, and next to them the bounds of the cells: the first n_sums workgroups
+__global__ __launch_bounds__(kBuildBlock) void k_sums_and_cells(unsigned n_sums, int64_t n_pieces,
+                                                                const int32_t* __restrict__ row_len, int32_t heavy_len,
+                                                                HeavySums sums, CellShape cs,
+                                                                const int64_t* __restrict__ bucket_row_ptr,
+                                                                const int32_t* __restrict__ rem_part_ptr,
+                                                                const int32_t* __restrict__ row_ids, int32_t* bin_rb_ptr) {
+  if (blockIdx.x < n_sums) heavy_sums_workgroup(n_pieces, blockIdx.x, row_len, heavy_len, sums);
+  else cell_bounds_workgroup(cs, blockIdx.x - n_sums, bucket_row_ptr, rem_part_ptr, row_ids, bin_rb_ptr);
 }
 
 // Exclusive scan of data[0 .. n) in place by one workgroup of kOneBlock threads (a run of elements each); *total and
@@ -707,6 +733,7 @@ __global__ __launch_bounds__(kOneBlock) void k_totals(int64_t n_groups, long lon
   scan_by_one_block(data, which == 0 ? n_groups : n_spans, &total, &most);
   if (threadIdx.x != 0) return;
   if (which == 0) {
+    if (n_groups > 0) group_chunks[n_groups] = total;  // (the end of the last list)
     report[0] = total; report[1] = most;
     report[5] = sums.not_taken ? (long long)sums.not_taken[0] : 0;
     report[6] = sums.not_taken ? (long long)sums.not_taken[1] : 0;
@@ -720,12 +747,12 @@ __global__ __launch_bounds__(kOneBlock) void k_totals(int64_t n_groups, long lon
 // chunk w*L) + w.
 // A heavy piece q learns its number and its first slot (unit[q] = number << 32 | slot; the words of other pieces are not
 // written), and the lists that start in it (in it: their first slot is one of its own) where their first write goes.
-__global__ __launch_bounds__(kBuildBlock) void k_heavy_units(int64_t n_pieces, const int32_t* __restrict__ row_len,
-                                                             int32_t heavy_len, HeavySums sums, int32_t list_chunks,
-                                                             unsigned long long* __restrict__ unit,
-                                                             int32_t* __restrict__ hlist_first_slot) {
+__device__ __forceinline__ void heavy_units_workgroup(int64_t n_pieces, unsigned wg, const int32_t* __restrict__ row_len,
+                                                      int32_t heavy_len, const HeavySums& sums, int32_t list_chunks,
+                                                      unsigned long long* __restrict__ unit,
+                                                      int32_t* __restrict__ hlist_first_slot) {
   __shared__ unsigned long long wave_sums[kWaves];
-  const int64_t q0 = (int64_t)blockIdx.x * kHeavySpan + threadIdx.x * kHeavyPerThread;
+  const int64_t q0 = (int64_t)wg * kHeavySpan + threadIdx.x * kHeavyPerThread;
   int len[kHeavyPerThread];
   unsigned long long mine = 0;
 #pragma unroll
@@ -734,8 +761,8 @@ __global__ __launch_bounds__(kBuildBlock) void k_heavy_units(int64_t n_pieces, c
     if (len[i] > heavy_len) mine += (1ull << 32) + (unsigned)heavy_footprint(len[i], heavy_len);
   }
   unsigned long long tot;
-  unsigned long long at = block_exclusive_scan(mine, wave_sums, &tot) + ((unsigned long long)sums.units[blockIdx.x] << 32) +
-                          (unsigned long long)sums.slots[blockIdx.x];
+  unsigned long long at = block_exclusive_scan(mine, wave_sums, &tot) + ((unsigned long long)sums.units[wg] << 32) +
+                          (unsigned long long)sums.slots[wg];
   const int per_list = list_chunks * kChunkSlots;
 #pragma unroll
   for (int i = 0; i < kHeavyPerThread; ++i) {
@@ -746,6 +773,26 @@ __global__ __launch_bounds__(kBuildBlock) void k_heavy_units(int64_t n_pieces, c
       hlist_first_slot[w] = (int32_t)(u + w);
     at += (1ull << 32) + (unsigned)heavy_footprint(len[i], heavy_len);
   }
+}
+
+// What remains of the order of the row blocks by list length where one digit tells the lengths apart (order.hip): its three steps
+// go with launches that are there anyway.
+struct SortPass {
+  SortInput in;
+  int32_t n_rb, tiles, n_launches;
+  int32_t* hist;
+  int32_t* order;
+};
+
+__global__ __launch_bounds__(kBuildBlock) void k_units_and_hist(unsigned n_units, int64_t n_pieces,
+                                                                const int32_t* __restrict__ row_len, int32_t heavy_len,
+                                                                HeavySums sums, int32_t list_chunks,
+                                                                unsigned long long* __restrict__ unit,
+                                                                int32_t* __restrict__ hlist_first_slot, SortPass sort) {
+  if (blockIdx.x < n_units)
+    heavy_units_workgroup(n_pieces, blockIdx.x, row_len, heavy_len, sums, list_chunks, unit, hlist_first_slot);
+  else
+    sort_hist_workgroup(sort.in, sort.n_rb, sort.tiles, 0, blockIdx.x - n_units, sort.hist);
 }
 
 // The partial-sum rows of heavy piece number u whose real entries are the slots [e0, e1) of the heavy sequence:
@@ -782,8 +829,15 @@ __device__ __forceinline__ void for_row_slots(const RowSlotArgs& a, int r, F&& f
   }
 }
 
-__global__ __launch_bounds__(kBuildBlock) void k_row_slot_sums(RowSlotArgs a) {
+// The counts; the workgroups past n_sums scan the histograms of the sort
+__global__ __launch_bounds__(kBuildBlock) void k_row_slot_sums(unsigned n_sums, RowSlotArgs a, SortPass sort) {
   __shared__ unsigned long long wave_sums[kWaves];
+  __shared__ int32_t hist_sums[kWaves];
+  if (blockIdx.x >= n_sums) {
+    const int32_t len = kDigits * sort.tiles;
+    (void)scan_sequence(sort.hist + (int64_t)(blockIdx.x - n_sums) * len, len, hist_sums);
+    return;
+  }
   unsigned long long n = 0, tot;
   for_row_slots(a, blockIdx.x * kBuildBlock + threadIdx.x, [&](int, int count) { n += count; });
   block_exclusive_scan((n << 32) + (n > 0), wave_sums, &tot);
@@ -796,12 +850,12 @@ __global__ __launch_bounds__(kOneBlock) void k_row_slot_scan(unsigned long long*
   if (threadIdx.x == 0) { report[0] = (int32_t)(total >> 32); report[1] = (int32_t)(uint32_t)total; }
 }
 
-__global__ __launch_bounds__(kBuildBlock) void k_row_slot_fill(RowSlotArgs a) {
+__device__ __forceinline__ void row_slot_fill_workgroup(const RowSlotArgs& a, unsigned wg) {
   __shared__ unsigned long long wave_sums[kWaves];
-  const int r = blockIdx.x * kBuildBlock + threadIdx.x;
+  const int r = wg * kBuildBlock + threadIdx.x;
   unsigned long long n = 0, tot;
   for_row_slots(a, r, [&](int, int count) { n += count; });
-  const unsigned long long at = a.sums[blockIdx.x] + block_exclusive_scan((n << 32) + (n > 0), wave_sums, &tot);
+  const unsigned long long at = a.sums[wg] + block_exclusive_scan((n << 32) + (n > 0), wave_sums, &tot);
   if (r >= a.n_rows) return;
   a.row_slot_ptr[r] = (int32_t)(at >> 32);
   if (r == a.n_rows - 1) a.row_slot_ptr[a.n_rows] = (int32_t)((at >> 32) + n);
@@ -842,8 +896,34 @@ constexpr int kCopyPieces = 1024;  // most pieces a workgroup holds at a time
 constexpr int kCopyWords = 6;      // LDS words per piece
 constexpr int kCopyLog2Rows = 7;   // at most 128 rows a block
 
-__global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, StreamShape ss, CopyArgs a, int pieces_at_a_time) {
+// What goes with the copy, in workgroups before its own: the ends of the lists, the partial-sum rows, the order of the row blocks
+struct CopyCompany {
+  unsigned n_ends, n_slots, n_sort;  // workgroups of each
+  unsigned first;                    // the copy's first, a multiple of 8
+  int64_t n_parts;
+  const int32_t* queue_len;
+  int64_t* rb_chunk_ptr;
+  int64_t n_chunks;
+  RowSlotArgs slots;
+  SortPass sort;
+};
+
+__global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, StreamShape ss, CopyArgs a, int pieces_at_a_time,
+                                              CopyCompany with) {
   extern __shared__ int lds[];
+  if (blockIdx.x < with.first) {
+    unsigned wg = blockIdx.x;
+    if (wg < with.n_slots) return row_slot_fill_workgroup(with.slots, wg);
+    wg -= with.n_slots;
+    if (wg < with.n_ends)
+      return list_ends_workgroup(cs, ss, with.n_parts, wg, a.cell_first_chunk, a.group_first_chunk, with.queue_len,
+                                 with.rb_chunk_ptr, with.n_chunks);
+    wg -= with.n_ends;
+    if (wg < with.n_sort)
+      sort_scatter_workgroup(with.sort.in, with.sort.n_rb, with.sort.tiles, 0, wg, with.sort.hist, nullptr, with.sort.order);
+    return;
+  }
+  const unsigned copy_wg = blockIdx.x - with.first, n_copy = gridDim.x - with.first;
   __shared__ int row_lo[(1 << kCopyLog2Rows) + 1];
   const int log2_rows = a.log2_rows, n_rows_here = 1 << log2_rows;
   int* piece_lo = lds;                                                 // first entry in the input
@@ -854,7 +934,7 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
   int* piece_last = piece_chunk + pieces_at_a_time;                    // last column
   const int tid = threadIdx.x;
   const bool with_stream = ss.stream != nullptr, gapless = cs.long_len >= kChunkSlots;
-  if (blockIdx.x == 0 && tid < kChunkSlots) {  // the spare entries past the end of the arrays
+  if (copy_wg == 0 && tid < kChunkSlots) {  // the spare entries past the end of the arrays
     a.cols[a.S + a.T + tid] = 0;
     a.vals[a.S + a.T + tid] = 0.f;
   }
@@ -906,11 +986,11 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
 
   // Workgroup ids go round the 8 XCDs: ids b, b + 8, b + 16, .. take consecutive ranges, so that the lines two ranges
   // write parts of (pieces of neighbouring rows lie next to each other) meet in one L2.
-  const int64_t per_xcd = ((int64_t)gridDim.x + 7) / 8;
-  int64_t work = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  const int64_t per_xcd = ((int64_t)n_copy + 7) / 8;
+  int64_t work = (int64_t)(copy_wg & 7) * per_xcd + (copy_wg >> 3);
   // (a grid that is no multiple of 8 leaves the last XCDs one workgroup short: numbers past the end wrap into the gaps)
-  const int full = (int)(gridDim.x & 7);
-  if (full != 0 && (int)(blockIdx.x & 7) >= full) work -= (int)(blockIdx.x & 7) - full;
+  const int full = (int)(n_copy & 7);
+  if (full != 0 && (int)(copy_wg & 7) >= full) work -= (int)(copy_wg & 7) - full;
   const int64_t first = work * a.per_wg;
   const int64_t last = first + a.per_wg < a.nnz ? first + a.per_wg : a.nnz;
   for (int64_t at = first; at < last;) {
@@ -1060,6 +1140,14 @@ PinnedPool& pinned_pool() {
   return *pool;
 }
 
+struct ValidationGrid {
+  int row_wgs, elem_wgs, vec;
+  explicit ValidationGrid(const sptir_csr_t* csr)
+      : row_wgs((int)std::min<int64_t>(((int64_t)csr->n_rows + 255) / 256, 4096)),
+        elem_wgs((int)std::min<int64_t>((csr->nnz + 2047) / 2048, 8192)),
+        vec((((uintptr_t)csr->indices | (uintptr_t)csr->values) & 15) == 0) {}
+};
+
 struct Blob {  // bump allocator over one device allocation
   char* base = nullptr;
   size_t size = 0;
@@ -1100,12 +1188,10 @@ void pinned_release(PinnedBuf b) { pinned_pool().release(b); }
 void launch_validation(const sptir_csr_t* csr, bool with_values, unsigned long long* flags, hipStream_t stream,
                        int32_t min_deg) {
   const int32_t* value_bits = with_values ? (const int32_t*)csr->values : nullptr;
-  const int row_wgs = (int)std::min<int64_t>(((int64_t)csr->n_rows + 255) / 256, 4096);
-  const int elem_wgs = (int)std::min<int64_t>((csr->nnz + 2047) / 2048, 8192);
-  if (row_wgs + elem_wgs > 0)
-    hipLaunchKernelGGL(k_validate, dim3((unsigned)(row_wgs + elem_wgs)), dim3(256), 0, stream, row_wgs, csr->n_rows,
-                       csr->nnz, csr->n_cols, (int)((((uintptr_t)csr->indices | (uintptr_t)csr->values) & 15) == 0),
-                       csr->indptr, csr->indices, value_bits, min_deg, flags);
+  const ValidationGrid v(csr);
+  if (v.row_wgs + v.elem_wgs > 0)
+    hipLaunchKernelGGL(k_validate, dim3((unsigned)(v.row_wgs + v.elem_wgs)), dim3(256), 0, stream, v.row_wgs, csr->n_rows,
+                       csr->nnz, csr->n_cols, v.vec, csr->indptr, csr->indices, value_bits, min_deg, flags);
 }
 
 sptir_status_t validation_verdict(const unsigned long long* flag_slots, bool* one_value_per_row) {
@@ -1363,11 +1449,15 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     BUILD_HIP(hipMemsetAsync(d_flags, 0, (kValidationWords + 2) * sizeof(unsigned long long), stream));
     const bool want_slices = with_spmm_plan && opt.column_slices != 2 && opt.full_rows != 1;
     if (want_slices) min_deg = (int32_t)std::min<int64_t>(INT32_MAX, slice_min_degree(s.n_cols));
-    launch_validation(csr, value_bits != nullptr, d_flags, stream, min_deg);
+    {
+      const ValidationGrid v(csr);
+      const int64_t n_wg = n_bound_blocks + v.row_wgs + v.elem_wgs;
+      if (n_wg > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
+      if (n_wg > 0)
+        hipLaunchKernelGGL(k_first_pass, dim3((unsigned)n_wg), dim3(256), 0, stream, (unsigned)n_bound_blocks, v.row_wgs, s, csr->nnz,
+                           v.vec, csr->indptr, csr->indices, value_bits, min_deg, d_flags, d_bound);
+    }
     if (s.NB > 0) {
-      if (n_bound_blocks > 0)
-        hipLaunchKernelGGL(k_piece_bounds, dim3((unsigned)n_bound_blocks), dim3(256), 0, stream, s, (int32_t)csr->nnz,
-                           csr->indptr, csr->indices, d_bound);
       hipLaunchKernelGGL(k_count, dim3((unsigned)n_pair_blocks), dim3(kBuildBlock), 0, stream, s, csr->indptr,
                          d_bound, d_counts, d_rnnz);
     }
@@ -1471,7 +1561,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     if (n_cells > 0x7FFFFFFF || n_bounds > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
     const size_t o_bounds = tmp2.reserve(sizeof(int32_t) * (size_t)(n_bounds ? n_bounds : 1));
     const size_t o_cell_chunks = tmp2.reserve(sizeof(long long) * (size_t)(n_cells ? n_cells : 1));
-    const size_t o_group_tot = tmp2.reserve(sizeof(long long) * (size_t)(n_groups ? n_groups : 1));
+    const size_t o_group_tot = tmp2.reserve(sizeof(long long) * (size_t)(n_groups + 1));
     const size_t o_queue_len = tmp2.reserve(sizeof(int32_t) * 8 * (size_t)(n_parts ? n_parts : 1));
     const size_t o_piece_of = tmp2.reserve(sizeof(int32_t) * (size_t)s.c * (size_t)(s.n_rows ? s.n_rows : 1));
     // per piece: what the lists do with it, or its number among the heavy pieces; the sums of the scans
@@ -1547,14 +1637,16 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       BUILD_HIP(hipMemsetAsync(h->vals + h->S + T, 0, sizeof(float) * kChunkSlots, stream));
     }
     BUILD_HIP(hipGetLastError());
-    if (n_spans > 0)
-      hipLaunchKernelGGL(k_heavy_sums, dim3((unsigned)n_spans), dim3(kBuildBlock), 0, stream, n_pieces, h->row_len,
-                         cs.long_len, sums);
+    {
+      const int64_t n_wg = n_spans + (n_cells > 0 ? (n_bounds + kBuildBlock - 1) / kBuildBlock : 0);
+      if (n_wg > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
+      if (n_wg > 0)
+        hipLaunchKernelGGL(k_sums_and_cells, dim3((unsigned)n_wg), dim3(kBuildBlock), 0, stream, (unsigned)n_spans, n_pieces,
+                           h->row_len, cs.long_len, sums, cs, h->bucket_row_ptr, h->rem_part_ptr, h->row_ids, d_bounds);
+    }
 
     // ---- the pieces of every (launch, row block, partition) dealt to its queues; chunks of the lists
     if (n_cells > 0) {
-      hipLaunchKernelGGL(k_cell_bounds, dim3((unsigned)((n_bounds + 255) / 256)), dim3(256), 0, stream, cs,
-                         h->bucket_row_ptr, h->rem_part_ptr, h->row_ids, d_bounds);
       hipLaunchKernelGGL(k_deal, dim3((unsigned)((n_parts + kDealParts - 1) / kDealParts)), dim3(8 * kDealParts),
                          (sizeof(int) * 2 * kDealParts) << cs.log2_rb, stream, cs, n_parts, d_bounds, h->row_len, d_cell_chunks,
                          d_dealt, d_queue_len);
@@ -1629,21 +1721,40 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       if (n_groups > 0) h->rb_order = (int32_t*)(c0 + c_rb_order);
       h->stream = (int32_t*)(c0 + c_stream);
     }
-    if (h->n_heavy > 0) {
-      // ---- heavy pieces: their numbers and slots, the first partial-sum row of every heavy list, which
-      // partial-sum rows each row of Y takes, the rows that have any (the launch that adds them visits only those)
-      hipLaunchKernelGGL(k_heavy_units, dim3((unsigned)n_spans), dim3(kBuildBlock), 0, stream, n_pieces, h->row_len,
-                         cs.long_len, sums, list_chunks, d_unit, h->hlist_first_slot);
-      RowSlotArgs a;
-      a.n_rows = s.n_rows; a.c = s.c; a.list_chunks = list_chunks; a.heavy_len = cs.long_len;
-      a.indptr = csr->indptr; a.piece_of = d_piece_of; a.row_len = h->row_len; a.unit = d_unit;
-      a.sums = (unsigned long long*)(tmp2.base + o_row_sums);
-      a.row_slot_ptr = h->row_slot_ptr; a.row_slots = h->row_slots; a.heavy_rows = h->heavy_rows;
-      hipLaunchKernelGGL(k_row_slot_sums, dim3((unsigned)s.NB), dim3(kBuildBlock), 0, stream, a);
-      hipLaunchKernelGGL(k_row_slot_scan, dim3(1), dim3(kOneBlock), 0, stream, a.sums, (int64_t)s.NB,
-                         (int32_t*)(host.base + h_report3));
-      hipLaunchKernelGGL(k_row_slot_fill, dim3((unsigned)s.NB), dim3(kBuildBlock), 0, stream, a);
+    // ---- launch order of the row blocks: longest list first.  One digit is enough for most graphs; its steps then go with the
+    // launches below.  (169,343 rows, 1.17 M entries, build + SpMM + release: see k_copy.)
+    SortPass sort;
+    memset(&sort, 0, sizeof(sort));
+    const bool sort_here = n_groups > 0 && max_list_len < kDigits;
+    if (sort_here) {
+      sort.in.list_ptr = (const int64_t*)d_group_tot;
+      sort.n_rb = cs.n_rb; sort.n_launches = cs.n_phases;
+      sort.tiles = (cs.n_rb + kSortTile - 1) / kSortTile;
+      sort.order = h->rb_order;
+      tmp_order = scratch_alloc(sizeof(int32_t) * kDigits * (size_t)sort.tiles * (size_t)sort.n_launches, alloc, actx, stream);
+      if (!tmp_order) { st = SPTIR_ERR_ALLOC; goto fail; }
+      sort.hist = (int32_t*)tmp_order;
     }
+    const unsigned sort_wgs = (unsigned)sort.tiles * (unsigned)sort.n_launches;
+    // ---- heavy pieces: their numbers and slots, the first partial-sum row of every heavy list, which
+    // partial-sum rows each row of Y takes, the rows that have any (the launch that adds them visits only those)
+    const bool heavy = h->n_heavy > 0;
+    RowSlotArgs slots;
+    memset(&slots, 0, sizeof(slots));
+    slots.n_rows = s.n_rows; slots.c = s.c; slots.list_chunks = list_chunks; slots.heavy_len = cs.long_len;
+    slots.indptr = csr->indptr; slots.piece_of = d_piece_of; slots.row_len = h->row_len; slots.unit = d_unit;
+    slots.sums = (unsigned long long*)(tmp2.base + o_row_sums);
+    slots.row_slot_ptr = h->row_slot_ptr; slots.row_slots = h->row_slots; slots.heavy_rows = h->heavy_rows;
+    const unsigned unit_wgs = heavy ? (unsigned)n_spans : 0, slot_wgs = heavy ? (unsigned)s.NB : 0;
+    if (unit_wgs + sort_wgs > 0)
+      hipLaunchKernelGGL(k_units_and_hist, dim3(unit_wgs + sort_wgs), dim3(kBuildBlock), 0, stream, unit_wgs, n_pieces, h->row_len,
+                         cs.long_len, sums, list_chunks, d_unit, h->hlist_first_slot, sort);
+    if (slot_wgs + (unsigned)sort.n_launches > 0)
+      hipLaunchKernelGGL(k_row_slot_sums, dim3(slot_wgs + (unsigned)sort.n_launches), dim3(kBuildBlock), 0, stream, slot_wgs, slots,
+                         sort);
+    if (heavy)
+      hipLaunchKernelGGL(k_row_slot_scan, dim3(1), dim3(kOneBlock), 0, stream, slots.sums, (int64_t)s.NB,
+                         (int32_t*)(host.base + h_report3));
     StreamShape ss;
     ss.stream = h->stream; ss.compact = h->compact_stream; ss.log2_rb = cs.log2_rb; ss.unit = h->row_val ? 1 : 0;
     ss.phase_width = (int32_t)((int64_t)cs.ppg * s.w > 0x7FFFFFFF ? 0x7FFFFFFF : (int64_t)cs.ppg * s.w);
@@ -1666,20 +1777,22 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       while (a.log2_rows > 0 && ((int64_t)s.c << a.log2_rows) > kCopyPieces) --a.log2_rows;
       const int pieces = (int)std::min<int64_t>((int64_t)s.c << a.log2_rows, kCopyPieces);
       const int64_t n_wg = std::max<int64_t>(1, (csr->nnz + a.per_wg - 1) / a.per_wg);
-      hipLaunchKernelGGL(k_copy, dim3((unsigned)n_wg), dim3(256), sizeof(int) * kCopyWords * (size_t)pieces, stream, s, cs,
-                         ss, a, pieces);
+      CopyCompany with;
+      with.n_slots = slot_wgs; with.n_ends = (unsigned)((n_parts + 3) / 4); with.n_sort = sort_wgs;
+      with.first = (with.n_slots + with.n_ends + with.n_sort + 7) / 8 * 8;
+      with.n_parts = n_parts; with.queue_len = d_queue_len; with.rb_chunk_ptr = h->rb_chunk_ptr; with.n_chunks = n_chunks;
+      with.slots = slots; with.sort = sort;
+      if (n_wg + with.first > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
+      hipLaunchKernelGGL(k_copy, dim3((unsigned)n_wg + with.first), dim3(256), sizeof(int) * kCopyWords * (size_t)pieces, stream, s,
+                         cs, ss, a, pieces, with);
     }
-    if (n_parts > 0)
-      hipLaunchKernelGGL(k_list_ends, dim3((unsigned)((n_parts + 3) / 4)), dim3(256), 0, stream, cs, ss, n_parts,
-                         d_cell_chunks, d_group_tot, d_queue_len, h->rb_chunk_ptr, (int64_t)n_chunks);
     BUILD_HIP(hipGetLastError());
     if (n_parts == 0) {  // no lists: the one element of rb_chunk_ptr
       int64_t* zero = (int64_t*)(host.base + h_misc + 16);
       *zero = 0;
       BUILD_HIP(hipMemcpyAsync(h->rb_chunk_ptr, zero, sizeof(int64_t), hipMemcpyHostToDevice, stream));
     }
-    if (n_groups > 0) {
-      // ---- launch order of the row blocks: longest list first
+    if (n_groups > 0 && !sort_here) {
       st = order_row_blocks(h->rb_chunk_ptr, cs.n_phases, cs.n_rb, max_list_len, h->rb_order, alloc, free_, actx,
                             stream, &tmp_order);
       if (st != SPTIR_OK) goto fail;
