@@ -99,8 +99,16 @@ enum RowEnd { kWhole, kQuads, kTail };
 // cache does hold would come from memory every time: 7.9 M entries 70 -> 105 us).
 enum Source { kCsr, kPlan, kLargePlan };
 constexpr int64_t kLargeList = 24 << 20;  // entries: 12 bytes each, 256 MB and more
+template <int T, Source SOURCE>
+constexpr int sddmm_waves() { return T == 4 && SOURCE != kCsr ? 3 : T <= 4 ? 4 : 2; }
+// Rows of X a wavefront stages per chunk with a plan.  A chunk of more rows loads them entry by entry: with 16 for four float4 half of
+// the chunks of short pieces did (45 M listed entries of 232,965 rows, 128 features, the call: 16 rows 2.56 ms, 20 2.49, 26 2.47, 32,
+// which leave room for 8 wavefronts a CU, 2.60).  One float4: none 632, 24 600 us (50 M entries); five: 8 1370, 16 1200 us (25 M).
+// Two: none, as 16 to 32 lose up to 15 % where pieces are long.
+template <int T>
+constexpr int sddmm_staged_rows() { return T == 1 ? 24 : T == 2 ? 0 : T == 3 ? 24 : T == 4 ? 26 : 16; }
 template <int T, RowEnd END, bool MANY, Source SOURCE>
-__global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(SddmmArgs a) {
+__global__ __launch_bounds__(64 * kSddmmWaves, (sddmm_waves<T, SOURCE>())) void k_sddmm(SddmmArgs a) {
   constexpr bool PLAN = SOURCE != kCsr;
   const int lane = threadIdx.x & 63, g = lane >> 3, fl = lane & 7;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -191,7 +199,7 @@ __global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(Sddm
   // different rows (one per lane group), where a reload inside the entry loop costs the address path a whole
   // instruction even if a single lane group asks for it - and in partition order a row lasts only a few entries.
   // (CSR order: no gain, measured.)
-  constexpr int kStage = MANY || !PLAN ? 0 : (T == 3 || T == 4 ? 16 : (T > 4 ? 8 : 0));  // rows of X staged per wavefront
+  constexpr int kStage = MANY || !PLAN ? 0 : sddmm_staged_rows<T>();
   __shared__ __align__(16) float x_stage[kSddmmWaves][kStage > 0 ? kStage : 1][32 * T];
   __shared__ int row_table[kSddmmWaves][kStage > 0 ? kStage : 1];
   float4 x[T];
@@ -206,7 +214,7 @@ __global__ __launch_bounds__(64 * kSddmmWaves, T <= 4 ? 4 : 2) void k_sddmm(Sddm
     if constexpr (PLAN) c.val = a.values[c.pos];
     // Gathers run kAhead entries ahead of the multiplies; the scheduling barriers keep the compiler from
     // hoisting all eight entries' loads to the top (T*8 float4 of registers).
-    constexpr int kAhead = 2;
+    constexpr int kAhead = PLAN && T == 4 ? 3 : 2;
     float p[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) p[i] = 0.f;
