@@ -15,14 +15,16 @@
 //           the rest of its graph together.
 // Every wavefront loads the 64 row lengths itself (one coalesced load), so all
 // of them know the long rows without a barrier, and a workgroup without long
-// rows never meets one.  Sums have a fixed order: results are reproducible.
+// rows never meets one.  Where rows are short in the mean, the long ones are taken
+// by workgroups that come before all others instead.  Sums have a fixed order: results are reproducible.
 // The fourth lane of a tail reads (and writes) the last four floats of the
 // row, so any feature size of four or more uses 16-byte accesses; they need
 // only 4-byte alignment.
-// Measured (169,343 rows, 1,166,243 entries, 128 features): 0.65 -> 0.127 ms on
-// operands that change from call to call (0.113 on the same ones), 4.7 TB/s of
+// Measured (169,343 rows, 1,166,243 entries, 128 features): 0.65 -> 0.117 ms on
+// operands that change from call to call (0.104 on the same ones), 5.1 TB/s of
 // gathered rows of which a quarter hit L2; the memory-side cache delivers 7.9 at
 // random.
+#include <algorithm>
 #include <type_traits>
 
 #include "sptir_internal.h"
@@ -42,6 +44,9 @@ struct CsrArgs {
   int32_t n_tiles;
   int32_t map_mode;
   int32_t map_param;
+  // LONG_FIRST: the workgroups before the others (a multiple of 8), and among them those of a tile
+  uint32_t long_grid;
+  int32_t long_mode, long_param, long_units;
 };
 
 constexpr int kCsrRows = 64;     // most rows per workgroup: one per lane when their lengths are loaded
@@ -50,7 +55,8 @@ constexpr int kLongRow = 512;    // eight steps of one wavefront (1024: 5 % slow
                                  // of it with 16 rows per workgroup, twice of it where every wavefront has one row
                                  // (3,576 rows, 514,589 entries: 14 us against 17)
 
-template <int VEC, int LG, int ROWS>
+// LONG_FIRST: workgroups of their own take the long rows, before the others begin
+template <int VEC, int LG, int ROWS, bool LONG_FIRST>
 __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
   constexpr int kGroups = 64 / LG, kWaves = 8, kRowsPerWave = ROWS / kWaves;
   constexpr int UB = LG < 8 ? LG : 8, kTile = VEC * LG;
@@ -58,9 +64,11 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
   __shared__ __align__(16) float part[kWaves][kTile];
   int64_t unit;
   int tile_id;
-  decode_block(blockIdx.x, a.map_mode, a.map_param, a.n_tiles, &unit, &tile_id);
-  const int64_t row0 = unit * ROWS;
-  if (row0 >= a.n_rows) return;
+  const bool for_long = LONG_FIRST && blockIdx.x < a.long_grid;
+  if (for_long) decode_block(blockIdx.x, a.long_mode, a.long_param, a.n_tiles, &unit, &tile_id);
+  else decode_block(blockIdx.x - (LONG_FIRST ? a.long_grid : 0u), a.map_mode, a.map_param, a.n_tiles, &unit, &tile_id);
+  const int64_t row0 = for_long ? 0 : unit * ROWS;
+  if (row0 >= a.n_rows || (for_long && unit >= a.long_units)) return;
   const int lane = threadIdx.x & 63, g = lane / LG, fl = lane & (LG - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int f_nominal = tile_id * kTile + fl * VEC;
@@ -72,13 +80,12 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
 
   // lane l: first entry and length of row row0 + l
   int row_begin = 0, row_len = 0;
-  if (lane < ROWS && row0 + lane < a.n_rows) {
+  if (!for_long && lane < ROWS && row0 + lane < a.n_rows) {
     row_begin = a.indptr[row0 + lane];
     row_len = a.indptr[row0 + lane + 1] - row_begin;
   }
 
   constexpr int kLong = ROWS == 8 ? 2 * kLongRow : ROWS == 16 ? kLongRow / 2 : kLongRow;
-  unsigned long long long_rows = __ballot(row_len > kLong);
   float acc[VEC];
   // entries [first, first + left) of a row summed by this lane group, `stride` entries apart from step to step; the
   // next step's entries are fetched while this one's gathers are in flight (two steps of gathers in flight measured
@@ -126,11 +133,8 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
       for (int e = 0; e < VEC; ++e) acc[e] += __shfl_xor(acc[e], d, 64);
   };
 
-  // long rows: the workgroup each (every wavefront sees the same mask)
-  while (long_rows) {
-    const int src = __builtin_ctzll(long_rows);
-    long_rows &= long_rows - 1;
-    const int first = __builtin_amdgcn_readlane(row_begin, src), len = __builtin_amdgcn_readlane(row_len, src);
+  // a long row, by the whole workgroup
+  auto long_row = [&](int64_t row, int first, int len) {
     const int o = (wave * kGroups + g) * UB;
     clear();
     walk(first + o, len - o, kWaves * kGroups * UB);
@@ -145,9 +149,35 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
       for (int w = 1; w < kWaves; ++w)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[e] += part[w][fl * VEC + e];
-      store_unaligned<VEC>(Yf + (size_t)(row0 + src) * feat, acc);
+      store_unaligned<VEC>(Yf + (size_t)row * feat, acc);
     }
     __syncthreads();
+  };
+  if constexpr (LONG_FIRST) {
+    if (for_long) {
+      __shared__ unsigned long long span_long[2][kWaves];
+      int turn = 0;
+      for (int64_t r0 = unit * 512; r0 < a.n_rows; r0 += (int64_t)a.long_units * 512, turn ^= 1) {  // 512 rows at a time, one per thread
+        const int64_t r = r0 + threadIdx.x;
+        const int len = r < a.n_rows ? a.indptr[r + 1] - a.indptr[r] : 0;
+        const unsigned long long mine = __ballot(len > kLong);
+        if (lane == 0) span_long[turn][wave] = mine;
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w)
+          for (unsigned long long left = span_long[turn][w]; left; left &= left - 1) {
+            const int64_t row = r0 + w * 64 + __builtin_ctzll(left);
+            const int first = __builtin_amdgcn_readfirstlane(a.indptr[row]);
+            long_row(row, first, __builtin_amdgcn_readfirstlane(a.indptr[row + 1]) - first);
+          }
+      }
+      return;
+    }
+  } else {
+    // (every wavefront sees the same mask)
+    for (unsigned long long long_rows = __ballot(row_len > kLong); long_rows; long_rows &= long_rows - 1) {
+      const int src = __builtin_ctzll(long_rows);
+      long_row(row0 + src, __builtin_amdgcn_readlane(row_begin, src), __builtin_amdgcn_readlane(row_len, src));
+    }
   }
   // short rows: a lane group each
   constexpr int kPasses = (kRowsPerWave + kGroups - 1) / kGroups;
@@ -211,15 +241,34 @@ extern "C" sptir_status_t sptir_spmm_csr(const sptir_csr_t* csr, const float* X,
   CsrArgs a;
   a.indptr = csr->indptr; a.indices = csr->indices; a.values = csr->values; a.X = X; a.Y = Y;
   a.n_rows = csr->n_rows; a.feat = feat; a.n_tiles = g.n_tiles; a.map_mode = g.map_mode; a.map_param = g.map_param;
-  dim3 grid((unsigned)g.grid), block(512);
+  // Long rows first, by workgroups of their own (512 over all tiles, which look through all rows): a long row that a workgroup in the
+  // middle of the grid meets is worked on when the others have ended (169,343 rows, 13,000 entries the longest: 113 -> 104 us; 80
+  // graphs: power-law rows of less than 24 entries in the mean 1.02 to 1.39 times as fast, even ones 0.96 to 1.01).  Longer rows
+  // are long too often for 512 workgroups (mean of 24 to 100 entries: 0.7 to 1.07).
+  const bool long_first = csr->nnz < 24 * (int64_t)csr->n_rows;
+  int64_t long_grid = 0;
+  if (long_first) {
+    Geometry first = g;
+    a.long_units = (int32_t)std::max<int64_t>(1, std::min<int64_t>(512 / g.n_tiles, ((int64_t)csr->n_rows + 511) / 512));
+    if (!plan_tiles(a.long_units, &first)) return SPTIR_ERR_OVERFLOW;
+    long_grid = (first.grid + 7) / 8 * 8;
+    a.long_grid = (uint32_t)long_grid; a.long_mode = first.map_mode; a.long_param = first.map_param;
+    if (long_grid + g.grid > 0x7FFFFFFF) return SPTIR_ERR_OVERFLOW;
+  }
+  dim3 grid((unsigned)(long_grid + g.grid)), block(512);
   hipStream_t stream = (hipStream_t)stream_;
   auto launch = [&](auto n) {
     constexpr int kRows = decltype(n)::value;
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, a); };
-    if (g.vec == 1) go(k_spmm_csr<1, 8, kRows>);
-    else if (g.lg == 4) go(k_spmm_csr<4, 4, kRows>);
-    else if (g.lg == 16) go(k_spmm_csr<4, 16, kRows>);
-    else go(k_spmm_csr<4, 8, kRows>);
+    auto shape = [&](auto first) {
+      constexpr bool kFirst = decltype(first)::value;
+      if (g.vec == 1) go(k_spmm_csr<1, 8, kRows, kFirst>);
+      else if (g.lg == 4) go(k_spmm_csr<4, 4, kRows, kFirst>);
+      else if (g.lg == 16) go(k_spmm_csr<4, 16, kRows, kFirst>);
+      else go(k_spmm_csr<4, 8, kRows, kFirst>);
+    };
+    if (kRows == kCsrRows && long_first) shape(std::integral_constant<bool, kRows == kCsrRows>{});
+    else shape(std::false_type{});
   };
   if (rows == kCsrRows) launch(std::integral_constant<int, kCsrRows>{});
   else if (rows == 16) launch(std::integral_constant<int, 16>{});

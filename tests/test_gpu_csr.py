@@ -43,3 +43,20 @@ def test_rows_per_workgroup(gpu_lib, n_rows, feat, mean):
     gpu_lib.sptir_spmm_csr(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, d.X, Y)
     Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
     assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"rows={n_rows} feat={feat} mean={mean}")
+
+
+@pytest.mark.parametrize("n_rows,feat", [(1, 4), (511, 3), (513, 16), (1025, 41), (6000, 67), (40_000, 36), (17_000, 1028)])
+def test_long_rows_among_short_ones(gpu_lib, n_rows, feat):
+    """Rows of a few entries, whose long ones workgroups of their own take: none, one in the last row, several next to each
+    other, more rows than those workgroups look through at a time."""
+    rng = np.random.default_rng(n_rows)
+    deg = rng.integers(0, 6, n_rows)
+    if n_rows > 500:
+        at = np.r_[n_rows - 1, 63, 64, 65, rng.choice(n_rows - 1, min(12, n_rows // 400), replace=False)]
+        deg[at] = rng.choice([512, 513, 600, 1100], at.size)
+    w = workloads.random_csr(n_rows, 1200, deg, feat, feat)
+    d = upload(w)
+    Y = torch.full((n_rows, feat), float("nan"), device="cuda")
+    gpu_lib.sptir_spmm_csr(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, d.X, Y)
+    Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"rows={n_rows} feat={feat}")
