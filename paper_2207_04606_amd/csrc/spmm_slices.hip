@@ -465,7 +465,7 @@ sptir_status_t spmm_slices_count(SpmmSliceBuild* b, const sptir_csr_t* csr, int3
 // Second half, once the stream has been waited for: panels, units and the handle's arrays.  The host side of `b` has to stay until
 // the stream has drained.
 sptir_status_t spmm_slices_fill(SpmmSliceBuild* b, const sptir_csr_t* csr, int32_t feat_hint, bool with_values, SpmmSlices* out,
-                                sptir_alloc_fn alloc, void* actx, hipStream_t stream) {
+                                sptir_alloc_fn alloc, void* actx, hipStream_t stream) try {
   const int32_t* block_steps = (const int32_t*)b->host.p;
   const int32_t* slice_steps = block_steps + b->n_blocks;
   int64_t n_steps = 0;
@@ -571,6 +571,8 @@ sptir_status_t spmm_slices_fill(SpmmSliceBuild* b, const sptir_csr_t* csr, int32
   out->rows = (const int32_t*)(base + o_rows); out->step_of = step_of;
   out->cols = cols; out->vals = vals; out->partial = (float*)(base + o_partial);
   return SPTIR_OK;
+} catch (const std::bad_alloc&) {  // (the tables of units and panels)
+  return SPTIR_ERR_ALLOC;
 }
 
 void spmm_slices_done(SpmmSliceBuild* b, sptir_free_fn free_, void* actx) {
