@@ -1665,6 +1665,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     const long long n_chunks = report2[0];
     h->n_heavy_nnz = report2[4];
     const int64_t max_list_len = report2[1];
+    h->longest_list = max_list_len;
     // the lists' chunks come first in the stream (each list a whole number of quads), then the heavy chunks
     // (report2[3]: slots of the heavy sequence)
     const int64_t n_heavy_chunks = (chunks_of_slots(report2[3]) + kChunksPerQuad - 1) / kChunksPerQuad * kChunksPerQuad;

@@ -76,6 +76,7 @@ struct sptir_hyb {
   int64_t* rb_chunk_ptr;     // device [n_phases * n_row_blocks + 1], first chunk of each group
   int32_t* rb_order;         // device [n_phases * n_row_blocks]: the row blocks of a launch, longest list first
   int64_t n_chunks;
+  int64_t longest_list;      // chunks
   // heavy pieces (see kHeavyListChunks): their chunks sit in `stream` from chunk heavy_chunk0 on
   int32_t heavy_len;
   int64_t n_heavy;            // heavy pieces
