@@ -1260,6 +1260,10 @@ bool partitions_matter(int32_t c, int32_t w, int32_t n_rows, int64_t slots, long
 //    are fewer than 2^19 entries and the whole takes about as long as those launches);
 //  * or the graph is large enough for 8 microseconds not to matter;
 //  * or it has so few lists that they leave most of the GPU idle.
+// One launch of fewer than 1024 lists, no row of kHeavyLenMax entries: none, its lists are shared by the wavefronts of
+// workgroups (shared_list_waves() in spmm.hip) and there is no second launch to wait for.  (55 graphs, 0.5 to 3.7 M entries, 16
+// to 256 features: 1.01 to 1.59 times as fast in all of them, 1.23 in the mean; 3,265 rows, 666,264 entries, 64 features 18.8 ->
+// 12.4 us.)
 // An even matrix (no row four times the mean) keeps all of its pieces in the lists.  Pieces leave from one chunk on.
 // Measured on 320 graphs with power-law degrees, 2,500 to 235,000 rows, 60,000 to 8 M entries, 32 to 128 features.  Where the
 // rule takes pieces out, against the rule before it (nothing out below 2^19 entries, beyond that pieces of more than two
@@ -1274,6 +1278,7 @@ int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int
   if (rounds) return kChunkSlots;
   const int64_t n_lists = n_row_blocks * n_phases, per_list = n_lists > 0 ? nnz / n_lists : 0;
   const int64_t longest = longest_row / std::max(1, n_phases);
+  if (n_phases == 1 && n_row_blocks < 1024 && longest_row < kHeavyLenMax && nnz < (1 << 22)) return kHeavyLenMax;
   const bool small = nnz < (1 << 19);
   const bool uneven = longest_row * n_rows >= 4 * nnz;
   const bool worth = (longest >= (small ? 32 : 16) * kChunkSlots && longest >= 2 * per_list) || nnz >= (1 << 22) ||
