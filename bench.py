@@ -25,6 +25,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
+LDS_GATHER_GBS = 66000.0       # random 64-byte rows out of LDS, every CU at once (a microbenchmark; 128-byte rows 71 TB/s)
 GATHER_THEORY_GBS = 39300.0    # 256 CUs x 64 B/clk x 2.4 GHz: what the vector-memory return path could carry
 FMA_PEAK_TFLOPS = 157.3        # fp32 vector, published (plain v_fma_f32 measures ~129 here: the packed forms are not needed)
 
@@ -371,14 +372,19 @@ def main():
     kt = head["kernels"]
     fingerprint = source_fingerprint()
     feat = 128
+    n_long = int(sptir.sptir_hyb_array(hyb, "plan_long_rows").size)   # rows summed from column slices in LDS
+    from_lds = n_long > 0 and kt["ms_heavy"] >= kt["ms_lists"]
     if kt["ms_heavy"] >= kt["ms_lists"]:
-        kernel, n_launch, ms = "k_spmm_heavy<4, 8, true, false, %s>" % ("true" if info["values_per_row"] else "false"), \
-            kt["n_heavy_launches"], kt["ms_heavy"]
+        # (rows in column slices: k_spmm_slices, and k_spmm_heavy for the few pieces left)
+        kernel = "k_spmm_heavy<4, 8, true, false, %s>" % ("true" if info["values_per_row"] else "false")
+        if n_long:
+            kernel = "k_spmm_slices<%s> + %s" % ("true" if info["values_per_row"] else "false", kernel)
+        n_launch, ms = kt["n_heavy_launches"], kt["ms_heavy"]
         # its share of the minimal byte model: the heavy pieces' entries once, X once, its partial sums written
         alg_bytes = (8.0 * info["n_heavy_nnz"] + 4.0 * w.n_cols * feat +
                      4.0 * feat * (info["n_heavy_pieces"] + info["n_heavy_lists"]))
         gathered = info["n_heavy_nnz"] * feat * 4.0
-        key = args.workload + "_feat128_k_spmm_heavy"
+        key = args.workload + ("_feat128_k_spmm_slices_and_heavy" if n_long else "_feat128_k_spmm_heavy")
     else:
         kernel, n_launch, ms = "k_spmm_hyb<4, 8, true, false, %s>" % ("true" if info["values_per_row"] else "false"), \
             kt["n_list_launches"], kt["ms_lists"]
@@ -396,7 +402,7 @@ def main():
         "kernel": kernel, "launches_per_step": n_launch,
         "avg_launch_ms": round(per_launch_ms, 4), "algorithmic_bytes_per_launch": alg_bytes / max(n_launch, 1),
         "kernel_ms_per_step": {"k_spmm_hyb": round(kt["ms_lists"], 4), "k_spmm_heavy": round(kt["ms_heavy"], 4),
-                               "k_heavy_reduce": round(kt["ms_reduce"], 4),
+                               "k_heavy_reduce": round(kt["ms_reduce"], 4), "rows_in_column_slices": n_long,
                                "launches": [kt["n_list_launches"], kt["n_heavy_launches"], kt["n_reduce_launches"]]},
         "whole_call": {"achieved": round(head["bmin_gbs"], 1), "frac": round(head["bmin_gbs"] / HBM_PEAK_GBS, 4),
                        "algorithmic_bytes": head["bmin"]},
@@ -406,10 +412,12 @@ def main():
     # vector-memory return path.  Its roof is measured here, on this GPU, by the library's microbenchmark.
     roof = gather_roof(sptir, torch, dev, quick=True)
     out["roofline"]["binding_roof"] = {
-        "name": "vector-memory gather of 128-byte rows of X out of an XCD's L2",
+        "name": "gather of 64-byte rows of X out of a CU's LDS (measured once)" if from_lds else
+                "vector-memory gather of 128-byte rows of X out of an XCD's L2",
+        "roof_gbs": LDS_GATHER_GBS if from_lds else roof["l2_resident_gbs"],
         "kernel_gathered_gbs": round(gathered / ms / 1e6, 1),
         "measured_l2_resident_gbs": roof["l2_resident_gbs"], "theory_gbs": GATHER_THEORY_GBS,
-        "frac_of_measured": round(gathered / ms / 1e6 / roof["l2_resident_gbs"], 4),
+        "frac_of_measured": round(gathered / ms / 1e6 / (LDS_GATHER_GBS if from_lds else roof["l2_resident_gbs"]), 4),
         "frac_of_theory": round(gathered / ms / 1e6 / GATHER_THEORY_GBS, 4),
         "whole_call_gathered_gbs": round(head["gather_gbs"], 1),
         "whole_call_frac_of_measured": round(head["gather_gbs"] / roof["l2_resident_gbs"], 4),

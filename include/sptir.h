@@ -292,7 +292,8 @@ sptir_status_t sptir_launch_plan(int32_t n_rows, int32_t n_cols, int64_t stored_
  * such sweeps, each over a group of feature columns).  Heavy row pieces
  * (n_heavy_pieces > 0) take two more launches per 128 features (one where the
  * chunk lists are a single launch and the heavy lists the smaller part: they
- * then share that launch): their partial
+ * then share that launch), rows in column slices (SPTIR_PLAN_LONG_ROWS) two more
+ * per 128 features: their partial
  * sums pass through scratch memory that the handle owns, so calls on one handle
  * that has heavy pieces must not overlap in time.  No atomics are used and every
  * sum has a fixed order, so two calls with the same handle and X on the same GPU
@@ -309,8 +310,8 @@ sptir_status_t sptir_spmm(const sptir_hyb_t* hyb, const float* X, float* Y, int3
  * benchmark can price each kernel by the time it really took inside the call.  Synchronises `stream` before it
  * returns; creates and destroys a few events.  Same results as sptir_spmm.
  *   ms_lists   the chunk-list launches (k_spmm_hyb), n_list_launches of them
- *   ms_heavy   the heavy-piece launches (k_spmm_heavy)
- *   ms_reduce  the launches that add the heavy pieces' partial sums to Y (k_heavy_reduce)
+ *   ms_heavy   the heavy-piece launches (k_spmm_heavy) and those over column slices (k_spmm_slices)
+ *   ms_reduce  the launches that add the heavy pieces' partial sums to Y (k_heavy_reduce) and the slices' (k_slice_sums)
  */
 typedef struct {
   float ms_lists, ms_heavy, ms_reduce;
@@ -343,8 +344,10 @@ sptir_status_t sptir_roof_fma(int32_t n_workgroups, int32_t iters, float* sink, 
  * (sptir_hyb_info_t.n_heavy_pieces > 0; 64 to 512 floats for every heavy piece and every heavy list), does not come
  * from the handle here but from a static device array of SPTIR_NOALLOC_SCRATCH_BYTES inside the library, which
  * every GPU the library runs on holds until the process ends.  The call allocates and frees nothing, on any path.
+ * (The partial sums of rows in column slices stay in the handle.)
  * A matrix whose partial sums do not fit ((n_heavy_pieces + n_heavy_lists) * 512 bytes exceed the array; * 256 bytes,
- * taken in more sweeps, where the library chose a heavy_len below 2048 and rounds == 0) is
+ * taken in more sweeps, where the library chose a heavy_len below 2048 and rounds == 0; with the pieces and lists that rows
+ * in column slices would make if they were not there) is
  * refused with SPTIR_ERR_UNSUPPORTED before anything is enqueued, and sptir_last_hip_error() then says by how
  * much.  Every call on one GPU shares that GPU's array: calls that overlap in time on one GPU race (also calls
  * on different handles and different streams); calls ordered by a stream or by the caller are fine.  Nothing in

@@ -30,10 +30,10 @@
 // complete where it is computed - so one launch covers all of them.
 // Rows with entries in every slice of columns that fits LDS leave the lists (sddmm_slices.hip).
 //
-// Measured: CSR order, 169,343 rows, 1.17 M entries: 64 features 97 -> 53 us (50 on the same operands again), 32: 91 -> 27, 128:
+// Measured: CSR order, 169,343 rows, 1.17 M entries: 64 features 97 -> 52 us (50 on the same operands again), 32: 91 -> 27, 128:
 // 127 -> 102 (5.8 TB/s of gathered rows, all beyond L2); 41 features, 1.5 M entries 612 -> 47 us; 2,708 rows 42 -> 7 us, most of
-// which is the call.  With a plan, 232,965 rows, 114.6 M entries, 128 features: 3.56 -> 3.46 -> 2.56 ms (with the slices); 20 M entries, 53 features
-// 3.20 -> 0.55 ms.
+// which is the call.  With a plan, 232,965 rows, 114.6 M entries, 128 features: 3.46 ms, with the slices 2.64, with the
+// lists read past L2 and X staged 2.46; 20 M entries, 53 features 3.20 -> 0.55 ms.
 #include <string.h>
 
 #include <algorithm>

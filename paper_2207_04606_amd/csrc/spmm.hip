@@ -9,7 +9,7 @@
 // every chunk of the row block's list (all column partitions of the launch, the
 // rows of all ELL buckets and the remainder, real entries only) and finally
 // writes the Y tile with plain coalesced stores.
-// Nothing is shared between wavefronts: no atomics, no barriers, no zero fill
+// Nothing else is shared between wavefronts: no atomics, no barriers, no zero fill
 // of Y, and rows without non-zeros come out as 0 (the init block of the SpMM
 // script in appendix A).
 //
@@ -34,6 +34,9 @@
 // rounds) are summed by k_spmm_heavy: their chunks form one sequence in
 // partition order, cut into lists of 16 chunks, a wavefront each, which leave
 // partial sums in memory; k_heavy_reduce adds them to Y in a fixed order.
+// Rows with entries in every slice of columns that fits LDS are in neither:
+// spmm_slices.hip sums them last and overwrites their rows of Y.  On a small
+// graph the wavefronts of a workgroup share a list (k_spmm_hyb_shared).
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
