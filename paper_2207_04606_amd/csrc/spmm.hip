@@ -783,15 +783,18 @@ void launch_lists(V, const Geometry& g, size_t lds_bytes, hipStream_t stream, co
   hipLaunchKernelGGL(kernel, dim3((unsigned)g.grid), dim3(kHybBlock), lds_bytes, stream, a);
 }
 
+// (small graphs: offsets of 32 bits, and no whole 512-byte runs of X; compiled for nothing else)
 template <typename V>
 void launch_shared_lists(V, const Geometry& g, int waves, size_t lds_bytes, hipStream_t stream, const SpmmArgs& a) {
-  auto* kernel = &k_spmm_hyb_shared<V::vec, V::lg, V::idx32, V::wide, V::unit>;
-  static std::once_flag raised;
-  std::call_once(raised, [&] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              160 * 1024 - 1024);
-  });
-  hipLaunchKernelGGL(kernel, dim3((unsigned)g.grid), dim3(64 * (unsigned)waves), lds_bytes, stream, a);
+  if constexpr (V::idx32 && V::lg <= 16) {
+    auto* kernel = &k_spmm_hyb_shared<V::vec, V::lg, true, V::wide, V::unit>;
+    static std::once_flag raised;
+    std::call_once(raised, [&] {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                160 * 1024 - 1024);
+    });
+    hipLaunchKernelGGL(kernel, dim3((unsigned)g.grid), dim3(64 * (unsigned)waves), lds_bytes, stream, a);
+  }
 }
 
 // Wavefronts per chunk list: 1, or 2 to 8 that share one (k_spmm_hyb_shared).  n_lists lists of n_quads quads in all, over the
@@ -1084,9 +1087,10 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
       if (!plan_tiles(n_units, &g)) return SPTIR_ERR_OVERFLOW;
       // (where the column partitions take several launches, lists are shared in none of them: 21,104 rows, 2.2 M entries, 32
       //  features, two launches 30 us, 45 with two wavefronts a list)
-      const int waves = h->n_phases > 1 ? 1 : shared_list_waves((int64_t)h->n_row_blocks * g.n_tiles,
-                                                                h->heavy_chunk0 / kChunksPerQuad * g.n_tiles,
-                                                                h->longest_list, g.lg, lds_bytes / kHybWaves);
+      const bool may_share = h->n_phases == 1 && idx32 && g.lg <= 16;
+      const int waves = !may_share ? 1 : shared_list_waves((int64_t)h->n_row_blocks * g.n_tiles,
+                                                           h->heavy_chunk0 / kChunksPerQuad * g.n_tiles,
+                                                           h->longest_list, g.lg, lds_bytes / kHybWaves);
       Geometry gs = g;
       if (waves > 1 && !plan_tiles(h->n_row_blocks, &gs)) return SPTIR_ERR_OVERFLOW;
       a.n_tiles = g.n_tiles; a.tile0 = tile0; a.map_mode = g.map_mode; a.map_param = g.map_param;  // (of gs as well)
