@@ -17,7 +17,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("wide", [0, 1])
 def test_shared_lists(gpu_lib, feat, one_value, wide):
     for n_rows, n_cols, kind in ((1, 300, "rows"), (9, 2100, "rows"), (300, 2100, "rows"), (500, 900, "even"), (2000, 900, "even"),
-                                 (700, 6000, "one")):
+                                 (700, 6000, "one"),
+                                 (300, 165_000, "rows"), (900, 165_000, "even")):   # 16 lanes a group from 41 features on
+        if n_cols > 100_000 and feat not in (41, 100):
+            continue
         say(f"[shared lists] feat={feat} one_value={one_value} wide={wide} {n_rows}x{n_cols} {kind}")
         rng = np.random.default_rng(n_rows + feat)
         deg = rng.integers(0, 9, n_rows)
