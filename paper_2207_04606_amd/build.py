@@ -29,10 +29,8 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "sptir_internal.h"), os.path.join(CSRC, "sptir_scan.h"),
-                        os.path.join(CSRC, "sptir_tiles.h"), os.path.join(CSRC, "sddmm_lanes.h"),
-                        os.path.join(CSRC, "sptir_sort.h"),
-                        os.path.join(ROOT, "include", "sptir.h")]
+    headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
+    deps = sources() + headers + [os.path.join(ROOT, "include", "sptir.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 

@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "sddmm_lanes.h"
+#include "sddmm_slice_shape.h"
 #include "sptir_internal.h"
 #include "sptir_scan.h"
 #include "sptir_tiles.h"
@@ -29,7 +30,6 @@
 namespace sptir {
 namespace {
 
-constexpr int kSliceBytes = 155 * 1024;  // of Yt in LDS; one workgroup a CU (two of 64 KB: 6 % slower, pieces half as long)
 // Rows are long from kMinPiece entries per slice on.  232,965 rows, 114.6 M entries, the call: 2 2645 us, 3 2636, 5 2695, none 3464.
 constexpr int64_t kMinPiece = 3;
 constexpr int64_t kMinUnits = 2048;
@@ -37,7 +37,6 @@ constexpr int64_t kPartBytes = 1 << 20;  // rows of X of a part (2 MB: 1 % slowe
 constexpr int64_t kMinUnitNnz = 4096;    // entries that pay for loading a slice
 constexpr int kSegment = 8;             // entries of a segment
 constexpr int kClasses = 8;             // full segments, then those of 7 .. 1 entries
-constexpr int kColumnBits = 13;         // of a column inside its slice (4 floats: 8192 columns)
 
 struct SliceArgs {
   const int4* units;       // slice, first segment, end of segments
@@ -70,10 +69,6 @@ __device__ __forceinline__ int column_of(const uint4& c, int u) {
   const unsigned w = u < 2 ? c.x : (u < 4 ? c.y : (u < 6 ? c.z : c.w));
   return (int)((u & 1) ? w >> 16 : w & 0xFFFFu);
 }
-
-// Row to row in LDS: where all rows would begin in the same half of the 64 banks, half a row of banks more, or the lane groups
-// meet in it (random 512-byte rows: 75 TB/s, 83 if half of them begin in the other half).
-constexpr __host__ __device__ int slice_stride(int quads) { return quads % 16 == 0 ? quads + 8 : quads; }
 
 template <int T> constexpr int slice_threads() { return T <= 4 ? 1024 : 512; }
 
@@ -186,8 +181,7 @@ __global__ __launch_bounds__(slice_threads<T>()) void k_sddmm_slices(SliceArgs a
   }
 }
 
-// The same segments where a call has more features than the plan's slices have room for, or fewer than four: rows of Yt
-// from memory, 256 features at a time.
+// The same segments for the calls that slice_lane_quads() gives no LDS kernel: rows of Yt from memory, 256 features at a time.
 __global__ __launch_bounds__(512) void k_sddmm_segments(SliceArgs a) {
   constexpr int T = 8, kGroups = 64;
   const int lane = threadIdx.x & 63, g = lane >> 3, fl = lane & 7;
@@ -367,11 +361,6 @@ int64_t min_entries(int64_t feat) {
   return (feat <= 64 || feat % 4 ? (int64_t)1 << 29 : (int64_t)1 << 27) / feat;
 }
 
-int32_t slice_width(int64_t feat) {
-  if (feat > 256) return 0;
-  return (int32_t)std::min<int64_t>(kSliceBytes / (16 * slice_stride((int)(feat + 3) / 4)), 1 << kColumnBits);
-}
-
 }  // namespace
 
 void sddmm_slices_free(SddmmSlices* s, sptir_free_fn free_, void* actx) {
@@ -518,20 +507,18 @@ sptir_status_t sddmm_slices_run(const SddmmSlices& s, int32_t n_cols, const floa
   a.feat = feat; a.quads = (feat + 3) / 4; a.stride = slice_stride(a.quads); a.width = s.width; a.n_cols = n_cols;
   const unsigned n = (unsigned)s.n_units;
   hipError_t e;
-  if (feat < 4 || (int64_t)s.width * a.stride * 16 > kSliceBytes) {
-    hipLaunchKernelGGL(k_sddmm_segments, dim3(n), dim3(512), 0, stream, a);
-    e = hipGetLastError();
-  } else {
-    switch ((feat + 31) / 32) {
-      case 1: e = launch_rows<1>(a, n, stream); break;
-      case 2: e = launch_rows<2>(a, n, stream); break;
-      case 3: e = launch_rows<3>(a, n, stream); break;
-      case 4: e = launch_rows<4>(a, n, stream); break;
-      case 5: e = launch_rows<5>(a, n, stream); break;
-      case 6: e = launch_rows<6>(a, n, stream); break;
-      case 7: e = launch_rows<7>(a, n, stream); break;
-      default: e = launch_rows<8>(a, n, stream);
-    }
+  switch (slice_lane_quads(s.width, feat)) {
+    case 1: e = launch_rows<1>(a, n, stream); break;
+    case 2: e = launch_rows<2>(a, n, stream); break;
+    case 3: e = launch_rows<3>(a, n, stream); break;
+    case 4: e = launch_rows<4>(a, n, stream); break;
+    case 5: e = launch_rows<5>(a, n, stream); break;
+    case 6: e = launch_rows<6>(a, n, stream); break;
+    case 7: e = launch_rows<7>(a, n, stream); break;
+    case 8: e = launch_rows<8>(a, n, stream); break;
+    default:
+      hipLaunchKernelGGL(k_sddmm_segments, dim3(n), dim3(512), 0, stream, a);
+      e = hipGetLastError();
   }
   if (e != hipSuccess) return note_hip_error(e, "sddmm slices");
   return SPTIR_OK;

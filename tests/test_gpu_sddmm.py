@@ -207,7 +207,8 @@ def matrix_with_long_rows(n_rows, n_long, n_cols, seed, feat):
 
 @pytest.mark.parametrize("hint,feat", [(36, 36), (41, 41), (64, 64), (96, 96), (97, 97), (128, 128), (131, 131), (160, 160), (192, 192),
                                        (224, 224), (250, 250), (255, 255), (256, 256),
-                                       (128, 3), (128, 20), (128, 64), (128, 132), (128, 300)])
+                                       (128, 3), (128, 20), (128, 64), (128, 132), (128, 300),
+                                       (253, 257), (256, 257), (256, 260), (256, 272), (256, 288), (256, 289)])
 def test_sddmm_plan_takes_long_rows_in_column_slices(gpu_lib, hint, feat):
     """Rows with entries in every slice of columns, next to short and empty ones; pieces of full segments, of every
     remainder, and none; the last slice narrower; also calls with fewer and more features than the slices were made for."""
