@@ -212,7 +212,9 @@ typedef struct {
                                  the tiles bound to XCDs; 2: never.  Never chosen: it measured slower on every
                                  workload tried (the option stays so that the comparison can be repeated) */
   int32_t column_slices;      /* rows with entries in every slice of columns whose rows of X (a tile of 16 features) fit a
-                                 workgroup's LDS, summed from there: 0: chosen; 1: all that are long enough; 2: none */
+                                 workgroup's LDS, summed from there: 0: chosen (also none where rows of like length have
+                                 their entries in different slices, or where there is no memory for them); 1: all that
+                                 are long enough; 2: none */
 } sptir_build_options_t;
 
 sptir_status_t sptir_hyb_build_ex(const sptir_csr_t* csr, int32_t n_col_parts, int32_t max_bucket_log2,

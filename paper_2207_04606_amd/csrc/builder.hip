@@ -1553,7 +1553,26 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       n_long += (int64_t)(report1.flags[slot * kFlagStride + 7] >> 32);
       long_nnz += (int64_t)(uint32_t)report1.flags[slot * kFlagStride + 7];
     }
+    // Without slices after all: `st` says why, nothing that uses their memory is running.  No build ends here for their sake
+    // unless the caller has asked for them.
+    auto no_slices = [&]() {
+      scratch_free(h->slices.blob, free_, actx);
+      h->slices = SpmmSlices();
+      spmm_slices_done(&slice_build, free_, actx);
+      min_deg = INT32_MAX; n_long = 0;
+      st = SPTIR_OK;
+    };
+    auto slices_or_none = [&]() {  // false: the build fails
+      if (st == SPTIR_OK) return true;
+      if (opt.column_slices == 1 || (st != SPTIR_ERR_ALLOC && st != SPTIR_ERR_OVERFLOW)) return false;
+      no_slices();
+      return true;
+    };
     if (!use_slices(opt, cs.long_len, s.c, longest_row, long_nnz)) { min_deg = INT32_MAX; n_long = 0; }
+    if (n_long > 0) {
+      st = spmm_slices_count(&slice_build, csr, min_deg, (int32_t)n_long, longest_row, alloc, actx, stream);
+      if (!slices_or_none()) goto fail;
+    }
     if (!with_spmm_plan) cs.n_rb = 0;  // no row blocks, no cells, no chunks: only the canonical arrays are built
     h->spmm_plan = with_spmm_plan ? 1 : 0;
     h->log2_row_block = cs.log2_rb; h->n_row_blocks = cs.n_rb;
@@ -1586,7 +1605,6 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     uint32_t* d_dealt = (uint32_t*)(tmp2.base + o_dealt);
     unsigned long long* d_unit = (unsigned long long*)(tmp2.base + o_unit);
     HeavySums sums;
-    sums.not_taken = n_long > 0 ? d_flags + kValidationWords : nullptr;
     sums.units = (long long*)(tmp2.base + o_spans); sums.slots = sums.units + n_spans; sums.entries = sums.slots + n_spans;
 
     // ---- the handle's device arrays whose sizes are known now: two allocations (cols and vals can be released
@@ -1624,6 +1642,21 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
     }
     BUILD_HIP(hipMemcpyAsync(h->blobs[0], host.base + h_small, small_bytes, hipMemcpyHostToDevice, stream));
 
+    // ---- do the long rows go to column slices?  (Their lengths alone do not say how far the steps are padded.)
+    if (n_long > 0) {
+      BUILD_HIP(hipStreamSynchronize(stream));
+      if (opt.column_slices != 1 && !spmm_slices_even(slice_build, long_nnz)) {
+        no_slices();
+      } else {
+        st = spmm_slices_plan(&slice_build, opt.feat_hint, !one_value_per_row, &h->slices, alloc, actx, stream);
+        h->blobs[3] = h->slices.blob;
+        if (!slices_or_none()) goto fail;
+      }
+      h->blobs[3] = h->slices.blob;  // (none: NULL)
+      h->device_bytes += h->slices.device_bytes;
+    }
+    sums.not_taken = n_long > 0 ? d_flags + kValidationWords : nullptr;
+
     // ---- stable placement
     if (s.NB > 0) {
       PlaceArgs a;
@@ -1658,10 +1691,6 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       hipLaunchKernelGGL(k_group_scan, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, stream, cs, n_groups,
                          d_cell_chunks, d_group_tot);
     }
-    if (n_long > 0) {
-      st = spmm_slices_count(&slice_build, csr, min_deg, (int32_t)n_long, longest_row, alloc, actx, stream);
-      if (st != SPTIR_OK) goto fail;
-    }
     hipLaunchKernelGGL(k_totals, dim3(4), dim3(kOneBlock), 0, stream, n_cells > 0 ? n_groups : 0, d_group_tot, n_spans,
                        sums, (long long*)(host.base + h_report2));
     BUILD_HIP(hipGetLastError());
@@ -1692,10 +1721,8 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       h->whole_partial_rows = h->n_heavy + report2[5] + (chunks + per_list - 1) / per_list;
     }
     if (n_long > 0) {
-      st = spmm_slices_fill(&slice_build, csr, opt.feat_hint, !one_value_per_row, &h->slices, alloc, actx, stream);
-      h->blobs[3] = h->slices.blob;
-      h->device_bytes += h->slices.device_bytes;
       h->slices.nnz = long_nnz;
+      st = spmm_slices_fill(slice_build, csr, h->slices, stream);
       if (st != SPTIR_OK) goto fail;
     }
     h->partial_feat = h->n_partial_rows <= kWidePartialRows ? kWidePartialFeat : kPartialFeat;

@@ -37,6 +37,13 @@ constexpr int kBlockRows = 64 / kLanes;
 constexpr int kMaxBlocksPerWave = 8;                    // sums: 4 registers each
 constexpr int kMaxPanelBlocks = kWavesHere * kMaxBlocksPerWave;
 constexpr int kAhead = 2;                               // steps between the request for one and its use
+// Most slots walked per entry (8 x 16 a step).  A block takes as many steps in a slice as its longest row there, and its rows have
+// nothing in common but their length: 1.1 to 1.45 where columns are close to uniform or fall in popularity, 4 to 9 where rows
+// have 30 to 80 % of their entries in one of 50 ranges of columns (232,965 rows, 80 %: 2.1 ms a product without slices, 6.2 with).
+// At 2 the entries take as many bytes as in the stream.  80 drawn graphs, 3 to 25 % of a row's entries in such a range or all in
+// a band, products against no slices: up to 1.5 slots 1.65 times as fast (0.86 to 3.2), to 2 1.49 (0.93 to 3.0; 1.0 and more from 12 M
+// long entries on), to 2.5 1.33 (0.79 to 3.2), to 3.7 1.06 (0.6 to 2.5).
+constexpr double kMostSlotsPerEntry = 2.0;
 constexpr size_t kSliceLds = sizeof(float4) * kLanes * (kSliceCols + 1);
 
 struct Unit {
@@ -433,7 +440,7 @@ size_t up(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 
 int64_t slice_min_degree(int32_t n_cols) { return std::max<int64_t>(kChunkSlots, (int64_t)kMinSlicePiece * n_cols / kSliceCols); }
 
-// First half of the build: everything up to the numbers of steps, which land in b->host; only enqueues work.
+// First part of the build: everything up to the numbers of steps, which land in b->host; only enqueues work.
 sptir_status_t spmm_slices_count(SpmmSliceBuild* b, const sptir_csr_t* csr, int32_t min_deg, int32_t n_long, int64_t longest,
                                  sptir_alloc_fn alloc, void* actx, hipStream_t stream) {
   b->n_long = n_long;
@@ -462,14 +469,24 @@ sptir_status_t spmm_slices_count(SpmmSliceBuild* b, const sptir_csr_t* csr, int3
   return SPTIR_OK;
 }
 
-// Second half, once the stream has been waited for: panels, units and the handle's arrays.  The host side of `b` has to stay until
-// the stream has drained.
-sptir_status_t spmm_slices_fill(SpmmSliceBuild* b, const sptir_csr_t* csr, int32_t feat_hint, bool with_values, SpmmSlices* out,
-                                sptir_alloc_fn alloc, void* actx, hipStream_t stream) try {
+// The steps that were counted, once the stream has been waited for
+int64_t spmm_slices_steps(const SpmmSliceBuild& b) {
+  const int32_t* block_steps = (const int32_t*)b.host.p;
+  int64_t n_steps = 0;
+  for (int32_t i = 0; i < b.n_blocks; ++i) n_steps += block_steps[i];
+  return n_steps;
+}
+
+bool spmm_slices_even(const SpmmSliceBuild& b, int64_t long_nnz) {
+  return (double)spmm_slices_steps(b) * (8 * kBlockRows) <= kMostSlotsPerEntry * (double)long_nnz;
+}
+
+// Then: panels, units and the handle's memory.  Host work only; where it does not succeed nothing has been enqueued.
+sptir_status_t spmm_slices_plan(SpmmSliceBuild* b, int32_t feat_hint, bool with_values, SpmmSlices* out, sptir_alloc_fn alloc,
+                                void* actx, hipStream_t stream) try {
   const int32_t* block_steps = (const int32_t*)b->host.p;
   const int32_t* slice_steps = block_steps + b->n_blocks;
-  int64_t n_steps = 0;
-  for (int32_t i = 0; i < b->n_blocks; ++i) n_steps += block_steps[i];
+  const int64_t n_steps = spmm_slices_steps(*b);
   if (n_steps + kAhead > 0x3FFFFFFF) return SPTIR_ERR_OVERFLOW;
   // In units of what a step costs where LDS binds (8 KB): loading a slice, and the steps of a panel in a slice that outweigh it,
   // fewer where there would not be enough units for every CU (9,306 rows, 4.6 M entries, 32 features: 81 us with 2048, 34 with this)
@@ -544,35 +561,39 @@ sptir_status_t spmm_slices_fill(SpmmSliceBuild* b, const sptir_csr_t* csr, int32
   for (size_t i = 0; i < ranked.size(); ++i) memcpy(t + sizeof(Unit) * i, &ranked[i].u, sizeof(Unit));
   memcpy(t + up(table_sizes[0]), panels.data(), table_sizes[1]);
   memcpy(t + up(table_sizes[0]) + up(table_sizes[1]), panel_of.data(), table_sizes[2]);
-  SPTIR_HIP(hipMemcpyAsync(base, t, table_bytes, hipMemcpyHostToDevice, stream));
-  const Panel* d_panels = (const Panel*)(base + up(table_sizes[0]));
-  const int32_t* d_panel_of = (const int32_t*)(base + up(table_sizes[0]) + up(table_sizes[1]));
-  int32_t *step_of = (int32_t*)(base + o_words), *first_step = (int32_t*)(base + o_first);
-  uint4* cols = (uint4*)(base + o_cols);
-  float4* vals = with_values ? (float4*)(base + o_vals) : nullptr;
+  b->n_steps = n_steps; b->words = words; b->table_bytes = table_bytes;
+  b->first_step = (int32_t*)(base + o_first); b->seq_base = (int32_t*)(base + o_seq);
+  out->n_long = b->n_long; out->n_units = (int32_t)ranked.size(); out->n_slices = b->n_slices;
+  out->units = base; out->panels = base + up(table_sizes[0]);
+  out->panel_of = (const int32_t*)(base + up(table_sizes[0]) + up(table_sizes[1]));
+  out->rows = (int32_t*)(base + o_rows); out->step_of = (int32_t*)(base + o_words);
+  out->cols = (uint4*)(base + o_cols); out->vals = with_values ? (float4*)(base + o_vals) : nullptr;
+  out->partial = (float*)(base + o_partial);
+  return SPTIR_OK;
+} catch (const std::bad_alloc&) {  // (the tables of units and panels)
+  return SPTIR_ERR_ALLOC;
+}
+
+// Last: the contents of the handle's arrays.  The host side of `b` has to stay until the stream has drained.
+sptir_status_t spmm_slices_fill(const SpmmSliceBuild& b, const sptir_csr_t* csr, const SpmmSlices& s, hipStream_t stream) {
+  SPTIR_HIP(hipMemcpyAsync(s.blob, b.tables.p, b.table_bytes, hipMemcpyHostToDevice, stream));
   FillArgs f;
-  f.n = (int64_t)b->n_blocks * b->n_slices; f.nnz = csr->nnz; f.n_steps = n_steps;
-  f.n_slices = b->n_slices; f.room = (int32_t)room; f.n_long = b->n_long;
-  f.panels = d_panels; f.panel_of = d_panel_of; f.count = b->count; f.first_step = first_step; f.bound = b->bound;
-  f.order = b->order; f.indices = csr->indices; f.values = csr->values;
-  f.step_of = step_of; f.rows = (int32_t*)(base + o_rows); f.cols = cols; f.vals = vals;
-  hipLaunchKernelGGL(k_order_steps, dim3((unsigned)((f.n + 255) / 256)), dim3(256), 0, stream, f.n, b->n_slices, d_panels,
-                     d_panel_of, b->count, first_step);
-  if (words <= kScanOneMost) {
-    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanThreads), 0, stream, first_step, (int32_t)words);
+  f.n = (int64_t)b.n_blocks * b.n_slices; f.nnz = csr->nnz; f.n_steps = b.n_steps;
+  f.n_slices = b.n_slices; f.room = b.n_blocks * kBlockRows; f.n_long = b.n_long;
+  f.panels = (const Panel*)s.panels; f.panel_of = s.panel_of; f.count = b.count; f.first_step = b.first_step; f.bound = b.bound;
+  f.order = b.order; f.indices = csr->indices; f.values = csr->values;
+  f.step_of = s.step_of; f.rows = s.rows; f.cols = s.cols; f.vals = s.vals;
+  hipLaunchKernelGGL(k_order_steps, dim3((unsigned)((f.n + 255) / 256)), dim3(256), 0, stream, f.n, b.n_slices, f.panels,
+                     f.panel_of, b.count, b.first_step);
+  if (b.words <= kScanOneMost) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanThreads), 0, stream, b.first_step, (int32_t)b.words);
   } else {
-    const sptir_status_t st = device_exclusive_scan(first_step, words, (int32_t*)(base + o_seq), stream);
+    const sptir_status_t st = device_exclusive_scan(b.first_step, b.words, b.seq_base, stream);
     if (st != SPTIR_OK) return st;
   }
   hipLaunchKernelGGL(k_fill_steps, dim3((unsigned)((f.n * 64 + 255) / 256)), dim3(256), 0, stream, f);
   SPTIR_HIP(hipGetLastError());
-  out->n_long = b->n_long; out->n_units = (int32_t)ranked.size(); out->n_slices = b->n_slices;
-  out->units = base; out->panels = d_panels; out->panel_of = d_panel_of;
-  out->rows = (const int32_t*)(base + o_rows); out->step_of = step_of;
-  out->cols = cols; out->vals = vals; out->partial = (float*)(base + o_partial);
   return SPTIR_OK;
-} catch (const std::bad_alloc&) {  // (the tables of units and panels)
-  return SPTIR_ERR_ALLOC;
 }
 
 void spmm_slices_done(SpmmSliceBuild* b, sptir_free_fn free_, void* actx) {

@@ -46,9 +46,10 @@ struct SpmmSlices {
   void* blob = nullptr;               // one allocation that holds all of it
   size_t device_bytes = 0;
   const void *units = nullptr, *panels = nullptr;
-  const int32_t *panel_of = nullptr, *rows = nullptr, *step_of = nullptr;
-  const uint4* cols = nullptr;
-  const float4* vals = nullptr;
+  const int32_t* panel_of = nullptr;
+  int32_t *rows = nullptr, *step_of = nullptr;
+  uint4* cols = nullptr;
+  float4* vals = nullptr;
   float* partial = nullptr;           // partial sums of kPartialFeat features
 };
 }  // namespace sptir
@@ -209,17 +210,22 @@ void sddmm_slices_free(SddmmSlices* s, sptir_free_fn free_, void* actx);
 sptir_status_t sddmm_slices_run(const SddmmSlices& s, int32_t n_cols, const float* values, const float* X, const float* Yt, float* B,
                                 int32_t feat, hipStream_t stream);
 
-struct SpmmSliceBuild {               // between the two halves of the build
+struct SpmmSliceBuild {               // between the parts of the build
   int32_t n_long = 0, n_blocks = 0, n_slices = 0;
   void* temporary = nullptr;
   int32_t *bound = nullptr, *count = nullptr, *order = nullptr;
   PinnedBuf host, tables;
+  int64_t n_steps = 0, words = 0;
+  size_t table_bytes = 0;
+  int32_t *first_step = nullptr, *seq_base = nullptr;
 };
 int64_t slice_min_degree(int32_t n_cols);
 sptir_status_t spmm_slices_count(SpmmSliceBuild* b, const sptir_csr_t* csr, int32_t min_deg, int32_t n_long, int64_t longest,
                                  sptir_alloc_fn alloc, void* actx, hipStream_t stream);
-sptir_status_t spmm_slices_fill(SpmmSliceBuild* b, const sptir_csr_t* csr, int32_t feat_hint, bool with_values, SpmmSlices* out,
-                                sptir_alloc_fn alloc, void* actx, hipStream_t stream);
+bool spmm_slices_even(const SpmmSliceBuild& b, int64_t long_nnz);
+sptir_status_t spmm_slices_plan(SpmmSliceBuild* b, int32_t feat_hint, bool with_values, SpmmSlices* out, sptir_alloc_fn alloc,
+                                void* actx, hipStream_t stream);
+sptir_status_t spmm_slices_fill(const SpmmSliceBuild& b, const sptir_csr_t* csr, const SpmmSlices& s, hipStream_t stream);
 void spmm_slices_done(SpmmSliceBuild* b, sptir_free_fn free_, void* actx);
 sptir_status_t spmm_slices_gather(const SpmmSlices& s, int32_t n_cols, const float* X, int32_t feat, int32_t feat0, int32_t width,
                                   hipStream_t stream);

@@ -13,6 +13,7 @@ from test_gpu_stream import decode
 
 pytestmark = pytest.mark.gpu
 SLICE, PIECE, LEAST = 2496, 8, 64     # columns of a slice, entries per slice and entries from which on a row is long
+ERR_ALLOC = 4
 
 
 def matrix(n_rows, n_cols, n_long, feat, seed, one_value):
@@ -91,3 +92,98 @@ def test_rows_of_x_that_are_not_finite_stay_with_their_rows(gpu_lib, one_value):
     for col, f in ((17, 3), (2495, 0), (3999, 19)):
         want[rows[w.indices == col], f] = False
     assert np.array_equal(got[long_rows], want[long_rows])
+
+
+def large_matrix(n_rows, share, n_cols=40000, n_groups=10, deg=1600, feat=8):
+    """Rows of like length, a few longer; `share` of a row's entries in one of n_groups ranges of columns, the others anywhere."""
+    rng = np.random.default_rng(n_rows)
+    lens = rng.integers(deg - 60, deg, n_rows)
+    lens[rng.choice(n_rows, 5, replace=False)] = 5 * deg
+    width = n_cols // n_groups
+    inside = np.minimum((share * lens).astype(np.int64), width * 7 // 8)
+    a = workloads.random_csr(n_rows, width, inside, 1, feat)
+    b = workloads.random_csr(n_rows, n_cols, lens - inside, 2, feat)
+    row_of = lambda w: np.repeat(np.arange(n_rows, dtype=np.int64), np.diff(w.indptr))
+    ra, rb = row_of(a), row_of(b)
+    key = np.unique(np.concatenate([ra * n_cols + ra % n_groups * width + a.indices, rb * n_cols + b.indices]))
+    rows = key // n_cols
+    w = b
+    w.indptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n_rows))]).astype(np.int32)
+    w.indices = (key - rows * n_cols).astype(np.int32)
+    w.values = rng.standard_normal(key.size).astype(np.float32)
+    return w
+
+
+def build_and_multiply(sptir, w, d, options):
+    hyb = sptir.sptir_hyb_build_ex(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, 2, 7, options)
+    Y = torch.full((w.n_rows, w.X.shape[1]), float("nan"), device="cuda")
+    sptir.sptir_spmm(hyb, d.X, Y)
+    info, n_long = sptir.sptir_hyb_info(hyb), sptir.sptir_hyb_array(hyb, "plan_long_rows").size
+    hyb.destroy()
+    return Y, info, n_long
+
+
+@pytest.mark.parametrize("share", [0.0, 0.3, 0.8])
+def test_slices_only_where_a_block_of_rows_is_alike(gpu_lib, share):
+    """Where rows have their entries in ranges of their own, a block's steps are those of a different row in every slice:
+    such a graph is built as without column slices, unless they are asked for."""
+    sptir = gpu_lib
+    w = large_matrix(9000, share)
+    say(f"[long rows] share={share} nnz={w.indices.size}")
+    assert w.indices.size > 12_700_000
+    d = upload(w)
+    Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    sptir.sptir_release_scratch()
+    plain, plain_info, none = build_and_multiply(sptir, w, d, {"column_slices": 2})
+    assert none == 0
+    sptir.sptir_release_scratch()
+    Y, info, n_long = build_and_multiply(sptir, w, d, {})
+    assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"share {share}")
+    if share == 0:
+        assert n_long == w.n_rows
+    else:
+        assert n_long == 0 and torch.equal(Y, plain)
+        assert {k: v for k, v in info.items() if k != "device_bytes"} == \
+               {k: v for k, v in plain_info.items() if k != "device_bytes"}
+        assert info["device_bytes"] <= 1.3 * plain_info["device_bytes"]      # (a kept block counts whole, up to a quarter larger)
+    Y, _, n_long = build_and_multiply(sptir, w, d, {"column_slices": 1})
+    assert n_long == w.n_rows
+    assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"share {share}, asked for")
+
+
+def test_slices_that_find_no_memory_are_left_out(gpu_lib):
+    """An allocation that only column slices ask for may fail: the build then does without them, unless the caller asked for
+    them.  (A caller's allocator that refuses one size, an error code and no GPU work.)"""
+    import ctypes
+    from paper_2207_04606_amd import binding
+    sptir = gpu_lib
+    w = large_matrix(9000, 0.0)
+    d = upload(w)
+    asked, refuse = [], set()
+
+    @binding._ALLOC_FN
+    def take(nbytes, ctx, stream):
+        asked.append(int(nbytes))
+        return None if int(nbytes) in refuse else binding._torch_alloc(nbytes, ctx, stream)
+
+    lib = sptir.load_library()
+    assert lib.sptir_set_allocator(take, binding._torch_free, None) == 0
+    try:
+        plain, _, _ = build_and_multiply(sptir, w, d, {"column_slices": 2})
+        without = set(asked)
+        asked.clear()
+        _, _, n_long = build_and_multiply(sptir, w, d, {})
+        assert n_long == w.n_rows
+        only = sorted(set(asked) - without, key=asked.index)[:2]   # the counts of steps, the handle's arrays of slices
+        assert len(only) == 2
+        before = len(binding._torch_blocks)
+        for size in only:
+            refuse = {size}
+            Y, _, n_long = build_and_multiply(sptir, w, d, {})
+            assert n_long == 0 and torch.equal(Y, plain), size
+            with pytest.raises(sptir.SptirError) as e:
+                build_and_multiply(sptir, w, d, {"column_slices": 1})
+            assert e.value.status == ERR_ALLOC
+        assert len(binding._torch_blocks) == before, "a build that failed keeps memory"
+    finally:
+        sptir.sptir_set_allocator(False)
