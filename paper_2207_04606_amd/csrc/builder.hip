@@ -1289,9 +1289,11 @@ int32_t heavy_len_setting(int64_t nnz, int32_t n_rows, int64_t n_row_blocks, int
 
 // Do the long rows leave lists and heavy pieces for column slices (spmm_slices.hip)?  Only where pieces leave the lists at all
 // and the longest row has one that does, so that no handle without heavy pieces comes to own partial sums; and from so many
-// entries on that a product wins what the build loses (some ten launches, 60 us; below 4 M entries products were 0.6 to 1.2 times as
-// fast, above 0.94 to 1.8 with 1.25 in the mean, a build and one product together 0.81 to 1.18).
-constexpr int64_t kMinSliceNnz = (int64_t)1 << 22;
+// entries on that a build and ONE product together win: slices cost a build some ten launches and a synchronisation, 50 to 150 us.
+// 86 graphs of uniform columns, 16 to 256 features, against column_slices = 2: 4.2 to 12.6 M long entries, build and product 0.94
+// times as fast in the mean (0.80 to 1.17; the product alone 1.20); to 16.8 M 1.05 (0.83 to 1.25; 1.45); beyond 1.24 (0.91 to 1.79;
+// 1.97).  A caller who multiplies often with fewer asks for them (column_slices = 1).
+constexpr int64_t kMinSliceNnz = (int64_t)3 << 22;
 bool use_slices(const sptir_build_options_t& opt, int32_t heavy_len, int32_t c, int64_t longest_row, int64_t long_nnz) {
   if (opt.no_spmm_plan || opt.column_slices == 2 || opt.full_rows == 1 || long_nnz == 0) return false;
   if (opt.column_slices == 1) return true;

@@ -151,6 +151,15 @@ def test_slices_only_where_a_block_of_rows_is_alike(gpu_lib, share):
     assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"share {share}, asked for")
 
 
+def test_few_long_entries_stay_in_the_stream(gpu_lib):
+    """A build and one product of so few entries take longer with column slices: they are left to callers who ask."""
+    w = large_matrix(5000, 0.0)
+    assert 6_000_000 < w.indices.size < 12_500_000
+    d = upload(w)
+    assert build_and_multiply(gpu_lib, w, d, {})[2] == 0
+    assert build_and_multiply(gpu_lib, w, d, {"column_slices": 1})[2] == w.n_rows
+
+
 def test_slices_that_find_no_memory_are_left_out(gpu_lib):
     """An allocation that only column slices ask for may fail: the build then does without them, unless the caller asked for
     them.  (A caller's allocator that refuses one size, an error code and no GPU work.)"""
