@@ -38,7 +38,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <mutex>
 #include <new>
 #include <type_traits>
 #include <utility>
@@ -563,10 +562,8 @@ int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) 
 template <int TIN, bool ORDERED, bool WIDE_X>
 void launch_rgms(dim3 grid, dim3 block, size_t lds, hipStream_t stream, const RgmsArgs& a) {
   auto* kernel = &k_rgms<TIN, ORDERED, WIDE_X>;
-  static std::once_flag raised;  // blocks of 512 rows need more than the default 64 KB of dynamic LDS
-  std::call_once(raised, [&] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  });
+  static OncePerDevice allowed;
+  allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, allowed);
   hipLaunchKernelGGL(kernel, grid, block, lds, stream, a);
 }
 

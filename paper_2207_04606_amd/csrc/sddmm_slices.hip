@@ -17,7 +17,6 @@
 // 232,965 rows, 114.6 M entries, 128 features: 70 M entries in 0.80 ms (11.4 ps an entry, 30 in k_sddmm; LDS busy 55 % and
 // vector ALU 57 % of it); segments not kept apart by range of rows 1.20 ms, slices dealt to the XCDs in turn 1.04 (twice the misses).
 #include <algorithm>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -339,11 +338,10 @@ __global__ __launch_bounds__(kBuildBlock) void k_fill_segments(int32_t n_long, i
 template <int T, bool TAIL>
 hipError_t launch(const SliceArgs& a, unsigned n_units, hipStream_t stream) {
   auto* kernel = &k_sddmm_slices<T, TAIL>;
-  static std::once_flag raised;  // more than the default 64 KB of dynamic LDS
-  std::call_once(raised, [&] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  });
-  hipLaunchKernelGGL(kernel, dim3(n_units), dim3(slice_threads<T>()), sizeof(float4) * ((size_t)a.width * a.stride + 1), stream, a);
+  const size_t lds = sizeof(float4) * ((size_t)a.width * a.stride + 1);
+  static OncePerDevice allowed;
+  allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, allowed);
+  hipLaunchKernelGGL(kernel, dim3(n_units), dim3(slice_threads<T>()), lds, stream, a);
   return hipGetLastError();
 }
 

@@ -775,11 +775,8 @@ void with_variant(int vec, int lg, bool idx32, bool wide, bool unit, F&& f) {
 template <typename V>
 void launch_lists(V, const Geometry& g, size_t lds_bytes, hipStream_t stream, const SpmmArgs& a) {
   auto* kernel = &k_spmm_hyb<V::vec, V::lg, V::idx32, V::wide, V::unit>;
-  static std::once_flag raised;  // row blocks of 256 rows need more than the default 64 KB of dynamic LDS
-  std::call_once(raised, [&] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              160 * 1024 - 1024);
-  });
+  static OncePerDevice allowed;
+  allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds_bytes, allowed);
   hipLaunchKernelGGL(kernel, dim3((unsigned)g.grid), dim3(kHybBlock), lds_bytes, stream, a);
 }
 
@@ -788,11 +785,8 @@ template <typename V>
 void launch_shared_lists(V, const Geometry& g, int waves, size_t lds_bytes, hipStream_t stream, const SpmmArgs& a) {
   if constexpr (V::idx32 && V::lg <= 16) {
     auto* kernel = &k_spmm_hyb_shared<V::vec, V::lg, true, V::wide, V::unit>;
-    static std::once_flag raised;
-    std::call_once(raised, [&] {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                160 * 1024 - 1024);
-    });
+    static OncePerDevice allowed;
+    allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds_bytes, allowed);
     hipLaunchKernelGGL(kernel, dim3((unsigned)g.grid), dim3(64 * (unsigned)waves), lds_bytes, stream, a);
   }
 }
@@ -832,11 +826,8 @@ template <typename V>
 void launch_heavy_and_lists(V, unsigned n_heavy_workgroups, unsigned n_list_workgroups, size_t lds_bytes,
                             hipStream_t stream, const SpmmArgs& a, const HeavyArgs& ha) {
   auto* kernel = &k_spmm_hyb_heavy<V::vec, V::lg, V::idx32, V::wide, V::unit>;
-  static std::once_flag raised;
-  std::call_once(raised, [&] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              160 * 1024 - 1024);
-  });
+  static OncePerDevice allowed;
+  allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds_bytes, allowed);
   hipLaunchKernelGGL(kernel, dim3(n_heavy_workgroups + n_list_workgroups), dim3(kHybBlock), lds_bytes, stream, a, ha,
                      n_heavy_workgroups);
 }

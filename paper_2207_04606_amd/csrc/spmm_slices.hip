@@ -20,7 +20,6 @@
 // in k_spmm_heavy), LDS busy 80 % of it, vector ALU 75 %; the rest is loading slices and wavefronts that wait there for the last.
 #include <algorithm>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -427,10 +426,8 @@ __global__ __launch_bounds__(256) void k_fill_steps(FillArgs a) {
 template <bool UNIT>
 void launch_gather(const SliceArgs& a, unsigned grid, hipStream_t stream) {
   auto* kernel = &k_spmm_slices<UNIT>;
-  static std::once_flag raised;  // more than the default 64 KB of dynamic LDS
-  std::call_once(raised, [&] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  });
+  static OncePerDevice allowed;
+  allow_dynamic_lds(reinterpret_cast<const void*>(kernel), kSliceLds, allowed);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), kSliceLds, stream, a);
 }
 

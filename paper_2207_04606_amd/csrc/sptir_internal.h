@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "per_device.h"
 #include "sptir.h"
 
 namespace sptir {
@@ -239,6 +240,17 @@ sptir_status_t order_rows_by_class(const int32_t* row_ptr, int32_t n_rows, int32
 
 // records a failed HIP call for sptir_last_hip_error(); returns SPTIR_ERR_HIP
 sptir_status_t note_hip_error(hipError_t e, const char* what);
+
+// A launch with more than the default 64 KB of dynamic LDS has to be allowed on the device it runs on, which is the current one.
+// (Where it cannot be, the launch says so.)
+inline void allow_dynamic_lds(const void* kernel, size_t lds_bytes, OncePerDevice& allowed) {
+  constexpr size_t kDefaultLds = 64 * 1024, kMostLds = 159 * 1024;  // (a kilobyte is for static arrays)
+  int device = 0;
+  if (lds_bytes <= kDefaultLds || hipGetDevice(&device) != hipSuccess) return;
+  allowed(device, [&] {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMostLds) == hipSuccess;
+  });
+}
 
 // text for sptir_last_hip_error() where a refusal needs more than its status code
 void note_error_text(const char* text);
