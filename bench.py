@@ -25,7 +25,6 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
-LDS_GATHER_GBS = 66000.0       # random 64-byte rows out of LDS, every CU at once (a microbenchmark; 128-byte rows 71 TB/s)
 GATHER_THEORY_GBS = 39300.0    # 256 CUs x 64 B/clk x 2.4 GHz: what the vector-memory return path could carry
 FMA_PEAK_TFLOPS = 157.3        # fp32 vector, published (plain v_fma_f32 measures ~129 here: the packed forms are not needed)
 
@@ -169,7 +168,7 @@ def read_traffic(key, fingerprint):
 def gather_roof(sptir, torch, dev, quick=True):
     """Measured rate of random 128-byte row gathers (the access every stored non-zero costs) for working sets that
     sit in L1, in one XCD's L2 (the case of the SpMM kernels: a partition's slice of one feature tile), in the
-    memory-side cache and in HBM, and over wavefronts per SIMD; plus the float32 FMA rate."""
+    memory-side cache and in HBM, and over wavefronts per SIMD; of random rows out of LDS; plus the float32 FMA rate."""
     rows_max = 1 << (18 if quick else 21)
     X = torch.zeros(rows_max, 128, device=dev)
     sink = torch.zeros(16, device=dev)
@@ -192,6 +191,13 @@ def gather_roof(sptir, torch, dev, quick=True):
                                        "gbs_at_1.86MB": round(run(14561, 4, wgs, 512), 1)})
     out["l2_resident_gbs"] = max(p["gbs_at_1.86MB"] for p in out["occupancy_sweep"])
     out["theory_gbs"] = GATHER_THEORY_GBS
+    # rows out of LDS, the case of the column slices: 64-byte rows are what k_spmm_slices reads, 512-byte rows a stride of
+    # 160 floats apart what k_sddmm_slices does at 128 features
+    out["lds_sweep"] = []
+    for row_floats, stride in ((16, 16), (128, 160)) if quick else ((4, 4), (8, 8), (16, 16), (16, 20), (32, 32), (128, 128), (128, 160)):
+        ms, nbytes = sptir.sptir_roof_lds_gather(row_floats, stride, 256, 1024 if row_floats == 128 else 4096, sink)
+        out["lds_sweep"].append({"row_bytes": 4 * row_floats, "stride_bytes": 4 * stride, "gbs": round(nbytes / ms / 1e6, 1)})
+    out["lds_64_byte_rows_gbs"] = next(p["gbs"] for p in out["lds_sweep"] if (p["row_bytes"], p["stride_bytes"]) == (64, 64))
     ms, flops = sptir.sptir_roof_fma(8192, 4096, sink)
     out["fma_tflops"] = round(flops / ms / 1e9, 2)
     return out
@@ -307,6 +313,7 @@ def main():
         sptir.sptir_set_allocator(False)
     build_cached_ms = sorted(cached_times[1:])[1]
     info = sptir.sptir_hyb_info(hyb)
+    n_long = int(sptir.sptir_hyb_array(hyb, "plan_long_rows").size)   # rows summed from column slices in LDS
 
     results = {}
     X_host_128 = None
@@ -360,7 +367,7 @@ def main():
         "hyb_build_ms": round(build_ms, 3), "hyb_build_first_call_ms": round(build_first_ms, 3),
         "hyb_build_caching_allocator_ms": round(build_cached_ms, 3),
         "hyb_build": {"ms": round(build_ms, 3), "ms_caching_allocator": round(build_cached_ms, 3),
-                      "host_synchronisations": 3, "algorithmic_bytes": bytes_build(info, w.nnz, w.n_rows),
+                      "host_synchronisations": 4 if n_long else 3, "algorithmic_bytes": bytes_build(info, w.nnz, w.n_rows),
                       "gbs": round(bytes_build(info, w.nnz, w.n_rows) / build_ms / 1e6, 1),
                       "frac_of_hbm_peak": round(bytes_build(info, w.nnz, w.n_rows) / build_ms / 1e6 / HBM_PEAK_GBS, 4),
                       "device_bytes": info["device_bytes"]},
@@ -372,7 +379,6 @@ def main():
     kt = head["kernels"]
     fingerprint = source_fingerprint()
     feat = 128
-    n_long = int(sptir.sptir_hyb_array(hyb, "plan_long_rows").size)   # rows summed from column slices in LDS
     from_lds = n_long > 0 and kt["ms_heavy"] >= kt["ms_lists"]
     if kt["ms_heavy"] >= kt["ms_lists"]:
         # (rows in column slices: k_spmm_slices, and k_spmm_heavy for the few pieces left)
@@ -409,15 +415,16 @@ def main():
         "sources": fingerprint,
     }
     # the path is a cache-served gather, not an HBM stream: each non-zero pulls feat*4 bytes of X through the
-    # vector-memory return path.  Its roof is measured here, on this GPU, by the library's microbenchmark.
+    # vector-memory return path or out of LDS.  Both roofs are measured here, on this GPU, by the library's microbenchmarks.
     roof = gather_roof(sptir, torch, dev, quick=True)
+    binding_gbs = roof["lds_64_byte_rows_gbs"] if from_lds else roof["l2_resident_gbs"]
     out["roofline"]["binding_roof"] = {
-        "name": "gather of 64-byte rows of X out of a CU's LDS (measured once)" if from_lds else
+        "name": "gather of 64-byte rows of X out of a CU's LDS" if from_lds else
                 "vector-memory gather of 128-byte rows of X out of an XCD's L2",
-        "roof_gbs": LDS_GATHER_GBS if from_lds else roof["l2_resident_gbs"],
+        "roof_gbs": binding_gbs,
         "kernel_gathered_gbs": round(gathered / ms / 1e6, 1),
         "measured_l2_resident_gbs": roof["l2_resident_gbs"], "theory_gbs": GATHER_THEORY_GBS,
-        "frac_of_measured": round(gathered / ms / 1e6 / (LDS_GATHER_GBS if from_lds else roof["l2_resident_gbs"]), 4),
+        "frac_of_measured": round(gathered / ms / 1e6 / binding_gbs, 4),
         "frac_of_theory": round(gathered / ms / 1e6 / GATHER_THEORY_GBS, 4),
         "whole_call_gathered_gbs": round(head["gather_gbs"], 1),
         "whole_call_frac_of_measured": round(head["gather_gbs"] / roof["l2_resident_gbs"], 4),

@@ -323,19 +323,23 @@ sptir_status_t sptir_spmm_timed(const sptir_hyb_t* hyb, const float* X, float* Y
                                 sptir_spmm_times_t* out);
 
 /*
- * The two on-chip roofs the SpMM kernels are priced against, measured on the current device (Section 4.2.1
+ * The on-chip roofs the SpMM and SDDMM kernels are priced against, measured on the current device (Section 4.2.1
  * names the cache hit rate of X as what column partitions buy; what a hit then costs is this gather rate).
  * sptir_roof_gather: every group of 8 lanes of n_workgroups x 4 wavefronts reads one 128-byte line (16 bytes a
  * lane, 8 loads in flight) of a random row of X[0 .. n_rows) (row_floats floats per row, 16-byte aligned),
  * iters x 8 times; `tiles` > 1 spreads the lines over that many 32-float feature tiles, bound to workgroup id
  * modulo 8 like the SpMM kernels bind tiles to XCDs.  *ms_out receives the time of one launch (after one
- * untimed launch), *bytes_out the bytes it gathered.  sptir_roof_fma: n_workgroups x 256 lanes issue iters x 8
+ * untimed launch), *bytes_out the bytes it gathered.  sptir_roof_lds_gather: the same out of LDS, the case of the column
+ * slices; n_workgroups of 1024 lanes (one to a CU) read rows of row_floats = 4, 8, 16, 32 or 128 floats at random, row_stride
+ * floats (a multiple of 4, up to 256) from one to the next, from as many of them, a power of two, as 156 KB hold.  sptir_roof_fma: n_workgroups x 256 lanes issue iters x 8
  * independent float32 FMAs; *flops_out receives 2 flops per FMA.  `sink` is a device float the kernels may
- * write (they all but never do).  Both create two events and synchronise `stream`.
+ * write (they all but never do).  All create two events and synchronise `stream`.
  */
 sptir_status_t sptir_roof_gather(const float* X, int64_t n_rows, int32_t row_floats, int32_t tiles,
                                  int32_t n_workgroups, int32_t iters, float* sink, void* stream, float* ms_out,
                                  double* bytes_out);
+sptir_status_t sptir_roof_lds_gather(int32_t row_floats, int32_t row_stride, int32_t n_workgroups, int32_t iters, float* sink,
+                                     void* stream, float* ms_out, double* bytes_out);
 sptir_status_t sptir_roof_fma(int32_t n_workgroups, int32_t iters, float* sink, void* stream, float* ms_out,
                               double* flops_out);
 

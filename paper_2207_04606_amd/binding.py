@@ -114,7 +114,7 @@ class _SpmmTimes(ctypes.Structure):
                 ("n_reduce_launches", ctypes.c_int32)]
 
 
-EXPORTED_SYMBOLS = ("sptir_spmm_timed", "sptir_roof_gather", "sptir_roof_fma", "sptir_set_allocator", "sptir_release_scratch", "sptir_hyb_build", "sptir_hyb_build_ex", "sptir_hyb_search", "sptir_default_bucket_log2", "sptir_gather_offsets_fit_32", "sptir_spmm",
+EXPORTED_SYMBOLS = ("sptir_spmm_timed", "sptir_roof_gather", "sptir_roof_lds_gather", "sptir_roof_fma", "sptir_set_allocator", "sptir_release_scratch", "sptir_hyb_build", "sptir_hyb_build_ex", "sptir_hyb_search", "sptir_default_bucket_log2", "sptir_gather_offsets_fit_32", "sptir_spmm",
                     "sptir_spmm_noalloc",
                     "sptir_spmm_csr", "sptir_sddmm_csr", "sptir_sddmm_plan_build", "sptir_sddmm",
                     "sptir_sddmm_plan_info", "sptir_sddmm_plan_destroy", "sptir_rgms_build", "sptir_rgms", "sptir_rgms_info",
@@ -151,6 +151,9 @@ def load_library(path: str | None = None):
     lib.sptir_roof_gather.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                       ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
                                       ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_double)]
+    lib.sptir_roof_lds_gather.restype = ctypes.c_int
+    lib.sptir_roof_lds_gather.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p,
+                                          ctypes.c_void_p, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_double)]
     lib.sptir_roof_fma.restype = ctypes.c_int
     lib.sptir_roof_fma.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
                                    ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_double)]
@@ -416,6 +419,17 @@ def sptir_roof_gather(X, n_rows: int, tiles: int, n_workgroups: int, iters: int,
                                           sink.data_ptr(), _stream_ptr(stream), ctypes.byref(ms), ctypes.byref(nbytes))
     if st != SPTIR_OK:
         raise SptirError(st, "sptir_roof_gather")
+    return float(ms.value), float(nbytes.value)
+
+
+def sptir_roof_lds_gather(row_floats: int, row_stride: int, n_workgroups: int, iters: int, sink, stream=None):
+    """(milliseconds, bytes gathered) of one launch of the microbenchmark of random rows out of LDS."""
+    _dev(sink, torch.float32, "sink")
+    ms = ctypes.c_float(0.0); nbytes = ctypes.c_double(0.0)
+    st = load_library().sptir_roof_lds_gather(row_floats, row_stride, n_workgroups, iters, sink.data_ptr(), _stream_ptr(stream),
+                                              ctypes.byref(ms), ctypes.byref(nbytes))
+    if st != SPTIR_OK:
+        raise SptirError(st, "sptir_roof_lds_gather")
     return float(ms.value), float(nbytes.value)
 
 

@@ -416,6 +416,21 @@ def test_timed_call_and_roof_microbenchmarks(gpu_lib):
             sptir.sptir_roof_gather(*bad, sink)
 
 
+@pytest.mark.parametrize("row_floats,stride", [(4, 4), (8, 256), (16, 16), (16, 20), (32, 32), (128, 128), (128, 160)])
+def test_lds_roof(gpu_lib, row_floats, stride):
+    """The microbenchmark of random rows out of LDS: the bytes it says it read, at a rate between one CU's share and twice
+    128 bytes a clock on all of them; rows that do not fit their stride are refused."""
+    sink = torch.zeros(4, device="cuda")
+    ms, nbytes = gpu_lib.sptir_roof_lds_gather(row_floats, stride, 256, 256, sink)
+    assert nbytes == 256 * 1024 * 256 * 8 * 16 * (4 if row_floats == 128 else 1)
+    assert ms > 0 and 1e3 < nbytes / ms / 1e6 < 157e3       # GB/s
+    assert float(sink.sum()) == 0.0
+    for bad in ((12, 12, 8, 8), (64, 64, 8, 8), (row_floats, row_floats - 4, 8, 8), (row_floats, stride + 1, 8, 8),
+                (row_floats, 260, 8, 8), (row_floats, stride, 0, 8), (row_floats, stride, 8, 0)):
+        with pytest.raises(gpu_lib.SptirError):
+            gpu_lib.sptir_roof_lds_gather(*bad, sink)
+
+
 def test_build_options_are_validated(gpu_lib):
     w = ragged_workload(1, 50, 60, 4, max_deg=20)
     d = upload(w)
