@@ -24,6 +24,7 @@
 #include "sddmm_slice_shape.h"
 #include "sptir_internal.h"
 #include "sptir_scan.h"
+#include "sptir_slice_bounds.h"
 #include "sptir_tiles.h"
 
 namespace sptir {
@@ -253,29 +254,6 @@ __global__ __launch_bounds__(kBuildBlock) void k_list_long_rows(int32_t n_rows, 
   if (r < n_rows && rank[r + 1] > rank[r]) rows[rank[r]] = (int32_t)r;
 }
 
-// bound[s * n_long + p] = first entry of long row p whose column is in slice s or later, s = 0 .. n_slices; slices fastest over the
-// lanes, so that the probes of a wavefront stay in one row, and through an LDS tile, so that the stores are whole lines
-constexpr int kTile = 64;
-__global__ __launch_bounds__(256) void k_slice_bounds(int32_t n_slices, int32_t width, int32_t n_long,
-                                                      const int32_t* __restrict__ rows, const int32_t* __restrict__ indptr,
-                                                      const int32_t* __restrict__ indices, int32_t* __restrict__ bound) {
-  __shared__ int32_t tile[kTile][kTile + 1];
-  const int n_sc = (n_slices + 1 + kTile - 1) / kTile;
-  const int s0 = (int)(blockIdx.x % n_sc) * kTile, p0 = (int)(blockIdx.x / n_sc) * kTile;
-  const int ns = min(kTile, n_slices + 1 - s0), np = min(kTile, n_long - p0);
-  for (int i = threadIdx.x; i < np * kTile; i += 256) {
-    const int pl = i / kTile, sl = i % kTile, s = s0 + sl;
-    if (sl >= ns) continue;
-    const int r = rows[p0 + pl], a = indptr[r], b = indptr[r + 1];
-    tile[sl][pl] = s == 0 ? a : (s == n_slices ? b : lower_bound_col(indices, a, b, (int64_t)s * width));
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < ns * kTile; i += 256) {
-    const int sl = i / kTile, pl = i % kTile;
-    if (pl < np) bound[(int64_t)(s0 + sl) * n_long + p0 + pl] = tile[sl][pl];
-  }
-}
-
 // Unit u = part * n_slices + slice: the segments that rows part * part_rows .. of the long rows have in the slice.
 // counts[u * kClasses + k]: those of class k; *bad: a row whose pieces are not in order
 __global__ __launch_bounds__(kBuildBlock) void k_count_segments(int32_t n_long, int32_t n_slices, int32_t part_rows,
@@ -428,9 +406,9 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
     if (!rows || !bound || !counts) return;
     int32_t* bad = (int32_t*)(entries + 1);
     hipLaunchKernelGGL(k_list_long_rows, dim3(row_blocks), dim3(kBuildBlock), 0, stream, n_rows, rank, rows);
-    const int64_t tiles = ((int64_t)(n_slices + 1 + kTile - 1) / kTile) * ((n_long + kTile - 1) / kTile);
-    hipLaunchKernelGGL(k_slice_bounds, dim3((unsigned)tiles), dim3(256), 0, stream, n_slices, width, n_long, rows, csr->indptr,
-                       csr->indices, bound);
+    constexpr int kTile = 64;
+    hipLaunchKernelGGL(k_slice_bounds<kTile>, dim3(slice_bounds_workgroups<kTile>(n_slices, n_long)), dim3(kBoundsBlock), 0, stream,
+                       n_slices, width, n_long, n_long, rows, csr->indptr, csr->indices, bound);
     hipLaunchKernelGGL(k_count_segments, dim3((unsigned)n_units), dim3(kBuildBlock), 0, stream, n_long, n_slices, part_rows, bound,
                        counts, bad);
     if (!hip(hipGetLastError(), "slice bounds")) return;

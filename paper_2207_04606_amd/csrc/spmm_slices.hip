@@ -25,6 +25,7 @@
 
 #include "sptir_internal.h"
 #include "sptir_scan.h"
+#include "sptir_slice_bounds.h"
 #include "sptir_tiles.h"
 
 namespace sptir {
@@ -251,32 +252,6 @@ __global__ __launch_bounds__(256) void k_slice_sums(const int32_t* __restrict__ 
 }
 
 // ------------------------------------------------------------------- build
-// bound[s * room + p] = first entry of the p-th long row whose column is in slice s or later, s = 0 .. n_slices
-constexpr int kTile = 32;
-__global__ __launch_bounds__(256) void k_slice_bounds(int32_t n_slices, int32_t n_long, int32_t room,
-                                                      const int32_t* __restrict__ order,
-                                                      const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
-                                                      int32_t* __restrict__ bound) {
-  __shared__ int32_t tile[kTile][kTile + 1];
-  const int n_sc = (n_slices + 1 + kTile - 1) / kTile;
-  const int s0 = (int)(blockIdx.x % n_sc) * kTile, p0 = (int)(blockIdx.x / n_sc) * kTile;
-  const int ns = min(kTile, n_slices + 1 - s0), np = min(kTile, room - p0);
-  for (int i = threadIdx.x; i < np * ns; i += 256) {
-    const int pl = i / ns, sl = i - pl * ns, s = s0 + sl;
-    int at = 0;
-    if (p0 + pl < n_long) {  // (the last block is filled up with rows of no entries)
-      const int r = order[p0 + pl], a = indptr[r], b = indptr[r + 1];
-      at = s == 0 ? a : (s == n_slices ? b : lower_bound_col(indices, a, b, (int64_t)s * kSliceCols));
-    }
-    tile[sl][pl] = at;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < ns * kTile; i += 256) {
-    const int sl = i / kTile, pl = i % kTile;
-    if (pl < np) bound[(int64_t)(s0 + sl) * room + p0 + pl] = tile[sl][pl];
-  }
-}
-
 // A workgroup per block of rows: count[block * n_slices + s] = half steps in slice s, those of its longest row;
 // block_steps[block]: its steps (in host memory)
 __global__ __launch_bounds__(256) void k_count_steps(int32_t n_slices, int32_t room, const int32_t* __restrict__ bound, int32_t* count,
@@ -455,9 +430,9 @@ sptir_status_t spmm_slices_count(SpmmSliceBuild* b, const sptir_csr_t* csr, int3
   int32_t* block_steps = (int32_t*)b->host.p;
   const sptir_status_t st = order_rows_by_class(csr->indptr, csr->n_rows, min_deg, longest, b->order, t + o_sort, stream);
   if (st != SPTIR_OK) return st;
-  const int64_t tiles = ((int64_t)(b->n_slices + 1 + kTile - 1) / kTile) * (((int64_t)room + kTile - 1) / kTile);
-  hipLaunchKernelGGL(k_slice_bounds, dim3((unsigned)tiles), dim3(256), 0, stream, b->n_slices, n_long, (int32_t)room, b->order,
-                     csr->indptr, csr->indices, b->bound);
+  constexpr int kTile = 32;
+  hipLaunchKernelGGL(k_slice_bounds<kTile>, dim3(slice_bounds_workgroups<kTile>(b->n_slices, (int64_t)room)), dim3(kBoundsBlock), 0,
+                     stream, b->n_slices, kSliceCols, n_long, (int32_t)room, b->order, csr->indptr, csr->indices, b->bound);
   hipLaunchKernelGGL(k_count_steps, dim3((unsigned)b->n_blocks), dim3(256), 0, stream, b->n_slices, (int32_t)room, b->bound, b->count,
                      block_steps);
   hipLaunchKernelGGL(k_slice_steps, dim3((unsigned)b->n_slices), dim3(256), 0, stream, b->n_slices, b->n_blocks, b->count,
