@@ -5,6 +5,9 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+#include <vector>
+
 namespace sptir {
 
 constexpr int kSliceBytes = 155 * 1024;  // of Yt in LDS; one workgroup a CU (two of 64 KB: 6 % slower, pieces half as long)
@@ -28,6 +31,65 @@ constexpr int slice_lane_quads(int32_t width, int32_t feat) {
   if (feat < 4 || feat > kLdsMostFeat) return 0;
   if ((int64_t)width * slice_stride((feat + 3) / 4) * 16 > kSliceBytes) return 0;
   return (feat + 31) / 32;
+}
+
+// Entries that long rows must have together for slices to pay: up to 32 features nothing is won (the reduction over the lanes costs
+// what LDS saves); the loads of the slices, and the last wave of workgroups, want half a gigabyte of gathered rows, and 2 GB where a
+// lane has two float4 or rows are cut inside one.  Drawn graphs: 96 features, 1.4 M entries 32 -> 22 us; 64, 2.0 M 40 -> 46;
+// 64, 10.8 M 221 -> 197; 32, 6.3 M 59 -> 76; 67, 3.0 M 69 -> 98.
+constexpr int64_t slice_min_entries(int64_t feat) {
+  if (feat <= 32) return INT64_MAX;
+  return (feat <= 64 || feat % 4 ? (int64_t)1 << 29 : (int64_t)1 << 27) / feat;
+}
+
+// Do slices pay for n_long rows with that many entries together?  Where Yt comes close to fitting an XCD's 4 MB of L2, the lists
+// gather it at 17 to 20 TB/s, and slices, whose segments each ask for a row of X, are no faster; unless there are so few long rows
+// that X stays near as well.  uneven: a slice and part has more than two CUs' share of the segments; it is cut, but hot columns
+// are those the lists find in the caches too.  420 graphs, 37 to 256 features, columns uniform, skewed, hot in a range, in
+// communities and in a band, where slice_min_entries() is met: Yt of 7 MB and more (uneven: 12) 1.27 times as fast (0.92 to 2.6), the
+// others 0.85 (0.54 to 1.6).  40 dense matrices: long rows of X within 512 KB 1.3 times as fast (0.92 to 2.2), more 0.99 (0.35 to 2.2).
+constexpr bool slices_pay(int64_t n_cols, int64_t feat, int64_t n_long, int64_t long_nnz, bool uneven) {
+  if (long_nnz < slice_min_entries(feat)) return false;
+  return n_cols * feat >= (uneven ? (int64_t)12 << 18 : (int64_t)7 << 18) || n_long * feat <= (int64_t)1 << 17;
+}
+
+// A workgroup's work: segments begin .. end - 1, all of one slice.
+struct SliceUnit {
+  int32_t slice, begin, end, reserved;
+};
+
+// Units in the order of their workgroup ids, which go round the 8 XCDs.  begin[part * n_slices + slice]: the first segment of that
+// part of the rows in that slice, one after the other, and the end of the last.  Each XCD has a range of slices of its own: what they
+// share of a line of values and results (neighbouring pieces of a row) then meets in one L2.  What has more than `most` segments, a
+// range of columns that many entries are in, is cut and dealt to the XCDs that have least.
+inline std::vector<SliceUnit> slice_units(const std::vector<int32_t>& begin, int32_t n_slices, int64_t parts, int64_t most) {
+  constexpr int kXcds = 8;
+  const int32_t per_xcd = (n_slices + kXcds - 1) / kXcds;
+  std::vector<SliceUnit> units, of_xcd[kXcds];
+  int64_t load[kXcds] = {0};
+  for (int64_t part = 0; part < parts; ++part) {
+    const int32_t* at = begin.data() + part * n_slices;
+    for (int32_t s = 0; s < n_slices; ++s)
+      if (at[s + 1] - at[s] <= most) {
+        of_xcd[s / per_xcd].push_back({s, at[s], at[s + 1], 0});
+        load[s / per_xcd] += at[s + 1] - at[s];
+      }
+    for (int32_t s = 0; s < n_slices; ++s) {
+      const int64_t n = at[s + 1] - at[s], pieces = (n + most - 1) / most;
+      for (int64_t i = 0; n > most && i < pieces; ++i) {
+        const int x = (int)(std::min_element(load, load + kXcds) - load);
+        const int32_t lo = (int32_t)(n * i / pieces), hi = (int32_t)(n * (i + 1) / pieces);
+        of_xcd[x].push_back({s, at[s] + lo, at[s] + hi, 0});
+        load[x] += hi - lo;
+      }
+    }
+    size_t longest = 0;
+    for (const auto& list : of_xcd) longest = std::max(longest, list.size());
+    for (size_t i = 0; i < longest; ++i)
+      for (const auto& list : of_xcd) units.push_back(i < list.size() ? list[i] : SliceUnit{0, 0, 0, 0});
+    for (auto& list : of_xcd) list.clear();
+  }
+  return units;
 }
 
 }  // namespace sptir

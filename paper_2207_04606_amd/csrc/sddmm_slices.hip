@@ -34,12 +34,13 @@ namespace {
 constexpr int64_t kMinPiece = 3;
 constexpr int64_t kMinUnits = 2048;
 constexpr int64_t kPartBytes = 1 << 20;  // rows of X of a part (2 MB: 1 % slower)
+constexpr int64_t kCus = 256;
 constexpr int64_t kMinUnitNnz = 4096;    // entries that pay for loading a slice
 constexpr int kSegment = 8;             // entries of a segment
 constexpr int kClasses = 8;             // full segments, then those of 7 .. 1 entries
 
 struct SliceArgs {
-  const int4* units;       // slice, first segment, end of segments
+  const int4* units;       // SliceUnit
   const int2* seg_at;      // row, CSR position of the first entry
   const uint4* seg_cols;   // eight 16-bit columns inside the slice (the last one repeated); bits 13 .. 15 of the first: entries - 1
   const float* values;
@@ -328,15 +329,6 @@ hipError_t launch_rows(const SliceArgs& a, unsigned n_units, hipStream_t stream)
   return a.feat == 32 * T ? launch<T, false>(a, n_units, stream) : launch<T, true>(a, n_units, stream);
 }
 
-// Entries that long rows must have together for slices to pay: up to 32 features nothing is won (the reduction over the lanes costs
-// what LDS saves); the loads of the slices, and the last wave of workgroups, want half a gigabyte of gathered rows, and 2 GB where a
-// lane has two float4 or rows are cut inside one.  Drawn graphs: 96 features, 1.4 M entries 32 -> 22 us; 64, 2.0 M 40 -> 46;
-// 64, 10.8 M 221 -> 197; 32, 6.3 M 59 -> 76; 67, 3.0 M 69 -> 98.
-int64_t min_entries(int64_t feat) {
-  if (feat <= 32) return INT64_MAX;
-  return (feat <= 64 || feat % 4 ? (int64_t)1 << 29 : (int64_t)1 << 27) / feat;
-}
-
 }  // namespace
 
 void sddmm_slices_free(SddmmSlices* s, sptir_free_fn free_, void* actx) {
@@ -350,7 +342,7 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
                                   hipStream_t stream, SddmmSlices* out, int32_t** rank_out) {
   *out = SddmmSlices();
   *rank_out = nullptr;
-  const int64_t feat = feat_hint > 0 ? feat_hint : 128, min_nnz = min_entries(feat);
+  const int64_t feat = feat_hint > 0 ? feat_hint : 128, min_nnz = slice_min_entries(feat);
   const int32_t n_rows = csr->n_rows, n_cols = csr->n_cols, width = slice_width(feat);
   if (width == 0 || csr->nnz < min_nnz) return SPTIR_OK;
   const int64_t n_slices64 = ((int64_t)n_cols + width - 1) / width;
@@ -391,7 +383,7 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
     if (!hip(hipMemcpyAsync(&n_long, seq_base + n_seq, sizeof(n_long), hipMemcpyDeviceToHost, stream), "hipMemcpyAsync") ||
         !read_back(&long_nnz, entries, sizeof(long_nnz)))
       return;
-    if (n_long <= 0 || (int64_t)long_nnz < min_nnz || (int64_t)long_nnz > csr->nnz) return;
+    if (n_long <= 0 || (int64_t)long_nnz > csr->nnz || !slices_pay(n_cols, feat, n_long, (int64_t)long_nnz, false)) return;
 
     int32_t* rows = (int32_t*)temporary(sizeof(int32_t) * (size_t)n_long);
     int32_t* bound = (int32_t*)temporary(sizeof(int32_t) * ((size_t)n_slices + 1) * (size_t)n_long);
@@ -419,23 +411,22 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
       return;
     if (is_bad) return;
 
-    std::vector<int4> units;
-    int64_t at = 0;
-    // Workgroup ids go round the XCDs.  Each has a range of slices of its own: what they share of a line of values and results
-    // (neighbouring pieces of a row) then meets in one L2.
-    const int32_t per_xcd = (n_slices + 7) / 8;
-    for (int64_t part = 0; part < parts; ++part)
-      for (int32_t i = 0; i < 8 * per_xcd; ++i) {
-        const int32_t slice = (i % 8) * per_xcd + i / 8;
-        const size_t u = (size_t)part * n_slices + slice;
-        const int64_t begin = at;
-        for (int k = 0; k < kClasses && slice < n_slices; ++k) {
-          const int32_t n = count[u * kClasses + k];
-          count[u * kClasses + k] = (int32_t)at;
-          at += n;
-        }
-        units.push_back(make_int4(slice, (int)begin, (int)at, 0));
+    std::vector<int32_t> begin(n_units + 1);
+    int64_t at = 0, largest = 0;
+    for (size_t u = 0; u < n_units; ++u) {
+      begin[u] = (int32_t)at;
+      for (int k = 0; k < kClasses; ++k) {
+        const int32_t n = count[u * kClasses + k];
+        count[u * kClasses + k] = (int32_t)at;
+        at += n;
       }
+      largest = std::max(largest, at - begin[u]);
+    }
+    begin[n_units] = (int32_t)at;
+    const int64_t share = (at + kCus - 1) / kCus;  // of a CU
+    if (!slices_pay(n_cols, feat, n_long, (int64_t)long_nnz, largest > 2 * share)) return;
+    const std::vector<SliceUnit> units = slice_units(begin, n_slices, parts, share);
+    if (units.size() > 0x7FFFFFFF) return;
     s.n_segs = at; s.n_units = (int64_t)units.size();
     s.width = width; s.nnz = (int64_t)long_nnz;
     auto keep = [&](size_t bytes) {
@@ -445,10 +436,10 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
     };
     s.seg_at = (int2*)keep(sizeof(int2) * (size_t)at);
     s.seg_cols = (uint4*)keep(sizeof(uint4) * (size_t)at);
-    s.units = (int4*)keep(sizeof(int4) * units.size());
+    s.units = (int4*)keep(sizeof(SliceUnit) * units.size());
     if (!s.seg_at || !s.seg_cols || !s.units) return;
     if (!hip(hipMemcpyAsync(counts, count.data(), sizeof(int32_t) * count.size(), hipMemcpyHostToDevice, stream), "hipMemcpyAsync") ||
-        !hip(hipMemcpyAsync(s.units, units.data(), sizeof(int4) * units.size(), hipMemcpyHostToDevice, stream), "hipMemcpyAsync"))
+        !hip(hipMemcpyAsync(s.units, units.data(), sizeof(SliceUnit) * units.size(), hipMemcpyHostToDevice, stream), "hipMemcpyAsync"))
       return;
     hipLaunchKernelGGL(k_fill_segments, dim3((unsigned)n_units), dim3(kBuildBlock), 0, stream, n_long, n_slices, part_rows, width,
                        n_cols, rows, csr->indices, bound, counts, s.seg_at, s.seg_cols, bad);

@@ -1,16 +1,32 @@
-// Prints "hint feat width lane_quads" for every feature size a plan can be made for and every size it may be called with.
+// Host rules of the column slices of an SDDMM plan, for test_sddmm_slice_shape.py.
+//   shape MOST_HINT MOST_FEAT: prints "hint feat width lane_quads" for every feature size a plan can be made for and every
+//                              size it may be called with
+//   pay N_COLS FEAT N_LONG LONG_NNZ UNEVEN: prints whether slices are chosen
+//   units N_SLICES PARTS MOST: reads the first segment of every part and slice, and the end, and prints "slice begin end" of every unit
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 
 #include "sddmm_slice_shape.h"
 
 int main(int argc, char** argv) {
-  const int most_hint = atoi(argv[1]), most_feat = atoi(argv[2]);
-  (void)argc;
-  for (int hint = 1; hint <= most_hint; ++hint)
-    for (int feat = 1; feat <= most_feat; ++feat) {
-      const int32_t width = sptir::slice_width(hint);
-      printf("%d %d %d %d\n", hint, feat, (int)width, width ? sptir::slice_lane_quads(width, feat) : 0);
-    }
+  if (argc == 4 && !strcmp(argv[1], "shape")) {
+    const int most_hint = atoi(argv[2]), most_feat = atoi(argv[3]);
+    for (int hint = 1; hint <= most_hint; ++hint)
+      for (int feat = 1; feat <= most_feat; ++feat) {
+        const int32_t width = sptir::slice_width(hint);
+        printf("%d %d %d %d\n", hint, feat, (int)width, width ? sptir::slice_lane_quads(width, feat) : 0);
+      }
+  } else if (argc == 7 && !strcmp(argv[1], "pay")) {
+    printf("%d\n", sptir::slices_pay(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]), atoll(argv[5]), atoi(argv[6]) != 0) ? 1 : 0);
+  } else if (argc == 5 && !strcmp(argv[1], "units")) {
+    const int n_slices = atoi(argv[2]), parts = atoi(argv[3]);
+    std::vector<int32_t> begin((size_t)n_slices * parts + 1);
+    for (int32_t& b : begin)
+      if (scanf("%d", &b) != 1) return 1;
+    for (const sptir::SliceUnit& u : sptir::slice_units(begin, n_slices, parts, atoll(argv[4]))) printf("%d %d %d\n", u.slice, u.begin, u.end);
+  } else {
+    return 2;
+  }
   return 0;
 }

@@ -243,3 +243,40 @@ def test_sddmm_plan_slices_keep_non_finite_rows_apart(gpu_lib):
     with np.errstate(invalid="ignore"):
         want = w.values * np.einsum("ij,ij->i", Xr[rows], Yt[w.indices])
     assert np.array_equal(np.isfinite(got), np.isfinite(want))
+
+
+@pytest.mark.parametrize("feat", [96, 128, 256])
+def test_sddmm_plan_slices_with_hot_columns(gpu_lib, feat):
+    """Many entries in one slice of columns, whose work is dealt to several workgroups; rows without any there; short rows."""
+    n_long, n_cols = 131072 // feat, 12001
+    rng = np.random.default_rng(feat)
+    far = workloads.random_csr(n_long + 50, n_cols - 130, np.r_[rng.integers(1000, 1300, n_long), rng.integers(0, 9, 50)], feat, feat)
+    near = workloads.random_csr(n_long + 50, 130, np.r_[rng.integers(0, 131, n_long), np.zeros(50, dtype=int)], feat + 1, feat)
+    rows = [np.repeat(np.arange(n_long + 50, dtype=np.int64), np.diff(m.indptr)) for m in (near, far)]
+    key = np.sort(np.concatenate([rows[0] * n_cols + 5000 + near.indices,
+                                  rows[1] * n_cols + np.where(far.indices < 5000, far.indices, far.indices + 130)]))
+    w = near
+    w.n_cols = n_cols
+    w.indptr = np.concatenate([[0], np.cumsum(np.bincount(key // n_cols, minlength=n_long + 50))]).astype(np.int32)
+    w.indices = (key % n_cols).astype(np.int32)
+    w.values = rng.standard_normal(key.size).astype(np.float32)
+    w.X = rng.standard_normal((n_cols, feat)).astype(np.float32)
+    assert w.nnz * feat >= 1 << 27
+    say(f"[sddmm hot columns] feat={feat} nnz={w.nnz}")
+    Xr = left_operand(w, feat, feat)
+    want = run_sddmm(gpu_lib, w, Xr, w.X)
+    got, info = run_sddmm_plan(gpu_lib, w, Xr, w.X, 8, feat_hint=feat)
+    assert info["n_runs"] < 16, "the long rows are in the runs"
+    assert np.array_equal(got, want)
+    Br, Mr = oracle.sddmm_csr(w.n_rows, w.indptr, w.indices, w.values, Xr, w.X)
+    assert_b_close(got, Br, Mr, f"hot feat={feat}")
+
+
+def test_sddmm_plan_lists_where_yt_is_near(gpu_lib):
+    """Rows long enough for slices stay in the lists where Yt comes out of L2 as it is."""
+    w = workloads.random_csr(9000, 9000, np.random.default_rng(7).integers(120, 300, 9000), 7, 128)
+    assert w.nnz * 128 >= 1 << 27
+    Xr = left_operand(w, 128, 2)
+    got, info = run_sddmm_plan(gpu_lib, w, Xr, w.X, 8, feat_hint=128)
+    assert info["n_runs"] >= w.nnz // 512
+    assert np.array_equal(got, run_sddmm(gpu_lib, w, Xr, w.X))

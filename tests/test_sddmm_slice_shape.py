@@ -1,5 +1,6 @@
-"""Which kernel an SDDMM plan with column slices takes for a call, over all pairs of the feature size the plan was made for
-and the one it is called with: the host rule of csrc/sddmm_slice_shape.h, compiled alone."""
+"""The host rules of an SDDMM plan with column slices (csrc/sddmm_slice_shape.h, compiled alone): which kernel takes a call, over
+all pairs of the feature size the plan was made for and the one it is called with; where slices are chosen; how the work is
+dealt to workgroups."""
 import os
 import subprocess
 
@@ -14,12 +15,21 @@ GROUP_LANES, QUAD = 8, 4          # lanes of a group, floats of a lane's load
 
 
 @pytest.fixture(scope="module")
-def choices(tmp_path_factory):
+def rules(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("shape") / "shape")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", sptir_build.CSRC, "-o", exe,
                            os.path.join(HERE, "sddmm_slice_shape_main.cpp")])
-    out = subprocess.run([exe, "300", "1100"], check=True, capture_output=True, text=True).stdout
-    return np.array(out.split(), dtype=np.int64).reshape(-1, 4)
+
+    def ask(*args, text=None):
+        out = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True, input=text).stdout
+        return np.array(out.split(), dtype=np.int64)
+
+    return ask
+
+
+@pytest.fixture(scope="module")
+def choices(rules):
+    return rules("shape", 300, 1100).reshape(-1, 4)
 
 
 def test_the_lanes_hold_every_feature(choices):
@@ -43,3 +53,47 @@ def test_the_slice_fits_lds(choices):
     same = (hint == feat) & (width > 0) & (feat >= QUAD)
     assert in_lds[same].all()
     assert (width[hint > 256] == 0).all() and (width[hint <= 256] >= 1).all()
+
+
+@pytest.mark.parametrize("n_cols,feat,n_long,long_nnz,even,uneven", [
+    (9696, 96, 9000, 1_930_000, 0, 0),          # Yt of 3.7 MB: lists gather it from L2 (42 us, 66 with slices)
+    (7873, 160, 7800, 2_530_000, 0, 0),
+    (25117, 96, 23000, 13_170_000, 1, 0),       # 9.6 MB
+    (34000, 96, 30000, 14_000_000, 1, 1),       # 13 MB
+    (232965, 128, 60000, 70_000_000, 1, 1),
+    (3001, 128, 531, 1_200_000, 1, 1),          # few long rows
+    (3001, 128, 531, 1_000_000, 0, 0),          # fewer entries than slices need
+    (232965, 32, 60000, 70_000_000, 0, 0),      # too few features
+    (2**31 - 1, 256, 2**31 - 1, 2**31 - 1, 1, 1),
+])
+def test_where_slices_are_chosen(rules, n_cols, feat, n_long, long_nnz, even, uneven):
+    assert rules("pay", n_cols, feat, n_long, long_nnz, 0) == [even]
+    assert rules("pay", n_cols, feat, n_long, long_nnz, 1) == [uneven]
+
+
+@pytest.mark.parametrize("n_slices,parts,hot,most", [(1, 1, 0, 1), (1, 3, 0, 40), (7, 2, 3, 50), (8, 1, 7, 64), (61, 9, 5, 300),
+                                                     (61, 9, 60, 1), (200, 3, 0, 10**9), (9, 4, None, 25)])
+def test_units_hold_every_segment_once(rules, n_slices, parts, hot, most):
+    """No unit has more than `most` segments, each lies in the slice it names, what is not cut stays with the XCD of its
+    slice, and none of the 8 XCDs has much more than the others where a slice is hot."""
+    rng = np.random.default_rng(n_slices * parts)
+    n = rng.integers(0, 30, (parts, n_slices))
+    n[rng.random(n.shape) < 0.2] = 0
+    if hot is not None:
+        n[:, hot] = 1700
+    begin = np.concatenate([[0], np.cumsum(n)])
+    units = rules("units", n_slices, parts, most, text=" ".join(map(str, begin))).reshape(-1, 3)
+    slice_of = np.repeat(np.tile(np.arange(n_slices), parts), n.ravel())
+    per_xcd = -(-n_slices // 8)
+    seen = np.zeros(begin[-1], dtype=int)
+    load = np.zeros(8, dtype=int)
+    for i, (s, lo, hi) in enumerate(units):
+        assert 0 <= hi - lo <= most
+        seen[lo:hi] += 1
+        assert (slice_of[lo:hi] == s).all()
+        load[i % 8] += hi - lo
+        if hi > lo and lo in begin and hi in begin:
+            assert i % 8 == s // per_xcd
+    assert (seen == 1).all()
+    if hot is not None and most < 1000:
+        assert load.max() - load.min() <= max(most, n.sum() // 8)
