@@ -53,6 +53,12 @@ constexpr bool slices_pay(int64_t n_cols, int64_t feat, int64_t n_long, int64_t 
   return n_cols * feat >= (uneven ? (int64_t)12 << 18 : (int64_t)7 << 18) || n_long * feat <= (int64_t)1 << 17;
 }
 
+// Is a row that begins and ends there long?  One that is not inside the entries is none: nothing is read for it here, and the
+// general path treats it as it treats every other row.
+constexpr bool is_long_row(int64_t begin, int64_t end, int64_t nnz, int64_t min_deg) {
+  return begin >= 0 && end <= nnz && end - begin >= min_deg;
+}
+
 // A workgroup's work: segments begin .. end - 1, all of one slice.
 struct SliceUnit {
   int32_t slice, begin, end, reserved;

@@ -238,15 +238,15 @@ __global__ __launch_bounds__(512) void k_sddmm_segments(SliceArgs a) {
 
 // ------------------------------------------------------------------- build
 // taken[r]: 1 where row r is long enough (taken[n_rows] = 0); *entries: their entries together
-__global__ __launch_bounds__(kBuildBlock) void k_long_rows(int32_t n_rows, const int32_t* __restrict__ indptr, int64_t min_deg,
-                                                           int32_t* taken, unsigned long long* entries) {
+__global__ __launch_bounds__(kBuildBlock) void k_long_rows(int32_t n_rows, int64_t nnz, const int32_t* __restrict__ indptr,
+                                                           int64_t min_deg, int32_t* taken, unsigned long long* entries) {
   __shared__ long long wave_sums[kWaves];
   const int64_t r = (int64_t)blockIdx.x * kBuildBlock + threadIdx.x;
-  const long long deg = r < n_rows ? (long long)indptr[r + 1] - indptr[r] : 0;
-  const bool is_long = r < n_rows && deg >= min_deg;
+  const long long begin = r < n_rows ? indptr[r] : 0, end = r < n_rows ? indptr[r + 1] : 0;
+  const bool is_long = r < n_rows && is_long_row(begin, end, nnz, min_deg);
   if (r <= n_rows) taken[r] = is_long ? 1 : 0;
   long long sum;
-  (void)block_exclusive_scan<long long>(is_long ? deg : 0, wave_sums, &sum);
+  (void)block_exclusive_scan<long long>(is_long ? end - begin : 0, wave_sums, &sum);
   if (threadIdx.x == 0 && sum > 0) atomicAdd(entries, (unsigned long long)sum);
 }
 
@@ -376,7 +376,8 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
     if (!rank || !seq_base || !entries) return;
     const unsigned row_blocks = (unsigned)(((int64_t)n_rows + 1 + kBuildBlock - 1) / kBuildBlock);
     if (!hip(hipMemsetAsync(entries, 0, 16, stream), "hipMemsetAsync")) return;
-    hipLaunchKernelGGL(k_long_rows, dim3(row_blocks), dim3(kBuildBlock), 0, stream, n_rows, csr->indptr, min_deg, rank, entries);
+    hipLaunchKernelGGL(k_long_rows, dim3(row_blocks), dim3(kBuildBlock), 0, stream, n_rows, csr->nnz, csr->indptr, min_deg, rank,
+                       entries);
     if ((st = device_exclusive_scan(rank, (int64_t)n_rows + 1, seq_base, stream)) != SPTIR_OK) return;
     unsigned long long long_nnz = 0;
     int32_t n_long = 0;

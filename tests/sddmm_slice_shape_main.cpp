@@ -2,6 +2,7 @@
 //   shape MOST_HINT MOST_FEAT: prints "hint feat width lane_quads" for every feature size a plan can be made for and every
 //                              size it may be called with
 //   pay N_COLS FEAT N_LONG LONG_NNZ UNEVEN: prints whether slices are chosen
+//   long BEGIN END NNZ MIN_DEG: prints whether the row is one that slices may take
 //   units N_SLICES PARTS MOST: reads the first segment of every part and slice, and the end, and prints "slice begin end" of every unit
 #include <stdio.h>
 #include <stdlib.h>
@@ -19,6 +20,8 @@ int main(int argc, char** argv) {
       }
   } else if (argc == 7 && !strcmp(argv[1], "pay")) {
     printf("%d\n", sptir::slices_pay(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]), atoll(argv[5]), atoi(argv[6]) != 0) ? 1 : 0);
+  } else if (argc == 6 && !strcmp(argv[1], "long")) {
+    printf("%d\n", sptir::is_long_row(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]), atoll(argv[5])) ? 1 : 0);
   } else if (argc == 5 && !strcmp(argv[1], "units")) {
     const int n_slices = atoi(argv[2]), parts = atoi(argv[3]);
     std::vector<int32_t> begin((size_t)n_slices * parts + 1);

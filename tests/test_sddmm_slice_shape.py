@@ -97,3 +97,11 @@ def test_units_hold_every_segment_once(rules, n_slices, parts, hot, most):
     assert (seen == 1).all()
     if hot is not None and most < 1000:
         assert load.max() - load.min() <= max(most, n.sum() // 8)
+
+
+@pytest.mark.parametrize("begin,end,is_long", [(0, 300, 1), (700, 1000, 1), (0, 299, 0), (5, 5, 0), (600, 300, 0),
+                                               (-1, 300, 0), (-400, 0, 0), (700, 1001, 0), (1000, 1300, 0),
+                                               (-2**31, 2**31 - 1, 0), (2**31 - 1, -2**31, 0)])
+def test_rows_outside_the_entries_are_not_long(rules, begin, end, is_long):
+    """Row pointers are not validated when a plan is built: a row that is not inside the entries is not searched."""
+    assert rules("long", begin, end, 1000, 300) == [is_long]
