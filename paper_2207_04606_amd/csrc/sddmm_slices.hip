@@ -455,6 +455,7 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
     st = SPTIR_ERR_ALLOC;
   }
   if (st != SPTIR_OK) use = false;
+  if (st == SPTIR_ERR_ALLOC) st = SPTIR_OK;  // (a plan without slices needs less at a time)
   (void)hipStreamSynchronize(stream);  // (nothing that is given back below is still written to)
   for (void* p : temporaries)
     if (!(use && p == rank)) free_(p, actx);

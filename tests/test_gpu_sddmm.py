@@ -280,3 +280,39 @@ def test_sddmm_plan_lists_where_yt_is_near(gpu_lib):
     got, info = run_sddmm_plan(gpu_lib, w, Xr, w.X, 8, feat_hint=128)
     assert info["n_runs"] >= w.nnz // 512
     assert np.array_equal(got, run_sddmm(gpu_lib, w, Xr, w.X))
+
+
+def test_sddmm_plan_slices_that_find_no_memory_are_left_out(gpu_lib):
+    """An allocation that only column slices ask for may fail: the plan then lists all rows.  (A caller's allocator that refuses
+    one size, an error code and no GPU work.)"""
+    from paper_2207_04606_amd import binding
+    w = matrix_with_long_rows(900, 600, 3001, 5, 128)
+    Xr = left_operand(w, 128, 1)
+    want = run_sddmm(gpu_lib, w, Xr, w.X)
+    asked, refuse = [], set()
+
+    @binding._ALLOC_FN
+    def take(nbytes, ctx, stream):
+        asked.append(int(nbytes))
+        return None if int(nbytes) in refuse else binding._torch_alloc(nbytes, ctx, stream)
+
+    assert gpu_lib.load_library().sptir_set_allocator(take, binding._torch_free, None) == 0
+    try:
+        for c in (1, 8):
+            run_sddmm_plan(gpu_lib, w, Xr, w.X, c, feat_hint=16)          # (no slices)
+        without = set(asked)
+        asked.clear()
+        got, info = run_sddmm_plan(gpu_lib, w, Xr, w.X, 8, feat_hint=128)
+        assert info["n_runs"] < 64 and np.array_equal(got, want)
+        only = [size for size in asked[:9] if size not in without]        # (the slices' come first)
+        assert len(only) >= 8
+        before = len(binding._torch_blocks)
+        for size in only:
+            refuse = {size}
+            for c in (1, 8):
+                got, info = run_sddmm_plan(gpu_lib, w, Xr, w.X, c, feat_hint=128)
+                assert np.array_equal(got, want), size
+                assert info["n_runs"] == 0 if c == 1 else info["n_runs"] >= w.nnz // 512, size
+            assert len(binding._torch_blocks) == before
+    finally:
+        gpu_lib.sptir_set_allocator(False)
