@@ -157,15 +157,18 @@ __global__ __launch_bounds__(512) void k_spmm_csr(CsrArgs a) {
     if (for_long) {
       __shared__ unsigned long long span_long[2][kWaves];
       int turn = 0;
-      for (int64_t r0 = unit * 512; r0 < a.n_rows; r0 += (int64_t)a.long_units * 512, turn ^= 1) {  // 512 rows at a time, one per thread
-        const int64_t r = r0 + threadIdx.x;
+      // 512 rows at a time, one per thread and a.long_units apart: where long rows are neighbours (rows in the order of their
+      // lengths) each of these workgroups has its share.  (512 in a row: 169,343 rows so ordered 1247 us, 113 in no order.)
+      const int64_t step = a.long_units;
+      for (int64_t r0 = unit; r0 < a.n_rows; r0 += 512 * step, turn ^= 1) {
+        const int64_t r = r0 + threadIdx.x * step;
         const int len = r < a.n_rows ? a.indptr[r + 1] - a.indptr[r] : 0;
         const unsigned long long mine = __ballot(len > kLong);
         if (lane == 0) span_long[turn][wave] = mine;
         __syncthreads();
         for (int w = 0; w < kWaves; ++w)
           for (unsigned long long left = span_long[turn][w]; left; left &= left - 1) {
-            const int64_t row = r0 + w * 64 + __builtin_ctzll(left);
+            const int64_t row = r0 + (w * 64 + __builtin_ctzll(left)) * step;
             const int first = __builtin_amdgcn_readfirstlane(a.indptr[row]);
             long_row(row, first, __builtin_amdgcn_readfirstlane(a.indptr[row + 1]) - first);
           }
@@ -241,15 +244,16 @@ extern "C" sptir_status_t sptir_spmm_csr(const sptir_csr_t* csr, const float* X,
   CsrArgs a;
   a.indptr = csr->indptr; a.indices = csr->indices; a.values = csr->values; a.X = X; a.Y = Y;
   a.n_rows = csr->n_rows; a.feat = feat; a.n_tiles = g.n_tiles; a.map_mode = g.map_mode; a.map_param = g.map_param;
-  // Long rows first, by workgroups of their own (512 over all tiles, which look through all rows): a long row that a workgroup in the
-  // middle of the grid meets is worked on when the others have ended (169,343 rows, 13,000 entries the longest: 113 -> 104 us; 80
-  // graphs: power-law rows of less than 24 entries in the mean 1.02 to 1.39 times as fast, even ones 0.96 to 1.01).  Longer rows
-  // are long too often for 512 workgroups (mean of 24 to 100 entries: 0.7 to 1.07).
+  // Long rows first, by workgroups of their own (up to 512 over all tiles, which look through all rows): a long row that a workgroup
+  // in the middle of the grid meets is worked on when the others have ended (169,343 rows, 13,000 entries the longest: 113 -> 104
+  // us).  One of them per 128 rows: 160 graphs of 3.5 to 24 entries a row, against none, power-law rows 1.16 times as fast (0.91 to
+  // 1.7), in the order of their lengths 3.3 (1.0 to 14), even rows 0.98 (0.9 to 1.05); one per 512 rows 1.08, 3.4 and 0.98.
+  // Longer rows are long too often for 512 workgroups (mean of 24 to 100 entries: 0.7 to 1.07).
   const bool long_first = csr->nnz < 24 * (int64_t)csr->n_rows;
   int64_t long_grid = 0;
   if (long_first) {
     Geometry first = g;
-    a.long_units = (int32_t)std::max<int64_t>(1, std::min<int64_t>(512 / g.n_tiles, ((int64_t)csr->n_rows + 511) / 512));
+    a.long_units = (int32_t)std::max<int64_t>(1, std::min<int64_t>(512 / g.n_tiles, ((int64_t)csr->n_rows + 127) / 128));
     if (!plan_tiles(a.long_units, &first)) return SPTIR_ERR_OVERFLOW;
     long_grid = (first.grid + 7) / 8 * 8;
     a.long_grid = (uint32_t)long_grid; a.long_mode = first.map_mode; a.long_param = first.map_param;

@@ -60,3 +60,19 @@ def test_long_rows_among_short_ones(gpu_lib, n_rows, feat):
     gpu_lib.sptir_spmm_csr(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, d.X, Y)
     Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
     assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"rows={n_rows} feat={feat}")
+
+
+@pytest.mark.parametrize("n_rows,feat", [(129, 4), (4000, 13), (20_000, 64), (70_000, 36), (3000, 1028)])
+def test_long_rows_that_are_neighbours(gpu_lib, n_rows, feat):
+    """Rows in the order of their lengths: those workgroups that take the long rows each have some of them, and all are taken once."""
+    rng = np.random.default_rng(n_rows)
+    deg = rng.integers(0, 6, n_rows)
+    deg[:n_rows // 400 + 1] = rng.choice([512, 513, 600, 1100], n_rows // 400 + 1)
+    deg = np.sort(deg)[::-1] if n_rows % 3 else np.sort(deg)
+    w = workloads.random_csr(n_rows, 1200, deg, feat, feat)
+    assert w.nnz < 24 * n_rows
+    d = upload(w)
+    Y = torch.full((n_rows, feat), float("nan"), device="cuda")
+    gpu_lib.sptir_spmm_csr(w.n_rows, w.n_cols, d.indptr, d.indices, d.values, d.X, Y)
+    Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"rows={n_rows} feat={feat}")
