@@ -465,7 +465,7 @@ typedef struct {
   int64_t n_pad_slots;            /* what a hyb(1, max_bucket_log2) decomposition of the slices would pad */
   int64_t n_tiles;                /* matrix-core products: up to 16 pieces of at most 8 entries, of one relation and row block */
   int32_t workspace_d_out;        /* widest d_out that is summed in a fixed order (0: none) */
-  int32_t reserved;
+  int32_t row_block;              /* rows of Y that a workgroup sums in LDS */
   int64_t device_bytes;
 } sptir_rgms_info_t;
 

@@ -98,7 +98,7 @@ class _RgmsInfo(ctypes.Structure):
     _fields_ = [("n_relations", ctypes.c_int32), ("n_rows", ctypes.c_int32), ("n_cols", ctypes.c_int32),
                 ("max_bucket_log2", ctypes.c_int32), ("nnz", ctypes.c_int64),
                 ("n_stacked_rows_stored", ctypes.c_int64), ("n_pad_slots", ctypes.c_int64),
-                ("n_tiles", ctypes.c_int64), ("workspace_d_out", ctypes.c_int32), ("reserved", ctypes.c_int32),
+                ("n_tiles", ctypes.c_int64), ("workspace_d_out", ctypes.c_int32), ("row_block", ctypes.c_int32),
                 ("device_bytes", ctypes.c_int64)]
 
 

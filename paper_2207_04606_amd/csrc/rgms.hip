@@ -607,7 +607,7 @@ extern "C" sptir_status_t sptir_rgms_info(const sptir_rgms_t* p, sptir_rgms_info
   sptir_rgms_info_t o;
   o.n_relations = p->n_rel; o.n_rows = p->n_rows; o.n_cols = p->n_cols; o.max_bucket_log2 = p->k;
   o.nnz = p->nnz; o.n_stacked_rows_stored = p->n_pairs; o.n_pad_slots = p->n_pads;
-  o.n_tiles = p->n_tiles; o.workspace_d_out = p->workspace_d_out; o.reserved = 0;
+  o.n_tiles = p->n_tiles; o.workspace_d_out = p->workspace_d_out; o.row_block = 1 << p->log2_block;
   o.device_bytes = (int64_t)p->device_bytes;
   *out = o;
   return SPTIR_OK;

@@ -161,7 +161,11 @@ def test_rgms_named_configs(gpu_lib, name, workspace):
                                                 (4000, 2, 128, 64), (60_000, 4, 32, 32), (9000, 1, 128, 128)])
 def test_rgms_tile_edges(gpu_lib, n, n_rel, d_in, d_out, workspace):
     """Pairs of 1, 4 +- 1, 8 +- 1, 64 +- 1 and 1500 entries (steps, pieces and batches of a tile), cells of 15 to 17 pairs,
-    row blocks of every size, undivided, divided and shared between workgroups, one and several passes over Y."""
+    row blocks of several sizes, undivided, divided and shared between workgroups, one and several passes over Y."""
+    check_tile_edges(gpu_lib, n, n_rel, d_in, d_out, workspace)
+
+
+def check_tile_edges(gpu_lib, n, n_rel, d_in, d_out, workspace):
     rng = np.random.default_rng(n + d_out)
     counts = np.zeros(n_rel * n, dtype=np.int64)
     lens = np.minimum([1, 1, 2, 3, 4, 5, 7, 8, 9, 63, 64, 65], n)
@@ -178,6 +182,7 @@ def test_rgms_tile_edges(gpu_lib, n, n_rel, d_in, d_out, workspace):
     Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, w.X, w.W)
     assert_y_close(Y, Yr, Sr, f"n={n} d_in={d_in} d_out={d_out}")
     assert np.array_equal(Y, Y2) if workspace >= d_out else np.allclose(Y, Y2, rtol=1e-4, atol=1e-4)
+    return info
 
 
 def test_rgms_features_beyond_4_gb(gpu_lib):
@@ -206,11 +211,14 @@ def test_rgms_non_finite_rows_stay_with_their_rows(gpu_lib, n, n_rel, d_in, d_ou
     tile, step of four or repeated last entry it shares with theirs; an infinite value of A and an infinite W[r]
     likewise.  (Which of infinity and NaN comes out depends on the order of the sums; that it is not finite does not.)"""
     rng = np.random.default_rng(n + d_in)
-    counts = np.minimum(rng.integers(0, 4, n_rel * n), n)
+    check_non_finite_rows(gpu_lib, n, n_rel, d_in, d_out, workspace, np.minimum(rng.integers(0, 4, n_rel * n), n), rng)
+
+
+def check_non_finite_rows(gpu_lib, n, n_rel, d_in, d_out, workspace, counts, rng):
     counts[rng.choice(n_rel * n, 40, replace=False)] = rng.choice([5, 8, 9, 16, 64, 65, 130], 40)  # several pieces, batches
     w = workloads.random_csr(n_rel * n, n, counts, 3, 1, "uniform")
     X = rng.standard_normal((n, d_in)).astype(np.float32)
-    bad = rng.choice(n, 6, replace=False)
+    bad = rng.choice(n if counts.sum() > n else np.unique(w.indices), 6, replace=False)  # (columns that entries name)
     X[bad[0]] = np.nan
     X[bad[1], 0] = np.inf
     X[bad[2], d_in - 1] = -np.inf
@@ -223,7 +231,7 @@ def test_rgms_non_finite_rows_stay_with_their_rows(gpu_lib, n, n_rel, d_in, d_ou
         if W_bad:
             W[n_rel - 1, d_in // 3, 5] = np.inf
         hw = workloads.HeteroWorkload("non-finite", n, n_rel, w.indptr, w.indices, values, X, W)
-        Y, _ = run_rgms(gpu_lib, hw, workspace_d_out=workspace)
+        Y, info = run_rgms(gpu_lib, hw, workspace_d_out=workspace)
         with np.errstate(invalid="ignore", over="ignore"):
             Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, values, X, W)
         finite = np.isfinite(Yr)
@@ -231,11 +239,14 @@ def test_rgms_non_finite_rows_stay_with_their_rows(gpu_lib, n, n_rel, d_in, d_ou
         wrong = np.isfinite(Y) != finite
         assert not wrong.any(), f"{int(wrong.sum())} of {int(finite.sum())} elements"
         assert_y_close(np.where(finite, Y, 0), np.where(finite, Yr, 0), np.where(finite, Sr, 0), "finite rows")
+    return info
 
 
 @pytest.mark.parametrize("d_in,d_out", [(32, 32), (64, 96), (128, 64)])
 def test_rgms_blocks_of_512_rows(gpu_lib, d_in, d_out):
     """Many rows and few entries per relation: the largest row blocks, the last one with part of its rows."""
     say(f"[rgms 512] d_in={d_in} d_out={d_out}")
-    test_rgms_tile_edges(gpu_lib, 512 * 512 + 77, 8, d_in, d_out, 0)
-    test_rgms_non_finite_rows_stay_with_their_rows(gpu_lib, 512 * 512 + 1, 8, d_in, d_out, 0)
+    assert check_tile_edges(gpu_lib, 512 * 512 + 77, 8, d_in, d_out, 0)["row_block"] == 512
+    rng = np.random.default_rng(d_in)
+    counts = (rng.random(8 * (512 * 512 + 1)) < 0.03).astype(np.int64)    # (16 entries a relation and block)
+    assert check_non_finite_rows(gpu_lib, 512 * 512 + 1, 8, d_in, d_out, 0, counts, rng)["row_block"] == 512
