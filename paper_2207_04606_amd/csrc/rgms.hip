@@ -549,14 +549,16 @@ __global__ __launch_bounds__(256) void k_pair_entries(int64_t nnz, const int32_t
 // larger blocks divided into items were tried and lose more in global atomics than fuller tiles gain (27,163 rows,
 // 64 x 64: 0.042 -> 0.093 ms).
 // Blocks of 512 rows take the LDS of a CU and 16 wavefronts; what they win is W[r] read for half as many tiles.  They need two
-// workgroups' worth of them per CU (158,566 rows: 0.81 times as fast as with 256) and no workspace, whose tiles take turns (0.79 to
-// 1.08); then 1.0 to 1.21 times as fast as 256 (40 graphs; 1.9 M rows, 96 relations, 5.7 M entries, 32 x 32: 0.527 -> 0.458 ms).
+// workgroups' worth of them per CU (158,566 rows: 0.81 times as fast as with 256), no workspace, whose tiles take turns (0.79 to
+// 1.08), and fewer than 40 entries for every (relation, block) even so.  78 graphs and feature sizes, against 256 rows: up to 24 entries
+// 1.10 times as fast (0.97 to 1.21), to 40 1.03 (0.94 to 1.10; 32 x 32 features 0.98), to 64 0.98 (0.87 to 1.05).  1.9 M rows, 96
+// relations, 5.7 M entries, 32 x 32, 16 entries: 0.527 -> 0.458 ms.
 int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
   int s = kMinLog2Block;
-  while (((int64_t)1 << s) * nnz < 32 * n_rows * n_rel && s < kMaxLog2Block - (workspace ? 1 : 0) &&
-         (n_rows >> (s + 1)) >= (s + 1 < kMaxLog2Block ? 160 : 512))
-    ++s;
-  return s;
+  while (((int64_t)1 << s) * nnz < 32 * n_rows * n_rel && s < kMaxLog2Block - 1 && (n_rows >> (s + 1)) >= 160) ++s;
+  const bool large = s == kMaxLog2Block - 1 && !workspace && (n_rows >> kMaxLog2Block) >= 512 &&
+                     ((int64_t)1 << kMaxLog2Block) * nnz < 40 * n_rows * n_rel;
+  return large ? kMaxLog2Block : s;
 }
 
 template <int TIN, bool ORDERED, bool WIDE_X>

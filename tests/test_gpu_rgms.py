@@ -250,3 +250,19 @@ def test_rgms_blocks_of_512_rows(gpu_lib, d_in, d_out):
     rng = np.random.default_rng(d_in)
     counts = (rng.random(8 * (512 * 512 + 1)) < 0.03).astype(np.int64)    # (16 entries a relation and block)
     assert check_non_finite_rows(gpu_lib, 512 * 512 + 1, 8, d_in, d_out, 0, counts, rng)["row_block"] == 512
+
+
+@pytest.mark.parametrize("mean,rows", [(0.03, 512), (0.07, 512), (0.085, 256), (0.11, 256), (0.2, 256), (0.3, 128), (1.1, 32)])
+def test_rgms_rows_of_a_block(gpu_lib, mean, rows):
+    """So many that 32 entries are in a relation's part of a block, and 512 only where even those have fewer than 40."""
+    n, n_rel = 512 * 512 + 5, 4
+    counts = np.random.default_rng(1).poisson(mean, n_rel * n)
+    w = workloads.random_csr(n_rel * n, n, counts, 1, 1)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    h = gpu_lib.sptir_rgms_build(n_rel, n, n, dev(w.indptr), dev(w.indices), dev(w.values))
+    assert gpu_lib.sptir_rgms_info(h)["row_block"] == rows
+    h.destroy()
+    if rows == 512:
+        h = gpu_lib.sptir_rgms_build(n_rel, n, n, dev(w.indptr), dev(w.indices), dev(w.values), -1, 32)
+        assert gpu_lib.sptir_rgms_info(h)["row_block"] == 256          # (tiles that take turns)
+        h.destroy()
