@@ -111,7 +111,7 @@ _hip = None
 class _SpmmTimes(ctypes.Structure):
     _fields_ = [("ms_lists", ctypes.c_float), ("ms_heavy", ctypes.c_float), ("ms_reduce", ctypes.c_float),
                 ("n_list_launches", ctypes.c_int32), ("n_heavy_launches", ctypes.c_int32),
-                ("n_reduce_launches", ctypes.c_int32)]
+                ("n_reduce_launches", ctypes.c_int32), ("list_waves", ctypes.c_int32), ("tile_floats", ctypes.c_int32)]
 
 
 EXPORTED_SYMBOLS = ("sptir_spmm_timed", "sptir_roof_gather", "sptir_roof_lds_gather", "sptir_roof_fma", "sptir_set_allocator", "sptir_release_scratch", "sptir_hyb_build", "sptir_hyb_build_ex", "sptir_hyb_search", "sptir_default_bucket_log2", "sptir_gather_offsets_fit_32", "sptir_spmm",

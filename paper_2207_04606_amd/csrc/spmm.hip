@@ -929,6 +929,7 @@ struct LaunchTimers {
   enum Tag { kStart = 0, kLists = 1, kHeavy = 2, kReduce = 3 };
   std::vector<std::pair<hipEvent_t, int>> marks;
   int launches[4] = {0, 0, 0, 0};
+  int list_waves = 1, tile_floats = 0;
   bool failed = false;
   void mark(hipStream_t stream, int tag, int n_launches) {
     hipEvent_t e = nullptr;
@@ -981,7 +982,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   partial_feat = std::min(partial_feat, all_tiles * g.vec * g.lg);  // rows no wider than Y
   int n_list_launches = 0;
   bool heavy_with_lists = false;
-  if (timers) timers->mark(stream, LaunchTimers::kStart, 0);
+  if (timers) { timers->mark(stream, LaunchTimers::kStart, 0); timers->tile_floats = g.vec * g.lg; }
   const bool idx32_all = offsets_fit_32(h->n_cols, feat);
   // the launch over the heavy lists for the features feat0 .. feat0 + width - 1 (width <= partial_feat)
   auto heavy_launch_shape = [&](int feat0, int width, HeavyArgs* ha, Geometry* gh) -> bool {
@@ -1107,6 +1108,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) {
             launch_shared_lists(v, gs, waves, lds_bytes / kHybWaves * waves, stream, a);
           });
+          if (timers) timers->list_waves = waves;
         } else {
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, lds_bytes, stream, a); });
         }
@@ -1162,6 +1164,7 @@ extern "C" sptir_status_t sptir_spmm_timed(const sptir_hyb_t* h, const float* X,
   t.n_list_launches = timers.launches[LaunchTimers::kLists];
   t.n_heavy_launches = timers.launches[LaunchTimers::kHeavy];
   t.n_reduce_launches = timers.launches[LaunchTimers::kReduce];
+  t.list_waves = timers.list_waves; t.tile_floats = timers.tile_floats;
   *out = t;
   return SPTIR_OK;
 }

@@ -43,6 +43,12 @@ def test_shared_lists(gpu_lib, feat, one_value, wide):
             Y = torch.full((n_rows, feat), float("nan"), device="cuda")
             gpu_lib.sptir_spmm(hyb, d.X, Y)
             assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"{n_rows}x{n_cols} {kind} c={c}")
+            timed = torch.full_like(Y, float("nan"))
+            times = gpu_lib.sptir_spmm_timed(hyb, d.X, timed)
+            assert torch.equal(Y, timed)
+            several_launches = n_cols > 100_000 and c == 3
+            assert (times["list_waves"] > 1) != several_launches and times["list_waves"] <= 8
+            assert times["tile_floats"] == (64 if n_cols > 100_000 else 32 if feat > 16 else 16 if feat >= 4 else 4)
             again = torch.full_like(Y, float("nan"))
             gpu_lib.sptir_spmm_noalloc(hyb, d.X, again)
             assert torch.equal(Y, again)
