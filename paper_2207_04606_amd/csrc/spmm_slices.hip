@@ -44,6 +44,10 @@ constexpr int kAhead = 2;                               // steps between the req
 // a band, products against no slices: up to 1.5 slots 1.65 times as fast (0.86 to 3.2), to 2 1.49 (0.93 to 3.0; 1.0 and more from 12 M
 // long entries on), to 2.5 1.33 (0.79 to 3.2), to 3.7 1.06 (0.6 to 2.5).
 constexpr double kMostSlotsPerEntry = 2.0;
+// Nor where one slice has more than so many times the mean's steps: a panel is one workgroup there, and panels small enough for all
+// CUs to have some load every other slice for little.  80 graphs of 13 M entries and more, columns skewed, hot in a range, in bands or
+// uniform, products against no slices: 1.31 times as fast up to 16 (0.91 to 2.8), beyond 0.80 and 0.91.
+constexpr double kMostOfMean = 16.0;
 constexpr size_t kSliceLds = sizeof(float4) * kLanes * (kSliceCols + 1);
 
 struct Unit {
@@ -449,8 +453,16 @@ int64_t spmm_slices_steps(const SpmmSliceBuild& b) {
   return n_steps;
 }
 
+// The share of all steps that the slice with most of them has
+static double hottest_slice(const SpmmSliceBuild& b, int64_t n_steps) {
+  const int32_t* slice_steps = (const int32_t*)b.host.p + b.n_blocks;
+  return *std::max_element(slice_steps, slice_steps + b.n_slices) / (double)std::max<int64_t>(1, n_steps);
+}
+
 bool spmm_slices_even(const SpmmSliceBuild& b, int64_t long_nnz) {
-  return (double)spmm_slices_steps(b) * (8 * kBlockRows) <= kMostSlotsPerEntry * (double)long_nnz;
+  const int64_t n_steps = spmm_slices_steps(b);
+  return (double)n_steps * (8 * kBlockRows) <= kMostSlotsPerEntry * (double)long_nnz &&
+         hottest_slice(b, n_steps) * b.n_slices <= kMostOfMean;
 }
 
 // Then: panels, units and the handle's memory.  Host work only; where it does not succeed nothing has been enqueued.
@@ -465,6 +477,9 @@ sptir_status_t spmm_slices_plan(SpmmSliceBuild* b, int32_t feat_hint, bool with_
   constexpr double kLoad = 64.0, kMostWorth = 2048.0, kLeastWorth = 128.0;
   const double tiles = std::max(1, ((feat_hint > 0 ? std::min(feat_hint, kPartialFeat) : 64) + kTileFloats - 1) / kTileFloats);
   const double worth = std::max(kLeastWorth, std::min(kMostWorth, (double)n_steps * tiles / (256.0 * 4.0)));
+  // ... and no more in the hottest slice than half of what a CU has to do.  (79 of those graphs against panels without this limit:
+  // 1.09 times as fast in the mean, 0.88 to 1.8; uniform columns alike.)
+  const double panel_most = std::min(worth * b->n_slices, 0.5 * n_steps * tiles / 256.0 / hottest_slice(*b, n_steps));
   std::vector<Panel> panels;
   std::vector<int32_t> panel_of((size_t)b->n_blocks);
   std::vector<double> panel_steps;
@@ -473,7 +488,7 @@ sptir_status_t spmm_slices_plan(SpmmSliceBuild* b, int32_t feat_hint, bool with_
     Panel p{at, 0, 0, (int32_t)words, 0, 0};
     double steps = 0;
     while (at < b->n_blocks && p.n_blocks < kMaxPanelBlocks &&
-           (p.n_blocks % kWavesHere != 0 || p.n_blocks == 0 || steps < worth * b->n_slices)) {
+           (p.n_blocks % kWavesHere != 0 || p.n_blocks == 0 || steps < panel_most)) {
       steps += block_steps[at];
       panel_of[(size_t)at] = (int32_t)panels.size();
       ++at; ++p.n_blocks;

@@ -94,8 +94,9 @@ def test_rows_of_x_that_are_not_finite_stay_with_their_rows(gpu_lib, one_value):
     assert np.array_equal(got[long_rows], want[long_rows])
 
 
-def large_matrix(n_rows, share, n_cols=40000, n_groups=10, deg=1600, feat=8):
-    """Rows of like length, a few longer; `share` of a row's entries in one of n_groups ranges of columns, the others anywhere."""
+def large_matrix(n_rows, share, n_cols=40000, n_groups=10, deg=1600, feat=8, one_range=False):
+    """Rows of like length, a few longer; `share` of a row's entries in one of n_groups ranges of columns (the same one for all
+    rows, or its own), the others anywhere."""
     rng = np.random.default_rng(n_rows)
     lens = rng.integers(deg - 60, deg, n_rows)
     lens[rng.choice(n_rows, 5, replace=False)] = 5 * deg
@@ -105,7 +106,7 @@ def large_matrix(n_rows, share, n_cols=40000, n_groups=10, deg=1600, feat=8):
     b = workloads.random_csr(n_rows, n_cols, lens - inside, 2, feat)
     row_of = lambda w: np.repeat(np.arange(n_rows, dtype=np.int64), np.diff(w.indptr))
     ra, rb = row_of(a), row_of(b)
-    key = np.unique(np.concatenate([ra * n_cols + ra % n_groups * width + a.indices, rb * n_cols + b.indices]))
+    key = np.unique(np.concatenate([ra * n_cols + (0 if one_range else ra % n_groups * width) + a.indices, rb * n_cols + b.indices]))
     rows = key // n_cols
     w = b
     w.indptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n_rows))]).astype(np.int32)
@@ -196,3 +197,22 @@ def test_slices_that_find_no_memory_are_left_out(gpu_lib):
         assert len(binding._torch_blocks) == before, "a build that failed keeps memory"
     finally:
         sptir.sptir_set_allocator(False)
+
+
+@pytest.mark.parametrize("share,sliced", [(0.1, True), (0.6, False)])
+def test_slices_only_where_none_is_much_hotter_than_the_mean(gpu_lib, share, sliced):
+    """Entries in one range of columns: panels as small as it takes for all CUs to have some of the hot slice, and no slices where
+    it has more than 16 times the mean's entries, unless they are asked for."""
+    w = large_matrix(9000, share, n_cols=82000, n_groups=34, one_range=True)
+    say(f"[long rows] hot share={share} nnz={w.indices.size}")
+    assert w.indices.size > 12_700_000
+    d = upload(w)
+    Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+    Y, _, n_long = build_and_multiply(gpu_lib, w, d, {})
+    assert n_long == (w.n_rows if sliced else 0)
+    assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"hot share {share}")
+    if not sliced:
+        assert torch.equal(Y, build_and_multiply(gpu_lib, w, d, {"column_slices": 2})[0])
+        Y, _, n_long = build_and_multiply(gpu_lib, w, d, {"column_slices": 1})
+        assert n_long == w.n_rows
+        assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"hot share {share}, asked for")
