@@ -15,7 +15,7 @@ constexpr int kColumnBits = 13;          // of a column inside its slice (4 floa
 constexpr int kLdsMostFeat = 256;        // floats of a row that the eight lanes of a group hold in eight float4 each
 
 // Row to row in LDS, in float4: where all rows would begin in the same half of the 64 banks, half a row of banks more, or the
-// lane groups meet in it (random 512-byte rows: 75 TB/s, 83 if half of them begin in the other half).
+// lane groups meet in it (random 512-byte rows: 77 TB/s, 85 if half of them begin in the other half).
 constexpr int slice_stride(int quads) { return quads % 16 == 0 ? quads + 8 : quads; }
 
 // Columns per slice of a plan made for `feat` features; 0: no slices.

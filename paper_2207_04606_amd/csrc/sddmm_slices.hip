@@ -1,8 +1,8 @@
 // SDDMM of the long rows of a plan, from column slices in LDS.
 //
 // A column of A costs its row of Yt once per entry, and through L1 no more than 32 TB/s of them arrive whatever the caches
-// hold (40 at 64 bytes a cycle and CU).  LDS delivers twice that and more: random 128-byte rows at 71, random 512-byte rows
-// at 75 TB/s (123 bytes a cycle and CU).  Where rows are so long that each has entries in every slice of columns that
+// hold (40 at 64 bytes a cycle and CU).  LDS delivers twice that and more: random 128-byte rows at 76, random 512-byte rows
+// at 77 TB/s (125 bytes a cycle and CU).  Where rows are so long that each has entries in every slice of columns that
 // fits LDS, a workgroup loads the slice's rows of Yt once and takes all of its entries from there.
 //
 // Mapping.  `width` columns make a slice: as many rows of Yt as kSliceBytes hold.  The entries of a (row, slice) pair are
@@ -11,11 +11,11 @@
 // group holds floats 4*(8t + fl) .. +3 of the segment's row of X, reads the same floats of an entry's column from LDS, and
 // the eight partial sums of a lane meet as in k_sddmm: the products of an entry, and their order, are those of the other
 // kernels, so its result is the same bit for bit.  Rows of X come from L2, one per segment (an eighth of the bytes of the entries).
-// A unit of work is a slice and a range of the long rows; units go by range of rows first, so that the rows of X
+// A unit of work is a slice and a range of the long rows, or a piece of what they have; units go by range of rows first, so that the rows of X
 // that an XCD's workgroups want at a time stay in its L2, and by neighbouring slices inside an XCD, so that the lines of values
 // and results that pieces share do.
-// 232,965 rows, 114.6 M entries, 128 features: 70 M entries in 0.80 ms (11.4 ps an entry, 30 in k_sddmm; LDS busy 55 % and
-// vector ALU 57 % of it); segments not kept apart by range of rows 1.20 ms, slices dealt to the XCDs in turn 1.04 (twice the misses).
+// 232,965 rows, 114.6 M entries, 128 features: 70 M entries in 0.78 ms (11.1 ps an entry, 30 in k_sddmm): 46 TB/s of gathered
+// rows where LDS gives 85, vector ALU issuing 54 % of it, bank conflicts 24 %; segments not kept apart by range of rows 1.20 ms, slices dealt to the XCDs in turn 1.04 (twice the misses).
 #include <algorithm>
 #include <new>
 #include <vector>

@@ -20,8 +20,8 @@
 // The fourth lane of a tail reads (and writes) the last four floats of the
 // row, so any feature size of four or more uses 16-byte accesses; they need
 // only 4-byte alignment.
-// Measured (169,343 rows, 1,166,243 entries, 128 features): 0.65 -> 0.117 ms on
-// operands that change from call to call (0.104 on the same ones), 5.1 TB/s of
+// Measured (169,343 rows, 1,166,243 entries, 128 features): 0.65 -> 0.114 ms on
+// operands that change from call to call (0.107 on the same ones), 5.2 TB/s of
 // gathered rows of which a quarter hit L2; the memory-side cache delivers 7.9 at
 // random.
 #include <algorithm>

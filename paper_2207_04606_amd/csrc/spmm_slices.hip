@@ -1,7 +1,7 @@
 // SpMM of the long rows of a hyb handle, from column slices in LDS.
 //
 // A gathered row of X costs L1 time wherever it comes from: 32 TB/s of them arrive from an XCD's L2, 28 in k_spmm_heavy.  LDS
-// delivers random rows of 128 bytes at 71 TB/s, of 64 at 67, of 32 at 56.  A row of A that has entries in every slice of columns
+// delivers random rows of 128 bytes at 76 TB/s, of 64 at 70, of 32 at 58.  A row of A that has entries in every slice of columns
 // that fits LDS can take its rows of X from there.
 //
 // Mapping.  A slice is kSliceCols columns, their features a tile of 16 (64 bytes: narrower tiles hold more columns, so that a
@@ -16,8 +16,9 @@
 // row of zeros after the slice's last (a fifth of what is read; the last step may have half).  The steps of a wavefront follow each
 // other from slice to slice, whatever the block, and are asked for two steps ahead.
 //
-// 232,965 rows, 114.6 M entries, 128 features: the call 2.38 -> 1.79 ms.  80 M entries in 0.95 ms, 43 TB/s of gathered rows (28.5
-// in k_spmm_heavy), LDS busy 80 % of it, vector ALU 75 %; the rest is loading slices and wavefronts that wait there for the last.
+// 232,965 rows, 114.6 M entries, 128 features: the call 2.39 -> 1.82 ms.  87 M entries in 0.99 ms, 45 TB/s of gathered rows (28.5
+// in k_spmm_heavy; 1.2 times as many slots), vector ALU issuing 67 % of it, bank conflicts 34 %; the rest is loading slices and
+// wavefronts that wait there for the last.
 #include <algorithm>
 #include <cstring>
 #include <new>
