@@ -42,15 +42,38 @@ constexpr int64_t slice_min_entries(int64_t feat) {
   return (feat <= 64 || feat % 4 ? (int64_t)1 << 29 : (int64_t)1 << 27) / feat;
 }
 
-// Do slices pay for n_long rows with that many entries together?  Where Yt comes close to fitting an XCD's 4 MB of L2, the lists
+// Do slices pay for n_long rows with that many entries together?  Where Yt comes close to fitting an XCD's 4 MB of L2 the lists
 // gather it at 17 to 20 TB/s, and slices, whose segments each ask for a row of X, are no faster; unless there are so few long rows
-// that X stays near as well.  uneven: a slice and part has more than two CUs' share of the segments; it is cut, but hot columns
-// are those the lists find in the caches too.  420 graphs, 37 to 256 features, columns uniform, skewed, hot in a range, in
-// communities and in a band, where slice_min_entries() is met: Yt of 7 MB and more (uneven: 12) 1.27 times as fast (0.92 to 2.6), the
-// others 0.85 (0.54 to 1.6).  40 dense matrices: long rows of X within 512 KB 1.3 times as fast (0.92 to 2.2), more 0.99 (0.35 to 2.2).
-constexpr bool slices_pay(int64_t n_cols, int64_t feat, int64_t n_long, int64_t long_nnz, bool uneven) {
+// that X stays near as well (40 dense matrices: within 512 KB 1.3 times as fast, 0.92 to 2.2; more 0.99, 0.35 to 2.2).
+constexpr bool few_long_rows(int64_t feat, int64_t n_long) { return n_long * feat <= (int64_t)1 << 17; }
+constexpr bool slices_pay(int64_t n_cols, int64_t feat, int64_t n_long, int64_t long_nnz) {
   if (long_nnz < slice_min_entries(feat)) return false;
-  return n_cols * feat >= (uneven ? (int64_t)12 << 18 : (int64_t)7 << 18) || n_long * feat <= (int64_t)1 << 17;
+  return few_long_rows(feat, n_long) || n_cols * feat >= (int64_t)7 << 18;  // (floats: 7 MB of Yt)
+}
+
+// And once the segments have been counted?  `units` are the pairs of a slice and a part of the rows that have any.  From 12 MB of Yt on,
+// where a quarter of the slices has half of the segments, columns that the lists find in the caches too, or where segments are short
+// and a lane's last float4 is partly used.  Never for fewer units than leave two CUs in five idle.  620 graphs, 37 to 256
+// features, columns uniform, skewed, hot in a range, in communities and in a band, all with slice_min_entries(): where this takes them
+// 1.27 times as fast as lists (0.92 to 2.6), elsewhere 0.9 (0.54 to 2).
+constexpr bool slices_pay_as_counted(int64_t n_cols, int64_t feat, int64_t n_long, int64_t long_nnz, int64_t units, int64_t n_segs,
+                                     int32_t n_slices, int32_t half_in) {
+  if (!slices_pay(n_cols, feat, n_long, long_nnz)) return false;
+  if (few_long_rows(feat, n_long)) return true;
+  const bool hot = 4 * (int64_t)half_in < n_slices, is_short = feat % 32 != 0 && 10 * long_nnz < 47 * n_segs;
+  return units >= 160 && n_cols * feat >= (int64_t)(hot || is_short ? 12 : 7) << 18;
+}
+
+// The fewest slices that have half of the segments.  begin: see slice_units().
+inline int32_t slices_of_half(const std::vector<int32_t>& begin, int32_t n_slices, int64_t parts) {
+  std::vector<int64_t> segs((size_t)n_slices, 0);
+  for (int64_t part = 0; part < parts; ++part)
+    for (int32_t s = 0; s < n_slices; ++s) segs[(size_t)s] += begin[(size_t)(part * n_slices + s + 1)] - begin[(size_t)(part * n_slices + s)];
+  std::sort(segs.begin(), segs.end(), [](int64_t x, int64_t y) { return x > y; });
+  int64_t sum = 0;
+  int32_t n = 0;
+  while (n < n_slices && 2 * sum < begin.back() - begin.front()) sum += segs[(size_t)n++];
+  return n;
 }
 
 // Is a row that begins and ends there long?  One that is not inside the entries is none: nothing is read for it here, and the

@@ -384,7 +384,7 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
     if (!hip(hipMemcpyAsync(&n_long, seq_base + n_seq, sizeof(n_long), hipMemcpyDeviceToHost, stream), "hipMemcpyAsync") ||
         !read_back(&long_nnz, entries, sizeof(long_nnz)))
       return;
-    if (n_long <= 0 || (int64_t)long_nnz > csr->nnz || !slices_pay(n_cols, feat, n_long, (int64_t)long_nnz, false)) return;
+    if (n_long <= 0 || (int64_t)long_nnz > csr->nnz || !slices_pay(n_cols, feat, n_long, (int64_t)long_nnz)) return;
 
     int32_t* rows = (int32_t*)temporary(sizeof(int32_t) * (size_t)n_long);
     int32_t* bound = (int32_t*)temporary(sizeof(int32_t) * ((size_t)n_slices + 1) * (size_t)n_long);
@@ -413,7 +413,7 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
     if (is_bad) return;
 
     std::vector<int32_t> begin(n_units + 1);
-    int64_t at = 0, largest = 0;
+    int64_t at = 0, used = 0;
     for (size_t u = 0; u < n_units; ++u) {
       begin[u] = (int32_t)at;
       for (int k = 0; k < kClasses; ++k) {
@@ -421,12 +421,12 @@ sptir_status_t sddmm_slices_build(const sptir_csr_t* csr, int32_t feat_hint, spt
         count[u * kClasses + k] = (int32_t)at;
         at += n;
       }
-      largest = std::max(largest, at - begin[u]);
+      used += at > begin[u];
     }
     begin[n_units] = (int32_t)at;
-    const int64_t share = (at + kCus - 1) / kCus;  // of a CU
-    if (!slices_pay(n_cols, feat, n_long, (int64_t)long_nnz, largest > 2 * share)) return;
-    const std::vector<SliceUnit> units = slice_units(begin, n_slices, parts, share);
+    if (!slices_pay_as_counted(n_cols, feat, n_long, (int64_t)long_nnz, used, at, n_slices, slices_of_half(begin, n_slices, parts)))
+      return;
+    const std::vector<SliceUnit> units = slice_units(begin, n_slices, parts, (at + kCus - 1) / kCus);
     if (units.size() > 0x7FFFFFFF) return;
     s.n_segs = at; s.n_units = (int64_t)units.size();
     s.width = width; s.nnz = (int64_t)long_nnz;

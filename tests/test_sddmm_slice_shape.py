@@ -55,20 +55,26 @@ def test_the_slice_fits_lds(choices):
     assert (width[hint > 256] == 0).all() and (width[hint <= 256] >= 1).all()
 
 
-@pytest.mark.parametrize("n_cols,feat,n_long,long_nnz,even,uneven", [
-    (9696, 96, 9000, 1_930_000, 0, 0),          # Yt of 3.7 MB: lists gather it from L2 (42 us, 66 with slices)
-    (7873, 160, 7800, 2_530_000, 0, 0),
-    (25117, 96, 23000, 13_170_000, 1, 0),       # 9.6 MB
-    (34000, 96, 30000, 14_000_000, 1, 1),       # 13 MB
-    (232965, 128, 60000, 70_000_000, 1, 1),
-    (3001, 128, 531, 1_200_000, 1, 1),          # few long rows
-    (3001, 128, 531, 1_000_000, 0, 0),          # fewer entries than slices need
-    (232965, 32, 60000, 70_000_000, 0, 0),      # too few features
-    (2**31 - 1, 256, 2**31 - 1, 2**31 - 1, 1, 1),
+@pytest.mark.parametrize("n_cols,feat,n_long,long_nnz,units,per_segment,slices,half_in,before,after", [
+    (9696, 96, 9000, 1_930_000, 900, 5.7, 24, 12, 0, 0),     # Yt of 3.7 MB: lists gather it from L2 (42 us, 66 with slices)
+    (7873, 160, 7800, 2_530_000, 900, 5.7, 24, 12, 0, 0),
+    (25117, 96, 23000, 13_170_000, 2074, 6.2, 61, 30, 1, 1),  # 9.6 MB
+    (25117, 96, 23000, 13_170_000, 2074, 6.2, 61, 15, 1, 0),  # (a hot range)
+    (34000, 96, 30000, 14_000_000, 2074, 6.2, 83, 1, 1, 1),  # 13 MB
+    (25117, 96, 23000, 13_170_000, 2074, 3.5, 61, 16, 1, 1),  # short segments: only where a float4 is partly used
+    (25000, 100, 23000, 13_170_000, 2074, 3.5, 64, 32, 1, 0),
+    (25000, 100, 23000, 13_170_000, 2074, 4.8, 64, 32, 1, 1),
+    (34000, 100, 30000, 14_000_000, 2074, 3.5, 86, 43, 1, 1),
+    (33007, 128, 1100, 1_050_000, 134, 5.5, 134, 67, 1, 0),    # too few units (86 us, 115 with slices)
+    (33007, 128, 1100, 1_050_000, 160, 5.5, 134, 67, 1, 1),
+    (232965, 128, 60000, 70_000_000, 3000, 5.9, 940, 470, 1, 1),
+    (3001, 128, 531, 1_200_000, 13, 7.9, 13, 1, 1, 1),      # few long rows
+    (3001, 128, 531, 1_000_000, 13, 7.9, 13, 1, 0, 0),      # fewer entries than slices need
+    (232965, 32, 60000, 70_000_000, 3000, 5.9, 940, 470, 0, 0),  # too few features
+    (2**31 - 1, 256, 2**31 - 1, 2**31 - 1, 2**31 - 1, 1.0, 2**31 - 1, 2**31 - 1, 1, 1),
 ])
-def test_where_slices_are_chosen(rules, n_cols, feat, n_long, long_nnz, even, uneven):
-    assert rules("pay", n_cols, feat, n_long, long_nnz, 0) == [even]
-    assert rules("pay", n_cols, feat, n_long, long_nnz, 1) == [uneven]
+def test_where_slices_are_chosen(rules, n_cols, feat, n_long, long_nnz, units, per_segment, slices, half_in, before, after):
+    assert rules("pay", n_cols, feat, n_long, long_nnz, units, int(long_nnz / per_segment), slices, half_in).tolist() == [before, after]
 
 
 @pytest.mark.parametrize("n_slices,parts,hot,most", [(1, 1, 0, 1), (1, 3, 0, 40), (7, 2, 3, 50), (8, 1, 7, 64), (61, 9, 5, 300),
@@ -85,6 +91,8 @@ def test_units_hold_every_segment_once(rules, n_slices, parts, hot, most):
     units = rules("units", n_slices, parts, most, text=" ".join(map(str, begin))).reshape(-1, 3)
     slice_of = np.repeat(np.tile(np.arange(n_slices), parts), n.ravel())
     per_xcd = -(-n_slices // 8)
+    by_load = np.sort(n.sum(axis=0))[::-1].cumsum()
+    assert rules("half", n_slices, parts, text=" ".join(map(str, begin))) == [1 + int((2 * by_load < n.sum()).sum())]
     seen = np.zeros(begin[-1], dtype=int)
     load = np.zeros(8, dtype=int)
     for i, (s, lo, hi) in enumerate(units):
