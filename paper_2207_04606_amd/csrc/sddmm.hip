@@ -94,19 +94,27 @@ __device__ __forceinline__ int count_not_above(int ascending, int v) {
 // (The second launch bound tells the register allocator how many wavefronts per SIMD to leave room for; left
 //  alone it spreads the pipeline stages over 280+ registers although 16*T + 30 are live at any time.)
 enum RowEnd { kWhole, kQuads, kTail };
-// Where the entries come from: CSR order, a plan, or a plan whose lists the memory-side cache does not hold from call to call.
-// Those are read, and B is written, past the rows of Yt that L2 is to keep (45 M listed entries 2636 -> 2560 us; lists that the
-// cache does hold would come from memory every time: 7.9 M entries 70 -> 105 us).
-enum Source { kCsr, kPlan, kLargePlan };
+// Where the entries come from: CSR order, a plan, one of few entries (below; four float4 only), or one whose lists the memory-side
+// cache does not hold from call to call.  Those are read, and B is written, past the rows of Yt that L2 is to keep (45 M listed
+// entries 2636 -> 2560 us; lists that the cache does hold would come from memory every time: 7.9 M entries 70 -> 105 us).
+enum Source { kCsr, kPlan, kShortPlan, kLargePlan };
 constexpr int64_t kLargeList = 24 << 20;  // entries: 12 bytes each, 256 MB and more
 template <int T, Source SOURCE>
-constexpr int sddmm_waves() { return T == 4 && SOURCE != kCsr ? 3 : T <= 4 ? 4 : 2; }
+constexpr int sddmm_waves() { return T == 4 && (SOURCE == kPlan || SOURCE == kLargePlan) ? 3 : T <= 4 ? 4 : 2; }
 // Rows of X a wavefront stages per chunk with a plan.  A chunk of more rows loads them entry by entry: with 16 for four float4 half of
 // the chunks of short pieces did (45 M listed entries of 232,965 rows, 128 features, the call: 16 rows 2.56 ms, 20 2.49, 26 2.47, 32,
 // which leave room for 8 wavefronts a CU, 2.60).  One float4: none 632, 24 600 us (50 M entries); five: 8 1370, 16 1200 us (25 M).
-// Two: none, as 16 to 32 lose up to 15 % where pieces are long.
-template <int T>
-constexpr int sddmm_staged_rows() { return T == 1 ? 24 : T == 2 ? 0 : T == 3 ? 24 : T == 4 ? 26 : 16; }
+// Two: none, as 16 to 32 lose up to 15 % where pieces are long.  The 26 rows leave room for three wavefronts a SIMD, which pays where
+// gathers miss L2 or the runs are many turns of the GPU.  Elsewhere 16 rows and four wavefronts: 1.9 M entries of 45,461 rows, 128
+// features, 102 against 84 us, 4.1 M of 21,584 108 against 95; but 5.9 M of 112,672 rows, 7 MB of Yt a partition, 213 against 252.
+// (42 plans of up to 8.4 M entries and 4 MB: 0.96 times as fast with 26 rows, 0.80 to 1.09; 15 of more than 4 MB 1.04, 0.98 to 1.19;
+//  30 from 8.4 M entries on 1.09, 0.95 to 1.38.)
+template <int T, Source SOURCE>
+constexpr int sddmm_staged_rows() {
+  return T == 1 ? 24 : T == 2 ? 0 : T == 3 ? 24 : T == 4 && SOURCE != kShortPlan ? 26 : 16;
+}
+constexpr int64_t kShortList = 8 << 20;       // entries
+constexpr int64_t kShortPartBytes = 4 << 20;  // rows of Yt of a partition
 template <int T, RowEnd END, bool MANY, Source SOURCE>
 __global__ __launch_bounds__(64 * kSddmmWaves, (sddmm_waves<T, SOURCE>())) void k_sddmm(SddmmArgs a) {
   constexpr bool PLAN = SOURCE != kCsr;
@@ -199,7 +207,7 @@ __global__ __launch_bounds__(64 * kSddmmWaves, (sddmm_waves<T, SOURCE>())) void 
   // different rows (one per lane group), where a reload inside the entry loop costs the address path a whole
   // instruction even if a single lane group asks for it - and in partition order a row lasts only a few entries.
   // (CSR order: no gain, measured.)
-  constexpr int kStage = MANY || !PLAN ? 0 : sddmm_staged_rows<T>();
+  constexpr int kStage = MANY || !PLAN ? 0 : sddmm_staged_rows<T, SOURCE>();
   __shared__ __align__(16) float x_stage[kSddmmWaves][kStage > 0 ? kStage : 1][32 * T];
   __shared__ int row_table[kSddmmWaves][kStage > 0 ? kStage : 1];
   float4 x[T];
@@ -214,7 +222,7 @@ __global__ __launch_bounds__(64 * kSddmmWaves, (sddmm_waves<T, SOURCE>())) void 
     if constexpr (PLAN) c.val = a.values[c.pos];
     // Gathers run kAhead entries ahead of the multiplies; the scheduling barriers keep the compiler from
     // hoisting all eight entries' loads to the top (T*8 float4 of registers).
-    constexpr int kAhead = PLAN && T == 4 ? 3 : 2;
+    constexpr int kAhead = T == 4 && (SOURCE == kPlan || SOURCE == kLargePlan) ? 3 : 2;
     float p[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) p[i] = 0.f;
@@ -630,7 +638,9 @@ extern "C" sptir_status_t sptir_sddmm(const sptir_sddmm_plan_t* p, const float* 
     a.nnz = p->nnz - p->slices.nnz;
     if (a.nnz == 0) return SPTIR_OK;
     const dim3 grid((unsigned)(8 * ((p->max_runs_per_xcd + kSddmmWaves - 1) / kSddmmWaves)));
+    const bool short_list = a.nnz < kShortList && (int64_t)p->w * feat * (int64_t)sizeof(float) <= kShortPartBytes;
     if (a.nnz >= kLargeList) launch_sddmm<kLargePlan>(a, grid, stream);
+    else if (short_list && feat > 96 && feat <= 128) launch_stripes<kShortPlan, 4>(a, grid, stream);
     else launch_sddmm<kPlan>(a, grid, stream);
   }
   SPTIR_HIP(hipGetLastError());

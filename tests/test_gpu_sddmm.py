@@ -196,6 +196,25 @@ def test_sddmm_rows_of_a_chunk_and_row_ends(gpu_lib, gap, feat):
     assert_b_close(run_sddmm_plan(gpu_lib, w, Xr, w.X, 8)[0], Br, Mr, f"plan gap={gap} feat={feat}")
 
 
+@pytest.mark.parametrize("feat", [96, 97, 100, 127, 128, 129])
+@pytest.mark.parametrize("past", [0, 1])
+def test_sddmm_plan_lists_on_both_sides_of_l2(gpu_lib, past, feat):
+    """Chunks of 64 entries of about 16 rows, of about 26 and of any number, all in one partition whose rows of Yt are 4 MB at most or
+    one row more: with four float4 a lane other numbers of rows are staged there.  The bits are those of CSR order."""
+    say(f"[sddmm L2] past={past} feat={feat}")
+    width = (4 << 20) // (4 * feat) + past
+    deg = np.concatenate([np.full(160, 4), np.tile([2, 3], 130), np.full(70, 64 // 15), np.random.default_rng(feat).integers(0, 9, 300)])
+    w = workloads.random_csr(deg.size, width, deg, feat + past, feat)
+    w.n_cols = 8 * width
+    w.X = np.random.default_rng(past).standard_normal((w.n_cols, feat)).astype(np.float32)
+    Xr = left_operand(w, feat, 3)
+    got, info = run_sddmm_plan(gpu_lib, w, Xr, w.X, 8, feat_hint=feat)
+    assert info["part_width"] == width and info["n_runs"] == -(-w.nnz // 512)
+    assert np.array_equal(got, run_sddmm(gpu_lib, w, Xr, w.X))
+    Br, Mr = oracle.sddmm_csr(w.n_rows, w.indptr, w.indices, w.values, Xr, w.X)
+    assert_b_close(got, Br, Mr, f"past={past} feat={feat}")
+
+
 def matrix_with_long_rows(n_rows, n_long, n_cols, seed, feat):
     rng = np.random.default_rng(seed)
     deg = rng.integers(0, 12, n_rows)
