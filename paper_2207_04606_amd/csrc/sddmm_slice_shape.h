@@ -51,17 +51,18 @@ constexpr bool slices_pay(int64_t n_cols, int64_t feat, int64_t n_long, int64_t 
   return few_long_rows(feat, n_long) || n_cols * feat >= (int64_t)7 << 18;  // (floats: 7 MB of Yt)
 }
 
-// And once the segments have been counted?  `units` are the pairs of a slice and a part of the rows that have any.  From 12 MB of Yt on,
-// where a quarter of the slices has half of the segments, columns that the lists find in the caches too, or where segments are short
-// and a lane's last float4 is partly used.  Never for fewer units than leave two CUs in five idle.  620 graphs, 37 to 256
-// features, columns uniform, skewed, hot in a range, in communities and in a band, all with slice_min_entries(): where this takes them
-// 1.27 times as fast as lists (0.92 to 2.6), elsewhere 0.9 (0.54 to 2).
+// And once the segments have been counted?  `units` are the pairs of a slice and a part of the rows that have any.  Below 10 MB of Yt
+// a plan without slices keeps CSR order, which finds columns that many entries name in the caches too: where half of the segments lie
+// in less than 42 % of the slices, slices pay from 10 MB on.  Where columns are even and a lane's last float4 is partly used, short
+// segments pay from 12 MB on.  Never fewer units than leave two CUs in five idle.  500 graphs of 7 to 15 MB, 48 to 256 features,
+// columns uniform, skewed, hot in a range, in communities and in a band, slices against lists: uneven ones up to 10 MB 0.90 times as
+// fast (0.44 to 1.8), beyond 1.67 (1.1 to 5.4); even ones 1.22 (0.6 to 2.5), short segments up to 12 MB 0.92 (0.5 to 1.2).
 constexpr bool slices_pay_as_counted(int64_t n_cols, int64_t feat, int64_t n_long, int64_t long_nnz, int64_t units, int64_t n_segs,
                                      int32_t n_slices, int32_t half_in) {
   if (!slices_pay(n_cols, feat, n_long, long_nnz)) return false;
   if (few_long_rows(feat, n_long)) return true;
-  const bool hot = 4 * (int64_t)half_in < n_slices, is_short = feat % 32 != 0 && 10 * long_nnz < 47 * n_segs;
-  return units >= 160 && n_cols * feat >= (int64_t)(hot || is_short ? 12 : 7) << 18;
+  const bool uneven = 50 * (int64_t)half_in < 21 * (int64_t)n_slices, is_short = feat % 32 != 0 && 10 * long_nnz < 47 * n_segs;
+  return units >= 160 && n_cols * feat >= (int64_t)(uneven ? 10 : is_short ? 12 : 7) << 18;
 }
 
 // The fewest slices that have half of the segments.  begin: see slice_units().

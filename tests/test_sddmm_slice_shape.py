@@ -61,7 +61,14 @@ def test_the_slice_fits_lds(choices):
     (25117, 96, 23000, 13_170_000, 2074, 6.2, 61, 30, 1, 1),  # 9.6 MB
     (25117, 96, 23000, 13_170_000, 2074, 6.2, 61, 15, 1, 0),  # (a hot range)
     (34000, 96, 30000, 14_000_000, 2074, 6.2, 83, 1, 1, 1),  # 13 MB
-    (25117, 96, 23000, 13_170_000, 2074, 3.5, 61, 16, 1, 1),  # short segments: only where a float4 is partly used
+    (25117, 96, 23000, 13_170_000, 2074, 3.5, 61, 16, 1, 0),  # uneven: half of the segments in less than 42 % of the slices, below 10 MB
+    (50642, 48, 23604, 16_520_000, 2108, 5.9, 62, 17, 1, 0),  # (312 us, 663 with slices)
+    (27625, 100, 19864, 11_876_000, 2100, 5.3, 70, 10, 1, 1),  # (806 us, 1,645 without)
+    (27306, 96, 23000, 13_170_000, 2074, 5.7, 61, 25, 1, 0),  # 10 MB, but for a row
+    (27306, 96, 23000, 13_170_000, 2074, 5.7, 50, 21, 1, 1),  # (42 % of the slices)
+    (27306, 96, 23000, 13_170_000, 2074, 5.7, 51, 21, 1, 0),
+    (27307, 96, 23000, 13_170_000, 2074, 5.7, 61, 25, 1, 1),
+    (25117, 96, 23000, 13_170_000, 2074, 3.5, 61, 30, 1, 1),  # short segments: only where a float4 is partly used
     (25000, 100, 23000, 13_170_000, 2074, 3.5, 64, 32, 1, 0),
     (25000, 100, 23000, 13_170_000, 2074, 4.8, 64, 32, 1, 1),
     (34000, 100, 30000, 14_000_000, 2074, 3.5, 86, 43, 1, 1),
