@@ -318,11 +318,16 @@ sptir_status_t sptir_spmm(const sptir_hyb_t* hyb, const float* X, float* Y, int3
 typedef struct {
   float ms_lists, ms_heavy, ms_reduce;
   int32_t n_list_launches, n_heavy_launches, n_reduce_launches;
-  int32_t list_waves;   /* wavefronts that share a chunk list (1: a wavefront has its lists to itself) */
-  int32_t tile_floats;  /* floats of a row of X that a wavefront's lane group takes */
 } sptir_spmm_times_t;
 sptir_status_t sptir_spmm_timed(const sptir_hyb_t* hyb, const float* X, float* Y, int32_t feat, void* stream,
                                 sptir_spmm_times_t* out);
+/* The same, with how the chunk lists were walked (`lists` may be NULL). */
+typedef struct {
+  int32_t list_waves;   /* wavefronts that share a chunk list (1: a wavefront has its lists to itself) */
+  int32_t tile_floats;  /* floats of a row of X that a wavefront's lane group takes */
+} sptir_spmm_lists_t;
+sptir_status_t sptir_spmm_timed_lists(const sptir_hyb_t* hyb, const float* X, float* Y, int32_t feat, void* stream,
+                                      sptir_spmm_times_t* out, sptir_spmm_lists_t* lists);
 
 /*
  * The on-chip roofs the SpMM and SDDMM kernels are priced against, measured on the current device (Section 4.2.1

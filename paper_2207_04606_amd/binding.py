@@ -111,10 +111,14 @@ _hip = None
 class _SpmmTimes(ctypes.Structure):
     _fields_ = [("ms_lists", ctypes.c_float), ("ms_heavy", ctypes.c_float), ("ms_reduce", ctypes.c_float),
                 ("n_list_launches", ctypes.c_int32), ("n_heavy_launches", ctypes.c_int32),
-                ("n_reduce_launches", ctypes.c_int32), ("list_waves", ctypes.c_int32), ("tile_floats", ctypes.c_int32)]
+                ("n_reduce_launches", ctypes.c_int32)]
 
 
-EXPORTED_SYMBOLS = ("sptir_spmm_timed", "sptir_roof_gather", "sptir_roof_lds_gather", "sptir_roof_fma", "sptir_set_allocator", "sptir_release_scratch", "sptir_hyb_build", "sptir_hyb_build_ex", "sptir_hyb_search", "sptir_default_bucket_log2", "sptir_gather_offsets_fit_32", "sptir_spmm",
+class _SpmmLists(ctypes.Structure):
+    _fields_ = [("list_waves", ctypes.c_int32), ("tile_floats", ctypes.c_int32)]
+
+
+EXPORTED_SYMBOLS = ("sptir_spmm_timed", "sptir_spmm_timed_lists", "sptir_roof_gather", "sptir_roof_lds_gather", "sptir_roof_fma", "sptir_set_allocator", "sptir_release_scratch", "sptir_hyb_build", "sptir_hyb_build_ex", "sptir_hyb_search", "sptir_default_bucket_log2", "sptir_gather_offsets_fit_32", "sptir_spmm",
                     "sptir_spmm_noalloc",
                     "sptir_spmm_csr", "sptir_sddmm_csr", "sptir_sddmm_plan_build", "sptir_sddmm",
                     "sptir_sddmm_plan_info", "sptir_sddmm_plan_destroy", "sptir_rgms_build", "sptir_rgms", "sptir_rgms_info",
@@ -147,6 +151,8 @@ def load_library(path: str | None = None):
     lib.sptir_spmm.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]
     lib.sptir_spmm_timed.restype = ctypes.c_int
     lib.sptir_spmm_timed.argtypes = lib.sptir_spmm.argtypes + [ctypes.POINTER(_SpmmTimes)]
+    lib.sptir_spmm_timed_lists.restype = ctypes.c_int
+    lib.sptir_spmm_timed_lists.argtypes = lib.sptir_spmm_timed.argtypes + [ctypes.POINTER(_SpmmLists)]
     lib.sptir_roof_gather.restype = ctypes.c_int
     lib.sptir_roof_gather.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                       ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
@@ -397,18 +403,19 @@ def sptir_spmm(hyb: Hyb, X, Y, stream=None) -> None:
 
 
 def sptir_spmm_timed(hyb: Hyb, X, Y, stream=None) -> dict:
-    """sptir_spmm with HIP events between its groups of launches; returns their times (ms) and launch counts."""
+    """sptir_spmm with HIP events between its groups of launches; returns their times (ms) and launch counts, and how the
+    chunk lists were walked."""
     _dev(X, torch.float32, "X"); _dev(Y, torch.float32, "Y")
     if X.dim() != 2 or Y.dim() != 2 or X.shape[1] != Y.shape[1]:
         raise ValueError("X and Y must be 2-D with the same number of columns")
     if X.shape[0] != hyb.n_cols or Y.shape[0] != hyb.n_rows:
         raise ValueError("X / Y row counts do not match the matrix")
-    out = _SpmmTimes()
-    st = load_library().sptir_spmm_timed(hyb.handle, X.data_ptr() or None, Y.data_ptr() or None, X.shape[1],
-                                         _stream_ptr(stream), ctypes.byref(out))
+    out = _SpmmTimes(); lists = _SpmmLists()
+    st = load_library().sptir_spmm_timed_lists(hyb.handle, X.data_ptr() or None, Y.data_ptr() or None, X.shape[1],
+                                               _stream_ptr(stream), ctypes.byref(out), ctypes.byref(lists))
     if st != SPTIR_OK:
         raise SptirError(st, "sptir_spmm_timed")
-    return {name: getattr(out, name) for name, _ in _SpmmTimes._fields_}
+    return {name: getattr(s, name) for s in (out, lists) for name, _ in s._fields_}
 
 
 def sptir_roof_gather(X, n_rows: int, tiles: int, n_workgroups: int, iters: int, sink, stream=None):

@@ -1146,6 +1146,11 @@ extern "C" sptir_status_t sptir_spmm(const sptir_hyb_t* h, const float* X, float
 
 extern "C" sptir_status_t sptir_spmm_timed(const sptir_hyb_t* h, const float* X, float* Y, int32_t feat,
                                            void* stream_, sptir_spmm_times_t* out) {
+  return sptir_spmm_timed_lists(h, X, Y, feat, stream_, out, nullptr);
+}
+
+extern "C" sptir_status_t sptir_spmm_timed_lists(const sptir_hyb_t* h, const float* X, float* Y, int32_t feat, void* stream_,
+                                                 sptir_spmm_times_t* out, sptir_spmm_lists_t* lists) {
   if (!out) return SPTIR_ERR_INVALID_ARG;
   LaunchTimers timers;
   const sptir_status_t st = spmm_on_hyb(h, X, Y, feat, stream_, h ? h->partial : nullptr, h ? h->partial_feat : 0, &timers);
@@ -1164,8 +1169,8 @@ extern "C" sptir_status_t sptir_spmm_timed(const sptir_hyb_t* h, const float* X,
   t.n_list_launches = timers.launches[LaunchTimers::kLists];
   t.n_heavy_launches = timers.launches[LaunchTimers::kHeavy];
   t.n_reduce_launches = timers.launches[LaunchTimers::kReduce];
-  t.list_waves = timers.list_waves; t.tile_floats = timers.tile_floats;
   *out = t;
+  if (lists) { lists->list_waves = timers.list_waves; lists->tile_floats = timers.tile_floats; }
   return SPTIR_OK;
 }
 

@@ -61,3 +61,16 @@ def test_header_is_plain_c():
     done = subprocess.run(["gcc", "-fsyntax-only", "-x", "c", "-std=c99", "-Wall", "-Werror", header],
                           capture_output=True, text=True)
     assert done.returncode == 0, done.stderr
+
+
+def test_structs_that_callers_hand_in_keep_their_size(tmp_path):
+    """The library fills these structs whole: a program built against an earlier header has no room for more."""
+    import subprocess
+    sizes = {"sptir_csr_t": 40, "sptir_spmm_times_t": 24, "sptir_launch_plan_t": 36, "sptir_hyb_info_t": 160,
+             "sptir_sddmm_plan_info_t": 40, "sptir_rgms_info_t": 64}
+    src = tmp_path / "sizes.c"
+    src.write_text('#include "sptir.h"\n' + "".join(f"char a{i}[sizeof({t}) == {n} ? 1 : -1];\n"
+                                                   for i, (t, n) in enumerate(sizes.items())))
+    done = subprocess.run(["gcc", "-fsyntax-only", "-std=c99", "-I", os.path.join(ROOT, "include"), str(src)],
+                          capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
