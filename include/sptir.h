@@ -446,9 +446,9 @@ sptir_status_t sptir_sddmm_plan_destroy(sptir_sddmm_plan_t* plan); /* NULL is ac
  * in the paper, one fused kernel gathers rows of X, multiplies by W[r] on the
  * matrix cores and scatters into Y; X W[r] is never materialised.  Where the
  * paper decomposes every slice into hyb(1, 5) buckets and goes relation by
- * relation, the handle here holds the entries in their order, cut into tiles of
+ * relation, the handle here holds the entries in steps of four, cut into tiles of
  * up to 16 (relation, row) pairs by blocks of rows of Y, and a workgroup keeps
- * the sums of its block on chip: no bucket is built and nothing is padded.
+ * the sums of its block on chip: no bucket is built.
  *   stacked   A as one CSR matrix of n_relations * n_rows rows and n_cols
  *             columns: stacked row r * n_rows + i holds A[r,i,:] (device arrays,
  *             int32 indices strictly ascending inside a stacked row, float32
@@ -470,7 +470,7 @@ typedef struct {
   int64_t nnz;
   int64_t n_stacked_rows_stored;  /* (relation, row) pairs with at least one entry */
   int64_t n_pad_slots;            /* what a hyb(1, max_bucket_log2) decomposition of the slices would pad */
-  int64_t n_tiles;                /* matrix-core products: up to 16 pieces of at most 8 entries, of one relation and row block */
+  int64_t n_tiles;                /* up to 16 pieces of at most 4 entries, of one relation and row block */
   int32_t workspace_d_out;        /* widest d_out that is summed in a fixed order (0: none) */
   int32_t row_block;              /* rows of Y that a workgroup sums in LDS */
   int64_t device_bytes;

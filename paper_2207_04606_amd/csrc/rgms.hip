@@ -9,27 +9,26 @@
 // workgroup owns a block, keeps its rows of Y in LDS, walks the block's pairs
 // (r, i) relation after relation and writes Y once.  The scatter of the
 // relation-stationary order (a float atomic per element of every pair's product
-// row, at L2) was what bound it.  32 x 32 features: 94 K rows, 51 relations, 4.76 M entries 0.257 -> 0.159 ms; 1.38 M rows, 25
-// relations, 5.6 M entries 0.472 -> 0.294; 1.9 M rows, 96 relations, 5.7 M entries 0.560 -> 0.503, where a
-// (relation, block) has few entries and what bounds the kernel is the trips to L2 for W[r].  Over 250 graphs and feature
-// sizes it is 1.22 times as fast in the mean (1.5 to 2 with a workspace), but 58 of them lost: a tile reads all of W[r] however
-// few pairs it holds, where the relation-stationary tiles held 32, so wide W[r] with few entries per (relation, block) take up
-// to 2.3 times as long (1.7 M rows, 54 relations, 1.4 M entries, 128 x 128: 1.07 -> 2.43 ms; 9,788 rows, 52 relations, 30 K entries, 64 x 64:
-// 19 -> 35 us).
+// row, at L2) was what bound it; over 250 graphs and feature sizes it took 1.22 times as long as a first kernel in this one.
 //
-// The entries of (relation, block) are consecutive in the stacked CSR, so the handle needs little more than a copy of the
-// entries in their order.  A piece is the entries of one pair (longer pairs are several pieces of 8), a tile up to
-// 16 consecutive pieces of one relation in one block.  A wavefront takes a tile:
-//   gather    Z^T = X^T S on the matrix cores, four entries a step: S holds the value of an entry in the column of its
-//             piece.  Lane (m, q) brings the features of entry q that are its row of X^T, so every load is whole rows of X
-//             and nothing but rows that are needed: L1 returns 64 bytes a cycle, and loads laid out by piece, a
-//             row per four lanes and most of them masked off, were what bound an earlier form (84 % of its
-//             time).  Z comes out as the A operand of the next product;
-//   multiply  Z W[r], v_mfma_f32_16x16x4_f32, float32 throughout, W[r] from L1 / L2, where the tiles of one relation
-//             that a workgroup's wavefronts take together meet;
-//   add       the 16 x 32 results to the block's rows in LDS, as float64 atomics: ds_add_f64 takes 21 cycles a
+// A *piece* is up to 4 entries of one (relation, row) pair, a *quad* four pieces of one relation in one block, a *tile*
+// up to four quads.  The pieces of a (relation, block) are sorted by length, so that the pieces of a quad are alike, and
+// the entries are stored in *steps* of four, one for each piece of a quad.  A wavefront takes a tile:
+//   gather    Z[i] = sum of value x row of X over the entries of piece i: 16 lanes for each of a step's four entries, whole rows
+//             of X and plain multiply-adds;
+//   multiply  Z W[r], v_mfma_f32_4x4x1_f32 with 16 blocks: float32 throughout, four rows at a time; W[r] from L1 / L2, for 32
+//             features kept in registers over the tiles of a relation;
+//   add       four rows x 32 results to the block's rows in LDS, as float64 atomics: ds_add_f64 takes 9 cycles a
 //             wavefront, ds_add_f32 193 (measured), and the sums lose nothing.
-// Blocks are as large as gives (relation, block) a tile's worth of pieces, and small enough that there are workgroups
+// float32 matrix instructions are issued to the vector units: four 16x16x4 products take 134 cycles of a SIMD, 32 multiply-adds 88, and
+// both together 237.  An earlier form gathered by selection matrices and multiplied 16 rows at a time; without any of its loads
+// of X and W and without its adds it took 94 % of its time.  Now a relation with few pairs in a block does not pay for
+// rows that it has not got, and the gather is two instructions a step.  What counts beside that: a tile's loads depend on each other and are
+// waited for one tile later, so whatever makes the compiler wait for the newest load (a copy of a register that is being loaded, a
+// count of loads that depends on a branch) costs a trip past L2 a tile; and wavefronts (32 x 32 features, 94 K rows, 51 relations, 4.76 M
+// entries: 118 us with six per SIMD, 132 with five).  That graph 153 -> 110 us, 1.9 M rows, 96 relations, 5.7 M entries
+// 435 -> 354; 27,163 rows, 46 relations, 148,100 entries, 64 x 64: 39 -> 31.5.  45 drawn graphs and feature sizes: 1.2 times as fast (0.95 to 1.55).
+// Blocks are as large as gives (relation, block) enough pieces, and small enough that there are workgroups
 // for all CUs; a block with far more tiles than the others is several work items, whose sums meet in Y by global atomics.
 //
 // The order of the adds is not fixed (the last float32 bit may differ from call to call) unless the handle was built
@@ -50,9 +49,9 @@
 namespace sptir {
 namespace {
 
-constexpr int kTileRows = 16;      // pieces per tile: the rows of one matrix-core product
-constexpr int kPieceEntries = 8;   // most entries per piece: at most two batches of 64 per tile
-constexpr int kNoRow = 0xFFFF;
+constexpr int kTileRows = 16;      // pieces per tile
+constexpr int kPieceEntries = 4;   // most entries per piece: a tile has 16 steps at most, 64 entries, a lane each
+constexpr uint32_t kPad = 0x80000000u;  // in the column of a place without an entry: a column of its step, to be multiplied by 0
 constexpr int kMinLog2Block = 5, kMaxLog2Block = 9;
 constexpr int kYTileBytes = 64 * 1024;  // LDS for the rows of Y: two workgroups per CU; blocks of 2^kMaxLog2Block rows: twice that, one
 
@@ -64,17 +63,18 @@ struct RgmsItem {
 };
 
 struct RgmsTile {
-  int32_t first, end;  // its entries
+  int32_t first;       // its first step: entries 4 first ..
   int32_t rel;
-  int32_t pad_;
+  uint32_t shape;      // bits 3e .. + 2: quads that have more than e steps (the longest are first); bits 12 + 4e .. + 3: steps for entries before e
+  int32_t n_steps;
+  uint16_t rows[kTileRows];  // of its pieces, in the block; 1 << log2_block: none
 };
+constexpr int kTileWords = sizeof(RgmsTile) / 4;
 
 struct RgmsArgs {
   const RgmsItem* items;
   const RgmsTile* tiles;
-  const ushort4* tile_rows;  // [n_tiles][4]: the row in the block of each of the tile's 16 pieces, kNoRow: none
-  const int2* entries;       // column, value bits
-  const uint8_t* entry_piece;  // which of its tile's pieces an entry belongs to
+  const int2* entries;       // [steps][4]: column, value bits; a step: entry e of each piece of a quad; inside a tile e major
   const float* X;
   const float* W;
   float* Y;
@@ -90,11 +90,7 @@ struct RgmsArgs {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// Place in the LDS tile: an instruction adds to 16 columns of any four rows; every other row has its halves of 32 columns
-// swapped, so that the four are spread over all banks.
-__device__ __forceinline__ int y_index(int row, int col, int width) { return row * width + (col ^ ((row & 1) << 4)); }
-
-// f(0), f(1), .. f(N - 1) with the number as a type
+// f(0) .. f(N - 1) with the number as a type
 template <int N, typename F, int I = 0>
 __device__ __forceinline__ void for_steps(F&& f) {
   if constexpr (I < N) {
@@ -102,13 +98,6 @@ __device__ __forceinline__ void for_steps(F&& f) {
     for_steps<N, F, I + 1>(std::forward<F>(f));
   }
 }
-
-// An entry of a tile as lane (m, q) holds it: number 4 m + q of a batch of 64.
-struct Entry {
-  int col;
-  float val;
-  int piece;  // (past the end of the tile: a piece that is none of the 16)
-};
 
 // lane S of every 16
 template <int S>
@@ -120,22 +109,30 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint3
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 
-constexpr int kPass = 32;       // columns of Y per pass: two products side by side
+__device__ __forceinline__ int from_lane(int byte, int v) { return __builtin_amdgcn_ds_bpermute(byte, v); }
 
-// TIN: d_in / 32.  Lane (m, q) = 16 q + m of a 16x16x4 product holds row m of A and column m of B at k = q, and rows
-// 4 q .. + 3 of column m of the result.  The features are dealt to the rows of X^T so that a lane's are consecutive:
-// row m of product (g, l) is feature 16 VW g + VW m + l.  Column m of product j of a pass over Y stands for the pass's
-// column 4 (m & 7) + 2 (m >> 3) + j: that is what the lanes hold after a load of 16 consecutive bytes each (see
-// load_w).  In the LDS tile the columns lie in the order of the products.
+constexpr int kPass = 32;       // columns of Y per pass
+
+// TIN: d_in / 32.  In a 4x4x1 product of 16 blocks lane 4 b + i holds row i of block b's A, or column i of its B, and column i
+// of all four rows of its result; A can be one block's for eight blocks together (cbsz 3).  So lanes 0 .. 31 form a product of
+// four rows, one feature and 32 columns, lanes 32 .. 63 another one, with the feature that lies kHalf further on, and the two meet at
+// the end.  W[r] is loaded in whole rows of 32 columns.  The gather leaves piece i's row in lanes 16 i .. + 15 (a load of 16 lanes
+// that name four rows takes four times the lines: 246 against 206 us); lane 16 i + b's features go to lane 4 b + i, once a quad.
 // WIDE_X: X has 4 GB or more.
 template <int TIN, bool ORDERED, bool WIDE_X>
 __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
   constexpr int VW = TIN == 1 ? 2 : 4;              // floats per lane and load of a row of X
-  constexpr int kLoads = 2 * TIN / VW;              // loads per row
-  constexpr int kZ = 2 * TIN;                       // 16-feature products per step
-  constexpr int kAhead = TIN <= 2 ? 8 : 4;                        // steps of four entries whose rows are in flight together
-  constexpr int kDin = 32 * TIN, kRowBytes = 4 * kDin;
-  extern __shared__ __align__(16) double y_tile[];  // [rows][width], then ORDERED: turn[width / kPass]
+  constexpr int kGroups = 2 * TIN / VW;             // loads per row
+  constexpr int kZ = 2 * TIN;                       // registers per row
+  constexpr int kDin = 32 * TIN, kRowBytes = 4 * kDin, kLog2RowBytes = TIN == 1 ? 7 : TIN == 2 ? 8 : 9;
+  constexpr bool kTwoAhead = TIN == 1;              // rows for the first two entries of a tile's pieces are loaded ahead, or for one
+  constexpr bool kInTurns = ORDERED || TIN > 1;     // the wavefronts take tiles in turns, not a run each
+  constexpr int kHalf = 8 * VW;                     // of the features of a load, those of lanes 0 .. 31 of a product
+  // Rows of W (and as many of the other half) that are loaded together: all of a pass, or 4, of which two lots are held.
+  // (16: 153 registers; 8: 64 x 64 features 2 % slower, 128 x 32 16 %, whose wavefronts are then three per SIMD and not four.)
+  constexpr int kChunk = TIN == 1 ? 16 : 4;
+  constexpr int kChunks = kDin / 2 / kChunk;        // per pass
+  extern __shared__ __align__(16) double y_tile[];  // [rows + 1][width] (the last for pieces that are none), then ORDERED: turn[width / kPass]
   RgmsItem item = a.items[blockIdx.x / (unsigned)a.sharers];
   if (a.sharers > 1) {
     const int part = (int)(blockIdx.x % (unsigned)a.sharers), n = item.n_tiles;
@@ -147,178 +144,258 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
   const int rows = 1 << a.log2_block, width = a.width;
   const int n0 = blockIdx.y * width;
   const int cols = min(width, a.d_out - n0);
-  int* turn = reinterpret_cast<int*>(y_tile + rows * width);
-  for (int i = threadIdx.x * 2; i < rows * width; i += blockDim.x * 2)
-    *reinterpret_cast<double2*>(y_tile + i) = make_double2(0., 0.);
-  if (ORDERED && threadIdx.x < (unsigned)(width / kPass)) turn[threadIdx.x] = 0;
-  __syncthreads();
-
-  const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
+  int* turn = reinterpret_cast<int*>(y_tile + (rows + 1) * width);
+  using std::integral_constant;
+  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), n_waves = a.n_waves;
+
+  // The wavefront's tiles: a run of them, so that one W[r] serves many; where they take turns, every n_waves-th.
+  const int stride = kInTurns ? n_waves : 1;
+  const int tile_lo = kInTurns ? wave : (int)((int64_t)item.n_tiles * wave / n_waves);
+  const int tile_hi = kInTurns ? item.n_tiles : (int)((int64_t)item.n_tiles * (wave + 1) / n_waves);
 
   // A tile's loads depend on each other (the tile, its entries, the rows those name), each a trip past L2, so they run
   // ahead by three tiles, two and one: what is issued while tile t is multiplied has arrived when t + 1 begins.
-  auto tile_number = [&](int t) { return item.tile0 + (t < item.n_tiles ? t : 0); };
-  auto load_tile = [&](int t) -> RgmsTile { return a.tiles[tile_number(t)]; };
-  auto load_rows = [&](int t) -> ushort4 { return a.tile_rows[(size_t)tile_number(t) * 4 + q]; };
-  auto load_entry = [&](const RgmsTile& t, int batch) -> Entry {
-    const int i = t.first + 64 * batch + 4 * m + q, at = min(i, t.end - 1);
-    const int2 e = a.entries[at];
-    const int p = a.entry_piece[at];
-    return Entry{e.x, __int_as_float(e.y), i < t.end ? p : kNoRow};
+  const char* tiles = reinterpret_cast<const char*>(a.tiles + item.tile0);
+  const unsigned tile_word = 4u * min(lane, kTileWords - 1);
+  auto load_tile = [&](int t) -> int {  // lane i: word i
+    return *reinterpret_cast<const int*>(tiles + ((unsigned)(t < tile_hi ? t : tile_lo) * (unsigned)sizeof(RgmsTile) + tile_word));
   };
+  auto first_of = [&](int tile) { return __builtin_amdgcn_readlane(tile, 0); };
+  auto rel_of = [&](int tile) { return __builtin_amdgcn_readlane(tile, 1); };
+  auto shape_of = [&](int tile) { return __builtin_amdgcn_readlane(tile, 2); };
+  auto steps_of = [&](int tile) { return __builtin_amdgcn_readlane(tile, 3); };
+  auto load_entries = [&](int first, int shape, int steps) -> int2 {  // lane 16 i + 4 e + q: entry e of piece i of quad q
+    const int at = __builtin_amdgcn_ubfe(shape, 12 + (lane & 12), 4) + (lane & 3);
+    const char* from = reinterpret_cast<const char*>(a.entries + (size_t)first * 4);
+    return *reinterpret_cast<const int2*>(from + (unsigned)(min(at, steps - 1) * 32 + (lane >> 4) * 8));
+  };
+  auto wait_for_loads = [] { __builtin_amdgcn_s_waitcnt(0x0F70); };  // vmcnt(0)
+  // (values that only some turns set: without this they would be kept from turn to turn)
+  auto undefined = [](float (&v)[4][kZ]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int k = 0; k < kZ; ++k) asm volatile("" : "=v"(v[q][k]));
+  };
+  // (a loaded value moves on here, and not where the load that takes its place would be waited for)
+  auto moved = [](int v) { asm volatile("" : "+v"(v)); return v; };
   const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.X, a.x_bytes);
-  auto load_x = [&](int col, float (&x)[kLoads][VW]) {
+  const unsigned x_lane = (unsigned)(lane & 15) * (4 * VW);
+  auto x_place = [&](int col) { return WIDE_X ? col : (int)((unsigned)col << kLog2RowBytes); };  // (the shift drops kPad)
+  auto load_x = [&](int place, float (&x)[kZ]) {
     typedef float vec __attribute__((ext_vector_type(VW)));
 #pragma unroll
-    for (int g = 0; g < kLoads; ++g) {
+    for (int g = 0; g < kGroups; ++g) {
       vec v;
-      if constexpr (WIDE_X) v = *reinterpret_cast<const vec*>(a.X + (size_t)col * kDin + VW * m + 16 * VW * g);
+      if constexpr (WIDE_X)
+        v = *reinterpret_cast<const vec*>(a.X + (size_t)(place & ~kPad) * kDin + (lane & 15) * VW + 16 * VW * g);
       else if constexpr (VW == 2)
-        v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(x_buf, (int)((unsigned)col * kRowBytes + 8u * m), 128 * g, 0));
+        v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(x_buf, (int)((unsigned)place + x_lane), 0, 0));
       else
-        v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(x_buf, (int)((unsigned)col * kRowBytes + 16u * m), 256 * g, 0));
+        v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(x_buf, (int)((unsigned)place + x_lane), 256 * g, 0));
 #pragma unroll
-      for (int l = 0; l < VW; ++l) x[g][l] = v[l];
+      for (int l = 0; l < VW; ++l) x[VW * g + l] = v[l];
     }
   };
-  // the rows of X of steps S0 .. S0 + kAhead - 1 of a batch with n entries left (steps past them: nothing)
-  float x[kAhead][kLoads][VW];
-  auto load_steps = [&](auto s0, const Entry& e, int n) {
-    for_steps<kAhead>([&](auto i) {
-      constexpr int S = decltype(s0)::value + decltype(i)::value;
-      if (4 * S < n) load_x(bcast16<S>(e.col), x[decltype(i)::value]);
+  int tile = 0, tile_1 = 0, tile_2 = 0;
+  int2 e = make_int2(0, 0), e_1 = e;
+  float xa[4][kZ], xb[4][kZ];
+  float w[2][kChunk];
+  // entry E of the pieces of the first n quads
+  auto load_rows = [&](auto entry, float (&x)[4][kZ], const int2& e, int n) {
+    for_steps<4>([&](auto q) {
+      constexpr int Q = decltype(q)::value;
+      if (Q < n) load_x(bcast16<4 * decltype(entry)::value + Q>(e.x), x[Q]);
     });
   };
-  floatx4 z[kLoads][VW];
-  auto sum_steps = [&](auto s0, const Entry& e, int n) {
-    for_steps<kAhead>([&](auto i) {
-      constexpr int S = decltype(s0)::value + decltype(i)::value;
-      if (4 * S < n) {
-        const float v = __int_as_float(bcast16<S>(__float_as_int(e.val)));
-        const float b = bcast16<S>(e.piece) == m ? v : 0.f;
+  auto sum_rows = [&](auto entry, const float (&x)[4][kZ], const int2& e, int n, float (&z)[4][kZ]) {
+    for_steps<4>([&](auto q) {
+      constexpr int Q = decltype(q)::value, E = decltype(entry)::value;
+      if (Q < n) {
 #pragma unroll
-        for (int g = 0; g < kLoads; ++g)
-#pragma unroll
-          for (int l = 0; l < VW; ++l)
-            z[g][l] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[decltype(i)::value][g][l], b, z[g][l], 0, 0, 0);
+        for (int k = 0; k < kZ; ++k) {
+          const float v = __int_as_float(bcast16<4 * E + Q>(e.y));
+          z[Q][k] = E == 0 ? v * x[Q][k] : fmaf(v, x[Q][k], z[Q][k]);
+        }
       }
     });
   };
-  auto sum_rest = [&](const Entry& e, int n) {  // the steps of a batch that were not loaded ahead
-    for_steps<16 / kAhead - 1>([&](auto c) {
-      constexpr int S0 = (decltype(c)::value + 1) * kAhead;
-      if (4 * S0 < n) {
-        load_steps(std::integral_constant<int, S0>{}, e, n);
-        sum_steps(std::integral_constant<int, S0>{}, e, n);
-      }
-    });
-  };
-  // W[r], part (g, l): the rows k = 16 VW g + VW (4 q + i) + l, i = 0 .. 3, that meet z[g][l][i].  Parts l and l + 1
-  // are loaded together, a pair of rows (k, k + 1) at a time: lanes m < 8 take row k, the others k + 1, eight lanes to 128
-  // consecutive bytes; take_w then trades halves between lanes m and m ^ 8, so that every lane holds two columns
-  // of both rows.  (A lane loading its own two columns of one row costs L1 twice the cycles.)
-  const bool upper = (m & 8) != 0;
-  const int w_lane = 4 * ((4 * VW * q + (m >> 3)) * a.d_out + 4 * (m & 7));
-  auto load_w = [&](int rel, int c0, int part, float4 (&wb)[4]) {  // part: number of a pair of parts
-    const int g = part / (VW / 2), l = part % (VW / 2) * 2;
+  // W[r], chunk c of the pass at c0: w[i] is one row of the lower half in lanes 0 .. 31 and one of the upper half in the others
+  const int w_lane = 4 * ((lane >> 5) * kHalf * a.d_out + (lane & 31));
+  auto load_w = [&](int rel, int c0, int c, float (&w)[kChunk]) {
     const __amdgpu_buffer_rsrc_t w_buf = buffer_of(a.W + (size_t)rel * kDin * (size_t)a.d_out, (uint32_t)(kRowBytes * a.d_out));
+    const int j = c * kChunk;
+    int at = 4 * ((2 * kHalf * (j / kHalf) + j % kHalf) * a.d_out + n0 + c0);
+    asm volatile("" : "+s"(at));  // (or the places of all rows are kept in registers)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      wb[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(
-                                             w_buf, w_lane, 4 * ((16 * VW * g + VW * i + l) * a.d_out + n0 + c0), 0));
+    for (int i = 0; i < kChunk; ++i, at += 4 * a.d_out)
+      w[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(w_buf, w_lane, at, 0));
   };
-  auto take_w = [&](const float4 w, float2& even, float2& odd) {
-    auto pick = [&](float when_upper, float otherwise) { return upper ? when_upper : otherwise; };
-    auto other_half = [&](float v) {  // lane m ^ 8's: row_ror:8
-      return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, true));
-    };
-    const float here_x = other_half(pick(w.x, w.z)), here_y = other_half(pick(w.y, w.w));
-    even = make_float2(pick(here_x, w.x), pick(here_y, w.y));
-    odd = make_float2(pick(w.z, here_x), pick(w.w, here_y));
-  };
-  constexpr int kParts = kZ / 2, kHeld = kParts < 2 ? kParts : 2;  // pairs of parts of W, and how many are held at a time
 
-  using std::integral_constant;
-  if (wave < item.n_tiles) {
-    RgmsTile tile = load_tile(wave), tile_1 = load_tile(wave + n_waves), tile_2 = load_tile(wave + 2 * n_waves);
-    Entry e = load_entry(tile, 0), e_1 = load_entry(tile_1, 0);
-    ushort4 rows_now = load_rows(wave), rows_next;
-    float4 w[kHeld][4];  // a part is loaded anew as soon as it is used
-    load_steps(integral_constant<int, 0>{}, e, tile.end - tile.first);
+  // the place in LDS of the lane's column `lane_place` of a row, the upper or lower half of `two`: one instruction
+  const unsigned row_bytes = 8 * width;
+  auto place_of_row = [&](int two, auto which, unsigned lane_place) {
+    unsigned at;
+    if constexpr (decltype(which)::value % 2)
+      asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(at) : "v"(two), "s"(row_bytes), "v"(lane_place));
+    else
+      asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(two), "s"(row_bytes), "v"(lane_place));
+    return at;
+  };
+  // rows of X for the next tile.  (Where W[r] streams in behind them they are four whatever the tile holds: a load can only be
+  // waited for by the number of those after it.)
+  auto load_next = [&](int shape) {
+    load_rows(integral_constant<int, 0>{}, xa, e, kChunks == 1 ? shape & 7 : 4);
+    if constexpr (kTwoAhead) load_rows(integral_constant<int, 1>{}, xb, e, shape >> 3 & 7);
+  };
+  const int z_from = 4 * (16 * (lane & 3) + (lane >> 2));
+  const int y_lane = 8 * (lane & 31);
+  if (tile_lo < tile_hi) {
+    tile = load_tile(tile_lo); tile_1 = load_tile(tile_lo + stride); tile_2 = load_tile(tile_lo + 2 * stride);
+  }
+  for (int i = threadIdx.x * 2; i < (rows + 1) * width; i += blockDim.x * 2)
+    *reinterpret_cast<double2*>(y_tile + i) = make_double2(0., 0.);
+  if (ORDERED && threadIdx.x < (unsigned)(width / kPass)) turn[threadIdx.x] = 0;
+  if (tile_lo < tile_hi) {
+    e = load_entries(first_of(tile), shape_of(tile), steps_of(tile));
+    e_1 = load_entries(first_of(tile_1), shape_of(tile_1), steps_of(tile_1));
+    e.x = x_place(e.x);
+    load_w(rel_of(tile), 0, 0, w[0]);
+    if constexpr (kChunks > 1) load_w(rel_of(tile), 0, 1, w[1]);
+    const int shape = shape_of(tile);
+    load_next(shape);
+  }
+  __syncthreads();
+
+  for (int t = tile_lo; t < tile_hi; t += stride) {
+    // ---- gather: entry 0 of all pieces, entry 1, ..
+    // (All that the last turn has loaded is waited for here, and what only some turns load is waited for where they do: past
+    // that the compiler cannot count what is in flight, and would wait for the loads that are to stay there.)
+    if constexpr (kChunks == 1) wait_for_loads();
+    const int shape = shape_of(tile), n_quads = shape & 7, n_1 = shape >> 3 & 7, n_2 = shape >> 6 & 7, n_3 = shape >> 9 & 7;
+    const int rel = rel_of(tile), rel_next = rel_of(tile_1), shape_1 = shape_of(tile_1);
+    const int first_2 = first_of(tile_2), shape_2 = shape_of(tile_2), steps_2 = steps_of(tile_2);
+    int piece_rows[4];  // two each: of pieces 8 p + 4 (lane >> 5) ..
 #pragma unroll
-    for (int p = 0; p < kHeld; ++p) load_w(tile.rel, 0, p, w[p]);
-    for (int t = wave; t < item.n_tiles; t += n_waves) {
-      // ---- gather
+    for (int p = 0; p < 2; ++p)
 #pragma unroll
-      for (int g = 0; g < kLoads; ++g)
-#pragma unroll
-        for (int l = 0; l < VW; ++l) z[g][l] = floatx4{0.f, 0.f, 0.f, 0.f};
-      const int n = tile.end - tile.first;
-      sum_steps(integral_constant<int, 0>{}, e, n);
-      sum_rest(e, n);
-#pragma unroll 1
-      for (int batch = 1; 64 * batch < n; ++batch) {
-        const Entry more = load_entry(tile, batch);
-        load_steps(integral_constant<int, 0>{}, more, n - 64 * batch);
-        sum_steps(integral_constant<int, 0>{}, more, n - 64 * batch);
-        sum_rest(more, n - 64 * batch);
-      }
-      // ---- what the next tiles need
-      load_steps(integral_constant<int, 0>{}, e_1, tile_1.end - tile_1.first);
-      e = e_1;
-      e_1 = load_entry(tile_2, 0);
-      rows_next = load_rows(t + n_waves);
-      const int rel = tile.rel, rel_next = tile_1.rel;
-      tile = tile_1; tile_1 = tile_2;
-      tile_2 = load_tile(t + 3 * n_waves);
-      const int y_row[4] = {rows_now.x, rows_now.y, rows_now.z, rows_now.w};
-      // ---- multiply, a pass at a time
-#pragma unroll 1
-      for (int c0 = 0; c0 < cols; c0 += kPass) {
-        const bool last = c0 + kPass >= cols;
-        const int rel_then = last ? rel_next : rel, c_then = last ? 0 : c0 + kPass;
-        floatx4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int p = 0; p < kParts; ++p) {
-          constexpr int kPairs = VW / 2;
-          const int g = p / kPairs, l = p % kPairs * 2;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            float2 even, odd;
-            take_w(w[p % kHeld][i], even, odd);
-            d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l][i], even.x, d0, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l][i], even.y, d1, 0, 0, 0);
-            d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l + 1][i], odd.x, d0, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][l + 1][i], odd.y, d1, 0, 0, 0);
-          }
-          if (p + kHeld < kParts) load_w(rel, c0, p + kHeld, w[p % kHeld]);
-          else load_w(rel_then, c_then, p + kHeld - kParts, w[p % kHeld]);
+      for (int i = 0; i < 2; ++i) piece_rows[2 * p + i] = from_lane(4 * (4 + 4 * p + i) + 8 * (lane >> 5), tile);
+    float z[4][kZ];
+    undefined(z);
+    sum_rows(integral_constant<int, 0>{}, xa, e, n_quads, z);
+    if (n_1 > 0) {
+      if constexpr (kTwoAhead) {
+        load_rows(integral_constant<int, 2>{}, xa, e, n_2);
+        sum_rows(integral_constant<int, 1>{}, xb, e, n_1, z);
+        if (n_2 > 0) {
+          load_rows(integral_constant<int, 3>{}, xb, e, n_3);
+          sum_rows(integral_constant<int, 2>{}, xa, e, n_2, z);
+          sum_rows(integral_constant<int, 3>{}, xb, e, n_3, z);
         }
-        // ---- add: d[v] belongs to piece 4q + v
-        if constexpr (ORDERED) {
-          // tile t adds after tile t - 1, which an earlier turn of this loop or another wavefront of this workgroup
-          // is on its way to: the wait ends
-          while (__hip_atomic_load(turn + c0 / kPass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != t)
-            __builtin_amdgcn_s_sleep(1);
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (y_row[v] != kNoRow) {
-            double* y = y_tile + y_row[v] * width + c0 + m;
-            const int half = (y_row[v] & 1) << 4;
-            atomicAdd(y + half, (double)d0[v]);
-            atomicAdd(y + (half ^ 16), (double)d1[v]);
-          }
-        if constexpr (ORDERED) {
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  // (LDS only: the prefetches stay in flight)
-          if (lane == 0)
-            __hip_atomic_store(turn + c0 / kPass, t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      } else {
+        float x[4][kZ];
+        undefined(x);
+        load_rows(integral_constant<int, 1>{}, x, e, n_1);
+        sum_rows(integral_constant<int, 1>{}, x, e, n_1, z);
+        if (n_2 > 0) {
+          load_rows(integral_constant<int, 2>{}, x, e, n_2);
+          sum_rows(integral_constant<int, 2>{}, x, e, n_2, z);
+          load_rows(integral_constant<int, 3>{}, x, e, n_3);
+          sum_rows(integral_constant<int, 3>{}, x, e, n_3, z);
         }
       }
-      rows_now = rows_next;
     }
+    for_steps<4>([&](auto q) {  // to the places of the product
+      constexpr int Q = decltype(q)::value;
+      if (Q < n_quads) {
+#pragma unroll
+        for (int k = 0; k < kZ; ++k) z[Q][k] = __int_as_float(from_lane(z_from, __float_as_int(z[Q][k])));
+      }
+    });
+    // ---- what the next tiles need
+    if constexpr (kChunks == 1) wait_for_loads();
+    e = make_int2(x_place(moved(e_1.x)), moved(e_1.y));
+    e_1 = load_entries(first_2, shape_2, steps_2);
+    tile = moved(tile_1); tile_1 = moved(tile_2);
+    tile_2 = load_tile(t + 3 * stride);
+    if constexpr (kChunks == 1) load_next(shape_1);
+    // ---- multiply: quads Q0 .. Q0 + NQ - 1 and the pass at c0
+    auto products = [&](auto q0, auto nq, auto is_last, int c0) {
+      constexpr int Q0 = decltype(q0)::value, NQ = decltype(nq)::value, kPairs = (NQ + 1) / 2;
+      constexpr bool kLast = decltype(is_last)::value;
+      floatx4 d[2 * kPairs];
+#pragma unroll
+      for (int q = 0; q < 2 * kPairs; ++q) d[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for_steps<kChunks>([&](auto chunk) {
+        constexpr int C = decltype(chunk)::value;
+        // (as late as leaves two chunks of W to load behind them, since those are waited for in order)
+        if constexpr (kLast && kChunks > 1 && C == kChunks - 2) load_next(shape_1);
+        for_steps<kChunk>([&](auto step) {
+          constexpr int I = decltype(step)::value, J = C * kChunk + I;
+          constexpr int R = VW * (J / kHalf) + J % VW, S = J % kHalf / VW;  // the feature's register, and the block that holds it
+          for_steps<NQ>([&](auto q) {
+            constexpr int Q = decltype(q)::value;
+            d[Q] = __builtin_amdgcn_mfma_f32_4x4x1f32(z[Q0 + Q][R], w[C & 1][I], d[Q], 3, S, 0);
+          });
+        });
+        if constexpr (kChunks > 1) {
+          if constexpr (C + 2 < kChunks) load_w(rel, c0, C + 2, w[C & 1]);
+          else load_w(kLast ? rel_next : rel, kLast ? 0 : c0 + kPass, C & 1, w[C & 1]);
+        }
+      });
+      // ---- add: after the halves have met, d[2 p][i] belongs to piece 4 Q0 + 8 p + 4 (lane >> 5) + i
+      if constexpr (ORDERED && Q0 == 0) {
+        // tile t adds after tile t - 1, which an earlier turn of this loop or another wavefront of this workgroup
+        // is on its way to: the wait ends
+        while (__hip_atomic_load(turn + c0 / kPass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != t)
+          __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+      }
+#pragma unroll
+      for (int p = 0; p < kPairs; ++p)
+        for_steps<4>([&](auto row) {
+          constexpr int i = decltype(row)::value;
+          const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[2 * p][i]), __float_as_uint(d[2 * p + 1][i]), false, false);
+          const float sum = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+          const unsigned at = place_of_row(piece_rows[Q0 + 2 * p + i / 2], row, y_lane + 8 * c0);
+          atomicAdd(reinterpret_cast<double*>(reinterpret_cast<char*>(y_tile) + at), (double)sum);
+        });
+    };
+    auto pass = [&](auto is_last, int c0) {
+      using C0 = integral_constant<int, 0>;
+      using C2 = integral_constant<int, 2>;
+      if constexpr (kChunks == 1) {
+        // (all of W is there: two quads at a time take fewer registers)
+        if (n_quads > 1) products(C0{}, C2{}, is_last, c0);
+        else products(C0{}, integral_constant<int, 1>{}, is_last, c0);
+        if (n_quads > 3) products(C2{}, C2{}, is_last, c0);
+        else if (n_quads > 2) products(C2{}, integral_constant<int, 1>{}, is_last, c0);
+      } else {
+        if (n_quads == 4) products(C0{}, integral_constant<int, 4>{}, is_last, c0);
+        else if (n_quads == 3) products(C0{}, integral_constant<int, 3>{}, is_last, c0);
+        else if (n_quads == 2) products(C0{}, C2{}, is_last, c0);
+        else products(C0{}, integral_constant<int, 1>{}, is_last, c0);
+      }
+      if constexpr (ORDERED) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  // (LDS only: the prefetches stay in flight)
+        if (lane == 0)
+          __hip_atomic_store(turn + c0 / kPass, t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    };
+    int c0 = 0;
+#pragma unroll 1
+    for (; c0 + kPass < cols; c0 += kPass) {
+      pass(std::false_type{}, c0);
+      if constexpr (kChunks == 1) {
+        load_w(rel, c0 + kPass, 0, w[0]);
+#pragma unroll
+        for (int i = 0; i < kChunk; ++i) asm volatile("" : "+v"(w[0][i]));  // (waited for here: see above)
+      }
+    }
+    pass(std::true_type{}, c0);
+    if constexpr (kChunks == 1)
+      if (rel_next != rel || cols > kPass) load_w(rel_next, 0, 0, w[0]);
   }
   __syncthreads();
 
@@ -327,11 +404,9 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63;
-    // The gather multiplies an entry's row of X with the value 0 for the pieces it does not belong to, and a lane past the end
-    // of a tile does so with the tile's last row: a NaN or an infinity in a row of X has reached every pair of the tile.  Sums
-    // that are not finite are therefore formed again before they are written, from their own row's entries only; the
-    // wavefront takes a row of the block at a time.  y[0 .. 3] of a lane: columns n0 + c .. + 3 of row `row`.  (Testing every
-    // tile's sums in front of its product instead: 0.505 -> 0.542 ms on 1.9 M rows; here the test does not show.)
+    // A place without an entry multiplies a row of X that its step has anyway by 0: a NaN or an infinity in it has reached the
+    // place's piece.  Sums that are not finite are therefore formed again before they are written, from their own row's entries
+    // only; the wavefront takes a row of the block at a time.  y[0 .. 3] of a lane: columns n0 + c .. + 3 of row `row`.
     auto sum_again = [&](int row, int c, bool not_finite, float (&y)[4]) {
       unsigned long long todo = __ballot(not_finite);
       while (todo) {
@@ -341,32 +416,29 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
         double sum[4] = {0., 0., 0., 0.};
         for (int t0 = 0; t0 < item.n_tiles; t0 += 64) {
           bool has = false;  // a piece of row r in tile t0 + lane
-          if (t0 + lane < item.n_tiles)
+          if (t0 + lane < item.n_tiles) {
+            const uint16_t* of = a.tiles[item.tile0 + t0 + lane].rows;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const ushort4 of = a.tile_rows[(size_t)(item.tile0 + t0 + lane) * 4 + i];
-              has |= of.x == r || of.y == r || of.z == r || of.w == r;
-            }
+            for (int i = 0; i < kTileRows; ++i) has |= of[i] == r;
+          }
           for (unsigned long long tiles = __ballot(has); tiles; tiles &= tiles - 1) {
-            const int t = item.tile0 + t0 + __builtin_ctzll(tiles);
-            const RgmsTile tile = a.tiles[t];
-            const int of_slot = reinterpret_cast<const uint16_t*>(a.tile_rows + (size_t)t * 4)[lane & 15];
-            const unsigned slots = (unsigned)__ballot(of_slot == r) & 0xFFFFu;
+            const RgmsTile& tile = a.tiles[item.tile0 + t0 + __builtin_ctzll(tiles)];
+            const int n = 4 * tile.n_steps;
+            const unsigned slots = (unsigned)__ballot(tile.rows[lane & 15] == r) & 0xFFFFu;
             constexpr int kPerLane = (kDin + 63) / 64;
             float sums[kPerLane];  // features lane, lane + 64
 #pragma unroll
             for (int i = 0; i < kPerLane; ++i) sums[i] = 0.f;
-            for (int first = tile.first; first < tile.end; first += 64) {
-              const int at = min(first + lane, tile.end - 1);
-              const int2 e = a.entries[at];
-              const bool take = first + lane < tile.end && (slots >> a.entry_piece[at] & 1u) != 0;
-              for (unsigned long long left = __ballot(take); left; left &= left - 1) {
-                const int from = __builtin_ctzll(left);
-                const float* x_row = a.X + (size_t)__builtin_amdgcn_readlane(e.x, from) * kDin;
-                const float v = __int_as_float(__builtin_amdgcn_readlane(e.y, from));
+            const int2 e = a.entries[(size_t)tile.first * 4 + min(lane, n - 1)];
+            int quad = lane >> 2;  // of this lane's entry
+            for (int left = tile.shape & 0xFFF; left != 0 && quad >= (left & 7); left >>= 3) quad -= left & 7;
+            const bool take = lane < n && e.x >= 0 && (slots >> ((4 * quad + (lane & 3)) & 15) & 1u) != 0;
+            for (unsigned long long left = __ballot(take); left; left &= left - 1) {
+              const int from = __builtin_ctzll(left);
+              const float* x_row = a.X + (size_t)__builtin_amdgcn_readlane(e.x, from) * kDin;
+              const float v = __int_as_float(__builtin_amdgcn_readlane(e.y, from));
 #pragma unroll
-                for (int i = 0; i < kPerLane; ++i) sums[i] = fmaf(v, x_row[(64 * i + lane) % kDin], sums[i]);
-              }
+              for (int i = 0; i < kPerLane; ++i) sums[i] = fmaf(v, x_row[(64 * i + lane) % kDin], sums[i]);
             }
             const float* w = a.W + (size_t)tile.rel * kDin * (size_t)a.d_out + n0 + c;
             float d[4] = {0.f, 0.f, 0.f, 0.f};
@@ -394,16 +466,14 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
     const int rows_here = min(rows, a.n_rows - row0);
     const int quads = cols / 4;
     const int n_quads = rows_here * quads;
+    const int shift = (quads & (quads - 1)) == 0 ? 31 - __builtin_clz((unsigned)quads) : -1;
     // (whole wavefronts: sum_again needs all lanes)
     for (int i0 = __builtin_amdgcn_readfirstlane(tid); i0 < n_quads; i0 += (int)blockDim.x) {
       const int i = min(i0 + lane, n_quads - 1);
-      const int row = i / quads, c = (i - row * quads) * 4;
+      const int row = shift >= 0 ? i >> shift : i / quads, c = (i - row * quads) * 4;
       float y[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int p = (c + k) % kPass;
-        y[k] = (float)y_tile[y_index(row, c + k - p + 16 * (p & 1) + 8 * ((p >> 1) & 1) + (p >> 2), width)];
-      }
+      for (int k = 0; k < 4; ++k) y[k] = (float)y_tile[row * width + c + k];
       const bool not_finite = fmaf(y[0], 0.f, fmaf(y[1], 0.f, fmaf(y[2], 0.f, y[3] * 0.f))) != 0.f;
       if (__any(not_finite)) sum_again(row, c, not_finite, y);
       if (i0 + lane >= n_quads) continue;
@@ -449,8 +519,54 @@ struct CellArgs {
 };
 constexpr int kCountSlots = 64, kCountStride = 8;
 
-// tiles of every cell, entries of every block (zeroed before); counts[slot][0] += pairs with entries, [1] += slots of padding that hyb(1, k) has for them
-__global__ __launch_bounds__(256) void k_cell_tiles(CellArgs a, int32_t* cell_tiles, int32_t* block_entries,
+// The pieces of a cell in the order of its tiles: longest first, in quads of four and tiles of four quads.
+// at_least[L]: quads with a piece of at least L entries, which therefore have so many steps.
+struct CellShape {
+  int count[kPieceEntries + 1];      // pieces of L entries
+  int at_least[kPieceEntries + 1];
+  __device__ __forceinline__ int tiles() const { return (at_least[1] + 3) >> 2; }
+  __device__ __forceinline__ int steps_of(int quad) const {
+    int n = 0;
+#pragma unroll
+    for (int len = 1; len <= kPieceEntries; ++len) n += at_least[len] > quad;
+    return n;
+  }
+  __device__ __forceinline__ int steps_before(int quad) const {
+    int n = 0;
+#pragma unroll
+    for (int len = 1; len <= kPieceEntries; ++len) n += min(at_least[len], quad);
+    return n;
+  }
+};
+
+// (one wavefront; the result in all lanes)  row(n): what else there is to do for a row of n entries
+template <typename F>
+__device__ __forceinline__ CellShape cell_shape(const int32_t* __restrict__ ptr, int rows, int lane, F&& row) {
+  CellShape c;
+#pragma unroll
+  for (int len = 0; len <= kPieceEntries; ++len) c.count[len] = c.at_least[len] = 0;
+  int full = 0;
+  for (int i0 = 0; i0 < rows; i0 += 64) {
+    const int i = i0 + lane;
+    const int n = i < rows ? ptr[i + 1] - ptr[i] : 0;
+    row(n);
+    full += n / kPieceEntries;
+#pragma unroll
+    for (int len = 1; len < kPieceEntries; ++len) c.count[len] += __popcll(__ballot(n % kPieceEntries == len));
+  }
+  for (int d = 32; d > 0; d >>= 1) full += __shfl_xor(full, d, 64);
+  c.count[kPieceEntries] = full;
+  int pieces = 0;
+#pragma unroll
+  for (int len = kPieceEntries; len >= 1; --len) {
+    pieces += c.count[len];
+    c.at_least[len] = (pieces + 3) >> 2;
+  }
+  return c;
+}
+
+// tiles and steps of every cell; counts[slot][0] += pairs with entries, [1] += slots of padding that hyb(1, k) has for them
+__global__ __launch_bounds__(256) void k_cell_tiles(CellArgs a, int32_t* cell_tiles, int32_t* cell_steps,
                                                     unsigned long long* counts) {
   const int lane = threadIdx.x & 63;
   const int64_t cell = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -459,88 +575,130 @@ __global__ __launch_bounds__(256) void k_cell_tiles(CellArgs a, int32_t* cell_ti
   const int64_t row0 = block << a.log2_block;
   const int rows = (int)min((int64_t)1 << a.log2_block, (int64_t)a.n_rows - row0);
   const int32_t* ptr = a.indptr + rel * a.n_rows + row0;
-  int pieces = 0, pairs = 0, pads = 0;
-  for (int i = lane; i < rows; i += 64) {
-    const int len = ptr[i + 1] - ptr[i];
-    pieces += (len + kPieceEntries - 1) / kPieceEntries;
+  int pairs = 0, pads = 0;
+  const CellShape c = cell_shape(ptr, rows, lane, [&](int len) {
     pairs += len > 0;
     if (len > 1) {
       const int log2w = 32 - __clz(len - 1);
       if (log2w <= a.k) pads += (1 << log2w) - len;
     }
-  }
+  });
   for (int d = 32; d > 0; d >>= 1) {
-    pieces += __shfl_down(pieces, d, 64);
     pairs += __shfl_down(pairs, d, 64);
     pads += __shfl_down(pads, d, 64);
   }
   if (lane == 0) {
-    cell_tiles[cell] = (pieces + kTileRows - 1) / kTileRows;
-    const int entries = ptr[rows] - ptr[0];
-    if (entries > 0) atomicAdd(&block_entries[block], entries);
-    unsigned long long* c = counts + (blockIdx.x & (kCountSlots - 1)) * kCountStride;
-    if (pairs) atomicAdd(&c[0], (unsigned long long)pairs);
-    if (pads) atomicAdd(&c[1], (unsigned long long)pads);
+    cell_tiles[cell] = c.tiles();
+    cell_steps[cell] = c.steps_before(c.at_least[1]);
+    unsigned long long* to = counts + (blockIdx.x & (kCountSlots - 1)) * kCountStride;
+    if (pairs) atomicAdd(&to[0], (unsigned long long)pairs);
+    if (pads) atomicAdd(&to[1], (unsigned long long)pads);
   }
 }
 
-// block_tile[b] = first tile of block b (b = n_blocks: their number)
+// block_tile[b] = first tile of block b (b = n_blocks: their number), block_step[b] = first step
 __global__ void k_block_tiles(int32_t n_blocks, int32_t n_rel, const int32_t* __restrict__ cell_tile0,
-                              const int32_t* __restrict__ total, int32_t* block_tile) {
+                              const int32_t* __restrict__ n_tiles, const int32_t* __restrict__ cell_step0,
+                              const int32_t* __restrict__ n_steps, int32_t* block_tile, int32_t* block_step) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b <= n_blocks) block_tile[b] = b < n_blocks ? cell_tile0[(int64_t)b * n_rel] : *total;
+  if (b > n_blocks) return;
+  block_tile[b] = b < n_blocks ? cell_tile0[(int64_t)b * n_rel] : *n_tiles;
+  block_step[b] = b < n_blocks ? cell_step0[(int64_t)b * n_rel] : *n_steps;
 }
 
-// the tiles of every cell: pieces in row order
-__global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* __restrict__ cell_tile0,
-                                                    const int32_t* __restrict__ total, RgmsTile* tiles,
-                                                    uint16_t* tile_rows, uint8_t* entry_piece) {
+// the tiles of every cell and their entries
+__global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* __restrict__ indices,
+                                                    const float* __restrict__ values, const int32_t* __restrict__ cell_tile0,
+                                                    const int32_t* __restrict__ cell_step0, RgmsTile* tiles, int2* entries) {
   const int lane = threadIdx.x & 63;
   const int64_t cell = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (cell >= a.n_cells) return;
   const int64_t block = cell / a.n_rel, rel = cell - block * a.n_rel;
-  const int tile0 = cell_tile0[cell], tile_end = cell + 1 < a.n_cells ? cell_tile0[cell + 1] : *total;
-  if (tile0 == tile_end) return;
   const int64_t row0 = block << a.log2_block;
   const int rows = (int)min((int64_t)1 << a.log2_block, (int64_t)a.n_rows - row0);
   const int32_t* ptr = a.indptr + rel * a.n_rows + row0;
-  const int cell_end = ptr[rows];
-  uint16_t* out = tile_rows + (size_t)tile0 * kTileRows;
-  for (int t = tile0 + lane; t < tile_end; t += 64) tiles[t].rel = (int)rel;
-  int done = 0;
-  for (int i0 = 0; i0 < rows; i0 += 64) {
-    const int i = i0 + lane;
-    int first = 0, len = 0;
-    if (i < rows) { first = ptr[i]; len = ptr[i + 1] - first; }
-    const int n = (len + kPieceEntries - 1) / kPieceEntries;
-    const int incl = wave_inclusive_scan(n, lane);
-    const int slot0 = done + incl - n;
-    for (int p = 0; p < n; ++p) {
-      const int slot = slot0 + p, at = first + p * kPieceEntries, end = min(at + kPieceEntries, first + len);
-      out[slot] = (uint16_t)i;
-      RgmsTile* t = tiles + tile0 + slot / kTileRows;
-      if (slot % kTileRows == 0) t->first = at;
-      if (slot % kTileRows == kTileRows - 1 || end == cell_end) t->end = end;
-    }
-    // an entry's piece, 64 entries of a row at a time (short rows: a lane each)
-    if (len <= 8)
-      for (int k = 0; k < len; ++k) entry_piece[first + k] = (uint8_t)(slot0 % kTileRows);
-    unsigned long long longer = __ballot(len > 8);
-    while (longer) {
-      const int src = __builtin_ctzll(longer);
-      longer &= longer - 1;
-      const int f = __shfl(first, src, 64), l = __shfl(len, src, 64), s0 = __shfl(slot0, src, 64);
-      for (int k = lane; k < l; k += 64) entry_piece[f + k] = (uint8_t)((s0 + k / kPieceEntries) % kTileRows);
-    }
-    done += __shfl(incl, 63, 64);
-  }
-  for (int i = done + lane; i < (tile_end - tile0) * kTileRows; i += 64) out[i] = kNoRow;
-}
+  if (ptr[rows] == ptr[0]) return;
+  // the rows with entries, so that the lanes below have one each
+  __shared__ uint16_t filled[4][1 << kMaxLog2Block];
+  uint16_t* rows_of = filled[threadIdx.x >> 6];
+  int n_filled = 0, row = 0;
+  const CellShape c = cell_shape(ptr, rows, lane, [&](int n) {
+    const unsigned long long some = __ballot(n > 0);
+    if (n > 0) rows_of[n_filled + __popcll(some & (((unsigned long long)1 << lane) - 1))] = (uint16_t)(row + lane);
+    n_filled += __popcll(some);
+    row += 64;
+  });
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const int tile0 = cell_tile0[cell], step0 = cell_step0[cell];
+  const int n_tiles = c.tiles();
+  int n_pieces = 0;
+#pragma unroll
+  for (int len = 1; len <= kPieceEntries; ++len) n_pieces += c.count[len];
 
-__global__ __launch_bounds__(256) void k_pair_entries(int64_t nnz, const int32_t* __restrict__ cols,
-                                                      const float* __restrict__ vals, int2* entries) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nnz) entries[i] = make_int2(cols[i], __float_as_int(vals[i]));
+  // what a tile is, and the rows of pieces that are none
+  auto quads_with = [&](int quad0, int e) { return min(max(c.at_least[e + 1] - quad0, 0), 4); };
+  for (int t = lane; t < n_tiles; t += 64) {
+    RgmsTile* to = tiles + tile0 + t;
+    uint32_t shape = 0;
+    int steps = 0;
+#pragma unroll
+    for (int e = 0; e < kPieceEntries; ++e) {
+      const int n = quads_with(4 * t, e);
+      shape |= (uint32_t)n << (3 * e) | (uint32_t)(steps & 15) << (12 + 4 * e);
+      steps += n;
+    }
+    to->first = step0 + c.steps_before(4 * t);
+    to->rel = (int)rel;
+    to->shape = shape;
+    to->n_steps = steps;
+    for (int i = 0; i < kTileRows; ++i)
+      if (kTileRows * t + i >= n_pieces) to->rows[i] = (uint16_t)(1 << a.log2_block);
+  }
+
+  // piece number `place`: `len` entries from `from` on, of row `row`
+  auto put = [&](int place, int row, int from, int len) {
+    const int quad = place >> 2, quad0 = quad & ~3;
+    tiles[tile0 + (place >> 4)].rows[place & 15] = (uint16_t)row;
+    const int steps = c.steps_of(quad);
+    const int i_end = place == n_pieces - 1 ? 4 : (place & 3) + 1;  // (the last piece fills its quad)
+    int64_t step = step0 + c.steps_before(quad0) + (quad & 3);
+#pragma unroll
+    for (int e = 0; e < kPieceEntries; ++e) {
+      if (e >= steps) break;
+      const int at = from + min(e, len - 1);
+      const int col = indices[at];
+      int2* to = entries + step * 4 + (place & 3);
+      *to = e < len ? make_int2(col, __float_as_int(values[at])) : make_int2((int)((uint32_t)col | kPad), 0);
+      for (int i = (place & 3) + 1; i < i_end; ++i) *++to = make_int2((int)((uint32_t)col | kPad), 0);
+      step += quads_with(quad0, e);
+    }
+  };
+  int place_of[kPieceEntries + 1];  // of the next piece of every length
+#pragma unroll
+  for (int len = kPieceEntries; len >= 1; --len)
+    place_of[len] = len == kPieceEntries ? 0 : place_of[len == kPieceEntries ? len : len + 1] + c.count[len == kPieceEntries ? len : len + 1];
+  for (int i0 = 0; i0 < n_filled; i0 += 64) {
+    int i = 0, from = 0, n = 0;
+    if (i0 + lane < n_filled) { i = rows_of[i0 + lane]; from = ptr[i]; n = ptr[i + 1] - from; }
+    const int full = n / kPieceEntries, rest = n % kPieceEntries;
+    int place = 0;
+#pragma unroll
+    for (int len = 1; len < kPieceEntries; ++len) {
+      const unsigned long long same = __ballot(rest == len);
+      if (rest == len) place = place_of[len] + __popcll(same & (((unsigned long long)1 << lane) - 1));
+      place_of[len] += __popcll(same);
+    }
+    if (rest > 0) put(place, i, from + n - rest, rest);
+    const int incl = wave_inclusive_scan(full, lane);
+    const int place0 = place_of[kPieceEntries] + incl - full;
+    if (full == 1) put(place0, i, from, kPieceEntries);
+    for (unsigned long long longer = __ballot(full > 1); longer; longer &= longer - 1) {
+      const int src = __builtin_ctzll(longer);
+      const int f = __shfl(from, src, 64), m = __shfl(full, src, 64), p0 = __shfl(place0, src, 64), r = __shfl(i, src, 64);
+      for (int k = lane; k < m; k += 64) put(p0 + k, r, f + k * kPieceEntries, kPieceEntries);
+    }
+    place_of[kPieceEntries] += __shfl(incl, 63, 64);
+  }
 }
 
 // Rows per block: 32 entries for every (relation, block), so that tiles fill (16: 4 to 14 % slower, 64: the same), as long
@@ -579,9 +737,7 @@ struct sptir_rgms_handle {
   int32_t log2_block;
   int64_t n_tiles;
   sptir::RgmsTile* tiles;
-  uint16_t* tile_rows;    // [n_tiles][16]
-  int2* entries;          // [nnz]
-  uint8_t* entry_piece;   // [nnz]
+  int2* entries;          // [n_steps][4]
   sptir::RgmsItem* items;
   int32_t n_items;
   int4* divided;          // divided blocks: block, first part, parts
@@ -643,15 +799,17 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
   const int64_t cell_wgs = (ca.n_cells + 3) / 4;
   const int64_t n_seq = (int64_t)(scan_room(std::max<int64_t>(ca.n_cells, 1)) / kScanSeq);
 
-  // temporaries: validation flags and counts (one copy brings both to the host), cells, block starts
+  // temporaries: validation flags and counts, block starts (one copy brings them to the host), cells
   constexpr size_t kReport = (kValidationWords + kCountSlots * kCountStride) * sizeof(unsigned long long);
-  const size_t cleared = kReport + sizeof(int32_t) * (size_t)n_blocks;
-  size_t tmp_bytes = cleared;
+  size_t tmp_bytes = kReport;
   auto reserve = [](size_t* size, size_t bytes) { const size_t at = *size; *size = (at + bytes + 255) & ~(size_t)255; return at; };
   const size_t o_block_tile = reserve(&tmp_bytes, sizeof(int32_t) * ((size_t)n_blocks + 1));
-  const size_t report_bytes = o_block_tile + sizeof(int32_t) * ((size_t)n_blocks + 1);
+  const size_t o_block_step = reserve(&tmp_bytes, sizeof(int32_t) * ((size_t)n_blocks + 1));
+  const size_t report_bytes = o_block_step + sizeof(int32_t) * ((size_t)n_blocks + 1);
   const size_t o_cells = reserve(&tmp_bytes, sizeof(int32_t) * (size_t)n_seq * kScanSeq);
+  const size_t o_cell_steps = reserve(&tmp_bytes, sizeof(int32_t) * (size_t)n_seq * kScanSeq);
   const size_t o_seq = reserve(&tmp_bytes, sizeof(int32_t) * ((size_t)n_seq + 1));
+  const size_t o_step_seq = reserve(&tmp_bytes, sizeof(int32_t) * ((size_t)n_seq + 1));
   char* tmp = (char*)scratch_alloc(tmp_bytes, p->alloc, p->alloc_ctx, stream);
   PinnedBuf host = pinned_acquire(std::max(report_bytes, (size_t)16));
   std::vector<RgmsItem> items;
@@ -667,20 +825,24 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
     unsigned long long* d_flags = (unsigned long long*)tmp;
     unsigned long long* d_counts = d_flags + kValidationWords;
     int32_t* d_block_tile = (int32_t*)(tmp + o_block_tile);
+    int32_t* d_block_step = (int32_t*)(tmp + o_block_step);
     int32_t* d_cells = (int32_t*)(tmp + o_cells);
+    int32_t* d_cell_steps = (int32_t*)(tmp + o_cell_steps);
     int32_t* d_seq = (int32_t*)(tmp + o_seq);
+    int32_t* d_step_seq = (int32_t*)(tmp + o_step_seq);
     if (cell_wgs > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
-    RGMS_HIP(hipMemsetAsync(tmp, 0, cleared, stream));
+    RGMS_HIP(hipMemsetAsync(tmp, 0, kReport, stream));
     launch_validation(stacked, false, d_flags, stream);
     if (ca.n_cells > 0) {
       // (the numbers below mean something only if the verdict is good, and index nothing before it is known)
-      hipLaunchKernelGGL(k_cell_tiles, dim3((unsigned)cell_wgs), dim3(256), 0, stream, ca, d_cells,
-                         (int32_t*)(tmp + kReport), d_counts);
+      hipLaunchKernelGGL(k_cell_tiles, dim3((unsigned)cell_wgs), dim3(256), 0, stream, ca, d_cells, d_cell_steps,
+                         d_counts);
       RGMS_HIP(hipGetLastError());
       st = device_exclusive_scan(d_cells, ca.n_cells, d_seq, stream);
+      if (st == SPTIR_OK) st = device_exclusive_scan(d_cell_steps, ca.n_cells, d_step_seq, stream);
       if (st != SPTIR_OK) goto fail;
       hipLaunchKernelGGL(k_block_tiles, dim3((unsigned)(n_blocks / 256 + 1)), dim3(256), 0, stream, n_blocks,
-                         n_relations, d_cells, d_seq + n_seq, d_block_tile);
+                         n_relations, d_cells, d_seq + n_seq, d_cell_steps, d_step_seq + n_seq, d_block_tile, d_block_step);
       RGMS_HIP(hipGetLastError());
     }
     RGMS_HIP(hipMemcpyAsync(host.p, tmp, report_bytes, hipMemcpyDeviceToHost, stream));
@@ -697,15 +859,17 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
       p->n_pads += (int64_t)counts[s * kCountStride + 1];
     }
     const int32_t* block_tile = (const int32_t*)(host.p + o_block_tile);
+    const int32_t* block_step = (const int32_t*)(host.p + o_block_step);
     p->n_tiles = n_blocks > 0 ? block_tile[n_blocks] : 0;
+    const int64_t n_steps = n_blocks > 0 ? block_step[n_blocks] : 0;  // (at most nnz: a step has an entry)
 
     // ---- work items: a block each.  A block of more than twice the mean work is divided; where there are few blocks,
     //      all are, into about 512 items.
-    const int32_t* block_entries = (const int32_t*)(host.p + kReport);
     auto tiles_of = [&](int32_t b) { return block_tile[b + 1] - block_tile[b]; };
-    auto cost_of = [&](int32_t b) { return (int64_t)tiles_of(b) + block_entries[b] / 32; };  // (measured: 32 entries cost about what a tile does)
-    const int64_t cost = p->n_tiles + nnz / 32, mean = n_blocks > 0 ? cost / n_blocks : 0;
-    const int64_t most = n_blocks >= 160 ? std::max<int64_t>(64, 2 * mean) : std::max<int64_t>(8, cost / 512);
+    auto cost_of = [&](int32_t b) { return (int64_t)tiles_of(b) + (block_step[b + 1] - block_step[b]) / 8; };
+    const int64_t cost = p->n_tiles + n_steps / 8, mean = n_blocks > 0 ? cost / n_blocks : 0;
+    // (an item's tiles lie within 4 GB)
+    const int64_t most = std::min<int64_t>(n_blocks >= 160 ? std::max<int64_t>(64, 2 * mean) : std::max<int64_t>(8, cost / 512), 1 << 26);
     items.reserve((size_t)n_blocks + 16);
     for (int32_t b = 0; b < n_blocks; ++b) {  // divided blocks first: theirs are the longest items
       const int64_t c = cost_of(b);
@@ -726,9 +890,7 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
     // ---- the handle's arrays
     size_t bytes = 0;
     const size_t o_tiles = reserve(&bytes, sizeof(RgmsTile) * (size_t)p->n_tiles);
-    const size_t o_rows = reserve(&bytes, sizeof(uint16_t) * (size_t)p->n_tiles * kTileRows);
-    const size_t o_entries = reserve(&bytes, sizeof(int2) * (size_t)nnz);
-    const size_t o_piece = reserve(&bytes, (size_t)nnz);
+    const size_t o_entries = reserve(&bytes, sizeof(int2) * 4 * (size_t)n_steps);
     const size_t o_items = reserve(&bytes, sizeof(RgmsItem) * items.size());
     const size_t o_divided = reserve(&bytes, sizeof(int4) * divided.size());
     const size_t o_partial = reserve(&bytes, sizeof(float) * (((size_t)p->n_parts * workspace_d_out) << p->log2_block));
@@ -738,18 +900,13 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
     p->device_bytes = bytes;
     char* base = (char*)p->blob;
     p->tiles = (RgmsTile*)(base + o_tiles);
-    p->tile_rows = (uint16_t*)(base + o_rows);
     p->entries = (int2*)(base + o_entries);
-    p->entry_piece = (uint8_t*)(base + o_piece);
     p->items = (RgmsItem*)(base + o_items);
     p->divided = (int4*)(base + o_divided);
     p->partial = (float*)(base + o_partial);
     if (p->n_tiles > 0)
-      hipLaunchKernelGGL(k_fill_tiles, dim3((unsigned)cell_wgs), dim3(256), 0, stream, ca, d_cells, d_seq + n_seq,
-                         p->tiles, p->tile_rows, p->entry_piece);
-    if (nnz > 0)
-      hipLaunchKernelGGL(k_pair_entries, dim3((unsigned)((nnz + 255) / 256)), dim3(256), 0, stream, nnz,
-                         stacked->indices, stacked->values, p->entries);
+      hipLaunchKernelGGL(k_fill_tiles, dim3((unsigned)cell_wgs), dim3(256), 0, stream, ca, stacked->indices, stacked->values,
+                         d_cells, d_cell_steps, p->tiles, p->entries);
     RGMS_HIP(hipGetLastError());
     if (!items.empty())
       RGMS_HIP(hipMemcpyAsync(p->items, items.data(), sizeof(RgmsItem) * items.size(), hipMemcpyHostToDevice, stream));
@@ -780,8 +937,7 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
     return SPTIR_ERR_UNSUPPORTED;
   hipStream_t stream = (hipStream_t)stream_;
   RgmsArgs a;
-  a.items = p->items; a.tiles = p->tiles; a.tile_rows = (const ushort4*)p->tile_rows;
-  a.entries = p->entries; a.entry_piece = p->entry_piece;
+  a.items = p->items; a.tiles = p->tiles; a.entries = p->entries;
   a.X = X; a.W = W; a.Y = Y; a.partial = p->partial;
   a.n_rows = p->n_rows; a.log2_block = p->log2_block; a.d_out = d_out;
   const bool large_block = p->log2_block == kMaxLog2Block;
@@ -806,7 +962,7 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs
   // and feature sizes: against 8 everywhere it is alike in the mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)
   a.n_waves = large_block ? 16 : large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;
-  const size_t lds = sizeof(double) * ((size_t)a.width << p->log2_block) + (ordered ? sizeof(int) * (a.width / 16) : 0);
+  const size_t lds = sizeof(double) * (size_t)a.width * (((size_t)1 << p->log2_block) + 1) + (ordered ? sizeof(int) * (a.width / 16) : 0);
   const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);
   auto divided = [&](const float* partial) {
     if (p->n_divided > 0)

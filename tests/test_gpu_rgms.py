@@ -266,3 +266,35 @@ def test_rgms_rows_of_a_block(gpu_lib, mean, rows):
         h = gpu_lib.sptir_rgms_build(n_rel, n, n, dev(w.indptr), dev(w.indices), dev(w.values), -1, 32)
         assert gpu_lib.sptir_rgms_info(h)["row_block"] == 256          # (tiles that take turns)
         h.destroy()
+
+
+@pytest.mark.parametrize("workspace", [0, 96])
+@pytest.mark.parametrize("d_in,d_out", [(32, 32), (32, 96), (64, 64), (128, 32)])
+def test_rgms_quads_and_steps(gpu_lib, d_in, d_out, workspace):
+    """Cells of 0 to 37 pairs of 0 to 5 entries each: pieces of up to four entries, quads and tiles of every length, places without
+    an entry, with NaN in a row of X that a few pairs name and others share a step with."""
+    rng = np.random.default_rng(d_in + d_out)
+    n, n_rel, block = 38 * 32, 3, 32                       # (32 rows per block: so many entries are in a cell)
+    counts = np.zeros((n_rel, n), dtype=np.int64)
+    for b in range(n // block):
+        for r in range(n_rel):
+            pairs = min(b, block)
+            at = b * block + rng.choice(block, pairs, replace=False)
+            counts[r, at] = [rng.integers(1, 6, pairs), np.full(pairs, 1 + b % 5), 1 + np.arange(pairs) % 4][r]
+            if b > block:
+                counts[r, at[: b - block]] += 4            # two pieces each
+    w0 = workloads.random_csr(n_rel * n, n, counts.reshape(-1), 7, 1, "uniform")
+    X = rng.standard_normal((n, d_in)).astype(np.float32)
+    W = rng.standard_normal((n_rel, d_in, d_out)).astype(np.float32)
+    for bad in (False, True):
+        if bad:
+            X[np.unique(w0.indices)[::97]] = np.nan
+        w = workloads.HeteroWorkload("quads", n, n_rel, w0.indptr, w0.indices, w0.values, X, W)
+        Y, info = run_rgms(gpu_lib, w, workspace_d_out=workspace)
+        assert info["row_block"] == block and info["n_stacked_rows_stored"] == int((counts > 0).sum())
+        with np.errstate(invalid="ignore"):
+            Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, X, W)
+        finite = np.isfinite(Yr)
+        assert finite.all() != bad and finite.any()
+        assert np.array_equal(np.isfinite(Y), finite)
+        assert_y_close(np.where(finite, Y, 0), np.where(finite, Yr, 0), np.where(finite, Sr, 0), f"d_in={d_in} d_out={d_out}")
