@@ -312,7 +312,8 @@ sptir_status_t sptir_spmm(const sptir_hyb_t* hyb, const float* X, float* Y, int3
  * benchmark can price each kernel by the time it really took inside the call.  Synchronises `stream` before it
  * returns; creates and destroys a few events.  Same results as sptir_spmm.
  *   ms_lists   the chunk-list launches (k_spmm_hyb), n_list_launches of them
- *   ms_heavy   the heavy-piece launches (k_spmm_heavy) and those over column slices (k_spmm_slices)
+ *   ms_heavy   the heavy-piece launches (k_spmm_heavy; sptir_spmm itself may let them share the last launch of the
+ *              chunk lists) and those over column slices (k_spmm_slices)
  *   ms_reduce  the launches that add the heavy pieces' partial sums to Y (k_heavy_reduce) and the slices' (k_slice_sums)
  */
 typedef struct {

@@ -642,14 +642,15 @@ __global__ __launch_bounds__(kHybBlock) void k_spmm_heavy(HeavyArgs a) {
   heavy_workgroup<VEC, LG, IDX32, WIDE, UNIT>(a, blockIdx.x, smem);
 }
 
-// Both in one launch, for a matrix whose chunk lists and heavy lists are one launch each and small: the first
-// n_heavy_workgroups workgroups (a multiple of 8, so that the others keep their place among the XCDs; those past the
-// last heavy list leave at once) walk heavy lists, the rest chunk lists, and neither waits for the other.
+// Both in one launch, neither waiting for the other: the first n_first workgroups (a multiple of 8, so that the others keep
+// their place among the XCDs; those past the last list leave at once) walk one kind, the rest the other (rule at its launch).
 template <int VEC, int LG, bool IDX32, bool WIDE, bool UNIT>
-__global__ __launch_bounds__(kHybBlock) void k_spmm_hyb_heavy(SpmmArgs a, HeavyArgs ha, unsigned n_heavy_workgroups) {
+__global__ __launch_bounds__(kHybBlock) void k_spmm_hyb_heavy(SpmmArgs a, HeavyArgs ha, unsigned n_first, int heavy_first) {
   extern __shared__ __align__(16) float smem[];
-  if (blockIdx.x < n_heavy_workgroups) heavy_workgroup<VEC, LG, IDX32, WIDE, UNIT>(ha, blockIdx.x, smem);
-  else lists_workgroup<VEC, LG, IDX32, WIDE, UNIT>(a, blockIdx.x - n_heavy_workgroups, smem);
+  const bool first = blockIdx.x < n_first;
+  const unsigned bid = first ? blockIdx.x : blockIdx.x - n_first;
+  if (first == (heavy_first != 0)) heavy_workgroup<VEC, LG, IDX32, WIDE, UNIT>(ha, bid, smem);
+  else lists_workgroup<VEC, LG, IDX32, WIDE, UNIT>(a, bid, smem);
 }
 
 // Y[r, feat0 + f] += (row_val[r] *) the partial sums of row r's heavy pieces.  SPLIT groups of (width / VEC) threads per
@@ -823,13 +824,14 @@ int shared_list_waves(int64_t n_lists, int64_t n_quads, int64_t longest_chunks, 
 }
 
 template <typename V>
-void launch_heavy_and_lists(V, unsigned n_heavy_workgroups, unsigned n_list_workgroups, size_t lds_bytes,
+void launch_heavy_and_lists(V, int64_t n_heavy_workgroups, int64_t n_list_workgroups, bool heavy_first, size_t lds_bytes,
                             hipStream_t stream, const SpmmArgs& a, const HeavyArgs& ha) {
   auto* kernel = &k_spmm_hyb_heavy<V::vec, V::lg, V::idx32, V::wide, V::unit>;
   static OncePerDevice allowed;
   allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds_bytes, allowed);
-  hipLaunchKernelGGL(kernel, dim3(n_heavy_workgroups + n_list_workgroups), dim3(kHybBlock), lds_bytes, stream, a, ha,
-                     n_heavy_workgroups);
+  const int64_t n_first = ((heavy_first ? n_heavy_workgroups : n_list_workgroups) + 7) / 8 * 8;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(n_first + (heavy_first ? n_list_workgroups : n_heavy_workgroups))), dim3(kHybBlock),
+                     lds_bytes, stream, a, ha, (unsigned)n_first, heavy_first ? 1 : 0);
 }
 
 // workgroups of k_spmm_hyb the GPU holds at once (0: unknown)
@@ -998,6 +1000,26 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
     ha->map_mode = gh->map_mode; ha->map_param = gh->map_param;
     return true;
   };
+  // The last launch of the chunk lists takes the heavy lists along (those of the first partial_feat features, from feat_begin
+  // on; a timed call launches each kind by itself): each fills the CUs that the other leaves idle.  A few heavy lists go first; more
+  // than there are chunk lists, which are launched longest first, or those of rounds, whose lists start together, last.  False:
+  // nothing was launched.  50,021 rows, 1.5 M entries, 41 features 52.1 -> 37.9 us.  Against two launches (one only where the chunk
+  // lists were a single launch, not in rounds, and more than the heavy ones), 110 drawn power-law graphs with heavy lists: single
+  // launch 1.08 times as fast in the mean (0.99 to 1.57), in rounds 1.07 (0.98 to 1.31), several launches 1.01 (0.99 to 1.02).
+  auto lists_and_heavy = [&](int feat_begin, int feat_end, bool few_heavy_first) -> bool {
+    HeavyArgs ha;
+    Geometry gh;
+    if (h->n_heavy <= 0 || idx32 != idx32_all ||
+        !heavy_launch_shape(feat_begin, std::min(feat_end - feat_begin, partial_feat), &ha, &gh) ||
+        gh.grid + g.grid + 8 > 0x7FFFFFFF)
+      return false;
+    with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) {
+      if (timers) launch_lists(v, g, lds_bytes, stream, a);
+      else launch_heavy_and_lists(v, gh.grid, g.grid, few_heavy_first && gh.grid <= g.grid, lds_bytes, stream, a, ha);
+    });
+    heavy_with_lists = !timers;
+    return true;
+  };
   // Heavy pieces: partial sums of partial_feat features at a time, added to the Y the lists have written, for
   // the features feat_begin .. feat_end - 1.  already_launched: the heavy
   // lists went with the chunk lists' launch, only the sums remain to be added.
@@ -1013,7 +1035,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
       // slice of X, or two while it passes a partition boundary; a launch per partition measured slower (each
       // ended with a partly filled GPU: 1.62 ms against 1.53 on the largest graph).
       if (!heavy_launch_shape(feat0, width, &ha, &gh)) return SPTIR_ERR_OVERFLOW;
-      if (!already_launched) {
+      if (!already_launched || feat0 > feat_begin) {
         with_variant(g.vec, g.lg, idx32_all, wide, unit, [&](auto v) { launch_heavy(v, gh, stream, ha); });
         if (timers) timers->mark(stream, LaunchTimers::kHeavy, 1);
       }
@@ -1053,6 +1075,8 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
     for (int tile0 = 0; tile0 < all_tiles; tile0 += per_sweep) {
       g.n_tiles = all_tiles - tile0 < per_sweep ? all_tiles - tile0 : per_sweep;
       a.n_tiles = g.n_tiles; a.tile0 = tile0;
+      heavy_with_lists = false;
+      const int feat_begin = tile0 * tile_floats, feat_end = std::min(feat, (tile0 + g.n_tiles) * tile_floats);
       int64_t per_round = (int64_t)capacity / g.n_tiles * kHybWaves;  // row blocks
       if (per_round < 8 * kHybWaves) per_round = 8 * kHybWaves;
       const int64_t n_rounds = (h->n_row_blocks + per_round - 1) / per_round;
@@ -1063,13 +1087,14 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         a.n_row_blocks = (int32_t)here;
         if (!plan_tiles((here + kHybWaves - 1) / kHybWaves, &g)) return SPTIR_ERR_OVERFLOW;
         a.map_mode = g.map_mode; a.map_param = g.map_param;
-        with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, lds_bytes, stream, a); });
+        const bool last = first + here == h->n_row_blocks;
+        if (!last || !lists_and_heavy(feat_begin, feat_end, false))
+          with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, lds_bytes, stream, a); });
         ++n_list_launches;
       }
       if (timers) timers->mark(stream, LaunchTimers::kLists, n_list_launches);
       n_list_launches = 0;
-      const int feat_end = (tile0 + g.n_tiles) * tile_floats;
-      const sptir_status_t st = heavy_sweeps(tile0 * tile_floats, feat_end < feat ? feat_end : feat);
+      const sptir_status_t st = heavy_sweeps(feat_begin, feat_end, heavy_with_lists);
       if (st != SPTIR_OK) return st;
     }
   } else {
@@ -1091,20 +1116,10 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         a.rb_order = h->rb_order + (size_t)phase * h->n_row_blocks;
         a.accumulate = phase > 0;
         a.X = wide ? X : X + (size_t)phase * (size_t)span * (size_t)feat;
-        // A matrix whose chunk lists are one launch and whose heavy lists are the smaller part runs both in one
-        // launch: the few wavefronts of the heavy lists then fill CUs the chunk lists leave idle instead of
-        // waiting for them (19,717 rows, 88,651 non-zeros, two heavy rows: 0.026 -> 0.023 ms per call).
-        HeavyArgs ha;
-        Geometry gh;
-        if (h->n_heavy > 0 && h->n_phases == 1 && per_sweep == all_tiles && feat <= partial_feat &&
-            idx32 == idx32_all && heavy_launch_shape(0, feat, &ha, &gh) && gh.grid <= g.grid &&
-            (gh.grid + 7) / 8 * 8 + g.grid <= 0x7FFFFFFF) {
-          const int64_t heavy_wgs = (gh.grid + 7) / 8 * 8;
-          with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) {
-            launch_heavy_and_lists(v, (unsigned)heavy_wgs, (unsigned)g.grid, lds_bytes, stream, a, ha);
-          });
-          heavy_with_lists = true;
-        } else if (waves > 1) {
+        const bool last = phase + 1 == h->n_phases && tile0 + g.n_tiles == all_tiles;
+        ++n_list_launches;
+        if (last && lists_and_heavy(0, feat, true)) continue;
+        if (waves > 1) {
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) {
             launch_shared_lists(v, gs, waves, lds_bytes / kHybWaves * waves, stream, a);
           });
@@ -1112,7 +1127,6 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         } else {
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, lds_bytes, stream, a); });
         }
-        ++n_list_launches;
       }
     }
   }
