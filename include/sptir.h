@@ -94,7 +94,7 @@ typedef enum {
    * chunks: the column itself), bits 20..26 the row relative to the row block (heavy chunks: the slot at which a
    * piece ends in the chunk), bit 27 "the slot holds an entry", bits 28..30 the chunk kind (3: eight queues of
    * eight slots, slot 8q + j continuing queue q; 7: 64 slots of one row piece), bit 31 the hand-over flag (queue
-   * chunk: this slot is the last entry of a row piece; otherwise the chunk's: a piece ends in it).  Without
+   * chunk: this slot is the last entry of a row piece in its queue; otherwise the chunk's: a piece ends in it).  Without
    * compact_stream the column word is the column and the row word holds bits 0..15 row (or end slot), 16..21 kind
    * (3 or 31), bit 22 hand-over, bit 23 / the value -1 "no entry". */
   SPTIR_PLAN_STREAM = 100,            /* int32 */

@@ -367,6 +367,7 @@ struct CellShape {
   int32_t log2_rb, n_rb, ppg, n_phases;
   int32_t long_len;  // pieces with more real entries are not in the lists (heavy pieces)
   int32_t wide_margin;  // see below
+  bool cut_queues = false;  // see there too
   int64_t R;
 };
 
@@ -414,7 +415,13 @@ __device__ __forceinline__ void cell_bounds_workgroup(const CellShape& cs, unsig
 //    (A piece of 60 entries among rows of four makes its queue, and with it the list, 60 entries long: 14,964 rows,
 //    156,998 entries in 16 partitions 59 -> 33 us.  Two chunks of margin, as the wide chunk costs one; in rounds, whose
 //    lists are long enough to be even, four.)
-// The rows of one partition are distinct, so two queues never hand over the same row of Y in one instruction.
+// Where that takes a chunk more than the entries need, the queues may be cut instead (cut_queues): the pieces follow each other
+// through all eight queues, each as long as the entries need, and what does not fit the end of a queue goes on at the start
+// of the next, flagged at both ends.  A dozen or two of long rows do not divide by eight: rows of 37 +- 12 entries in blocks of
+// 32 walk 9 % more slots than there are entries when dealt whole, 3 % when cut (132,534 rows of 37 in each of eight partitions,
+// 128 features: 1031 -> 973 us; cut only where two chunks are saved 1010, where four 1031).
+// The rows of one partition are distinct, and a piece that is cut is a chunk shorter than a queue, so that its ends lie in
+// different chunks: two queues never hand over the same row of Y in one instruction.
 __device__ __forceinline__ int cells_per_part(const CellShape& cs) { return cs.nb + 1; }
 __device__ __forceinline__ int cells_per_group(const CellShape& cs) { return cs.ppg * (cs.nb + 1) + 1; }
 
@@ -422,9 +429,11 @@ __device__ __forceinline__ int chunks_of_length(int len) { return (len + kChunkS
 inline int64_t chunks_of_slots(int64_t slots) { return (slots + kChunkSlots - 1) / kChunkSlots; }
 
 // What becomes of a piece of at most long_len entries, one word per piece (in the order of row_ids):
-//   queued    its first entry's position in the queue (bits 0..27) and the queue (28..30)
+//   queued    its first entry's position in the queue (bits 0..27; 0..26 where queues may be cut) and the queue (28..30)
+//   cut       bit 27: the position (bits 0..14), the chunks of the queue (15..26) and the queue; the rest is in the next queue
 //   cut wide  bit 31 and the chunks of the pieces before it in its bin's cell
-constexpr uint32_t kWidePiece = 0x80000000u;
+constexpr uint32_t kWidePiece = 0x80000000u, kCutPiece = 1u << 27;
+constexpr int kCutPosBits = 15, kCutQueueMax = 1 << kCutPosBits;  // entries of a queue that may be cut: fewer than this
 
 __device__ __forceinline__ unsigned min_of_8(unsigned v) {  // over the eight lanes of a lane group
   v = min(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));   // quad_perm 1 0 3 2
@@ -437,10 +446,11 @@ __device__ __forceinline__ unsigned min_of_8(unsigned v) {  // over the eight la
 // read a length at a time, once to count and once more to fill, took 35 + 93 us on 169,343 rows; this takes 15.)
 // Writes the chunk counts of the partition's cells, a word per piece (see above) and the entries of every queue.
 constexpr int kDealParts = 8;  // partitions per workgroup, a wavefront
+template <bool MAY_CUT>
 __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n_parts, const int32_t* __restrict__ bin_rb_ptr,
                                               const int32_t* __restrict__ row_len, long long* __restrict__ cell_chunks,
                                               uint32_t* __restrict__ dealt, int32_t* __restrict__ queue_len) {
-  extern __shared__ int piece_len[];                 // [kDealParts][rows of a row block]: lengths, then positions
+  extern __shared__ int piece_len[];                 // [kDealParts][rows of a row block]: lengths (then words), then positions
   __shared__ int before[kDealParts][kMaxBins + 1];   // pieces before a bin, widest bin first
   __shared__ int first[kDealParts][kMaxBins];        // first piece of a bin
   __shared__ int wide[kDealParts][kMaxBins];         // chunks cut wide so far
@@ -490,14 +500,19 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
     return first[part][b] + (i - before[part][b]);
   };
   unsigned to_deal = 0;  // entries not dealt yet (fewer than 2^31)
+  unsigned most = 0;     // of the longest piece
   for (int i = l; i < n; i += 8) {
     const int q = piece(i), len = max(row_len[q], 0);  // (of a long row: nothing to deal)
     len_of[i] = len;
     piece_at[i] = q;
-    if (len <= cs.long_len) to_deal += (unsigned)len;
+    if (len <= cs.long_len) { to_deal += (unsigned)len; most = max(most, (unsigned)len); }
   }
 #pragma unroll
-  for (int d = 1; d < 8; d <<= 1) to_deal += (unsigned)__shfl_xor((int)to_deal, d, 8);
+  for (int d = 1; d < 8; d <<= 1) {
+    to_deal += (unsigned)__shfl_xor((int)to_deal, d, 8);
+    most = max(most, (unsigned)__shfl_xor((int)most, d, 8));
+  }
+  const unsigned total = to_deal;
   __syncthreads();
 
   unsigned load = 0;  // entries of queue l
@@ -510,7 +525,8 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
       to_deal -= (unsigned)len;
       const unsigned best = min_of_8(load * 8 + l);  // of equally short queues the first
       uint32_t word;
-      if (len > kChunkSlots ? (unsigned)len > share : (best >> 3) + (unsigned)len > level + (unsigned)cs.wide_margin) {
+      if ((len > kChunkSlots ? (unsigned)len > share : (best >> 3) + (unsigned)len > level + (unsigned)cs.wide_margin) ||
+          (MAY_CUT && (best >> 3) + (unsigned)len >= kCutPiece)) {
         const int at = cs.nb - 1 - bin_of_length(len, cs.k);
         const int w = wide[part][at];
         if (l == 0) wide[part][at] = w + chunks_of_length(len);
@@ -528,10 +544,40 @@ __global__ __launch_bounds__(8 * kDealParts) void k_deal(CellShape cs, int64_t n
 #pragma unroll
   for (int d = 1; d < 8; d <<= 1) longest = max(longest, (unsigned)__shfl_xor((int)longest, d, 8));
   __syncthreads();
+  bool cut = false;
+  if constexpr (MAY_CUT) {
+    unsigned n_wide = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxBins / 8; ++i) n_wide += (unsigned)wide[part][l * (kMaxBins / 8) + i];
+#pragma unroll
+    for (int d = 1; d < 8; d <<= 1) n_wide += (unsigned)__shfl_xor((int)n_wide, d, 8);
+    const unsigned per_queue = (total + kChunkSlots - 1) / kChunkSlots * 8;
+    cut = per_queue / 8 < ((longest + 7) >> 3) + n_wide && most + 8 <= per_queue && per_queue < (unsigned)kCutQueueMax;
+    if (cut) {
+      unsigned done = 0;  // entries of the pieces before
+      for (int i0 = 0; i0 < n; i0 += 8) {
+        const int i = i0 + l, own = i < n ? max(row_len[piece_at[i]], 0) : 0;
+        const unsigned here = own <= cs.long_len ? (unsigned)own : 0u;
+        unsigned upto = here;
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) {
+          const unsigned o = (unsigned)__shfl_up((int)upto, d, 8);
+          if (l >= d) upto += o;
+        }
+        const unsigned at = done + upto - here, queue = at / per_queue, pos = at - queue * per_queue;
+        if (i < n)
+          len_of[i] = (int)((queue << 28) | pos | (pos + here > per_queue ? kCutPiece | (per_queue / 8 << kCutPosBits) : 0u));
+        done += (unsigned)__shfl((int)upto, 7, 8);
+      }
+      const unsigned start = l * per_queue;
+      load = total <= start ? 0u : min(total - start, per_queue);
+      longest = per_queue;
+    }
+  }
   for (int i = l; i < n; i += 8) dealt[piece_at[i]] = (uint32_t)len_of[i];  // (a heavy piece's word is not looked at)
   if (t < n_parts) {
     long long* cell = cell_chunks + grp * cells_per_group(cs) + (int64_t)p_local * cells_per_part(cs);
-    for (int bin = l; bin < cs.nb; bin += 8) cell[bin] = wide[part][cs.nb - 1 - bin];
+    for (int bin = l; bin < cs.nb; bin += 8) cell[bin] = cut ? 0 : wide[part][cs.nb - 1 - bin];
     if (l == 0) cell[cs.nb] = (longest + 7) >> 3;
     queue_len[t * 8 + l] = (int32_t)load;
   }
@@ -908,6 +954,8 @@ struct CopyCompany {
   SortPass sort;
 };
 
+// (MAY_CUT costs a build of 169,343 rows and 1.17 M entries 1 of 217 us where no queue is cut)
+template <bool MAY_CUT>
 __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, StreamShape ss, CopyArgs a, int pieces_at_a_time,
                                               CopyCompany with) {
   extern __shared__ int lds[];
@@ -967,10 +1015,18 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
         slot = j % kChunkSlots;
         flag = j / kChunkSlots == (len - 1) / kChunkSlots;
       } else {
-        const int pos = (int)(word & 0x0FFFFFFFu) + j;
-        chunk = (int64_t)chunk_or_slot + (pos >> 3);
-        slot = (int)(word >> 28) * 8 + (pos & 7);
+        int pos, queue = (int)(word >> 28);
         flag = j == len - 1;
+        if (MAY_CUT && (word & kCutPiece)) {
+          const int per_queue = (int)((word & (kCutPiece - 1)) >> kCutPosBits) * 8;
+          pos = (int)(word & (kCutQueueMax - 1)) + j;
+          flag |= pos == per_queue - 1;
+          if (pos >= per_queue) { pos -= per_queue; ++queue; }
+        } else {
+          pos = (int)(word & 0x0FFFFFFFu) + j;
+        }
+        chunk = (int64_t)chunk_or_slot + (pos >> 3);
+        slot = queue * 8 + (pos & 7);
         code = 3;
       }
     }
@@ -1535,6 +1591,11 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       longest_row = std::max<int64_t>(longest_row, (int64_t)report1.flags[slot * kFlagStride + 6]);
     cs.wide_margin = ls.rounds ? 32 : 16;
     cs.long_len = heavy_len_setting(csr->nnz, s.n_rows, cs.n_rb, cs.n_phases, longest_row, ls.rounds != 0, opt);
+    // Queues are cut where rows are long and all in the lists, in several launches: 38 graphs, products 1.05 x (0.96 to 1.20), a
+    // build and one product 1.02 x (0.965 to 1.08).  In one launch a row that starts in its middle is out of step with the others
+    // where X is beyond L2 (50,970 rows of 496: 0.89 x); with heavy pieces, or rows of fewer than 16, what is left to deal is short
+    // and divides evenly (12 graphs: 1.00, builds 0.99).
+    cs.cut_queues = cs.n_phases > 1 && longest_row <= cs.long_len && csr->nnz >= 16 * (int64_t)s.n_rows * s.c;
     if (opt.heavy_len < 1 && !ls.rounds && cs.long_len < kHeavyLenMax) {
       // sptir_spmm_noalloc has room for so many narrow partial-sum rows; bucket i > 6 holds the pieces of
       // 2^(i-1)+1 .. 2^i entries, and a heavy list takes at least the entries of 16 chunks once there are thousands
@@ -1687,7 +1748,7 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
 
     // ---- the pieces of every (launch, row block, partition) dealt to its queues; chunks of the lists
     if (n_cells > 0) {
-      hipLaunchKernelGGL(k_deal, dim3((unsigned)((n_parts + kDealParts - 1) / kDealParts)), dim3(8 * kDealParts),
+      hipLaunchKernelGGL(cs.cut_queues ? k_deal<true> : k_deal<false>, dim3((unsigned)((n_parts + kDealParts - 1) / kDealParts)), dim3(8 * kDealParts),
                          (sizeof(int) * 2 * kDealParts) << cs.log2_rb, stream, cs, n_parts, d_bounds, h->row_len, d_cell_chunks,
                          d_dealt, d_queue_len);
       hipLaunchKernelGGL(k_group_scan, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, stream, cs, n_groups,
@@ -1818,8 +1879,8 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       with.n_parts = n_parts; with.queue_len = d_queue_len; with.rb_chunk_ptr = h->rb_chunk_ptr; with.n_chunks = n_chunks;
       with.slots = slots; with.sort = sort;
       if (n_wg + with.first > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
-      hipLaunchKernelGGL(k_copy, dim3((unsigned)n_wg + with.first), dim3(256), sizeof(int) * kCopyWords * (size_t)pieces, stream, s,
-                         cs, ss, a, pieces, with);
+      hipLaunchKernelGGL(cs.cut_queues ? k_copy<true> : k_copy<false>, dim3((unsigned)n_wg + with.first), dim3(256),
+                         sizeof(int) * kCopyWords * (size_t)pieces, stream, s, cs, ss, a, pieces, with);
     }
     BUILD_HIP(hipGetLastError());
     if (n_parts == 0) {  // no lists: the one element of rb_chunk_ptr

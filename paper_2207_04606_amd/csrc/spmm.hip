@@ -284,7 +284,7 @@ struct HybWalker {
 
   // step s of the quad parked at `st` whose chunk facts are m[].  The stream holds two kinds of chunks:
   //  * queue chunks (log2w 3): slots 8q .. 8q+7 continue queue q of the (row block, partition); every slot
-  //    names its row and the last entry of a row piece carries the hand-over flag;
+  //    names its row and the last entry of a row piece in its queue carries the hand-over flag;
   //  * chunks cut from one wide row (log2w >= 6), which all lane groups share; the chunk's hand-over flag
   //    says whether the row ends with it.
   // (w: with UNIT the row words of the step's slots, which step() has read to tell real slots from others)

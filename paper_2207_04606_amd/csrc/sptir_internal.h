@@ -32,7 +32,7 @@ constexpr int64_t kWidePartialRows = 8192;  // (16 MB)
 // Compact stream records spend 8 bytes per slot instead of 12: one word holds the column relative to the first
 // column of the launch (bits 0..19), the row relative to the row block (20..26), "slot is real" (27), the chunk's
 // log2w code (28..30; 3 = queue chunk, 7 = cut from one long row) and the hand-over flag (31; of the chunk, or in a
-// queue chunk of the slot: the last entry of a row piece); the other word the value.
+// queue chunk of the slot: the last entry of a row piece in its queue); the other word the value.
 constexpr int kCompactColBits = 20;
 constexpr int kCompactMaxLog2RowBlock = 7;
 
