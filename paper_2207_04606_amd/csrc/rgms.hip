@@ -701,16 +701,17 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
   }
 }
 
-// Rows per block: 32 entries for every (relation, block), so that tiles fill (16: 4 to 14 % slower, 64: the same), as long
-// as that leaves 160 blocks, about what keeps the matrix cores of 256 CUs busy with 16 wavefronts each.  (60 graphs, 32 x 32: the
-// best block for each is 2.7 % faster in the mean, 20 % at most; any one size for all 16 to 34 % slower.)  Fewer,
+// Rows per block: 32 entries for every (relation, block), so that tiles fill, as long
+// as that leaves 160 blocks, about what keeps 256 CUs busy with 16 wavefronts each.  (64 entries: 42 graphs where that makes
+// 128 rows 256, 0.97 times as fast in the mean, 0.79 to 1.15; what decides there is whether the last turn of workgroups is
+// nearly empty.  26 drawn graphs and feature sizes: the best block for each 1.4 % faster in the mean, 9 % at most.)  Fewer,
 // larger blocks divided into items were tried and lose more in global atomics than fuller tiles gain (27,163 rows,
 // 64 x 64: 0.042 -> 0.093 ms).
 // Blocks of 512 rows take the LDS of a CU and 16 wavefronts; what they win is W[r] read for half as many tiles.  They need two
 // workgroups' worth of them per CU (158,566 rows: 0.81 times as fast as with 256), no workspace, whose tiles take turns (0.79 to
 // 1.08), and fewer than 40 entries for every (relation, block) even so.  78 graphs and feature sizes, against 256 rows: up to 24 entries
 // 1.10 times as fast (0.97 to 1.21), to 40 1.03 (0.94 to 1.10; 32 x 32 features 0.98), to 64 0.98 (0.87 to 1.05).  1.9 M rows, 96
-// relations, 5.7 M entries, 32 x 32, 16 entries: 0.527 -> 0.458 ms.
+// relations, 5.7 M entries, 32 x 32, 16 entries: 399 -> 353 us.
 int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
   int s = kMinLog2Block;
   while (((int64_t)1 << s) * nnz < 32 * n_rows * n_rel && s < kMaxLog2Block - 1 && (n_rows >> (s + 1)) >= 160) ++s;
