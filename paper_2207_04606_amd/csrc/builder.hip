@@ -416,10 +416,13 @@ __device__ __forceinline__ void cell_bounds_workgroup(const CellShape& cs, unsig
 //    156,998 entries in 16 partitions 59 -> 33 us.  Two chunks of margin, as the wide chunk costs one; in rounds, whose
 //    lists are long enough to be even, four.)
 // Where that takes a chunk more than the entries need, the queues may be cut instead (cut_queues): the pieces follow each other
-// through all eight queues, each as long as the entries need, and what does not fit the end of a queue goes on at the start
-// of the next, flagged at both ends.  A dozen or two of long rows do not divide by eight: rows of 37 +- 12 entries in blocks of
-// 32 walk 9 % more slots than there are entries when dealt whole, 3 % when cut (132,534 rows of 37 in each of eight partitions,
-// 128 features: 1031 -> 973 us; cut only where two chunks are saved 1010, where four 1031).
+// through all eight queues, each as long as the entries need, and a piece that does not fit the end of a queue has its first entries
+// at the start of the next, flagged at both ends.  A dozen or two of long rows do not divide by eight: rows of 37 +- 12 entries in
+// blocks of 32 walk 9 % more slots than there are entries when dealt whole, 3 % when cut (132,534 rows of 37 in each of eight
+// partitions, 128 features: 1048 -> 997 us; cut only where two chunks are saved 0.96 times as fast as that, where four 0.94).
+// The first entries and not the last: so all queues begin at the first columns of the partition and sweep X together at first, as they
+// do where rows are dealt whole.  With queues that began in the middle of a row, 34 drawn graphs whose rows of X are no whole lines (100 and 200
+// features, a partition's X beyond L2) took 1.02 times as long (up to 1.06) as with rows dealt whole, now 0.98 (up to 1.01).
 // The rows of one partition are distinct, and a piece that is cut is a chunk shorter than a queue, so that its ends lie in
 // different chunks: two queues never hand over the same row of Y in one instruction.
 __device__ __forceinline__ int cells_per_part(const CellShape& cs) { return cs.nb + 1; }
@@ -430,7 +433,8 @@ inline int64_t chunks_of_slots(int64_t slots) { return (slots + kChunkSlots - 1)
 
 // What becomes of a piece of at most long_len entries, one word per piece (in the order of row_ids):
 //   queued    its first entry's position in the queue (bits 0..27; 0..26 where queues may be cut) and the queue (28..30)
-//   cut       bit 27: the position (bits 0..14), the chunks of the queue (15..26) and the queue; the rest is in the next queue
+//   cut       bit 27: the position (bits 0..14), the chunks of the queue (15..26) and the queue: the last entries, to the end of the
+//             queue; those before are at the start of the next
 //   cut wide  bit 31 and the chunks of the pieces before it in its bin's cell
 constexpr uint32_t kWidePiece = 0x80000000u, kCutPiece = 1u << 27;
 constexpr int kCutPosBits = 15, kCutQueueMax = 1 << kCutPosBits;  // entries of a queue that may be cut: fewer than this
@@ -1020,8 +1024,9 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
         if (MAY_CUT && (word & kCutPiece)) {
           const int per_queue = (int)((word & (kCutPiece - 1)) >> kCutPosBits) * 8;
           pos = (int)(word & (kCutQueueMax - 1)) + j;
-          flag |= pos == per_queue - 1;
-          if (pos >= per_queue) { pos -= per_queue; ++queue; }
+          const int in_next = pos - j + len - per_queue;  // the first so many entries are in the next queue
+          flag |= j == in_next - 1;
+          if (j < in_next) { pos = j; ++queue; } else { pos -= in_next; }
         } else {
           pos = (int)(word & 0x0FFFFFFFu) + j;
         }
@@ -1591,10 +1596,10 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       longest_row = std::max<int64_t>(longest_row, (int64_t)report1.flags[slot * kFlagStride + 6]);
     cs.wide_margin = ls.rounds ? 32 : 16;
     cs.long_len = heavy_len_setting(csr->nnz, s.n_rows, cs.n_rb, cs.n_phases, longest_row, ls.rounds != 0, opt);
-    // Queues are cut where rows are long and all in the lists, in several launches: 38 graphs, products 1.05 x (0.96 to 1.20), a
-    // build and one product 1.02 x (0.965 to 1.08).  In one launch a row that starts in its middle is out of step with the others
-    // where X is beyond L2 (50,970 rows of 496: 0.89 x); with heavy pieces, or rows of fewer than 16, what is left to deal is short
-    // and divides evenly (12 graphs: 1.00, builds 0.99).
+    // Queues are cut where rows are long and all in the lists, in several launches: 85 drawn graphs, products 1.05 x (0.986 to 1.34), 27 more,
+    // a build and one product 1.02 x (0.982 to 1.19).  In one launch, whose lists sweep X beyond L2, it lost (50,970 rows of 496: 0.89 x,
+    // measured with queues that began in the middle of a row); with heavy pieces, or rows of fewer than 16, what is left to deal is short and
+    // divides evenly (12 graphs: 1.00, builds 0.99).
     cs.cut_queues = cs.n_phases > 1 && longest_row <= cs.long_len && csr->nnz >= 16 * (int64_t)s.n_rows * s.c;
     if (opt.heavy_len < 1 && !ls.rounds && cs.long_len < kHeavyLenMax) {
       // sptir_spmm_noalloc has room for so many narrow partial-sum rows; bucket i > 6 holds the pieces of

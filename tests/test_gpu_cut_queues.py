@@ -18,18 +18,26 @@ LENGTHS = {"48 of 56": [48] + [40] * 9, "49 of 56": [49] + [40] * 9, "divides": 
 CUT = ("48 of 56", "spread")
 
 
-def rows_in_two_queues(sptir, hyb, info):
-    """Rows with entries in more than one queue of a list (a partition a launch: a row has one piece in it)."""
+def rows_in_two_queues(sptir, hyb, info, w):
+    """Rows with entries in more than one queue of a list (a partition a launch: a row has one piece in it).  Every queue begins
+    with the first entries of a row, also of one that is cut, so that all queues begin at the partition's first columns."""
     st = Stream(sptir, hyb, info)
     ptr = sptir.sptir_hyb_array(hyb, "plan_rb_chunk_ptr")
+    n_rb = info["n_row_blocks"]
     n = 0
-    for b in range(info["n_row_blocks"] * info["n_phases"]):
-        queues = {}
+    for b in range(n_rb * info["n_phases"]):
+        queues, begun = {}, set()
+        col0 = b // n_rb * info["part_width"]
         for k in range(int(ptr[b]), int(ptr[b + 1])):
-            kind, _, real, _, row, _, _ = st.chunk(k)
+            kind, _, real, col, row, _, _ = st.chunk(k)
             if kind == QUEUE_KIND:
                 for s in np.flatnonzero(real):
                     queues.setdefault(int(row[s]), set()).add(s // 8)
+                    if s // 8 not in begun:
+                        begun.add(s // 8)
+                        r = b % n_rb * info["row_block"] + int(row[s])
+                        cols = w.indices[w.indptr[r]:w.indptr[r + 1]]
+                        assert int(col[s]) + (col0 if st.compact else 0) == cols[cols >= col0][0]
         n += sum(len(q) > 1 for q in queues.values())
     return n
 
@@ -56,7 +64,7 @@ def test_cut_queues(gpu_lib, kind, wide, one_value):
                                       "column_slices": 2, "wide_stream": wide})
     info = gpu_lib.sptir_hyb_info(hyb)
     assert info["n_heavy_pieces"] == 0 and info["n_phases"] == 2 and info["values_per_row"] == int(one_value)
-    assert (rows_in_two_queues(gpu_lib, hyb, info) > 0) == (kind in CUT)
+    assert (rows_in_two_queues(gpu_lib, hyb, info, w) > 0) == (kind in CUT)
     rows, cols, vals = decode(gpu_lib, hyb, info, w)
     key = np.repeat(np.arange(w.n_rows, dtype=np.int64), np.diff(w.indptr)) * w.n_cols + w.indices
     o = np.argsort(rows * w.n_cols + cols, kind="stable")
