@@ -803,25 +803,37 @@ void launch_shared_lists(V, const Geometry& g, int waves, size_t lds_bytes, hipS
 // 300 drawn graphs of up to 1.5 M entries, 190 of them without heavy pieces: 1.19 times as fast in the mean (0.95 to 3.7; the
 // best w for each 1.23; as many wavefronts as fit, whatever the lists, 1.15 with losses to 0.87).  2,708 rows, 10,556 entries,
 // 64 features 8.0 -> 5.9 us; 2,745 rows, 521,654 entries, 64 features 33.9 -> 11.5 us.
-int shared_list_waves(int64_t n_lists, int64_t n_quads, int64_t longest_chunks, int lg, size_t lds_per_wave) {
+struct SharedLists {
+  int waves = 1;
+  int64_t saved = 0;  // what the launch is shorter by, in quads
+};
+constexpr int64_t kCuCount = 256;
+int64_t waves_per_cu(int lg) { return lg >= 16 ? 12 : 16; }
+SharedLists shared_list_waves(int64_t n_lists, int64_t n_quads, int64_t longest_chunks, int lg, size_t lds_per_wave) {
   const int64_t longest = (longest_chunks + kChunksPerQuad - 1) / kChunksPerQuad;
-  const int64_t waves_per_cu = lg >= 16 ? 12 : 16, n_cu = 256;
   auto cost = [&](int64_t w) {
-    const int64_t at_once = n_cu * std::min(waves_per_cu / w, (int64_t)(160 * 1024 / (lds_per_wave * (size_t)w)));
+    const int64_t at_once = kCuCount * std::min(waves_per_cu(lg) / w, (int64_t)(160 * 1024 / (lds_per_wave * (size_t)w)));
     const int64_t mean = (n_quads + n_lists * w - 1) / (n_lists * w);
     return std::max((longest + w - 1) / w + 1, (mean + 1) * ((n_lists + at_once - 1) / at_once));
   };
-  if (n_lists < 1 || longest < 2) return 1;
-  int best = 1;
+  SharedLists best;
+  if (n_lists < 1 || longest < 2) return best;
   const int64_t alone = cost(1);
   int64_t least = alone;
   for (int w = 2; w <= kSharedWaves && w <= longest && lds_per_wave * w <= (size_t)64 * 1024; ++w) {
     const int64_t here = cost(w);
-    if (here < least) { best = w; least = here; }
+    if (here < least) { best = {w, alone - here}; least = here; }
   }
   const bool idle = n_lists <= 1024 || (n_lists <= 4096 && longest * n_lists >= 2 * n_quads);
-  return 5 * least <= 3 * alone || (idle && 4 * least <= 3 * alone) ? best : 1;
+  return 5 * least <= 3 * alone || (idle && 4 * least <= 3 * alone) ? best : SharedLists();
 }
+
+// Lists that are shared are not in a launch with heavy lists: those that a wavefront has to itself are, unless sharing saves more
+// than the heavy lists and a launch of their own take (`heavy_quads` and about two quads).  110 drawn graphs with heavy lists in a
+// single launch: 29 with lists to share, 8 of them apart by the rule, which take 0.61 to 0.94 times as long apart as in one launch; the others
+// 1.05 to 1.44 times.  The 81 with nothing to share are in one launch, apart 1.02 to 1.49 times as long.  101,047 rows, 2.0 M entries, 32 features, 4477 heavy
+// lists beside 1579 whose longest is far beyond the mean: 64 us in one launch, 51 apart.
+bool share_rather_than_join(const SharedLists& shared, int64_t heavy_quads) { return shared.saved >= heavy_quads + 2; }
 
 template <typename V>
 void launch_heavy_and_lists(V, int64_t n_heavy_workgroups, int64_t n_list_workgroups, bool heavy_first, size_t lds_bytes,
@@ -1002,10 +1014,13 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   };
   // The last launch of the chunk lists takes the heavy lists along (those of the first partial_feat features, from feat_begin
   // on; a timed call launches each kind by itself): each fills the CUs that the other leaves idle.  A few heavy lists go first; more
-  // than there are chunk lists, which are launched longest first, or those of rounds, whose lists start together, last.  False:
-  // nothing was launched.  50,021 rows, 1.5 M entries, 41 features 52.1 -> 37.9 us.  Against two launches (one only where the chunk
-  // lists were a single launch, not in rounds, and more than the heavy ones), 110 drawn power-law graphs with heavy lists: single
-  // launch 1.08 times as fast in the mean (0.99 to 1.57), in rounds 1.07 (0.98 to 1.31), several launches 1.01 (0.99 to 1.02).
+  // than there are chunk lists, which are launched longest first, or those of rounds, whose lists start together, last.  Not where
+  // the lists are shared (share_rather_than_join()).  False: nothing was launched.  50,021 rows, 1.5 M entries, 41 features 52.1 -> 37.9 us.
+  // Against two launches (one only where the chunk lists were a single launch, not in rounds, and more than the heavy ones): 110 drawn
+  // power-law graphs with heavy lists, a single launch 1.08 times as fast in the mean (0.99 to 1.57), in rounds 1.07 (0.98 to 1.31).  Where
+  // 3 to 99 % of the entries are heavy: in rounds 1.05 (0.995 to 1.21), several launches 1.02 (0.97 to 1.16; what loses is 120,000
+  // rows whose 7,004 heavy lists are 1.7 times what the GPU holds), full_rows 1.08 (0.98 to 1.32): a heavy list holds the LDS
+  // of a chunk list's tile of Y, and that costs less than the CUs that a launch's end leaves idle.
   auto lists_and_heavy = [&](int feat_begin, int feat_end, bool few_heavy_first) -> bool {
     HeavyArgs ha;
     Geometry gh;
@@ -1105,9 +1120,14 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
       // (where the column partitions take several launches, lists are shared in none of them: 21,104 rows, 2.2 M entries, 32
       //  features, two launches 30 us, 45 with two wavefronts a list)
       const bool may_share = h->n_phases == 1 && idx32 && g.lg <= 16;
-      const int waves = !may_share ? 1 : shared_list_waves((int64_t)h->n_row_blocks * g.n_tiles,
-                                                           h->heavy_chunk0 / kChunksPerQuad * g.n_tiles,
-                                                           h->longest_list, g.lg, lds_bytes / kHybWaves);
+      SharedLists shared;
+      if (may_share)
+        shared = shared_list_waves((int64_t)h->n_row_blocks * g.n_tiles, h->heavy_chunk0 / kChunksPerQuad * g.n_tiles,
+                                   h->longest_list, g.lg, lds_bytes / kHybWaves);
+      const int waves = shared.waves;
+      const int64_t heavy_at_once = kCuCount * waves_per_cu(g.lg);
+      const int64_t heavy_quads = (h->heavy_list_chunks / kChunksPerQuad + 1) *
+                                  (((int64_t)h->n_heavy_lists * g.n_tiles + heavy_at_once - 1) / heavy_at_once);
       Geometry gs = g;
       if (waves > 1 && !plan_tiles(h->n_row_blocks, &gs)) return SPTIR_ERR_OVERFLOW;
       a.n_tiles = g.n_tiles; a.tile0 = tile0; a.map_mode = g.map_mode; a.map_param = g.map_param;  // (of gs as well)
@@ -1118,7 +1138,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         a.X = wide ? X : X + (size_t)phase * (size_t)span * (size_t)feat;
         const bool last = phase + 1 == h->n_phases && tile0 + g.n_tiles == all_tiles;
         ++n_list_launches;
-        if (last && lists_and_heavy(0, feat, true)) continue;
+        if (last && !share_rather_than_join(shared, heavy_quads) && lists_and_heavy(0, feat, true)) continue;
         if (waves > 1) {
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) {
             launch_shared_lists(v, gs, waves, lds_bytes / kHybWaves * waves, stream, a);

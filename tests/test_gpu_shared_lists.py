@@ -53,3 +53,33 @@ def test_shared_lists(gpu_lib, feat, one_value, wide):
             gpu_lib.sptir_spmm_noalloc(hyb, d.X, again)
             assert torch.equal(Y, again)
             hyb.destroy()
+
+
+@pytest.mark.parametrize("feat", [1, 4, 17, 41, 64])
+@pytest.mark.parametrize("long_list", [False, True])
+def test_lists_to_share_beside_heavy_ones(gpu_lib, feat, long_list):
+    """A list of 8 quads among lists of one is shared, and heavy lists then have a launch of their own; lists that are all short are in
+    the heavy lists' launch, each for one wavefront.  More heavy lists than chunk lists, and fewer."""
+    for n_rows, n_heavy in ((700, 3), (100, 60)):
+        say(f"[shared beside heavy] feat={feat} long_list={long_list} {n_rows} rows, {n_heavy} heavy")
+        rng = np.random.default_rng(n_rows + feat)
+        deg = rng.integers(1, 9, n_rows)
+        deg[:n_heavy] = rng.integers(2049, 2400, n_heavy)
+        if long_list:
+            deg[n_rows // 2 + 20] = 2047
+        w = workloads.random_csr(n_rows, 6000, deg, feat, feat)
+        d = upload(w)
+        Yr, Sr = oracle.spmm_csr(w.n_rows, w.indptr, w.indices, w.values, w.X)
+        hyb = gpu_lib.sptir_hyb_build_ex(n_rows, 6000, d.indptr, d.indices, d.values, 1, 11, {"heavy_len": 2048, "rounds": 2,
+                                                                                           "column_slices": 2})
+        assert gpu_lib.sptir_hyb_info(hyb)["n_heavy_pieces"] == n_heavy
+        Y = torch.full((n_rows, feat), float("nan"), device="cuda")
+        gpu_lib.sptir_spmm(hyb, d.X, Y)
+        assert_y_close(Y.cpu().numpy(), Yr, Sr, what=f"{n_rows} rows, {n_heavy} heavy")
+        timed = torch.full_like(Y, float("nan"))
+        assert (gpu_lib.sptir_spmm_timed(hyb, d.X, timed)["list_waves"] > 1) == long_list
+        assert torch.equal(Y, timed)
+        again = torch.full_like(Y, float("nan"))
+        gpu_lib.sptir_spmm_noalloc(hyb, d.X, again)
+        assert torch.equal(Y, again)
+        hyb.destroy()
