@@ -488,8 +488,8 @@ sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n_relations,
  * instructions; the sums over relations are float64 on chip).  Without the workspace the contributions of different
  * relations meet in no fixed order, so results agree between runs to rounding, not bit for bit.  Calls that share a
  * handle's workspace must not overlap in time.
- * A row of X with a NaN or an infinity makes the rows of Y that have an entry naming it non-finite and no others; sums
- * that are not finite are formed a second time, a wavefront per row (a call in which all are takes about 20 times as long).
+ * A row of X with a NaN or an infinity makes the rows of Y that have an entry naming it non-finite and no others, and a call
+ * takes as long with them as without.
  */
 sptir_status_t sptir_rgms(const sptir_rgms_t* rgms, const float* X, const float* W, float* Y, int32_t d_in,
                           int32_t d_out, void* stream);

@@ -51,7 +51,7 @@ namespace {
 
 constexpr int kTileRows = 16;      // pieces per tile
 constexpr int kPieceEntries = 4;   // most entries per piece: a tile has 16 steps at most, 64 entries, a lane each
-constexpr uint32_t kPad = 0x80000000u;  // in the column of a place without an entry: a column of its step, to be multiplied by 0
+constexpr int kPad = -1;           // the column of a place without an entry: past the end of X, where a buffer load gives 0
 constexpr int kMinLog2Block = 5, kMaxLog2Block = 9;
 constexpr int kYTileBytes = 64 * 1024;  // LDS for the rows of Y: two workgroups per CU; blocks of 2^kMaxLog2Block rows: twice that, one
 
@@ -112,6 +112,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint3
 __device__ __forceinline__ int from_lane(int byte, int v) { return __builtin_amdgcn_ds_bpermute(byte, v); }
 
 constexpr int kPass = 32;       // columns of Y per pass
+
+__device__ float zero_row[128];  // what a place without an entry names where X has 4 GB or more (never written)
 
 // TIN: d_in / 32.  In a 4x4x1 product of 16 blocks lane 4 b + i holds row i of block b's A, or column i of its B, and column i
 // of all four rows of its result; A can be one block's for eight blocks together (cbsz 3).  So lanes 0 .. 31 form a product of
@@ -182,14 +184,15 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
   auto moved = [](int v) { asm volatile("" : "+v"(v)); return v; };
   const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.X, a.x_bytes);
   const unsigned x_lane = (unsigned)(lane & 15) * (4 * VW);
-  auto x_place = [&](int col) { return WIDE_X ? col : (int)((unsigned)col << kLog2RowBytes); };  // (the shift drops kPad)
+  // (kPad: past the last row that an X below 4 GB can have)
+  auto x_place = [&](int col) { return WIDE_X ? col : (int)((unsigned)col << kLog2RowBytes); };
   auto load_x = [&](int place, float (&x)[kZ]) {
     typedef float vec __attribute__((ext_vector_type(VW)));
 #pragma unroll
     for (int g = 0; g < kGroups; ++g) {
       vec v;
       if constexpr (WIDE_X)
-        v = *reinterpret_cast<const vec*>(a.X + (size_t)(place & ~kPad) * kDin + (lane & 15) * VW + 16 * VW * g);
+        v = *reinterpret_cast<const vec*>((place == kPad ? zero_row : a.X + (size_t)place * kDin) + (lane & 15) * VW + 16 * VW * g);
       else if constexpr (VW == 2)
         v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(x_buf, (int)((unsigned)place + x_lane), 0, 0));
       else
@@ -403,80 +406,17 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
   {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    const int lane = tid & 63;
-    // A place without an entry multiplies a row of X that its step has anyway by 0: a NaN or an infinity in it has reached the
-    // place's piece.  Sums that are not finite are therefore formed again before they are written, from their own row's entries
-    // only; the wavefront takes a row of the block at a time.  y[0 .. 3] of a lane: columns n0 + c .. + 3 of row `row`.
-    auto sum_again = [&](int row, int c, bool not_finite, float (&y)[4]) {
-      unsigned long long todo = __ballot(not_finite);
-      while (todo) {
-        const int r = __builtin_amdgcn_readlane(row, __builtin_ctzll(todo));
-        const bool here = not_finite && row == r;
-        todo &= ~__ballot(here);
-        double sum[4] = {0., 0., 0., 0.};
-        for (int t0 = 0; t0 < item.n_tiles; t0 += 64) {
-          bool has = false;  // a piece of row r in tile t0 + lane
-          if (t0 + lane < item.n_tiles) {
-            const uint16_t* of = a.tiles[item.tile0 + t0 + lane].rows;
-#pragma unroll
-            for (int i = 0; i < kTileRows; ++i) has |= of[i] == r;
-          }
-          for (unsigned long long tiles = __ballot(has); tiles; tiles &= tiles - 1) {
-            const RgmsTile& tile = a.tiles[item.tile0 + t0 + __builtin_ctzll(tiles)];
-            const int n = 4 * tile.n_steps;
-            const unsigned slots = (unsigned)__ballot(tile.rows[lane & 15] == r) & 0xFFFFu;
-            constexpr int kPerLane = (kDin + 63) / 64;
-            float sums[kPerLane];  // features lane, lane + 64
-#pragma unroll
-            for (int i = 0; i < kPerLane; ++i) sums[i] = 0.f;
-            const int2 e = a.entries[(size_t)tile.first * 4 + min(lane, n - 1)];
-            int quad = lane >> 2;  // of this lane's entry
-            for (int left = tile.shape & 0xFFF; left != 0 && quad >= (left & 7); left >>= 3) quad -= left & 7;
-            const bool take = lane < n && e.x >= 0 && (slots >> ((4 * quad + (lane & 3)) & 15) & 1u) != 0;
-            for (unsigned long long left = __ballot(take); left; left &= left - 1) {
-              const int from = __builtin_ctzll(left);
-              const float* x_row = a.X + (size_t)__builtin_amdgcn_readlane(e.x, from) * kDin;
-              const float v = __int_as_float(__builtin_amdgcn_readlane(e.y, from));
-#pragma unroll
-              for (int i = 0; i < kPerLane; ++i) sums[i] = fmaf(v, x_row[(64 * i + lane) % kDin], sums[i]);
-            }
-            const float* w = a.W + (size_t)tile.rel * kDin * (size_t)a.d_out + n0 + c;
-            float d[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < kPerLane; ++i)
-#pragma unroll 4
-              for (int k = 0; k < (kDin < 64 ? kDin : 64); ++k) {
-                const float s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sums[i]), k));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) d[j] = fmaf(s, w[(size_t)(64 * i + k) * a.d_out + j], d[j]);
-              }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) sum[j] += d[j];
-          }
-        }
-        if (here) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) y[j] = (float)sum[j];
-        }
-      }
-    };
-
     // ---- the block's rows
     const int row0 = item.block << a.log2_block;
     const int rows_here = min(rows, a.n_rows - row0);
     const int quads = cols / 4;
     const int n_quads = rows_here * quads;
     const int shift = (quads & (quads - 1)) == 0 ? 31 - __builtin_clz((unsigned)quads) : -1;
-    // (whole wavefronts: sum_again needs all lanes)
-    for (int i0 = __builtin_amdgcn_readfirstlane(tid); i0 < n_quads; i0 += (int)blockDim.x) {
-      const int i = min(i0 + lane, n_quads - 1);
+    for (int i = tid; i < n_quads; i += (int)blockDim.x) {
       const int row = shift >= 0 ? i >> shift : i / quads, c = (i - row * quads) * 4;
       float y[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) y[k] = (float)y_tile[row * width + c + k];
-      const bool not_finite = fmaf(y[0], 0.f, fmaf(y[1], 0.f, fmaf(y[2], 0.f, y[3] * 0.f))) != 0.f;
-      if (__any(not_finite)) sum_again(row, c, not_finite, y);
-      if (i0 + lane >= n_quads) continue;
       if (item.part < 0) {
         store_unaligned<4>(a.Y + (size_t)(row0 + row) * a.d_out + n0 + c, y);
       } else if constexpr (ORDERED) {
@@ -665,11 +605,10 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
 #pragma unroll
     for (int e = 0; e < kPieceEntries; ++e) {
       if (e >= steps) break;
-      const int at = from + min(e, len - 1);
-      const int col = indices[at];
+      const int at = from + e;
       int2* to = entries + step * 4 + (place & 3);
-      *to = e < len ? make_int2(col, __float_as_int(values[at])) : make_int2((int)((uint32_t)col | kPad), 0);
-      for (int i = (place & 3) + 1; i < i_end; ++i) *++to = make_int2((int)((uint32_t)col | kPad), 0);
+      *to = e < len ? make_int2(indices[at], __float_as_int(values[at])) : make_int2(kPad, 0);
+      for (int i = (place & 3) + 1; i < i_end; ++i) *++to = make_int2(kPad, 0);
       step += quads_with(quad0, e);
     }
   };

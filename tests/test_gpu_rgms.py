@@ -272,7 +272,8 @@ def test_rgms_rows_of_a_block(gpu_lib, mean, rows):
 @pytest.mark.parametrize("d_in,d_out", [(32, 32), (32, 96), (64, 64), (128, 32)])
 def test_rgms_quads_and_steps(gpu_lib, d_in, d_out, workspace):
     """Cells of 0 to 37 pairs of 0 to 5 entries each: pieces of up to four entries, quads and tiles of every length, places without
-    an entry, with NaN in a row of X that a few pairs name and others share a step with."""
+    an entry, with NaN in a row of X that a few pairs name and others share a step with, and with infinities where no sum has both signs: places
+    without an entry multiply zeros, not a row of X, so an infinity stays one."""
     rng = np.random.default_rng(d_in + d_out)
     n, n_rel, block = 38 * 32, 3, 32                       # (32 rows per block: so many entries are in a cell)
     counts = np.zeros((n_rel, n), dtype=np.int64)
@@ -298,3 +299,39 @@ def test_rgms_quads_and_steps(gpu_lib, d_in, d_out, workspace):
         assert finite.all() != bad and finite.any()
         assert np.array_equal(np.isfinite(Y), finite)
         assert_y_close(np.where(finite, Y, 0), np.where(finite, Yr, 0), np.where(finite, Sr, 0), f"d_in={d_in} d_out={d_out}")
+    X = np.abs(np.nan_to_num(X)) + np.float32(0.1)
+    X[np.unique(w0.indices)[::29], d_in // 2] = np.inf
+    w = workloads.HeteroWorkload("infinities", n, n_rel, w0.indptr, w0.indices, w0.values, X, np.abs(W) + np.float32(0.1))
+    Y, _ = run_rgms(gpu_lib, w, workspace_d_out=workspace)
+    Yr, _ = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, w.X, w.W)
+    assert (Yr == np.inf).any() and not np.isnan(Yr).any()
+    assert np.array_equal(Y == np.inf, Yr == np.inf) and not np.isnan(Y).any()
+
+
+def test_rgms_non_finite_rows_cost_nothing(gpu_lib):
+    """A call on an X that is all NaN does what one on numbers does.  (1.0 times as long; sums formed a second time took 20 to 30.)"""
+    rng = np.random.default_rng(5)
+    n, n_rel = 40_000, 16
+    w = workloads.random_csr(n_rel * n, n, rng.integers(0, 5, n_rel * n), 3, 1)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    h = gpu_lib.sptir_rgms_build(n_rel, n, n, dev(w.indptr), dev(w.indices), dev(w.values))
+    W = torch.ones(n_rel, 32, 32, device="cuda")
+    Y = torch.empty(n, 32, device="cuda")
+
+    def least_ms(X):
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            gpu_lib.sptir_rgms(h, X, W, Y)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    finite = least_ms(torch.ones(n, 32, device="cuda"))
+    nan = least_ms(torch.full((n, 32), float("nan"), device="cuda"))
+    has_entries = np.diff(w.indptr).reshape(n_rel, n).sum(0) > 0
+    assert np.array_equal(torch.isnan(Y).all(1).cpu().numpy(), has_entries)
+    assert nan < 4 * finite, f"{nan:.3f} ms against {finite:.3f}"
+    h.destroy()
