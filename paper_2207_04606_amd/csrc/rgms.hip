@@ -120,9 +120,10 @@ __device__ float zero_row[128];  // what a place without an entry names where X 
 // four rows, one feature and 32 columns, lanes 32 .. 63 another one, with the feature that lies kHalf further on, and the two meet at
 // the end.  W[r] is loaded in whole rows of 32 columns.  The gather leaves piece i's row in lanes 16 i .. + 15 (a load of 16 lanes
 // that name four rows takes four times the lines: 246 against 206 us); lane 16 i + b's features go to lane 4 b + i, once a quad.
-// WIDE_X: X has 4 GB or more.
+// WIDE_X: X has 4 GB or more.  (32 features: six wavefronts per SIMD, 80 registers, for which ORDERED spills two; with five, 3.2 M entries, 20
+// relations, 20,000 rows, 32 x 32 took 92 us, with six 65.)
 template <int TIN, bool ORDERED, bool WIDE_X>
-__global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(TIN == 1 ? 6 : 4))) void k_rgms(RgmsArgs a) {
   constexpr int VW = TIN == 1 ? 2 : 4;              // floats per lane and load of a row of X
   constexpr int kGroups = 2 * TIN / VW;             // loads per row
   constexpr int kZ = 2 * TIN;                       // registers per row
@@ -323,13 +324,12 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
     tile = moved(tile_1); tile_1 = moved(tile_2);
     tile_2 = load_tile(t + 3 * stride);
     if constexpr (kChunks == 1) load_next(shape_1);
-    // ---- multiply: quads Q0 .. Q0 + NQ - 1 and the pass at c0
-    auto products = [&](auto q0, auto nq, auto is_last, int c0) {
-      constexpr int Q0 = decltype(q0)::value, NQ = decltype(nq)::value, kPairs = (NQ + 1) / 2;
+    // ---- multiply: quads Q0 .. Q0 + NQ - 1 and the pass at c0, to d
+    auto products = [&](auto q0, auto nq, auto is_last, int c0, floatx4* d) {
+      constexpr int Q0 = decltype(q0)::value, NQ = decltype(nq)::value;
       constexpr bool kLast = decltype(is_last)::value;
-      floatx4 d[2 * kPairs];
 #pragma unroll
-      for (int q = 0; q < 2 * kPairs; ++q) d[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < (NQ + 1) / 2 * 2; ++q) d[q] = floatx4{0.f, 0.f, 0.f, 0.f};
       for_steps<kChunks>([&](auto chunk) {
         constexpr int C = decltype(chunk)::value;
         // (as late as leaves two chunks of W to load behind them, since those are waited for in order)
@@ -347,38 +347,78 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
           else load_w(kLast ? rel_next : rel, kLast ? 0 : c0 + kPass, C & 1, w[C & 1]);
         }
       });
-      // ---- add: after the halves have met, d[2 p][i] belongs to piece 4 Q0 + 8 p + 4 (lane >> 5) + i
-      if constexpr (ORDERED && Q0 == 0) {
+    };
+    // ---- two quads' sums: the halves meet, and row i of d is then that of piece 4 (lane >> 5) + i of them
+    auto meet = [&](const floatx4* d, int i) {
+      const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[0][i]), __float_as_uint(d[1][i]), false, false);
+      return __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+    };
+    auto add = [&](auto&& sum, int rows_01, int rows_23, int c0) {  // sum(i)
+      for_steps<4>([&](auto row) {
+        constexpr int i = decltype(row)::value;
+        const float s = sum(i);
+        const unsigned at = place_of_row(i < 2 ? rows_01 : rows_23, row, y_lane + 8 * c0);
+        atomicAdd(reinterpret_cast<double*>(reinterpret_cast<char*>(y_tile) + at), (double)s);
+      });
+    };
+    auto wait_for_turn = [&](int c0) {
+      if constexpr (ORDERED) {
         // tile t adds after tile t - 1, which an earlier turn of this loop or another wavefront of this workgroup
         // is on its way to: the wait ends
         while (__hip_atomic_load(turn + c0 / kPass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != t)
           __builtin_amdgcn_s_sleep(1);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
       }
-#pragma unroll
-      for (int p = 0; p < kPairs; ++p)
-        for_steps<4>([&](auto row) {
-          constexpr int i = decltype(row)::value;
-          const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[2 * p][i]), __float_as_uint(d[2 * p + 1][i]), false, false);
-          const float sum = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
-          const unsigned at = place_of_row(piece_rows[Q0 + 2 * p + i / 2], row, y_lane + 8 * c0);
-          atomicAdd(reinterpret_cast<double*>(reinterpret_cast<char*>(y_tile) + at), (double)sum);
-        });
     };
     auto pass = [&](auto is_last, int c0) {
       using C0 = integral_constant<int, 0>;
+      using C1 = integral_constant<int, 1>;
       using C2 = integral_constant<int, 2>;
       if constexpr (kChunks == 1) {
-        // (all of W is there: two quads at a time take fewer registers)
-        if (n_quads > 1) products(C0{}, C2{}, is_last, c0);
-        else products(C0{}, integral_constant<int, 1>{}, is_last, c0);
-        if (n_quads > 3) products(C2{}, C2{}, is_last, c0);
-        else if (n_quads > 2) products(C2{}, integral_constant<int, 1>{}, is_last, c0);
+        // (All of W is there: two quads at a time take fewer registers.  ORDERED: both are formed before the wait for the turn, with four
+        // floats each until then.  Before, the others waited for the second product as well: 27,163 rows, 46 relations, 145 K entries, 32 x 32
+        // features 28.1 -> 22.9 us, with the load of W below.)
+        floatx4 d[2];
+        float first[4], last[4];
+        auto keep = [&](float (&sum)[4]) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sum[i] = meet(d, i);
+        };
+        if (n_quads > 2) {
+          products(C0{}, C2{}, is_last, c0, d);
+          keep(first);
+          if constexpr (!ORDERED) add([&](int i) { return first[i]; }, piece_rows[0], piece_rows[1], c0);
+          if (n_quads > 3) products(C2{}, C2{}, is_last, c0, d);
+          else products(C2{}, C1{}, is_last, c0, d);
+        } else if (n_quads > 1) {
+          products(C0{}, C2{}, is_last, c0, d);
+        } else {
+          products(C0{}, C1{}, is_last, c0, d);
+        }
+        keep(last);
+        // (W[r] that is multiplied next, on its way while the sums are added; asked for after them, every pass waited for it.  Held twice
+        // and asked for before the products it takes 16 registers, a wavefront per SIMD: graphs of full tiles 3 to 10 % slower.)
+        if constexpr (!decltype(is_last)::value) load_w(rel, c0 + kPass, 0, w[0]);
+        else if (rel_next != rel || cols > kPass) load_w(rel_next, 0, 0, w[0]);
+        wait_for_turn(c0);
+        if (n_quads > 2) {
+          if constexpr (ORDERED) add([&](int i) { return first[i]; }, piece_rows[0], piece_rows[1], c0);
+          add([&](int i) { return last[i]; }, piece_rows[2], piece_rows[3], c0);
+        } else {
+          add([&](int i) { return last[i]; }, piece_rows[0], piece_rows[1], c0);
+        }
       } else {
-        if (n_quads == 4) products(C0{}, integral_constant<int, 4>{}, is_last, c0);
-        else if (n_quads == 3) products(C0{}, integral_constant<int, 3>{}, is_last, c0);
-        else if (n_quads == 2) products(C0{}, C2{}, is_last, c0);
-        else products(C0{}, integral_constant<int, 1>{}, is_last, c0);
+        auto quads = [&](auto nq) {
+          floatx4 d[(decltype(nq)::value + 1) / 2 * 2];
+          products(C0{}, nq, is_last, c0, d);
+          wait_for_turn(c0);
+          add([&](int i) { return meet(d, i); }, piece_rows[0], piece_rows[1], c0);
+          if constexpr (decltype(nq)::value > 2) add([&](int i) { return meet(d + 2, i); }, piece_rows[2], piece_rows[3], c0);
+        };
+        if (n_quads == 4) quads(integral_constant<int, 4>{});
+        else if (n_quads == 3) quads(integral_constant<int, 3>{});
+        else if (n_quads == 2) quads(C2{});
+        else quads(C1{});
       }
       if constexpr (ORDERED) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  // (LDS only: the prefetches stay in flight)
@@ -390,15 +430,9 @@ __global__ __launch_bounds__(1024) void k_rgms(RgmsArgs a) {
 #pragma unroll 1
     for (; c0 + kPass < cols; c0 += kPass) {
       pass(std::false_type{}, c0);
-      if constexpr (kChunks == 1) {
-        load_w(rel, c0 + kPass, 0, w[0]);
-#pragma unroll
-        for (int i = 0; i < kChunk; ++i) asm volatile("" : "+v"(w[0][i]));  // (waited for here: see above)
-      }
+      if constexpr (kChunks == 1) wait_for_loads();
     }
     pass(std::true_type{}, c0);
-    if constexpr (kChunks == 1)
-      if (rel_next != rel || cols > kPass) load_w(rel_next, 0, 0, w[0]);
   }
   __syncthreads();
 
