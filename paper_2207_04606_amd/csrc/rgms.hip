@@ -13,7 +13,10 @@
 //
 // A *piece* is up to 4 entries of one (relation, row) pair, a *quad* four pieces of one relation in one block, a *tile*
 // up to four quads.  The pieces of a (relation, block) are sorted by length, so that the pieces of a quad are alike, and
-// the entries are stored in *steps* of four, one for each piece of a quad.  A wavefront takes a tile:
+// the entries are stored in *steps* of four, one for each piece of a quad.  Pieces of one pair lie in the same place of two or four quads of a
+// tile, as far as they fill tiles, and meet before the product: a pair of many entries is multiplied by W[r] once for sixteen or eight of
+// them.  (Once for four: 20,000 rows, 20 relations, 3.2 M entries, 32 x 256 features 265 -> 203 us, 64 x 128 249 -> 196, 32 x 32 52 -> 46; with
+// pieces of eight entries, for which W[r] is read half as often, the kernel of 16-row products below took 192, 212 and 77.)  A wavefront takes a tile:
 //   gather    Z[i] = sum of value x row of X over the entries of piece i: 16 lanes for each of a step's four entries, whole rows
 //             of X and plain multiply-adds;
 //   multiply  Z W[r], v_mfma_f32_4x4x1_f32 with 16 blocks: float32 throughout, four rows at a time; W[r] from L1 / L2, for 32
@@ -65,7 +68,9 @@ struct RgmsItem {
 struct RgmsTile {
   int32_t first;       // its first step: entries 4 first ..
   int32_t rel;
-  uint32_t shape;      // bits 3e .. + 2: quads that have more than e steps (the longest are first); bits 12 + 4e .. + 3: steps for entries before e
+  // bits 3e .. + 2: quads that have more than e steps (the longest are first); bits 12 + 4e .. + 3: steps for entries before e; bits 28, 29: quads
+  // that hold pieces of the same rows, place for place, are 1 << so many (their sums meet before the product, and `rows` has them once)
+  uint32_t shape;
   int32_t n_steps;
   uint16_t rows[kTileRows];  // of its pieces, in the block; 1 << log2_block: none
 };
@@ -277,7 +282,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(TIN == 1 ?
     // (All that the last turn has loaded is waited for here, and what only some turns load is waited for where they do: past
     // that the compiler cannot count what is in flight, and would wait for the loads that are to stay there.)
     if constexpr (kChunks == 1) wait_for_loads();
-    const int shape = shape_of(tile), n_quads = shape & 7, n_1 = shape >> 3 & 7, n_2 = shape >> 6 & 7, n_3 = shape >> 9 & 7;
+    const int shape = shape_of(tile), n_1 = shape >> 3 & 7, n_2 = shape >> 6 & 7, n_3 = shape >> 9 & 7;
+    int n_quads = shape & 7;
     const int rel = rel_of(tile), rel_next = rel_of(tile_1), shape_1 = shape_of(tile_1);
     const int first_2 = first_of(tile_2), shape_2 = shape_of(tile_2), steps_2 = steps_of(tile_2);
     int piece_rows[4];  // two each: of pieces 8 p + 4 (lane >> 5) ..
@@ -309,6 +315,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(TIN == 1 ?
           sum_rows(integral_constant<int, 3>{}, x, e, n_3, z);
         }
       }
+    }
+    if (const int joined = (unsigned)shape >> 28; joined != 0) {  // (four quads)
+      const bool all = joined == 2;
+#pragma unroll
+      for (int k = 0; k < kZ; ++k) {
+        z[0][k] += z[1][k];
+        z[1][k] = z[2][k] + z[3][k];
+      }
+      if (all)
+#pragma unroll
+        for (int k = 0; k < kZ; ++k) z[0][k] += z[1][k];
+      n_quads = all ? 1 : 2;
     }
     for_steps<4>([&](auto q) {  // to the places of the product
       constexpr int Q = decltype(q)::value;
@@ -596,7 +614,10 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
   __shared__ uint16_t filled[4][1 << kMaxLog2Block];
   uint16_t* rows_of = filled[threadIdx.x >> 6];
   int n_filled = 0, row = 0;
+  int fours = 0, twos = 0;  // see below
   const CellShape c = cell_shape(ptr, rows, lane, [&](int n) {
+    fours += n / (4 * kPieceEntries);
+    twos += __popcll(__ballot((n / kPieceEntries & 2) != 0));
     const unsigned long long some = __ballot(n > 0);
     if (n > 0) rows_of[n_filled + __popcll(some & (((unsigned long long)1 << lane) - 1))] = (uint16_t)(row + lane);
     n_filled += __popcll(some);
@@ -608,6 +629,17 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
   int n_pieces = 0;
 #pragma unroll
   for (int len = 1; len <= kPieceEntries; ++len) n_pieces += c.count[len];
+
+  // The full pieces of a row are taken by fours, what is left by twos, what is left of that singly.  Fours fill tiles, a piece in the same place of
+  // each of the tile's quads; then twos, in the same place of quads 0 and 1 or 2 and 3.  Fours that fill no tile are twos, and twos that fill
+  // none are single pieces: there are as many tiles and steps as without, and a row's entries are multiplied by W[r] sixteen or eight at a
+  // time.
+  for (int d = 32; d > 0; d >>= 1) fours += __shfl_xor(fours, d, 64);
+  const int tiles_of_fours = fours / 4;
+  const int twos_of_fours = fours % 4 * 2;  // (the first twos)
+  twos += twos_of_fours;
+  const int tiles_of_twos = twos / 8, joined_tiles = tiles_of_fours + tiles_of_twos;
+  const int singles_of_twos = twos % 8 * 2;
 
   // what a tile is, and the rows of pieces that are none
   auto quads_with = [&](int quad0, int e) { return min(max(c.at_least[e + 1] - quad0, 0), 4); };
@@ -623,16 +655,18 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
     }
     to->first = step0 + c.steps_before(4 * t);
     to->rel = (int)rel;
-    to->shape = shape;
+    const int joined = t < tiles_of_fours ? 2 : t < joined_tiles ? 1 : 0;
+    to->shape = shape | (uint32_t)joined << 28;
     to->n_steps = steps;
+    const int n_rows_of = min(kTileRows >> joined, n_pieces - kTileRows * t);
     for (int i = 0; i < kTileRows; ++i)
-      if (kTileRows * t + i >= n_pieces) to->rows[i] = (uint16_t)(1 << a.log2_block);
+      if (i >= n_rows_of) to->rows[i] = (uint16_t)(1 << a.log2_block);
   }
 
-  // piece number `place`: `len` entries from `from` on, of row `row`
-  auto put = [&](int place, int row, int from, int len) {
+  // piece number `place`: `len` entries from `from` on, of row `row`, which is number `slot` of its tile's rows (negative: another piece says so)
+  auto put = [&](int place, int slot, int row, int from, int len) {
     const int quad = place >> 2, quad0 = quad & ~3;
-    tiles[tile0 + (place >> 4)].rows[place & 15] = (uint16_t)row;
+    if (slot >= 0) tiles[tile0 + (place >> 4)].rows[slot] = (uint16_t)row;
     const int steps = c.steps_of(quad);
     const int i_end = place == n_pieces - 1 ? 4 : (place & 3) + 1;  // (the last piece fills its quad)
     int64_t step = step0 + c.steps_before(quad0) + (quad & 3);
@@ -646,10 +680,39 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
       step += quads_with(quad0, e);
     }
   };
-  int place_of[kPieceEntries + 1];  // of the next piece of every length
+  // full piece k of a row with `full` of them, before which there are so many fours, twos and single pieces
+  auto put_full = [&](int k, int full, int before_4, int before_2, int before_1, int row, int from) {
+    const int in_fours = full & ~3, in_twos = full & ~1;
+    int place, slot;
+    int two = -1, part = k & 1;  // the two that the piece belongs to, and which half of it
+    if (k < in_fours) {
+      const int four = before_4 + (k >> 2);
+      if (four < 4 * tiles_of_fours) {
+        place = (four & ~3) * 4 + (k & 3) * 4 + (four & 3);
+        slot = (k & 3) == 0 ? four & 3 : -1;
+      } else {
+        two = (four - 4 * tiles_of_fours) * 2 + (k >> 1 & 1);
+      }
+    } else if (k < in_twos) {
+      two = twos_of_fours + before_2;
+    } else {
+      place = joined_tiles * kTileRows + singles_of_twos + before_1;
+      slot = place & 15;
+    }
+    if (two >= 8 * tiles_of_twos) {
+      place = joined_tiles * kTileRows + (two - 8 * tiles_of_twos) * 2 + part;
+      slot = place & 15;
+    } else if (two >= 0) {
+      place = (tiles_of_fours + (two >> 3)) * kTileRows + (two & 4) * 2 + part * 4 + (two & 3);
+      slot = part == 0 ? two & 7 : -1;
+    }
+    put(place, slot, row, from + k * kPieceEntries, kPieceEntries);
+  };
+  int place_of[kPieceEntries];  // of the next piece of every smaller length
 #pragma unroll
-  for (int len = kPieceEntries; len >= 1; --len)
-    place_of[len] = len == kPieceEntries ? 0 : place_of[len == kPieceEntries ? len : len + 1] + c.count[len == kPieceEntries ? len : len + 1];
+  for (int len = kPieceEntries - 1; len >= 1; --len)
+    place_of[len] = len == kPieceEntries - 1 ? c.count[kPieceEntries] : place_of[len + 1] + c.count[len + 1];
+  int done_4 = 0, done_2 = 0, done_1 = 0;
   for (int i0 = 0; i0 < n_filled; i0 += 64) {
     int i = 0, from = 0, n = 0;
     if (i0 + lane < n_filled) { i = rows_of[i0 + lane]; from = ptr[i]; n = ptr[i + 1] - from; }
@@ -661,16 +724,29 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
       if (rest == len) place = place_of[len] + __popcll(same & (((unsigned long long)1 << lane) - 1));
       place_of[len] += __popcll(same);
     }
-    if (rest > 0) put(place, i, from + n - rest, rest);
-    const int incl = wave_inclusive_scan(full, lane);
-    const int place0 = place_of[kPieceEntries] + incl - full;
-    if (full == 1) put(place0, i, from, kPieceEntries);
-    for (unsigned long long longer = __ballot(full > 1); longer; longer &= longer - 1) {
-      const int src = __builtin_ctzll(longer);
-      const int f = __shfl(from, src, 64), m = __shfl(full, src, 64), p0 = __shfl(place0, src, 64), r = __shfl(i, src, 64);
-      for (int k = lane; k < m; k += 64) put(p0 + k, r, f + k * kPieceEntries, kPieceEntries);
+    if (rest > 0) put(place, place & 15, i, from + n - rest, rest);
+    if (c.count[kPieceEntries] == 0) continue;
+    // full pieces, a lane each
+    const unsigned long long before = ((unsigned long long)1 << lane) - 1;
+    const unsigned long long with_two = __ballot((full & 2) != 0), with_one = __ballot((full & 1) != 0);
+    const int upto = wave_inclusive_scan(full, lane), upto_4 = wave_inclusive_scan(full >> 2, lane);
+    const int before_4 = done_4 + upto_4 - (full >> 2);
+    const int before_2 = done_2 + __popcll(with_two & before), before_1 = done_1 + __popcll(with_one & before);
+    const int packed = i | before_2 << 10 | before_1 << 20;  // (at most 512 rows)
+    const int total = __shfl(upto, 63, 64);
+    for (int k0 = 0; k0 < total; k0 += 64) {
+      int src = 0;  // the row whose piece it is: the first with more pieces up to it
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1)
+        if (__shfl(upto, src + step - 1, 64) <= k0 + lane) src += step;
+      const int m = __shfl(full, src, 64), f = __shfl(from, src, 64), b4 = __shfl(before_4, src, 64);
+      const int first = __shfl(upto - full, src, 64), rest_of = __shfl(packed, src, 64);
+      if (k0 + lane < total)
+        put_full(k0 + lane - first, m, b4, rest_of >> 10 & 1023, rest_of >> 20, rest_of & 1023, f);
     }
-    place_of[kPieceEntries] += __shfl(incl, 63, 64);
+    done_4 += __shfl(upto_4, 63, 64);
+    done_2 += __popcll(with_two);
+    done_1 += __popcll(with_one);
   }
 }
 

@@ -308,6 +308,35 @@ def test_rgms_quads_and_steps(gpu_lib, d_in, d_out, workspace):
     assert np.array_equal(Y == np.inf, Yr == np.inf) and not np.isnan(Y).any()
 
 
+@pytest.mark.parametrize("workspace", [0, 288])
+@pytest.mark.parametrize("d_in,d_out", [(32, 32), (32, 256), (64, 288), (128, 160)])
+def test_rgms_long_pairs(gpu_lib, d_in, d_out, workspace):
+    """Pairs of 4 to 130 entries, whose pieces meet by fours and by twos before the product: as many of either in a cell as leave
+    every remainder of the tiles of four and of eight, and rows of Y wider than a workgroup's."""
+    say(f"[rgms long pairs] d_in={d_in} d_out={d_out} workspace={workspace}")
+    rng = np.random.default_rng(d_in + d_out)
+    n, n_rel, block = 38 * 32, 4, 32
+    counts = np.zeros((n_rel, n), dtype=np.int64)
+    for b in range(n // block):
+        at = b * block + rng.permutation(block)
+        pairs = min(b, block)
+        counts[0, at[:pairs]] = 16                                   # fours only
+        counts[1, at[:pairs]] = 8                                    # twos only
+        counts[2, at] = rng.choice([0, 3, 4, 7, 8, 12, 13, 16, 17, 24, 28, 31, 33, 64, 130], block)
+        counts[3, at[:1 + b % 5]] = [130, 15, 16, 48, 9][: 1 + b % 5]
+    w0 = workloads.random_csr(n_rel * n, n, counts.reshape(-1), 11, 1, "uniform")
+    X = rng.standard_normal((n, d_in)).astype(np.float32)
+    W = rng.standard_normal((n_rel, d_in, d_out)).astype(np.float32)
+    w = workloads.HeteroWorkload("long", n, n_rel, w0.indptr, w0.indices, w0.values, X, W)
+    (Y, again), info = run_rgms(gpu_lib, w, workspace_d_out=workspace, repeat=2)
+    assert info["row_block"] == block and info["n_stacked_rows_stored"] == int((counts > 0).sum())
+    pieces = (counts.reshape(n_rel, n // block, block) + 3) // 4
+    assert info["n_tiles"] == int(((pieces.sum(2) + 15) // 16).sum())
+    Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, X, W)
+    assert_y_close(Y, Yr, Sr, f"d_in={d_in} d_out={d_out}")
+    assert workspace == 0 or np.array_equal(Y, again)
+
+
 def test_rgms_non_finite_rows_cost_nothing(gpu_lib):
     """A call on an X that is all NaN does what one on numbers does.  (1.0 times as long; sums formed a second time took 20 to 30.)"""
     rng = np.random.default_rng(5)
