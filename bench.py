@@ -88,8 +88,9 @@ def median_spmm_ms(sptir, torch, hyb, X, Y, steps):
 
 
 def kernel_times(sptir, torch, hyb, X, Y, reps):
-    """Mean time of each group of launches inside sptir_spmm (HIP events on the launch stream, recorded by the
-    library between its launches) and the launch counts."""
+    """Mean time of each group of launches of sptir_spmm_timed (HIP events on the launch stream, recorded by the
+    library between its launches) and the launch counts.  It launches chunk lists and heavy lists apart; in sptir_spmm, and so in the
+    timed steps, heavy lists may share the last launch of the chunk lists."""
     acc = None
     for _ in range(reps):
         t = sptir.sptir_spmm_timed(hyb, X, Y)
@@ -374,8 +375,8 @@ def main():
     }
 
     # ------------------------------------------------------------- roofline
-    # The dominant kernel is whichever group of launches takes longer inside a call; its launches are timed live
-    # by HIP events the library records on the launch stream between its launches.
+    # The dominant kernel is whichever group of launches takes longer inside a timed call (see kernel_times); its launches are
+    # timed live by HIP events the library records on the launch stream between its launches.
     kt = head["kernels"]
     fingerprint = source_fingerprint()
     feat = 128
@@ -405,11 +406,12 @@ def main():
         "bound": "hbm", "achieved": round(alg_bytes / ms / 1e6, 1), "peak": HBM_PEAK_GBS,
         "unit": "GB/s", "frac": round(alg_bytes / ms / 1e6 / HBM_PEAK_GBS, 4),
         "traffic": traffic, "traffic_source": traffic_note,
-        "kernel": kernel, "launches_per_step": n_launch,
+        "kernel": kernel, "launches_per_timed_call": n_launch,
         "avg_launch_ms": round(per_launch_ms, 4), "algorithmic_bytes_per_launch": alg_bytes / max(n_launch, 1),
-        "kernel_ms_per_step": {"k_spmm_hyb": round(kt["ms_lists"], 4), "k_spmm_heavy": round(kt["ms_heavy"], 4),
-                               "k_heavy_reduce": round(kt["ms_reduce"], 4), "rows_in_column_slices": n_long,
-                               "launches": [kt["n_list_launches"], kt["n_heavy_launches"], kt["n_reduce_launches"]]},
+        "kernel_ms_per_timed_call": {"k_spmm_hyb": round(kt["ms_lists"], 4), "k_spmm_heavy": round(kt["ms_heavy"], 4),
+                                     "k_heavy_reduce": round(kt["ms_reduce"], 4), "rows_in_column_slices": n_long,
+                                     "launches": [kt["n_list_launches"], kt["n_heavy_launches"], kt["n_reduce_launches"]],
+                                     "note": "chunk lists and heavy lists launched apart; in a step they may share a launch"},
         "whole_call": {"achieved": round(head["bmin_gbs"], 1), "frac": round(head["bmin_gbs"] / HBM_PEAK_GBS, 4),
                        "algorithmic_bytes": head["bmin"]},
         "sources": fingerprint,

@@ -292,10 +292,10 @@ sptir_status_t sptir_launch_plan(int32_t n_rows, int32_t n_cols, int64_t stored_
  * of column partitions (n_phases launches, each adding to what the earlier ones
  * left in Y; a Y wider than the memory-side cache is then produced in several
  * such sweeps, each over a group of feature columns).  Heavy row pieces
- * (n_heavy_pieces > 0) take two more launches per 128 features (one where the
- * chunk lists are a single launch and the heavy lists the smaller part: they
- * then share that launch), rows in column slices (SPTIR_PLAN_LONG_ROWS) two more
- * per 128 features: their partial
+ * (n_heavy_pieces > 0) take two more launches per 128 features (up to 512 where
+ * there are few), of which the first is the last launch of the chunk lists unless
+ * sharing those among wavefronts saves more; rows in column slices
+ * (SPTIR_PLAN_LONG_ROWS) two more per 128 features: their partial
  * sums pass through scratch memory that the handle owns, so calls on one handle
  * that has heavy pieces must not overlap in time.  No atomics are used and every
  * sum has a fixed order, so two calls with the same handle and X on the same GPU
@@ -309,11 +309,12 @@ sptir_status_t sptir_spmm(const sptir_hyb_t* hyb, const float* X, float* Y, int3
 
 /*
  * Measurement aid: sptir_spmm with HIP events recorded on `stream` between its groups of launches, so that a
- * benchmark can price each kernel by the time it really took inside the call.  Synchronises `stream` before it
- * returns; creates and destroys a few events.  Same results as sptir_spmm.
- *   ms_lists   the chunk-list launches (k_spmm_hyb), n_list_launches of them
- *   ms_heavy   the heavy-piece launches (k_spmm_heavy; sptir_spmm itself may let them share the last launch of the
- *              chunk lists) and those over column slices (k_spmm_slices)
+ * benchmark can price each kind of work by itself.  Heavy pieces have a launch of their own here, where sptir_spmm may
+ * let them share the last launch of the chunk lists: the times are of this call, and their sum is a little more than
+ * what sptir_spmm takes.  Synchronises `stream` before it returns; creates and destroys a few events.  Same results as
+ * sptir_spmm.
+ *   ms_lists   the chunk-list launches (k_spmm_hyb, k_spmm_hyb_shared), n_list_launches of them
+ *   ms_heavy   the heavy-piece launches (k_spmm_heavy) and those over column slices (k_spmm_slices)
  *   ms_reduce  the launches that add the heavy pieces' partial sums to Y (k_heavy_reduce) and the slices' (k_slice_sums)
  */
 typedef struct {
