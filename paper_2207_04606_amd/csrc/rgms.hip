@@ -996,19 +996,25 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   if (chunks > 65535) return SPTIR_ERR_OVERFLOW;
   const bool ordered = d_out <= p->workspace_d_out;
   // Where the matrices W[r] are large (32 KB and up, more than L1 holds) the tiles are long, and a few hundred workgroups
-  // leave the CUs unevenly filled: items are then shared by several, eight wavefronts each, whose sums meet in Y by
-  // atomics, until there are 512 (8,370 rows, 128 x 128, 262 items: 0.215 -> 0.168 ms).  Clearing Y and the atomics have to be
-  // worth it, so an item needs 200,000 elements of W to read for two sharers and 250,000 more for each further one (27,608
-  // rows, 64 x 128, 188,000: 35 us alone, 80 shared by two; 6,903 rows, 128 x 128, 328,000: 75 alone, 62 by two, 72 by three;
-  // 6,110 rows, 983,000: 144 alone, 120 by two, 117 by three).  Where there are fewer than 160 row blocks all are
-  // divided into items already (26 graphs, shared until there were 512 workgroups: 12 % slower in the mean, up to 1.7 times).
+  // leave the CUs unevenly filled: items are then shared by up to four, eight wavefronts each, whose sums meet in Y by
+  // atomics.  An item takes about 0.12 us for 1000 elements of W that its tiles read; shared by s it takes an s-th of that, 8 us for the launch that
+  // clears Y and 24 + 6 s us for a million elements of Y, cleared and added to: the s for which that is least.  98 drawn graphs: 1.09 times
+  // as fast in the mean as with none shared (0.82 to 1.94), the best s for each 1.12.  (By the elements of W alone, two from 200,000 on and one more
+  // for every further 250,000: 1.00 on 49 of them (0.50 to 1.53).  32,415 rows, 64 x 128, 471,000: 60 us alone, 119 by two; 7,119 rows, 128 x 128,
+  // 2.7 million: 420 alone, 300 by two, 240 by four.)  Where there are fewer than 160 row blocks all are divided into items already.
   const int64_t whole = (int64_t)p->n_items * chunks;
   const bool large_w = d_in * d_out >= 64 * 128;
   const int64_t tiles_each = p->n_tiles / std::max<int64_t>(p->n_items, 1), w_each = tiles_each * d_in * d_out;
   const bool undivided = ((int64_t)p->n_rows - 1) >> p->log2_block >= 159;
   a.sharers = 1;
-  if (!ordered && large_w && undivided && whole < 512 && w_each >= 200000)
-    a.sharers = (int32_t)std::min<int64_t>(std::max<int64_t>(2, w_each / 250000), std::min<int64_t>(8, (512 + whole - 1) / whole));
+  if (!ordered && large_w && undivided && whole < 512) {
+    const double alone = 0.12e-3 * (double)w_each, y = 1e-6 * (double)p->n_rows * d_out;
+    double least = alone;
+    for (int32_t n = 2; n <= 4; ++n) {
+      const double shared = alone / n + 8. + (24. + 6. * n) * y;
+      if (shared < least) { least = shared; a.sharers = n; }
+    }
+  }
   // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs
   // and feature sizes: against 8 everywhere it is alike in the mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)
   a.n_waves = large_block ? 16 : large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;

@@ -337,6 +337,26 @@ def test_rgms_long_pairs(gpu_lib, d_in, d_out, workspace):
     assert workspace == 0 or np.array_equal(Y, again)
 
 
+@pytest.mark.parametrize("d_in,d_out,n_rel", [(128, 128, 32), (64, 128, 64), (128, 64, 40)])
+def test_rgms_shared_items(gpu_lib, d_in, d_out, n_rel):
+    """163 row blocks with a tile and more for every relation: an item's tiles read half a million elements of W and more, and four
+    workgroups share it (128 x 64: none, or three).  The last block has part of its rows; rows without entries are 0."""
+    say(f"[rgms shared items] d_in={d_in} d_out={d_out} n_rel={n_rel}")
+    rng = np.random.default_rng(d_in + n_rel)
+    n = 163 * 32 - 5
+    counts = rng.choice([0, 0, 1, 2, 5], n_rel * n, p=[0.3, 0.2, 0.3, 0.15, 0.05]).reshape(n_rel, n)
+    counts[:, ::37] = 0
+    w0 = workloads.random_csr(n_rel * n, n, counts.reshape(-1), 13, 1, "uniform")
+    w = workloads.HeteroWorkload("shared", n, n_rel, w0.indptr, w0.indices, w0.values,
+                                 rng.standard_normal((n, d_in)).astype(np.float32),
+                                 rng.standard_normal((n_rel, d_in, d_out)).astype(np.float32))
+    (Y, Y2), info = run_rgms(gpu_lib, w, repeat=2)
+    assert info["row_block"] == 32 and info["n_tiles"] * d_in * d_out >= 163 * 300_000
+    Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, w.X, w.W)
+    assert_y_close(Y, Yr, Sr, f"d_in={d_in} d_out={d_out}")
+    assert_y_close(Y2, Yr, Sr, f"d_in={d_in} d_out={d_out}, again")
+
+
 def test_rgms_non_finite_rows_cost_nothing(gpu_lib):
     """A call on an X that is all NaN does what one on numbers does.  (1.0 times as long; sums formed a second time took 20 to 30.)"""
     rng = np.random.default_rng(5)
