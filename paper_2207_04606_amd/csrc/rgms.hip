@@ -756,16 +756,19 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
 // nearly empty.  26 drawn graphs and feature sizes: the best block for each 1.4 % faster in the mean, 9 % at most.)  Fewer,
 // larger blocks divided into items were tried and lose more in global atomics than fuller tiles gain (27,163 rows,
 // 64 x 64: 0.042 -> 0.093 ms).
-// Blocks of 512 rows take the LDS of a CU and 16 wavefronts; what they win is W[r] read for half as many tiles.  They need two
-// workgroups' worth of them per CU (158,566 rows: 0.81 times as fast as with 256), no workspace, whose tiles take turns (0.79 to
-// 1.08), and fewer than 40 entries for every (relation, block) even so.  78 graphs and feature sizes, against 256 rows: up to 24 entries
-// 1.10 times as fast (0.97 to 1.21), to 40 1.03 (0.94 to 1.10; 32 x 32 features 0.98), to 64 0.98 (0.87 to 1.05).  1.9 M rows, 96
-// relations, 5.7 M entries, 32 x 32, 16 entries: 399 -> 353 us.
+// Blocks of 512 rows take the LDS of a CU and 16 wavefronts; what they win is W[r] read for half as many tiles, if that is for few entries, and
+// twice as many pieces to fill a tile with.  Against 256 rows, without a workspace, 142 graphs and feature sizes of 160 blocks of 512 and more: up
+// to 24 entries for every (relation, block) 1.15 times as fast (0.90 to 1.39), however many the blocks; up to 40 entries 1.04 from 384 blocks on
+// (0.97 to 1.22), where the last turn of workgroups weighs less, 1.01 below (0.88 to 1.24); up to 64 1.03 (0.88 to 1.34), beyond 1.01 (0.93 to
+// 1.27), some of it lost to CUs without work.  Below 160 blocks, where all are divided, 0.39.  117,840 rows, 74 relations,
+// 900 K entries, 64 x 64: 131 -> 114 us; 1.9 M rows, 96 relations, 5.7 M entries, 32 x 32, 16 entries: 394 -> 344.  With a workspace tiles take
+// turns, and larger blocks lose sooner.
 int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
   int s = kMinLog2Block;
   while (((int64_t)1 << s) * nnz < 32 * n_rows * n_rel && s < kMaxLog2Block - 1 && (n_rows >> (s + 1)) >= 160) ++s;
-  const bool large = s == kMaxLog2Block - 1 && !workspace && (n_rows >> kMaxLog2Block) >= 512 &&
-                     ((int64_t)1 << kMaxLog2Block) * nnz < 40 * n_rows * n_rel;
+  const int64_t entries = nnz << kMaxLog2Block, blocks = n_rows >> kMaxLog2Block;
+  const bool large = s == kMaxLog2Block - 1 && !workspace &&
+                     ((blocks >= 160 && entries < 24 * n_rows * n_rel) || (blocks >= 384 && entries < 40 * n_rows * n_rel));
   return large ? kMaxLog2Block : s;
 }
 
@@ -1001,11 +1004,12 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   // clears Y and 24 + 6 s us for a million elements of Y, cleared and added to: the s for which that is least.  98 drawn graphs: 1.09 times
   // as fast in the mean as with none shared (0.82 to 1.94), the best s for each 1.12.  (By the elements of W alone, two from 200,000 on and one more
   // for every further 250,000: 1.00 on 49 of them (0.50 to 1.53).  32,415 rows, 64 x 128, 471,000: 60 us alone, 119 by two; 7,119 rows, 128 x 128,
-  // 2.7 million: 420 alone, 300 by two, 240 by four.)  Where there are fewer than 160 row blocks all are divided into items already.
+  // 2.7 million: 420 alone, 300 by two, 240 by four.)  Where there are fewer than 160 row blocks all are divided into items already; blocks of 512 rows have
+  // 16 wavefronts as it is.
   const int64_t whole = (int64_t)p->n_items * chunks;
   const bool large_w = d_in * d_out >= 64 * 128;
   const int64_t tiles_each = p->n_tiles / std::max<int64_t>(p->n_items, 1), w_each = tiles_each * d_in * d_out;
-  const bool undivided = ((int64_t)p->n_rows - 1) >> p->log2_block >= 159;
+  const bool undivided = ((int64_t)p->n_rows - 1) >> p->log2_block >= 159 && !large_block;
   a.sharers = 1;
   if (!ordered && large_w && undivided && whole < 512) {
     const double alone = 0.12e-3 * (double)w_each, y = 1e-6 * (double)p->n_rows * d_out;

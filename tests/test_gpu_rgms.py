@@ -308,6 +308,24 @@ def test_rgms_quads_and_steps(gpu_lib, d_in, d_out, workspace):
     assert np.array_equal(Y == np.inf, Yr == np.inf) and not np.isnan(Y).any()
 
 
+@pytest.mark.parametrize("blocks,mean,rows", [(160, 0.043, 512), (159, 0.043, 256), (160, 0.051, 256), (384, 0.051, 512), (383, 0.051, 256),
+                                              (384, 0.085, 256)])
+def test_rgms_fewer_blocks_of_512_rows(gpu_lib, blocks, mean, rows):
+    """Blocks of 512 rows where 160 of them have fewer than 24 entries of a relation each, or 384 fewer than 40, and nobody shares their
+    items (128 x 64 features: two workgroups an item of smaller blocks)."""
+    say(f"[rgms 512, few] {blocks} blocks, {mean * 512:.0f} entries a relation and block")
+    n, n_rel, d_in, d_out = 512 * blocks + 3, 5, 128, 64
+    rng = np.random.default_rng(blocks)
+    w = workloads.random_csr(n_rel * n, n, rng.poisson(mean, n_rel * n), 1, 1)
+    X = rng.standard_normal((n, d_in)).astype(np.float32)
+    W = rng.standard_normal((n_rel, d_in, d_out)).astype(np.float32)
+    w = workloads.HeteroWorkload("few", n, n_rel, w.indptr, w.indices, w.values, X, W)
+    Y, info = run_rgms(gpu_lib, w)
+    assert info["row_block"] == rows
+    Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, w.X, w.W)
+    assert_y_close(Y, Yr, Sr, f"{blocks} blocks")
+
+
 @pytest.mark.parametrize("workspace", [0, 288])
 @pytest.mark.parametrize("d_in,d_out", [(32, 32), (32, 256), (64, 288), (128, 160)])
 def test_rgms_long_pairs(gpu_lib, d_in, d_out, workspace):
