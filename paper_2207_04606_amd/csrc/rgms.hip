@@ -750,12 +750,13 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
   }
 }
 
-// Rows per block: 32 entries for every (relation, block), so that tiles fill, as long
-// as that leaves 160 blocks, about what keeps 256 CUs busy with 16 wavefronts each.  (64 entries: 42 graphs where that makes
-// 128 rows 256, 0.97 times as fast in the mean, 0.79 to 1.15; what decides there is whether the last turn of workgroups is
-// nearly empty.  26 drawn graphs and feature sizes: the best block for each 1.4 % faster in the mean, 9 % at most.)  Fewer,
-// larger blocks divided into items were tried and lose more in global atomics than fuller tiles gain (27,163 rows,
-// 64 x 64: 0.042 -> 0.093 ms).
+// Rows per block: 32 entries for every (relation, block), so that tiles fill, as long as that leaves 160 blocks, about what keeps
+// 256 CUs busy with 16 wavefronts each.  557 pairs of blocks of 32 to 256 rows, the larger against the smaller: with 16 to 24 entries in the
+// smaller 1.05 times as fast, with 24 to 32 1.01, with 32 to 48 1.01, with 48 to 64 0.98 (0.74 to 1.45: what decides is whether the last
+// turn of workgroups is nearly empty).  16 entries with a workspace: a tile's turn comes sooner where a block has fewer of them.  553 pairs: with
+// less than 16 entries in the smaller 0.97, with 16 to 32 0.94 (0.58 to 1.47), with 32 to 64 0.90.
+// Fewer, larger blocks divided into items lose more in global atomics than fuller tiles gain (27,163 rows, 64 x 64: blocks of 256 rows 83 us,
+// of 128 30).
 // Blocks of 512 rows take the LDS of a CU and 16 wavefronts; what they win is W[r] read for half as many tiles, if that is for few entries, and
 // twice as many pieces to fill a tile with.  Against 256 rows, without a workspace, 142 graphs and feature sizes of 160 blocks of 512 and more: up
 // to 24 entries for every (relation, block) 1.15 times as fast (0.90 to 1.39), however many the blocks; up to 40 entries 1.04 from 384 blocks on
@@ -765,7 +766,8 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
 // turns, and larger blocks lose sooner.
 int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
   int s = kMinLog2Block;
-  while (((int64_t)1 << s) * nnz < 32 * n_rows * n_rel && s < kMaxLog2Block - 1 && (n_rows >> (s + 1)) >= 160) ++s;
+  const int64_t enough = workspace ? 16 : 32;
+  while (((int64_t)1 << s) * nnz < enough * n_rows * n_rel && s < kMaxLog2Block - 1 && (n_rows >> (s + 1)) >= 160) ++s;
   const int64_t entries = nnz << kMaxLog2Block, blocks = n_rows >> kMaxLog2Block;
   const bool large = s == kMaxLog2Block - 1 && !workspace &&
                      ((blocks >= 160 && entries < 24 * n_rows * n_rel) || (blocks >= 384 && entries < 40 * n_rows * n_rel));

@@ -308,6 +308,18 @@ def test_rgms_quads_and_steps(gpu_lib, d_in, d_out, workspace):
     assert np.array_equal(Y == np.inf, Yr == np.inf) and not np.isnan(Y).any()
 
 
+@pytest.mark.parametrize("mean,rows", [(0.03, 256), (0.12, 256), (0.13, 128), (0.24, 128), (0.26, 64), (0.49, 64), (0.51, 32)])
+def test_rgms_rows_of_a_block_with_a_workspace(gpu_lib, mean, rows):
+    """Sixteen entries of a relation in a block are enough where tiles take turns."""
+    n, n_rel = 512 * 128 + 5, 16
+    counts = np.random.default_rng(1).poisson(mean, n_rel * n)
+    w = workloads.random_csr(n_rel * n, n, counts, 1, 1)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    h = gpu_lib.sptir_rgms_build(n_rel, n, n, dev(w.indptr), dev(w.indices), dev(w.values), -1, 32)
+    assert gpu_lib.sptir_rgms_info(h)["row_block"] == rows
+    h.destroy()
+
+
 @pytest.mark.parametrize("blocks,mean,rows", [(160, 0.043, 512), (159, 0.043, 256), (160, 0.051, 256), (384, 0.051, 512), (383, 0.051, 256),
                                               (384, 0.085, 256)])
 def test_rgms_fewer_blocks_of_512_rows(gpu_lib, blocks, mean, rows):
