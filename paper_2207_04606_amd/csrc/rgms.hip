@@ -29,8 +29,9 @@
 // rows that it has not got, and the gather is two instructions a step.  What counts beside that: a tile's loads depend on each other and are
 // waited for one tile later, so whatever makes the compiler wait for the newest load (a copy of a register that is being loaded, a
 // count of loads that depends on a branch) costs a trip past L2 a tile; and wavefronts (32 x 32 features, 94 K rows, 51 relations, 4.76 M
-// entries: 118 us with six per SIMD, 132 with five).  That graph 153 -> 110 us, 1.9 M rows, 96 relations, 5.7 M entries
-// 435 -> 354; 27,163 rows, 46 relations, 148,100 entries, 64 x 64: 39 -> 31.5.  45 drawn graphs and feature sizes: 1.2 times as fast (0.95 to 1.55).
+// entries: six per SIMD 1.12 times as fast as five).  That graph 161 -> 107 us, 1.9 M rows, 96 relations, 5.7 M entries
+// 439 -> 342; 27,163 rows, 46 relations, 148,100 entries, 64 x 64: 39 -> 30.  130 drawn graphs and feature sizes, 1.3 to 40 entries a pair: 1.21 times as fast up
+// to 128 columns of Y (0.97 to 1.85), 1.06 for 256 and 512 (0.88 to 1.31: 16 entries a pair, for which W[r] is read twice as often).
 // Blocks are as large as gives (relation, block) enough pieces, and small enough that there are workgroups
 // for all CUs; a block with far more tiles than the others is several work items, whose sums meet in Y by global atomics.
 //
@@ -137,7 +138,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(TIN == 1 ?
   constexpr bool kInTurns = ORDERED || TIN > 1;     // the wavefronts take tiles in turns, not a run each
   constexpr int kHalf = 8 * VW;                     // of the features of a load, those of lanes 0 .. 31 of a product
   // Rows of W (and as many of the other half) that are loaded together: all of a pass, or 4, of which two lots are held.
-  // (16: 153 registers; 8: 64 x 64 features 2 % slower, 128 x 32 16 %, whose wavefronts are then three per SIMD and not four.)
+  // (8, which spills 2 registers for 128 features: 94,806 rows, 96 relations, 670 K entries, 64 x 64 features 102 -> 106 us, 128 x 128
+  // 327 -> 338; 16 spills 6 for 64 features, 127 for 128: 128 and 719 us.)
   constexpr int kChunk = TIN == 1 ? 16 : 4;
   constexpr int kChunks = kDin / 2 / kChunk;        // per pass
   extern __shared__ __align__(16) double y_tile[];  // [rows + 1][width] (the last for pieces that are none), then ORDERED: turn[width / kPass]

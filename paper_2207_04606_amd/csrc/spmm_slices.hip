@@ -16,8 +16,8 @@
 // row of zeros after the slice's last (a fifth of what is read; the last step may have half).  The steps of a wavefront follow each
 // other from slice to slice, whatever the block, and are asked for two steps ahead.
 //
-// 232,965 rows, 114.6 M entries, 128 features: the call 2.39 -> 1.82 ms.  87 M entries in 0.99 ms, 45 TB/s of gathered rows (28.5
-// in k_spmm_heavy; 1.2 times as many slots), vector ALU issuing 67 % of it, bank conflicts 34 %; the rest is loading slices and
+// 232,965 rows, 114.6 M entries, 128 features: the call 2.39 -> 1.80 ms.  87 M entries in 0.98 ms, 46 TB/s of gathered rows (28.5
+// in k_spmm_heavy; 1.2 times as many slots), vector ALU issuing 68 % of it, bank conflicts 34 %; the rest is loading slices and
 // wavefronts that wait there for the last.
 #include <algorithm>
 #include <cstring>
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void k_spmm_slices(SliceArgs a) {
     int bound[kMaxBlocksPerWave + 1];
 #pragma unroll
     for (int r = 0; r <= kMaxBlocksPerWave; ++r) bound[r] = word(s * u.blocks_per_wave + min(r, u.blocks_per_wave));
-    get_slice(s, staged);  // (wavefronts that are done load while others work: the call of the header 1.82 -> 1.80 ms)
+    get_slice(s, staged);  // (wavefronts that are done load while others work: with the load after the barrier the call of the header took 1.82 ms)
     __syncthreads();       // (the slice before is no longer read)
     put_slice(s, staged);
     __syncthreads();
