@@ -144,10 +144,8 @@ struct SpmmArgs {
   int32_t n_row_blocks;
   int32_t log2_row_block;
   int32_t feat;
-  int32_t n_tiles;     // feature tiles of this launch, the first of which is tile0
+  TileDeal deal;       // of the feature tiles of this launch, the first of which is tile0
   int32_t tile0;
-  int32_t map_mode;
-  int32_t map_param;
   int32_t accumulate;  // 0: Y tile is overwritten, 1: added to (a later phase)
   const float* row_val;  // UNIT kernels: the value of every entry of row r
 };
@@ -480,7 +478,7 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
   using W = HybWalker<VEC, LG, IDX32, WIDE, UNIT, TileSink<VEC, LG>>;
   int64_t unit;
   int tile_id;
-  decode_block(bid, a.map_mode, a.map_param, a.n_tiles, &unit, &tile_id);
+  decode_deal(bid, a.deal, &unit, &tile_id);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t slot = SHARED ? unit : unit * kHybWaves + wave;
@@ -598,9 +596,7 @@ struct HeavyArgs {
   int32_t feat;
   int32_t feat0;               // first feature of this sweep
   int32_t partial_feat;        // features a partial-sum row holds
-  int32_t n_tiles;             // feature tiles of this sweep
-  int32_t map_mode;
-  int32_t map_param;
+  TileDeal deal;               // of the feature tiles of this sweep
 };
 
 // One wavefront per (heavy list, feature tile): the list's chunks (list_chunks of them) are walked like any other
@@ -614,7 +610,7 @@ __device__ __forceinline__ void heavy_workgroup(const HeavyArgs& a, unsigned bid
   using W = HybWalker<VEC, LG, IDX32, WIDE, UNIT, PartialSink<VEC, LG>>;
   int64_t unit;
   int tile_id;
-  decode_block(bid, a.map_mode, a.map_param, a.n_tiles, &unit, &tile_id);
+  decode_deal(bid, a.deal, &unit, &tile_id);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (unit * kHybWaves + wave >= a.n_lists) return;
@@ -974,11 +970,13 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   //  asks for full rows gets narrower tiles)
   static_assert(kHybWaves == 4, "full_rows_fit() and half_rows_fit() count four wavefronts per workgroup");
   const ListShape lists{h->rounds != 0, h->full_rows != 0, h->log2_row_block, h->n_row_blocks, h->n_cols};
+  // columns of a launch of the chunk lists
+  const int64_t span = (int64_t)h->parts_per_phase * (int64_t)h->w, list_cols = std::min<int64_t>(span, h->n_cols);
   if (!plan(n_units, feat, X, Y, lists, &g)) return SPTIR_ERR_OVERFLOW;
   SpmmArgs a;
   a.stream = h->stream;
   a.X = X; a.Y = Y; a.n_rows = h->n_rows; a.n_row_blocks = h->n_row_blocks; a.log2_row_block = h->log2_row_block;
-  a.feat = feat; a.n_tiles = g.n_tiles; a.map_mode = g.map_mode; a.map_param = g.map_param;
+  a.feat = feat;
   // per wavefront: its Y tile and its ring of two quads
   const bool wide = !h->compact_stream, unit = h->row_val != nullptr;
   a.row_val = h->row_val;
@@ -986,8 +984,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
       (size_t)kHybWaves * (sizeof(float) * ((size_t)g.vec * g.lg << h->log2_row_block) +
                            sizeof(int) * 2 * ((wide ? 3 : 2) - (unit ? 1 : 0)) * kChunkSlots * kChunksPerQuad);
   // A compact list holds columns relative to the first column of its launch, which moves into the X pointer.
-  const int64_t span = (int64_t)h->parts_per_phase * (int64_t)h->w;
-  const bool idx32 = offsets_fit_32(wide ? (int64_t)h->n_cols : (span < h->n_cols ? span : (int64_t)h->n_cols), feat);
+  const bool idx32 = offsets_fit_32(wide ? (int64_t)h->n_cols : list_cols, feat);
   const int all_tiles = g.n_tiles;
   // Wide partial-sum rows take the heavy lists through all features at once.  Feature tiles that do not map to whole XCDs
   // then share the L2s, which an X beyond them pays for (62,000 rows of 160 floats, five tiles: 150 us against 127).
@@ -1006,10 +1003,11 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
     *gh = g;
     const int tile = g.vec * g.lg;
     gh->n_tiles = (width + tile - 1) / tile;
-    ha->feat0 = feat0; ha->n_tiles = gh->n_tiles; ha->partial_feat = partial_feat;
+    ha->feat0 = feat0; ha->partial_feat = partial_feat;
     ha->list0 = 0; ha->n_lists = h->n_heavy_lists;
     if (!plan_tiles(((int64_t)ha->n_lists + kHybWaves - 1) / kHybWaves, gh)) return false;
-    ha->map_mode = gh->map_mode; ha->map_param = gh->map_param;
+    ha->deal = deal_of(((int64_t)ha->n_lists + kHybWaves - 1) / kHybWaves, *gh);
+    deal_ranges(&ha->deal);
     return true;
   };
   // The last launch of the chunk lists takes the heavy lists along (those of the first partial_feat features, from feat_begin
@@ -1089,7 +1087,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
     a.rb_chunk_ptr = h->rb_chunk_ptr; a.accumulate = 0;
     for (int tile0 = 0; tile0 < all_tiles; tile0 += per_sweep) {
       g.n_tiles = all_tiles - tile0 < per_sweep ? all_tiles - tile0 : per_sweep;
-      a.n_tiles = g.n_tiles; a.tile0 = tile0;
+      a.tile0 = tile0;
       heavy_with_lists = false;
       const int feat_begin = tile0 * tile_floats, feat_end = std::min(feat, (tile0 + g.n_tiles) * tile_floats);
       int64_t per_round = (int64_t)capacity / g.n_tiles * kHybWaves;  // row blocks
@@ -1101,7 +1099,8 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         a.rb_order = h->rb_order + first;
         a.n_row_blocks = (int32_t)here;
         if (!plan_tiles((here + kHybWaves - 1) / kHybWaves, &g)) return SPTIR_ERR_OVERFLOW;
-        a.map_mode = g.map_mode; a.map_param = g.map_param;
+        a.deal = deal_of((here + kHybWaves - 1) / kHybWaves, g);
+        move_slow_units((uintptr_t)(X + tile0 * tile_floats), feat, list_cols, &g, &a.deal);
         const bool last = first + here == h->n_row_blocks;
         if (!last || !lists_and_heavy(feat_begin, feat_end, false))
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, lds_bytes, stream, a); });
@@ -1130,7 +1129,8 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
                                   (((int64_t)h->n_heavy_lists * g.n_tiles + heavy_at_once - 1) / heavy_at_once);
       Geometry gs = g;
       if (waves > 1 && !plan_tiles(h->n_row_blocks, &gs)) return SPTIR_ERR_OVERFLOW;
-      a.n_tiles = g.n_tiles; a.tile0 = tile0; a.map_mode = g.map_mode; a.map_param = g.map_param;  // (of gs as well)
+      a.tile0 = tile0; a.deal = deal_of(n_units, g);
+      move_slow_units((uintptr_t)(X + tile0 * g.vec * g.lg), feat, list_cols, &g, &a.deal);
       for (int phase = 0; phase < h->n_phases; ++phase) {
         a.rb_chunk_ptr = h->rb_chunk_ptr + (size_t)phase * h->n_row_blocks;
         a.rb_order = h->rb_order + (size_t)phase * h->n_row_blocks;
@@ -1140,6 +1140,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         ++n_list_launches;
         if (last && !share_rather_than_join(shared, heavy_quads) && lists_and_heavy(0, feat, true)) continue;
         if (waves > 1) {
+          a.deal = deal_of(h->n_row_blocks, gs);
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) {
             launch_shared_lists(v, gs, waves, lds_bytes / kHybWaves * waves, stream, a);
           });
