@@ -944,8 +944,18 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
         items.push_back({b, t0 + lo, hi - lo, p->n_parts++});
       }
     }
+    // Then the others, longest first (by 1024 classes of work), so that what the last workgroups leave idle is small: 93,773 rows, 51
+    // relations, 4.76 M entries, 32 x 32, 1477 blocks of 52 to 204 tiles in two turns of the CUs: 104 -> 98 us.
+    constexpr int kClasses = 1024;
+    std::vector<int32_t> class_end(kClasses + 1, 0);
+    auto class_of = [&](int64_t c) { return (int)((most - c) * (kClasses - 1) / most); };
     for (int32_t b = 0; b < n_blocks; ++b)
-      if (cost_of(b) <= most) items.push_back({b, block_tile[b], tiles_of(b), -1});
+      if (cost_of(b) <= most) ++class_end[class_of(cost_of(b)) + 1];
+    for (int i = 0; i < kClasses; ++i) class_end[i + 1] += class_end[i];
+    const size_t n_before = items.size();
+    items.resize(n_before + (size_t)class_end[kClasses]);
+    for (int32_t b = 0; b < n_blocks; ++b)
+      if (cost_of(b) <= most) items[n_before + (size_t)class_end[class_of(cost_of(b))]++] = {b, block_tile[b], tiles_of(b), -1};
     p->n_items = (int32_t)items.size();
     p->n_divided = (int32_t)divided.size();
 
