@@ -146,10 +146,14 @@ struct SpmmArgs {
   int32_t feat;
   TileDeal deal;       // of the feature tiles of this launch, the first of which is tile0
   int32_t tile0;
+  int32_t wg_waves;    // wavefronts per workgroup, each with a list of its own
   int32_t accumulate;  // 0: Y tile is overwritten, 1: added to (a later phase)
   const float* row_val;  // UNIT kernels: the value of every entry of row r
 };
 
+// Wavefronts per workgroup: kHybWaves in rounds, where neighbours walk the same slices of X at a time (232,965 rows, 114.6 M entries: 1791 us, one
+// 1815); else one, whose place on the CU is free when it ends (132,534 rows, 39.6 M entries in eight launches: 997 -> 980 us; 169,343 rows,
+// 1.17 M entries, both directions 172.0 -> 170.5).  90 drawn graphs, products and builds: 1.016 times as fast (0.97, of calls of 6 us, to 1.17).
 constexpr int kHybWaves = 4;
 constexpr int kHybBlock = 64 * kHybWaves;
 
@@ -472,7 +476,8 @@ struct HybWalker {
 // SHARED: the wavefronts of a workgroup walk consecutive ranges of quads of one list, each into a tile of its own, and the
 // tiles are added in the order of the wavefronts (the launch is the only one: Y is overwritten); otherwise a wavefront has a
 // list to itself.
-template <int VEC, int LG, bool IDX32, bool WIDE, bool UNIT, bool SHARED = false>
+// WITH_HEAVY: in a kernel that walks heavy lists too.
+template <int VEC, int LG, bool IDX32, bool WIDE, bool UNIT, bool SHARED = false, bool WITH_HEAVY = false>
 __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid, float* smem) {
   using S = Shape<VEC, LG>;
   using W = HybWalker<VEC, LG, IDX32, WIDE, UNIT, TileSink<VEC, LG>>;
@@ -481,7 +486,7 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
   decode_deal(bid, a.deal, &unit, &tile_id);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t slot = SHARED ? unit : unit * kHybWaves + wave;
+  const int64_t slot = SHARED ? unit : unit * a.wg_waves + wave;
   if (slot >= a.n_row_blocks) return;
   const int64_t rb = a.rb_order[slot];
   const int row_block = 1 << a.log2_row_block;
@@ -500,12 +505,27 @@ __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid,
   // the tile starts from zero, or from what earlier launches (column partitions) left in Y; with UNIT what it
   // sums still has to be multiplied by the row's value, so the earlier Y joins at the end instead
   float* y0 = a.Y + (size_t)rb_first * (size_t)a.feat + f0;
-  for (int r = g; r < row_block; r += S::kGroups) {
-    float init[VEC];
+  if (!SHARED && !UNIT && !WITH_HEAVY && a.accumulate) {
+    // (The loads of four rows at a time: one after the other they were a fifth of a wavefront's life, 132,534 rows, 39.6 M entries 980 -> 967
+    // us.  Where heavy lists are in the launch, which is then the only one as a rule, this code costs the others 0.4 of 38 us.)
+    const float* y_from = f_active ? y0 : a.Y + (size_t)rb_first * (size_t)a.feat;
+    for (int r = g; r < row_block; r += 4 * S::kGroups) {
+      float init[4][VEC];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) init[e] = 0.f;
-    if (!SHARED && !UNIT && a.accumulate && f_active && r < rows_here) load_unaligned<VEC>(init, y0 + (size_t)r * (size_t)a.feat);
-    store_vec<VEC>(tile + tile_index<VEC, LG>(r, fl), init);
+      for (int u = 0; u < 4; ++u) load_unaligned<VEC>(init[u], y_from + (size_t)min(r + u * S::kGroups, rows_here - 1) * (size_t)a.feat);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (r + u * S::kGroups < row_block) store_vec<VEC>(tile + tile_index<VEC, LG>(r + u * S::kGroups, fl), init[u]);
+    }
+  } else {
+    for (int r = g; r < row_block; r += S::kGroups) {
+      float init[VEC];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) init[e] = 0.f;
+      if (!SHARED && !UNIT && WITH_HEAVY && a.accumulate && f_active && r < rows_here)
+        load_unaligned<VEC>(init, y0 + (size_t)r * (size_t)a.feat);
+      store_vec<VEC>(tile + tile_index<VEC, LG>(r, fl), init);
+    }
   }
 
   const int64_t c0 = a.rb_chunk_ptr[rb];
@@ -597,6 +617,7 @@ struct HeavyArgs {
   int32_t feat0;               // first feature of this sweep
   int32_t partial_feat;        // features a partial-sum row holds
   TileDeal deal;               // of the feature tiles of this sweep
+  int32_t wg_waves;            // wavefronts per workgroup
 };
 
 // One wavefront per (heavy list, feature tile): the list's chunks (list_chunks of them) are walked like any other
@@ -613,8 +634,9 @@ __device__ __forceinline__ void heavy_workgroup(const HeavyArgs& a, unsigned bid
   decode_deal(bid, a.deal, &unit, &tile_id);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (unit * kHybWaves + wave >= a.n_lists) return;
-  const int64_t list = a.list0 + unit * kHybWaves + wave;
+  const int64_t number = unit * a.wg_waves + wave;
+  if (number >= a.n_lists) return;
+  const int64_t list = a.list0 + number;
   const int g = lane / LG, fl = lane & (LG - 1);
   const int f_in_sweep = tile_id * S::kTile + fl * VEC;
   const bool f_active = a.feat0 + f_in_sweep < a.feat;
@@ -646,7 +668,7 @@ __global__ __launch_bounds__(kHybBlock) void k_spmm_hyb_heavy(SpmmArgs a, HeavyA
   const bool first = blockIdx.x < n_first;
   const unsigned bid = first ? blockIdx.x : blockIdx.x - n_first;
   if (first == (heavy_first != 0)) heavy_workgroup<VEC, LG, IDX32, WIDE, UNIT>(ha, bid, smem);
-  else lists_workgroup<VEC, LG, IDX32, WIDE, UNIT>(a, bid, smem);
+  else lists_workgroup<VEC, LG, IDX32, WIDE, UNIT, false, true>(a, bid, smem);
 }
 
 // Y[r, feat0 + f] += (row_val[r] *) the partial sums of row r's heavy pieces.  SPLIT groups of (width / VEC) threads per
@@ -770,11 +792,11 @@ void with_variant(int vec, int lg, bool idx32, bool wide, bool unit, F&& f) {
 }
 
 template <typename V>
-void launch_lists(V, const Geometry& g, size_t lds_bytes, hipStream_t stream, const SpmmArgs& a) {
+void launch_lists(V, const Geometry& g, int waves, size_t lds_bytes, hipStream_t stream, const SpmmArgs& a) {
   auto* kernel = &k_spmm_hyb<V::vec, V::lg, V::idx32, V::wide, V::unit>;
   static OncePerDevice allowed;
   allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds_bytes, allowed);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)g.grid), dim3(kHybBlock), lds_bytes, stream, a);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)g.grid), dim3(64 * (unsigned)waves), lds_bytes, stream, a);
 }
 
 // (small graphs: offsets of 32 bits, and no whole 512-byte runs of X; compiled for nothing else)
@@ -832,14 +854,14 @@ SharedLists shared_list_waves(int64_t n_lists, int64_t n_quads, int64_t longest_
 bool share_rather_than_join(const SharedLists& shared, int64_t heavy_quads) { return shared.saved >= heavy_quads + 2; }
 
 template <typename V>
-void launch_heavy_and_lists(V, int64_t n_heavy_workgroups, int64_t n_list_workgroups, bool heavy_first, size_t lds_bytes,
-                            hipStream_t stream, const SpmmArgs& a, const HeavyArgs& ha) {
+void launch_heavy_and_lists(V, int64_t n_heavy_workgroups, int64_t n_list_workgroups, bool heavy_first, int waves,
+                            size_t lds_bytes, hipStream_t stream, const SpmmArgs& a, const HeavyArgs& ha) {
   auto* kernel = &k_spmm_hyb_heavy<V::vec, V::lg, V::idx32, V::wide, V::unit>;
   static OncePerDevice allowed;
   allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds_bytes, allowed);
   const int64_t n_first = ((heavy_first ? n_heavy_workgroups : n_list_workgroups) + 7) / 8 * 8;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(n_first + (heavy_first ? n_list_workgroups : n_heavy_workgroups))), dim3(kHybBlock),
-                     lds_bytes, stream, a, ha, (unsigned)n_first, heavy_first ? 1 : 0);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(n_first + (heavy_first ? n_list_workgroups : n_heavy_workgroups))),
+                     dim3(64 * (unsigned)waves), lds_bytes, stream, a, ha, (unsigned)n_first, heavy_first ? 1 : 0);
 }
 
 // workgroups of k_spmm_hyb the GPU holds at once (0: unknown)
@@ -859,11 +881,11 @@ int resident_workgroups(V, size_t lds_bytes) {
 }
 
 template <typename V>
-void launch_heavy(V, const Geometry& g, hipStream_t stream, const HeavyArgs& a) {
+void launch_heavy(V, const Geometry& g, int waves, hipStream_t stream, const HeavyArgs& a) {
   const size_t lds_bytes =
-      (size_t)kHybWaves * sizeof(int) * 2 * ((V::wide ? 3 : 2) - (V::unit ? 1 : 0)) * kChunkSlots * kChunksPerQuad;
-  hipLaunchKernelGGL((k_spmm_heavy<V::vec, V::lg, V::idx32, V::wide, V::unit>), dim3((unsigned)g.grid), dim3(kHybBlock),
-                     lds_bytes, stream, a);
+      (size_t)waves * sizeof(int) * 2 * ((V::wide ? 3 : 2) - (V::unit ? 1 : 0)) * kChunkSlots * kChunksPerQuad;
+  hipLaunchKernelGGL((k_spmm_heavy<V::vec, V::lg, V::idx32, V::wide, V::unit>), dim3((unsigned)g.grid),
+                     dim3(64 * (unsigned)waves), lds_bytes, stream, a);
 }
 
 }  // namespace
@@ -965,7 +987,8 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   if (!h->spmm_plan) return SPTIR_ERR_UNSUPPORTED;
 
   Geometry g;
-  const int64_t n_units = ((int64_t)h->n_row_blocks + kHybWaves - 1) / kHybWaves;
+  const int wg_waves = h->rounds ? kHybWaves : 1;
+  const int64_t n_units = ((int64_t)h->n_row_blocks + wg_waves - 1) / wg_waves;
   // (512-byte tiles only where a workgroup's Y tiles fit the CU's LDS: a caller who fixes large row blocks and
   //  asks for full rows gets narrower tiles)
   static_assert(kHybWaves == 4, "full_rows_fit() and half_rows_fit() count four wavefronts per workgroup");
@@ -976,12 +999,12 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   SpmmArgs a;
   a.stream = h->stream;
   a.X = X; a.Y = Y; a.n_rows = h->n_rows; a.n_row_blocks = h->n_row_blocks; a.log2_row_block = h->log2_row_block;
-  a.feat = feat;
+  a.feat = feat; a.wg_waves = wg_waves;
   // per wavefront: its Y tile and its ring of two quads
   const bool wide = !h->compact_stream, unit = h->row_val != nullptr;
   a.row_val = h->row_val;
   const size_t lds_bytes =
-      (size_t)kHybWaves * (sizeof(float) * ((size_t)g.vec * g.lg << h->log2_row_block) +
+      (size_t)wg_waves * (sizeof(float) * ((size_t)g.vec * g.lg << h->log2_row_block) +
                            sizeof(int) * 2 * ((wide ? 3 : 2) - (unit ? 1 : 0)) * kChunkSlots * kChunksPerQuad);
   // A compact list holds columns relative to the first column of its launch, which moves into the X pointer.
   const bool idx32 = offsets_fit_32(wide ? (int64_t)h->n_cols : list_cols, feat);
@@ -1003,10 +1026,11 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
     *gh = g;
     const int tile = g.vec * g.lg;
     gh->n_tiles = (width + tile - 1) / tile;
-    ha->feat0 = feat0; ha->partial_feat = partial_feat;
+    ha->feat0 = feat0; ha->wg_waves = wg_waves; ha->partial_feat = partial_feat;
     ha->list0 = 0; ha->n_lists = h->n_heavy_lists;
-    if (!plan_tiles(((int64_t)ha->n_lists + kHybWaves - 1) / kHybWaves, gh)) return false;
-    ha->deal = deal_of(((int64_t)ha->n_lists + kHybWaves - 1) / kHybWaves, *gh);
+    const int64_t n_heavy_units = ((int64_t)ha->n_lists + wg_waves - 1) / wg_waves;
+    if (!plan_tiles(n_heavy_units, gh)) return false;
+    ha->deal = deal_of(n_heavy_units, *gh);
     deal_ranges(&ha->deal);
     return true;
   };
@@ -1027,8 +1051,9 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         gh.grid + g.grid + 8 > 0x7FFFFFFF)
       return false;
     with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) {
-      if (timers) launch_lists(v, g, lds_bytes, stream, a);
-      else launch_heavy_and_lists(v, gh.grid, g.grid, few_heavy_first && gh.grid <= g.grid, lds_bytes, stream, a, ha);
+      if (timers) launch_lists(v, g, wg_waves, lds_bytes, stream, a);
+      else launch_heavy_and_lists(v, gh.grid, g.grid, few_heavy_first && gh.grid <= g.grid, wg_waves, lds_bytes,
+                                  stream, a, ha);
     });
     heavy_with_lists = !timers;
     return true;
@@ -1049,7 +1074,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
       // ended with a partly filled GPU: 1.62 ms against 1.53 on the largest graph).
       if (!heavy_launch_shape(feat0, width, &ha, &gh)) return SPTIR_ERR_OVERFLOW;
       if (!already_launched || feat0 > feat_begin) {
-        with_variant(g.vec, g.lg, idx32_all, wide, unit, [&](auto v) { launch_heavy(v, gh, stream, ha); });
+        with_variant(g.vec, g.lg, idx32_all, wide, unit, [&](auto v) { launch_heavy(v, gh, wg_waves, stream, ha); });
         if (timers) timers->mark(stream, LaunchTimers::kHeavy, 1);
       }
       const int block = width < kReduceFeat ? width : kReduceFeat;
@@ -1103,7 +1128,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         move_slow_units((uintptr_t)(X + tile0 * tile_floats), feat, list_cols, &g, &a.deal);
         const bool last = first + here == h->n_row_blocks;
         if (!last || !lists_and_heavy(feat_begin, feat_end, false))
-          with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, lds_bytes, stream, a); });
+          with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, wg_waves, lds_bytes, stream, a); });
         ++n_list_launches;
       }
       if (timers) timers->mark(stream, LaunchTimers::kLists, n_list_launches);
@@ -1122,7 +1147,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
       SharedLists shared;
       if (may_share)
         shared = shared_list_waves((int64_t)h->n_row_blocks * g.n_tiles, h->heavy_chunk0 / kChunksPerQuad * g.n_tiles,
-                                   h->longest_list, g.lg, lds_bytes / kHybWaves);
+                                   h->longest_list, g.lg, lds_bytes / wg_waves);
       const int waves = shared.waves;
       const int64_t heavy_at_once = kCuCount * waves_per_cu(g.lg);
       const int64_t heavy_quads = (h->heavy_list_chunks / kChunksPerQuad + 1) *
@@ -1142,11 +1167,11 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         if (waves > 1) {
           a.deal = deal_of(h->n_row_blocks, gs);
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) {
-            launch_shared_lists(v, gs, waves, lds_bytes / kHybWaves * waves, stream, a);
+            launch_shared_lists(v, gs, waves, lds_bytes / wg_waves * waves, stream, a);
           });
           if (timers) timers->list_waves = waves;
         } else {
-          with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, lds_bytes, stream, a); });
+          with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, wg_waves, lds_bytes, stream, a); });
         }
       }
     }
