@@ -60,7 +60,7 @@ constexpr int kMinLog2Block = 5, kMaxLog2Block = 9;
 constexpr int kYTileBytes = 64 * 1024;  // LDS for the rows of Y: two workgroups per CU; blocks of 2^kMaxLog2Block rows: twice that, one
 
 struct RgmsItem {
-  int32_t block;    // rows block << log2_block .. of Y
+  int32_t block;    // rows block * block_rows .. of Y
   int32_t tile0;
   int32_t n_tiles;
   int32_t part;     // -1: the whole block; otherwise number of this item among the items of divided blocks
@@ -73,7 +73,7 @@ struct RgmsTile {
   // that hold pieces of the same rows, place for place, are 1 << so many (their sums meet before the product, and `rows` has them once)
   uint32_t shape;
   int32_t n_steps;
-  uint16_t rows[kTileRows];  // of its pieces, in the block; 1 << log2_block: none
+  uint16_t rows[kTileRows];  // of its pieces, in the block; block_rows: none
 };
 constexpr int kTileWords = sizeof(RgmsTile) / 4;
 
@@ -86,7 +86,7 @@ struct RgmsArgs {
   float* Y;
   float* partial;           // ORDERED: sums of the items of divided blocks
   int32_t n_rows;
-  int32_t log2_block;
+  int32_t block_rows;
   int32_t d_out;
   int32_t width;            // columns of Y per workgroup, a multiple of 32
   int32_t n_waves;          // per workgroup
@@ -145,13 +145,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(TIN == 1 ?
   extern __shared__ __align__(16) double y_tile[];  // [rows + 1][width] (the last for pieces that are none), then ORDERED: turn[width / kPass]
   RgmsItem item = a.items[blockIdx.x / (unsigned)a.sharers];
   if (a.sharers > 1) {
-    const int part = (int)(blockIdx.x % (unsigned)a.sharers), n = item.n_tiles;
-    const int lo = (int)((int64_t)n * part / a.sharers);
-    item.n_tiles = (int)((int64_t)n * (part + 1) / a.sharers) - lo;
-    item.tile0 += lo;
+    const unsigned part = blockIdx.x % (unsigned)a.sharers, n = (unsigned)item.n_tiles;
+    const unsigned lo = n * part / (unsigned)a.sharers;
+    item.n_tiles = (int)(n * (part + 1) / (unsigned)a.sharers - lo);
+    item.tile0 += (int)lo;
     item.part = 0;  // (its sums are added to Y)
   }
-  const int rows = 1 << a.log2_block, width = a.width;
+  const int rows = a.block_rows, width = a.width;
   const int n0 = blockIdx.y * width;
   const int cols = min(width, a.d_out - n0);
   int* turn = reinterpret_cast<int*>(y_tile + (rows + 1) * width);
@@ -161,8 +161,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(TIN == 1 ?
 
   // The wavefront's tiles: a run of them, so that one W[r] serves many; where they take turns, every n_waves-th.
   const int stride = kInTurns ? n_waves : 1;
-  const int tile_lo = kInTurns ? wave : (int)((int64_t)item.n_tiles * wave / n_waves);
-  const int tile_hi = kInTurns ? item.n_tiles : (int)((int64_t)item.n_tiles * (wave + 1) / n_waves);
+  // (an item has at most 2^26 tiles, so 32 bits hold sixteen times as many; divisions of 64 bits are 150 instructions of a scalar unit each)
+  const unsigned n_tiles = (unsigned)item.n_tiles;
+  const int tile_lo = kInTurns ? wave : (int)(n_tiles * (unsigned)wave / (unsigned)n_waves);
+  const int tile_hi = kInTurns ? item.n_tiles : (int)(n_tiles * (unsigned)(wave + 1) / (unsigned)n_waves);
 
   // A tile's loads depend on each other (the tile, its entries, the rows those name), each a trip past L2, so they run
   // ahead by three tiles, two and one: what is issued while tile t is multiplied has arrived when t + 1 begins.
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(TIN == 1 ?
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     // ---- the block's rows
-    const int row0 = item.block << a.log2_block;
+    const int row0 = item.block * rows;
     const int rows_here = min(rows, a.n_rows - row0);
     const int quads = cols / 4;
     const int n_quads = rows_here * quads;
@@ -492,14 +494,14 @@ __global__ __launch_bounds__(256) void k_fill_zero(float* p, int64_t n) {
 // The rows of a divided block: cleared before its items add to them, or, with a workspace, the sum of its items' parts
 // in their order.  divided[b] = {block, first part, parts}.
 __global__ __launch_bounds__(256) void k_rgms_divided(const int4* __restrict__ divided, int32_t n_rows,
-                                                      int32_t log2_block, int32_t d_out,
+                                                      int32_t block_rows, int32_t d_out,
                                                       const float* __restrict__ partial, float* Y) {
   const int4 d = divided[blockIdx.x];
-  const int row0 = d.x << log2_block, rows = min(1 << log2_block, n_rows - row0);
-  for (int i = threadIdx.x; i < rows * d_out; i += blockDim.x) {
+  const int row0 = d.x * block_rows, rows = min(block_rows, n_rows - row0);
+  for (int i = blockIdx.y * blockDim.x + threadIdx.x; i < rows * d_out; i += gridDim.y * blockDim.x) {
     float sum = 0.f;
     if (partial)
-      for (int p = 0; p < d.z; ++p) sum += partial[(((size_t)(d.y + p)) << log2_block) * d_out + i];
+      for (int p = 0; p < d.z; ++p) sum += partial[(size_t)(d.y + p) * block_rows * d_out + i];
     Y[(size_t)row0 * d_out + i] = sum;
   }
 }
@@ -509,7 +511,7 @@ __global__ __launch_bounds__(256) void k_rgms_divided(const int4* __restrict__ d
 struct CellArgs {
   const int32_t* indptr;
   int64_t n_cells;
-  int32_t n_rel, n_rows, log2_block, k;
+  int32_t n_rel, n_rows, block_rows, k;
 };
 constexpr int kCountSlots = 64, kCountStride = 8;
 
@@ -566,8 +568,8 @@ __global__ __launch_bounds__(256) void k_cell_tiles(CellArgs a, int32_t* cell_ti
   const int64_t cell = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (cell >= a.n_cells) return;
   const int64_t block = cell / a.n_rel, rel = cell - block * a.n_rel;
-  const int64_t row0 = block << a.log2_block;
-  const int rows = (int)min((int64_t)1 << a.log2_block, (int64_t)a.n_rows - row0);
+  const int64_t row0 = block * a.block_rows;
+  const int rows = (int)min((int64_t)a.block_rows, (int64_t)a.n_rows - row0);
   const int32_t* ptr = a.indptr + rel * a.n_rows + row0;
   int pairs = 0, pads = 0;
   const CellShape c = cell_shape(ptr, rows, lane, [&](int len) {
@@ -608,8 +610,8 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
   const int64_t cell = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (cell >= a.n_cells) return;
   const int64_t block = cell / a.n_rel, rel = cell - block * a.n_rel;
-  const int64_t row0 = block << a.log2_block;
-  const int rows = (int)min((int64_t)1 << a.log2_block, (int64_t)a.n_rows - row0);
+  const int64_t row0 = block * a.block_rows;
+  const int rows = (int)min((int64_t)a.block_rows, (int64_t)a.n_rows - row0);
   const int32_t* ptr = a.indptr + rel * a.n_rows + row0;
   if (ptr[rows] == ptr[0]) return;
   // the rows with entries, so that the lanes below have one each
@@ -662,7 +664,7 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
     to->n_steps = steps;
     const int n_rows_of = min(kTileRows >> joined, n_pieces - kTileRows * t);
     for (int i = 0; i < kTileRows; ++i)
-      if (i >= n_rows_of) to->rows[i] = (uint16_t)(1 << a.log2_block);
+      if (i >= n_rows_of) to->rows[i] = (uint16_t)a.block_rows;
   }
 
   // piece number `place`: `len` entries from `from` on, of row `row`, which is number `slot` of its tile's rows (negative: another piece says so)
@@ -776,6 +778,16 @@ int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) 
   return large ? kMaxLog2Block : s;
 }
 
+// Where that leaves one block for most CUs, but not for all, as many rows as give every one of the 256 a block: 60 drawn graphs and feature
+// sizes of 192 to 255 blocks or near it, with the launches below 1.023 times as fast (0.96 to 1.23); 27,163 rows, 46 relations, 64 x 64, 213 blocks of 128
+// rows 28.8 us, 256 of 107 28.1.  Fewer than 192 lose what their tiles hold (a quarter and more); blocks of 32 rows have few pieces as it is.
+// (Nor elsewhere: 1.9 M rows, 3682 blocks of 512 rows 341 us, 3840 of 491, whole turns of the CUs, 351.)
+int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
+  const int s = log2_block_rows(n_rows, n_rel, nnz, workspace);
+  const int64_t blocks = (n_rows + ((int64_t)1 << s) - 1) >> s;
+  return blocks >= 192 && blocks < 256 && s > kMinLog2Block ? (int32_t)((n_rows + 255) / 256) : 1 << s;
+}
+
 template <int TIN, bool ORDERED, bool WIDE_X>
 void launch_rgms(dim3 grid, dim3 block, size_t lds, hipStream_t stream, const RgmsArgs& a) {
   auto* kernel = &k_rgms<TIN, ORDERED, WIDE_X>;
@@ -791,7 +803,7 @@ void launch_rgms(dim3 grid, dim3 block, size_t lds, hipStream_t stream, const Rg
 struct sptir_rgms_handle {
   int32_t n_rel, n_rows, n_cols, k;
   int64_t nnz, n_pairs, n_pads;
-  int32_t log2_block;
+  int32_t block_rows;
   int64_t n_tiles;
   sptir::RgmsTile* tiles;
   int2* entries;          // [n_steps][4]
@@ -822,7 +834,7 @@ extern "C" sptir_status_t sptir_rgms_info(const sptir_rgms_t* p, sptir_rgms_info
   sptir_rgms_info_t o;
   o.n_relations = p->n_rel; o.n_rows = p->n_rows; o.n_cols = p->n_cols; o.max_bucket_log2 = p->k;
   o.nnz = p->nnz; o.n_stacked_rows_stored = p->n_pairs; o.n_pad_slots = p->n_pads;
-  o.n_tiles = p->n_tiles; o.workspace_d_out = p->workspace_d_out; o.row_block = 1 << p->log2_block;
+  o.n_tiles = p->n_tiles; o.workspace_d_out = p->workspace_d_out; o.row_block = p->block_rows;
   o.device_bytes = (int64_t)p->device_bytes;
   *out = o;
   return SPTIR_OK;
@@ -848,11 +860,11 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
   current_allocator(&p->alloc, &p->free_, &p->alloc_ctx);
   p->n_rel = n_relations; p->n_rows = stacked->n_rows / n_relations; p->n_cols = stacked->n_cols; p->k = k;
   p->nnz = nnz; p->workspace_d_out = workspace_d_out;
-  p->log2_block = log2_block_rows(p->n_rows, n_relations, nnz, workspace_d_out > 0);
-  const int32_t n_blocks = (int32_t)(((int64_t)p->n_rows + (1 << p->log2_block) - 1) >> p->log2_block);
+  p->block_rows = rows_of_a_block(p->n_rows, n_relations, nnz, workspace_d_out > 0);
+  const int32_t n_blocks = (int32_t)(((int64_t)p->n_rows + p->block_rows - 1) / p->block_rows);
   CellArgs ca;
   ca.indptr = stacked->indptr; ca.n_cells = (int64_t)n_blocks * n_relations; ca.n_rel = n_relations;
-  ca.n_rows = p->n_rows; ca.log2_block = p->log2_block; ca.k = k;
+  ca.n_rows = p->n_rows; ca.block_rows = p->block_rows; ca.k = k;
   const int64_t cell_wgs = (ca.n_cells + 3) / 4;
   const int64_t n_seq = (int64_t)(scan_room(std::max<int64_t>(ca.n_cells, 1)) / kScanSeq);
 
@@ -965,7 +977,7 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
     const size_t o_entries = reserve(&bytes, sizeof(int2) * 4 * (size_t)n_steps);
     const size_t o_items = reserve(&bytes, sizeof(RgmsItem) * items.size());
     const size_t o_divided = reserve(&bytes, sizeof(int4) * divided.size());
-    const size_t o_partial = reserve(&bytes, sizeof(float) * (((size_t)p->n_parts * workspace_d_out) << p->log2_block));
+    const size_t o_partial = reserve(&bytes, sizeof(float) * ((size_t)p->n_parts * workspace_d_out * p->block_rows));
     bytes = std::max<size_t>(bytes, 256);
     p->blob = p->alloc(bytes, p->alloc_ctx, stream);
     if (!p->blob) { st = SPTIR_ERR_ALLOC; goto fail; }
@@ -1011,9 +1023,9 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   RgmsArgs a;
   a.items = p->items; a.tiles = p->tiles; a.entries = p->entries;
   a.X = X; a.W = W; a.Y = Y; a.partial = p->partial;
-  a.n_rows = p->n_rows; a.log2_block = p->log2_block; a.d_out = d_out;
-  const bool large_block = p->log2_block == kMaxLog2Block;
-  a.width = std::min<int32_t>(d_out, ((large_block ? 2 : 1) * kYTileBytes / 8 >> p->log2_block) / 32 * 32);
+  a.n_rows = p->n_rows; a.block_rows = p->block_rows; a.d_out = d_out;
+  const bool large_block = p->block_rows > 1 << (kMaxLog2Block - 1);
+  a.width = std::min<int32_t>(d_out, (large_block ? 2 : 1) * kYTileBytes / 8 / p->block_rows / 32 * 32);
   const int64_t chunks = (d_out + a.width - 1) / a.width;
   if (chunks > 65535) return SPTIR_ERR_OVERFLOW;
   const bool ordered = d_out <= p->workspace_d_out;
@@ -1028,7 +1040,7 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   const int64_t whole = (int64_t)p->n_items * chunks;
   const bool large_w = d_in * d_out >= 64 * 128;
   const int64_t tiles_each = p->n_tiles / std::max<int64_t>(p->n_items, 1), w_each = tiles_each * d_in * d_out;
-  const bool undivided = ((int64_t)p->n_rows - 1) >> p->log2_block >= 159 && !large_block;
+  const bool undivided = ((int64_t)p->n_rows - 1) / p->block_rows >= 159 && !large_block;
   a.sharers = 1;
   if (!ordered && large_w && undivided && whole < 512) {
     const double alone = 0.12e-3 * (double)w_each, y = 1e-6 * (double)p->n_rows * d_out;
@@ -1041,12 +1053,12 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs
   // and feature sizes: against 8 everywhere it is alike in the mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)
   a.n_waves = large_block ? 16 : large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= 24 ? 8 : 4;
-  const size_t lds = sizeof(double) * (size_t)a.width * (((size_t)1 << p->log2_block) + 1) + (ordered ? sizeof(int) * (a.width / 16) : 0);
+  const size_t lds = sizeof(double) * (size_t)a.width * ((size_t)p->block_rows + 1) + (ordered ? sizeof(int) * (a.width / 16) : 0);
   const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);
   auto divided = [&](const float* partial) {
     if (p->n_divided > 0)
-      hipLaunchKernelGGL(k_rgms_divided, dim3((unsigned)p->n_divided), dim3(256), 0, stream, p->divided, p->n_rows,
-                         p->log2_block, d_out, partial, Y);
+      hipLaunchKernelGGL(k_rgms_divided, dim3((unsigned)p->n_divided, 16), dim3(256), 0, stream, p->divided, p->n_rows,
+                         p->block_rows, d_out, partial, Y);
   };
   if (a.sharers > 1) {
     const int64_t n = (int64_t)p->n_rows * d_out;

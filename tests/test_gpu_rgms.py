@@ -338,6 +338,28 @@ def test_rgms_fewer_blocks_of_512_rows(gpu_lib, blocks, mean, rows):
     assert_y_close(Y, Yr, Sr, f"{blocks} blocks")
 
 
+@pytest.mark.parametrize("workspace", [0, 64])
+@pytest.mark.parametrize("n,mean,rows", [(128 * 191, 0.4, 128), (128 * 192, 0.4, 96), (128 * 213 - 37, 0.4, 107), (128 * 254 + 1, 0.4, 128),
+                                         (64 * 200 + 5, 0.9, 51), (256 * 230, 0.22, 230)])
+def test_rgms_a_block_for_every_cu(gpu_lib, n, mean, rows, workspace):
+    """Where blocks of a power of two rows are fewer than the CUs, but not by much, there is one for every CU, of any number of rows; the
+    last has part of its rows, and some none."""
+    say(f"[rgms one turn] {n} rows workspace={workspace}")
+    if workspace:
+        mean /= 2                                               # (16 entries of a relation fill a block's part)
+    n_rel, d_in, d_out = 3, 64, 64
+    rng = np.random.default_rng(n)
+    w = workloads.random_csr(n_rel * n, n, rng.poisson(mean, n_rel * n), 1, 1)
+    X = rng.standard_normal((n, d_in)).astype(np.float32)
+    W = rng.standard_normal((n_rel, d_in, d_out)).astype(np.float32)
+    w = workloads.HeteroWorkload("one turn", n, n_rel, w.indptr, w.indices, w.values, X, W)
+    (Y, again), info = run_rgms(gpu_lib, w, workspace_d_out=workspace, repeat=2)
+    assert info["row_block"] == rows
+    Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, w.X, w.W)
+    assert_y_close(Y, Yr, Sr, f"{n} rows")
+    assert workspace == 0 or np.array_equal(Y, again)
+
+
 @pytest.mark.parametrize("workspace", [0, 288])
 @pytest.mark.parametrize("d_in,d_out", [(32, 32), (32, 256), (64, 288), (128, 160)])
 def test_rgms_long_pairs(gpu_lib, d_in, d_out, workspace):
