@@ -778,14 +778,19 @@ int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) 
   return large ? kMaxLog2Block : s;
 }
 
-// Where that leaves one block for most CUs, but not for all, as many rows as give every one of the 256 a block: 60 drawn graphs and feature
-// sizes of 192 to 255 blocks or near it, with the launches below 1.023 times as fast (0.96 to 1.23); 27,163 rows, 46 relations, 64 x 64, 213 blocks of 128
-// rows 28.8 us, 256 of 107 28.1.  Fewer than 192 lose what their tiles hold (a quarter and more); blocks of 32 rows have few pieces as it is.
-// (Nor elsewhere: 1.9 M rows, 3682 blocks of 512 rows 341 us, 3840 of 491, whole turns of the CUs, 351.)
+// Where that is a few blocks for every CU, as many rows as make it whole turns of the 256: 192 to 255 blocks give one, and so, without a workspace and
+// for up to 128 rows, up to 1300 the nearest.  60 drawn graphs and feature sizes of 257 to 340 blocks and up: 256 instead of 257 to 320 1.04 to 1.45 times
+// as fast, 512 instead of 385 to 522 0.98 to 1.19, 768 instead of 624 to 944 1.07 in the mean (0.89 to 1.19), 1024 instead of 1179 to 1233 1.03 and
+// 1.18, beyond 0.94 to 1.06.  Below 192 blocks tiles lose a quarter of what they hold and more; blocks of 256 rows cannot grow, and 512 instead of
+// 316 to 477 of those are 0.94 to 1.20 times as fast; 1.9 M rows, 3682 blocks of 512 rows 341 us, 3840 of 491 351.
+// 27,163 rows, 46 relations, 64 x 64, 213 blocks of 128 rows 28.8 us, 256 of 107 28.1.
 int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
   const int s = log2_block_rows(n_rows, n_rel, nnz, workspace);
   const int64_t blocks = (n_rows + ((int64_t)1 << s) - 1) >> s;
-  return blocks >= 192 && blocks < 256 && s > kMinLog2Block ? (int32_t)((n_rows + 255) / 256) : 1 << s;
+  const bool any = !workspace && s < kMaxLog2Block - 1 && blocks >= 192 && blocks <= 1300;
+  const int64_t turns = blocks < 256 ? (blocks >= 192 && s > kMinLog2Block) : !any ? 0 : blocks <= 340 ? 1 : blocks <= 576 ? 2 : blocks <= 960 ? 3 : 4;
+  const int32_t rows = turns > 0 ? (int32_t)((n_rows + 256 * turns - 1) / (256 * turns)) : 1 << s;
+  return rows > 128 && 1 << s == 128 && turns > 2 ? 128 : rows;  // (64 columns of Y fit beside 128 rows, 32 beside more)
 }
 
 template <int TIN, bool ORDERED, bool WIDE_X>

@@ -340,11 +340,14 @@ def test_rgms_fewer_blocks_of_512_rows(gpu_lib, blocks, mean, rows):
 
 @pytest.mark.parametrize("workspace", [0, 64])
 @pytest.mark.parametrize("n,mean,rows", [(128 * 191, 0.4, 128), (128 * 192, 0.4, 96), (128 * 213 - 37, 0.4, 107), (128 * 254 + 1, 0.4, 128),
-                                         (64 * 200 + 5, 0.9, 51), (256 * 230, 0.22, 230)])
-def test_rgms_a_block_for_every_cu(gpu_lib, n, mean, rows, workspace):
-    """Where blocks of a power of two rows are fewer than the CUs, but not by much, there is one for every CU, of any number of rows; the
-    last has part of its rows, and some none."""
-    say(f"[rgms one turn] {n} rows workspace={workspace}")
+                                         (64 * 200 + 5, 0.9, 51), (256 * 230, 0.22, 230), (128 * 300 + 7, 0.4, (151, 128)),
+                                         (64 * 400, 0.9, (50, 64)), (32 * 900 + 3, 1.5, (38, 32)), (128 * 800, 0.4, 128),
+                                         (128 * 700 - 1, 0.4, (117, 128)), (64 * 1200 + 1, 0.9, (76, 64)), (64 * 1301, 0.9, 64)])
+def test_rgms_whole_turns_of_blocks(gpu_lib, n, mean, rows, workspace):
+    """Where blocks of a power of two rows are a few for every CU, there are as many as make whole turns of the CUs, of any number of rows
+    (with a workspace, one turn); the last has part of its rows, or some have none."""
+    rows = rows if isinstance(rows, int) else rows[workspace > 0]
+    say(f"[rgms whole turns] {n} rows workspace={workspace}")
     if workspace:
         mean /= 2                                               # (16 entries of a relation fill a block's part)
     n_rel, d_in, d_out = 3, 64, 64
@@ -352,7 +355,7 @@ def test_rgms_a_block_for_every_cu(gpu_lib, n, mean, rows, workspace):
     w = workloads.random_csr(n_rel * n, n, rng.poisson(mean, n_rel * n), 1, 1)
     X = rng.standard_normal((n, d_in)).astype(np.float32)
     W = rng.standard_normal((n_rel, d_in, d_out)).astype(np.float32)
-    w = workloads.HeteroWorkload("one turn", n, n_rel, w.indptr, w.indices, w.values, X, W)
+    w = workloads.HeteroWorkload("whole turns", n, n_rel, w.indptr, w.indices, w.values, X, W)
     (Y, again), info = run_rgms(gpu_lib, w, workspace_d_out=workspace, repeat=2)
     assert info["row_block"] == rows
     Yr, Sr = oracle.rgms(n_rel, n, w.indptr, w.indices, w.values, w.X, w.W)
