@@ -922,7 +922,7 @@ __device__ __forceinline__ void row_slot_fill_workgroup(const RowSlotArgs& a, un
 // workgroup takes `per_wg` consecutive entries, whatever rows they belong to, so that the longest row costs no more than
 // its share; it walks them by blocks of 2^log2_rows rows.  What is the same for all entries of a piece (where it goes) is
 // put into LDS first, then a lane per entry finds its row by a search over the rows' starts and its partition from its
-// column.  169,343 rows, 1.17 M entries in four partitions: 27 us alone, of which 18 are the chain of loads up to the pieces
+// column.  169,343 rows, 1.17 M entries in four partitions: 29 us with what goes along, most of it the chain of loads up to the pieces
 // (three kernels with a wavefront per 64 pieces took 78 us, most of it in a few wavefronts with long pieces).
 struct CopyArgs {
   const int32_t *indptr, *indices;
@@ -946,10 +946,12 @@ constexpr int kCopyPieces = 1024;  // most pieces a workgroup holds at a time
 constexpr int kCopyWords = 6;      // LDS words per piece
 constexpr int kCopyLog2Rows = 7;   // at most 128 rows a block
 
-// What goes with the copy, in workgroups before its own: the ends of the lists, the partial-sum rows, the order of the row blocks
+// What goes with the copy, in workgroups after its own: the ends of the lists, the partial-sum rows, the order of the row blocks.  (They take a
+// third of the time that one of the copy's does, so they fill what those leave.  169,343 rows, 1.17 M entries: before them 33 us, after them 29, with the
+// entries asked for before it is known where they go and no pieces looked up that have none of a workgroup's entries.)
 struct CopyCompany {
   unsigned n_ends, n_slots, n_sort;  // workgroups of each
-  unsigned first;                    // the copy's first, a multiple of 8
+  unsigned n_copy;                   // the copy's
   int64_t n_parts;
   const int32_t* queue_len;
   int64_t* rb_chunk_ptr;
@@ -963,8 +965,8 @@ template <bool MAY_CUT>
 __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, StreamShape ss, CopyArgs a, int pieces_at_a_time,
                                               CopyCompany with) {
   extern __shared__ int lds[];
-  if (blockIdx.x < with.first) {
-    unsigned wg = blockIdx.x;
+  if (blockIdx.x >= with.n_copy) {
+    unsigned wg = blockIdx.x - with.n_copy;
     if (wg < with.n_slots) return row_slot_fill_workgroup(with.slots, wg);
     wg -= with.n_slots;
     if (wg < with.n_ends)
@@ -975,7 +977,7 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
       sort_scatter_workgroup(with.sort.in, with.sort.n_rb, with.sort.tiles, 0, wg, with.sort.hist, nullptr, with.sort.order);
     return;
   }
-  const unsigned copy_wg = blockIdx.x - with.first, n_copy = gridDim.x - with.first;
+  const unsigned copy_wg = blockIdx.x, n_copy = with.n_copy;
   __shared__ int row_lo[(1 << kCopyLog2Rows) + 1];
   const int log2_rows = a.log2_rows, n_rows_here = 1 << log2_rows;
   int* piece_lo = lds;                                                 // first entry in the input
@@ -1054,6 +1056,20 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
   if (full != 0 && (int)(copy_wg & 7) >= full) work -= (int)(copy_wg & 7) - full;
   const int64_t first = work * a.per_wg;
   const int64_t last = first + a.per_wg < a.nnz ? first + a.per_wg : a.nnz;
+  // A workgroup's first entries are on their way while it finds out where they go.
+  constexpr int kUnroll = 4;
+  int32_t col[kUnroll];
+  float val[kUnroll];
+  auto fetch = [&](unsigned e0) {
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const unsigned e = e0 + u * 256 + tid;
+      col[u] = 0; val[u] = 0.f;
+      if (e < (unsigned)last) { col[u] = a.indices[e]; val[u] = a.values[e]; }
+    }
+  };
+  unsigned held = (unsigned)first;  // the entries that col and val hold: from here on
+  fetch(held);
   for (int64_t at = first; at < last;) {
     r0 = row_of_entry(a.indptr, s.n_rows, at, tid & 63);
     __syncthreads();  // (the last block's rows are no longer read)
@@ -1067,7 +1083,7 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
       if (p0 > 0) __syncthreads();  // (the pieces of the last turn are no longer read)
       for (int i = tid; i < np << log2_rows; i += 256) {
         const int p = p0 + (i >> log2_rows), rl = i & (n_rows_here - 1);
-        if (rl >= s.n_rows - r0) { piece_len[i] = 0; continue; }
+        if (rl >= s.n_rows - r0 || (unsigned)row_lo[rl] >= e_end) { piece_len[i] = 0; continue; }  // (none of its entries is here)
         const int r = r0 + rl;
         // (everything that the row alone decides is on its way before the piece's position is needed)
         const int32_t q = a.piece_of[(int64_t)p * s.n_rows + r];
@@ -1102,20 +1118,12 @@ __global__ __launch_bounds__(256) void k_copy(BuildShape s, CellShape cs, Stream
         }
       }
       __syncthreads();
-      constexpr int kUnroll = 4;
-      for (unsigned e0 = e_begin; e0 < e_end; e0 += 256 * kUnroll) {
-        int32_t col[kUnroll];
-        float val[kUnroll];
+      for (unsigned e0 = (unsigned)first + (e_begin - (unsigned)first) / (256 * kUnroll) * (256 * kUnroll); e0 < e_end; e0 += 256 * kUnroll) {
+        if (e0 != held) { held = e0; fetch(e0); }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
           const unsigned e = e0 + u * 256 + tid;
-          col[u] = 0; val[u] = 0.f;
-          if (e < e_end) { col[u] = a.indices[e]; val[u] = a.values[e]; }
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const unsigned e = e0 + u * 256 + tid;
-          if (e >= e_end) continue;
+          if (e < e_begin || e >= e_end) continue;
           int rl = 0;  // the last row that starts at or before e
           for (int step = n_rows_here >> 1; step > 0; step >>= 1)
             if ((unsigned)row_lo[rl + step] <= e) rl += step;
@@ -1880,11 +1888,12 @@ sptir_status_t sptir::hyb_build_impl(const sptir_csr_t* csr, int32_t n_col_parts
       const int64_t n_wg = std::max<int64_t>(1, (csr->nnz + a.per_wg - 1) / a.per_wg);
       CopyCompany with;
       with.n_slots = slot_wgs; with.n_ends = (unsigned)((n_parts + 3) / 4); with.n_sort = sort_wgs;
-      with.first = (with.n_slots + with.n_ends + with.n_sort + 7) / 8 * 8;
+      with.n_copy = (unsigned)n_wg;
+      const int64_t n_company = (int64_t)with.n_slots + with.n_ends + with.n_sort;
       with.n_parts = n_parts; with.queue_len = d_queue_len; with.rb_chunk_ptr = h->rb_chunk_ptr; with.n_chunks = n_chunks;
       with.slots = slots; with.sort = sort;
-      if (n_wg + with.first > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
-      hipLaunchKernelGGL(cs.cut_queues ? k_copy<true> : k_copy<false>, dim3((unsigned)n_wg + with.first), dim3(256),
+      if (n_wg + n_company > 0x7FFFFFFF) { st = SPTIR_ERR_OVERFLOW; goto fail; }
+      hipLaunchKernelGGL(cs.cut_queues ? k_copy<true> : k_copy<false>, dim3((unsigned)(n_wg + n_company)), dim3(256),
                          sizeof(int) * kCopyWords * (size_t)pieces, stream, s, cs, ss, a, pieces, with);
     }
     BUILD_HIP(hipGetLastError());
