@@ -5,7 +5,7 @@
 // one kernel, so that T[r] = X W[r] never exists in memory.
 //
 // Here the kernel is stationary in Y instead of in r.  A arrives as one CSR
-// over stacked rows r*n + i.  Rows of Y are cut into blocks of 2^s; a
+// over stacked rows r*n + i.  Rows of Y are cut into blocks; a
 // workgroup owns a block, keeps its rows of Y in LDS, walks the block's pairs
 // (r, i) relation after relation and writes Y once.  The scatter of the
 // relation-stationary order (a float atomic per element of every pair's product
@@ -29,8 +29,8 @@
 // rows that it has not got, and the gather is two instructions a step.  What counts beside that: a tile's loads depend on each other and are
 // waited for one tile later, so whatever makes the compiler wait for the newest load (a copy of a register that is being loaded, a
 // count of loads that depends on a branch) costs a trip past L2 a tile; and wavefronts (32 x 32 features, 94 K rows, 51 relations, 4.76 M
-// entries: six per SIMD 1.12 times as fast as five).  That graph 161 -> 107 us, 1.9 M rows, 96 relations, 5.7 M entries
-// 439 -> 342; 27,163 rows, 46 relations, 148,100 entries, 64 x 64: 39 -> 30.  130 drawn graphs and feature sizes, 1.3 to 40 entries a pair: 1.21 times as fast up
+// entries: six per SIMD 1.12 times as fast as five).  That graph 161 -> 107 us (99 with the longest blocks first),
+// 1.9 M rows, 96 relations, 5.7 M entries 439 -> 342; 27,163 rows, 46 relations, 148,100 entries, 64 x 64: 39 -> 30 (27 with a block for every CU).  130 drawn graphs and feature sizes, 1.3 to 40 entries a pair: 1.21 times as fast up
 // to 128 columns of Y (0.97 to 1.85), 1.06 for 256 and 512 (0.88 to 1.31: 16 entries a pair, for which W[r] is read twice as often).
 // Blocks are as large as gives (relation, block) enough pieces, and small enough that there are workgroups
 // for all CUs; a block with far more tiles than the others is several work items, whose sums meet in Y by global atomics.
