@@ -937,10 +937,10 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
     p->n_tiles = n_blocks > 0 ? block_tile[n_blocks] : 0;
     const int64_t n_steps = n_blocks > 0 ? block_step[n_blocks] : 0;  // (at most nnz: a step has an entry)
 
-    // ---- work items: a block each.  A block far beyond the mean is divided, which costs a launch of 5 us that clears its rows of Y, and atomics: of more
-    //      than twice the mean work, or four times it from 1024 blocks on, which the longest begin first and leave no CU waiting (1.9 M rows, 3682
-    //      blocks 341 -> 336 us; 100 drawn graphs, those of 1024 blocks and more 0.98 to 1.03 times as fast; fewer blocks, at twice the mean
-    //      and 32, or three times it, 0.86 to 1.10, mean 0.99).
+    // ---- work items: a block each.  A block of more than twice the mean work is divided: 1775 drawn graphs and feature sizes of 30,000 to
+    //      700,000 rows by popularity, without a workspace: at 1.6 times the mean 0.98 times as fast (0.75 to 1.26), at three times
+    //      0.98 (0.67 to 1.55), at four 0.96 (0.53 to 1.58).  (564 with a workspace, which a divided block passes through: at three
+    //      times 1.06 (0.75 to 1.51), at four 1.09, but 0.67 at worst.)
     //      Where there are few blocks, all are, into about 384 items: three for two CUs, so that some with less to do fill the gaps
     //      that others leave.  1169 drawn graphs of 1,500 to 18,000 rows, against 512 items: 1.07 times as fast (0.92 to 1.39); 256
     //      1.01 (0.55 to 1.83), 768 0.96, 1024 0.92.
@@ -948,7 +948,7 @@ extern "C" sptir_status_t sptir_rgms_build(const sptir_csr_t* stacked, int32_t n
     auto cost_of = [&](int32_t b) { return (int64_t)tiles_of(b) + (block_step[b + 1] - block_step[b]) / 8; };
     const int64_t cost = p->n_tiles + n_steps / 8, mean = n_blocks > 0 ? cost / n_blocks : 0;
     // (an item's tiles lie within 4 GB)
-    const int64_t most = std::min<int64_t>(n_blocks >= 160 ? std::max<int64_t>(64, (n_blocks >= 1024 ? 4 : 2) * mean) : std::max<int64_t>(8, cost / 384), 1 << 26);
+    const int64_t most = std::min<int64_t>(n_blocks >= 160 ? std::max<int64_t>(64, 2 * mean) : std::max<int64_t>(8, cost / 384), 1 << 26);
     items.reserve((size_t)n_blocks + 16);
     for (int32_t b = 0; b < n_blocks; ++b) {  // divided blocks first: theirs are the longest items
       const int64_t c = cost_of(b);
