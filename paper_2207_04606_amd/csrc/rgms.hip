@@ -46,6 +46,7 @@
 #include <utility>
 #include <vector>
 
+#include "rgms_blocks.h"
 #include "sptir_internal.h"
 #include "sptir_scan.h"
 #include "sptir_tiles.h"
@@ -56,8 +57,6 @@ namespace {
 constexpr int kTileRows = 16;      // pieces per tile
 constexpr int kPieceEntries = 4;   // most entries per piece: a tile has 16 steps at most, 64 entries, a lane each
 constexpr int kPad = -1;           // the column of a place without an entry: past the end of X, where a buffer load gives 0
-constexpr int kMinLog2Block = 5, kMaxLog2Block = 9;
-constexpr int kYTileBytes = 64 * 1024;  // LDS for the rows of Y: two workgroups per CU; blocks of 2^kMaxLog2Block rows: twice that, one
 
 struct RgmsItem {
   int32_t block;    // rows block * block_rows .. of Y
@@ -754,45 +753,6 @@ __global__ __launch_bounds__(256) void k_fill_tiles(CellArgs a, const int32_t* _
   }
 }
 
-// Rows per block: 32 entries for every (relation, block), so that tiles fill, as long as that leaves 160 blocks, about what keeps
-// 256 CUs busy with 16 wavefronts each.  557 pairs of blocks of 32 to 256 rows, the larger against the smaller: with 16 to 24 entries in the
-// smaller 1.05 times as fast, with 24 to 32 1.01, with 32 to 48 1.01, with 48 to 64 0.98 (0.74 to 1.45: what decides is whether the last
-// turn of workgroups is nearly empty).  16 entries with a workspace: a tile's turn comes sooner where a block has fewer of them.  553 pairs: with
-// less than 16 entries in the smaller 0.97, with 16 to 32 0.94 (0.58 to 1.47), with 32 to 64 0.90.
-// Fewer, larger blocks divided into items lose more in global atomics than fuller tiles gain (27,163 rows, 64 x 64: blocks of 256 rows 83 us,
-// of 128 30).
-// Blocks of 512 rows take the LDS of a CU and 16 wavefronts; what they win is W[r] read for half as many tiles, if that is for few entries, and
-// twice as many pieces to fill a tile with.  Against 256 rows, without a workspace, 142 graphs and feature sizes of 160 blocks of 512 and more: up
-// to 24 entries for every (relation, block) 1.15 times as fast (0.90 to 1.39), however many the blocks; up to 40 entries 1.04 from 384 blocks on
-// (0.97 to 1.22), where the last turn of workgroups weighs less, 1.01 below (0.88 to 1.24); up to 64 1.03 (0.88 to 1.34), beyond 1.01 (0.93 to
-// 1.27), some of it lost to CUs without work.  Below 160 blocks, where all are divided, 0.39.  117,840 rows, 74 relations,
-// 900 K entries, 64 x 64: 131 -> 114 us; 1.9 M rows, 96 relations, 5.7 M entries, 32 x 32, 16 entries: 394 -> 344.  With a workspace tiles take
-// turns, and larger blocks lose sooner.
-int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
-  int s = kMinLog2Block;
-  const int64_t enough = workspace ? 16 : 32;
-  while (((int64_t)1 << s) * nnz < enough * n_rows * n_rel && s < kMaxLog2Block - 1 && (n_rows >> (s + 1)) >= 160) ++s;
-  const int64_t entries = nnz << kMaxLog2Block, blocks = n_rows >> kMaxLog2Block;
-  const bool large = s == kMaxLog2Block - 1 && !workspace &&
-                     ((blocks >= 160 && entries < 24 * n_rows * n_rel) || (blocks >= 384 && entries < 40 * n_rows * n_rel));
-  return large ? kMaxLog2Block : s;
-}
-
-// Where that is a few blocks for every CU, as many rows as make it whole turns of the 256: 192 to 255 blocks give one, and so, without a workspace and
-// for up to 128 rows, up to 1300 the nearest.  60 drawn graphs and feature sizes of 257 to 340 blocks and up: 256 instead of 257 to 320 1.04 to 1.45 times
-// as fast, 512 instead of 385 to 522 0.98 to 1.19, 768 instead of 624 to 944 1.07 in the mean (0.89 to 1.19), 1024 instead of 1179 to 1233 1.03 and
-// 1.18, beyond 0.94 to 1.06.  Below 192 blocks tiles lose a quarter of what they hold and more; blocks of 256 rows cannot grow, and 512 instead of
-// 316 to 477 of those are 0.94 to 1.20 times as fast; 1.9 M rows, 3682 blocks of 512 rows 341 us, 3840 of 491 351.
-// 27,163 rows, 46 relations, 64 x 64, 213 blocks of 128 rows 28.8 us, 256 of 107 28.1.
-int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
-  const int s = log2_block_rows(n_rows, n_rel, nnz, workspace);
-  const int64_t blocks = (n_rows + ((int64_t)1 << s) - 1) >> s;
-  const bool any = !workspace && s < kMaxLog2Block - 1 && blocks >= 192 && blocks <= 1300;
-  const int64_t turns = blocks < 256 ? (blocks >= 192 && s > kMinLog2Block) : !any ? 0 : blocks <= 340 ? 1 : blocks <= 576 ? 2 : blocks <= 960 ? 3 : 4;
-  const int32_t rows = turns > 0 ? (int32_t)((n_rows + 256 * turns - 1) / (256 * turns)) : 1 << s;
-  return rows > 128 && 1 << s == 128 && turns > 2 ? 128 : rows;  // (64 columns of Y fit beside 128 rows, 32 beside more)
-}
-
 template <int TIN, bool ORDERED, bool WIDE_X>
 void launch_rgms(dim3 grid, dim3 block, size_t lds, hipStream_t stream, const RgmsArgs& a) {
   auto* kernel = &k_rgms<TIN, ORDERED, WIDE_X>;
@@ -1029,8 +989,8 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
   a.items = p->items; a.tiles = p->tiles; a.entries = p->entries;
   a.X = X; a.W = W; a.Y = Y; a.partial = p->partial;
   a.n_rows = p->n_rows; a.block_rows = p->block_rows; a.d_out = d_out;
-  const bool large_block = p->block_rows > 1 << (kMaxLog2Block - 1);
-  a.width = std::min<int32_t>(d_out, (large_block ? 2 : 1) * kYTileBytes / 8 / p->block_rows / 32 * 32);
+  const bool large_block = is_large_block(p->block_rows);
+  a.width = std::min<int32_t>(d_out, columns_beside(p->block_rows));
   const int64_t chunks = (d_out + a.width - 1) / a.width;
   if (chunks > 65535) return SPTIR_ERR_OVERFLOW;
   const bool ordered = d_out <= p->workspace_d_out;
