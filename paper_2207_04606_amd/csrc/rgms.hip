@@ -1015,11 +1015,7 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
       if (shared < least) { least = shared; a.sharers = n; }
     }
   }
-  // wavefronts per workgroup: 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs
-  // and feature sizes: against 8 everywhere it is alike in the mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)
-  // Fewer tiles than 24 are for 8 wavefronts as well while workgroups are few: a launch is then as long as one of them takes (60 drawn graphs
-  // of 12,000 rows and more: those of 320 to 1024 workgroups 1.05 to 1.38 times as fast with 8, those of more 0.88 to 1.00).
-  a.n_waves = large_block ? 16 : large_w ? 8 : whole <= 320 && tiles_each >= 16 ? 16 : tiles_each >= (whole <= 1024 ? 8 : 24) ? 8 : 4;
+  a.n_waves = wavefronts_per_workgroup(large_block, large_w, whole, tiles_each);
   const size_t lds = sizeof(double) * (size_t)a.width * ((size_t)p->block_rows + 1) + (ordered ? sizeof(int) * (a.width / 16) : 0);
   const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);
   auto divided = [&](const float* partial) {

@@ -78,6 +78,19 @@ inline int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool 
   return columns_beside(rows) < columns_beside(power) || (rows > 128 && power == 128 && turns > 2) ? power : rows;
 }
 
+// 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs and feature sizes: against 8 everywhere it is alike in the
+// mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)  Fewer tiles than 24 are for 8 wavefronts as well while workgroups are few: a launch is then
+// as long as one of them takes (60 drawn graphs of 12,000 rows and more: those of 320 to 1024 workgroups 1.05 to 1.38 times as fast with 8, those of more 0.88 to
+// 1.00).  12 tiles and more are for 16, since blocks that make one whole turn have down to three quarters of the tiles of a power of two (see
+// rows_of_a_block()): from 16 on, 13,600 rows of 8 relations, 71,720 entries, 64 x 64, took 15.4 us where the power of two took 13.2, now 13.1; 60 graphs with
+// d_out up to 64 and 192 to 255 blocks 1.01 times as fast, 60 of fewer 1.00 (0.98 to 1.13).
+inline int32_t wavefronts_per_workgroup(bool large_block, bool large_w, int64_t workgroups, int64_t tiles_each) {
+  if (large_block) return 16;
+  if (large_w) return 8;
+  if (workgroups <= 320 && tiles_each >= 12) return 16;
+  return tiles_each >= (workgroups <= 1024 ? 8 : 24) ? 8 : 4;
+}
+
 }  // namespace
 }  // namespace sptir
 

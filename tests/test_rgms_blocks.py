@@ -20,10 +20,10 @@ def blocks(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-Wno-unused-function", "-I", sptir_build.CSRC,
                            "-o", exe, os.path.join(HERE, "rgms_blocks_main.cpp")])
 
-    def ask(graphs):  # rows of (n_rows, n_rel, nnz, workspace)
-        text = "\n".join(" ".join(str(v) for v in g) for g in graphs)
-        out = subprocess.run([exe], input=text, check=True, capture_output=True, text=True).stdout
-        return np.array(out.split(), dtype=np.int64).reshape(-1, 4)
+    def ask(rows, *what):  # (n_rows, n_rel, nnz, workspace), or "waves": (large_block, large_w, workgroups, tiles_each)
+        text = "\n".join(" ".join(str(v) for v in row) for row in rows)
+        out = subprocess.run([exe, *what], input=text, check=True, capture_output=True, text=True).stdout
+        return np.array(out.split(), dtype=np.int64).reshape(len(rows), -1)
 
     return ask
 
@@ -47,3 +47,14 @@ def test_no_more_passes_over_x_than_with_a_power_of_two(blocks, log2_rows, works
     assert (np.where(rows > 256, 1, 2) * lds <= LDS).all()
     assert (2 * rows > power).all() and (4 * rows < 5 * power).all()
     assert (rows != power).any() != (workspace and log2_rows == 5)  # (those of 32 rows stay as they are with one)
+
+
+def test_blocks_of_a_whole_turn_have_the_wavefronts_of_those_they_stand_for(blocks):
+    """192 to 255 blocks become 256 with as many fewer tiles each."""
+    pairs = [(b, t) for b in range(192, 256) for t in range(16, 200)]
+    assert (blocks([(0, 0, b, t) for b, t in pairs], "waves") == 16).all()
+    assert (blocks([(0, 0, 256, -(-t * b // 256)) for b, t in pairs], "waves") == 16).all()
+    for large_block, large_w, workgroups, tiles, waves in ((1, 0, 200, 5, 16), (0, 1, 200, 50, 8), (0, 0, 320, 12, 16), (0, 0, 320, 11, 8),
+                                                           (0, 0, 321, 12, 8), (0, 0, 1024, 8, 8), (0, 0, 1024, 7, 4), (0, 0, 1025, 23, 4),
+                                                           (0, 0, 1025, 24, 8)):
+        assert blocks([(large_block, large_w, workgroups, tiles)], "waves") == waves
