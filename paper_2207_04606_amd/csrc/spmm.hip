@@ -484,13 +484,13 @@ template <int VEC, int LG, bool IDX32, bool WIDE, bool UNIT, bool SHARED = false
 __device__ __forceinline__ void lists_workgroup(const SpmmArgs& a, unsigned bid, float* smem) {
   using S = Shape<VEC, LG>;
   using W = HybWalker<VEC, LG, IDX32, WIDE, UNIT, TileSink<VEC, LG>>;
-  int64_t unit;
+  unsigned unit;
   int tile_id;
-  decode_deal(bid, a.deal, &unit, &tile_id);
+  decode_deal<S::kTile == 32, false>(bid, a.deal, &unit, &tile_id);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t slot = SHARED ? unit : unit * a.wg_waves + wave;
-  if (slot >= a.n_row_blocks) return;
+  const unsigned slot = SHARED ? unit : unit * (unsigned)a.wg_waves + (unsigned)wave;  // (a row block has 8 rows at least: 32 bits hold them all)
+  if (slot >= (unsigned)a.n_row_blocks) return;
   const int64_t rb = a.rb_order[slot];
   const int row_block = 1 << a.log2_row_block;
   const int rb_first = (int)(rb << a.log2_row_block);
@@ -632,14 +632,14 @@ template <int VEC, int LG, bool IDX32, bool WIDE, bool UNIT>
 __device__ __forceinline__ void heavy_workgroup(const HeavyArgs& a, unsigned bid, float* smem) {
   using S = Shape<VEC, LG>;
   using W = HybWalker<VEC, LG, IDX32, WIDE, UNIT, PartialSink<VEC, LG>>;
-  int64_t unit;
+  unsigned unit;
   int tile_id;
-  decode_deal(bid, a.deal, &unit, &tile_id);
+  decode_deal<false, true>(bid, a.deal, &unit, &tile_id);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t number = unit * a.wg_waves + wave;
-  if (number >= a.n_lists) return;
-  const int64_t list = a.list0 + number;
+  const unsigned number = unit * (unsigned)a.wg_waves + (unsigned)wave;
+  if (number >= (unsigned)a.n_lists) return;
+  const int64_t list = a.list0 + (int64_t)number;
   const int g = lane / LG, fl = lane & (LG - 1);
   const int f_in_sweep = tile_id * S::kTile + fl * VEC;
   const bool f_active = a.feat0 + f_in_sweep < a.feat;
