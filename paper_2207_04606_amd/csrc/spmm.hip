@@ -44,6 +44,7 @@
 #include <mutex>
 #include <utility>
 #include <vector>
+#include "list_waves.h"
 #include "sptir_internal.h"
 #include "sptir_tiles.h"
 
@@ -151,14 +152,9 @@ struct SpmmArgs {
   const float* row_val;  // UNIT kernels: the value of every entry of row r
 };
 
-// Wavefronts per workgroup: kHybWaves where the lists of a launch go through slices of X nearly in step, as neighbours then walk the same ones: in
-// rounds (232,965 rows, 114.6 M entries: 1791 us, one 1815), and in a single launch over several partitions of an X beyond L2 whose lists are long
-// (from 1280 entries on: 179,397 rows, 17.2 M entries 0.75 times as fast with one, 119,079 rows, 7.3 M entries 0.86).  Else one, whose place on the CU is
-// free when it ends (132,534 rows, 39.6 M entries in eight launches: 997 -> 980 us; 169,343 rows, 1.17 M entries, both directions 172.0 ->
-// 170.5).  106 drawn graphs of 0.8 M entries and more, not in rounds: 1.01 times as fast as with four everywhere (0.97 to 1.19).
+// most wavefronts per workgroup, each with a list of its own (rule in list_waves.h)
 constexpr int kHybWaves = 4;
 constexpr int kHybBlock = 64 * kHybWaves;
-constexpr int64_t kInStepEntries = 1280;  // of a list, where several partitions are in one launch
 
 // One wavefront's walk over its share of a row block's chunk list.
 //
@@ -990,17 +986,16 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   if (!h->spmm_plan) return SPTIR_ERR_UNSUPPORTED;
 
   Geometry g;
-  const bool in_step = h->rounds || (h->n_phases == 1 && h->parts_per_phase > 1 && (int64_t)h->n_cols * 128 >= kMovedBytes &&
-                                     h->nnz - h->n_heavy_nnz - h->slices.nnz >= kInStepEntries * (int64_t)h->n_row_blocks);
-  const int wg_waves = in_step ? kHybWaves : 1;
-  const int64_t n_units = ((int64_t)h->n_row_blocks + wg_waves - 1) / wg_waves;
   // (512-byte tiles only where a workgroup's Y tiles fit the CU's LDS: a caller who fixes large row blocks and
   //  asks for full rows gets narrower tiles)
   static_assert(kHybWaves == 4, "full_rows_fit() and half_rows_fit() count four wavefronts per workgroup");
   const ListShape lists{h->rounds != 0, h->full_rows != 0, h->log2_row_block, h->n_row_blocks, h->n_cols};
   // columns of a launch of the chunk lists
   const int64_t span = (int64_t)h->parts_per_phase * (int64_t)h->w, list_cols = std::min<int64_t>(span, h->n_cols);
-  if (!plan(n_units, feat, X, Y, lists, &g)) return SPTIR_ERR_OVERFLOW;
+  if (!plan(h->n_row_blocks, feat, X, Y, lists, &g)) return SPTIR_ERR_OVERFLOW;
+  const int wg_waves = list_waves({h->rounds != 0, h->n_phases, h->parts_per_phase, h->n_cols, h->n_row_blocks,
+                                   h->nnz - h->n_heavy_nnz - h->slices.nnz, h->heavy_chunk0, h->longest_list, feat, g.vec * g.lg, g.n_tiles});
+  const int64_t n_units = ((int64_t)h->n_row_blocks + wg_waves - 1) / wg_waves;
   SpmmArgs a;
   a.stream = h->stream;
   a.X = X; a.Y = Y; a.n_rows = h->n_rows; a.n_row_blocks = h->n_row_blocks; a.log2_row_block = h->log2_row_block;
