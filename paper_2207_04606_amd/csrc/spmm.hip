@@ -993,8 +993,9 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
   // columns of a launch of the chunk lists
   const int64_t span = (int64_t)h->parts_per_phase * (int64_t)h->w, list_cols = std::min<int64_t>(span, h->n_cols);
   if (!plan(h->n_row_blocks, feat, X, Y, lists, &g)) return SPTIR_ERR_OVERFLOW;
+  const int64_t list_entries = h->nnz - h->n_heavy_nnz - h->slices.nnz;
   const int wg_waves = list_waves({h->rounds != 0, h->n_phases, h->parts_per_phase, h->n_cols, h->n_row_blocks,
-                                   h->nnz - h->n_heavy_nnz - h->slices.nnz, h->heavy_chunk0, h->longest_list, feat, g.vec * g.lg, g.n_tiles});
+                                   list_entries, h->heavy_chunk0, h->longest_list, feat, g.vec * g.lg, g.n_tiles});
   const int64_t n_units = ((int64_t)h->n_row_blocks + wg_waves - 1) / wg_waves;
   SpmmArgs a;
   a.stream = h->stream;
@@ -1155,7 +1156,8 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
       Geometry gs = g;
       if (waves > 1 && !plan_tiles(h->n_row_blocks, &gs)) return SPTIR_ERR_OVERFLOW;
       a.tile0 = tile0; a.deal = deal_of(n_units, g);
-      move_slow_units((uintptr_t)(X + tile0 * g.vec * g.lg), feat, list_cols, &g, &a.deal);
+      move_slow_units((uintptr_t)(X + tile0 * g.vec * g.lg), feat, list_cols, &g, &a.deal, list_entries, h->n_heavy_nnz,
+                      (int64_t)h->n_phases * h->n_row_blocks);
       for (int phase = 0; phase < h->n_phases; ++phase) {
         a.rb_chunk_ptr = h->rb_chunk_ptr + (size_t)phase * h->n_row_blocks;
         a.rb_order = h->rb_order + (size_t)phase * h->n_row_blocks;
