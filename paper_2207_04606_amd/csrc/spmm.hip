@@ -1126,7 +1126,6 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
         a.n_row_blocks = (int32_t)here;
         if (!plan_tiles((here + kHybWaves - 1) / kHybWaves, &g)) return SPTIR_ERR_OVERFLOW;
         a.deal = deal_of((here + kHybWaves - 1) / kHybWaves, g);
-        move_slow_units((uintptr_t)(X + tile0 * tile_floats), feat, list_cols, &g, &a.deal);
         const bool last = first + here == h->n_row_blocks;
         if (!last || !lists_and_heavy(feat_begin, feat_end, false))
           with_variant(g.vec, g.lg, idx32, wide, unit, [&](auto v) { launch_lists(v, g, wg_waves, lds_bytes, stream, a); });

@@ -115,6 +115,7 @@ inline TileDeal deal_of(int64_t n_units, const Geometry& g) {
 // x: the address of the launch's first feature; n_cols: the rows of X that its entries range over; list_entries, heavy_entries: of the call's n_lists lists, and of
 // its heavy ones
 constexpr int64_t kMovedBytes = (int64_t)8 << 20, kMovedUnits = 512, kMovedEntries = 200;
+// (Launches of rounds are too small for it: what a GPU holds at once are at most 256 workgroups of four lists for each of four tiles.)
 inline void move_slow_units(uintptr_t x, int feat, int64_t n_cols, Geometry* g, TileDeal* d, int64_t list_entries = 1, int64_t heavy_entries = 1,
                             int64_t n_lists = 0) {
   if (d->mode != kMapXcdsPerTile || d->n_tiles != 4 || g->vec * g->lg != 32 || feat % 128 != 0 || x % 128 != 0 ||
@@ -130,10 +131,9 @@ inline void move_slow_units(uintptr_t x, int feat, int64_t n_cols, Geometry* g, 
 }
 
 // Heavy lists: an XCD of a tile's takes consecutive ones.  They are in partition order, so that it gathers from fewer columns of X
-// than where the XCDs of a tile take turns.  169,343 rows, 1.17 M entries, 128 features (two XCDs a tile, two partitions of four
-// each) 105.5 -> 101.3 us, 64 features 1.02 times as fast, 230,000 rows, 10 M entries in rounds 509 -> 489; 50,000 x 60,000 columns, 0.9 M
-// entries, two partitions 63 -> 60.  Not with a single tile, whose chunk lists and heavy lists then are in different
-// partitions at a time (50,021 rows, 1.5 M entries, 41 features: 38.4 us, 42.1 with it).
+// than where the XCDs of a tile take turns.  25 power-law graphs with heavy lists and two or four tiles: 1.07 times as fast (1.00 to 1.17; in rounds 1.00, 1.03
+// and 1.09).  144,465 rows, 1.04 M entries, 100 features 129 -> 110 us; 230,000 rows, 10 M entries, 128 features in a single launch 521 -> 513.  Not with a
+// single tile, whose chunk lists and heavy lists then are in different partitions at a time (50,021 rows, 1.5 M entries, 41 features: 38.4 us, 42.1 with it).
 inline void deal_ranges(TileDeal* d) {
   if (d->mode == kMapXcdsPerTile && d->n_tiles > 1) d->mode = kMapRanges;
 }
