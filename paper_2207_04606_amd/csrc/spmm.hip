@@ -819,7 +819,8 @@ void launch_shared_lists(V, const Geometry& g, int waves, size_t lds_bytes, hipS
 // more.  Taken where that is two fifths less than alone, or a quarter where lists are uneven or so few that they leave CUs idle.
 // 300 drawn graphs of up to 1.5 M entries, 190 of them without heavy pieces: 1.19 times as fast in the mean (0.95 to 3.7; the
 // best w for each 1.23; as many wavefronts as fit, whatever the lists, 1.15 with losses to 0.87).  2,708 rows, 10,556 entries,
-// 64 features 8.0 -> 5.9 us; 2,745 rows, 521,654 entries, 64 features 33.9 -> 11.5 us.
+// 64 features 8.0 -> 5.9 us; 2,745 rows, 521,654 entries, 64 features 33.9 -> 11.5 us.  Those were against workgroups of four lists; against one list each 68
+// graphs that are shared 1.29 times as fast (0.87 to 2.4).
 struct SharedLists {
   int waves = 1;
   int64_t saved = 0;  // what the launch is shorter by, in quads
@@ -849,7 +850,8 @@ SharedLists shared_list_waves(int64_t n_lists, int64_t n_quads, int64_t longest_
 // than the heavy lists and a launch of their own take (`heavy_quads` and about two quads).  110 drawn graphs with heavy lists in a
 // single launch: 29 with lists to share, 8 of them apart by the rule, which take 0.61 to 0.94 times as long apart as in one launch; the others
 // 1.05 to 1.44 times.  The 81 with nothing to share are in one launch, apart 1.02 to 1.49 times as long.  101,047 rows, 2.0 M entries, 32 features, 4477 heavy
-// lists beside 1579 whose longest is far beyond the mean: 64 us in one launch, 51 apart.
+// lists beside 1579 whose longest is far beyond the mean: 64 us in one launch, 51 apart.  (Against workgroups of one list: 18 graphs in one launch, apart 0.99 to
+// 1.37 times as long, 1.06 in the mean.)
 bool share_rather_than_join(const SharedLists& shared, int64_t heavy_quads) { return shared.saved >= heavy_quads + 2; }
 
 template <typename V>
@@ -1156,7 +1158,7 @@ static sptir_status_t spmm_on_hyb(const sptir_hyb_t* h, const float* X, float* Y
       if (waves > 1 && !plan_tiles(h->n_row_blocks, &gs)) return SPTIR_ERR_OVERFLOW;
       a.tile0 = tile0; a.deal = deal_of(n_units, g);
       move_slow_units((uintptr_t)(X + tile0 * g.vec * g.lg), feat, list_cols, &g, &a.deal, list_entries, h->n_heavy_nnz,
-                      (int64_t)h->n_phases * h->n_row_blocks);
+                      (int64_t)h->n_phases * h->n_row_blocks, h->parts_per_phase == 1);
       for (int phase = 0; phase < h->n_phases; ++phase) {
         a.rb_chunk_ptr = h->rb_chunk_ptr + (size_t)phase * h->n_row_blocks;
         a.rb_order = h->rb_order + (size_t)phase * h->n_row_blocks;

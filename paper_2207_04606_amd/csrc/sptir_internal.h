@@ -176,8 +176,9 @@ struct ListShape {
   int64_t n_row_blocks, n_cols;
 };
 void lane_shape(int32_t feat, bool aligned16, const ListShape& lists, int* vec, int* lg);
-// 512-byte feature tiles need row blocks whose Y tiles (4 wavefronts x rows x 512 bytes, plus the chunk rings) fit a
-// CU's LDS: up to 64 rows.  With larger row blocks sptir_spmm uses the 128-byte tiles whatever the handle asks for.
+// 512-byte feature tiles need row blocks whose Y tiles (rows x 512 bytes and the chunk rings, for the most wavefronts a workgroup can have: 4)
+// fit a CU's LDS: up to 64 rows.  With larger row blocks sptir_spmm uses the 128-byte tiles whatever the handle asks for.  (A workgroup of one wavefront
+// could have them beside more rows; what that would give was not measured.)
 inline bool full_rows_fit(int log2_row_block) {
   return (size_t)4 * (((size_t)512 << log2_row_block) + 6 * 1024) <= (size_t)159 * 1024;
 }

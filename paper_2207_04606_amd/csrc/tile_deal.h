@@ -105,23 +105,25 @@ inline TileDeal deal_of(int64_t n_units, const Geometry& g) {
 // Where the four tiles of a launch of chunk lists are the four lines of every 512 bytes of X, those of the last line are served
 // more slowly from beyond L2, whichever XCD asks for them (a gather of 169,343 rows that no cache holds: 69, 79, 68 and 83 us for the
 // XCDs of the four lines; one line at a time 49, 49, 49 and 53), and the two XCDs bound to that tile end when the others have been
-// idle for a sixth of the launch.  So the others take units of its lists after their own: a sixteenth, and where heavy lists, which stay where they are, have
-// entries too, a sixteenth of all entries' worth, up to a quarter of the units.  169,343 rows, 1.17 M entries, 128 features, half of them heavy, operands that
-// change from call to call: 178 -> 173 us for a product and the transposed one (an eighth 172).  130 graphs of 128 features with lists of 200 entries and
-// more: 1.012 times as fast as with none moved (0.987 to 1.055; an eighth of the units always 1.008, 0.953 to 1.07: even lists lose).  Shorter lists: 0.993 on 50
-// graphs (0.92 to 1.03).  The fewest units, 512, when a unit had four lists; with one list each 35 graphs of 400 to 1900 of them 0.995, by their short lists.
+// idle for a sixth of the launch.  So the others take units of its lists after their own: an eighth, and where heavy lists, which stay where they are, have
+// more entries than these, a sixteenth of all entries' worth, up to a quarter of the units.  169,343 rows, 1.17 M entries, 128 features, operands that
+// change from call to call: 178 -> 170 us for a product and the transposed one (a sixteenth 173, a tenth 171).  Of 128 features: 35 power-law graphs, both products,
+// 1.024 times as fast as with none moved (a twelfth 1.019, a sixteenth 1.016); even lists whose columns are alike, 76 of them, 1.002 (0.95 to 1.07; a
+// sixteenth 1.010), and which it is the handle does not know.  Over a single partition even lists lose 2 to 5 % by an eighth, nothing by a sixteenth.  Lists of
+// fewer than 200 entries: 0.993 on 50 graphs (0.92 to 1.03), so none of those.  The fewest units, 512, when a unit had four lists; with one list each 35 graphs of
+// 400 to 1900 of them 0.995, by their short lists.
 // Not where an L2 holds most of a tile's column of X (132,534 rows in eight launches: 994 us, 1019 with it).  Only the last line gives units away: that the second
 // one is late too (79 us) was seen, but nothing dealt by it yet.
 // x: the address of the launch's first feature; n_cols: the rows of X that its entries range over; list_entries, heavy_entries: of the call's n_lists lists, and of
-// its heavy ones
+// its heavy ones; one_partition: so a launch ranges over
 constexpr int64_t kMovedBytes = (int64_t)8 << 20, kMovedUnits = 512, kMovedEntries = 200;
 // (Launches of rounds are too small for it: what a GPU holds at once are at most 256 workgroups of four lists for each of four tiles.)
 inline void move_slow_units(uintptr_t x, int feat, int64_t n_cols, Geometry* g, TileDeal* d, int64_t list_entries = 1, int64_t heavy_entries = 1,
-                            int64_t n_lists = 0) {
+                            int64_t n_lists = 0, bool one_partition = false) {
   if (d->mode != kMapXcdsPerTile || d->n_tiles != 4 || g->vec * g->lg != 32 || feat % 128 != 0 || x % 128 != 0 ||
       n_cols * 128 < kMovedBytes || d->n_units < kMovedUnits || list_entries < 1 || list_entries < kMovedEntries * n_lists)
     return;
-  const double share = std::min(0.25, (1. + (double)heavy_entries / (double)list_entries) / 16);
+  const double share = std::max(one_partition ? 1. / 16 : 1. / 8, std::min(0.25, (1. + (double)heavy_entries / (double)list_entries) / 16));
   const int64_t moved = (int64_t)((double)d->n_units * share), helpers = 8 - d->param;
   const int64_t grid = g->grid + 8 * ((moved + helpers - 1) / helpers);
   if (grid > 0x7FFFFFFF) return;

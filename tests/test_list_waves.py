@@ -8,8 +8,9 @@ from paper_2207_04606_amd import build as sptir_build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 FIELDS = ("rounds", "n_launches", "parts", "n_cols", "n_lists", "entries", "chunks", "longest", "feat", "tile_floats", "n_tiles")
-# 1000 lists of 300 entries, 5 chunks each, over two partitions of an X whose feature tiles of 32 floats have 8 MB
-EVEN = dict(rounds=0, n_launches=1, parts=2, n_cols=65536, n_lists=1000, entries=300000, chunks=5000, longest=10, feat=64, tile_floats=32, n_tiles=2)
+# 1000 lists of 600 entries, 10 chunks each, over two partitions of an X whose feature tiles of 32 floats have 8 MB
+EVEN = dict(rounds=0, n_launches=1, parts=2, n_cols=65536, n_lists=1000, entries=600000, chunks=10000, longest=20, feat=64, tile_floats=32, n_tiles=2)
+HALF_ROWS = dict(EVEN, n_cols=32768, entries=300000, chunks=5000, longest=10, feat=100, tile_floats=64)
 UNEVEN = dict(EVEN, entries=1280000, chunks=20000, longest=41)
 
 
@@ -27,16 +28,16 @@ def waves(tmp_path_factory):
     return ask
 
 
-@pytest.mark.parametrize("lists", [EVEN, UNEVEN])
+@pytest.mark.parametrize("lists", [EVEN, HALF_ROWS, UNEVEN])
 def test_one_without_any_of_what_four_need(waves, lists):
     assert waves(lists) == 4
-    for change in (dict(n_launches=2), dict(parts=1), dict(n_tiles=1), dict(n_cols=65535), dict(entries=lists["entries"] - 1)):
+    for change in (dict(n_launches=2), dict(parts=1), dict(n_tiles=1), dict(n_cols=lists["n_cols"] - 1), dict(entries=lists["entries"] - 1)):
         assert waves(lists, **change) == 1, change
         assert waves(lists, rounds=1, **change) == 4, change
 
 
 def test_lists_that_are_not_even_are_longer(waves):
-    assert waves(EVEN, longest=11) == 1 and waves(EVEN, longest=11, entries=1279999) == 1 and waves(EVEN, longest=11, entries=1280000) == 4
+    assert waves(EVEN, longest=21) == 1 and waves(EVEN, longest=21, entries=1279999) == 1 and waves(EVEN, longest=21, entries=1280000) == 4
 
 
 @pytest.mark.parametrize("feat,tile_floats,n_tiles,n_cols", [(128, 64, 2, 32768), (20, 16, 2, 131072), (65, 64, 2, 32768), (256, 128, 2, 16384)])

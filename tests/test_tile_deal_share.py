@@ -1,5 +1,5 @@
-"""How many units of the slow line's tile go to the XCDs of the others (csrc/tile_deal.h, compiled alone): a sixteenth of all entries' worth,
-heavy ones among them, up to a quarter; none of short lists; and every unit is dealt once."""
+"""How many units of the slow line's tile go to the XCDs of the others (csrc/tile_deal.h, compiled alone): an eighth (a single partition: a
+sixteenth), more where heavy lists have more entries than the others, up to a quarter; none of short lists; and every unit is dealt once."""
 import os
 import subprocess
 
@@ -21,11 +21,12 @@ def moved(tmp_path_factory):
 @pytest.mark.parametrize("n_units", [512, 515, 2646, 4099])
 def test_share(moved, n_units):
     entries = 200 * n_units
-    for heavy, sixteenths in ((0, 1), (entries, 2), (2 * entries, 3), (3 * entries, 4), (9 * entries, 4), (entries // 2, 1.5)):
-        assert moved(n_units, entries, heavy, n_units) == int(n_units * sixteenths / 16)
+    for heavy, one, several in ((0, 1, 2), (entries // 2, 1.5, 2), (entries, 2, 2), (2 * entries, 3, 3), (3 * entries, 4, 4), (9 * entries, 4, 4)):
+        assert moved(n_units, entries, heavy, n_units, 1) == int(n_units * one / 16)
+        assert moved(n_units, entries, heavy, n_units, 0) == int(n_units * several / 16)
 
 
 def test_none_of_short_lists(moved):
-    assert moved(2646, 200 * 2646 - 1, 0, 2646) == 0 and moved(2646, 0, 1000, 0) == 0 and moved(511, 200 * 511, 0, 511) == 0
-    assert moved(660, 200 * 2640, 0, 2640) == 41 and moved(660, 200 * 2640 - 1, 0, 2640) == 0  # (four lists a unit)
-    assert moved(2646, (1 << 31) - 1, (1 << 31) - 1, 2646) == 330
+    assert moved(2646, 200 * 2646 - 1, 0, 2646, 0) == 0 and moved(2646, 0, 1000, 0, 0) == 0 and moved(511, 200 * 511, 0, 511, 0) == 0
+    assert moved(660, 200 * 2640, 0, 2640, 0) == 82 and moved(660, 200 * 2640 - 1, 0, 2640, 0) == 0  # (four lists a unit)
+    assert moved(2646, (1 << 31) - 1, (1 << 31) - 1, 2646, 1) == 330
