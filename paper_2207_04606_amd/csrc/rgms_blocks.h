@@ -54,16 +54,19 @@ inline int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool work
 // (32 x 32; d_in of 64 and 128 with d_out up to 64; d_out of 128), 430 graphs of 1 to 70 relations:
 //   192 to 255 blocks    256              1.02, 1.02, 1.03 times as fast (0.81 to 1.23; what loses has as many tiles in the smaller blocks); 256 of 384 to 510
 //                                         rows instead of as many of 512, 60 graphs: 1.05, 1.04, 1.05 (0.96 to 1.14)
-//   257 to 312           512              1.12, 1.13, 1.19 (1.03 to 1.28); of 128 rows 256, as fast as 512 (1.17, 1.14 to 1.22, 1.04)
+//   257 to 312           256              1.14 (0.93 to 1.55; 240 graphs, 1.20 with fewer than 13 entries for every (relation, block); 512 1.07, 0.74 to 1.39)
 //   313 to 512           512              1.04, 1.07, 1.06 (0.83 to 1.34)
-//   513 to 624           512              1.03, 1.10, 1.07 (0.90 to 1.20)
-//   625 to 1300          the nearest of 768 and 1024, for blocks of fewer than 200 entries, which end as soon as they have begun: 1.00, 1.02, 1.01 (0.95 to 1.26)
-// Blocks of more entries beyond 624 keep the power of two: 768 instead of 769 to 948 of them are 1.04 times as fast with 32 features of X, of which a turn has
-// three workgroups of eight wavefronts for every CU, but 0.97 (0.90 to 1.03) with more, where it has two; 1024 are 0.96 to 1.01 with either.  Below 192 blocks
+//   513 to 576           512              1.04, 1.04, 1.03 (0.94 to 1.22)
+//   577 to 768           768              1.04, 1.02, 0.99 (0.92 to 1.14)
+//   769 to 1300          the nearest of 768 and 1024, up to 948 and from 1025 on, for blocks of fewer than 300 entries, which end as soon as they have begun:
+//                                         1.02, 1.02, 1.02 (0.92 to 1.27)
+// Blocks of more entries beyond 768 keep the power of two: 768 instead of 769 to 948 of them are 1.04 times as fast with 32 features of X, of which a turn has
+// three workgroups of eight wavefronts for every CU, but 0.97 (0.90 to 1.03) with more, where it has two; 1024 are 0.96 to 1.01 with either, also for few entries
+// where they stand for fewer.  Below 192 blocks
 // tiles lose a quarter of what they hold and more; blocks of 32 rows are as fast or slower by 256 (1.02, 0.82 to 1.16), and 512 instead of 316 to 477 of 256 rows
 // 0.94 to 1.20; 1.9 M rows, 3682 blocks of 512 rows 341 us, 3840 of 491 351.  With a workspace one turn only: tiles take their turns longer in larger blocks.
 // 27,163 rows, 46 relations, 64 x 64, 213 blocks of 128 rows 28.8 us, 256 of 107 28.1.
-constexpr int64_t kMostForTwoTurns = 624, kFewEntries = 200;
+constexpr int64_t kMostForOneTurn = 312, kMostForTwoTurns = 576, kMostForAll = 768, kFewEntries = 300;
 inline int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
   const int s = log2_block_rows(n_rows, n_rel, nnz, workspace);
   const int32_t power = 1 << s;
@@ -71,8 +74,9 @@ inline int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool 
   const bool several = !workspace && s < kMaxLog2Block - 1;
   int64_t turns = 0;
   if (blocks >= 192 && blocks <= 256) turns = s > kMinLog2Block ? 1 : 0;
-  else if (several && blocks > 256 && blocks <= kMostForTwoTurns) turns = blocks <= 312 && power == 128 ? 1 : 2;
-  else if (several && blocks > kMostForTwoTurns && blocks <= 1300 && nnz < kFewEntries * blocks) turns = blocks <= 960 ? 3 : 4;
+  else if (several && blocks > 256 && blocks <= kMostForTwoTurns) turns = blocks <= kMostForOneTurn ? 1 : 2;
+  else if (several && blocks > kMostForTwoTurns && (blocks <= kMostForAll || nnz < kFewEntries * blocks))
+    turns = blocks <= 948 ? 3 : blocks > 1024 && blocks <= 1300 ? 4 : 0;
   if (turns == 0) return power;
   const int32_t rows = (int32_t)((n_rows + 256 * turns - 1) / (256 * turns));
   return columns_beside(rows) < columns_beside(power) || (rows > 128 && power == 128 && turns > 2) ? power : rows;
@@ -82,12 +86,13 @@ inline int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool 
 // mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)  Fewer tiles than 24 are for 8 wavefronts as well while workgroups are few: a launch is then
 // as long as one of them takes (60 drawn graphs of 12,000 rows and more: those of 320 to 1024 workgroups 1.05 to 1.38 times as fast with 8, those of more 0.88 to
 // 1.00).  12 tiles and more are for 16, since blocks that make one whole turn have down to three quarters of the tiles of a power of two (see
-// rows_of_a_block()): from 16 on, 13,600 rows of 8 relations, 71,720 entries, 64 x 64, took 15.4 us where the power of two took 13.2, now 13.1; 60 graphs with
-// d_out up to 64 and 192 to 255 blocks 1.01 times as fast, 60 of fewer 1.00 (0.98 to 1.13).
-inline int32_t wavefronts_per_workgroup(bool large_block, bool large_w, int64_t workgroups, int64_t tiles_each) {
+// rows_of_a_block()): from 16 on, 13,500 rows of 8 relations, 71,720 entries, 64 x 64, took 15.4 us where the power of two took 13.2, now 13.1; 60 graphs with
+// d_out up to 64 and 192 to 255 blocks 1.01 times as fast, 60 of fewer 1.00 (0.98 to 1.13).  Where tiles add in their order they wait longer for 16: from 16 on
+// (18,484 rows, 9 relations, 59,392 entries, 64 x 64: 18.1 us, 19.7 from 12 on).
+inline int32_t wavefronts_per_workgroup(bool large_block, bool large_w, int64_t workgroups, int64_t tiles_each, bool ordered) {
   if (large_block) return 16;
   if (large_w) return 8;
-  if (workgroups <= 320 && tiles_each >= 12) return 16;
+  if (workgroups <= 320 && tiles_each >= (ordered ? 16 : 12)) return 16;
   return tiles_each >= (workgroups <= 1024 ? 8 : 24) ? 8 : 4;
 }
 

@@ -1,5 +1,5 @@
 // Rows of Y per block and columns per pass of RGMS (csrc/rgms_blocks.h, compiled alone), for test_rgms_blocks.py.
-//   waves: reads lines "large_block large_w workgroups tiles_each" and prints the wavefronts of a workgroup
+//   waves: reads lines "kind ordered workgroups tiles_each" and prints the wavefronts of a workgroup (kind 1: a large block, 2: large matrices W[r])
 //   otherwise reads lines "n_rows n_rel nnz workspace" and prints "rows columns power columns_of_power" of each: the block's rows, the columns beside
 //   them, the power of two that the rule on entries names, and the columns beside that
 #include <stdio.h>
@@ -11,7 +11,7 @@ int main(int argc, char**) {
   int workspace;
   if (argc > 1) {
     while (scanf("%lld %lld %lld %d", &n_rows, &n_rel, &nnz, &workspace) == 4)
-      printf("%d\n", sptir::wavefronts_per_workgroup(n_rows != 0, n_rel != 0, nnz, workspace));
+      printf("%d\n", sptir::wavefronts_per_workgroup(n_rows == 1, n_rows == 2, nnz, workspace, n_rel != 0));
     return 0;
   }
   while (scanf("%lld %lld %lld %d", &n_rows, &n_rel, &nnz, &workspace) == 4) {

@@ -20,7 +20,7 @@ def blocks(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-Wno-unused-function", "-I", sptir_build.CSRC,
                            "-o", exe, os.path.join(HERE, "rgms_blocks_main.cpp")])
 
-    def ask(rows, *what):  # (n_rows, n_rel, nnz, workspace), or "waves": (large_block, large_w, workgroups, tiles_each)
+    def ask(rows, *what):  # (n_rows, n_rel, nnz, workspace), or "waves": (kind, ordered, workgroups, tiles_each)
         text = "\n".join(" ".join(str(v) for v in row) for row in rows)
         out = subprocess.run([exe, *what], input=text, check=True, capture_output=True, text=True).stdout
         return np.array(out.split(), dtype=np.int64).reshape(len(rows), -1)
@@ -54,7 +54,7 @@ def test_blocks_of_a_whole_turn_have_the_wavefronts_of_those_they_stand_for(bloc
     pairs = [(b, t) for b in range(192, 256) for t in range(16, 200)]
     assert (blocks([(0, 0, b, t) for b, t in pairs], "waves") == 16).all()
     assert (blocks([(0, 0, 256, -(-t * b // 256)) for b, t in pairs], "waves") == 16).all()
-    for large_block, large_w, workgroups, tiles, waves in ((1, 0, 200, 5, 16), (0, 1, 200, 50, 8), (0, 0, 320, 12, 16), (0, 0, 320, 11, 8),
-                                                           (0, 0, 321, 12, 8), (0, 0, 1024, 8, 8), (0, 0, 1024, 7, 4), (0, 0, 1025, 23, 4),
-                                                           (0, 0, 1025, 24, 8)):
-        assert blocks([(large_block, large_w, workgroups, tiles)], "waves") == waves
+    for kind, ordered, workgroups, tiles, waves in ((1, 0, 200, 5, 16), (2, 0, 200, 50, 8), (0, 0, 320, 12, 16), (0, 0, 320, 11, 8),
+                                                    (0, 1, 320, 16, 16), (0, 1, 320, 15, 8), (0, 0, 321, 12, 8), (0, 0, 1024, 8, 8),
+                                                    (0, 0, 1024, 7, 4), (0, 0, 1025, 23, 4), (0, 0, 1025, 24, 8)):
+        assert blocks([(kind, ordered, workgroups, tiles)], "waves") == waves
