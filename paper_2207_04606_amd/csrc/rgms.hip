@@ -1015,7 +1015,7 @@ extern "C" sptir_status_t sptir_rgms(const sptir_rgms_t* p, const float* X, cons
       if (shared < least) { least = shared; a.sharers = n; }
     }
   }
-  a.n_waves = wavefronts_per_workgroup(large_block, large_w, whole, tiles_each, ordered);
+  a.n_waves = wavefronts_per_workgroup(large_block, large_w, whole * a.sharers, tiles_each / a.sharers, ordered);
   const size_t lds = sizeof(double) * (size_t)a.width * ((size_t)p->block_rows + 1) + (ordered ? sizeof(int) * (a.width / 16) : 0);
   const dim3 grid((unsigned)(p->n_items * a.sharers), (unsigned)chunks), block(64 * a.n_waves);
   auto divided = [&](const float* partial) {

@@ -82,17 +82,19 @@ inline int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool 
   return columns_beside(rows) < columns_beside(power) || (rows > 128 && power == 128 && turns > 2) ? power : rows;
 }
 
-// 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs and feature sizes: against 8 everywhere it is alike in the
+// Where matrices W[r] are large 8, else 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs and feature sizes: against 8 everywhere it is alike in the
 // mean, 0.83 to 1.2; 4 everywhere 8 % slower, 16 everywhere 7 %.)  Fewer tiles than 24 are for 8 wavefronts as well while workgroups are few: a launch is then
 // as long as one of them takes (60 drawn graphs of 12,000 rows and more: those of 320 to 1024 workgroups 1.05 to 1.38 times as fast with 8, those of more 0.88 to
 // 1.00).  12 tiles and more are for 16, since blocks that make one whole turn have down to three quarters of the tiles of a power of two (see
 // rows_of_a_block()): from 16 on, 13,500 rows of 8 relations, 71,720 entries, 64 x 64, took 15.4 us where the power of two took 13.2, now 13.1; 60 graphs with
 // d_out up to 64 and 192 to 255 blocks 1.01 times as fast, 60 of fewer 1.00 (0.98 to 1.13).  Where tiles add in their order they wait longer for 16: from 16 on
-// (18,484 rows, 9 relations, 59,392 entries, 64 x 64: 18.1 us, 19.7 from 12 on).
+// (18,484 rows, 9 relations, 59,392 entries, 64 x 64: 18.1 us, 19.7 from 12 on).  The same for large W[r], which had 8 always and one workgroup of them a CU where one
+// pass takes all columns: 120 graphs and feature sizes of 165 to 320 blocks 1.06 times as fast (0.96 to 1.40), 16,443 rows, 9 relations, 84,842 entries, 128 x 128
+// 45.3 -> 39.4 us.  (workgroups, tiles_each: with the sharers of an item.)
 inline int32_t wavefronts_per_workgroup(bool large_block, bool large_w, int64_t workgroups, int64_t tiles_each, bool ordered) {
   if (large_block) return 16;
-  if (large_w) return 8;
   if (workgroups <= 320 && tiles_each >= (ordered ? 16 : 12)) return 16;
+  if (large_w) return 8;
   return tiles_each >= (workgroups <= 1024 ? 8 : 24) ? 8 : 4;
 }
 

@@ -54,7 +54,7 @@ def test_blocks_of_a_whole_turn_have_the_wavefronts_of_those_they_stand_for(bloc
     pairs = [(b, t) for b in range(192, 256) for t in range(16, 200)]
     assert (blocks([(0, 0, b, t) for b, t in pairs], "waves") == 16).all()
     assert (blocks([(0, 0, 256, -(-t * b // 256)) for b, t in pairs], "waves") == 16).all()
-    for kind, ordered, workgroups, tiles, waves in ((1, 0, 200, 5, 16), (2, 0, 200, 50, 8), (0, 0, 320, 12, 16), (0, 0, 320, 11, 8),
+    for kind, ordered, workgroups, tiles, waves in ((1, 0, 200, 5, 16), (2, 0, 200, 12, 16), (2, 0, 200, 11, 8), (2, 0, 321, 50, 8), (0, 0, 320, 12, 16), (0, 0, 320, 11, 8),
                                                     (0, 1, 320, 16, 16), (0, 1, 320, 15, 8), (0, 0, 321, 12, 8), (0, 0, 1024, 8, 8),
                                                     (0, 0, 1024, 7, 4), (0, 0, 1025, 23, 4), (0, 0, 1025, 24, 8)):
         assert blocks([(kind, ordered, workgroups, tiles)], "waves") == waves
