@@ -15,13 +15,14 @@ constexpr int kHalfLds = 80 * 1024;     // what each of two workgroups can have
 
 inline bool is_large_block(int32_t rows) { return rows > 1 << (kMaxLog2Block - 1); }
 
-// Columns of Y beside so many rows (a multiple of 32): what a pass over X takes.  Rows that are a few more than a power of two have the columns of that
-// power, as long as the LDS of a CU holds two workgroups of them.
+// Columns of Y beside so many rows (a multiple of 32): what a pass over X takes.  Rows that are up to a quarter more than a power of two have the columns of that
+// power.  (At a quarter, all of these leave a CU one workgroup: more than kHalfLds.)
+inline int64_t y_tile_bytes(int32_t rows, int32_t columns) { return (int64_t)sizeof(double) * columns * (rows + 1); }
 inline int32_t columns_beside(int32_t rows) {
-  const int32_t cols = (is_large_block(rows) ? 2 : 1) * kYTileBytes / 8 / rows / 32 * 32;
-  int32_t of_power = kYTileBytes / 8;
-  for (int32_t r = rows; r > 1; r >>= 1) of_power >>= 1;
-  return of_power > cols && 8 * of_power * (rows + 1) <= kHalfLds ? of_power : cols;
+  int32_t power = 1;
+  while (2 * power <= rows) power *= 2;
+  const int32_t cols = (is_large_block(rows) ? 2 : 1) * kYTileBytes / 8 / rows / 32 * 32, of_power = kYTileBytes / 8 / power;
+  return of_power > cols && 4 * rows <= 5 * power ? of_power : cols;
 }
 
 // Rows per block: 32 entries for every (relation, block), so that tiles fill, as long as that leaves 160 blocks, about what keeps
@@ -54,8 +55,8 @@ inline int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool work
 // (32 x 32; d_in of 64 and 128 with d_out up to 64; d_out of 128), 430 graphs of 1 to 70 relations:
 //   192 to 255 blocks    256              1.02, 1.02, 1.03 times as fast (0.81 to 1.23; what loses has as many tiles in the smaller blocks); 256 of 384 to 510
 //                                         rows instead of as many of 512, 60 graphs: 1.05, 1.04, 1.05 (0.96 to 1.14)
-//   257 to 312           256              1.14 (0.93 to 1.55; 240 graphs, 1.20 with fewer than 13 entries for every (relation, block); 512 1.07, 0.74 to 1.39)
-//   313 to 512           512              1.04, 1.07, 1.06 (0.83 to 1.34)
+//   257 to 320           256              1.14 (0.93 to 1.55; 250 graphs, 1.20 with fewer than 13 entries for every (relation, block); 512 1.07, 0.74 to 1.39)
+//   321 to 512           512              1.04, 1.07, 1.06 (0.83 to 1.34)
 //   513 to 576           512              1.04, 1.04, 1.03 (0.94 to 1.22)
 //   577 to 768           768              1.04, 1.02, 0.99 (0.92 to 1.14)
 //   769 to 1300          the nearest of 768 and 1024, up to 948 and from 1025 on, for blocks of fewer than 300 entries, which end as soon as they have begun:
@@ -66,20 +67,25 @@ inline int log2_block_rows(int64_t n_rows, int64_t n_rel, int64_t nnz, bool work
 // tiles lose a quarter of what they hold and more; blocks of 32 rows are as fast or slower by 256 (1.02, 0.82 to 1.16), and 512 instead of 316 to 477 of 256 rows
 // 0.94 to 1.20; 1.9 M rows, 3682 blocks of 512 rows 341 us, 3840 of 491 351.  With a workspace one turn only: tiles take their turns longer in larger blocks.
 // 27,163 rows, 46 relations, 64 x 64, 213 blocks of 128 rows 28.8 us, 256 of 107 28.1.
-constexpr int64_t kMostForOneTurn = 312, kMostForTwoTurns = 576, kMostForAll = 768, kFewEntries = 300;
+constexpr int64_t kMostForOneTurn = 320, kMostForTwoTurns = 576, kMostForAll = 768, kFewEntries = 300;
 inline int32_t rows_of_a_block(int64_t n_rows, int64_t n_rel, int64_t nnz, bool workspace) {
   const int s = log2_block_rows(n_rows, n_rel, nnz, workspace);
   const int32_t power = 1 << s;
   const int64_t blocks = (n_rows + power - 1) >> s;
   const bool several = !workspace && s < kMaxLog2Block - 1;
-  int64_t turns = 0;
-  if (blocks >= 192 && blocks <= 256) turns = s > kMinLog2Block ? 1 : 0;
-  else if (several && blocks > 256 && blocks <= kMostForTwoTurns) turns = blocks <= kMostForOneTurn ? 1 : 2;
-  else if (several && blocks > kMostForTwoTurns && (blocks <= kMostForAll || nnz < kFewEntries * blocks))
-    turns = blocks <= 948 ? 3 : blocks > 1024 && blocks <= 1300 ? 4 : 0;
-  if (turns == 0) return power;
-  const int32_t rows = (int32_t)((n_rows + 256 * turns - 1) / (256 * turns));
-  return columns_beside(rows) < columns_beside(power) || (rows > 128 && power == 128 && turns > 2) ? power : rows;
+  auto rows_of = [&](int64_t turns) {
+    const int32_t rows = (int32_t)((n_rows + 256 * turns - 1) / (256 * turns));
+    const int32_t cols = columns_beside(rows);
+    const bool two_a_cu = turns == 1 || y_tile_bytes(rows, cols) <= kHalfLds;
+    return cols < columns_beside(power) || !two_a_cu || (rows > 128 && power == 128 && turns > 2) ? power : rows;
+  };
+  if (blocks < 192 || blocks > 1300) return power;
+  if (blocks <= 256) return s > kMinLog2Block ? rows_of(1) : power;
+  if (!several) return power;
+  if (blocks <= kMostForOneTurn) return rows_of(1);
+  if (blocks <= kMostForTwoTurns) return rows_of(2);
+  if (blocks > kMostForAll && nnz >= kFewEntries * blocks) return power;
+  return blocks <= 948 ? rows_of(3) : blocks > 1024 ? rows_of(4) : power;
 }
 
 // Where matrices W[r] are large 8, else 4, unless a workgroup has tiles for more; 16 where one workgroup per CU has to do.  (230 graphs and feature sizes: against 8 everywhere it is alike in the

@@ -11,8 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d_out", [64, 128, 256])
-@pytest.mark.parametrize("n,mean,rows", [(128 * 312, 0.3, 156), (128 * 313, 0.3, 79), (128 * 530, 0.3, 133), (128 * 576, 0.3, 144), (128 * 577, 0.3, 97),
-                                         (64 * 300, 0.6, 75), (64 * 570 + 3, 0.6, 72), (32 * 280, 1.2, 35), (32 * 320, 1.2, 20), (32 * 570, 1.2, 36), (32 * 936, 1.2, 39),
+@pytest.mark.parametrize("n,mean,rows", [(128 * 320, 0.3, 160), (128 * 321, 0.3, 81), (64 * 318, 0.6, 80), (32 * 319, 1.2, 40), (128 * 530, 0.3, 133), (128 * 576, 0.3, 144), (128 * 577, 0.3, 97),
+                                         (64 * 300, 0.6, 75), (64 * 570 + 3, 0.6, 72), (32 * 280, 1.2, 35), (32 * 321, 1.2, 21), (32 * 570, 1.2, 36), (32 * 936, 1.2, 39),
                                          (64 * 1230, 0.6, 77), (32 * 1249, 1.2, 32), (512 * 192, 0.03, 384), (512 * 200 + 3, 0.03, 401),
                                          (512 * 255 - 1, 0.03, 510)])
 def test_rgms_columns_beside_blocks_of_any_rows(gpu_lib, n, mean, rows, d_out):

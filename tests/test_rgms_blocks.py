@@ -42,10 +42,10 @@ def test_no_more_passes_over_x_than_with_a_power_of_two(blocks, log2_rows, works
     assert (cols % 32 == 0).all() and (cols >= 32).all() and (rows >= 1).all() and (rows <= 512).all()
     passes = -(-D_OUT // cols[:, None])
     assert (passes <= -(-D_OUT // cols_of_power[:, None])).all()
-    # two workgroups' rows of Y (and the one for places without an entry) in a CU; large blocks: one's
-    lds = 8 * cols * (rows + 1)
-    assert (np.where(rows > 256, 1, 2) * lds <= LDS).all()
-    assert (2 * rows > power).all() and (4 * rows < 5 * power).all()
+    # two workgroups' rows of Y (and the one for places without an entry) in a CU; one's of large blocks, and where there is a block for each
+    lds, blocks_of = 8 * cols * (rows + 1), -(-np.array(graphs(log2_rows, workspace))[:, 0] // rows)
+    assert (np.where((rows > 256) | (blocks_of <= 256), 1, 2) * lds <= LDS).all()
+    assert (2 * rows > power).all() and (4 * rows <= 5 * power).all()
     assert (rows != power).any() != (workspace and log2_rows == 5)  # (those of 32 rows stay as they are with one)
 
 
